@@ -27,10 +27,10 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
                              const int32_t max_count[4], const ItemK* items_k, const uint8_t* bits_ch,
                              uint32_t* k_range, int row_wide, hipStream_t st);
 int partition_block();
-int weights_block();
-size_t weights_scratch_floats(int64_t n_blocks, int64_t n_items, int64_t total_tokens, int R_pad, bool want_ch);
+int weights_key_tile();
+size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_tokens, int R, bool want_ch);
 hipError_t launch_weights(const rdkv_config& cfg, const int64_t* d_item_row_off, const int32_t* d_item_T,
-                          const int32_t* d_item_blk_off, int64_t n_blocks, int64_t n_items, int64_t total_tokens,
+                          const int32_t* d_item_tile_off, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
                           int max_T, const uint16_t* K, const uint16_t* Q_obs, float* w_tok, float* w_ch,
                           float* scratch, hipStream_t st);
 hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
@@ -479,7 +479,7 @@ struct Tables {
   double* avg = nullptr;         // average bits per cache element of the item's sequence
   int64_t* ch_off = nullptr;     // item * 128
   int32_t* T = nullptr;
-  int32_t* wblk_off = nullptr;   // first workgroup of the item in the weights kernels
+  int32_t* wblk_off = nullptr;   // [items + 1]: first key tile of the item in the weights kernels
   int32_t* blk_off = nullptr;    // first partition block of the item
   int32_t* ch_U = nullptr;       // 128
   int64_t n_wblk = 0;
@@ -489,23 +489,23 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
                         Tables* out) {
   const size_t n = static_cast<size_t>(std::max<int64_t>(it.n_items, 1));
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
-  std::vector<uint8_t> blob(48 * n, 0);
+  std::vector<uint8_t> blob(48 * n + 16, 0);
   int64_t* tok_off = reinterpret_cast<int64_t*>(blob.data());
   double* budget = reinterpret_cast<double*>(blob.data() + 8 * n);
   double* avg = reinterpret_cast<double*>(blob.data() + 16 * n);
   int64_t* ch_off = reinterpret_cast<int64_t*>(blob.data() + 24 * n);
   int32_t* T = reinterpret_cast<int32_t*>(blob.data() + 32 * n);
-  int32_t* wblk = T + n;
-  int32_t* blk = T + 2 * n;
-  int32_t* ch_U = T + 3 * n;
-  const int wb = weights_block();
+  int32_t* blk = T + n;
+  int32_t* ch_U = T + 2 * n;
+  int32_t* wblk = T + 3 * n;      // n + 1 entries
+  const int key_tile = weights_key_tile();
   int64_t n_wblk = 0;
   for (int64_t i = 0; i < it.n_items; ++i) {
     tok_off[i] = it.tok_off[i];
     T[i] = it.T[i];
     blk[i] = it.blk_off[i];
     wblk[i] = static_cast<int32_t>(n_wblk);
-    n_wblk += (it.T[i] + wb - 1) / wb;
+    n_wblk += (it.T[i] + key_tile - 1) / key_tile;
     ch_off[i] = i * kHeadDim;
     ch_U[i] = kHeadDim;
     if (with_budget) {
@@ -516,6 +516,7 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
       budget[i] = mixed ? static_cast<double>(static_cast<float>(2.0 * (1.0 - static_cast<double>(cfg->kv_split_rk)) * a)) : a;
     }
   }
+  wblk[it.n_items] = static_cast<int32_t>(n_wblk);
   uint8_t* d = tmp.get<uint8_t>(blob.size());
   if (!d) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   RDKV_HIP(upload(d, blob.data(), blob.size(), st));
@@ -524,9 +525,9 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
   out->avg = reinterpret_cast<double*>(d + 16 * n);
   out->ch_off = reinterpret_cast<int64_t*>(d + 24 * n);
   out->T = reinterpret_cast<int32_t*>(d + 32 * n);
-  out->wblk_off = out->T + n;
-  out->blk_off = out->T + 2 * n;
-  out->ch_U = out->T + 3 * n;
+  out->blk_off = out->T + n;
+  out->ch_U = out->T + 2 * n;
+  out->wblk_off = out->T + 3 * n;
   out->n_wblk = n_wblk;
   return RDKV_OK;
 }
@@ -534,8 +535,8 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
 // Stage 1 of Alg. 1; everything is enqueued on st, nothing waits.
 rdkv_status weights_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const void* K, const void* Q_obs,
                          float* w_tok, float* w_ch, Temp& tmp, hipStream_t st) {
-  const int R_pad = (cfg->hq / cfg->hkv * cfg->s_obs + 15) / 16 * 16;
-  const size_t nscr = weights_scratch_floats(tb.n_wblk, it.n_items, it.total_tokens, R_pad, w_ch != nullptr);
+  const int R = cfg->hq / cfg->hkv * cfg->s_obs;
+  const size_t nscr = weights_scratch_floats(tb.n_wblk, it.n_items, it.total_tokens, R, w_ch != nullptr);
   float* scratch = tmp.get<float>(nscr);
   if (!scratch) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   TimedScope ts(RDKV_TIME_WEIGHTS, st);
@@ -1185,11 +1186,11 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   const size_t ni = static_cast<size_t>(std::max<int64_t>(it.n_items, 1));
   const size_t nc = ni * kHeadDim;
   {
-    const int R_pad = (cfg->hq / cfg->hkv * cfg->s_obs + 15) / 16 * 16;
+    const int R = cfg->hq / cfg->hkv * cfg->s_obs, key_tile = weights_key_tile();
     int64_t n_wblk = 0;
-    for (int64_t i = 0; i < it.n_items; ++i) n_wblk += (it.T[i] + weights_block() - 1) / weights_block();
-    tmp.reserve({48 * ni, nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
-                 weights_scratch_floats(n_wblk, it.n_items, it.total_tokens, R_pad, mixed) * sizeof(float),
+    for (int64_t i = 0; i < it.n_items; ++i) n_wblk += (it.T[i] + key_tile - 1) / key_tile;
+    tmp.reserve({48 * ni + 16, nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
+                 weights_scratch_floats(n_wblk, it.n_items, it.total_tokens, R, mixed) * sizeof(float),
                  mixed ? ni * sizeof(int32_t) : 0, mixed ? ni * sizeof(double) : 0,
                  static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t),
                  (ni * 4 + 1) * sizeof(int32_t), ni * 20 * sizeof(int64_t), ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),

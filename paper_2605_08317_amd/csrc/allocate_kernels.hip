@@ -1,5 +1,5 @@
 // Stages 2-3 of Alg. 1 on the GPU: the multiple-choice knapsack of Eq. 6 solved by
-// Lagrangian bisection (Alg. 2), one workgroup per item.
+// Lagrangian bisection (Alg. 2), one search per item.
 //
 // For a multiplier lam the per-unit minimiser of w eps(b) + lam b is the highest
 // vertex k of the lower convex hull of (b, eps(b)) with (double) w > lam * r_k,
@@ -7,6 +7,21 @@
 // are fp64, the summed bits are integers, and the search returns the feasible
 // iterate with the smallest multiplier (first one inside the tolerance band
 // below the budget), so the result never exceeds the budget.
+//
+// Three things make a step cheap without changing a single verdict:
+//   - (double) w > t is w > below(t), the largest fp32 number not above t, so units are compared in fp32, one
+//     instruction per threshold, and counted by the scalar unit (population count of the comparison mask);
+//   - a histogram over the leading bits of the fp32 pattern bounds the bit sum of any multiplier from both sides; while
+//     the two bounds agree, no unit is read.  One wavefront evaluates the 63 multipliers the next six steps can visit at
+//     once (a lane walks the midpoints to its node of the tree, so the multipliers are bit for bit those of Alg. 2);
+//   - at the first step the bounds cannot decide, the units of the buckets that a threshold can still reach inside the
+//     bracket [lo, hi] move to LDS and the remaining steps are evaluated exactly on those; what the other units add to
+//     the bit sum follows from the histogram.
+// Items of up to 32K units are searched by one workgroup that holds the units in registers and also writes the bit map
+// and the counts the packing stage starts from (allocate_item_kernel: one launch instead of four to eight).  Longer
+// items spread the three passes over the units over many workgroups (hist_kernel, gather_kernel, write_kernel); the
+// workgroup that finishes an item's pass last runs the steps that follow it.
+// Channel maps (128 units) take one wavefront (channel_allocate_kernel).
 #include <algorithm>
 
 #include "rdkv_internal.h"
@@ -16,7 +31,11 @@ namespace rdkv {
 namespace {
 
 constexpr int kThreads = 1024;
+constexpr int kWaves = kThreads / 64;
 constexpr int kMaxHull = 5;
+constexpr int kThr = kMaxHull - 1;
+constexpr int kBlockUnits = 1024;   // units per block of the per-block tier counts (the packing stage's partition block)
+static_assert(kBlockUnits == kThreads, "a quarter of a round of allocate_item_kernel is one block");
 
 struct AllocArgs {
   const float* w;
@@ -31,86 +50,536 @@ struct AllocArgs {
   double need_frac;            // 1 - rel_tol
   double* lam_out;             // [items] or null: the multiplier of the returned allocation (NaN: no search ran)
   int32_t* iters_out;          // [items] or null: bisection steps taken
+  const int32_t* item_blk_off; // [items]: first 1024-unit block of the item, or null (no counts wanted)
+  int4* blk_counts;            // [blocks] out: units of the block in tiers 16, 8, 4, 2
 };
 
-__device__ __forceinline__ long long block_sum(long long v, long long* sm) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sm[wave] = v;
-  __syncthreads();
-  long long t = 0;
-  for (int i = 0; i < kThreads / 64; ++i) t += sm[i];
-  return t;
+// largest fp32 number not above t (t >= 0): for fp32 w, (double) w > t exactly when w > below(t)
+__device__ __forceinline__ float below(double t) {
+  const float f = static_cast<float>(t);
+  return static_cast<double>(f) > t ? __uint_as_float(__float_as_uint(f) - 1u) : f;
 }
 
-// Sum of a small int over the workgroup with one barrier: DPP row rotations inside a row of 16 lanes, four lane
-// reads for the rows, one LDS slot per wavefront.  `sm` holds two sets of slots used alternately (parity), so that a
-// call never overwrites slots another wavefront may still be reading from the previous call.
-template <int CTRL>
-__device__ __forceinline__ int dpp_add(int v) {
-  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
-}
-__device__ __forceinline__ int block_sum_small(int v, int* sm, int parity) {
-  v = dpp_add<0x128>(v);   // row_ror:8
-  v = dpp_add<0x124>(v);   // row_ror:4
-  v = dpp_add<0x122>(v);   // row_ror:2
-  v = dpp_add<0x121>(v);   // row_ror:1
-  const int ws = __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
-                 __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
-  int* slots = sm + parity * (kThreads / 64);
-  if ((threadIdx.x & 63) == 0) slots[threadIdx.x >> 6] = ws;
-  __syncthreads();
-  int t = 0;
+__device__ __forceinline__ int tier_slot(int b) { return b == 16 ? 0 : b == 8 ? 1 : b == 4 ? 2 : b == 2 ? 3 : -1; }
+
+// ---- the search of one item ------------------------------------------------------------------------------------------
+struct Problem {
+  int32_t tiers[kMaxHull];
+  int32_t step_bits[kThr];     // bits gained at threshold k (0 past the hull)
+  double r[kThr];
+  int nh, max_iters;
+  long long base, B_int, need; // base: the bit sum with every unit in the lowest tier
+  __device__ __forceinline__ Problem(const AllocArgs& a, int U, double budget) {
+    nh = a.n_hull;
+    max_iters = a.max_iters;
 #pragma unroll
-  for (int i = 0; i < kThreads / 64; ++i) t += slots[i];
-  return t;
+    for (int k = 0; k < kMaxHull; ++k) tiers[k] = a.tiers[k];
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) {
+      r[k] = a.r[k];
+      step_bits[k] = k < nh - 1 ? a.tiers[k + 1] - a.tiers[k] : 0;
+    }
+    base = static_cast<long long>(tiers[0]) * U;
+    B_int = static_cast<long long>(floor(budget * static_cast<double>(U)));
+    need = static_cast<long long>(ceil(a.need_frac * static_cast<double>(B_int)));
+  }
+  // the tier every unit gets without a search, or -1
+  __device__ __forceinline__ int fill(int U) const {
+    const int top = tiers[nh - 1];
+    if (B_int >= static_cast<long long>(top) * U) return top;
+    if (nh == 1 || B_int < tiers[1]) return tiers[0];
+    return -1;
+  }
+  // a unit is above threshold k of lam when it exceeds this
+  __device__ __forceinline__ float thr(double lam, int k) const { return k < nh - 1 ? below(lam * r[k]) : INFINITY; }
+  // bits of n units above threshold k
+  __device__ __forceinline__ long long gain(int k, int n) const {
+    return static_cast<long long>(static_cast<unsigned long long>(static_cast<unsigned>(step_bits[k])) * static_cast<unsigned>(n));
+  }
+  __device__ __forceinline__ int verdict(long long s) const { return s > B_int ? 0 : (s >= need ? 2 : 1); }
+};
+
+struct Search {
+  double lo, hi, best;
+  int have, it, done;
+  // 0: over budget; 1: feasible, go on; 2: feasible and inside the band, stop
+  __device__ __forceinline__ void take(int verdict, double lam) {
+    ++it;
+    if (verdict == 0) {
+      lo = lam;
+    } else {
+      best = lam;
+      have = 1;
+      hi = lam;
+      done = verdict == 2;
+    }
+  }
+};
+
+// LDS slot of histogram bucket b: one word of padding per 32, so that threads that own 8 or 32 consecutive buckets do not
+// all hit the same banks
+__host__ __device__ constexpr int hist_slot(int b) { return b + (b >> 5); }
+
+// Histogram over the fp32 patterns of the positive units, ascending; suffix[b] = units in buckets >= b,
+// suffix[BUCKETS] = 0.  bucket() is monotone in the unit.
+//   anchored: 256 buckets per factor of two below the largest unit's pattern (everything 2^-32 below it in bucket 0)
+struct Anchored {
+  static constexpr int kBuckets = 8192, kShift = 15, kWords = (hist_slot(kBuckets) + 4) / 4 * 4;
+  uint32_t top;                // pattern of the largest unit
+  __device__ __forceinline__ int bucket(uint32_t u) const {
+    return u > top ? kBuckets : kBuckets - 1 - static_cast<int>(min((top - u) >> kShift, static_cast<uint32_t>(kBuckets - 1)));
+  }
+  // patterns of bucket b
+  __device__ __forceinline__ uint32_t lowest(int b) const {
+    const uint32_t d = ((static_cast<uint32_t>(kBuckets - b) << kShift) - 1u);      // largest top - u of the bucket
+    return b == 0 || d >= top ? 0u : top - d;
+  }
+  __device__ __forceinline__ uint32_t highest(int b) const {
+    const uint32_t d = static_cast<uint32_t>(kBuckets - 1 - b) << kShift;
+    return d >= top ? 0u : top - d;
+  }
+};
+//   full range: 64 buckets per factor of two
+struct FullRange {
+  static constexpr int kBuckets = 32768, kShift = 16, kWords = (hist_slot(kBuckets) + 4) / 4 * 4;
+  __device__ __forceinline__ int bucket(uint32_t u) const { return static_cast<int>(min(u, 0x7F7FFFFFu) >> kShift); }
+  __device__ __forceinline__ uint32_t lowest(int b) const { return static_cast<uint32_t>(b) << kShift; }
+  __device__ __forceinline__ uint32_t highest(int b) const {    // (infinity counts to the last bucket)
+    return b >= bucket(0x7F7FFFFFu) ? 0x7F800000u : ((static_cast<uint32_t>(b) + 1u) << kShift) - 1u;
+  }
+};
+
+// Steps of the search that the histogram decides, by one wavefront; returns with done set, max_iters reached or
+// standing before a step it cannot decide.
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u), lane), hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane);
+  return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+template <class Map>
+__device__ __forceinline__ void steps_on_histogram(const Problem& P, const Map& map, const int* suffix, Search& S) {
+  const int node = max(1, static_cast<int>(threadIdx.x & 63));
+  const int depth = 31 - __clz(node);
+  while (!S.done && S.it < P.max_iters) {
+    double lo = S.lo, hi = S.hi;                 // the bracket the search has at this lane's node
+    for (int d = depth - 1; d >= 0; --d) {       // child 2 i: over budget (lo rises), child 2 i + 1: feasible (hi falls)
+      const double mid = (lo + hi) * 0.5;
+      if ((node >> d) & 1) hi = mid; else lo = mid;
+    }
+    const double lam = (lo + hi) * 0.5;
+    long long s_min = P.base, s_max = P.base;
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) {
+      // units in higher buckets than the threshold's are above it, units in lower ones are not
+      const int b = map.bucket(__float_as_uint(P.thr(lam, k)));
+      s_min += P.gain(k, suffix[hist_slot(min(b + 1, Map::kBuckets))]);
+      s_max += P.gain(k, suffix[hist_slot(b)]);
+    }
+    const bool over = s_min > P.B_int;
+    const bool stop = !over && s_max <= P.B_int && s_min >= P.need;
+    const unsigned long long m_over = __ballot(over), m_stop = __ballot(stop);
+    const unsigned long long m_open = __ballot(!over && !stop && !(s_max < P.need));     // cannot be decided here
+    int cur = 1, feasible = 0, it = S.it;        // feasible: the last node on the way with a feasible verdict
+    bool open = false, done = false;
+    while (cur < 64 && it < P.max_iters && !open && !done) {
+      const unsigned long long bit = 1ull << cur;
+      if (m_open & bit) {
+        open = true;
+      } else {
+        ++it;
+        if (m_over & bit) {
+          cur = 2 * cur;
+        } else {
+          feasible = cur;
+          done = (m_stop & bit) != 0;
+          cur = 2 * cur + 1;
+        }
+      }
+    }
+    S.it = it;
+    S.done = done;
+    if (feasible) {
+      S.best = readlane_f64(lam, feasible);
+      S.have = 1;
+    }
+    if (cur < 64) {                              // the bracket at the node the walk stands before
+      S.lo = readlane_f64(lo, cur);
+      S.hi = readlane_f64(hi, cur);
+    } else {                                     // the bracket after the walk's last node
+      const int last = cur >> 1;
+      const double at = readlane_f64(lam, last);
+      S.lo = (cur & 1) ? readlane_f64(lo, last) : at;
+      S.hi = (cur & 1) ? at : readlane_f64(hi, last);
+    }
+    if (open) return;
+  }
 }
 
-__device__ __forceinline__ float block_max(float v, float* sm) {
+// In place: suffix[b] = sum of suffix[b ..]; suffix[BUCKETS] = 0.  All threads; barriers inside.
+template <int BUCKETS>
+__device__ __forceinline__ void suffix_sums(int* suffix, int* s_wave) {
+  constexpr int kPer = BUCKETS / kThreads;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int v[kPer], local = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    v[i] = suffix[hist_slot(tid * kPer + i)];
+    local += v[i];
+  }
+  int incl = local;                      // sum over this lane and the higher ones
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_down(incl, o);
+    if (lane + o < 64) incl += t;
+  }
+  if (lane == 0) s_wave[wave] = incl;
+  __syncthreads();
+  int run = incl - local;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) run += w > wave ? s_wave[w] : 0;
+#pragma unroll
+  for (int i = kPer - 1; i >= 0; --i) {
+    run += v[i];
+    suffix[hist_slot(tid * kPer + i)] = run;
+  }
+  if (tid == 0) suffix[hist_slot(BUCKETS)] = 0;
+  __syncthreads();
+}
+
+// The buckets that a threshold lam r_k can reach for lam in the bracket [lo, hi]: up to four disjoint ranges (rounded
+// products and the bucket are monotone).  Units of other buckets keep their side of every threshold.
+struct OpenBuckets {
+  int a[kThr], b[kThr];            // range k: buckets a[k] .. b[k], empty when a[k] > b[k]
+  __device__ __forceinline__ OpenBuckets() {}
+  template <class Map>
+  __device__ __forceinline__ OpenBuckets(const Problem& P, const Map& map, double lo, double hi) {
+    int prev = -1;
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) {
+      const bool used = k < P.nh - 1;
+      b[k] = used ? min(map.bucket(__float_as_uint(P.thr(hi, k))), Map::kBuckets - 1) : prev;
+      a[k] = used ? max(map.bucket(__float_as_uint(P.thr(lo, k))), prev + 1) : prev + 1;
+      prev = max(prev, b[k]);
+    }
+  }
+  // units in the open buckets
+  __device__ __forceinline__ int count(const int* suffix) const {
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) n += a[k] <= b[k] ? suffix[hist_slot(a[k])] - suffix[hist_slot(b[k] + 1)] : 0;
+    return n;
+  }
+  // bit sum without the open buckets' units' gains
+  __device__ __forceinline__ long long fixed(const Problem& P, const int* suffix) const {
+    long long s = P.base;
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) {
+      if (k >= P.nh - 1) continue;
+      int n = suffix[hist_slot(b[k] + 1)];
+#pragma unroll
+      for (int j = k + 1; j < kThr; ++j) n -= a[j] <= b[j] ? suffix[hist_slot(a[j])] - suffix[hist_slot(b[j] + 1)] : 0;
+      s += P.gain(k, n);
+    }
+    return s;
+  }
+};
+// the same ranges as fp32 patterns: unit u is in one when u - first <= span for some k
+struct OpenPatterns {
+  uint32_t first[kThr], span[kThr];
+  template <class Map>
+  __device__ __forceinline__ OpenPatterns(const OpenBuckets& o, const Map& map) {
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) {
+      const uint32_t lowest = max(map.lowest(o.a[k]), 1u), highest = map.highest(o.b[k]);   // (zero is above no threshold)
+      const bool any = o.a[k] <= o.b[k] && lowest <= highest;
+      first[k] = any ? lowest : 0xFFFFFFFFu;
+      span[k] = any ? highest - lowest : 0u;
+    }
+  }
+  __device__ __forceinline__ bool contains(float w) const {
+    const uint32_t u = __float_as_uint(w);
+    bool in = false;
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) in |= u - first[k] <= span[k];
+    return in;
+  }
+};
+
+// The remaining steps, exactly, on n undecided units in LDS beside the decided ones' bit sum `fixed`.
+// All threads; S is the same in all of them on entry and exit.  s_red: 2 kWaves ints.
+__device__ __forceinline__ void steps_on_list(const Problem& P, const float* list, int n, long long fixed, Search& S,
+                                              int* s_red) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  while (!S.done && S.it < P.max_iters) {
+    const double lam = (S.lo + S.hi) * 0.5;
+    float t[kThr];
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) t[k] = P.thr(lam, k);
+    int s = 0;                           // at most 32K units of 16 bits: fits
+    for (int i0 = wave * 64; i0 < n; i0 += kThreads) {
+      const int i = i0 + lane;
+      const float w = i < n ? list[i] : 0.f;
+#pragma unroll
+      for (int k = 0; k < kThr; ++k) s += P.step_bits[k] * __popcll(__ballot(w > t[k]));
+    }
+    int* slots = s_red + (S.it & 1) * kWaves;    // alternating, so that one barrier per step is enough
+    if (lane == 0) slots[wave] = s;
+    __syncthreads();
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += slots[w];
+    S.take(P.verdict(fixed + sum), lam);
+  }
+}
+// the same by one wavefront that holds up to 64 PER units in registers
+template <int PER>
+__device__ __forceinline__ void steps_in_wave(const Problem& P, const float (&w)[PER], long long fixed, Search& S) {
+  while (!S.done && S.it < P.max_iters) {
+    const double lam = (S.lo + S.hi) * 0.5;
+    long long s = fixed;
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) {
+      const float t = P.thr(lam, k);
+      int c = 0;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) c += __popcll(__ballot(w[i] > t));
+      s += P.gain(k, c);
+    }
+    S.take(P.verdict(s), lam);
+  }
+}
+
+__device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sm[wave] = v;
-  __syncthreads();
-  float t = sm[0];
-  for (int i = 1; i < kThreads / 64; ++i) t = fmaxf(t, sm[i]);
-  return t;
+  return v;
 }
 
-// Bit sum of one unit at thresholds thr: tiers[#thresholds strictly below w].
-__device__ __forceinline__ int classify_tier(double wu, const double (&thr)[kMaxHull - 1], const int32_t (&tiers)[kMaxHull]) {
-  int idx = 0;
+__device__ __forceinline__ void report(const AllocArgs& a, int item, bool searched, const Search& S) {
+  if (a.lam_out) a.lam_out[item] = searched && S.have ? S.best : __longlong_as_double(0x7FF8000000000000ll);
+  if (a.iters_out) a.iters_out[item] = searched ? S.it : 0;
+}
+
+// A round of 64 units: the tier of this lane's unit, and (in every lane) how many of the wavefront's units are above each
+// threshold.
+__device__ __forceinline__ int tier_of(const Problem& P, float w, const float (&t)[kThr], int (&above)[kThr]) {
+  int b = P.tiers[0];
 #pragma unroll
-  for (int k = 0; k < kMaxHull - 1; ++k) idx += (wu > thr[k]) ? 1 : 0;
-  return tiers[idx];
+  for (int k = 0; k < kThr; ++k) {                                       // thresholds ascend
+    const bool up = w > t[k];
+    b = up ? P.tiers[k + 1] : b;
+    above[k] = __popcll(__ballot(up));
+  }
+  return b;
 }
-
-// A unit is decided on the multiplier bracket [lo, hi] when no threshold lam * r_k, lam in [lo, hi], can change its
-// tier: for every k either w > hi * r_k (above for all lam) or not w > lo * r_k (below for all lam).  Rounded fp64
-// products are monotone in lam, so the test is exact.
-__device__ __forceinline__ bool undecided(double wu, const double (&thr_lo)[kMaxHull - 1],
-                                          const double (&thr_hi)[kMaxHull - 1]) {
-  bool u = false;
+// counts above the thresholds of a block with n units -> counts per stored tier
+__device__ __forceinline__ int4 tier_counts(const Problem& P, int n, const int4& above) {
+  const int c[kMaxHull + 1] = {n, above.x, above.y, above.z, above.w, 0};
+  int out[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int k = 0; k < kMaxHull - 1; ++k) u |= (wu > thr_lo[k]) && !(wu > thr_hi[k]);
-  return u;
+  for (int i = 0; i < kMaxHull; ++i) {
+    const int in = i < P.nh ? c[i] - (i < P.nh - 1 ? c[i + 1] : 0) : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[k] += P.tiers[i] == (16 >> k) ? in : 0;
+  }
+  return make_int4(out[0], out[1], out[2], out[3]);
 }
 
-constexpr int kListCap = 6144;    // undecided units kept in LDS (24 KiB)
-constexpr int kBuckets = 8192;    // histogram over the top 13 bits of the positive fp32 pattern (32 KiB)
-constexpr int kBucketShift = 18;
+// four consecutive units at any 4-byte boundary, and their four bytes of the bit map at any address
+struct __attribute__((packed, aligned(4))) Units4 { float v[4]; };
+struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 
-__device__ __forceinline__ int bucket_of(float w) {
-  const uint32_t u = __float_as_uint(w);
-  return (w > 0.0f) ? static_cast<int>(min(u, 0x7F7FFFFFu) >> kBucketShift) : 0;   // w <= 0 is never above a threshold
+// ---- one workgroup per item: up to 1024 REG units in registers ------------------------------------------------------
+// Thread t holds units 4096 j + 4 t .. + 3, so four wavefronts make one block of the per-block counts.  What bounds it:
+// one compute unit works on an item, through the latency of its loads and about fifteen barriers and then the number of
+// instructions per unit and pass (load, histogram, gather, write).  Measured against fp64
+// comparisons and one step at a time: 4K units 31 -> 15 us, 32K units (94 us in five kernels) -> 28 us, both with the
+// counting kernels (10 us) gone.
+constexpr int kItemListCap = 24576;        // units of open buckets in LDS (96 KB beside 34 KB of histogram)
+constexpr size_t kItemLds = Anchored::kWords * sizeof(int) + kItemListCap * sizeof(float);
+
+template <int REG>
+__global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
+  constexpr int kQ = REG / 4;
+  extern __shared__ __align__(16) unsigned char smem[];
+  int* s_hist = reinterpret_cast<int*>(smem);
+  float* s_list = reinterpret_cast<float*>(s_hist + Anchored::kWords);      // [kItemListCap]
+  int4* s_cnt = reinterpret_cast<int4*>(s_list);                                // [kQ][kWaves], after the search
+  __shared__ int s_wave[kWaves], s_red[2 * kWaves], s_n;
+  __shared__ float s_max[kWaves];
+  __shared__ Search s_search;
+  const int item = blockIdx.x;
+  const int U = a.item_U[item];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* __restrict__ w = a.w + a.item_off[item];
+  uint8_t* __restrict__ bits = a.bits + a.item_off[item];
+  float v[REG];                            // units past the end read as 0: never above a threshold
+#pragma unroll
+  for (int j = 0; j < kQ; ++j) {
+    const int u0 = 4 * (j * kThreads + tid);
+    if (u0 + 3 < U) {
+      const Units4 x = *reinterpret_cast<const Units4*>(w + u0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * j + e] = x.v[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * j + e] = u0 + e < U ? w[u0 + e] : 0.f;
+    }
+  }
+  for (int i = tid; i < Anchored::kWords / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
+  const Problem P(a, U, a.item_budget[item]);
+  const int fill = U > 0 ? P.fill(U) : P.tiers[0];
+  Search S{0.0, 0.0, 0.0, 0, 0, 0};
+  float t[kThr];
+#pragma unroll
+  for (int k = 0; k < kThr; ++k) t[k] = INFINITY;
+
+  if (fill < 0) {
+    float mx = 0.f;
+#pragma unroll
+    for (int j = 0; j < REG; ++j) mx = fmaxf(mx, v[j]);
+    mx = wave_max(mx);
+    if (lane == 0) s_max[wave] = mx;
+    __syncthreads();
+    mx = s_max[0];
+#pragma unroll
+    for (int i = 1; i < kWaves; ++i) mx = fmaxf(mx, s_max[i]);
+    const Anchored map{__float_as_uint(mx)};
+#pragma unroll
+    for (int j = 0; j < REG; ++j)
+      if (v[j] > 0.f) atomicAdd(&s_hist[hist_slot(map.bucket(__float_as_uint(v[j])))], 1);
+    __syncthreads();
+    suffix_sums<Anchored::kBuckets>(s_hist, s_wave);
+    S.hi = static_cast<double>(mx);
+
+    while (true) {
+      if (wave == 0) {
+        steps_on_histogram(P, map, s_hist, S);
+        if (lane == 0) {
+          s_search = S;
+          s_n = 0;
+        }
+      }
+      __syncthreads();
+      S = s_search;
+      if (S.done || S.it >= P.max_iters) break;
+      // the histogram cannot decide the next step
+      const OpenBuckets open(P, map, S.lo, S.hi);
+      const int n = open.count(s_hist);
+      if (n <= kItemListCap) {
+        const OpenPatterns pat(open, map);
+        uint32_t mine = 0;                 // which of this thread's units
+#pragma unroll
+        for (int j = 0; j < REG; ++j) mine |= pat.contains(v[j]) ? 1u << j : 0u;
+        int incl = __popc(mine);
+        const int own = incl;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int x = __shfl_up(incl, o);
+          if (lane >= o) incl += x;
+        }
+        int base = 0;
+        if (lane == 63) base = atomicAdd(&s_n, incl);
+        float* dst = s_list + __builtin_amdgcn_readlane(base, 63) + incl - own;
+#pragma unroll
+        for (int j = 0; j < REG; ++j)
+          if ((mine >> j) & 1) *dst++ = v[j];
+        __syncthreads();
+        const long long fixed = open.fixed(P, s_hist);
+        if (n <= 1024) {
+          if (wave == 0) {
+            float u[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) u[i] = i * 64 + lane < n ? s_list[i * 64 + lane] : 0.f;
+            steps_in_wave<16>(P, u, fixed, S);
+            if (lane == 0) s_search = S;
+          }
+          __syncthreads();
+          S = s_search;
+        } else {
+          steps_on_list(P, s_list, n, fixed, S, s_red);
+        }
+        break;
+      }
+      // too many for LDS: this one step on all units, then the histogram again with half the bracket
+      const double lam = (S.lo + S.hi) * 0.5;
+      int c = 0;
+#pragma unroll
+      for (int k = 0; k < kThr; ++k) {
+        const float tk = P.thr(lam, k);
+        int ck = 0;
+#pragma unroll
+        for (int j = 0; j < REG; ++j) ck += __popcll(__ballot(v[j] > tk));
+        c += P.step_bits[k] * ck;
+      }
+      if (lane == 0) s_red[wave] = c;
+      __syncthreads();
+      long long s = P.base;
+      for (int i = 0; i < kWaves; ++i) s += s_red[i];
+      S.take(P.verdict(s), lam);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) t[k] = S.have ? P.thr(S.best, k) : INFINITY;
+  }
+  if (tid == 0) report(a, item, fill < 0, S);
+
+  // ---- the bit map, and the tier counts of every block -----------------------------------------------------------
+  const int nblk = (U + kBlockUnits - 1) / kBlockUnits;
+  if (fill >= 0) {
+    for (int u = tid; u < U; u += kThreads) bits[u] = static_cast<uint8_t>(fill);
+    if (a.blk_counts && tid < nblk) {
+      const int n = min(kBlockUnits, U - tid * kBlockUnits);
+      a.blk_counts[a.item_blk_off[item] + tid] =
+          make_int4(fill == 16 ? n : 0, fill == 8 ? n : 0, fill == 4 ? n : 0, fill == 2 ? n : 0);
+    }
+    return;
+  }
+  __syncthreads();                         // the list is not read any more
+#pragma unroll
+  for (int j = 0; j < kQ; ++j) {
+    const int u0 = 4 * (j * kThreads + tid);
+    if (4 * j * kThreads < U) {            // (uniform)
+      uint32_t packed = 0;
+      int c[kThr] = {0, 0, 0, 0};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int above[kThr];
+        packed |= static_cast<uint32_t>(tier_of(P, v[4 * j + e], t, above)) << (8 * e);
+#pragma unroll
+        for (int k = 0; k < kThr; ++k) c[k] += above[k];
+      }
+      if (u0 + 3 < U) {
+        reinterpret_cast<Bytes4*>(bits + u0)->v = packed;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (u0 + e < U) bits[u0 + e] = static_cast<uint8_t>(packed >> (8 * e));
+      }
+      if (lane == 0) s_cnt[j * kWaves + wave] = make_int4(c[0], c[1], c[2], c[3]);
+    }
+  }
+  if (a.blk_counts) {
+    __syncthreads();
+    if (tid < nblk) {                      // block tid: wavefronts 4 tid .. 4 tid + 3 of the rounds in one line
+      int4 c = s_cnt[4 * tid];
+#pragma unroll
+      for (int i = 1; i < 4; ++i) {
+        const int4 x = s_cnt[4 * tid + i];
+        c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
+      }
+      a.blk_counts[a.item_blk_off[item] + tid] = tier_counts(P, min(kBlockUnits, U - tid * kBlockUnits), c);
+    }
+  }
 }
+constexpr int kItemUnits = 32 * kThreads;   // longest item of that kernel
 
-// An item's weights read as aligned 16-byte quads (one workgroup streams half a megabyte three times: with 4-byte
-// loads the passes are bound by the number of load instructions in flight).  Quad q covers units 4 q - a .. 4 q - a + 3,
-// a = how many floats the item's first weight sits past a 16-byte boundary; units outside [0, U) read as 0 and are
-// skipped by the caller.  The first and the last quad are read element by element (their neighbours may lie outside
-// the array).
+// ---- longer items: the passes over the units on many workgroups -------------------------------------------------
+// Beyond 32K units the registers of one compute unit no longer hold an item.  Measured, 8 items of 128K units: 98 to 255
+// us in six kernels -> 55 us in four; what is left is the latency of two hand-overs to the last workgroup and of the
+// dependent steps (22 + 20 us).
+// An item's weights read as aligned 16-byte quads.  Quad q covers units 4 q - a .. 4 q - a + 3,
+// a = how many floats the item's first weight sits past a 16-byte boundary; units outside [0, U) read as 0 (never above
+// a threshold).  The first and the last quad are read element by element (their neighbours may lie outside the array).
 struct Quads {
   const float* w;
   int a, U, nq;
@@ -118,7 +587,6 @@ struct Quads {
     a = static_cast<int>((reinterpret_cast<uintptr_t>(w_) >> 2) & 3);
     nq = (U_ + a + 3) >> 2;
   }
-  __device__ __forceinline__ int first_unit(int q) const { return 4 * q - a; }
   __device__ __forceinline__ void load(int q, float (&v)[4]) const {
     const int u0 = 4 * q - a;
     if (q > 0 && q + 1 < nq) {
@@ -129,654 +597,424 @@ struct Quads {
       for (int j = 0; j < 4; ++j) v[j] = (q < nq && u0 + j >= 0 && u0 + j < U) ? w[u0 + j] : 0.0f;
     }
   }
+  // this workgroup's quads
+  __device__ __forceinline__ void slice(int slices, int* q0, int* q1) const {
+    const int per = (nq + slices - 1) / slices;
+    *q0 = min(nq, static_cast<int>(blockIdx.x) * per);
+    *q1 = min(nq, *q0 + per);
+  }
 };
-constexpr int kQlp = 8;           // independent quad loads per thread in a streaming pass
 
-// Units with w > thr: at least those in buckets above thr's bucket, at most those plus thr's own bucket.
-// suffix[b] = number of units in buckets >= b (suffix[kBuckets] = 0).
-__device__ __forceinline__ void count_bounds(double thr, const int* __restrict__ suffix, int* lo_cnt, int* hi_cnt) {
-  // largest finite float <= thr (thr > 0): every float in a higher bucket exceeds thr, none in a lower bucket does
-  float tf = static_cast<float>(fmin(thr, 3.4028234663852886e38));
-  if (static_cast<double>(tf) > thr) tf = __uint_as_float(__float_as_uint(tf) - 1u);
-  const int bt = static_cast<int>(__float_as_uint(tf) >> kBucketShift);
-  *lo_cnt = suffix[bt + 1];
-  *hi_cnt = suffix[bt];
-}
-
-__global__ __launch_bounds__(kThreads) void bisect_kernel(AllocArgs a) {
-  __shared__ long long sm_sum[kThreads / 64];
-  __shared__ float sm_max[kThreads / 64];
-  __shared__ int s_hist[kBuckets + 1];
-  __shared__ float s_list[kListCap];
-  __shared__ int s_count;
-  __shared__ int sm_small[2 * (kThreads / 64)];
-  const int item = blockIdx.x;
-  const int U = a.item_U[item];
-  if (threadIdx.x == 0) {      // overwritten below when the search runs
-    if (a.lam_out) a.lam_out[item] = __longlong_as_double(0x7FF8000000000000ll);
-    if (a.iters_out) a.iters_out[item] = 0;
-  }
-  if (U == 0) return;
-  const float* __restrict__ w = a.w + a.item_off[item];
-  uint8_t* __restrict__ bits = a.bits + a.item_off[item];
-  const int nh = a.n_hull;
-  const long long B_int = static_cast<long long>(floor(a.item_budget[item] * static_cast<double>(U)));
-  const int top = a.tiers[nh - 1];
-  int fill = -1;
-  if (B_int >= static_cast<long long>(top) * U) fill = top;
-  else if (nh == 1 || B_int < a.tiers[1]) fill = a.tiers[0];
-  if (fill >= 0) {
-    for (int u = threadIdx.x; u < U; u += kThreads) bits[u] = static_cast<uint8_t>(fill);
-    return;
-  }
-  const long long need = static_cast<long long>(ceil(a.need_frac * static_cast<double>(B_int)));
-  int32_t tiers[kMaxHull];
-  double r[kMaxHull - 1];
-#pragma unroll
-  for (int k = 0; k < kMaxHull; ++k) tiers[k] = a.tiers[k];
-#pragma unroll
-  for (int k = 0; k < kMaxHull - 1; ++k) r[k] = a.r[k];
-
-  // ---- one pass: maximum and histogram ------------------------------------------------------------------
-  for (int i = threadIdx.x; i <= kBuckets; i += kThreads) s_hist[i] = 0;
-  __syncthreads();
-  float mx = 0.f;
-  const Quads quads(w, U);
-  for (int q0 = threadIdx.x; q0 < quads.nq; q0 += kQlp * kThreads) {
-    float wv[kQlp][4];
-#pragma unroll
-    for (int j = 0; j < kQlp; ++j) quads.load(q0 + j * kThreads, wv[j]);
-#pragma unroll
-    for (int j = 0; j < kQlp; ++j) {
-      const int u0 = quads.first_unit(q0 + j * kThreads);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (u0 + e >= 0 && u0 + e < U) {
-          mx = fmaxf(mx, wv[j][e]);
-          atomicAdd(&s_hist[bucket_of(wv[j][e])], 1);
-        }
-    }
-  }
-  mx = block_max(mx, sm_max);
-  // suffix sums in place: s_hist[b] = units in buckets >= b (each thread owns 8 consecutive buckets)
-  {
-    const int b0 = threadIdx.x * (kBuckets / kThreads);
-    int local = 0;
-#pragma unroll
-    for (int i = 0; i < kBuckets / kThreads; ++i) local += s_hist[b0 + i];
-    __shared__ int s_part[kThreads];
-    s_part[threadIdx.x] = local;
-    __syncthreads();
-    for (int off = 1; off < kThreads; off <<= 1) {   // inclusive suffix scan (Hillis-Steele)
-      const int v = (threadIdx.x + off < kThreads) ? s_part[threadIdx.x + off] : 0;
-      __syncthreads();
-      s_part[threadIdx.x] += v;
-      __syncthreads();
-    }
-    int run = s_part[threadIdx.x] - local;           // units in buckets above this thread's range
-#pragma unroll
-    for (int i = kBuckets / kThreads - 1; i >= 0; --i) {
-      run += s_hist[b0 + i];
-      s_hist[b0 + i] = run;
-    }
-    __syncthreads();
-  }
-
-  double lo = 0.0, hi = static_cast<double>(mx);
-  double best = 0.0;
-  bool have = false;
-  // Every step decides exactly as Alg. 2 does at lam = (lo + hi) / 2.  While the histogram bounds on the bit sum
-  // settle the comparisons, no unit is read.  At the first step they cannot, the units whose tier can still change
-  // inside the bracket are moved to LDS (the others add a constant) and the remaining steps evaluate those exactly;
-  // the same pass gives this step's exact sum, so if the units do not fit the search goes on with the bounds.
-  int mode = 0;   // 0: histogram bounds, 1: list in LDS
-  int n_list = 0;
-  long long s_fixed = 0;
-  int steps = 0;
-  for (int it = 0; it < a.max_iters; ++it) {
-    steps = it + 1;
-    const double lam = (lo + hi) * 0.5;
-    double thr[kMaxHull - 1];
-#pragma unroll
-    for (int k = 0; k < kMaxHull - 1; ++k) thr[k] = (k < nh - 1) ? lam * r[k] : INFINITY;
-    long long s = 0;
-    int verdict = -1;   // 0: over budget, 1: feasible (continue), 2: feasible and inside the band (stop)
-    if (mode == 0) {
-      long long s_min = static_cast<long long>(tiers[0]) * U, s_max = s_min;
-#pragma unroll
-      for (int k = 0; k < kMaxHull - 1; ++k) {
-        if (k < nh - 1) {
-          int c_lo, c_hi;
-          count_bounds(thr[k], s_hist, &c_lo, &c_hi);
-          s_min += static_cast<long long>(tiers[k + 1] - tiers[k]) * c_lo;
-          s_max += static_cast<long long>(tiers[k + 1] - tiers[k]) * c_hi;
-        }
-      }
-      if (s_min > B_int) verdict = 0;
-      else if (s_max <= B_int && s_min >= need) verdict = 2;
-      else if (s_max < need) verdict = 1;
-      if (verdict < 0) {
-        // ambiguous: collect the units still undecided on [lo, hi]
-        double t_lo[kMaxHull - 1], t_hi[kMaxHull - 1];
-#pragma unroll
-        for (int k = 0; k < kMaxHull - 1; ++k) {
-          t_lo[k] = (k < nh - 1) ? lo * r[k] : INFINITY;
-          t_hi[k] = (k < nh - 1) ? hi * r[k] : INFINITY;
-        }
-        if (threadIdx.x == 0) s_count = 0;
-        __syncthreads();
-        long long sf = 0;
-        for (int q0 = threadIdx.x; q0 < quads.nq; q0 += kQlp * kThreads) {
-          float wv[kQlp][4];
-#pragma unroll
-          for (int j = 0; j < kQlp; ++j) quads.load(q0 + j * kThreads, wv[j]);
-#pragma unroll
-          for (int j = 0; j < kQlp; ++j) {
-            const int u0 = quads.first_unit(q0 + j * kThreads);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (u0 + e >= 0 && u0 + e < U) {
-                const double wu = static_cast<double>(wv[j][e]);
-                s += classify_tier(wu, thr, tiers);                 // this step's exact bit sum
-                if (undecided(wu, t_lo, t_hi)) {
-                  const int pos = atomicAdd(&s_count, 1);
-                  if (pos < kListCap) s_list[pos] = wv[j][e];
-                } else {
-                  sf += classify_tier(wu, t_hi, tiers);
-                }
-              }
-          }
-        }
-        s = block_sum(s, sm_sum);
-        s_fixed = block_sum(sf, sm_sum);
-        __syncthreads();
-        n_list = s_count;
-        __syncthreads();                      // everyone has read the count before a later step resets it
-        if (n_list <= kListCap) mode = 1;     // else: too many for LDS; try again at the next unsettled step
-        verdict = s > B_int ? 0 : (s >= need ? 2 : 1);
-      }
-    } else if (mode == 1) {
-      int sl = 0;   // at most kListCap * 16: fits an int
-      for (int i = threadIdx.x; i < n_list; i += kThreads) sl += classify_tier(static_cast<double>(s_list[i]), thr, tiers);
-      s = block_sum_small(sl, sm_small, it & 1) + s_fixed;
-    }
-    if (verdict < 0) verdict = s > B_int ? 0 : (s >= need ? 2 : 1);
-    if (verdict == 0) {
-      lo = lam;
-    } else {
-      best = lam;
-      have = true;
-      hi = lam;
-      if (verdict == 2) break;
-    }
-  }
-  if (threadIdx.x == 0) {
-    if (a.lam_out && have) a.lam_out[item] = best;
-    if (a.iters_out) a.iters_out[item] = steps;
-  }
-  double thr[kMaxHull - 1];
-#pragma unroll
-  for (int k = 0; k < kMaxHull - 1; ++k) thr[k] = (k < nh - 1) ? best * r[k] : INFINITY;
-  for (int q0 = threadIdx.x; q0 < quads.nq; q0 += kQlp * kThreads) {
-    float wv[kQlp][4];
-#pragma unroll
-    for (int j = 0; j < kQlp; ++j) quads.load(q0 + j * kThreads, wv[j]);
-#pragma unroll
-    for (int j = 0; j < kQlp; ++j) {
-      const int u0 = quads.first_unit(q0 + j * kThreads);
-      uint32_t packed = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int t = tiers[0];
-        if (have) t = classify_tier(static_cast<double>(wv[j][e]), thr, tiers);
-        packed |= static_cast<uint32_t>(t) << (8 * e);
-      }
-      if (u0 >= 0 && u0 + 3 < U && (reinterpret_cast<uintptr_t>(bits + u0) & 3) == 0) {
-        *reinterpret_cast<uint32_t*>(bits + u0) = packed;          // four units' bytes at once
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (u0 + e >= 0 && u0 + e < U) bits[u0 + e] = static_cast<uint8_t>(packed >> (8 * e));
-      }
-    }
-  }
-}
-
-// ---- the same search with an item's three streaming passes spread over many workgroups ---------------------------
-// A long item (128K tokens) keeps one workgroup busy for 160 us in bisect_kernel while the rest of the chip idles.
-// Here the passes that touch every unit run on kSlices workgroups per item, and only the steps of the search itself
-// run on one:
-//   hist_kernel      every slice histograms its units (top 13 bits of the fp32 pattern) and adds to the item's
-//                    histogram and maximum;
-//   steps_kernel<0>  the steps of Alg. 2 that the histogram's two-sided bounds on the bit sum decide, up to the first
-//                    step they cannot; leaves the bracket [lo, hi] and the step index;
-//   gather_kernel    every slice appends its units whose tier can still change inside the bracket to the item's list
-//                    and adds the bits of the others (fixed from here on) to a sum;
-//   steps_kernel<1>  the remaining steps, each evaluated exactly on the list plus the fixed sum;
-//   write_kernel     the bit map at the multiplier found.
-// Every verdict is the same integer comparison as in bisect_kernel, so the multipliers visited and the bit maps are
-// the same bit for bit.  A list that would overflow makes steps_kernel<1> read all units of the item instead.
-constexpr int kGlobalListCap = 32768;       // undecided units kept per item (floats)
+constexpr int kListCap = 24576;             // undecided units of an item (96 KB of LDS in the exact steps)
 struct SearchState {
-  double lo, hi, best;
-  long long s_fixed, B_int, need;
-  float mx;
-  int32_t have, it, done, fill, n_list, steps;
+  Search s;
+  long long fixed;                          // what the units outside the open buckets add to the bit sum
+  int32_t open_a[kThr], open_b[kThr];       // the open buckets (OpenBuckets)
+  int32_t mx, n_open, n_list, arrive[2], fill;   // fill: >= 0: the tier of every unit
 };
 struct MultiArgs {
   AllocArgs a;
-  int32_t* hist;        // [items][kBuckets + 1], zero on entry
+  int32_t* hist;        // [items][kBuckets], zero on entry
   SearchState* state;   // [items], zero on entry
-  float* list;          // [items][2][kGlobalListCap]: the list, and the half it moves to when it shrinks
+  float* list;          // [items][kListCap]
   int32_t slices;
 };
 
-__device__ __forceinline__ void slice_range(const Quads& quads, int slices, int* q0, int* q1) {
-  const int per = (quads.nq + slices - 1) / slices;
-  *q0 = min(quads.nq, static_cast<int>(blockIdx.x) * per);
-  *q1 = min(quads.nq, *q0 + per);
+// Called by all threads of a workgroup after their stores and atomics of a pass: true in the workgroup that is the last
+// of `count` to call it.  What the others wrote with agent-scope accesses can then be read with agent-scope loads.
+__device__ __forceinline__ bool last_to_arrive(int32_t* counter, int count, int* s_flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *s_flag = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == count - 1;
+  __syncthreads();
+  return *s_flag != 0;
+}
+template <class T>
+__device__ __forceinline__ T load_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// every slice adds its units to the item's histogram and maximum; the last one takes the steps the histogram decides
+constexpr size_t kHistLds = FullRange::kWords * sizeof(int);
 __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
-  __shared__ int s_hist[kBuckets + 1];
-  __shared__ float sm_max[kThreads / 64];
+  extern __shared__ __align__(16) unsigned char smem[];
+  int* s_hist = reinterpret_cast<int*>(smem);
+  __shared__ int s_wave[kWaves], s_flag;
+  __shared__ float s_max[kWaves];
   const AllocArgs& a = m.a;
   const int item = blockIdx.y;
   const int U = a.item_U[item];
-  if (U == 0) return;
-  const float* __restrict__ w = a.w + a.item_off[item];
-  for (int i = threadIdx.x; i <= kBuckets; i += kThreads) s_hist[i] = 0;
-  __syncthreads();
-  const Quads quads(w, U);
+  const int tid = threadIdx.x;
+  SearchState& st = m.state[item];
+  const Quads quads(a.w + a.item_off[item], U);
   int q0, q1;
-  slice_range(quads, m.slices, &q0, &q1);
+  quads.slice(m.slices, &q0, &q1);
+  float wv[4] = {0.f, 0.f, 0.f, 0.f};
+  if (q0 + tid < q1) quads.load(q0 + tid, wv);
+  const Problem P(a, U, a.item_budget[item]);
+  const int fill = U > 0 ? P.fill(U) : P.tiers[0];
+  if (fill >= 0) {
+    if (blockIdx.x == 0 && tid == 0) {
+      st.fill = fill;
+      st.s = Search{0.0, 0.0, 0.0, 0, 0, 1};
+      report(a, item, false, st.s);
+    }
+    return;
+  }
+  const FullRange map{};
+  for (int i = tid; i < FullRange::kWords / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
+  __syncthreads();
   float mx = 0.f;
-  for (int q = q0 + threadIdx.x; q < q1; q += kThreads) {
-    float wv[4];
-    quads.load(q, wv);
-    const int u0 = quads.first_unit(q);
+  for (int q = q0 + tid; q < q1;) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (u0 + e >= 0 && u0 + e < U) {
-        mx = fmaxf(mx, wv[e]);
-        atomicAdd(&s_hist[bucket_of(wv[e])], 1);
-      }
+    for (int e = 0; e < 4; ++e) {
+      mx = fmaxf(mx, wv[e]);
+      if (wv[e] > 0.f) atomicAdd(&s_hist[hist_slot(map.bucket(__float_as_uint(wv[e])))], 1);
+    }
+    q += kThreads;
+    if (q < q1) quads.load(q, wv);
   }
-  mx = block_max(mx, sm_max);
+  mx = wave_max(mx);
+  if ((tid & 63) == 0) s_max[tid >> 6] = mx;
   __syncthreads();
-  int32_t* gh = m.hist + static_cast<int64_t>(item) * (kBuckets + 1);
-  for (int i = threadIdx.x; i < kBuckets; i += kThreads)
-    if (s_hist[i] != 0) atomicAdd(gh + i, s_hist[i]);
-  // weights are non-negative here (a negative one never exceeds a threshold and mx starts at 0): integer order = float order
-  if (threadIdx.x == 0 && mx > 0.f) atomicMax(reinterpret_cast<int*>(&m.state[item].mx), __float_as_int(mx));
-}
-
-// PHASE 0: steps decided by the histogram; PHASE 1: steps evaluated on the list (or on every unit after an overflow)
-template <int PHASE>
-__global__ __launch_bounds__(kThreads) void steps_kernel(MultiArgs m) {
-  __shared__ long long sm_sum[kThreads / 64];
-  __shared__ int s_hist[kBuckets + 1];
-  __shared__ float s_list[kListCap];
-  __shared__ int sm_small[2 * (kThreads / 64)];
-  const AllocArgs& a = m.a;
-  const int item = blockIdx.x;
-  const int U = a.item_U[item];
-  SearchState& st = m.state[item];
-  const int nh = a.n_hull;
-  int32_t tiers[kMaxHull];
-  double r[kMaxHull - 1];
-#pragma unroll
-  for (int k = 0; k < kMaxHull; ++k) tiers[k] = a.tiers[k];
-#pragma unroll
-  for (int k = 0; k < kMaxHull - 1; ++k) r[k] = a.r[k];
-  double lo, hi, best;
-  bool have;
-  int it0;
-  long long B_int, need;
-  if constexpr (PHASE == 0) {
-    if (threadIdx.x == 0) {
-      if (a.lam_out) a.lam_out[item] = __longlong_as_double(0x7FF8000000000000ll);
-      if (a.iters_out) a.iters_out[item] = 0;
-    }
-    if (U == 0) { if (threadIdx.x == 0) { st.done = 1; st.fill = a.tiers[0]; } return; }
-    B_int = static_cast<long long>(floor(a.item_budget[item] * static_cast<double>(U)));
-    const int top = a.tiers[nh - 1];
-    int fill = -1;
-    if (B_int >= static_cast<long long>(top) * U) fill = top;
-    else if (nh == 1 || B_int < a.tiers[1]) fill = a.tiers[0];
-    if (fill >= 0) { if (threadIdx.x == 0) { st.done = 1; st.fill = fill; } return; }
-    need = static_cast<long long>(ceil(a.need_frac * static_cast<double>(B_int)));
-    const int32_t* gh = m.hist + static_cast<int64_t>(item) * (kBuckets + 1);
-    for (int i = threadIdx.x; i <= kBuckets; i += kThreads) s_hist[i] = i < kBuckets ? gh[i] : 0;
-    __syncthreads();
-    {   // suffix sums in place: s_hist[b] = units in buckets >= b (each thread owns 8 consecutive buckets)
-      const int b0 = threadIdx.x * (kBuckets / kThreads);
-      int local = 0;
-#pragma unroll
-      for (int i = 0; i < kBuckets / kThreads; ++i) local += s_hist[b0 + i];
-      __shared__ int s_part[kThreads];
-      s_part[threadIdx.x] = local;
-      __syncthreads();
-      for (int off = 1; off < kThreads; off <<= 1) {
-        const int v = (threadIdx.x + off < kThreads) ? s_part[threadIdx.x + off] : 0;
-        __syncthreads();
-        s_part[threadIdx.x] += v;
-        __syncthreads();
-      }
-      int run = s_part[threadIdx.x] - local;
-#pragma unroll
-      for (int i = kBuckets / kThreads - 1; i >= 0; --i) {
-        run += s_hist[b0 + i];
-        s_hist[b0 + i] = run;
-      }
-      __syncthreads();
-    }
-    lo = 0.0; hi = static_cast<double>(st.mx); best = 0.0; have = false; it0 = 0;
-  } else {
-    if (st.done) return;
-    lo = st.lo; hi = st.hi; best = st.best; have = st.have != 0; it0 = st.it;
-    B_int = st.B_int; need = st.need;
+  int32_t* gh = m.hist + static_cast<int64_t>(item) * FullRange::kBuckets;
+  for (int i = tid; i < FullRange::kBuckets; i += kThreads)
+    if (s_hist[hist_slot(i)] != 0) atomicAdd(gh + i, s_hist[hist_slot(i)]);
+  if (tid == 0) {
+    for (int i = 1; i < kWaves; ++i) mx = fmaxf(mx, s_max[i]);
+    if (mx > 0.f) atomicMax(&st.mx, __float_as_int(mx));     // positive: integer order is float order
   }
-  const float* __restrict__ w = a.w + a.item_off[item];
-  int n_list = 0;
-  bool overflow = false;
-  long long s_fixed = 0;
-  float* gsrc = m.list + static_cast<int64_t>(item) * (2 * kGlobalListCap);   // the list, and where it moves when it shrinks
-  float* gdst = gsrc + kGlobalListCap;
-  if constexpr (PHASE == 1) {
-    n_list = st.n_list;
-    s_fixed = st.s_fixed;
-    overflow = n_list > kGlobalListCap;
-    if (!overflow && n_list <= kListCap) {
-      for (int i = threadIdx.x; i < n_list; i += kThreads) s_list[i] = gsrc[i];
-      __syncthreads();
-    }
+  if (!last_to_arrive(&st.arrive[0], m.slices, &s_flag)) return;
+  constexpr int kPer = FullRange::kBuckets / kThreads;
+  {
+    int h[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) h[k] = load_agent(gh + tid + k * kThreads);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) s_hist[hist_slot(tid + k * kThreads)] = h[k];
   }
-  int steps = it0;
-  for (int it = it0; it < a.max_iters; ++it) {
-    const double lam = (lo + hi) * 0.5;
-    double thr[kMaxHull - 1];
+  __syncthreads();
+  suffix_sums<FullRange::kBuckets>(s_hist, s_wave);
+  if (tid < 64) {
+    Search S{0.0, static_cast<double>(__int_as_float(load_agent(&st.mx))), 0.0, 0, 0, 0};
+    steps_on_histogram(P, map, s_hist, S);
+    S.done = S.done || S.it >= P.max_iters;
+    const OpenBuckets open(P, map, S.lo, S.hi);
+    if (tid == 0) {
+      st.s = S;
+      st.fill = -1;
+      st.fixed = open.fixed(P, s_hist);
+      st.n_open = open.count(s_hist);
 #pragma unroll
-    for (int k = 0; k < kMaxHull - 1; ++k) thr[k] = (k < nh - 1) ? lam * r[k] : INFINITY;
-    int verdict = -1;   // 0: over budget, 1: feasible (continue), 2: feasible and inside the band (stop)
-    if constexpr (PHASE == 0) {
-      long long s_min = static_cast<long long>(tiers[0]) * U, s_max = s_min;
-#pragma unroll
-      for (int k = 0; k < kMaxHull - 1; ++k)
-        if (k < nh - 1) {
-          int c_lo, c_hi;
-          count_bounds(thr[k], s_hist, &c_lo, &c_hi);
-          s_min += static_cast<long long>(tiers[k + 1] - tiers[k]) * c_lo;
-          s_max += static_cast<long long>(tiers[k + 1] - tiers[k]) * c_hi;
-        }
-      if (s_min > B_int) verdict = 0;
-      else if (s_max <= B_int && s_min >= need) verdict = 2;
-      else if (s_max < need) verdict = 1;
-      if (verdict < 0) {     // the histogram cannot decide this step: hand over to the list
-        if (threadIdx.x == 0) {
-          st.lo = lo; st.hi = hi; st.best = best; st.have = have; st.it = it; st.B_int = B_int; st.need = need;
-          st.done = 0; st.n_list = 0; st.s_fixed = 0;
-        }
-        return;
+      for (int k = 0; k < kThr; ++k) {
+        st.open_a[k] = open.a[k];
+        st.open_b[k] = open.b[k];
       }
-    } else {
-      long long s;
-      if (overflow) {        // every unit of the item
-        long long sl = 0;
-        for (int u = threadIdx.x; u < U; u += kThreads) sl += classify_tier(static_cast<double>(w[u]), thr, tiers);
-        s = block_sum(sl, sm_sum);
-      } else if (n_list <= kListCap) {
-        int sl = 0;
-        for (int i = threadIdx.x; i < n_list; i += kThreads) sl += classify_tier(static_cast<double>(s_list[i]), thr, tiers);
-        s = block_sum_small(sl, sm_small, it & 1) + s_fixed;
-      } else {
-        int sl = 0;
-        for (int i = threadIdx.x; i < n_list; i += kThreads) sl += classify_tier(static_cast<double>(gsrc[i]), thr, tiers);
-        s = block_sum_small(sl, sm_small, it & 1) + s_fixed;
-      }
-      verdict = s > B_int ? 0 : (s >= need ? 2 : 1);
-      if (!overflow && n_list > kListCap && verdict != 2) {
-        // The list does not fit LDS yet.  The bracket has just halved: the units it has decided leave the list (their
-        // bits join the fixed sum) and the rest moves to the other half of the item's list area, or into LDS once
-        // few enough are left.  The order of a list does not matter: every sum over it is an integer sum.
-        const double nlo = verdict == 0 ? lam : lo, nhi = verdict == 0 ? hi : lam;
-        double t_lo[kMaxHull - 1], t_hi[kMaxHull - 1];
-#pragma unroll
-        for (int k = 0; k < kMaxHull - 1; ++k) {
-          t_lo[k] = (k < nh - 1) ? nlo * r[k] : INFINITY;
-          t_hi[k] = (k < nh - 1) ? nhi * r[k] : INFINITY;
-        }
-        __shared__ int s_keep;
-        if (threadIdx.x == 0) s_keep = 0;
-        __syncthreads();
-        long long sf = 0;
-        for (int i = threadIdx.x; i < n_list; i += kThreads) {
-          const float wf = gsrc[i];
-          const double wu = static_cast<double>(wf);
-          if (undecided(wu, t_lo, t_hi)) gdst[atomicAdd(&s_keep, 1)] = wf;
-          else sf += classify_tier(wu, t_hi, tiers);
-        }
-        s_fixed += block_sum(sf, sm_sum);
-        __syncthreads();
-        n_list = s_keep;
-        __syncthreads();
-        float* t = gsrc; gsrc = gdst; gdst = t;
-        if (n_list <= kListCap) {
-          __threadfence_block();
-          for (int i = threadIdx.x; i < n_list; i += kThreads) s_list[i] = gsrc[i];
-          __syncthreads();
-        }
-      }
+      if (S.done) report(a, item, true, S);
     }
-    steps = it + 1;
-    if (verdict == 0) {
-      lo = lam;
-    } else {
-      best = lam;
-      have = true;
-      hi = lam;
-      if (verdict == 2) break;
-    }
-  }
-  if (threadIdx.x == 0) {   // the search is over
-    st.best = best; st.have = have; st.done = 1; st.fill = -1; st.steps = steps;
-    if (a.lam_out && have) a.lam_out[item] = best;
-    if (a.iters_out) a.iters_out[item] = steps;
   }
 }
 
+// every slice appends its units of open buckets to the item's list; the last one takes the other steps
+constexpr size_t kGatherLds = kListCap * sizeof(float);
 __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
-  __shared__ long long sm_sum[kThreads / 64];
+  extern __shared__ __align__(16) unsigned char smem[];
+  float* s_list = reinterpret_cast<float*>(smem);     // [kListCap]
+  __shared__ int s_n, s_base, s_above[kThr], s_flag, s_red[2 * kWaves];
+  __shared__ Search s_search;
   const AllocArgs& a = m.a;
   const int item = blockIdx.y;
   SearchState& st = m.state[item];
-  if (st.done) return;
+  if (st.s.done) return;                    // written by the previous kernel
+  const int n = st.n_open;
+  if (n > kListCap && blockIdx.x != 0) return;
   const int U = a.item_U[item];
-  const float* __restrict__ w = a.w + a.item_off[item];
-  const int nh = a.n_hull;
-  int32_t tiers[kMaxHull];
-#pragma unroll
-  for (int k = 0; k < kMaxHull; ++k) tiers[k] = a.tiers[k];
-  double t_lo[kMaxHull - 1], t_hi[kMaxHull - 1];
-#pragma unroll
-  for (int k = 0; k < kMaxHull - 1; ++k) {
-    t_lo[k] = (k < nh - 1) ? st.lo * a.r[k] : INFINITY;
-    t_hi[k] = (k < nh - 1) ? st.hi * a.r[k] : INFINITY;
-  }
-  float* gl = m.list + static_cast<int64_t>(item) * (2 * kGlobalListCap);
-  const Quads quads(w, U);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const Quads quads(a.w + a.item_off[item], U);
   int q0, q1;
-  slice_range(quads, m.slices, &q0, &q1);
-  // undecided units are collected in LDS first, so that the item's list counter sees one atomic per workgroup and
-  // round of 1024 quads instead of one per unit
-  __shared__ float s_buf[4 * kThreads];
-  __shared__ int s_cnt, s_base;
-  long long sf = 0;
-  for (int base = q0; base < q1; base += kThreads) {
-    if (threadIdx.x == 0) s_cnt = 0;
-    __syncthreads();
-    const int q = base + threadIdx.x;
-    if (q < q1) {
-      float wv[4];
-      quads.load(q, wv);
-      const int u0 = quads.first_unit(q);
+  quads.slice(m.slices, &q0, &q1);
+  Search S = st.s;
+  if (n <= kListCap) {
+    float* gl = m.list + static_cast<int64_t>(item) * kListCap;
+    OpenBuckets open;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (u0 + e >= 0 && u0 + e < U) {
-          const double wu = static_cast<double>(wv[e]);
-          if (undecided(wu, t_lo, t_hi)) s_buf[atomicAdd(&s_cnt, 1)] = wv[e];
-          else sf += classify_tier(wu, t_hi, tiers);
+    for (int k = 0; k < kThr; ++k) {
+      open.a[k] = st.open_a[k];
+      open.b[k] = st.open_b[k];
+    }
+    const OpenPatterns pat(open, FullRange{});
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    for (int qw = q0 + wave * 64; qw < q1; qw += kThreads) {
+      float wv[4] = {0.f, 0.f, 0.f, 0.f};
+      if (qw + lane < q1) quads.load(qw + lane, wv);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = pat.contains(wv[e]);
+        const unsigned long long mask = __ballot(in);
+        if (mask) {
+          int base = 0;
+          if (lane == 0) base = atomicAdd(&s_n, __popcll(mask));
+          base = __builtin_amdgcn_readfirstlane(base) + __popcll(mask & ((1ull << lane) - 1ull));
+          if (in) s_list[base] = wv[e];
         }
+      }
     }
     __syncthreads();
-    const int cnt = s_cnt;
-    if (cnt > 0) {
-      if (threadIdx.x == 0) s_base = atomicAdd(&st.n_list, cnt);
+    const int mine = s_n;
+    if (tid == 0) s_base = mine ? atomicAdd(&st.n_list, mine) : 0;
+    __syncthreads();
+    for (int i = tid; i < mine; i += kThreads)
+      __hip_atomic_store(gl + s_base + i, s_list[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!last_to_arrive(&st.arrive[1], m.slices, &s_flag)) return;
+    const Problem P(a, U, a.item_budget[item]);
+    const long long fixed = st.fixed;
+    if (n <= 1024) {
+      if (wave == 0) {
+        float u[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) u[i] = i * 64 + lane < n ? load_agent(gl + i * 64 + lane) : 0.f;
+        steps_in_wave<16>(P, u, fixed, S);
+        if (lane == 0) s_search = S;
+      }
       __syncthreads();
-      const int b0 = s_base;
-      for (int i = threadIdx.x; i < cnt; i += kThreads)
-        if (b0 + i < kGlobalListCap) gl[b0 + i] = s_buf[i];
+      S = s_search;
+    } else {
+      for (int i = tid; i < n; i += kThreads) s_list[i] = load_agent(gl + i);
+      __syncthreads();
+      steps_on_list(P, s_list, n, fixed, S, s_red);
     }
-    __syncthreads();
+  } else {                                  // more than the list holds: every step on all units, one workgroup
+    const Problem P(a, U, a.item_budget[item]);
+    while (!S.done && S.it < P.max_iters) {
+      const double lam = (S.lo + S.hi) * 0.5;
+      float t[kThr];
+#pragma unroll
+      for (int k = 0; k < kThr; ++k) t[k] = P.thr(lam, k);
+      int c[kThr] = {0, 0, 0, 0};
+      for (int qw = wave * 64; qw < quads.nq; qw += kThreads) {
+        float wv[4];
+        quads.load(qw + lane, wv);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int k = 0; k < kThr; ++k) c[k] += __popcll(__ballot(wv[e] > t[k]));
+      }
+      __syncthreads();
+      if (tid < kThr) s_above[tid] = 0;
+      __syncthreads();
+      if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < kThr; ++k)
+          if (c[k]) atomicAdd(&s_above[k], c[k]);
+      }
+      __syncthreads();
+      long long s = P.base;
+#pragma unroll
+      for (int k = 0; k < kThr; ++k) s += P.gain(k, s_above[k]);
+      S.take(P.verdict(s), lam);
+    }
   }
-  sf = block_sum(sf, sm_sum);
-  if (threadIdx.x == 0 && sf != 0) atomicAdd(reinterpret_cast<unsigned long long*>(&st.s_fixed), static_cast<unsigned long long>(sf));
+  if (tid == 0) {
+    st.s = S;
+    report(a, item, true, S);
+  }
 }
 
-__global__ __launch_bounds__(kThreads) void write_kernel(MultiArgs m) {
+// the bit map and the tier counts, one block of units per workgroup of 256
+__global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
+  __shared__ int4 s_cnt[4];
   const AllocArgs& a = m.a;
   const int item = blockIdx.y;
   const int U = a.item_U[item];
-  if (U == 0) return;
+  const int u0 = blockIdx.x * kBlockUnits, tid = threadIdx.x;
+  if (u0 >= U) return;
   const SearchState& st = m.state[item];
   const float* __restrict__ w = a.w + a.item_off[item];
   uint8_t* __restrict__ bits = a.bits + a.item_off[item];
-  const int nh = a.n_hull;
-  int32_t tiers[kMaxHull];
+  float v[4];
 #pragma unroll
-  for (int k = 0; k < kMaxHull; ++k) tiers[k] = a.tiers[k];
-  const int fill = st.fill >= 0 ? st.fill : (st.have ? -1 : tiers[0]);
-  double thr[kMaxHull - 1];
+  for (int j = 0; j < 4; ++j) v[j] = u0 + 256 * j + tid < U ? w[u0 + 256 * j + tid] : 0.f;
+  const Problem P(a, U, a.item_budget[item]);
+  const int n = min(kBlockUnits, U - u0);
+  const int fill = st.fill >= 0 ? st.fill : (st.s.have ? -1 : P.tiers[0]);
+  if (fill >= 0) {
 #pragma unroll
-  for (int k = 0; k < kMaxHull - 1; ++k) thr[k] = (k < nh - 1) ? st.best * a.r[k] : INFINITY;
-  const Quads quads(w, U);
-  int q0, q1;
-  slice_range(quads, m.slices, &q0, &q1);
-  for (int q = q0 + threadIdx.x; q < q1; q += kThreads) {
-    float wv[4];
-    if (fill < 0) quads.load(q, wv);
-    const int u0 = quads.first_unit(q);
-    uint32_t packed = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int t = fill >= 0 ? fill : classify_tier(static_cast<double>(wv[e]), thr, tiers);
-      packed |= static_cast<uint32_t>(t) << (8 * e);
-    }
-    if (u0 >= 0 && u0 + 3 < U && (reinterpret_cast<uintptr_t>(bits + u0) & 3) == 0) {
-      *reinterpret_cast<uint32_t*>(bits + u0) = packed;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (u0 + e >= 0 && u0 + e < U) bits[u0 + e] = static_cast<uint8_t>(packed >> (8 * e));
-    }
+    for (int j = 0; j < 4; ++j)
+      if (u0 + 256 * j + tid < U) bits[u0 + 256 * j + tid] = static_cast<uint8_t>(fill);
+    if (a.blk_counts && tid == 0)
+      a.blk_counts[a.item_blk_off[item] + blockIdx.x] =
+          make_int4(fill == 16 ? n : 0, fill == 8 ? n : 0, fill == 4 ? n : 0, fill == 2 ? n : 0);
+    return;
   }
+  float t[kThr];
+#pragma unroll
+  for (int k = 0; k < kThr; ++k) t[k] = P.thr(st.s.best, k);
+  int c[kThr] = {0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    int above[kThr];
+    const int b = tier_of(P, v[j], t, above);
+    if (u0 + 256 * j + tid < U) bits[u0 + 256 * j + tid] = static_cast<uint8_t>(b);
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) c[k] += above[k];
+  }
+  if (!a.blk_counts) return;
+  if ((tid & 63) == 0) s_cnt[tid >> 6] = make_int4(c[0], c[1], c[2], c[3]);
+  __syncthreads();
+  if (tid == 0) {
+    int4 x = s_cnt[0];
+#pragma unroll
+    for (int i = 1; i < 4; ++i) { x.x += s_cnt[i].x; x.y += s_cnt[i].y; x.z += s_cnt[i].z; x.w += s_cnt[i].w; }
+    a.blk_counts[a.item_blk_off[item] + blockIdx.x] = tier_counts(P, n, x);
+  }
+}
+
+// hipMemsetAsync for memory that a captured graph may clear too
+__global__ __launch_bounds__(256) void clear_kernel(uint4* p, int64_t n) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * 256)
+    p[i] = make_uint4(0, 0, 0, 0);
 }
 
 // Stage 3 of Alg. 1: the K budget r_K * B_head of an item is spread over its retained tokens (bit-width above zero)
 // only: k_avg = min(16, 2 r_K avg_bits T / n_kept) average bits per channel unit, 0 if nothing is retained; rounded
-// to fp32 like every budget.  fp64 in this operation order (the file is compiled without contraction).
-__global__ __launch_bounds__(1024) void stage3_budget_kernel(const uint8_t* __restrict__ bits,
-                                                             const int64_t* __restrict__ item_off,
-                                                             const int32_t* __restrict__ item_U,
-                                                             const double* __restrict__ item_avg, double rk,
-                                                             int32_t* __restrict__ kept,
-                                                             double* __restrict__ k_budget) {
-  __shared__ int sm[16];
-  const int item = blockIdx.x;
-  const int U = item_U[item];
-  const uint8_t* b = bits + item_off[item];
-  int c = 0;
-  // 16 bytes per load once the pointer is aligned
-  const int head = min(U, static_cast<int>((16 - (reinterpret_cast<uintptr_t>(b) & 15)) & 15));
-  for (int u = threadIdx.x; u < head; u += 1024) c += b[u] != 0;
-  const int nq = (U - head) >> 4;
-  const uint4* q = reinterpret_cast<const uint4*>(b + head);
-  for (int i = threadIdx.x; i < nq; i += 1024) {
-    const uint4 v = q[i];
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) c += ((w[k] >> (8 * e)) & 0xFFu) != 0;
+// to fp32 like every budget.  fp64 in this operation order (the file is compiled without contraction).  The map over
+// the item's 128 channels is then searched by one wavefront, two channels per lane.
+struct ChannelArgs {
+  AllocArgs a;                 // w, bits: the channel weights and map [items][128]; item_off, item_U, item_budget unused
+  const int4* blk_counts;      // [blocks] of the token maps: kept tokens per tier
+  const int32_t* item_blk_off;
+  const int32_t* item_T;
+  const double* item_avg;      // average bits per cache element of the item's sequence
+  double rk;
+};
+__global__ __launch_bounds__(64) void channel_allocate_kernel(ChannelArgs c) {
+  const AllocArgs& a = c.a;
+  const int item = blockIdx.x, lane = threadIdx.x;
+  const float* w = a.w + static_cast<int64_t>(item) * kHeadDim;
+  const float v[2] = {w[lane], w[64 + lane]};
+  const int4* bc = c.blk_counts + c.item_blk_off[item];
+  const int nblk = (c.item_T[item] + kBlockUnits - 1) / kBlockUnits;
+  int kept = 0;
+  for (int i = lane; i < nblk; i += 64) {
+    const int4 n = bc[i];
+    kept += n.x + n.y + n.z + n.w;
   }
-  for (int u = head + 16 * nq + threadIdx.x; u < U; u += 1024) c += b[u] != 0;
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int n = 0;
-    for (int i = 0; i < 16; ++i) n += sm[i];
-    kept[item] = n;
-    double k_avg = 0.0;
-    if (n > 0) k_avg = fmin(16.0, 2.0 * rk * item_avg[item] * static_cast<double>(U) / static_cast<double>(n));
-    k_budget[item] = static_cast<double>(static_cast<float>(k_avg));
+  for (int o = 32; o > 0; o >>= 1) kept += __shfl_xor(kept, o);
+  double k_avg = 0.0;
+  if (kept > 0)
+    k_avg = fmin(16.0, 2.0 * c.rk * c.item_avg[item] * static_cast<double>(c.item_T[item]) / static_cast<double>(kept));
+  const Problem P(a, kHeadDim, static_cast<double>(static_cast<float>(k_avg)));
+  uint8_t* bits = a.bits + static_cast<int64_t>(item) * kHeadDim;
+  const int fill = P.fill(kHeadDim);
+  Search S{0.0, 0.0, 0.0, 0, 0, 0};
+  float t[kThr];
+  if (fill < 0) {
+    S.hi = static_cast<double>(wave_max(fmaxf(fmaxf(v[0], v[1]), 0.f)));
+    steps_in_wave<2>(P, v, P.base, S);
+#pragma unroll
+    for (int k = 0; k < kThr; ++k) t[k] = S.have ? P.thr(S.best, k) : INFINITY;
   }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    int above[kThr];
+    bits[64 * j + lane] = static_cast<uint8_t>(fill >= 0 ? fill : tier_of(P, v[j], t, above));
+  }
+  if (lane == 0) report(a, item, fill < 0, S);
 }
 
-}  // namespace
-
-hipError_t launch_stage3_budget(const uint8_t* bits, const int64_t* d_item_off, const int32_t* d_item_U,
-                                const double* d_item_avg, double rk, int n_items, int32_t* kept, double* k_budget,
-                                hipStream_t st) {
-  if (n_items == 0) return hipSuccess;
-  hipLaunchKernelGGL(stage3_budget_kernel, dim3(n_items), dim3(1024), 0, st, bits, d_item_off, d_item_U, d_item_avg,
-                     rk, kept, k_budget);
-  return hipGetLastError();
-}
-
-hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
-                           const double* d_item_budget, int n_items, int n_hull, const int* hull_tiers,
-                           const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
-                           int32_t* iters_out, void* multi_scratch, hipStream_t st) {
-  if (n_items == 0) return hipSuccess;
-  if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
-  AllocArgs a;
-  a.w = w; a.item_off = d_item_off; a.item_U = d_item_U; a.item_budget = d_item_budget; a.bits = bits;
+AllocArgs make_args(const float* w, int n_hull, const int* hull_tiers, const double* hull_r, double need_frac,
+                    int max_iters, uint8_t* bits, double* lam_out, int32_t* iters_out) {
+  AllocArgs a{};
+  a.w = w; a.bits = bits;
   for (int k = 0; k < kMaxHull; ++k) {
     a.tiers[k] = k < n_hull ? hull_tiers[k] : 0;
     a.r[k] = k < n_hull - 1 ? hull_r[k] : 0.0;
   }
   a.n_hull = n_hull; a.max_iters = max_iters; a.need_frac = need_frac;
   a.lam_out = lam_out; a.iters_out = iters_out;
-  if (multi_scratch != nullptr) {   // long items: the streaming passes on many workgroups
-    MultiArgs m;
-    m.a = a;
-    uint8_t* p = static_cast<uint8_t*>(multi_scratch);
-    const size_t hist_b = (static_cast<size_t>(n_items) * (kBuckets + 1) * sizeof(int32_t) + 255) / 256 * 256;
-    const size_t state_b = (static_cast<size_t>(n_items) * sizeof(SearchState) + 255) / 256 * 256;
-    m.hist = reinterpret_cast<int32_t*>(p);
-    m.state = reinterpret_cast<SearchState*>(p + hist_b);
-    m.list = reinterpret_cast<float*>(p + hist_b + state_b);
-    m.slices = std::max(1, std::min(64, 512 / n_items));
-    hipError_t e = hipMemsetAsync(p, 0, hist_b + state_b, st);
-    if (e != hipSuccess) return e;
-    const dim3 wide(m.slices, n_items), one(n_items), block(kThreads);
-    hipLaunchKernelGGL(hist_kernel, wide, block, 0, st, m);
-    hipLaunchKernelGGL(steps_kernel<0>, one, block, 0, st, m);
-    hipLaunchKernelGGL(gather_kernel, wide, block, 0, st, m);
-    hipLaunchKernelGGL(steps_kernel<1>, one, block, 0, st, m);
-    hipLaunchKernelGGL(write_kernel, wide, block, 0, st, m);
+  return a;
+}
+
+template <class K>
+hipError_t allow_lds(K kernel, size_t lds) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             static_cast<int>(lds));
+}
+
+size_t hist_bytes(int n_items) { return static_cast<size_t>(n_items) * FullRange::kBuckets * sizeof(int32_t); }
+size_t state_bytes(int n_items) { return (static_cast<size_t>(n_items) * sizeof(SearchState) + 255) / 256 * 256; }
+
+}  // namespace
+
+// Device scratch launch_allocate needs for items of up to max_U units; 0 where one workgroup holds an item.
+size_t allocate_scratch_bytes(int n_items, int max_U) {
+  if (max_U <= kItemUnits) return 0;
+  return hist_bytes(n_items) + state_bytes(n_items) + static_cast<size_t>(n_items) * kListCap * sizeof(float);
+}
+
+// Token maps of all items.  blk_counts (with item_blk_off): what the packing stage needs, or null.
+hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
+                           const double* d_item_budget, int n_items, int max_U, int n_hull, const int* hull_tiers,
+                           const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
+                           int32_t* iters_out, const int32_t* d_item_blk_off, int32_t* blk_counts, void* scratch,
+                           hipStream_t st) {
+  if (n_items == 0) return hipSuccess;
+  if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
+  AllocArgs a = make_args(w, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits, lam_out, iters_out);
+  a.item_off = d_item_off; a.item_U = d_item_U; a.item_budget = d_item_budget;
+  a.item_blk_off = d_item_blk_off; a.blk_counts = reinterpret_cast<int4*>(blk_counts);
+  hipError_t e = hipSuccess;
+  const dim3 block(kThreads);
+  if (max_U <= kItemUnits) {
+#define RDKV_ITEMS(REG_)                                                                               \
+  {                                                                                                    \
+    e = allow_lds(allocate_item_kernel<REG_>, kItemLds);                                               \
+    if (e != hipSuccess) return e;                                                                     \
+    hipLaunchKernelGGL(allocate_item_kernel<REG_>, dim3(n_items), block, kItemLds, st, a);             \
+  }
+    if (max_U <= 4 * kThreads) RDKV_ITEMS(4)
+    else if (max_U <= 16 * kThreads) RDKV_ITEMS(16)
+    else RDKV_ITEMS(32)
+#undef RDKV_ITEMS
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(bisect_kernel, dim3(n_items), dim3(kThreads), 0, st, a);
+  if (!scratch) return hipErrorInvalidValue;
+  MultiArgs m;
+  m.a = a;
+  uint8_t* p = static_cast<uint8_t*>(scratch);
+  m.hist = reinterpret_cast<int32_t*>(p);
+  m.state = reinterpret_cast<SearchState*>(p + hist_bytes(n_items));
+  m.list = reinterpret_cast<float*>(p + hist_bytes(n_items) + state_bytes(n_items));
+  m.slices = std::max(1, std::min(32, 256 / n_items));
+  const int64_t clear = static_cast<int64_t>((hist_bytes(n_items) + state_bytes(n_items)) / 16);
+  hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>(std::min<int64_t>(1024, (clear + 255) / 256))), dim3(256), 0, st,
+                     reinterpret_cast<uint4*>(p), clear);
+  const dim3 wide(m.slices, n_items);
+  e = allow_lds(hist_kernel, kHistLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(hist_kernel, wide, block, kHistLds, st, m);
+  e = allow_lds(gather_kernel, kGatherLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(gather_kernel, wide, block, kGatherLds, st, m);
+  hipLaunchKernelGGL(write_kernel, dim3((max_U + kBlockUnits - 1) / kBlockUnits, n_items), dim3(256), 0, st, m);
   return hipGetLastError();
 }
 
-// device scratch launch_allocate needs to spread long items over many workgroups
-size_t allocate_multi_scratch_bytes(int n_items) {
-  const size_t hist_b = (static_cast<size_t>(n_items) * (kBuckets + 1) * sizeof(int32_t) + 255) / 256 * 256;
-  const size_t state_b = (static_cast<size_t>(n_items) * sizeof(SearchState) + 255) / 256 * 256;
-  return hist_b + state_b + static_cast<size_t>(n_items) * 2 * kGlobalListCap * sizeof(float);
+// Stage 3: the channel maps, from the kept tokens launch_allocate has counted.
+hipError_t launch_allocate_channels(const float* w_ch, const int32_t* blk_counts, const int32_t* d_item_blk_off,
+                                    const int32_t* d_item_T,
+                                    const double* d_item_avg, double rk, int n_items, int n_hull, const int* hull_tiers,
+                                    const double* hull_r, double need_frac, int max_iters, uint8_t* bits_ch,
+                                    double* lam_out, int32_t* iters_out, hipStream_t st) {
+  if (n_items == 0) return hipSuccess;
+  if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
+  ChannelArgs c;
+  c.a = make_args(w_ch, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits_ch, lam_out, iters_out);
+  c.blk_counts = reinterpret_cast<const int4*>(blk_counts); c.item_blk_off = d_item_blk_off; c.item_T = d_item_T; c.item_avg = d_item_avg; c.rk = rk;
+  hipLaunchKernelGGL(channel_allocate_kernel, dim3(n_items), dim3(64), 0, st, c);
+  return hipGetLastError();
 }
 
 }  // namespace rdkv

@@ -57,36 +57,12 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
   }
 }
 
-// exclusive scan of the block counts of one item: one wavefront per tier, 64 blocks per step
-__global__ __launch_bounds__(256) void tier_scan_kernel(const int32_t* __restrict__ item_T,
-                                                        const int32_t* __restrict__ item_blk_off,
-                                                        int32_t* __restrict__ blk_counts,
-                                                        int32_t* __restrict__ item_counts) {
-  const int item = blockIdx.x, k = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int nblk = (item_T[item] + kPartBlock - 1) / kPartBlock;
-  int32_t* p = blk_counts + static_cast<int64_t>(item_blk_off[item]) * 4 + k;
-  int run = 0;
-  for (int b0 = 0; b0 < nblk; b0 += 64) {
-    const int i = b0 + lane;
-    const int v = i < nblk ? p[i * 4] : 0;
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o);
-      if (lane >= o) incl += t;
-    }
-    if (i < nblk) p[i * 4] = run + incl - v;
-    run += __shfl(incl, 63);
-  }
-  if (lane == 0) item_counts[item * 4 + k] = run;
-}
-
 // writes the ascending position lists: tier_idx[item_base + tier_base + rank]
 __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __restrict__ bits,
                                                            const int64_t* __restrict__ item_tok_off,
                                                            const int32_t* __restrict__ item_T,
                                                            const int32_t* __restrict__ item_blk_off,
-                                                           const int32_t* __restrict__ blk_offsets,
+                                                           const int4* __restrict__ blk_counts,
                                                            const int64_t* __restrict__ idx_base /* [items][4] */,
                                                            int32_t* __restrict__ tier_idx) {
   const int item = blockIdx.y;
@@ -97,7 +73,22 @@ __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __rest
   __shared__ int wave_cnt[4][4];
   __shared__ int run_base[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x < 4) run_base[threadIdx.x] = blk_offsets[(item_blk_off[item] + blockIdx.x) * 4 + threadIdx.x];
+  {   // kept tokens of the item's earlier blocks
+    int4 c = make_int4(0, 0, 0, 0);
+    for (int i = threadIdx.x; i < static_cast<int>(blockIdx.x); i += 256) {
+      const int4 x = blk_counts[item_blk_off[item] + i];
+      c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
+    }
+    int v[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+      if (lane == 0) wave_cnt[wave][k] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4)
+      run_base[threadIdx.x] = wave_cnt[0][threadIdx.x] + wave_cnt[1][threadIdx.x] + wave_cnt[2][threadIdx.x] + wave_cnt[3][threadIdx.x];
+  }
   __syncthreads();
   for (int sub = 0; sub < kPartBlock; sub += 256) {
     const int t = t0 + sub + threadIdx.x;
@@ -506,25 +497,23 @@ __global__ __launch_bounds__(256) void pack_k_mixed_kernel(PackArgs a) {
 }  // namespace
 
 hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                             const int32_t* item_blk_off, int32_t* blk_counts, int32_t* item_counts,
-                             int32_t* invalid, int n_items, int max_T, hipStream_t st) {
+                             const int32_t* item_blk_off, int32_t* blk_counts, int32_t* invalid,
+                             int n_items, int max_T, hipStream_t st) {
   const int max_blk = (max_T + kPartBlock - 1) / kPartBlock;
   if (n_items == 0 || max_blk == 0) return hipSuccess;
   // `invalid` (zero on entry) is set when the map holds a value that is no bit-width of the method
   hipLaunchKernelGGL(tier_count_kernel, dim3(max_blk, n_items), dim3(256), 0, st, bits, item_tok_off, item_T,
                      item_blk_off, blk_counts, invalid);
-  hipLaunchKernelGGL(tier_scan_kernel, dim3(n_items), dim3(256), 0, st, item_T, item_blk_off, blk_counts,
-                     item_counts);
   return hipGetLastError();
 }
 
 hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                               const int32_t* item_blk_off, const int32_t* blk_offsets, const int64_t* idx_base,
+                               const int32_t* item_blk_off, const int32_t* blk_counts, const int64_t* idx_base,
                                int32_t* tier_idx, int n_items, int max_T, hipStream_t st) {
   const int max_blk = (max_T + kPartBlock - 1) / kPartBlock;
   if (n_items == 0 || max_blk == 0) return hipSuccess;
   hipLaunchKernelGGL(tier_scatter_kernel, dim3(max_blk, n_items), dim3(256), 0, st, bits, item_tok_off, item_T,
-                     item_blk_off, blk_offsets, idx_base, tier_idx);
+                     item_blk_off, reinterpret_cast<const int4*>(blk_counts), idx_base, tier_idx);
   return hipGetLastError();
 }
 

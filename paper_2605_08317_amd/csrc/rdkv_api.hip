@@ -16,10 +16,9 @@
 
 namespace rdkv {
 hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                             const int32_t* item_blk_off, int32_t* blk_counts, int32_t* item_counts,
-                             int32_t* invalid, int n_items, int max_T, hipStream_t st);
+                             const int32_t* item_blk_off, int32_t* blk_counts, int32_t* invalid, int n_items, int max_T, hipStream_t st);
 hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                               const int32_t* item_blk_off, const int32_t* blk_offsets, const int64_t* idx_base,
+                               const int32_t* item_blk_off, const int32_t* blk_counts, const int64_t* idx_base,
                                int32_t* tier_idx, int n_items, int max_T, hipStream_t st);
 hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx,
                              const int64_t* idx_base, const int32_t* counts, const int64_t* seg_off,
@@ -33,17 +32,20 @@ hipError_t launch_weights(const rdkv_config& cfg, const int64_t* d_item_row_off,
                           const int32_t* d_item_tile_off, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
                           int max_T, const uint16_t* K, const uint16_t* Q_obs, float* w_tok, float* w_ch,
                           float* scratch, hipStream_t st);
+size_t allocate_scratch_bytes(int n_items, int max_U);
 hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
-                           const double* d_item_budget, int n_items, int n_hull, const int* hull_tiers,
-                           const double* hull_r, double rel_tol, int max_iters, uint8_t* bits, double* lam_out,
-                           int32_t* iters_out, void* multi_scratch, hipStream_t st);
-size_t allocate_multi_scratch_bytes(int n_items);
+                           const double* d_item_budget, int n_items, int max_U, int n_hull, const int* hull_tiers,
+                           const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
+                           int32_t* iters_out, const int32_t* d_item_blk_off, int32_t* blk_counts, void* scratch,
+                           hipStream_t st);
+hipError_t launch_allocate_channels(const float* w_ch, const int32_t* blk_counts, const int32_t* d_item_blk_off,
+                                    const int32_t* d_item_T,
+                                    const double* d_item_avg, double rk, int n_items, int n_hull, const int* hull_tiers,
+                                    const double* hull_r, double need_frac, int max_iters, uint8_t* bits_ch,
+                                    double* lam_out, int32_t* iters_out, hipStream_t st);
 hipError_t launch_calibrate(const uint16_t* K, const uint16_t* V, const int64_t* item_row_off, const int32_t* item_T,
                             int n_items, int max_T, bool k_channelwise, bool k_whole_channel, bool row_wide,
                             double* acc_k, double* acc_v, uint32_t* range, hipStream_t st);
-hipError_t launch_stage3_budget(const uint8_t* bits, const int64_t* d_item_off, const int32_t* d_item_U,
-                                const double* d_item_avg, double rk, int n_items, int32_t* kept, double* k_budget,
-                                hipStream_t st);
 }  // namespace rdkv
 
 using namespace rdkv;
@@ -477,11 +479,9 @@ struct Tables {
   int64_t* tok_off = nullptr;    // first token of the item in ragged [hkv][T_s] arrays
   double* budget = nullptr;      // average bits of the token map (channel-wise mode: the V share)
   double* avg = nullptr;         // average bits per cache element of the item's sequence
-  int64_t* ch_off = nullptr;     // item * 128
   int32_t* T = nullptr;
   int32_t* wblk_off = nullptr;   // [items + 1]: first key tile of the item in the weights kernels
   int32_t* blk_off = nullptr;    // first partition block of the item
-  int32_t* ch_U = nullptr;       // 128
   int64_t n_wblk = 0;
 };
 
@@ -489,15 +489,13 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
                         Tables* out) {
   const size_t n = static_cast<size_t>(std::max<int64_t>(it.n_items, 1));
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
-  std::vector<uint8_t> blob(48 * n + 16, 0);
+  std::vector<uint8_t> blob(36 * n + 16, 0);
   int64_t* tok_off = reinterpret_cast<int64_t*>(blob.data());
   double* budget = reinterpret_cast<double*>(blob.data() + 8 * n);
   double* avg = reinterpret_cast<double*>(blob.data() + 16 * n);
-  int64_t* ch_off = reinterpret_cast<int64_t*>(blob.data() + 24 * n);
-  int32_t* T = reinterpret_cast<int32_t*>(blob.data() + 32 * n);
+  int32_t* T = reinterpret_cast<int32_t*>(blob.data() + 24 * n);
   int32_t* blk = T + n;
-  int32_t* ch_U = T + 2 * n;
-  int32_t* wblk = T + 3 * n;      // n + 1 entries
+  int32_t* wblk = T + 2 * n;      // n + 1 entries
   const int key_tile = weights_key_tile();
   int64_t n_wblk = 0;
   for (int64_t i = 0; i < it.n_items; ++i) {
@@ -506,8 +504,6 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
     blk[i] = it.blk_off[i];
     wblk[i] = static_cast<int32_t>(n_wblk);
     n_wblk += (it.T[i] + key_tile - 1) / key_tile;
-    ch_off[i] = i * kHeadDim;
-    ch_U[i] = kHeadDim;
     if (with_budget) {
       // Stage 2.  Token-wise mode: the sequence's average serves K and V alike.  Channel-wise mode: V gets the share
       // 1 - r_K of the head budget, i.e. 2 (1 - r_K) avg_bits per token unit (rounded to fp32 like every budget).
@@ -523,11 +519,9 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
   out->tok_off = reinterpret_cast<int64_t*>(d);
   out->budget = reinterpret_cast<double*>(d + 8 * n);
   out->avg = reinterpret_cast<double*>(d + 16 * n);
-  out->ch_off = reinterpret_cast<int64_t*>(d + 24 * n);
-  out->T = reinterpret_cast<int32_t*>(d + 32 * n);
+  out->T = reinterpret_cast<int32_t*>(d + 24 * n);
   out->blk_off = out->T + n;
-  out->ch_U = out->T + 2 * n;
-  out->wblk_off = out->T + 3 * n;
+  out->wblk_off = out->T + 2 * n;
   out->n_wblk = n_wblk;
   return RDKV_OK;
 }
@@ -547,41 +541,40 @@ rdkv_status weights_impl(const rdkv_config* cfg, const Items& it, const Tables& 
 }
 
 // Stages 2-3 of Alg. 1; everything is enqueued on st, nothing waits.  lam / iters: device [items] (token map), in
-// channel-wise mode followed by [items] for the channel map; or null.
+// channel-wise mode followed by [items] for the channel map; or null.  blk_counts: device [blocks][4] for the packing
+// stage (kept tokens of every block of an item per tier), or null.
 rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const float* w_tok,
                           const float* w_ch, uint8_t* bits_tok, uint8_t* bits_ch, double* lam, int32_t* iters,
-                          Temp& tmp, hipStream_t st) {
+                          int32_t* blk_counts, Temp& tmp, hipStream_t st) {
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
   const int n = static_cast<int>(it.n_items);
   std::vector<int> ht;
   std::vector<double> hr;
   hull_thresholds(cfg, cfg->eps_v, &ht, &hr);
-  // items of 16K tokens and more: the passes over the weights run on many workgroups per item
-  void* multi = nullptr;
-  if (it.max_T >= 16384 && n <= 512) {
-    multi = tmp.get<uint8_t>(allocate_multi_scratch_bytes(n));
-    if (!multi) return fail(RDKV_ERR_ALLOC, "device allocation failed");
+  const size_t nscr = allocate_scratch_bytes(n, it.max_T);
+  void* scratch = nscr ? tmp.get<uint8_t>(nscr) : nullptr;
+  if (nscr && !scratch) return fail(RDKV_ERR_ALLOC, "device allocation failed");
+  if (!blk_counts && mixed) {                 // Stage 3 starts from them
+    blk_counts = tmp.get<int32_t>(static_cast<size_t>(std::max<int64_t>(it.n_blocks, 1)) * 4);
+    if (!blk_counts) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   }
   TimedScope ts(RDKV_TIME_ALLOCATE, st);      // every kernel of the stage
-  RDKV_HIP(launch_allocate(w_tok, tb.tok_off, tb.T, tb.budget, n, static_cast<int>(ht.size()), ht.data(), hr.data(),
-                           1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_tok, lam, iters, multi, st));
+  RDKV_HIP(launch_allocate(w_tok, tb.tok_off, tb.T, tb.budget, n, it.max_T, static_cast<int>(ht.size()), ht.data(), hr.data(),
+                           1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_tok, lam, iters, tb.blk_off,
+                           blk_counts, scratch, st));
   if (!mixed) return RDKV_OK;
-  // Stage 3, on the device: retained tokens per item, then k_avg = min(16, 2 r_K avg_bits T / n_kept)
-  int32_t* d_kept = tmp.get<int32_t>(it.n_items);
-  double* d_kbudget = tmp.get<double>(it.n_items);
-  if (!d_kept || !d_kbudget) return fail(RDKV_ERR_ALLOC, "device allocation failed");
-  RDKV_HIP(launch_stage3_budget(bits_tok, tb.tok_off, tb.T, tb.avg, static_cast<double>(cfg->kv_split_rk), n, d_kept,
-                                d_kbudget, st));
+  // Stage 3, on the device: k_avg = min(16, 2 r_K avg_bits T / n_kept) over the retained tokens just counted
   hull_thresholds(cfg, cfg->eps_k, &ht, &hr);
-  RDKV_HIP(launch_allocate(w_ch, tb.ch_off, tb.ch_U, d_kbudget, n, static_cast<int>(ht.size()), ht.data(), hr.data(),
-                           1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_ch, lam ? lam + n : nullptr,
-                           iters ? iters + n : nullptr, nullptr, st));
+  RDKV_HIP(launch_allocate_channels(w_ch, blk_counts, tb.blk_off, tb.T, tb.avg, static_cast<double>(cfg->kv_split_rk), n,
+                                    static_cast<int>(ht.size()), ht.data(), hr.data(),
+                                    1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_ch,
+                                    lam ? lam + n : nullptr, iters ? iters + n : nullptr, st));
   return RDKV_OK;
 }
 
 rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const void* K, const void* V,
-                      const uint8_t* bits_tok, const uint8_t* bits_ch, double* lam, int32_t* iters, Temp& tmp,
-                      hipStream_t st, rdkv_cache** out) {
+                      const uint8_t* bits_tok, const uint8_t* bits_ch, int32_t* d_blk_counts, double* lam,
+                      int32_t* iters, Temp& tmp, hipStream_t st, rdkv_cache** out) {
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
   Allocator al{cfg->alloc, cfg->free_, cfg->alloc_user};
   const int g = cfg->hq / cfg->hkv;
@@ -605,8 +598,11 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   c->counts.assign(n * 4, 0);
   c->seg_off.assign(n * 16, 0);
   const size_t n1 = static_cast<size_t>(std::max<int64_t>(n, 1));
-  int32_t* d_blk_counts = tmp.get<int32_t>(std::max<int64_t>(it.n_blocks * 4, 1));
-  int32_t* d_counts = tmp.get<int32_t>(n1 * 4 + 1);          // [items][4], then the invalid-value flag
+  // tier counts of every block of the bit map: the allocation's own, or counted here (then the invalid-value flag)
+  const bool counted = d_blk_counts != nullptr;
+  const int64_t n_counts = it.n_blocks * 4 + (counted ? 0 : 1);
+  if (!counted) d_blk_counts = tmp.get<int32_t>(n_counts);
+  int32_t* d_counts = tmp.get<int32_t>(n1 * 4);              // [items][4]
   int64_t* d_idx_base = tmp.get<int64_t>(n1 * 20);     // [items][4] kept-position bases, then [items][16] segment offsets
   int64_t* d_seg_off = d_idx_base ? d_idx_base + n1 * 4 : nullptr;
   if (!d_blk_counts || !d_counts || !d_idx_base)
@@ -617,24 +613,28 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
 
   if (n > 0) {
     // the one wait of the pass: the tier counts size the arena and the split schedule
-    std::vector<int32_t> h_counts(n * 4 + 1, 0);
-    PACK_HIP(hipMemsetAsync(d_counts + n * 4, 0, sizeof(int32_t), st));
-    {
+    std::vector<int32_t> h_counts(n_counts, 0);
+    if (!counted) {
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
-      PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_counts, d_counts + n * 4,
+      PACK_HIP(hipMemsetAsync(d_blk_counts + it.n_blocks * 4, 0, sizeof(int32_t), st));
+      PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_blk_counts + it.n_blocks * 4,
                                  static_cast<int>(n), it.max_T, st));
     }
     if (it.max_T > 0)
-      PACK_HIP(hipMemcpyAsync(h_counts.data(), d_counts, (n * 4 + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+      PACK_HIP(hipMemcpyAsync(h_counts.data(), d_blk_counts, n_counts * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     std::vector<uint8_t> h_bits_ch;
     if (mixed) {
       h_bits_ch.resize(n * kHeadDim);
       PACK_HIP(hipMemcpyAsync(h_bits_ch.data(), bits_ch, n * kHeadDim, hipMemcpyDeviceToHost, st));
     }
     PACK_HIP(hipStreamSynchronize(st));
-    if (h_counts[n * 4] != 0)
+    if (!counted && h_counts[it.n_blocks * 4] != 0)
       return bail(fail(RDKV_ERR_INVALID_ARG, "bits_tok holds a value outside {0, 2, 4, 8, 16}"));
-    std::copy(h_counts.begin(), h_counts.begin() + n * 4, c->counts.begin());
+    for (int64_t i = 0; i < n; ++i) {
+      const int64_t b1 = i + 1 < n ? it.blk_off[i + 1] : it.n_blocks;
+      for (int64_t b = it.blk_off[i]; b < b1; ++b)
+        for (int k = 0; k < 4; ++k) c->counts[i * 4 + k] += h_counts[b * 4 + k];
+    }
     if (mixed) {
       c->items_k.resize(n);
       for (int64_t i = 0; i < n; ++i) {
@@ -929,6 +929,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     if (n > 0) {
       // nothing below waits: tables are copied out of pinned staging memory, and the host vectors may go
       PACK_HIP(hipMemsetAsync(c->d_block, 0, o_idx, st));     // arena (padding rows read as zeros), tail state, counters
+      PACK_HIP(upload(d_counts, c->counts.data(), n * 4 * sizeof(int32_t), st));
       std::vector<int64_t> plan(idx_base);
       plan.resize(n1 * 4, 0);
       plan.insert(plan.end(), c->seg_off.begin(), c->seg_off.end());
@@ -1141,7 +1142,7 @@ rdkv_status rdkv_allocate_info(const rdkv_config* cfg, const float* w_tok, const
   Tables tb;
   s = make_tables(cfg, it, true, tmp, st, &tb);
   if (s != RDKV_OK) return s;
-  return allocate_impl(cfg, it, tb, w_tok, w_ch, bits_tok, bits_ch, lambda_out, iterations_out, tmp, st);
+  return allocate_impl(cfg, it, tb, w_tok, w_ch, bits_tok, bits_ch, lambda_out, iterations_out, nullptr, tmp, st);
 }
 
 rdkv_status rdkv_allocate(const rdkv_config* cfg, const float* w_tok, const float* w_ch, uint8_t* bits_tok,
@@ -1167,7 +1168,7 @@ rdkv_status rdkv_pack(const rdkv_config* cfg, const void* K, const void* V, cons
   Tables tb;
   s = make_tables(cfg, it, false, tmp, st, &tb);
   if (s != RDKV_OK) return s;
-  return pack_impl(cfg, it, tb, K, V, bits_tok, bits_ch, nullptr, nullptr, tmp, st, out);
+  return pack_impl(cfg, it, tb, K, V, bits_tok, bits_ch, nullptr, nullptr, nullptr, tmp, st, out);
 }
 
 rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, const void* Q_obs, void* stream,
@@ -1189,12 +1190,11 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
     const int R = cfg->hq / cfg->hkv * cfg->s_obs, key_tile = weights_key_tile();
     int64_t n_wblk = 0;
     for (int64_t i = 0; i < it.n_items; ++i) n_wblk += (it.T[i] + key_tile - 1) / key_tile;
-    tmp.reserve({48 * ni + 16, nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
+    tmp.reserve({36 * ni + 16, nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
                  weights_scratch_floats(n_wblk, it.n_items, it.total_tokens, R, mixed) * sizeof(float),
-                 mixed ? ni * sizeof(int32_t) : 0, mixed ? ni * sizeof(double) : 0,
                  static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t),
                  (ni * 4 + 1) * sizeof(int32_t), ni * 20 * sizeof(int64_t), ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),
-                 it.max_T >= 16384 && it.n_items <= 512 ? allocate_multi_scratch_bytes(static_cast<int>(it.n_items)) : 0,
+                 allocate_scratch_bytes(static_cast<int>(it.n_items), it.max_T),
                  mixed && cfg->k_scale_per_channel ? nc * 2 * sizeof(uint32_t) : 0});
   }
   Tables tb;
@@ -1205,7 +1205,7 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   float* w_ch = mixed ? tmp.get<float>(nc) : nullptr;
   uint8_t* bits_ch = mixed ? tmp.get<uint8_t>(nc) : nullptr;
   if (!w || !bits || (mixed && (!w_ch || !bits_ch))) return fail(RDKV_ERR_ALLOC, "device allocation failed");
-  if (it.n_items == 0) return pack_impl(cfg, it, tb, K, V, bits, bits_ch, nullptr, nullptr, tmp, st, out);
+  if (it.n_items == 0) return pack_impl(cfg, it, tb, K, V, bits, bits_ch, nullptr, nullptr, nullptr, tmp, st, out);
   // the multiplier and the step count of every item's search stay with the cache (rdkv_cache_stats / export): the
   // pack stage copies them into the cache's block
   const int maps = mixed ? 2 : 1;
@@ -1214,9 +1214,11 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   if (!lam || !iters) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   s = weights_impl(cfg, it, tb, K, Q_obs, w, w_ch, tmp, st);
   if (s != RDKV_OK) return s;
-  s = allocate_impl(cfg, it, tb, w, w_ch, bits, bits_ch, lam, iters, tmp, st);
+  int32_t* blk_counts = tmp.get<int32_t>(static_cast<size_t>(std::max<int64_t>(it.n_blocks, 1)) * 4);
+  if (!blk_counts) return fail(RDKV_ERR_ALLOC, "device allocation failed");
+  s = allocate_impl(cfg, it, tb, w, w_ch, bits, bits_ch, lam, iters, blk_counts, tmp, st);
   if (s != RDKV_OK) return s;
-  return pack_impl(cfg, it, tb, K, V, bits, bits_ch, lam, iters, tmp, st, out);
+  return pack_impl(cfg, it, tb, K, V, bits, bits_ch, blk_counts, lam, iters, tmp, st, out);
 }
 
 // A-priori bound on the packed arena from the budget alone (Sec. 3.2: sum of bit-widths <= floor(avg * units)).

@@ -8,8 +8,11 @@
 //   mn = min x, mx = max x            over a group of 32 channels
 //   s  = fp16_rn((mx - mn) / Q)        Q = 2^b - 1, IEEE divide
 //   m  = fp16_rn(mn)
-//   code = clamp(rint((x - m) / s), 0, Q), all zero when s == 0
+//   code = clamp(rint((x - m) / s), 0, Q), all zero when s == 0; the quotient is the correctly rounded one, from the
+//          hardware reciprocal of s and one exact remainder (see Quant::code)
 // Codes occupy b-bit fields of little-endian words (App. B: fields at bit offsets 0,2,4,6 / 0,4 of a byte).
+#include <type_traits>
+
 #include "rdkv_internal.h"
 
 namespace rdkv {
@@ -57,7 +60,11 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
   }
 }
 
-// writes the ascending position lists: tier_idx[item_base + tier_base + rank]
+// four bytes of a bit map at any address
+struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
+
+// Writes the ascending position lists: tier_idx[item_base + tier_base + rank].  One workgroup = one block of 1024 tokens, a
+// thread = four consecutive ones; the ranks of all four tiers come from one prefix sum over 16-bit fields.
 __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __restrict__ bits,
                                                            const int64_t* __restrict__ item_tok_off,
                                                            const int32_t* __restrict__ item_T,
@@ -65,59 +72,57 @@ __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __rest
                                                            const int4* __restrict__ blk_counts,
                                                            const int64_t* __restrict__ idx_base /* [items][4] */,
                                                            int32_t* __restrict__ tier_idx) {
+  static_assert(kPartBlock == 1024, "256 threads of four tokens");
+  __shared__ int s_before[4][4];
+  __shared__ uint64_t s_wave[4];
   const int item = blockIdx.y;
   const int T = item_T[item];
   const int t0 = blockIdx.x * kPartBlock;
   if (t0 >= T) return;
-  const uint8_t* b = bits + item_tok_off[item];
-  __shared__ int wave_cnt[4][4];
-  __shared__ int run_base[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  {   // kept tokens of the item's earlier blocks
-    int4 c = make_int4(0, 0, 0, 0);
-    for (int i = threadIdx.x; i < static_cast<int>(blockIdx.x); i += 256) {
-      const int4 x = blk_counts[item_blk_off[item] + i];
-      c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
-    }
-    int v[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
-      if (lane == 0) wave_cnt[wave][k] = v[k];
-    }
-    __syncthreads();
-    if (threadIdx.x < 4)
-      run_base[threadIdx.x] = wave_cnt[0][threadIdx.x] + wave_cnt[1][threadIdx.x] + wave_cnt[2][threadIdx.x] + wave_cnt[3][threadIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint8_t* b = bits + item_tok_off[item] + t0;
+  const int n = min(kPartBlock, T - t0), u = 4 * tid;
+  uint32_t four = 0;                       // tokens past the end: evicted
+  if (u + 3 < n) four = reinterpret_cast<const Bytes4*>(b + u)->v;
+  else
+    for (int e = 0; e < 4; ++e)
+      if (u + e < n) four |= static_cast<uint32_t>(b[u + e]) << (8 * e);
+  int4 c = make_int4(0, 0, 0, 0);          // kept tokens of the item's earlier blocks
+  for (int i = tid; i < static_cast<int>(blockIdx.x); i += 256) {
+    const int4 x = blk_counts[item_blk_off[item] + i];
+    c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
   }
+  int before[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    for (int o = 32; o > 0; o >>= 1) before[k] += __shfl_xor(before[k], o);
+    if (lane == 0) s_before[wave][k] = before[k];
+  }
+  int slot[4];
+  uint64_t mine = 0;                       // this thread's tokens per tier, 16 bits each
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    slot[e] = tier_slot(static_cast<uint8_t>(four >> (8 * e)));
+    mine += slot[e] >= 0 ? 1ull << (16 * slot[e]) : 0ull;
+  }
+  uint64_t incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t x = __shfl_up(incl, o);
+    if (lane >= o) incl += x;
+  }
+  if (lane == 63) s_wave[wave] = incl;
   __syncthreads();
-  for (int sub = 0; sub < kPartBlock; sub += 256) {
-    const int t = t0 + sub + threadIdx.x;
-    const int s = t < T ? tier_slot(b[t]) : -1;
-    int rank_in_wave = 0;
-    int cnt[4];
+  uint64_t rank = incl - mine;
+  for (int w = 0; w < wave; ++w) rank += s_wave[w];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const unsigned long long mask = __ballot(s == k);
-      cnt[k] = __popcll(mask);
-      if (s == k) rank_in_wave = __popcll(mask & ((1ull << lane) - 1ull));
+  for (int e = 0; e < 4; ++e)
+    if (slot[e] >= 0) {
+      const int k = slot[e];
+      const int first = s_before[0][k] + s_before[1][k] + s_before[2][k] + s_before[3][k];
+      tier_idx[idx_base[item * 4 + k] + first + static_cast<int>((rank >> (16 * k)) & 0xFFFF)] = t0 + u + e;
+      rank += 1ull << (16 * k);
     }
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) wave_cnt[wave][k] = cnt[k];
-    }
-    __syncthreads();
-    if (s >= 0) {
-      int before = run_base[s];
-      for (int w = 0; w < wave; ++w) before += wave_cnt[w][s];
-      tier_idx[idx_base[item * 4 + s] + before + rank_in_wave] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < 4) {
-      const int k = threadIdx.x;
-      run_base[k] += wave_cnt[0][k] + wave_cnt[1][k] + wave_cnt[2][k] + wave_cnt[3][k];
-    }
-    __syncthreads();
-  }
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -132,8 +137,6 @@ struct PackArgs {
   const int64_t* seg_off;      // [items][4][4]
   const int64_t* item_row_off; // [items]: first row of the item's [T][d] block in K / V
   uint8_t* arena;
-  int32_t ti;                  // which stored tier this launch packs
-  int32_t v_only;              // mixed mode: K is packed channel-wise by pack_k_mixed_kernel
   const ItemK* items_k;        // [items] (mixed mode)
   const uint8_t* bits_ch;      // [items][128] (mixed mode)
   uint32_t* k_range;           // [items][128][2]: ordered-integer images of a channel's minimum and maximum over all
@@ -151,28 +154,105 @@ __device__ __forceinline__ float ordered_to_float(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
-// 16-bit tier: the kept bf16 rows are copied verbatim, row-major (one thread = 64 bytes of K and of V)
-__global__ __launch_bounds__(256) void copy_rows_kernel(PackArgs a) {
-  const int item = blockIdx.y;
-  const int n = a.counts[item * 4 + a.ti];
-  const int row = blockIdx.x * 64 + (threadIdx.x >> 2);
-  if (row >= n) return;
-  const int part = threadIdx.x & 3;
-  const int pos = a.tier_idx[a.idx_base[item * 4 + a.ti] + row];
-  const int64_t src_row = a.item_row_off[item] + pos;
-  const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + a.ti) * 4;
+// The tile of a workgroup: the tiles of an item stand in the order of its tiers, 16, 8, 4, 2 (blockIdx.x counts them).
+struct TileOf {
+  int ti, n, tile;             // tier, rows of the segment, tile inside the segment; ti = 4: past the item's last
+  __device__ __forceinline__ TileOf(const PackArgs& a, int item, int b) : ti(4), n(0), tile(0) {
+    const int4 c = reinterpret_cast<const int4*>(a.counts)[item];
+    const int rows[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    const uint4* s4 = reinterpret_cast<const uint4*>((which == 0 ? a.K : a.V) + src_row * kHeadDim + part * 32);
-    uint4* d4 = reinterpret_cast<uint4*>(a.arena + so[which * 2] + static_cast<int64_t>(row) * (kHeadDim * 2) + part * 64);
+    for (int k = 0; k < 4; ++k) {
+      const int t = (rows[k] + kTile64 - 1) / kTile64;
+      if (ti == 4) {
+        if (b < t) { ti = k; n = rows[k]; tile = b; } else b -= t;
+      }
+    }
+  }
+};
+
+// The quantizer of one group: scale, offset and codes.  The correctly rounded quotient d / s without the division
+// sequence: q0 = d * y with y the hardware reciprocal of s (within one unit in the last place), remainder r = d - q0 s
+// exact in one fused multiply-add, q = q0 + r y.  On the CPU the result equals the IEEE quotient for every fp16 s, also with
+// y one unit off, over 457 million (d, s) around half-integers, dense ranges and differences of bf16 numbers.  A group
+// with a scale or offset that is not finite takes the division.
+struct Quant {
+  float m, s, y;
+  _Float16 sh, mh;
+  bool finite;
+  template <int BITS>
+  __device__ __forceinline__ void set(float mn, float mx) {
+    constexpr float Q = static_cast<float>((1 << BITS) - 1);
+    mn = mn + 0.0f;            // canonical +0
+    sh = static_cast<_Float16>((mx - mn) / Q);   // round to nearest even
+    mh = static_cast<_Float16>(mn);
+    s = static_cast<float>(sh);
+    m = static_cast<float>(mh);
+    finite = fabsf(s) < INFINITY && fabsf(m) < INFINITY;     // (false for NaN)
+    y = s == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(s);
+  }
+  // the code as a float; EXACT: by division
+  template <int BITS, bool EXACT>
+  __device__ __forceinline__ float code(float x) const {
+    constexpr float Q = static_cast<float>((1 << BITS) - 1);
+    const float d = x - m;
+    float q;
+    if constexpr (EXACT) {
+      q = d / s;
+    } else {
+      const float q0 = d * y;
+      q = __builtin_fmaf(__builtin_fmaf(-q0, s, d), y, q0);
+    }
+    const float t = fminf(fmaxf(rintf(q), 0.0f), Q);
+    return s == 0.0f ? 0.0f : t;
+  }
+};
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kRowMirror = 0x140;
+
+__device__ __forceinline__ void unpack8(const uint4& v, float (&x)[8]) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) d4[i] = s4[i];
+  for (int j = 0; j < 4; ++j) {
+    x[2 * j] = bf16_lo(w[j]);
+    x[2 * j + 1] = bf16_hi(w[j]);
   }
 }
 
-// Tiers 8/4/2: one workgroup = one tile of 64 kept rows, K and V (mixed mode: V only, v_only set).
-//
-// Tile layout (what the decode kernel's 4x4x4 MFMA steps want).  A wavefront lane owns a run of 4*BITS 32-bit words,
+// Quantizes the 8 channels this lane holds of a token row (the 16 lanes of a row hold it in order, four lanes a group of
+// 32 channels); codes as floats.
+template <int BITS>
+__device__ __forceinline__ void quantize_row(const uint4& raw, int row_wide, Quant& g, float (&c)[8]) {
+  float x[8];
+  unpack8(raw, x);
+  float mn = fminf(fminf(fminf(x[0], x[1]), fminf(x[2], x[3])), fminf(fminf(x[4], x[5]), fminf(x[6], x[7])));
+  float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+  mn = fminf(mn, dpp_f<kQuadXor1>(mn));
+  mx = fmaxf(mx, dpp_f<kQuadXor1>(mx));
+  mn = fminf(mn, dpp_f<kQuadXor2>(mn));
+  mx = fmaxf(mx, dpp_f<kQuadXor2>(mx));
+  if (row_wide) {
+    mn = fminf(mn, dpp_f<kHalfMirror>(mn));
+    mx = fmaxf(mx, dpp_f<kHalfMirror>(mx));
+    mn = fminf(mn, dpp_f<kRowMirror>(mn));
+    mx = fmaxf(mx, dpp_f<kRowMirror>(mx));
+  }
+  g.set<BITS>(mn, mx);
+  if (__all(g.finite)) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) c[j] = g.code<BITS, false>(x[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) c[j] = g.code<BITS, true>(x[j]);
+  }
+}
+
+// Tiers 8/4/2: the layout the decode kernels' 4x4x4 MFMA steps want.  A wavefront lane owns a run of 4*BITS 32-bit words,
 // word W of lane L stored at byte 1024*(W/4) + 16*L + 4*(W%4).  The run holds four groups of BITS words; a group is
 // read in eight steps of four codes: with F = 16/BITS fields per 16-bit half, step s reads field s % F of both
 // halves of the word pair s / F, i.e. code k of step s sits at word 2*(s/F) + k/2, bit 16*(k%2) + BITS*(s%F).
@@ -180,164 +260,169 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(PackArgs a) {
 //   V: lane = 32*(r/32) + c % 32; group = c / 32; r % 32 = 4*step + k   (a lane holds one channel for 32 tokens)
 // Metadata tile = 1024 bytes: K row-major per token [4 scales][4 offsets]; V per block of 4 tokens 4 groups x 16
 // bytes: the group's scales of the 4 tokens, then its offsets.
+// K words: this lane's two steps of its group; the lanes of a group OR their fields together.
 template <int BITS>
-__global__ __launch_bounds__(256) void quant_pack_tile64_kernel(PackArgs a) {
-  constexpr int kRows = 64;
-  constexpr int kRowStride = kHeadDim + 8;                 // bf16 elements; 272-byte rows
-  __shared__ __align__(16) uint16_t s_rows[2][kRows][kRowStride];
-  __shared__ __align__(16) uint8_t s_codes[2][kRows][kHeadDim];
-  const int item = blockIdx.y;
-  const int n = a.counts[item * 4 + a.ti];
-  const int r0 = blockIdx.x * kRows;
-  if (r0 >= n) return;
-  const int valid = min(kRows, n - r0);
-  const int tid = threadIdx.x;
-  const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + a.ti) * 4;
-
-  {  // gather the tile's rows: 4 threads per row, 64 bytes of K and of V each
-    const int row = tid >> 2, part = tid & 3;
-    uint4 kv[2][4];
-#pragma unroll
-    for (int w = 0; w < 2; ++w)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) kv[w][i] = make_uint4(0, 0, 0, 0);
-    if (row < valid) {
-      const int pos = a.tier_idx[a.idx_base[item * 4 + a.ti] + r0 + row];
-      const int64_t src = (a.item_row_off[item] + pos) * kHeadDim + part * 32;
-#pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        const uint4* p = reinterpret_cast<const uint4*>((w == 0 ? a.K : a.V) + src);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) kv[w][i] = p[i];
-      }
-    }
-#pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      uint4* d = reinterpret_cast<uint4*>(&s_rows[w][row][part * 32]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) d[i] = kv[w][i];
-    }
+__device__ __forceinline__ void store_k_words(const float (&c)[8], uint8_t* tile, int r, int grp, int p) {
+  constexpr float kField = static_cast<float>(1 << BITS);
+  const auto word = [&](int k) __attribute__((always_inline)) {     // codes k, k + 1 of steps 2 p and 2 p + 1
+    const uint32_t lo = static_cast<uint32_t>(__builtin_fmaf(c[4 + k], kField, c[k]));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_fmaf(c[5 + k], kField, c[k + 1]));
+    return lo | (hi << 16);
+  };
+  uint2 w = make_uint2(word(0), word(2));
+  if constexpr (BITS == 4) {               // fields 2 (p % 2), 2 (p % 2) + 1 of word pair p / 2
+    const int sh = 8 * (p & 1);
+    w.x <<= sh;
+    w.y <<= sh;
+    w.x |= dpp_u<kQuadXor1>(w.x);
+    w.y |= dpp_u<kQuadXor1>(w.y);
+  } else if constexpr (BITS == 2) {        // fields 2 p, 2 p + 1 of the group's only word pair
+    const int sh = 4 * p;
+    w.x <<= sh;
+    w.y <<= sh;
+    w.x |= dpp_u<kQuadXor1>(w.x);
+    w.y |= dpp_u<kQuadXor1>(w.y);
+    w.x |= dpp_u<kQuadXor2>(w.x);
+    w.y |= dpp_u<kQuadXor2>(w.y);
   }
-  __syncthreads();
+  const int W = BITS * grp + (BITS == 8 ? 2 * p : BITS == 4 ? (p & 2) : 0);
+  if (BITS == 8 || (BITS == 4 && (p & 1) == 0) || (BITS == 2 && p == 0))
+    *reinterpret_cast<uint2*>(tile + 1024 * (W >> 2) + 16 * r + 4 * (W & 3)) = w;
+}
 
-  // quantize: one task = one group of 32 channels of one row of K or V (fixed-order fp32); 512 tasks
-  for (int task = tid; task < 2 * kRows * 4; task += 256) {
-    const int w = task >> 8, row = (task >> 2) & 63, grp = task & 3;
-    float x[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) x[i] = __uint_as_float(static_cast<uint32_t>(s_rows[w][row][grp * 32 + i]) << 16);
-    float mn = x[0], mx = x[0];
-#pragma unroll
-    for (int i = 1; i < 32; ++i) {
-      mn = fminf(mn, x[i]);
-      mx = fmaxf(mx, x[i]);
-    }
-    if (a.row_wide) {   // the four groups of a row are the four lanes of a quad (task % 4 = lane % 4)
-      mn = fminf(mn, __shfl_xor(mn, 1));
-      mx = fmaxf(mx, __shfl_xor(mx, 1));
-      mn = fminf(mn, __shfl_xor(mn, 2));
-      mx = fmaxf(mx, __shfl_xor(mx, 2));
-    }
-    mn = mn + 0.0f;   // canonical +0
-    constexpr float Q = static_cast<float>((1 << BITS) - 1);
-    const _Float16 sh = static_cast<_Float16>((mx - mn) / Q);   // round to nearest even
-    const _Float16 mh = static_cast<_Float16>(mn);
-    const float s = static_cast<float>(sh), m = static_cast<float>(mh);
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      float t = rintf((x[i] - m) / s);
-      t = fminf(fmaxf(t, 0.0f), Q);
-      s_codes[w][row][grp * 32 + i] = (s == 0.0f) ? uint8_t(0) : static_cast<uint8_t>(t);
-    }
-    if (row < valid && !(a.v_only && w == 0)) {
-      int si, oi;
-      if (w == 0) {
-        si = 8 * row + grp;
-        oi = si + 4;
-      } else {
-        si = 32 * (row >> 2) + 8 * grp + (row & 3);
-        oi = si + 4;
-      }
-      uint16_t* meta = reinterpret_cast<uint16_t*>(a.arena + so[w * 2 + 1] + static_cast<int64_t>(blockIdx.x) * 1024);
-      meta[si] = __builtin_bit_cast(unsigned short, sh);
-      meta[oi] = __builtin_bit_cast(unsigned short, mh);
-    }
-  }
-  __syncthreads();
-
-  // emit the tile's data words in their physical order (coalesced 32-bit stores)
-  constexpr int kWords = kRows * kHeadDim * BITS / 32;      // 2048 / 1024 / 512
+// V codes go through LDS: s_vc[channel][token] bytes, 68 bytes per channel (four tokens of a channel are one word of a
+// lane, and both the writes and the reads spread over the banks).
+constexpr int kVcStride = 68;
+template <int BITS>
+__device__ __forceinline__ void store_v_words(const uint8_t* s_vc, uint8_t* tile) {
   constexpr int F = 16 / BITS;
+  const int L = threadIdx.x & 63, G = threadIdx.x >> 6;    // lane of the layout, channel group
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(s_vc + (32 * G + (L & 31)) * kVcStride + 32 * (L >> 5));
+  uint32_t w[BITS];
 #pragma unroll
-  for (int w = 0; w < 2; ++w) {
-    if (a.v_only && w == 0) continue;
-    uint32_t* dst = reinterpret_cast<uint32_t*>(a.arena + so[w * 2] +
-                                                static_cast<int64_t>(blockIdx.x) * (kRows * kHeadDim * BITS / 8));
-    for (int word = tid; word < kWords; word += 256) {
-      const int chunk = word >> 8, lane = (word >> 2) & 63, dd = word & 3;
-      const int W = 4 * chunk + dd;
-      const int grp = W / BITS, wl = W % BITS;
-      const int pair = wl >> 1, kw = wl & 1;
-      uint32_t out = 0;
+  for (int i = 0; i < BITS; ++i) w[i] = 0;
 #pragma unroll
-      for (int half = 0; half < 2; ++half)
+  for (int st = 0; st < 8; ++st) {         // the four tokens of a step: bytes 0, 1 -> halves of one word, 2, 3 -> the other
+    const uint32_t d = src[st];
+    w[2 * (st / F)] |= __builtin_amdgcn_perm(0u, d, 0x0C010C00u) << (BITS * (st % F));
+    w[2 * (st / F) + 1] |= __builtin_amdgcn_perm(0u, d, 0x0C030C02u) << (BITS * (st % F));
+  }
+  if constexpr (BITS == 2) {
+    *reinterpret_cast<uint2*>(tile + 1024 * (G >> 1) + 16 * L + 8 * (G & 1)) = make_uint2(w[0], w[1]);
+  } else {
 #pragma unroll
-        for (int f = 0; f < F; ++f) {
-          const int idx = 4 * (pair * F + f) + 2 * kw + half;      // position inside the group: 4*step + k
-          int r, c;
-          if (w == 0) {
-            r = lane;
-            c = 32 * grp + idx;
-          } else {
-            r = 32 * (lane >> 5) + idx;
-            c = 32 * grp + (lane & 31);
-          }
-          out |= static_cast<uint32_t>(s_codes[w][r][c]) << (16 * half + BITS * f);
-        }
-      dst[word] = out;
+    for (int q = 0; q < BITS / 4; ++q)
+      *reinterpret_cast<uint4*>(tile + 1024 * (G * (BITS / 4) + q) + 16 * L) =
+          make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+  }
+}
+
+// One workgroup = one tile of 64 kept rows of any tier, K and V (V_ONLY: V, K of a channel-wise cache is packed by
+// pack_k_mixed_kernel); rows past the segment's last are zero rows, so a tile is always written whole.  A wavefront gathers
+// 16 rows, 16 lanes a row (whole 256-byte rows per load), a lane the same 8 channels of four consecutive tokens, which is
+// what a step of the V layout takes; codes are made in registers and only V passes through LDS, as bytes.  Bound: HBM (the
+// gather); 128 items x 20K tokens, mostly 2- and 4-bit rows: 298 us in three launches and 24 us for clearing the arena
+// -> 219 us (1.2 GB, 5.5 TB/s); a 128K-token layer 37 + 5 -> 21 us.
+template <bool V_ONLY>
+__global__ __launch_bounds__(256) void pack_tile_kernel(PackArgs a) {
+  __shared__ __align__(16) uint8_t s_buf[kTile64 * (kHeadDim + 8) * 2];   // V codes, or bf16 V rows of the 16-bit tier
+  __shared__ __align__(16) uint16_t s_km[kTile64][8];                     // K metadata
+  const int item = blockIdx.y;
+  const TileOf t(a, item, blockIdx.x);
+  if (t.ti == 4) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane >> 4, c16 = lane & 15, grp = c16 >> 2, p = c16 & 3;
+  const int row0 = 16 * wave + 4 * lr;     // this lane's rows row0 .. row0 + 3 of the tile
+  const int valid = min(kTile64, t.n - t.tile * kTile64);
+  const int32_t* idx = a.tier_idx + a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kTile64;
+  const int64_t item_row = a.item_row_off[item];
+  uint4 kq[4], vq[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    kq[i] = vq[i] = make_uint4(0, 0, 0, 0);
+    if (row0 + i < valid) {
+      const int64_t src = (item_row + idx[row0 + i]) * kHeadDim + c16 * 8;
+      if constexpr (!V_ONLY) kq[i] = *reinterpret_cast<const uint4*>(a.K + src);
+      vq[i] = *reinterpret_cast<const uint4*>(a.V + src);
     }
+  }
+  const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + t.ti) * 4;
+  const int bits = 16 >> t.ti;
+  uint8_t* kd = a.arena + so[0] + static_cast<int64_t>(t.tile) * (kTile64 * kHeadDim / 8) * bits;
+  uint8_t* vd = a.arena + so[2] + static_cast<int64_t>(t.tile) * (kTile64 * kHeadDim / 8) * bits;
+  if (t.ti == 0) {
+    if constexpr (!V_ONLY) {               // bf16 rows, row-major
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        *reinterpret_cast<uint4*>(kd + (row0 + i) * (kHeadDim * 2) + c16 * 16) = kq[i];
+        *reinterpret_cast<uint4*>(vd + (row0 + i) * (kHeadDim * 2) + c16 * 16) = vq[i];
+      }
+    } else {
+      // 16-bit V rows with the lane assignment of the quantized V tiers: lane 32 (r / 32) + c % 32 holds channel c for
+      // the 32 tokens of its tile half, eight tokens per 16-byte unit; unit u = 4 (c / 32) + (r % 32) / 8 sits at byte
+      // 1024 u + 16 lane of the 16 KiB tile
+      constexpr int kStride = kHeadDim + 8;
+      uint16_t* s_rows = reinterpret_cast<uint16_t*>(s_buf);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(s_rows + (row0 + i) * kStride + c16 * 8) = vq[i];
+      __syncthreads();
+      uint32_t* dst = reinterpret_cast<uint32_t*>(vd);
+      for (int word = tid; word < kTile64 * kHeadDim / 2; word += 256) {
+        const int u = word >> 8, l = (word >> 2) & 63, t8 = 2 * (word & 3);
+        const int r = 32 * (l >> 5) + 8 * (u & 3) + t8, c = 32 * (u >> 2) + (l & 31);
+        dst[word] = s_rows[r * kStride + c] | (static_cast<uint32_t>(s_rows[(r + 1) * kStride + c]) << 16);
+      }
+    }
+    return;
+  }
+  uint8_t* km = a.arena + so[1] + static_cast<int64_t>(t.tile) * 1024;
+  uint8_t* vm = a.arena + so[3] + static_cast<int64_t>(t.tile) * 1024;
+  const auto quantize = [&](auto bits_c) __attribute__((always_inline)) {
+    constexpr int BITS = decltype(bits_c)::value;
+    if constexpr (!V_ONLY) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        Quant g;
+        float c[8];
+        quantize_row<BITS>(kq[i], a.row_wide, g, c);
+        store_k_words<BITS>(c, kd, row0 + i, grp, p);
+        if (p == 0) {
+          s_km[row0 + i][grp] = __builtin_bit_cast(unsigned short, g.sh);
+          s_km[row0 + i][4 + grp] = __builtin_bit_cast(unsigned short, g.mh);
+        }
+      }
+    }
+    uint32_t sc[4], of[4], packed[8];      // packed: the four tokens' codes of a channel, one byte each
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      Quant g;
+      float c[8];
+      quantize_row<BITS>(vq[i], a.row_wide, g, c);
+      sc[i] = __builtin_bit_cast(unsigned short, g.sh);
+      of[i] = __builtin_bit_cast(unsigned short, g.mh);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t u = static_cast<uint32_t>(c[j]);
+        packed[j] = i == 0 ? u : packed[j] | (u << (8 * i));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) *reinterpret_cast<uint32_t*>(s_buf + (c16 * 8 + j) * kVcStride + row0) = packed[j];
+    if (p == 0)                            // block row0 / 4 of the tile, group grp
+      *reinterpret_cast<uint4*>(vm + 16 * row0 + 16 * grp) =
+          make_uint4(sc[0] | (sc[1] << 16), sc[2] | (sc[3] << 16), of[0] | (of[1] << 16), of[2] | (of[3] << 16));
+    __syncthreads();
+    store_v_words<BITS>(s_buf, vd);
+  };
+  if (t.ti == 1) quantize(std::integral_constant<int, 8>{});
+  else if (t.ti == 2) quantize(std::integral_constant<int, 4>{});
+  else quantize(std::integral_constant<int, 2>{});
+  if constexpr (!V_ONLY) {
+    if (tid < kTile64) *reinterpret_cast<uint4*>(km + 16 * tid) = *reinterpret_cast<const uint4*>(&s_km[tid][0]);
   }
 }
 
 // ---- mixed mode -------------------------------------------------------------------------------------------------
-// 16-bit V rows as 64-token tiles with the lane assignment of the quantized V tiers: lane 32 (r / 32) + c % 32 holds
-// channel c for the 32 tokens of its tile half, eight tokens per 16-byte unit; unit u = 4 (c / 32) + (r % 32) / 8
-// sits at byte 1024 u + 16 lane of the 16 KiB tile.
-__global__ __launch_bounds__(256) void pack_v16_tile64_kernel(PackArgs a) {
-  constexpr int kRows = 64;
-  constexpr int kRowStride = kHeadDim + 8;
-  __shared__ __align__(16) uint16_t s_rows[kRows][kRowStride];
-  const int item = blockIdx.y;
-  const int n = a.counts[item * 4 + a.ti];
-  const int r0 = blockIdx.x * kRows;
-  if (r0 >= n) return;
-  const int valid = min(kRows, n - r0);
-  const int tid = threadIdx.x;
-  const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + a.ti) * 4;
-  {
-    const int row = tid >> 2, part = tid & 3;
-    uint4 v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = make_uint4(0, 0, 0, 0);
-    if (row < valid) {
-      const int pos = a.tier_idx[a.idx_base[item * 4 + a.ti] + r0 + row];
-      const uint4* p = reinterpret_cast<const uint4*>(a.V + (a.item_row_off[item] + pos) * kHeadDim + part * 32);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = p[i];
-    }
-    uint4* d = reinterpret_cast<uint4*>(&s_rows[row][part * 32]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) d[i] = v[i];
-  }
-  __syncthreads();
-  uint32_t* dst = reinterpret_cast<uint32_t*>(a.arena + so[2] + static_cast<int64_t>(blockIdx.x) * (kRows * kHeadDim * 2));
-  for (int word = tid; word < kRows * kHeadDim / 2; word += 256) {
-    const int u = word >> 8, lane = (word >> 2) & 63, t8 = 2 * (word & 3);
-    const int r = 32 * (lane >> 5) + 8 * (u & 3) + t8, c = 32 * (u >> 2) + (lane & 31);
-    dst[word] = s_rows[r][c] | (static_cast<uint32_t>(s_rows[r + 1][c]) << 16);
-  }
-}
-
 // One scale per channel over all retained tokens (App. B): the channel's minimum and maximum over the kept rows of
 // all four tiers of the item.  k_range starts at (0xFFFFFFFF, 0).
 __global__ __launch_bounds__(256) void k_channel_range_kernel(PackArgs a) {
@@ -372,81 +457,86 @@ __global__ __launch_bounds__(256) void k_channel_range_kernel(PackArgs a) {
 // Metadata: per token group G and quantized step sq (4 slots) 4 fp16 scales then 4 fp16 offsets at fp16 index
 // 8 (G n_qsteps + sq).
 __global__ __launch_bounds__(256) void pack_k_mixed_kernel(PackArgs a) {
-  constexpr int kRows = 64;
+  constexpr int kRows = kTile64;
   constexpr int kRowStride = kHeadDim + 8;
-  __shared__ __align__(16) uint16_t s_rows[kRows][kRowStride];
-  __shared__ uint16_t s_codes[kRows][kHeadDim + 2];
+  __shared__ __align__(16) uint16_t s_rows[kRows][kRowStride];   // bf16 rows, then the codes in their place
   __shared__ uint16_t s_sc[2][kHeadDim], s_of[2][kHeadDim];
   __shared__ ItemK s_ik;
   const int item = blockIdx.y;
-  const int n = a.counts[item * 4 + a.ti];
-  const int r0 = blockIdx.x * kRows;
-  if (r0 >= n) return;
-  const int valid = min(kRows, n - r0);
+  const TileOf t(a, item, blockIdx.x);
+  if (t.ti == 4) return;
+  const int valid = min(kRows, t.n - t.tile * kRows);
   const int tid = threadIdx.x;
-  const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + a.ti) * 4;
-  for (int i = tid; i < static_cast<int>(sizeof(ItemK) / 4); i += 256)
-    reinterpret_cast<uint32_t*>(&s_ik)[i] = reinterpret_cast<const uint32_t*>(a.items_k + item)[i];
+  const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + t.ti) * 4;
   {
-    const int row = tid >> 2, part = tid & 3;
+    const int lane = tid & 63, c16 = lane & 15, row0 = 16 * (tid >> 6) + 4 * (lane >> 4);
+    const int32_t* idx = a.tier_idx + a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kRows;
+    const int64_t item_row = a.item_row_off[item];
     uint4 v[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = make_uint4(0, 0, 0, 0);
-    if (row < valid) {
-      const int pos = a.tier_idx[a.idx_base[item * 4 + a.ti] + r0 + row];
-      const uint4* p = reinterpret_cast<const uint4*>(a.K + (a.item_row_off[item] + pos) * kHeadDim + part * 32);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = p[i];
+    for (int i = 0; i < 4; ++i) {
+      v[i] = make_uint4(0, 0, 0, 0);
+      if (row0 + i < valid) v[i] = *reinterpret_cast<const uint4*>(a.K + (item_row + idx[row0 + i]) * kHeadDim + c16 * 8);
     }
-    uint4* d = reinterpret_cast<uint4*>(&s_rows[row][part * 32]);
+    for (int i = tid; i < static_cast<int>(sizeof(ItemK) / 4); i += 256)
+      reinterpret_cast<uint32_t*>(&s_ik)[i] = reinterpret_cast<const uint32_t*>(a.items_k + item)[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) d[i] = v[i];
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(&s_rows[row0 + i][c16 * 8]) = v[i];
   }
   __syncthreads();
-  {  // one thread = one (token group, channel)
+  {  // one thread = one (token group, channel), its 32 values in registers
     const int G = tid >> 7, c = tid & 127;
     const int rb = kKTokenGroup * G, vg = min(max(valid - rb, 0), kKTokenGroup);
     const int b = a.bits_ch[item * kHeadDim + c];
     uint16_t sc = 0, of = 0;
-    if (b == 16) {
-      for (int r = 0; r < kKTokenGroup; ++r) s_codes[rb + r][c] = s_rows[rb + r][c];   // rows beyond `valid` are zero
-    } else if ((b == 8 || b == 4 || b == 2) && vg > 0) {
+    const bool quantized = (b == 8 || b == 4 || b == 2) && vg > 0;
+    if (quantized) {
+      float x[kKTokenGroup];
+#pragma unroll
+      for (int r = 0; r < kKTokenGroup; ++r) x[r] = __uint_as_float(static_cast<uint32_t>(s_rows[rb + r][c]) << 16);
       float mn, mx;
       if (a.k_range) {   // the range of the whole unit
         mn = ordered_to_float(a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2]);
         mx = ordered_to_float(a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2 + 1]);
       } else {
-        mn = __uint_as_float(static_cast<uint32_t>(s_rows[rb][c]) << 16);
-        mx = mn;
-        for (int r = 1; r < vg; ++r) {
-          const float x = __uint_as_float(static_cast<uint32_t>(s_rows[rb + r][c]) << 16);
-          mn = fminf(mn, x);
-          mx = fmaxf(mx, x);
+        mn = x[0];
+        mx = x[0];
+#pragma unroll
+        for (int r = 1; r < kKTokenGroup; ++r) {
+          mn = r < vg ? fminf(mn, x[r]) : mn;
+          mx = r < vg ? fmaxf(mx, x[r]) : mx;
         }
       }
-      mn = mn + 0.0f;
-      const float Q = static_cast<float>((1 << b) - 1);
-      const _Float16 sh = static_cast<_Float16>((mx - mn) / Q);
-      const _Float16 mh = static_cast<_Float16>(mn);
-      const float s = static_cast<float>(sh), m = static_cast<float>(mh);
-      for (int r = 0; r < kKTokenGroup; ++r) {
-        const float x = __uint_as_float(static_cast<uint32_t>(s_rows[rb + r][c]) << 16);
-        float t = rintf((x - m) / s);
-        t = fminf(fmaxf(t, 0.0f), Q);
-        s_codes[rb + r][c] = (s == 0.0f || r >= vg) ? uint16_t(0) : static_cast<uint16_t>(t);
-      }
-      sc = __builtin_bit_cast(unsigned short, sh);
-      of = __builtin_bit_cast(unsigned short, mh);
-    } else {
-      for (int r = 0; r < kKTokenGroup; ++r) s_codes[rb + r][c] = 0;
+      Quant g;
+      const auto run = [&](auto bits_c) __attribute__((always_inline)) {
+        constexpr int BITS = decltype(bits_c)::value;
+        g.set<BITS>(mn, mx);
+        if (g.finite) {
+#pragma unroll
+          for (int r = 0; r < kKTokenGroup; ++r)
+            s_rows[rb + r][c] = r < vg ? static_cast<uint16_t>(g.code<BITS, false>(x[r])) : uint16_t(0);
+        } else {
+#pragma unroll 1
+          for (int r = 0; r < kKTokenGroup; ++r) {
+            const float xr = __uint_as_float(static_cast<uint32_t>(s_rows[rb + r][c]) << 16);
+            s_rows[rb + r][c] = r < vg ? static_cast<uint16_t>(g.code<BITS, true>(xr)) : uint16_t(0);
+          }
+        }
+      };
+      if (b == 8) run(std::integral_constant<int, 8>{});
+      else if (b == 4) run(std::integral_constant<int, 4>{});
+      else run(std::integral_constant<int, 2>{});
+      sc = __builtin_bit_cast(unsigned short, g.sh);
+      of = __builtin_bit_cast(unsigned short, g.mh);
     }
+    // (16-bit channels keep their bf16 values, rows past the last are zero; dropped channels are in no word)
     s_sc[G][c] = sc;
     s_of[G][c] = of;
   }
   __syncthreads();
 
   const int nwp = s_ik.n_words_padded, full = nwp & ~3;
-  uint32_t* dst = reinterpret_cast<uint32_t*>(a.arena + so[0] + static_cast<int64_t>(blockIdx.x) * s_ik.kt_bytes);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(a.arena + so[0] + static_cast<int64_t>(t.tile) * s_ik.kt_bytes);
   for (int idx = tid; idx < kRows * nwp; idx += 256) {
     int W, r;
     if (idx < kRows * full) {
@@ -458,39 +548,49 @@ __global__ __launch_bounds__(256) void pack_k_mixed_kernel(PackArgs a) {
     }
     uint32_t out = 0;
     if (W < s_ik.n_words) {
-      int t = 0;
-      while (W >= s_ik.word_end[t]) ++t;
-      const int b = 16 >> t, per_word = 32 / b;
-      const int lw = W - (t > 0 ? s_ik.word_end[t - 1] : 0);
-      const int16_t* sl = s_ik.slot_ch + s_ik.slot_base[t] + lw * per_word;
+      int tier = 0;
+      while (W >= s_ik.word_end[tier]) ++tier;
+      const int b = 16 >> tier, per_word = 32 / b;
+      const int lw = W - (tier > 0 ? s_ik.word_end[tier - 1] : 0);
+      const int16_t* sl = s_ik.slot_ch + s_ik.slot_base[tier] + lw * per_word;
       for (int jj = 0; jj < per_word; ++jj) {
         const int c = sl[jj];
         if (c < 0) continue;
         const int k = jj >> 2, e = jj & 3;
         const int bit = b == 16 ? 16 * jj : 16 * (e & 1) + b * (e >> 1) + 2 * b * k;
-        out |= static_cast<uint32_t>(s_codes[r][c]) << bit;
+        out |= static_cast<uint32_t>(s_rows[r][c]) << bit;
       }
     }
     dst[idx] = out;
   }
-  const int nqs = s_ik.n_qsteps;
+  // metadata; the segment's last tile also clears the bytes up to the next segment's alignment
+  const int nqs = s_ik.n_qsteps, n_tiles = (t.n + kRows - 1) / kRows;
+  const bool last = t.tile == n_tiles - 1;
   if (a.k_range) {   // one record for the whole segment, written by its first tile
-    if (blockIdx.x == 0) {
-      uint16_t* meta1 = reinterpret_cast<uint16_t*>(a.arena + so[1]);
-      for (int idx = tid; idx < 8 * nqs; idx += 256) {
-        const int sq = idx >> 3, e = idx & 3, is_off = (idx >> 2) & 1;
-        const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * sq + e];
-        meta1[idx] = c >= 0 ? (is_off ? s_of[0][c] : s_sc[0][c]) : uint16_t(0);
+    uint16_t* meta1 = reinterpret_cast<uint16_t*>(a.arena + so[1]);
+    const int words = 8 * nqs, padded = (2 * words + kSegAlign - 1) / kSegAlign * (kSegAlign / 2);
+    if (t.tile == 0)
+      for (int idx = tid; idx < padded; idx += 256) {
+        uint16_t v = 0;
+        if (idx < words) {
+          const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * (idx >> 3) + (idx & 3)];
+          if (c >= 0) v = (idx >> 2) & 1 ? s_of[0][c] : s_sc[0][c];
+        }
+        meta1[idx] = v;
       }
-    }
     return;
   }
-  uint16_t* meta = reinterpret_cast<uint16_t*>(a.arena + so[1] + static_cast<int64_t>(blockIdx.x) * s_ik.km_bytes);
-  for (int idx = tid; idx < 16 * nqs; idx += 256) {
-    const int G = idx / (8 * nqs), rem = idx - G * 8 * nqs;
-    const int sq = rem >> 3, e = rem & 3, is_off = (rem >> 2) & 1;
-    const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * sq + e];
-    meta[idx] = c >= 0 ? (is_off ? s_of[G][c] : s_sc[G][c]) : uint16_t(0);
+  uint16_t* meta = reinterpret_cast<uint16_t*>(a.arena + so[1] + static_cast<int64_t>(t.tile) * s_ik.km_bytes);
+  const int64_t end = static_cast<int64_t>(n_tiles) * s_ik.km_bytes;
+  const int pad = last ? static_cast<int>((kSegAlign - end % kSegAlign) % kSegAlign) / 2 : 0;
+  for (int idx = tid; idx < 16 * nqs + pad; idx += 256) {
+    uint16_t v = 0;
+    if (idx < 16 * nqs) {
+      const int G = idx / (8 * nqs), rem = idx - G * 8 * nqs;
+      const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * (rem >> 3) + (rem & 3)];
+      if (c >= 0) v = (rem >> 2) & 1 ? s_of[G][c] : s_sc[G][c];
+    }
+    meta[idx] = v;
   }
 }
 
@@ -517,37 +617,24 @@ hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off,
   return hipGetLastError();
 }
 
+// max_tiles: the most 64-row tiles any item has over its tiers
 hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx,
                              const int64_t* idx_base, const int32_t* counts, const int64_t* seg_off,
                              const int64_t* item_row_off, uint8_t* arena, int n_items,
-                             const int32_t max_count[4], const ItemK* items_k, const uint8_t* bits_ch,
+                             int max_tiles, const ItemK* items_k, const uint8_t* bits_ch,
                              uint32_t* k_range, int row_wide, hipStream_t st) {
-  const bool mixed = items_k != nullptr;
-  if (k_range) {   // k_range must hold (0xFFFFFFFF, 0) pairs on entry
-    PackArgs a{K, V, tier_idx, idx_base, counts, seg_off, item_row_off, arena, 0, 1, items_k, bits_ch, k_range,
-               row_wide};
-    hipLaunchKernelGGL(k_channel_range_kernel, dim3(64, n_items), dim3(256), 0, st, a);
+  if (n_items == 0 || max_tiles == 0) return hipSuccess;
+  const PackArgs a{K, V, tier_idx, idx_base, counts, seg_off, item_row_off, arena, items_k, bits_ch, k_range, row_wide};
+  const dim3 grid(max_tiles, n_items), block(256);
+  if (items_k == nullptr) {
+    hipLaunchKernelGGL(pack_tile_kernel<false>, grid, block, 0, st, a);
+    return hipGetLastError();
   }
-  for (int ti = 0; ti < 4; ++ti) {
-    if (max_count[ti] == 0) continue;
-    PackArgs a{K, V, tier_idx, idx_base, counts, seg_off, item_row_off, arena, ti, mixed ? 1 : 0, items_k, bits_ch,
-               k_range, row_wide};
-    dim3 grid64((max_count[ti] + 63) / 64, n_items);   // 64 rows per workgroup in every kernel below
-    dim3 block(256);
-    if (mixed) hipLaunchKernelGGL(pack_k_mixed_kernel, grid64, block, 0, st, a);
-    switch (ti) {
-      case 0:
-        if (mixed) hipLaunchKernelGGL(pack_v16_tile64_kernel, grid64, block, 0, st, a);
-        else hipLaunchKernelGGL(copy_rows_kernel, grid64, block, 0, st, a);
-        break;
-      case 1: hipLaunchKernelGGL(quant_pack_tile64_kernel<8>, grid64, block, 0, st, a); break;
-      case 2: hipLaunchKernelGGL(quant_pack_tile64_kernel<4>, grid64, block, 0, st, a); break;
-      default: hipLaunchKernelGGL(quant_pack_tile64_kernel<2>, grid64, block, 0, st, a); break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  // k_range must hold (0xFFFFFFFF, 0) pairs on entry
+  if (k_range) hipLaunchKernelGGL(k_channel_range_kernel, dim3(64, n_items), block, 0, st, a);
+  hipLaunchKernelGGL(pack_k_mixed_kernel, grid, block, 0, st, a);
+  hipLaunchKernelGGL(pack_tile_kernel<true>, grid, block, 0, st, a);
+  return hipGetLastError();
 }
 
 int partition_block() { return kPartBlock; }

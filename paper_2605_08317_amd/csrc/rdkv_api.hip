@@ -23,7 +23,7 @@ hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off,
 hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx,
                              const int64_t* idx_base, const int32_t* counts, const int64_t* seg_off,
                              const int64_t* item_row_off, uint8_t* arena, int n_items,
-                             const int32_t max_count[4], const ItemK* items_k, const uint8_t* bits_ch,
+                             int max_tiles, const ItemK* items_k, const uint8_t* bits_ch,
                              uint32_t* k_range, int row_wide, hipStream_t st);
 int partition_block();
 int weights_key_tile();
@@ -657,14 +657,16 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // ---- plan: kept-position lists, arena segments, split schedule -------------------------
   std::vector<int64_t> idx_base(n * 4, 0);
   int64_t kept = 0, cur = 0, stored = 0;
-  int32_t max_count[4] = {0, 0, 0, 0};
+  int max_tiles = 0;
   for (int64_t i = 0; i < n; ++i) {
+    int tiles = 0;
     for (int ti = 0; ti < 4; ++ti) {
       const int bits = pack_tier_bits(ti);
       const int64_t cnt = c->counts[i * 4 + ti];
       idx_base[i * 4 + ti] = kept;
       kept += cnt;
-      max_count[ti] = std::max<int32_t>(max_count[ti], static_cast<int32_t>(cnt));
+      tiles += static_cast<int>((cnt + kTile64 - 1) / kTile64);
+      max_tiles = std::max(max_tiles, tiles);
       const int64_t npad = round_up(cnt, kTile64);
       int64_t sizes[4] = {npad * tier_row_bytes(bits), npad * tier_meta_bytes(bits),
                           npad * tier_row_bytes(bits), npad * tier_meta_bytes(bits)};
@@ -928,7 +930,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     c->index_bytes = total - c->arena_bytes;     // everything else in the block
     if (n > 0) {
       // nothing below waits: tables are copied out of pinned staging memory, and the host vectors may go
-      PACK_HIP(hipMemsetAsync(c->d_block, 0, o_idx, st));     // arena (padding rows read as zeros), tail state, counters
+      // (the pack kernels write every byte of the arena)
+      PACK_HIP(hipMemsetAsync(c->d_block + o_state, 0, o_idx - o_state, st));     // tail state, counters
       PACK_HIP(upload(d_counts, c->counts.data(), n * 4 * sizeof(int32_t), st));
       std::vector<int64_t> plan(idx_base);
       plan.resize(n1 * 4, 0);
@@ -971,7 +974,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
                                    static_cast<int>(n), it.max_T, st));
       PACK_HIP(launch_quant_pack(static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), c->d_tier_idx,
                                  d_idx_base, d_counts, d_seg_off, d_tok_off, c->d_arena, static_cast<int>(n),
-                                 max_count, mixed ? c->d_items_k : nullptr, mixed ? c->d_bits_ch : nullptr, d_krange,
+                                 max_tiles, mixed ? c->d_items_k : nullptr, mixed ? c->d_bits_ch : nullptr, d_krange,
                                  c->group_size == kHeadDim ? 1 : 0, st));
     }
   }

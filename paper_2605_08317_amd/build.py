@@ -18,6 +18,7 @@ SOURCES = [
     ("rdkv_api.hip", "rdkv_api.o", []),
     ("decode_rows_mfma.hip", "decode_rows_mfma.o", []),
     ("decode_kernels.hip", "decode_kernels.o", []),
+    ("copy_kernels.hip", "copy_kernels.o", []),
     ("pack_kernels.hip", "pack_kernels.o", []),
     ("allocate_kernels.hip", "allocate_kernels.o", []),
     ("weights_kernels.hip", "weights_kernels.o", []),

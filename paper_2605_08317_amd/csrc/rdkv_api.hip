@@ -6,9 +6,11 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <initializer_list>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <utility>
 
 #include "decode_merge.h"
@@ -151,66 +153,164 @@ struct Temp {
   }
 };
 
-// Host-to-device copies of small tables without waiting for them: the source is copied into a ring of pinned host
-// memory (one per device), the copy is enqueued from there, and an event marks when the ring bytes may be reused.
-// A table larger than the ring is copied from the caller's memory and the stream is synchronised.
+// Host tables of a call, and the counts it reads back, travel through a ring of pinned memory (one per device) that
+// kernels read and write directly (launch_copy): no copy of the runtime, no event, no wait for the stream.  A region starts
+// with completion words that the kernel sets to the region's number when it is done with it; the ring's bytes are reused
+// once it has.
 constexpr int kMaxDevices = 64;
+constexpr size_t kStageHead = kStageWords * sizeof(uint32_t);
+
+struct StageRegion {
+  uint8_t* data = nullptr;        // pinned: what the host fills (or reads)
+  uint32_t* words = nullptr;
+  uint32_t seq = 0;
+  int blocks = 1;                 // workgroups that announce themselves
+  void* own = nullptr;            // not of the ring: an allocation of its own, given back by release()
+  bool done() const {
+    for (int i = 0; i < blocks; ++i)
+      if (__atomic_load_n(words + i, __ATOMIC_ACQUIRE) != seq) return false;
+    return true;
+  }
+  void mark_done() const {        // no kernel will
+    for (int i = 0; i < blocks; ++i) __atomic_store_n(words + i, seq, __ATOMIC_RELEASE);
+  }
+};
+
+// Spins until the region's kernel is done.  The stream is asked now and then, so that a failed launch or a fault ends the
+// wait.
+hipError_t stage_wait(const StageRegion& r, hipStream_t st) {
+  for (uint32_t spins = 1;; ++spins) {
+    if (r.done()) return hipSuccess;
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+    if ((spins & 0x3FFF) == 0) {
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipErrorNotReady) continue;
+      if (e == hipSuccess && r.done()) return hipSuccess;
+      r.mark_done();
+      return e != hipSuccess ? e : hipErrorUnknown;
+    }
+  }
+}
+
 class Staging {
-  struct Region { size_t begin, end; hipEvent_t ev; };
+  struct Live { size_t begin, end; StageRegion r; bool held; };
   std::mutex mu_;
   uint8_t* base_ = nullptr;
-  size_t cap_ = 0, head_ = 0;
-  std::vector<Region> live_;       // ring bytes whose copy may not have run yet
-  std::vector<hipEvent_t> pool_;
+  size_t head_ = 0;
+  uint32_t seq_ = 0;
+  std::deque<Live> live_;          // regions whose kernel may not have run yet, or that the host still reads
   static constexpr size_t kBytes = static_cast<size_t>(2) << 20;
 
  public:
-  hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t st) {
-    if (bytes == 0) return hipSuccess;
-    std::lock_guard<std::mutex> lk(mu_);
+  // A region of `bytes`; `held`: the host reads it back and calls release().
+  hipError_t acquire(size_t bytes, bool held, StageRegion* out) {
+    std::unique_lock<std::mutex> lk(mu_);
     if (!base_) {
       void* p = nullptr;
-      if (hipHostMalloc(&p, kBytes, hipHostMallocDefault) == hipSuccess) { base_ = static_cast<uint8_t*>(p); cap_ = kBytes; }
+      const hipError_t e = hipHostMalloc(&p, kBytes, hipHostMallocDefault);
+      if (e != hipSuccess) return e;
+      base_ = static_cast<uint8_t*>(p);
     }
-    const size_t need = (bytes + 255) / 256 * 256;
-    if (!base_ || need > cap_ / 2) {
-      hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
-      return e != hipSuccess ? e : hipStreamSynchronize(st);
-    }
-    if (head_ + need > cap_) head_ = 0;      // wrap: the bytes up to the end of the ring are skipped
-    for (size_t k = 0; k < live_.size();) {   // copies still reading the bytes about to be overwritten
-      if (live_[k].begin < head_ + need && live_[k].end > head_) {
-        (void)hipEventSynchronize(live_[k].ev);
-        pool_.push_back(live_[k].ev);
+    const size_t need = (kStageHead + bytes + 255) / 256 * 256;
+    StageRegion r;
+    r.seq = ++seq_ ? seq_ : ++seq_;
+    // 16 KB per workgroup and load round; a handful of them fill the link
+    r.blocks = static_cast<int>(std::min<size_t>(kStageWords, std::max<size_t>(1, bytes >> 15)));
+    uint8_t* p = nullptr;
+    if (need > kBytes / 2) {        // larger than the ring: memory of its own
+      const hipError_t e = hipHostMalloc(&r.own, need, hipHostMallocDefault);
+      if (e != hipSuccess) return e;
+      p = static_cast<uint8_t*>(r.own);
+    } else {
+      if (head_ + need > kBytes) head_ = 0;     // wrap: the bytes up to the end of the ring are skipped
+      for (size_t k = 0; k < live_.size();) {   // regions on the bytes about to be overwritten
+        const Live& l = live_[k];
+        if (l.begin >= head_ + need || l.end <= head_) { ++k; continue; }
+        if (l.held && !l.r.done()) {            // another thread waits for it: go on behind it
+          head_ = l.end + need > kBytes ? 0 : l.end;
+          k = 0;
+          continue;
+        }
+        wait_for(l.r);
+        if (l.held) {                           // read back within microseconds by the thread that holds it
+          lk.unlock();
+          std::this_thread::yield();
+          lk.lock();
+          k = 0;
+          continue;
+        }
         live_.erase(live_.begin() + static_cast<std::ptrdiff_t>(k));
-      } else {
-        ++k;
       }
+      while (!live_.empty() && !live_.front().held && live_.front().r.done()) live_.pop_front();
+      p = base_ + head_;
     }
-    uint8_t* p = base_ + head_;
-    std::memcpy(p, src, bytes);
-    hipError_t e = hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return e;
-    hipEvent_t ev = nullptr;
-    if (!pool_.empty()) { ev = pool_.back(); pool_.pop_back(); }
-    else if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return hipStreamSynchronize(st);
-    if ((e = hipEventRecord(ev, st)) != hipSuccess) { pool_.push_back(ev); return hipStreamSynchronize(st); }
-    live_.push_back(Region{head_, head_ + need, ev});
-    head_ += need;
+    r.words = reinterpret_cast<uint32_t*>(p);
+    r.data = p + kStageHead;
+    for (int i = 0; i < kStageWords; ++i) __atomic_store_n(r.words + i, 0u, __ATOMIC_RELAXED);
+    if (!r.own) {
+      live_.push_back(Live{head_, head_ + need, r, held});
+      head_ += need;
+    }
+    *out = r;
     return hipSuccess;
+  }
+  // The host is done with a held region.
+  void release(const StageRegion& r) {
+    std::lock_guard<std::mutex> lk(mu_);
+    for (Live& l : live_)
+      if (l.r.words == r.words && l.r.seq == r.seq) l.held = false;
+  }
+
+ private:
+  static void wait_for(const StageRegion& r) {
+    for (uint32_t spins = 1; !r.done(); ++spins) {
+#if defined(__x86_64__)
+      __builtin_ia32_pause();
+#endif
+      if ((spins & 0xFFFFFF) == 0 && hipDeviceSynchronize() != hipSuccess) return;   // the device is lost
+    }
   }
 };
 Staging g_staging[kMaxDevices];
 
-hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t st) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+hipError_t stage_acquire(size_t bytes, bool held, StageRegion* out, int* device) {
+  hipError_t e = hipGetDevice(device);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) {
-    e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
-    return e != hipSuccess ? e : hipStreamSynchronize(st);
+  if (*device < 0 || *device >= kMaxDevices) return hipErrorInvalidDevice;
+  return g_staging[*device].acquire(bytes, held, out);
+}
+
+// Launches a copy to or from a region.  `last`: the region's only launch and not read by the host; memory that is not of
+// the ring is given back then (after the kernel; the ring looks after itself).
+hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_t st) {
+  a.host_blocks = r.blocks;
+  a.words = r.words;
+  a.seq = r.seq;
+  hipError_t e = launch_copy(a, st);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (e == hipSuccess && !r.own) e = hipStreamIsCapturing(st, &cap);
+  // a captured copy reads the ring at its replay, if ever: nothing to wait for before the bytes are used again
+  if (e != hipSuccess || cap != hipStreamCaptureStatusNone) r.mark_done();
+  if (last && r.own) {
+    if (e == hipSuccess) e = stage_wait(r, st);
+    (void)hipHostFree(r.own);
   }
-  return g_staging[dev].upload(dst, src, bytes, st);
+  return e;
+}
+
+// One table to the device; nothing waits (a table larger than half the ring aside).
+hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t st) {
+  if (bytes == 0) return hipSuccess;
+  StageRegion r;
+  int dev = 0;
+  hipError_t e = stage_acquire(bytes, false, &r, &dev);
+  if (e != hipSuccess) return e;
+  std::memcpy(r.data, src, bytes);
+  CopyArgs a{};
+  a.add(r.data, dst, static_cast<int64_t>(bytes), true);
+  return stage_launch(a, r, true, st);
 }
 
 // Geometry of a ragged batch: one entry per item (sequence-major, head-minor).
@@ -398,17 +498,34 @@ void drop_workspaces(rdkv_cache* c) {
 // chunks of an item share an L2 (which then also holds the partials their merge reads); only speed depends on it.
 void order_chunks(std::vector<Chunk>::iterator first, std::vector<Chunk>::iterator last, int64_t n_items) {
   const int64_t count = last - first;
-  std::stable_sort(first, last, [](const Chunk& x, const Chunk& y) {
-    if (x.tier != y.tier) return x.tier < y.tier;
-    return static_cast<int64_t>(x.rows) * x.tier > static_cast<int64_t>(y.rows) * y.tier;
-  });
-  if (count > 1024 || n_items <= 1) return;
-  std::vector<std::vector<Chunk>> by_item(static_cast<size_t>(n_items));
-  for (auto it = first; it != last; ++it) by_item[it->item].push_back(*it);
-  auto out = first;
-  for (size_t k = 0; out != last; ++k)
-    for (int64_t i = 0; i < n_items; ++i)
-      if (k < by_item[i].size()) *out++ = by_item[i][k];
+  if (count < 2) return;
+  // (tier, size) in one key and the position behind it: a stable order without moving chunks about
+  using Key = std::pair<uint64_t, int32_t>;
+  auto key_of = [&](int64_t k) {
+    const Chunk& x = first[k];
+    const uint64_t size = static_cast<uint64_t>(x.rows) * static_cast<uint64_t>(x.tier);
+    return Key{(static_cast<uint64_t>(x.tier) << 48) + ((1ull << 48) - 1 - size), static_cast<int32_t>(k)};
+  };
+  std::vector<Key> key(count);
+  std::vector<Chunk> sorted(count);
+  if (count > 1024 || n_items <= 1) {
+    for (int64_t k = 0; k < count; ++k) key[k] = key_of(k);
+    std::sort(key.begin(), key.end());
+    for (int64_t k = 0; k < count; ++k) sorted[k] = first[key[k].second];
+  } else {
+    // each item's few chunks in that order, then dealt out a rank at a time (two sorts over all: 20 us more at 512)
+    std::vector<int32_t> begin(static_cast<size_t>(n_items) + 1, 0);
+    for (int64_t k = 0; k < count; ++k) ++begin[first[k].item + 1];
+    for (int64_t i = 0; i < n_items; ++i) begin[i + 1] += begin[i];
+    std::vector<int32_t> at(begin.begin(), begin.end() - 1);
+    for (int64_t k = 0; k < count; ++k) key[at[first[k].item]++] = key_of(k);
+    for (int64_t i = 0; i < n_items; ++i) std::sort(key.begin() + begin[i], key.begin() + begin[i + 1]);
+    int64_t out = 0;
+    for (int32_t rank = 0; out < count; ++rank)
+      for (int64_t i = 0; i < n_items; ++i)
+        if (begin[i] + rank < begin[i + 1]) sorted[out++] = first[key[begin[i] + rank].second];
+  }
+  std::copy(sorted.begin(), sorted.end(), first);
 }
 
 // every chunk learns its item's first partial slot and slot count (the merge inside the decode kernels needs them)
@@ -489,11 +606,18 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
                         Tables* out) {
   const size_t n = static_cast<size_t>(std::max<int64_t>(it.n_items, 1));
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
-  std::vector<uint8_t> blob(36 * n + 16, 0);
-  int64_t* tok_off = reinterpret_cast<int64_t*>(blob.data());
-  double* budget = reinterpret_cast<double*>(blob.data() + 8 * n);
-  double* avg = reinterpret_cast<double*>(blob.data() + 16 * n);
-  int32_t* T = reinterpret_cast<int32_t*>(blob.data() + 24 * n);
+  const size_t bytes = 36 * n + 16;
+  uint8_t* d = tmp.get<uint8_t>(bytes);
+  if (!d) return fail(RDKV_ERR_ALLOC, "device allocation failed");
+  StageRegion region;
+  int dev = 0;
+  RDKV_HIP(stage_acquire(bytes, false, &region, &dev));
+  uint8_t* blob = region.data;
+  std::memset(blob, 0, bytes);
+  int64_t* tok_off = reinterpret_cast<int64_t*>(blob);
+  double* budget = reinterpret_cast<double*>(blob + 8 * n);
+  double* avg = reinterpret_cast<double*>(blob + 16 * n);
+  int32_t* T = reinterpret_cast<int32_t*>(blob + 24 * n);
   int32_t* blk = T + n;
   int32_t* wblk = T + 2 * n;      // n + 1 entries
   const int key_tile = weights_key_tile();
@@ -513,9 +637,9 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
     }
   }
   wblk[it.n_items] = static_cast<int32_t>(n_wblk);
-  uint8_t* d = tmp.get<uint8_t>(blob.size());
-  if (!d) return fail(RDKV_ERR_ALLOC, "device allocation failed");
-  RDKV_HIP(upload(d, blob.data(), blob.size(), st));
+  CopyArgs ca{};
+  ca.add(blob, d, static_cast<int64_t>(bytes), true);
+  RDKV_HIP(stage_launch(ca, region, true, st));
   out->tok_off = reinterpret_cast<int64_t*>(d);
   out->budget = reinterpret_cast<double*>(d + 8 * n);
   out->avg = reinterpret_cast<double*>(d + 16 * n);
@@ -602,32 +726,47 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   const bool counted = d_blk_counts != nullptr;
   const int64_t n_counts = it.n_blocks * 4 + (counted ? 0 : 1);
   if (!counted) d_blk_counts = tmp.get<int32_t>(n_counts);
-  int32_t* d_counts = tmp.get<int32_t>(n1 * 4);              // [items][4]
-  int64_t* d_idx_base = tmp.get<int64_t>(n1 * 20);     // [items][4] kept-position bases, then [items][16] segment offsets
+  // [items][4] kept-position bases, [items][16] segment offsets, [items][4] rows per tier
+  int64_t* d_idx_base = tmp.get<int64_t>(n1 * 22);
   int64_t* d_seg_off = d_idx_base ? d_idx_base + n1 * 4 : nullptr;
-  if (!d_blk_counts || !d_counts || !d_idx_base)
+  int32_t* d_counts = d_idx_base ? reinterpret_cast<int32_t*>(d_idx_base + n1 * 20) : nullptr;
+  if (!d_blk_counts || !d_idx_base)
     return bail(fail(RDKV_ERR_ALLOC, "device allocation failed"));
   const int64_t* d_tok_off = tb.tok_off;
   const int32_t* d_T = tb.T;
   const int32_t* d_blk_off = tb.blk_off;
 
   if (n > 0) {
-    // the one wait of the pass: the tier counts size the arena and the split schedule
-    std::vector<int32_t> h_counts(n_counts, 0);
+    // the one wait of the pass: the tier counts size the arena and the split schedule.  A kernel writes them into pinned
+    // memory and the host watches for them (a copy to host memory and a wait for the stream: 25 us more).
     if (!counted) {
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
-      PACK_HIP(hipMemsetAsync(d_blk_counts + it.n_blocks * 4, 0, sizeof(int32_t), st));
+      CopyArgs clear{};
+      clear.fill(d_blk_counts + it.n_blocks * 4, sizeof(int32_t), 0u, 0u);
+      PACK_HIP(launch_copy(clear, st));
       PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_blk_counts + it.n_blocks * 4,
                                  static_cast<int>(n), it.max_T, st));
     }
-    if (it.max_T > 0)
-      PACK_HIP(hipMemcpyAsync(h_counts.data(), d_blk_counts, n_counts * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    std::vector<uint8_t> h_bits_ch;
-    if (mixed) {
-      h_bits_ch.resize(n * kHeadDim);
-      PACK_HIP(hipMemcpyAsync(h_bits_ch.data(), bits_ch, n * kHeadDim, hipMemcpyDeviceToHost, st));
+    std::vector<int32_t> h_counts(n_counts, 0);
+    std::vector<uint8_t> h_bits_ch(mixed ? n * kHeadDim : 0);
+    {
+      const int64_t counts_b = round_up(n_counts * static_cast<int64_t>(sizeof(int32_t)), 16);
+      StageRegion r;
+      int dev = 0;
+      PACK_HIP(stage_acquire(static_cast<size_t>(counts_b) + h_bits_ch.size(), true, &r, &dev));
+      CopyArgs a{};
+      a.add(d_blk_counts, r.data, n_counts * static_cast<int64_t>(sizeof(int32_t)), true);
+      if (mixed) a.add(bits_ch, r.data + counts_b, static_cast<int64_t>(h_bits_ch.size()), true);
+      hipError_t e = stage_launch(a, r, false, st);
+      if (e == hipSuccess) e = stage_wait(r, st);
+      if (e == hipSuccess) {
+        std::memcpy(h_counts.data(), r.data, h_counts.size() * sizeof(int32_t));
+        if (mixed) std::memcpy(h_bits_ch.data(), r.data + counts_b, h_bits_ch.size());
+      }
+      g_staging[dev].release(r);
+      if (r.own) (void)hipHostFree(r.own);
+      PACK_HIP(e);
     }
-    PACK_HIP(hipStreamSynchronize(st));
     if (!counted && h_counts[it.n_blocks * 4] != 0)
       return bail(fail(RDKV_ERR_INVALID_ARG, "bits_tok holds a value outside {0, 2, 4, 8, 16}"));
     for (int64_t i = 0; i < n; ++i) {
@@ -730,8 +869,10 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // (the 16-bit rows of a token-wise cache run in a kernel of their own and are cut separately below)
   const int ti0 = mixed ? 0 : 1;
   int64_t total_cost = 0, cost16 = 0;
+  std::vector<int64_t> item_cost(n, 0);                       // of the tiers this launch cuts together
   for (int64_t i = 0; i < n; ++i) {
-    for (int ti = ti0; ti < 4; ++ti) total_cost += c->counts[i * 4 + ti] * row_cost(i, pack_tier_bits(ti));
+    for (int ti = ti0; ti < 4; ++ti) item_cost[i] += c->counts[i * 4 + ti] * row_cost(i, pack_tier_bits(ti));
+    total_cost += item_cost[i];
     if (!mixed) cost16 += c->counts[i * 4] * row_cost(i, 16);
   }
   // Number of chunks a chunk cost of cb gives, and the largest chunk's cost.  Chunks of less than an eighth of cb (a
@@ -759,14 +900,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   auto count_shares = [&](int64_t cb, int64_t* max_cost) {
     int64_t total = 0;
     *max_cost = 0;
-    for (int64_t i = 0; i < n; ++i) {
-      int64_t item_cost = 0;
-      for (int ti = 1; ti < 4; ++ti) item_cost += c->counts[i * 4 + ti] * row_cost(i, pack_tier_bits(ti));
-      if (item_cost == 0) continue;
-      const int64_t n_wg = std::max<int64_t>(1, (item_cost + cb / 2) / cb);
-      total += n_wg;
-      *max_cost = std::max(*max_cost, item_cost / n_wg);
-    }
+    for (int64_t i = 0; i < n; ++i)
+      if (item_cost[i] > 0) total += std::max<int64_t>(1, (item_cost[i] + cb / 2) / cb);
     return total;
   };
   // Shares that span tiers pay a start-up per tier (operands rebuilt, the first tiles' latency waited for again):
@@ -791,6 +926,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   const int64_t round16 = 512;
   const int64_t chunk_bytes16 = std::max<int64_t>(96 << 10, (cost16 + round16 - 1) / round16);
   std::vector<int32_t> slot_begin(std::max<int64_t>(n, 1), 0), slot_count(std::max<int64_t>(n, 1), 0);
+  c->chunks.reserve(static_cast<size_t>(n_one_round + 2 * n));
   std::vector<Chunk> conts;     // continuation pieces (token-wise mode): reached through Chunk::next, never launched
   auto make_chunk = [&](int64_t i, int ti, int64_t r0, int64_t rows) {
     const int bits = pack_tier_bits(ti);
@@ -832,13 +968,11 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       // into equal shares of cost whatever the tiers' sizes: a workgroup's share may span two or three tiers (its
       // pieces are chained through Chunk::next and feed one softmax state), so every launch, single-tier or not,
       // gets chunks of even cost.
-      int64_t item_cost = 0;
-      for (int ti = 1; ti < 4; ++ti) item_cost += c->counts[i * 4 + ti] * row_cost(i, pack_tier_bits(ti));
-      const int64_t n_wg = item_cost == 0 ? 0 : std::max<int64_t>(1, (item_cost + chunk_bytes / 2) / chunk_bytes);
+      const int64_t n_wg = item_cost[i] == 0 ? 0 : std::max<int64_t>(1, (item_cost[i] + chunk_bytes / 2) / chunk_bytes);
       int ti = 3;            // walk the segments from the 2-bit tier up
       int64_t r0 = 0;        // first row of the current segment not handed out yet
       for (int64_t k = 0; k < n_wg; ++k) {
-        int64_t share = item_cost / n_wg;     // what this workgroup should take
+        int64_t share = item_cost[i] / n_wg;     // what this workgroup should take
         int32_t prev = -1;                    // index of the workgroup's previous piece: >= 0 in conts, -2 - x: chunk x
         while (ti >= 1) {
           const int64_t left = c->counts[i * 4 + ti] - r0;
@@ -902,6 +1036,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // ---- allocate what the cache owns: one block --------------------------------------------
   // [arena | tail state | arrival counters of this stream's workspace]  (cleared together)
   // [kept positions | token bit map | channel bit map | K row layouts, chunk table (one copy) | partials | lambda, steps]
+  uint32_t* d_krange = nullptr;
   {
     auto up = [](int64_t b) { return round_up(std::max<int64_t>(b, 16), 256); };
     const int64_t o_state = c->arena_bytes, o_arrive = o_state + 256, o_idx = o_arrive + up(n * 4);
@@ -929,18 +1064,34 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     c->d_chunks = reinterpret_cast<Chunk*>(c->d_block + o_ik + ik_b);
     c->index_bytes = total - c->arena_bytes;     // everything else in the block
     if (n > 0) {
-      // nothing below waits: tables are copied out of pinned staging memory, and the host vectors may go
-      // (the pack kernels write every byte of the arena)
-      PACK_HIP(hipMemsetAsync(c->d_block + o_state, 0, o_idx - o_state, st));     // tail state, counters
-      PACK_HIP(upload(d_counts, c->counts.data(), n * 4 * sizeof(int32_t), st));
-      std::vector<int64_t> plan(idx_base);
-      plan.resize(n1 * 4, 0);
-      plan.insert(plan.end(), c->seg_off.begin(), c->seg_off.end());
-      PACK_HIP(upload(d_idx_base, plan.data(), plan.size() * sizeof(int64_t), st));
-      std::vector<uint8_t> tables(static_cast<size_t>(ik_b + n_chunks * static_cast<int64_t>(sizeof(Chunk))));
-      if (mixed) std::memcpy(tables.data(), c->items_k.data(), n * sizeof(ItemK));
-      if (n_chunks > 0) std::memcpy(tables.data() + ik_b, c->chunks.data(), n_chunks * sizeof(Chunk));
-      if (!tables.empty()) PACK_HIP(upload(c->d_block + o_ik, tables.data(), tables.size(), st));
+      // one launch: the tables out of pinned memory, what the block keeps of the pass's scratch, the words that start at
+      // zero (the pack kernels write every byte of the arena)
+      const int64_t plan_b = static_cast<int64_t>(n1) * 22 * 8, tables_b = ik_b + n_chunks * static_cast<int64_t>(sizeof(Chunk));
+      if (c->k_per_unit) {
+        d_krange = tmp.get<uint32_t>(n * kHeadDim * 2);
+        if (!d_krange) return bail(fail(RDKV_ERR_ALLOC, "device allocation failed"));
+      }
+      StageRegion r;
+      int dev = 0;
+      PACK_HIP(stage_acquire(static_cast<size_t>(plan_b + tables_b), false, &r, &dev));
+      int64_t* plan = reinterpret_cast<int64_t*>(r.data);
+      std::memcpy(plan, idx_base.data(), n * 4 * sizeof(int64_t));
+      std::memcpy(plan + n1 * 4, c->seg_off.data(), n * 16 * sizeof(int64_t));
+      std::memcpy(plan + n1 * 20, c->counts.data(), n * 4 * sizeof(int32_t));
+      uint8_t* tables = r.data + plan_b;
+      if (mixed) std::memcpy(tables, c->items_k.data(), n * sizeof(ItemK));
+      if (n_chunks > 0) std::memcpy(tables + ik_b, c->chunks.data(), n_chunks * sizeof(Chunk));
+      CopyArgs a{};
+      a.add(plan, d_idx_base, plan_b, true);
+      a.add(tables, c->d_block + o_ik, tables_b, true);
+      a.fill(c->d_block + o_state, o_idx - o_state, 0u, 0u);     // tail state, arrival counters
+      a.add(bits_tok, c->d_bits_tok, it.total_tokens);
+      if (mixed) a.add(bits_ch, c->d_bits_ch, n * kHeadDim);
+      if (lam) a.add(lam, c->d_block + o_lam, maps * n * 8);
+      if (iters) a.add(iters, c->d_block + o_it, maps * n * 4);
+      // per-channel (minimum, maximum) over all retained tokens, as ordered integers
+      if (d_krange) a.fill(d_krange, n * kHeadDim * 2 * static_cast<int64_t>(sizeof(uint32_t)), 0xFFFFFFFFu, 0u);
+      PACK_HIP(stage_launch(a, r, true, st));
       c->slot_begin = slot_begin;
       c->slot_count = slot_count;
       {   // the split workspace of this stream lives in the block: a first decode under graph capture allocates nothing
@@ -949,26 +1100,13 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
                                                       reinterpret_cast<float*>(c->d_block + o_ml),
                                                       reinterpret_cast<int32_t*>(c->d_block + o_arrive), nullptr});
       }
-      if (lam) PACK_HIP(hipMemcpyAsync(c->d_block + o_lam, lam, maps * n * 8, hipMemcpyDeviceToDevice, st));
-      if (iters) PACK_HIP(hipMemcpyAsync(c->d_block + o_it, iters, maps * n * 4, hipMemcpyDeviceToDevice, st));
     }
     if (lam) c->d_lambda = reinterpret_cast<double*>(c->d_block + o_lam);
     if (iters) c->d_iters = reinterpret_cast<int32_t*>(c->d_block + o_it);
   }
 
   if (n > 0) {
-    if (it.total_tokens > 0)
-      PACK_HIP(hipMemcpyAsync(c->d_bits_tok, bits_tok, it.total_tokens, hipMemcpyDeviceToDevice, st));
-    if (mixed) PACK_HIP(hipMemcpyAsync(c->d_bits_ch, bits_ch, n * kHeadDim, hipMemcpyDeviceToDevice, st));
     if (kept > 0) {
-      uint32_t* d_krange = nullptr;
-      if (c->k_per_unit) {   // per-channel (minimum, maximum) over all retained tokens, as ordered integers
-        d_krange = tmp.get<uint32_t>(n * kHeadDim * 2);
-        if (!d_krange) return bail(fail(RDKV_ERR_ALLOC, "device allocation failed"));
-        std::vector<uint32_t> h_krange(static_cast<size_t>(n) * kHeadDim * 2);
-        for (size_t k = 0; k < h_krange.size(); k += 2) { h_krange[k] = 0xFFFFFFFFu; h_krange[k + 1] = 0u; }
-        PACK_HIP(upload(d_krange, h_krange.data(), h_krange.size() * sizeof(uint32_t), st));
-      }
       TimedScope ts(RDKV_TIME_PACK, st);      // second half: kept-position lists, quantize and pack
       PACK_HIP(launch_tier_scatter(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_idx_base, c->d_tier_idx,
                                    static_cast<int>(n), it.max_T, st));
@@ -1195,8 +1333,7 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
     for (int64_t i = 0; i < it.n_items; ++i) n_wblk += (it.T[i] + key_tile - 1) / key_tile;
     tmp.reserve({36 * ni + 16, nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
                  weights_scratch_floats(n_wblk, it.n_items, it.total_tokens, R, mixed) * sizeof(float),
-                 static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t),
-                 (ni * 4 + 1) * sizeof(int32_t), ni * 20 * sizeof(int64_t), ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),
+                 static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t), ni * 22 * sizeof(int64_t), ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),
                  allocate_scratch_bytes(static_cast<int>(it.n_items), it.max_T),
                  mixed && cfg->k_scale_per_channel ? nc * 2 * sizeof(uint32_t) : 0});
   }

@@ -59,6 +59,29 @@ struct ItemK {
   int16_t slot_ch[kMaxSlots];    // channel held by a slot, -1 for padding
 };
 
+// One launch of small copies (copy_kernels.hip).
+constexpr int kStageWords = 16;        // completion words at the head of a staging region
+struct CopySeg {
+  const void* src;                     // null: fill with the two words of `fill`
+  void* dst;
+  int64_t bytes;
+  uint32_t fill[2];
+  int32_t host;                        // one side is staging memory: only the first host_blocks workgroups take part
+};
+struct CopyArgs {
+  CopySeg seg[8];
+  int32_t n, host_blocks;
+  uint32_t* words;                     // completion words of the staging region, or null
+  uint32_t seq;
+  void add(const void* src, void* dst, int64_t bytes, bool host = false) {
+    if (bytes > 0) seg[n++] = CopySeg{src, dst, bytes, {0u, 0u}, host ? 1 : 0};
+  }
+  void fill(void* dst, int64_t bytes, uint32_t w0, uint32_t w1) {
+    if (bytes > 0) seg[n++] = CopySeg{nullptr, dst, bytes, {w0, w1}, 0};
+  }
+};
+hipError_t launch_copy(const CopyArgs& a, hipStream_t st);
+
 struct DenseArgs {
   const uint16_t* K;
   const uint16_t* V;

@@ -33,6 +33,8 @@ FLAGS = [
     "-ffp-contract=off",
     # MFMA results stay in ordinary vector registers (no copies through the accumulation registers)
     "-mllvm", "-amdgpu-mfma-vgpr-form",
+    # the leading kernel arguments arrive in registers with the wavefront (no load before the first address is known)
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wno-unused-function",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]

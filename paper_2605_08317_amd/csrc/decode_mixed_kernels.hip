@@ -46,7 +46,7 @@ struct LdsPlan {
     wtab = qraw + n_qsteps * hs * 32;
     wtab_wave = (2 * n_qsteps + 1) * hs * 64;   // one entry of padding: the step loop reads one entry ahead
     const int tables = wtab + kWaves * wtab_wave;
-    const int merge = kWaves * 4 * hs * 2 * 4 + 2 * kWaves * g * kHeadDim * 4;
+    const int merge = kWaves * 4 * hs * 2 * 4 + finish_lds_floats(kWaves, g) * 4;
     total = tables > merge ? tables : merge;
   }
 };
@@ -438,20 +438,17 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
 template <int NW, int HS, int NWV>
 __global__ __launch_bounds__(NWV * 64, (NW <= 32 && HS == 1) ? 3 : 2) void decode_mixed_kernel(
     const Chunk* __restrict__ chunks, const uint8_t* __restrict__ arena, const ItemK* __restrict__ items_k,
-    const uint16_t* __restrict__ q, MergeArgs ma, int lds_steps, int lds_qsteps, const int32_t* __restrict__ tail_len,
-    int per_unit) {
+    const uint16_t* __restrict__ q, const int32_t* __restrict__ tail_len, int lds_steps, int lds_qsteps, int per_unit,
+    int g, MergeArgs ma) {
   extern __shared__ __align__(16) uint8_t smem[];
   const Chunk ch = chunks[blockIdx.x];
-  const int g = ma.hq / ma.hkv;
-  const int seq = ch.item / ma.hkv, head = ch.item % ma.hkv;
-  const uint16_t* qp = q + (static_cast<int64_t>(seq) * ma.hq + head * g) * kHeadDim;
+  const uint16_t* qp = q + static_cast<int64_t>(ch.item) * g * kHeadDim;     // item = sequence x KV head
   const ChunkOut co{ch.item, ch.slot, ch.slot0, ch.nslots};
   const ItemK* ikp = items_k + ch.reserved;   // the K row layout of this chunk's (generation, item)
   switch (ch.tier) {
     case kTierTail: {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
       const int rows = max(0, min(ch.rows, *tail_len - ch.row0));
-      process_tail_tiles<HS, true, NWV>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, smem,
-                                        reinterpret_cast<float*>(smem),
+      process_tail_tiles<HS, true, NWV>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, reinterpret_cast<float*>(smem),
                                         reinterpret_cast<float*>(smem) + NWV * 4 * HS * 2, ma, co);
       break;
     }
@@ -466,14 +463,14 @@ template <int NW, int HS, int NWV>
 hipError_t launch_one(const Chunk* chunks, int n_chunks, const uint8_t* arena, const ItemK* items_k, int lds_steps,
                       int lds_qsteps, const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, int per_unit,
                       hipStream_t st) {
-  const size_t lds = static_cast<size_t>(LdsPlan(lds_steps, lds_qsteps, HS, ma.hq / ma.hkv, NWV).total);
+  const size_t lds = static_cast<size_t>(LdsPlan(lds_steps, lds_qsteps, HS, ma.g, NWV).total);
   if (lds > 48 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_mixed_kernel<NW, HS, NWV>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((decode_mixed_kernel<NW, HS, NWV>), dim3(n_chunks), dim3(NWV * 64), lds, st, chunks, arena,
-                     items_k, q, ma, lds_steps, lds_qsteps, tail_len, per_unit);
+                     items_k, q, tail_len, lds_steps, lds_qsteps, per_unit, ma.g, ma);
   return hipGetLastError();
 }
 

@@ -30,9 +30,9 @@ constexpr int kRowStride = 272;                       // bytes per token row in 
 constexpr int kStageBytes = kTile * kRowStride;       // one wavefront's staging region
 template <int HS>
 constexpr int rows_lds_bytes() {
-  // query operands [32 steps][HS][4 heads] x 8 bytes, the wavefronts' staging regions, [waves][4 HS][m, l] floats;
+  // the wavefronts' staging regions, [waves][4 HS][m, l] floats;
   // the end-of-chunk areas (per-wavefront accumulators [waves][g][128] floats, then the merge) reuse the staging
-  return 32 * HS * 32 + kRowsWaves * kStageBytes + kRowsWaves * 4 * HS * 2 * 4;
+  return kRowsWaves * kStageBytes + kRowsWaves * 4 * HS * 2 * 4;
 }
 
 __device__ __forceinline__ uint4 load_row_chunk(const uint8_t* __restrict__ base, int row, int c16) {
@@ -73,10 +73,9 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blk = lane >> 2, j = lane & 3;
-  uint8_t* s_q = smem;
-  uint8_t* s_stage = smem + 32 * HS * 32 + wave * kStageBytes;
-  float* s_ml = reinterpret_cast<float*>(smem + 32 * HS * 32 + kRowsWaves * kStageBytes);
-  float* s_acc = reinterpret_cast<float*>(smem + 32 * HS * 32);   // after the tile loop: [waves][g][128], then the merge
+  uint8_t* s_stage = smem + wave * kStageBytes;
+  float* s_ml = reinterpret_cast<float*>(smem + kRowsWaves * kStageBytes);
+  float* s_acc = reinterpret_cast<float*>(smem);   // after the tile loop: [waves][g][128], then the merge
   const int ntiles = (rows + kTile - 1) / kTile;
   const int last = rows - 1;
   const int lr = lane >> 4, lc = lane & 15;            // a load covers 4 rows x 16 chunks of 16 bytes
@@ -90,17 +89,10 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
 #pragma unroll
     for (int i = 0; i < 16; ++i) *reinterpret_cast<uint4*>(s_stage + (4 * i + lr) * kRowStride + 16 * lc) = st[i];
   };
+  uint4 qa[HS];      // the query on the A side, raw bf16 (exact products); loads return in order, so it goes first
+#pragma unroll
+  for (int hs = 0; hs < HS; ++hs) qa[hs] = load_query(q, 4 * hs + j, g, blk);
   if (wave < ntiles) load_tile(kd, wave);
-
-  // query operands of the K product: raw bf16, [step][HS][head] x 8 bytes
-  for (int e = tid; e < 32 * HS * 4; e += kRowsWG) {
-    const int s = e / (HS * 4), hs = (e >> 2) % HS, hj = e & 3;
-    const int head = 4 * hs + hj;
-    uint2 v = make_uint2(0, 0);
-    if (head < g) v = *reinterpret_cast<const uint2*>(q + head * kHeadDim + 4 * s);
-    *reinterpret_cast<uint2*>(s_q + ((s * HS + hs) * 4 + hj) * 8) = v;
-  }
-  __syncthreads();
 
   Run<HS> run;
   run.init();
@@ -113,30 +105,25 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
     floatx4 a16[HS];
 #pragma unroll
     for (int hs = 0; hs < HS; ++hs) a16[hs] = zero4;
-#pragma unroll
-    for (int part = 0; part < 4; ++part) {   // 64 bytes = 32 channels = 8 steps of the lane's own token row
-      uint4 kr[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        kr[u] = *reinterpret_cast<const uint4*>(s_stage + lane * kRowStride + 64 * part + 16 * u);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const int s = 8 * part + 2 * u + half;
-          const short4v a = half ? bf4(kr[u].z, kr[u].w) : bf4(kr[u].x, kr[u].y);
-#pragma unroll
-          for (int hs = 0; hs < HS; ++hs) {
-            const uint2 braw = *reinterpret_cast<const uint2*>(s_q + ((s * HS + hs) * 4 + j) * 8);
-            a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, bf4(braw.x, braw.y), a16[hs], 0, 0, 0);
-          }
-        }
-    }
-    float x[HS][4];
+    // 16 bytes of the lane's own token row = 8 channels = block I's two steps
+#define RDKV_ROWS_K(I_)                                                                                              \
+  {                                                                                                                 \
+    const uint4 kr = *reinterpret_cast<const uint4*>(s_stage + lane * kRowStride + 16 * (I_));                      \
+    _Pragma("unroll") for (int hs = 0; hs < HS; ++hs) {                                                             \
+      a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(bf4(qa[hs].x, qa[hs].y), bf4(kr.x, kr.y), a16[hs], 4, I_, 0); \
+      a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(bf4(qa[hs].z, qa[hs].w), bf4(kr.z, kr.w), a16[hs], 4, I_, 0); \
+    }                                                                                                               \
+  }
+    RDKV_ROWS_K(0) RDKV_ROWS_K(1) RDKV_ROWS_K(2) RDKV_ROWS_K(3) RDKV_ROWS_K(4) RDKV_ROWS_K(5) RDKV_ROWS_K(6)
+    RDKV_ROWS_K(7) RDKV_ROWS_K(8) RDKV_ROWS_K(9) RDKV_ROWS_K(10) RDKV_ROWS_K(11) RDKV_ROWS_K(12) RDKV_ROWS_K(13)
+    RDKV_ROWS_K(14) RDKV_ROWS_K(15)
+#undef RDKV_ROWS_K
+    float xt[HS][4], x[HS][4];
 #pragma unroll
     for (int hs = 0; hs < HS; ++hs)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[hs][i] = a16[hs][i] * kKUnit;
+      for (int i = 0; i < 4; ++i) xt[hs][i] = a16[hs][i] * kKUnit;
+    to_head_lanes<HS>(xt, j, x);
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
     softmax_tile<HS>(x, run, p);
@@ -158,54 +145,42 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
   for (int hs = 0; hs < HS; ++hs) run.l[hs] = head_sum(run.l[hs]);
   __syncthreads();                      // the staging regions become the accumulator area
 #pragma unroll
-  for (int hs = 0; hs < HS; ++hs)
-    if (lane < 4) {
-      s_ml[((wave * HS + hs) * 4 + lane) * 2] = run.m[hs] * kXScale - kPExp;   // log2 domain from here on
-      s_ml[((wave * HS + hs) * 4 + lane) * 2 + 1] = run.l[hs];
-    }
-  __syncthreads();
-#pragma unroll
-  for (int hs = 0; hs < HS; ++hs)
+  for (int hs = 0; hs < HS; ++hs) {
+    if (lane < 4)
+      *reinterpret_cast<float2*>(s_ml + ((wave * HS + hs) * 4 + lane) * 2) =
+          make_float2(run.m[hs] * kXScale - kPExp, run.l[hs]);      // log2 domain from here on
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int head = 4 * hs + i;
-      float mm = kNegBig;
-#pragma unroll
-      for (int w = 0; w < kRowsWaves; ++w) mm = fmaxf(mm, s_ml[((w * HS + hs) * 4 + i) * 2]);
-      const float f = fast_exp2(s_ml[((wave * HS + hs) * 4 + i) * 2] - mm);
-      if (head < g) {
+      if (head < g)
         *reinterpret_cast<float2*>(s_acc + (wave * g + head) * kHeadDim + 2 * lane) =
-            make_float2(run.acc[hs][0][i] * f, run.acc[hs][1][i] * f);
-      }
-    }
-  __syncthreads();
-  for (int idx = tid; idx < g * kHeadDim; idx += kRowsWG) {
-    float v = 0.f;
-#pragma unroll
-    for (int w = 0; w < kRowsWaves; ++w) v += s_acc[w * g * kHeadDim + idx];
-    if constexpr (TIERED) merge::store_agent(part_acc + idx, v); else part_acc[idx] = v;
-  }
-  if (tid < g) {
-    const int hs = tid >> 2, i = tid & 3;
-    float mm = kNegBig;
-#pragma unroll
-    for (int w = 0; w < kRowsWaves; ++w) mm = fmaxf(mm, s_ml[((w * HS + hs) * 4 + i) * 2]);
-    float ll = 0.f;
-#pragma unroll
-    for (int w = 0; w < kRowsWaves; ++w)
-      ll += s_ml[((w * HS + hs) * 4 + i) * 2 + 1] * fast_exp2(s_ml[((w * HS + hs) * 4 + i) * 2] - mm);
-    if constexpr (TIERED) {
-      merge::store_agent(part_ml + tid * 2, mm);
-      merge::store_agent(part_ml + tid * 2 + 1, ll);
-    } else {
-      part_ml[tid * 2] = mm;
-      part_ml[tid * 2 + 1] = ll;
+            make_float2(run.acc[hs][0][i], run.acc[hs][1][i]);
     }
   }
   if constexpr (TIERED) {
-    merge::partial_stores_done();
+    store_partial<HS, kRowsWaves>(g, s_ml, s_acc, *ma, *co);
+  } else {
     __syncthreads();
-    merge::arrive_and_merge<kRowsWG, 4 * HS>(*ma, co->item, co->slot0, co->nslots, g, s_acc);
+    for (int idx = tid; idx < g * kHeadDim; idx += kRowsWG) {
+      const int head = idx >> 7;
+      float m[kRowsWaves], mm = kNegBig, v = 0.f, ll = 0.f;
+#pragma unroll
+      for (int w = 0; w < kRowsWaves; ++w) {
+        m[w] = s_ml[(w * HS * 4 + head) * 2];
+        mm = fmaxf(mm, m[w]);
+      }
+#pragma unroll
+      for (int w = 0; w < kRowsWaves; ++w) {
+        const float f = fast_exp2(m[w] - mm);
+        v = __builtin_fmaf(s_acc[w * g * kHeadDim + idx], f, v);
+        ll = __builtin_fmaf(s_ml[(w * HS * 4 + head) * 2 + 1], f, ll);
+      }
+      part_acc[idx] = v;
+      if ((idx & 127) == 0) {
+        part_ml[head * 2] = mm;
+        part_ml[head * 2 + 1] = ll;
+      }
+    }
   }
 }
 
@@ -231,12 +206,10 @@ __global__ __launch_bounds__(kRowsWG, 2) void decode_dense_mfma_kernel(DenseArgs
 template <int HS>
 __global__ __launch_bounds__(kRowsWG, 2) void decode_tiered_mfma_kernel(const Chunk* __restrict__ chunks,
                                                                        const uint8_t* __restrict__ arena,
-                                                                       const uint16_t* __restrict__ q, MergeArgs ma) {
+                                                                       const uint16_t* __restrict__ q, int g, MergeArgs ma) {
   extern __shared__ __align__(16) uint8_t smem[];
   const Chunk ch = chunks[blockIdx.x];
-  const int g = ma.hq / ma.hkv;
-  const int seq = ch.item / ma.hkv, head = ch.item % ma.hkv;
-  const uint16_t* qp = q + (static_cast<int64_t>(seq) * ma.hq + head * g) * kHeadDim;
+  const uint16_t* qp = q + static_cast<int64_t>(ch.item) * g * kHeadDim;     // item = sequence x KV head
   const ChunkOut co{ch.item, ch.slot, ch.slot0, ch.nslots};
   process_rows_mfma<HS, true>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
                               ma.part_acc + static_cast<int64_t>(ch.slot) * g * kHeadDim,
@@ -271,18 +244,17 @@ hipError_t launch_decode_dense_split(const DenseArgs& a, int g, int n_seqs, hipS
 hipError_t launch_decode_tiered_split(const Chunk* chunks, int n_chunks, const uint8_t* arena, const uint16_t* q,
                                       const MergeArgs& ma, hipStream_t st) {
   if (n_chunks == 0) return hipSuccess;
-  const int g = ma.hq / ma.hkv;
   dim3 grid(n_chunks), block(kRowsWG);
-  if (g > 4) {
+  if (ma.g > 4) {
     const size_t lds = rows_lds_bytes<2>();
     hipError_t e = allow_lds(decode_tiered_mfma_kernel<2>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_tiered_mfma_kernel<2>, grid, block, lds, st, chunks, arena, q, ma);
+    hipLaunchKernelGGL(decode_tiered_mfma_kernel<2>, grid, block, lds, st, chunks, arena, q, ma.g, ma);
   } else {
     const size_t lds = rows_lds_bytes<1>();
     hipError_t e = allow_lds(decode_tiered_mfma_kernel<1>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_tiered_mfma_kernel<1>, grid, block, lds, st, chunks, arena, q, ma);
+    hipLaunchKernelGGL(decode_tiered_mfma_kernel<1>, grid, block, lds, st, chunks, arena, q, ma.g, ma);
   }
   return hipGetLastError();
 }

@@ -70,24 +70,69 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) {
   return __builtin_bit_cast(float, dpp_u32<CTRL>(__builtin_bit_cast(uint32_t, v)));
 }
-// reduction over the 16 lanes that hold the same head (lane % 4): lanes 4 apart inside a row of 16, then the rows
+// Row and half exchanges (the wait states they need after a write to their operands stand in front of them): rows 1 and 3
+// of a swapped with rows 0 and 2 of b; the upper half of a with the lower half of b.
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ float sum_xor16(float v) {
+  float o = v;
+  swap_rows(v, o);
+  return v + o;
+}
+// Reduction over the 16 lanes that hold the same head (lane % 4): lanes 4 apart inside a row of 16, then the rows.  No
+// step goes through LDS: with two or three wavefronts per SIMD nothing covers the 100 cycles of a ds_bpermute (a chunk's
+// five sums took 0.65 us).
 __device__ __forceinline__ float head_max(float v) {
   v = fmaxf(v, dpp_f32<0x124>(v));   // row_ror:4
   v = fmaxf(v, dpp_f32<0x128>(v));   // row_ror:8
-  v = fmaxf(v, __shfl_xor(v, 16));
-  v = fmaxf(v, __shfl_xor(v, 32));
-  return v;
+  float o = v;
+  swap_rows(v, o);
+  o = v = fmaxf(v, o);
+  swap_halves(v, o);
+  return fmaxf(v, o);
 }
 __device__ __forceinline__ float head_sum(float v) {
   v += dpp_f32<0x124>(v);
   v += dpp_f32<0x128>(v);
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
+  float o = v = sum_xor16(v);
+  swap_halves(v, o);
+  return v + o;
 }
 // value held by lane i of this lane's quad
 template <int I>
 __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) { return dpp_u32<I * 0x55>(v); }
+
+template <int G>
+struct GroupIndex {
+  static constexpr int value = G;
+};
+
+// Query on the A side of the K products: lane (block b, head j) holds channels 8 b .. 8 b + 7 of head 4 hs + j, that is
+// the operands of steps 2 b and 2 b + 1, and a product broadcasts the block that holds its step (cbsz = 4).  Sixteen
+// bytes per lane are the whole query of four heads, loaded by each wavefront for itself: no LDS, no barrier before the
+// first tile.  (With the query on the B side every lane needed every step's operand, 32 eight-byte LDS reads per tile and
+// head set: 1100 cycles of LDS bandwidth for eight wavefronts.)
+__device__ __forceinline__ uint4 load_query(const uint16_t* __restrict__ q, int head, int g, int blk) {
+  return head < g ? *reinterpret_cast<const uint4*>(q + head * kHeadDim + 8 * blk) : make_uint4(0, 0, 0, 0);
+}
+
+// The K products leave lane = token with the four heads of a set in its registers; the softmax and P V want lane (block,
+// head) with the block's four tokens: a 4x4 transposition per block, which products with unit vectors do exactly.
+template <int HS>
+__device__ __forceinline__ void to_head_lanes(const float (&xt)[HS][4], int j, float (&x)[HS][4]) {
+#pragma unroll
+  for (int hs = 0; hs < HS; ++hs) {
+    floatx4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t = __builtin_amdgcn_mfma_f32_4x4x1f32(xt[hs][k], j == k ? 1.0f : 0.0f, t, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[hs][i] = t[i];
+  }
+}
 
 // Field position of step s inside a 16-bit half, which right-shifted copy of the word it is read from, and the bit
 // offset that remains after that shift (the code then reads as code * 2^fb * 2^-24).
@@ -228,11 +273,6 @@ __device__ __forceinline__ float v_log2_kappa(int blk) {
   return lk;
 }
 
-template <int G>
-struct GroupIndex {
-  static constexpr int value = G;
-};
-
 // P V over a token-wise V tile of tier TIER (8, 4, 2).  fill_gw(GroupIndex<G>, gw) delivers the code words of
 // channel group G (and their shifted copies); vmeta = group (lane % 4)'s scales (x, y) and offsets (z, w) of
 // tokens 4 blk + 0..3; p = the probabilities times the lane's kappa (softmax_tile with lk).
@@ -294,82 +334,102 @@ struct ChunkOut {
   int item, slot, slot0, nslots;   // the chunk's item and partial slot; the item's first slot and slot count
 };
 
-// End of a chunk: scale the accumulators back (acc_scale = 2^24 where the V codes entered as fp16 subnormals),
-// take the lane's factor kappa = 2^lk out of the running sums, add the offset sums, merge the workgroup's NWV
-// wavefronts through LDS, store the chunk's partial result and announce it; the workgroup that completes its item
-// merges the item's partials (arrive_and_merge).
-// s_ml: [NWV][4 HS heads][m, l] floats; s_acc: [2 NWV streams][g][128] floats (also the merge's LDS).  ALIAS: the
-// two areas overlap LDS that the tile loop used, so a barrier separates the two uses.
-template <int HS, bool ALIAS, int NWV>
-__device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, float lk, int g, float* s_ml,
-                                             float* s_acc, const MergeArgs& ma, const ChunkOut& co) {
+// Sum of the wavefront's two halves: of a in lanes 0..31, of b in lanes 32..63.
+__device__ __forceinline__ float halves_sum(float a, float b) {
+  swap_halves(a, b);
+  return a + b;
+}
+
+// Floats of LDS the end of a chunk needs behind s_ml: the wavefronts' sums, later the merge of the item.
+__host__ __device__ constexpr int finish_lds_floats(int waves, int g) {
+  return waves * g * kHeadDim > merge::merge_lds_floats(waves * 64) ? waves * g * kHeadDim : merge::merge_lds_floats(waves * 64);
+}
+
+// Last part of a chunk's end, after s_ml ([NWV][4 HS heads] of maximum, sum) and s_acc ([NWV][g][128] unnormalised sums,
+// each relative to its wavefront's own maximum) are written: one barrier, then every thread weighs and adds the NWV
+// wavefronts' values of its (head, channel).  An item of a single chunk is finished here; otherwise the partial result is
+// stored and announced, and the workgroup that completes its item merges the item's partials (arrive_and_merge).
+template <int HS, int NWV>
+__device__ __forceinline__ void store_partial(int g, const float* s_ml, float* s_acc, const MergeArgs& ma, const ChunkOut& co) {
   constexpr int NT = NWV * 64;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int th = lane >> 5, cl = lane & 31;
+  const int tid = threadIdx.x;
   float* __restrict__ part_acc = ma.part_acc + static_cast<int64_t>(co.slot) * g * kHeadDim;
   float* __restrict__ part_ml = ma.part_ml + static_cast<int64_t>(co.slot) * g * 2;
-  const float inv_kappa = __builtin_ldexpf(1.0f, static_cast<int>(-lk));   // lk is a small integer
-#pragma unroll
-  for (int hs = 0; hs < HS; ++hs) {
-    run.l[hs] = head_sum(run.l[hs] * inv_kappa);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      // lanes (block, j) hold head i's sum_t p m of channel group j over the block's tokens: all blocks, then to the
-      // lanes of every group
-      const uint32_t ou = __builtin_bit_cast(uint32_t, head_sum(run.offv[hs][i] * inv_kappa));
-      const float og[4] = {__builtin_bit_cast(float, quad_bcast<0>(ou)), __builtin_bit_cast(float, quad_bcast<1>(ou)),
-                           __builtin_bit_cast(float, quad_bcast<2>(ou)), __builtin_bit_cast(float, quad_bcast<3>(ou))};
-#pragma unroll
-      for (int grp = 0; grp < 4; ++grp)
-        run.acc[hs][grp][i] = __builtin_fmaf(run.acc[hs][grp][i], acc_scale, th == 0 ? og[grp] : 0.f);
-    }
-  }
-  if constexpr (ALIAS) __syncthreads();
-#pragma unroll
-  for (int hs = 0; hs < HS; ++hs)
-    if (lane < 4) {
-      s_ml[((wave * HS + hs) * 4 + lane) * 2] = run.m[hs] * kXScale - kPExp;   // log2 domain from here on
-      s_ml[((wave * HS + hs) * 4 + lane) * 2 + 1] = run.l[hs];
-    }
-  __syncthreads();
-#pragma unroll
-  for (int hs = 0; hs < HS; ++hs)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int head = 4 * hs + i;
-      float mm = kNegBig;
-#pragma unroll
-      for (int w = 0; w < NWV; ++w) mm = fmaxf(mm, s_ml[((w * HS + hs) * 4 + i) * 2]);
-      const float f = fast_exp2(s_ml[((wave * HS + hs) * 4 + i) * 2] - mm);
-      if (head < g) {
-#pragma unroll
-        for (int grp = 0; grp < 4; ++grp)
-          s_acc[((wave * 2 + th) * g + head) * kHeadDim + 32 * grp + cl] = run.acc[hs][grp][i] * f;
-      }
-    }
+  const bool single = co.nslots == 1;
+  const int64_t qh0 = static_cast<int64_t>(co.item) * g;
   __syncthreads();
   for (int idx = tid; idx < g * kHeadDim; idx += NT) {
-    float v = 0.f;
+    const int head = idx >> 7;
+    float2 ml[NWV];
+    float a[NWV], mm = kNegBig;
 #pragma unroll
-    for (int w = 0; w < 2 * NWV; ++w) v += s_acc[w * g * kHeadDim + idx];
-    merge::store_agent(part_acc + idx, v);
+    for (int w = 0; w < NWV; ++w) {
+      ml[w] = *reinterpret_cast<const float2*>(s_ml + (w * HS * 4 + head) * 2);
+      a[w] = s_acc[w * g * kHeadDim + idx];
+    }
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) mm = fmaxf(mm, ml[w].x);
+    float v = 0.f, l = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) {
+      const float f = fast_exp2(ml[w].x - mm);
+      l = __builtin_fmaf(ml[w].y, f, l);
+      v = __builtin_fmaf(a[w], f, v);
+    }
+    if (single) {
+      ma.out[qh0 * kHeadDim + idx] = l > 0.f ? v / l : 0.f;
+      if ((idx & 127) == 0 && ma.lse != nullptr)
+        ma.lse[qh0 + head] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
+    } else {
+      merge::store_agent(part_acc + idx, v);
+      if ((idx & 127) == 0) {
+        merge::store_agent(part_ml + head * 2, mm);
+        merge::store_agent(part_ml + head * 2 + 1, l);
+      }
+    }
   }
-  if (tid < g) {
-    const int hs = tid >> 2, i = tid & 3;
-    float mm = kNegBig;
-#pragma unroll
-    for (int w = 0; w < NWV; ++w) mm = fmaxf(mm, s_ml[((w * HS + hs) * 4 + i) * 2]);
-    float ll = 0.f;
-#pragma unroll
-    for (int w = 0; w < NWV; ++w)
-      ll += s_ml[((w * HS + hs) * 4 + i) * 2 + 1] * fast_exp2(s_ml[((w * HS + hs) * 4 + i) * 2] - mm);
-    merge::store_agent(part_ml + tid * 2, mm);
-    merge::store_agent(part_ml + tid * 2 + 1, ll);
-  }
+  if (single) return;
   merge::partial_stores_done();
   __syncthreads();     // every partial store has landed, and nobody reads s_ml / s_acc any more
   merge::arrive_and_merge<NT, 4 * HS>(ma, co.item, co.slot0, co.nslots, g, s_acc);
+}
+
+// End of a chunk: scale the accumulators back (acc_scale = 2^24 where the V codes entered as fp16 subnormals),
+// take the lane's factor kappa = 2^lk out of the running sums, add the offset sums and the two token halves, and merge
+// the workgroup's NWV wavefronts through LDS (store_partial).
+// s_ml: [NWV][4 HS heads][m, l] floats; s_acc: finish_lds_floats(NWV, g) floats.  ALIAS: the two areas overlap LDS that
+// the tile loop used, so a barrier separates the two uses.
+template <int HS, bool ALIAS, int NWV>
+__device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, float lk, int g, float* s_ml,
+                                             float* s_acc, const MergeArgs& ma, const ChunkOut& co) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool upper = lane >= 32;
+  const float inv_kappa = __builtin_ldexpf(1.0f, static_cast<int>(-lk));   // lk is a small integer
+  if constexpr (ALIAS) __syncthreads();
+#pragma unroll
+  for (int hs = 0; hs < HS; ++hs) {
+    run.l[hs] = head_sum(run.l[hs] * inv_kappa);
+    if (lane < 4)
+      *reinterpret_cast<float2*>(s_ml + ((wave * HS + hs) * 4 + lane) * 2) =
+          make_float2(run.m[hs] * kXScale - kPExp, run.l[hs]);      // log2 domain from here on
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int head = 4 * hs + i;
+      // lanes (block, j) hold head i's sum_t p m of channel group j over the block's tokens: all blocks, then to the
+      // lanes of every group
+      const uint32_t ou = __builtin_bit_cast(uint32_t, head_sum(run.offv[hs][i] * inv_kappa));
+      const float o0 = __builtin_bit_cast(float, quad_bcast<0>(ou)), o1 = __builtin_bit_cast(float, quad_bcast<1>(ou));
+      const float o2 = __builtin_bit_cast(float, quad_bcast<2>(ou)), o3 = __builtin_bit_cast(float, quad_bcast<3>(ou));
+      const float v0 = __builtin_fmaf(halves_sum(run.acc[hs][0][i], run.acc[hs][1][i]), acc_scale, upper ? o1 : o0);
+      const float v1 = __builtin_fmaf(halves_sum(run.acc[hs][2][i], run.acc[hs][3][i]), acc_scale, upper ? o3 : o2);
+      if (head < g) {
+        s_acc[(wave * g + head) * kHeadDim + lane] = v0;
+        s_acc[(wave * g + head) * kHeadDim + 64 + lane] = v1;
+      }
+    }
+  }
+  store_partial<HS, NWV>(g, s_ml, s_acc, ma, co);
 }
 
 // A chunk of appended tokens (Sec. 3.3 Zone C: bf16 rows kept after the compression pass) on the same instruction
@@ -377,26 +437,20 @@ __device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, floa
 // bf16 channels 2W, 2W+1) of token r at byte 1024 (W / 4) + 16 r + 4 (W % 4), so a lane (= token) reads its row
 // with sixteen coalesced 16-byte loads; V tile = 16 KiB in the layout of the 16-bit V tiles of mixed mode (lane
 // 32 (r / 32) + c % 32 holds channel c, eight tokens per 16-byte unit u = 4 (c / 32) + (r % 32) / 8 at 1024 u).
-// s_q: LDS for the query operands, [32 steps][HS][4 heads] x 8 bytes (raw bf16; the products are exact).
 template <int HS, bool ALIAS, int NWV>
 __device__ __forceinline__ void process_tail_tiles(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
-                                                   int rows, int g, const uint16_t* __restrict__ q, uint8_t* s_q,
+                                                   int rows, int g, const uint16_t* __restrict__ q,
                                                    float* s_ml, float* s_acc, const MergeArgs& ma,
                                                    const ChunkOut& co) {
-  constexpr int kWG = NWV * 64, kWaves = NWV;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kWaves = NWV;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = lane >> 2, j = lane & 3;
   const int ntiles = (rows + kTile - 1) / kTile;
   constexpr int kTileBytes = kTile * kHeadDim * 2;
-  for (int e = tid; e < 32 * HS * 4; e += kWG) {
-    const int s = e / (HS * 4), hs = (e >> 2) % HS, hj = e & 3;
-    const int head = 4 * hs + hj;
-    uint2 v = make_uint2(0, 0);
-    if (head < g) v = *reinterpret_cast<const uint2*>(q + head * kHeadDim + 4 * s);
-    *reinterpret_cast<uint2*>(s_q + ((s * HS + hs) * 4 + hj) * 8) = v;
-  }
-  __syncthreads();
+  uint4 qa[HS];      // raw bf16: the products are exact
+#pragma unroll
+  for (int hs = 0; hs < HS; ++hs) qa[hs] = load_query(q, 4 * hs + j, g, blk);
   Run<HS> run;
   run.init();
   const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -411,29 +465,27 @@ __device__ __forceinline__ void process_tail_tiles(const uint8_t* __restrict__ k
     floatx4 a16[HS];
 #pragma unroll
     for (int hs = 0; hs < HS; ++hs) a16[hs] = zero4;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int s = 2 * i + half;   // step s = channels 4s .. 4s+3 = words 2s, 2s+1
-        const short4v a = half ? bf4(kq[i].z, kq[i].w) : bf4(kq[i].x, kq[i].y);
-#pragma unroll
-        for (int hs = 0; hs < HS; ++hs) {
-          const uint2 braw = *reinterpret_cast<const uint2*>(s_q + ((s * HS + hs) * 4 + j) * 8);
-          a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, bf4(braw.x, braw.y), a16[hs], 0, 0, 0);
-        }
-      }
-    }
+    // step s = channels 4 s .. 4 s + 3 = words 2 s, 2 s + 1
+#define RDKV_TAIL_K(I_)                                                                                         \
+  _Pragma("unroll") for (int hs = 0; hs < HS; ++hs) {                                                          \
+    a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(bf4(qa[hs].x, qa[hs].y), bf4(kq[I_].x, kq[I_].y), a16[hs], 4, I_, 0); \
+    a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(bf4(qa[hs].z, qa[hs].w), bf4(kq[I_].z, kq[I_].w), a16[hs], 4, I_, 0); \
+  }
+    RDKV_TAIL_K(0) RDKV_TAIL_K(1) RDKV_TAIL_K(2) RDKV_TAIL_K(3) RDKV_TAIL_K(4) RDKV_TAIL_K(5) RDKV_TAIL_K(6)
+    RDKV_TAIL_K(7) RDKV_TAIL_K(8) RDKV_TAIL_K(9) RDKV_TAIL_K(10) RDKV_TAIL_K(11) RDKV_TAIL_K(12) RDKV_TAIL_K(13)
+    RDKV_TAIL_K(14) RDKV_TAIL_K(15)
+#undef RDKV_TAIL_K
     __builtin_amdgcn_sched_barrier(0);   // the K registers are free: the other three channel groups of V
 #pragma unroll
     for (int i = 0; i < 4; ++i) vq[1][i] = *reinterpret_cast<const uint4*>(vp + 1024 * (4 + i));
 #pragma unroll
     for (int i = 0; i < 4; ++i) vq[2][i] = *reinterpret_cast<const uint4*>(vp + 1024 * (8 + i));
-    float x[HS][4];
+    float xt[HS][4], x[HS][4];
 #pragma unroll
     for (int hs = 0; hs < HS; ++hs)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[hs][i] = a16[hs][i] * kKUnit;
+      for (int i = 0; i < 4; ++i) xt[hs][i] = a16[hs][i] * kKUnit;
+    to_head_lanes<HS>(xt, j, x);
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
     softmax_tile<HS>(x, run, p);

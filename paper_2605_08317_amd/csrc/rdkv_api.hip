@@ -1437,7 +1437,7 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
   rdkv_cache::Workspace w;
   const rdkv_status ws = workspace_for(c, st, &w);
   if (ws != RDKV_OK) return ws;
-  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, c->hq, c->hkv};
+  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, c->hq / c->hkv};
   // every chunk of the schedule is launched, the tail's included: chunks of tail rows that do not exist yet find
   // the current length in the cache's device word and contribute an empty partial
   const int n16 = static_cast<int>(c->sched16), nrest = static_cast<int>(c->schedq + c->n_tail_chunks);

@@ -875,6 +875,39 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     total_cost += item_cost[i];
     if (!mixed) cost16 += c->counts[i * 4] * row_cost(i, 16);
   }
+  // Small launches are bound by latencies, not bytes: the tiles that one SIMD goes through one after the other, and the
+  // partials of an item (arrivals queue on one counter, the merge reads them).  Rows per chunk of such a launch: the
+  // multiple of 256 (one tile per SIMD) with the least sum of the two, fitted to (microseconds per launch, caches cold; rows
+  // per item in parentheses, the rows per chunk chosen marked):
+  //   16 MB layer, 40 % 8-bit rows (10000)   256: 12.5   512: 10.7*  768: 11.3   1024: 12.5
+  //   12 MB layer, few 8-bit rows (13000)                512: 11.6   768: 11.2*  1024: 11.6
+  //   keep / 4 bit / evict (16000)                       512: 12.5   768: 11.4*  1024: 11.8
+  //   2 items (3200)                         256:  7.2*  512:  7.8   768:  8.3   1024:  9.2
+  //   8 query heads per KV head (13000)      256: 17.5   512: 14.6*  768: 14.6   1024: 15.2
+  const int64_t floor_bytes = static_cast<int64_t>(wide ? 96 : 48) << 10;
+  int64_t small_rows = 0;
+  if (total_cost > 0 && total_cost <= round_chunks * floor_bytes) {
+    int64_t rows8 = 0, rows_all = 0;
+    for (int64_t i = 0; i < n; ++i)
+      for (int ti = ti0; ti < 4; ++ti) (ti == 1 ? rows8 : rows_all) += c->counts[i * 4 + ti];
+    rows_all += rows8;
+    const double share8 = static_cast<double>(rows8) / static_cast<double>(rows_all);
+    const double per_tile = mixed ? (g > 4 ? 6.0 : 3.0) : (g > 4 ? 1.6 : 1.3) + 1.6 * share8;
+    double best = 0.0;
+    for (int k = 1; k <= 8; k += k < 4 ? 1 : 2) {
+      const uint32_t rows = 256u * static_cast<uint32_t>(k);
+      int64_t n_wg = 0, most = 0;
+      for (int64_t i = 0; i < n; ++i) {
+        int64_t slots = 0;
+        for (int ti = ti0; ti < 4; ++ti) slots += (static_cast<uint32_t>(c->counts[i * 4 + ti]) + rows - 1) / rows;
+        n_wg += slots;
+        most = std::max(most, slots);
+      }
+      const double t = per_tile * k * static_cast<double>((n_wg + 255) / 256) + 0.07 * static_cast<double>(most) +
+                       0.13 * static_cast<double>(std::max<int64_t>(0, most - 14));
+      if (small_rows == 0 || t < best) { small_rows = rows; best = t; }
+    }
+  }
   // Number of chunks a chunk cost of cb gives, and the largest chunk's cost.  Chunks of less than an eighth of cb (a
   // tier with a handful of rows) do not count: they finish at once and leave their workgroup slot to the next chunk
   // (16 channel-wise sequences of 64K tokens: six even chunks per item and one tiny one, 899 in all on 768 slots,
@@ -907,11 +940,11 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // Shares that span tiers pay a start-up per tier (operands rebuilt, the first tiles' latency waited for again):
   // worth it when a chunk streams for tens of microseconds (32 sequences x 128K tokens at 0.4 bit/elt: 101.6 -> 97.6
   // us), not in latency-bound launches (a 16 MB layer: 12.2 -> 13.7 us), which keep one tier per chunk.
-  int64_t chunk_bytes = std::max<int64_t>((wide ? 96 : 48) << 10, total_cost / round_chunks);
+  int64_t chunk_bytes = std::max<int64_t>(floor_bytes, total_cost / round_chunks);
   const bool shares = !mixed && chunk_bytes >= (192 << 10);
   auto count_any = [&](int64_t cb, int64_t* max_cost) { return shares ? count_shares(cb, max_cost) : count_chunks(cb, max_cost); };
   int64_t max_cost = 0, n_one_round = count_any(chunk_bytes, &max_cost);
-  for (int tries = 0; tries < 64 && n_one_round > round_chunks + round_chunks / 50; ++tries) {   // (2 % over is fine)
+  for (int tries = 0; small_rows == 0 && tries < 64 && n_one_round > round_chunks + round_chunks / 50; ++tries) {   // (2 % over is fine)
     chunk_bytes += chunk_bytes / 16 + 1;
     n_one_round = count_any(chunk_bytes, &max_cost);
   }
@@ -919,8 +952,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // chunk more than a fifth above the mean), about two rounds of smaller chunks even things out instead.
   // (Shares are even up to the rounding of an item's share count and stay in one round: 16 ragged sequences at 8
   // query heads per KV head, 728 chunks 52.9 us against 57.6 us for 1529.)
-  if (!shares && (n_one_round > round_chunks + round_chunks / 50 || max_cost * n_one_round > total_cost + total_cost / 5))
-    chunk_bytes = std::max<int64_t>((wide ? 96 : 48) << 10, total_cost / (2 * round_chunks));
+  if (small_rows == 0 && !shares && (n_one_round > round_chunks + round_chunks / 50 || max_cost * n_one_round > total_cost + total_cost / 5))
+    chunk_bytes = std::max<int64_t>(floor_bytes, total_cost / (2 * round_chunks));
   // The row-major 16-bit kernel keeps two workgroups per compute unit resident (70 KB of LDS each): one round of
   // its own.
   const int64_t round16 = 512;
@@ -954,7 +987,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       const int64_t cnt = c->counts[i * 4 + ti];
       if (cnt == 0) continue;
       const int64_t per_row = row_cost(i, bits);
-      const int64_t want = std::max<int64_t>(64, (!mixed && bits == 16 ? chunk_bytes16 : chunk_bytes) / per_row);
+      int64_t want = std::max<int64_t>(64, (!mixed && bits == 16 ? chunk_bytes16 : chunk_bytes) / per_row);
+      if (small_rows > 0 && (mixed || bits != 16)) want = small_rows;
       const int64_t nch = (cnt + want - 1) / want;
       const int64_t rows_per = round_up((cnt + nch - 1) / nch, 64);
       for (int64_t r0 = 0; r0 < cnt; r0 += rows_per) {

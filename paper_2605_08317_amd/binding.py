@@ -131,11 +131,26 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_contiguous()
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# A decode step is one launch of 3 us on the host: what surrounds it must not cost more.  The raw handle of the current
+# stream comes from the bindings below torch.cuda.current_stream(), which builds a Stream object around it (2.9 us, 0.2 so).
+_current_device = torch._C._cuda_getDevice if hasattr(torch._C, "_cuda_getDevice") else None
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+if _current_device is not None and _raw_stream is not None:
+    def _stream():
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return _raw_stream(_current_device())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
+
+
+def _empty_f32(shape, strides, device):
+    return torch.empty_strided(shape, strides, dtype=torch.float32, device=device)      # 1.3 us; torch.empty 1.7
 
 
 def rdkv_version():
@@ -260,9 +275,9 @@ def rdkv_compress(cfg, K, V, Q_obs):
 def rdkv_decode_attn(cache, q, out=None, lse=None):
     cfg = cache.cfg
     if out is None:
-        out = torch.empty((len(cfg.seq_lens), cfg.hq, cfg.d), dtype=torch.float32, device=q.device)
+        out = _empty_f32((len(cfg.seq_lens), cfg.hq, cfg.d), (cfg.hq * cfg.d, cfg.d, 1), q.device)
     if lse is None:
-        lse = torch.empty((len(cfg.seq_lens), cfg.hq), dtype=torch.float32, device=q.device)
+        lse = _empty_f32((len(cfg.seq_lens), cfg.hq), (cfg.hq, 1), q.device)
     _check(lib.rdkv_decode_attn(cache.h, _ptr(q), _ptr(out), _ptr(lse), _stream()))
     return out, lse
 
@@ -285,14 +300,20 @@ def rdkv_cache_tail_len_sync(cache):
     return n.value
 
 
+# what torch.cuda.caching_allocator_alloc / _delete call, without their device guard and Stream object
+_raw_alloc = getattr(torch._C, "_cuda_cudaCachingAllocator_raw_alloc", None) or \
+    (lambda nbytes, stream: torch.cuda.caching_allocator_alloc(nbytes))
+_raw_delete = getattr(torch._C, "_cuda_cudaCachingAllocator_raw_delete", None) or torch.cuda.caching_allocator_delete
+
+
 @_ALLOC_FN
 def _torch_alloc(nbytes, user):
-    return torch.cuda.caching_allocator_alloc(nbytes)
+    return _raw_alloc(nbytes, _stream())
 
 
 @_FREE_FN
 def _torch_free(ptr, user):
-    torch.cuda.caching_allocator_delete(ptr)
+    _raw_delete(ptr)
 
 
 def torch_allocator_hooks():

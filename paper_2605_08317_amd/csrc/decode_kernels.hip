@@ -93,48 +93,46 @@ hipError_t launch_decode_dense_merge(const DenseArgs& a, int g, int n_seqs, hipS
   return hipGetLastError();
 }
 
-// Zone C: one new bf16 K row and V row per item, scattered into the item's tail at the token index held in the
-// cache's device word tail_state[0] (so that a captured launch appends at the right place on every replay).  The
-// tail is kept in the 64-token tiles the decode kernels read (see process_tail_tiles): per item tail_tiles tiles of
-// 16 KiB for K, then (after the K tiles of all items) the same for V.  tail_state[1] counts the workgroups that are
-// done: the last one advances the length and clears the count.  A full tail is left as it is.
+// Zone C: one new bf16 K row and V row per item, scattered into the item's tail at the token index held in the cache's
+// device words (so that a captured launch appends at the right place on every replay).  The tail is kept in the 64-token
+// tiles the decode kernels read (see process_tail_tiles): per item tail_tiles tiles of 16 KiB for K, then (after the K
+// tiles of all items) the same for V.  Every item counts its own rows, so that its workgroup needs no other's consent to
+// advance the count (with one count for all, the last workgroup to arrive at a counter advanced it: 88 ns per item on one
+// address behind a round trip; 2.96 us at 8 items).  The counts are equal; readers take item 0's.  A full tail is left as it is.
 __global__ __launch_bounds__(256) void append_rows_kernel(const uint16_t* __restrict__ k_new,
-                                                          const uint16_t* __restrict__ v_new, uint8_t* __restrict__ tail,
-                                                          int64_t n_items, int32_t tail_tiles, int32_t tail_cap,
-                                                          int32_t* tail_state) {
+                                                          const uint16_t* __restrict__ v_new, int32_t* tail_len,
+                                                          uint8_t* __restrict__ tail, int32_t tail_tiles, int32_t tail_cap,
+                                                          int64_t n_items) {
   const int64_t item = blockIdx.x;
   const int t = threadIdx.x;
-  const int row = __hip_atomic_load(tail_state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int tile = row >> 6, r = row & 63;
   constexpr int kTileBytes = 64 * kHeadDim * 2;
+  const int c = t - 128;   // threads 0..15 take the K row, 128..255 a V channel each; the loads do not wait for the count
+  uint4 k = make_uint4(0, 0, 0, 0);
+  uint16_t v = 0;
+  if (t < 16) k = *reinterpret_cast<const uint4*>(k_new + item * kHeadDim + t * 8);
+  else if (t >= 128) v = v_new[item * kHeadDim + c];
+  const int row = tail_len[item];
+  const int tile = row >> 6, r = row & 63;
   if (row < tail_cap) {
-    if (t < 16) {          // K: words 4t .. 4t+3 of the token's row = 16 bytes at 1024 t + 16 r
-      const uint4 v = *reinterpret_cast<const uint4*>(k_new + item * kHeadDim + t * 8);
+    if (t < 16) {          // words 4t .. 4t+3 of the token's row = 16 bytes at 1024 t + 16 r
       uint8_t* dst = tail + (item * tail_tiles + tile) * static_cast<int64_t>(kTileBytes) + 1024 * t + 16 * r;
-      *reinterpret_cast<uint4*>(dst) = v;
-    } else if (t >= 128) {  // V: channel c of the token: unit u = 4 (c / 32) + (r % 32) / 8, lane 32 (r / 32) + c % 32
-      const int c = t - 128;
+      *reinterpret_cast<uint4*>(dst) = k;
+    } else if (t >= 128) {  // channel c of the token: unit u = 4 (c / 32) + (r % 32) / 8, lane 32 (r / 32) + c % 32
       const int lane = 32 * (r >> 5) + (c & 31), u = 4 * (c >> 5) + ((r & 31) >> 3);
       uint8_t* dst = tail + ((n_items + item) * tail_tiles + tile) * static_cast<int64_t>(kTileBytes) + 1024 * u +
                      16 * lane + 2 * (r & 7);
-      *reinterpret_cast<uint16_t*>(dst) = v_new[item * kHeadDim + c];
+      *reinterpret_cast<uint16_t*>(dst) = v;
     }
   }
-  __syncthreads();         // every thread has read the length (and written its part of the row)
-  if (t == 0) {
-    const int done = __hip_atomic_fetch_add(tail_state + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (done == static_cast<int>(n_items) - 1) {   // every workgroup has read the length: advance it
-      __hip_atomic_store(tail_state + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (row < tail_cap) __hip_atomic_store(tail_state, row + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
+  __syncthreads();         // every thread has read the count
+  if (t == 0 && row < tail_cap) tail_len[item] = row + 1;
 }
 
 hipError_t launch_append_rows(const uint16_t* k_new, const uint16_t* v_new, uint8_t* tail, int64_t n_items,
-                              int32_t tail_tiles, int32_t tail_cap, int32_t* tail_state, hipStream_t st) {
+                              int32_t tail_tiles, int32_t tail_cap, int32_t* tail_len, hipStream_t st) {
   if (n_items == 0) return hipSuccess;
-  hipLaunchKernelGGL(append_rows_kernel, dim3(static_cast<unsigned>(n_items)), dim3(256), 0, st, k_new, v_new, tail,
-                     n_items, tail_tiles, tail_cap, tail_state);
+  hipLaunchKernelGGL(append_rows_kernel, dim3(static_cast<unsigned>(n_items)), dim3(256), 0, st, k_new, v_new, tail_len,
+                     tail, tail_tiles, tail_cap, n_items);
   return hipGetLastError();
 }
 

@@ -211,12 +211,13 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
     const int32_t* __restrict__ tail_len, int first, int g, MergeArgs ma) {
   extern __shared__ __align__(16) uint8_t smem[];
   Chunk ch = chunks[first + blockIdx.x];
+  const int n_tail = *tail_len;      // with the chunk, not after it
   const uint16_t* qp = q + static_cast<int64_t>(ch.item) * g * kHeadDim;     // item = sequence x KV head
   const ChunkOut co{ch.item, ch.slot, ch.slot0, ch.nslots};
   float* s_ml = reinterpret_cast<float*>(smem);   // [NWV][4 HS][2]
   float* s_acc = s_ml + NWV * 4 * HS * 2;           // finish_lds_floats(NWV, g)
   if (ch.tier == kTierTail) {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
-    const int rows = max(0, min(ch.rows, *tail_len - ch.row0));
+    const int rows = max(0, min(ch.rows, n_tail - ch.row0));
     process_tail_tiles<HS, false, NWV>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, s_ml, s_acc, ma, co);
     return;
   }

@@ -288,15 +288,29 @@ hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_
   a.host_blocks = r.blocks;
   a.words = r.words;
   a.seq = r.seq;
-  hipError_t e = launch_copy(a, st);
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (e == hipSuccess && !r.own) e = hipStreamIsCapturing(st, &cap);
+  hipError_t e = hipStreamIsCapturing(st, &cap);
+  const bool captured = cap != hipStreamCaptureStatusNone;
+  if (e == hipSuccess && captured && (!last || r.own)) e = hipErrorStreamCaptureUnsupported;   // the host waits for it
+  if (e == hipSuccess) e = launch_copy(a, st);
   // a captured copy reads the ring at its replay, if ever: nothing to wait for before the bytes are used again
-  if (e != hipSuccess || cap != hipStreamCaptureStatusNone) r.mark_done();
+  if (e != hipSuccess || captured) r.mark_done();
   if (last && r.own) {
     if (e == hipSuccess) e = stage_wait(r, st);
     (void)hipHostFree(r.own);
   }
+  return e;
+}
+
+// Launches a copy, waits for it -- and so for everything queued on the stream before it -- and hands the region to `read`.
+// (A copy to pageable memory and a wait for the stream: 25-35 us beyond the work; so 3-5.)
+template <class Read>
+hipError_t stage_round_trip(CopyArgs& a, int device, const StageRegion& r, hipStream_t st, Read&& read) {
+  hipError_t e = stage_launch(a, r, false, st);
+  if (e == hipSuccess) e = stage_wait(r, st);
+  if (e == hipSuccess) read();
+  g_staging[device].release(r);
+  if (r.own) (void)hipHostFree(r.own);
   return e;
 }
 
@@ -433,7 +447,7 @@ void free_cache_buffers(rdkv_cache* c) {
   put(c->d_chunks);
   for (const rdkv_cache::Workspace& w : c->workspaces) put(w.block);
   c->workspaces.clear();
-  put(c->d_tail_state);
+  put(c->d_tail_len);
   put(c->d_bits_tok);
   put(c->d_bits_ch);
   put(c->d_items_k);
@@ -448,6 +462,20 @@ void free_cache_buffers(rdkv_cache* c) {
     delete child;
   }
   c->absorbed.clear();
+}
+
+// Memory of a split workspace for n_slots partials; the caller clears the arrival counters.
+bool make_workspace(const rdkv_cache* c, hipStream_t st, int64_t n_slots, rdkv_cache::Workspace* w, size_t* arrive_bytes) {
+  Allocator al{c->alloc, c->free_, c->alloc_user};
+  const int g = c->hq / c->hkv;
+  const size_t slots = static_cast<size_t>(std::max<int64_t>(n_slots, 1));
+  const size_t acc_b = slots * g * kHeadDim * sizeof(float), ml_b = (slots * g * 2 * sizeof(float) + 255) / 256 * 256;
+  *arrive_bytes = static_cast<size_t>(std::max<int64_t>(c->n_items, 1)) * sizeof(int32_t);
+  uint8_t* block = static_cast<uint8_t*>(al.get(acc_b + ml_b + *arrive_bytes));
+  if (!block) return false;
+  *w = rdkv_cache::Workspace{st, reinterpret_cast<float*>(block), reinterpret_cast<float*>(block + acc_b),
+                             reinterpret_cast<int32_t*>(block + acc_b + ml_b), block};
+  return true;
 }
 
 // The split workspace of a cache for one stream (created on first use).  Calls on one stream are serialised by
@@ -465,18 +493,12 @@ rdkv_status workspace_for(const rdkv_cache* c, hipStream_t st, rdkv_cache::Works
       return RDKV_OK;
     }
   }
-  Allocator al{c->alloc, c->free_, c->alloc_user};
-  const int g = c->hq / c->hkv;
-  const size_t slots = static_cast<size_t>(std::max<int64_t>(c->n_slots, 1));
-  const size_t acc_b = slots * g * kHeadDim * sizeof(float), ml_b = (slots * g * 2 * sizeof(float) + 255) / 256 * 256;
-  const size_t arr_b = static_cast<size_t>(std::max<int64_t>(c->n_items, 1)) * sizeof(int32_t);
-  uint8_t* block = static_cast<uint8_t*>(al.get(acc_b + ml_b + arr_b));
-  if (!block) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
-  rdkv_cache::Workspace w{st, reinterpret_cast<float*>(block), reinterpret_cast<float*>(block + acc_b),
-                          reinterpret_cast<int32_t*>(block + acc_b + ml_b), block};
-  const hipError_t e = hipMemsetAsync(w.arrive, 0, arr_b, st);     // counters start at zero; the kernels keep them so
+  rdkv_cache::Workspace w;
+  size_t arrive_bytes = 0;
+  if (!make_workspace(c, st, c->n_slots, &w, &arrive_bytes)) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
+  const hipError_t e = hipMemsetAsync(w.arrive, 0, arrive_bytes, st);     // counters start at zero; the kernels keep them so
   if (e != hipSuccess) {
-    al.put(block);
+    Allocator{c->alloc, c->free_, c->alloc_user}.put(w.block);
     return fail(RDKV_ERR_HIP, "clearing a split workspace: %s", hipGetErrorString(e));
   }
   c->workspaces.push_back(w);
@@ -757,15 +779,10 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       CopyArgs a{};
       a.add(d_blk_counts, r.data, n_counts * static_cast<int64_t>(sizeof(int32_t)), true);
       if (mixed) a.add(bits_ch, r.data + counts_b, static_cast<int64_t>(h_bits_ch.size()), true);
-      hipError_t e = stage_launch(a, r, false, st);
-      if (e == hipSuccess) e = stage_wait(r, st);
-      if (e == hipSuccess) {
+      PACK_HIP(stage_round_trip(a, dev, r, st, [&] {
         std::memcpy(h_counts.data(), r.data, h_counts.size() * sizeof(int32_t));
         if (mixed) std::memcpy(h_bits_ch.data(), r.data + counts_b, h_bits_ch.size());
-      }
-      g_staging[dev].release(r);
-      if (r.own) (void)hipHostFree(r.own);
-      PACK_HIP(e);
+      }));
     }
     if (!counted && h_counts[it.n_blocks * 4] != 0)
       return bail(fail(RDKV_ERR_INVALID_ARG, "bits_tok holds a value outside {0, 2, 4, 8, 16}"));
@@ -903,6 +920,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
         n_wg += slots;
         most = std::max(most, slots);
       }
+      if (n_wg > 768 + 4 * n && k < 8) continue;      // more than any launch needs (and cache_max_table_bytes allows for)
       const double t = per_tile * k * static_cast<double>((n_wg + 255) / 256) + 0.07 * static_cast<double>(most) +
                        0.13 * static_cast<double>(std::max<int64_t>(0, most - 14));
       if (small_rows == 0 || t < best) { small_rows = rows; best = t; }
@@ -1068,12 +1086,12 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   c->own_slot_count.assign(slot_count.begin(), slot_count.begin() + n);
 
   // ---- allocate what the cache owns: one block --------------------------------------------
-  // [arena | tail state | arrival counters of this stream's workspace]  (cleared together)
+  // [arena | appended tokens per item | arrival counters of this stream's workspace]  (cleared together)
   // [kept positions | token bit map | channel bit map | K row layouts, chunk table (one copy) | partials | lambda, steps]
   uint32_t* d_krange = nullptr;
   {
     auto up = [](int64_t b) { return round_up(std::max<int64_t>(b, 16), 256); };
-    const int64_t o_state = c->arena_bytes, o_arrive = o_state + 256, o_idx = o_arrive + up(n * 4);
+    const int64_t o_state = c->arena_bytes, o_arrive = o_state + up(n * 4), o_idx = o_arrive + up(n * 4);
     const int64_t o_bt = o_idx + up(kept * 4), o_bc = o_bt + up(it.total_tokens);
     const int64_t o_ik = o_bc + (mixed ? up(n * kHeadDim) : 0);
     const int64_t ik_b = mixed ? round_up(n * static_cast<int64_t>(sizeof(ItemK)), 8) : 0;
@@ -1088,7 +1106,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       return bail(fail(RDKV_ERR_ALLOC, "device allocation of the packed cache failed (%lld bytes)", static_cast<long long>(total)));
     c->block_bytes = total;
     c->d_arena = c->d_block;
-    c->d_tail_state = reinterpret_cast<int32_t*>(c->d_block + o_state);
+    c->d_tail_len = reinterpret_cast<int32_t*>(c->d_block + o_state);
     c->d_tier_idx = reinterpret_cast<int32_t*>(c->d_block + o_idx);
     c->d_bits_tok = c->d_block + o_bt;
     if (mixed) {
@@ -1118,7 +1136,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       CopyArgs a{};
       a.add(plan, d_idx_base, plan_b, true);
       a.add(tables, c->d_block + o_ik, tables_b, true);
-      a.fill(c->d_block + o_state, o_idx - o_state, 0u, 0u);     // tail state, arrival counters
+      a.fill(c->d_block + o_state, o_idx - o_state, 0u, 0u);     // appended tokens, arrival counters
       a.add(bits_tok, c->d_bits_tok, it.total_tokens);
       if (mixed) a.add(bits_ch, c->d_bits_ch, n * kHeadDim);
       if (lam) a.add(lam, c->d_block + o_lam, maps * n * 8);
@@ -1449,7 +1467,7 @@ static size_t cache_max_table_bytes(const rdkv_config* cfg) {
   }
   const double items = static_cast<double>(cfg->batch) * cfg->hkv;
   const double chunks = 2.0 * 768.0 + 8.0 * items;
-  return static_cast<size_t>(4.0 * kept + tokens + items * (kHeadDim + sizeof(ItemK) + 4 + 2 * 12) +
+  return static_cast<size_t>(4.0 * kept + tokens + items * (kHeadDim + sizeof(ItemK) + 8 + 2 * 12) +
                              chunks * (sizeof(Chunk) + g * (kHeadDim + 2) * 4.0) + 16.0 * 256);
 }
 
@@ -1480,7 +1498,7 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
     RDKV_HIP(launch_decode_mixed(c->d_chunks, n16 + nrest, c->d_arena, c->d_items_sched ? c->d_items_sched : c->d_items_k,
                                  std::max(c->max_k_words, c->sched_k_words), std::max(c->max_k_steps, c->sched_k_steps),
                                  std::max(c->max_k_qsteps, c->sched_k_qsteps), static_cast<const uint16_t*>(q), ma,
-                                 c->d_tail_state, c->k_per_unit,
+                                 c->d_tail_len, c->k_per_unit,
                                  std::max(c->max_k_words, c->sched_k_words) <= 32 && c->hq / c->hkv <= 4 ? c->mixed_waves : 4,
                                  st));
     return RDKV_OK;
@@ -1490,7 +1508,7 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
   bool multi = c->n_cont > 0;      // some workgroup goes through more than one tier of its item
   for (const rdkv_cache* child : c->absorbed) multi = multi || child->n_cont > 0;
   RDKV_HIP(launch_decode_tiles(c->d_chunks, n16, nrest, multi, c->d_arena, static_cast<const uint16_t*>(q), ma,
-                               c->d_tail_state, st));
+                               c->d_tail_len, st));
   return RDKV_OK;
 }
 
@@ -1498,8 +1516,9 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
 // 16-bit chunks first, then the quantized ones), then the tail's chunks in (chunk index, item) order so that the
 // live ones are a prefix.  Every item keeps its partial slots contiguous: own chunks, generation by generation,
 // then the tail.  The decode kernels address everything relative to d_arena, so the offsets of the other
-// allocations are pointer differences.  Synchronises the stream; on failure the cache is unchanged.
-static rdkv_status rebuild_schedule(rdkv_cache* c, hipStream_t st) {
+// allocations are pointer differences.  `clear`: memory of the caller's that the same launch clears.  Waits for the stream;
+// on failure the cache is unchanged.
+static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_bytes, hipStream_t st) {
   Allocator al{c->alloc, c->free_, c->alloc_user};
   const int64_t n = c->n_items;
   const int npi = (c->tail_cap + kTailChunkRows - 1) / kTailChunkRows;     // tail chunks per item
@@ -1607,14 +1626,28 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, hipStream_t st) {
     al.put(d_items_sched);
     return fail(RDKV_ERR_ALLOC, "device allocation failed");
   }
-  hipError_t e = hipSuccess;
-  if (n_table > 0) e = upload(d_chunks, table.data(), table.size() * sizeof(Chunk), st);
-  if (e == hipSuccess && d_items_sched)
-    e = upload(d_items_sched, items_sched.data(), items_sched.size() * sizeof(ItemK), st);
-  // the stream must be idle before the old tables and workspaces go: a decode step may still be reading them
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  rdkv_cache::Workspace w;   // this stream's workspace right away: a decode under graph capture then allocates nothing
+  size_t arrive_bytes = 0;
+  const bool have_w = make_workspace(c, st, n_slots, &w, &arrive_bytes);   // (a failure is reported by the decode call that needs it)
+  // tables up, counters and the caller's memory cleared in one launch; the stream must be idle before the old tables and
+  // workspaces go: a decode step may still be reading them
+  const size_t table_b = table.size() * sizeof(Chunk), items_b = items_sched.size() * sizeof(ItemK);
+  StageRegion r;
+  int dev = 0;
+  hipError_t e = stage_acquire(table_b + items_b, true, &r, &dev);
+  if (e == hipSuccess) {
+    if (table_b > 0) std::memcpy(r.data, table.data(), table_b);
+    if (items_b > 0) std::memcpy(r.data + table_b, items_sched.data(), items_b);
+    CopyArgs a{};
+    a.add(r.data, d_chunks, static_cast<int64_t>(table_b), true);
+    a.add(r.data + table_b, d_items_sched, static_cast<int64_t>(items_b), true);
+    a.fill(clear, clear_bytes, 0u, 0u);
+    if (have_w) a.fill(w.arrive, static_cast<int64_t>(arrive_bytes), 0u, 0u);
+    e = stage_round_trip(a, dev, r, st, [] {});
+  }
   if (e != hipSuccess) {
     al.put(d_chunks); al.put(d_items_sched);
+    if (have_w) al.put(w.block);
     return fail(RDKV_ERR_HIP, "rebuilding the decode schedule: %s", hipGetErrorString(e));
   }
   drop_workspaces(c);      // the slot count changed: workspaces are created again on first use
@@ -1635,8 +1668,10 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, hipStream_t st) {
   c->chunks.swap(own);
   c->slot_begin.swap(nb);
   c->slot_count.swap(nc);
-  rdkv_cache::Workspace w;   // this stream's workspace right away: a decode under graph capture then allocates nothing
-  (void)workspace_for(c, st, &w);   // (a failure here is reported by the decode call that needs the workspace)
+  if (have_w) {
+    std::lock_guard<std::mutex> lk(c->ws_mu);
+    c->workspaces.push_back(w);
+  }
   return RDKV_OK;
 }
 
@@ -1651,15 +1686,10 @@ rdkv_status rdkv_cache_reserve_tail(rdkv_cache* c, int32_t max_new_tokens, void*
   const int64_t side = c->n_items * tail_tiles * tile_bytes;     // K tiles of all items, then V tiles
   uint8_t* d_tail = static_cast<uint8_t*>(al.get(2 * side));
   if (!d_tail) return fail(RDKV_ERR_ALLOC, "device allocation failed");
-  hipError_t e = hipMemsetAsync(d_tail, 0, 2 * side, st);   // rows not yet appended must read as zeros
-  if (e != hipSuccess) {
-    al.put(d_tail);
-    return fail(RDKV_ERR_HIP, "rdkv_cache_reserve_tail: %s", hipGetErrorString(e));
-  }
   c->d_tail = d_tail;
   c->tail_cap = max_new_tokens;
   c->tail_len = 0;
-  const rdkv_status s = rebuild_schedule(c, st);
+  const rdkv_status s = rebuild_schedule(c, d_tail, 2 * side, st);     // rows not yet appended must read as zeros
   if (s != RDKV_OK) {
     c->d_tail = nullptr;
     c->tail_cap = 0;
@@ -1675,7 +1705,7 @@ rdkv_status rdkv_cache_append(rdkv_cache* c, const void* k_new, const void* v_ne
     return fail(RDKV_ERR_INVALID_ARG, "the tail is full (%d tokens reserved)", c->tail_cap);
   if (c->n_items == 0) { c->tail_len += 1; return RDKV_OK; }
   RDKV_HIP(launch_append_rows(static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), c->d_tail,
-                              c->n_items, (c->tail_cap + kTile64 - 1) / kTile64, c->tail_cap, c->d_tail_state,
+                              c->n_items, (c->tail_cap + kTile64 - 1) / kTile64, c->tail_cap, c->d_tail_len,
                               static_cast<hipStream_t>(stream)));
   c->tail_len += 1;
   return RDKV_OK;
@@ -1685,12 +1715,14 @@ int32_t rdkv_cache_tail_len(const rdkv_cache* c) { return c ? c->tail_len : 0; }
 
 rdkv_status rdkv_cache_tail_len_sync(rdkv_cache* c, void* stream, int32_t* out) {
   if (!c) return fail(RDKV_ERR_INVALID_ARG, "cache is null");
-  if (c->n_items > 0 && c->d_tail_state) {
+  if (c->n_items > 0 && c->d_tail_len) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int32_t n = 0;
-    RDKV_HIP(hipMemcpyAsync(&n, c->d_tail_state, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    RDKV_HIP(hipStreamSynchronize(st));
-    c->tail_len = n;
+    StageRegion r;
+    int dev = 0;
+    RDKV_HIP(stage_acquire(sizeof(int32_t), true, &r, &dev));
+    CopyArgs a{};
+    a.add(c->d_tail_len, r.data, sizeof(int32_t), true);
+    RDKV_HIP(stage_round_trip(a, dev, r, st, [&] { std::memcpy(&c->tail_len, r.data, sizeof(int32_t)); }));
   }
   if (out) *out = c->tail_len;
   return RDKV_OK;
@@ -1734,15 +1766,13 @@ rdkv_status rdkv_cache_rebudget_tail(rdkv_cache* c, const rdkv_config* cfg, cons
   // The tail's tiles keep the rows just compressed: rows at or past tail_len are masked out of the softmax (their
   // values are finite, so a zero probability times a stale V row adds nothing), and later appends overwrite them.
   c->absorbed.push_back(child);
-  s = rebuild_schedule(c, st);
+  s = rebuild_schedule(c, c->d_tail_len, c->n_items * sizeof(int32_t), st);     // no token appended since
   if (s != RDKV_OK) {
     c->absorbed.pop_back();
     rdkv_cache_free(child);
     return s;
   }
   c->tail_len = 0;
-  const int32_t zeros[2] = {0, 0};
-  RDKV_HIP(upload(c->d_tail_state, zeros, sizeof(zeros), st));
   return RDKV_OK;
 }
 

@@ -102,9 +102,9 @@ struct MergeArgs;   // decode_merge.h
 // 16-bit tier of a token-wise cache (row-major bf16 rows)
 hipError_t launch_decode_tiered_split(const Chunk* chunks, int n_chunks, const uint8_t* arena, const uint16_t* q,
                                       const MergeArgs& ma, hipStream_t st);
-// tail_state: the cache's device words {appended tokens so far, workgroups of the running append that are done}
+// tail_len: the cache's device words, appended tokens so far of every item (equal for all)
 hipError_t launch_append_rows(const uint16_t* k_new, const uint16_t* v_new, uint8_t* tail, int64_t n_items,
-                              int32_t tail_tiles, int32_t tail_cap, int32_t* tail_state, hipStream_t st);
+                              int32_t tail_tiles, int32_t tail_cap, int32_t* tail_len, hipStream_t st);
 hipError_t launch_gather_tail_rows(const uint8_t* tail, int64_t n_items, int32_t tail_tiles, int32_t n,
                                    uint16_t* k_rows, uint16_t* v_rows, hipStream_t st);
 
@@ -177,7 +177,7 @@ struct rdkv_cache {
   mutable std::vector<Workspace> workspaces;
   mutable std::mutex ws_mu;
   int64_t n_slots = 0;                  // partial slots of the whole schedule
-  int32_t* d_tail_state = nullptr;      // {appended tokens so far, workgroups of the running append that are done}
+  int32_t* d_tail_len = nullptr;        // [items]: appended tokens so far (equal for all)
   int32_t mixed_waves = 4;              // channel-wise mode: wavefronts per workgroup of the decode kernel (4 or 8)
   uint8_t* d_bits_tok = nullptr;        // copy of the token bit map
   uint8_t* d_bits_ch = nullptr;         // [items][128] K channel bit map (mixed mode)

@@ -2,60 +2,97 @@
 // counts back into pinned memory, parts of a cache's block copied and cleared.  A launch costs the host 2-3 us whatever it
 // carries; as copies and memsets of the runtime the seven pieces of rdkv_pack took 25 us, and the two-way trip of the
 // tier counts (a copy to pageable memory and a wait for the stream) 25 us beyond the kernels.
+//
+// What bounds it is latency: a read over PCIe takes 1.5 us, so every piece has workgroups of its own (pieces one after the
+// other in each workgroup: 7 us a launch) and nothing is flushed: what goes to host memory goes past the caches, and a wait
+// for the workgroup's own accesses stands in front of the completion word (a system-scope release writes back all of L2).
 #include "rdkv_internal.h"
 
 namespace rdkv {
 
 namespace {
 
+constexpr int kCopyThreads = 256;
+constexpr int kCopyRound = 4 * kCopyThreads;      // 16-byte units of a workgroup's round: four loads in flight per thread
+
 struct __attribute__((packed, aligned(1))) Bytes16 { uint32_t v[4]; };
 
-__global__ __launch_bounds__(1024) void copy_kernel(CopyArgs a) {
-  const int tid = threadIdx.x;
-  for (int k = 0; k < a.n; ++k) {
+// 16 bytes past the caches (system scope), in one store: as four words the lanes' pieces cross PCIe one by one (70 us for 16 KB)
+constexpr int kSystemScope = 17;
+using uint4v = __attribute__((ext_vector_type(4))) unsigned;
+
+__global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
+  const int tid = threadIdx.x, b = blockIdx.x;
+  int k = 0;
+  for (int i = 1; i < a.n; ++i) k += b >= a.first[i];
+  bool host = false;
+  if (a.n > 0) {
     const CopySeg& s = a.seg[k];
-    const int workers = s.host ? a.host_blocks : static_cast<int>(gridDim.x);
-    if (static_cast<int>(blockIdx.x) >= workers) continue;
-    const int64_t n16 = s.bytes / 16, step = static_cast<int64_t>(workers) * 1024;
+    host = s.side != 0;
+    const bool to_host = s.side == kDstHost;
+    const int64_t n16 = s.bytes / 16, step = static_cast<int64_t>(a.first[k + 1] - a.first[k]) * kCopyRound;
     const Bytes16* src = static_cast<const Bytes16*>(s.src);
     Bytes16* dst = static_cast<Bytes16*>(s.dst);
-    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * 1024 + tid; i0 < n16; i0 += 4 * step) {
-      Bytes16 v[4];                        // four loads in flight
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(s.dst, 0, static_cast<int>(n16 * 16), 0x00027000);   // (to_host: < 2 GiB)
+    for (int64_t i0 = static_cast<int64_t>(b - a.first[k]) * kCopyRound + tid; i0 < n16; i0 += step) {
+      Bytes16 v[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         v[u] = Bytes16{{s.fill[0], s.fill[1], s.fill[0], s.fill[1]}};
-        if (s.src && i0 + u * step < n16) v[u] = src[i0 + u * step];
+        if (s.src && i0 + u * kCopyThreads < n16) v[u] = src[i0 + u * kCopyThreads];
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (i0 + u * step < n16) dst[i0 + u * step] = v[u];
+        if (i0 + u * kCopyThreads < n16) {
+          if (to_host)
+            __builtin_amdgcn_raw_buffer_store_b128(uint4v{v[u].v[0], v[u].v[1], v[u].v[2], v[u].v[3]}, rsrc,
+                                                   static_cast<int>(i0 + u * kCopyThreads) * 16, 0, kSystemScope);
+          else
+            dst[i0 + u * kCopyThreads] = v[u];
+        }
     }
     const int tail = static_cast<int>(s.bytes & 15);
-    if (blockIdx.x == 0 && tid < tail) {
+    if (b == a.first[k] && tid < tail) {
       const int64_t at = 16 * n16 + tid;
-      static_cast<uint8_t*>(s.dst)[at] = s.src ? static_cast<const uint8_t*>(s.src)[at]
-                                               : static_cast<uint8_t>(s.fill[(at >> 2) & 1] >> (8 * (at & 3)));
+      const uint8_t v = s.src ? static_cast<const uint8_t*>(s.src)[at] : static_cast<uint8_t>(s.fill[(at >> 2) & 1] >> (8 * (at & 3)));
+      if (to_host) __hip_atomic_store(static_cast<uint8_t*>(s.dst) + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      else static_cast<uint8_t*>(s.dst)[at] = v;
     }
   }
-  if (a.words && static_cast<int>(blockIdx.x) < a.host_blocks) {
-    __threadfence_system();                // everything read from or written to the staging region is done
-    __syncthreads();
-    if (tid == 0) __hip_atomic_store(a.words + blockIdx.x, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (a.words && (host || a.n == 0)) {       // segments with a side in host memory come first: block b owns word b
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                         // everything read from or written to the staging region is done
+    if (tid == 0) __hip_atomic_store(a.words + b, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
 }  // namespace
 
+void plan_copy(CopyArgs& a) {
+  // segments with a host side share the completion words
+  int n_host = 0;
+  int64_t host_bytes = 0;
+  for (int k = 0; k < a.n; ++k)
+    if (a.seg[k].side != 0) { ++n_host; host_bytes += a.seg[k].bytes; }
+  const int64_t least = kCopyRound * 16;
+  int64_t host_part = least;
+  if (n_host > 0) host_part = std::max(least, (host_bytes + kStageWords - n_host - 1) / (kStageWords - n_host));
+  int at = 0;
+  for (int k = 0; k < a.n; ++k) {
+    const CopySeg& s = a.seg[k];
+    a.first[k] = at;
+    const int64_t part = s.side != 0 ? host_part : least;
+    at += static_cast<int>(std::min<int64_t>(std::max<int64_t>((s.bytes + part - 1) / part, 1), 2048));
+    if (s.side != 0) a.host_blocks = at;
+  }
+  a.first[a.n] = at;
+  if (a.n == 0) a.host_blocks = 1;
+}
+
 hipError_t launch_copy(const CopyArgs& a, hipStream_t st) {
   if (a.n == 0 && !a.words) return hipSuccess;
-  int64_t most = 0;
-  for (int k = 0; k < a.n; ++k)
-    if (!a.seg[k].host && a.seg[k].bytes > most) most = a.seg[k].bytes;
-  int64_t blocks = (most + 65535) / 65536;         // four rounds of 16 KB each
-  if (blocks < a.host_blocks) blocks = a.host_blocks;
-  if (blocks > 256) blocks = 256;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(copy_kernel, dim3(static_cast<unsigned>(blocks)), dim3(1024), 0, st, a);
+  const int blocks = a.n == 0 ? 1 : a.first[a.n];
+  hipLaunchKernelGGL(copy_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kCopyThreads), 0, st, a);
   return hipGetLastError();
 }
 

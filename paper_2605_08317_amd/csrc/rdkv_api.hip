@@ -164,15 +164,14 @@ struct StageRegion {
   uint8_t* data = nullptr;        // pinned: what the host fills (or reads)
   uint32_t* words = nullptr;
   uint32_t seq = 0;
-  int blocks = 1;                 // workgroups that announce themselves
   void* own = nullptr;            // not of the ring: an allocation of its own, given back by release()
   bool done() const {
-    for (int i = 0; i < blocks; ++i)
+    for (int i = 0; i < kStageWords; ++i)
       if (__atomic_load_n(words + i, __ATOMIC_ACQUIRE) != seq) return false;
     return true;
   }
   void mark_done() const {        // no kernel will
-    for (int i = 0; i < blocks; ++i) __atomic_store_n(words + i, seq, __ATOMIC_RELEASE);
+    for (int i = 0; i < kStageWords; ++i) __atomic_store_n(words + i, seq, __ATOMIC_RELEASE);
   }
 };
 
@@ -216,8 +215,6 @@ class Staging {
     const size_t need = (kStageHead + bytes + 255) / 256 * 256;
     StageRegion r;
     r.seq = ++seq_ ? seq_ : ++seq_;
-    // 16 KB per workgroup and load round; a handful of them fill the link
-    r.blocks = static_cast<int>(std::min<size_t>(kStageWords, std::max<size_t>(1, bytes >> 15)));
     uint8_t* p = nullptr;
     if (need > kBytes / 2) {        // larger than the ring: memory of its own
       const hipError_t e = hipHostMalloc(&r.own, need, hipHostMallocDefault);
@@ -285,13 +282,14 @@ hipError_t stage_acquire(size_t bytes, bool held, StageRegion* out, int* device)
 // Launches a copy to or from a region.  `last`: the region's only launch and not read by the host; memory that is not of
 // the ring is given back then (after the kernel; the ring looks after itself).
 hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_t st) {
-  a.host_blocks = r.blocks;
+  plan_copy(a);
   a.words = r.words;
   a.seq = r.seq;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   hipError_t e = hipStreamIsCapturing(st, &cap);
   const bool captured = cap != hipStreamCaptureStatusNone;
   if (e == hipSuccess && captured && (!last || r.own)) e = hipErrorStreamCaptureUnsupported;   // the host waits for it
+  for (int i = a.host_blocks; i < kStageWords; ++i) __atomic_store_n(r.words + i, r.seq, __ATOMIC_RELAXED);   // nobody's
   if (e == hipSuccess) e = launch_copy(a, st);
   // a captured copy reads the ring at its replay, if ever: nothing to wait for before the bytes are used again
   if (e != hipSuccess || captured) r.mark_done();
@@ -314,6 +312,16 @@ hipError_t stage_round_trip(CopyArgs& a, int device, const StageRegion& r, hipSt
   return e;
 }
 
+// Waits until everything queued on the stream is done, the caches' write-backs included: a launch that comes after it.
+hipError_t stage_stream_idle(hipStream_t st) {
+  StageRegion r;
+  int dev = 0;
+  const hipError_t e = stage_acquire(0, true, &r, &dev);
+  if (e != hipSuccess) return e;
+  CopyArgs a{};
+  return stage_round_trip(a, dev, r, st, [] {});
+}
+
 // One table to the device; nothing waits (a table larger than half the ring aside).
 hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t st) {
   if (bytes == 0) return hipSuccess;
@@ -323,7 +331,7 @@ hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t st) {
   if (e != hipSuccess) return e;
   std::memcpy(r.data, src, bytes);
   CopyArgs a{};
-  a.add(r.data, dst, static_cast<int64_t>(bytes), true);
+  a.add(r.data, dst, static_cast<int64_t>(bytes), kSrcHost);
   return stage_launch(a, r, true, st);
 }
 
@@ -660,7 +668,7 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
   }
   wblk[it.n_items] = static_cast<int32_t>(n_wblk);
   CopyArgs ca{};
-  ca.add(blob, d, static_cast<int64_t>(bytes), true);
+  ca.add(blob, d, static_cast<int64_t>(bytes), kSrcHost);
   RDKV_HIP(stage_launch(ca, region, true, st));
   out->tok_off = reinterpret_cast<int64_t*>(d);
   out->budget = reinterpret_cast<double*>(d + 8 * n);
@@ -765,6 +773,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
       CopyArgs clear{};
       clear.fill(d_blk_counts + it.n_blocks * 4, sizeof(int32_t), 0u, 0u);
+      plan_copy(clear);
       PACK_HIP(launch_copy(clear, st));
       PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_blk_counts + it.n_blocks * 4,
                                  static_cast<int>(n), it.max_T, st));
@@ -777,8 +786,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       int dev = 0;
       PACK_HIP(stage_acquire(static_cast<size_t>(counts_b) + h_bits_ch.size(), true, &r, &dev));
       CopyArgs a{};
-      a.add(d_blk_counts, r.data, n_counts * static_cast<int64_t>(sizeof(int32_t)), true);
-      if (mixed) a.add(bits_ch, r.data + counts_b, static_cast<int64_t>(h_bits_ch.size()), true);
+      a.add(d_blk_counts, r.data, n_counts * static_cast<int64_t>(sizeof(int32_t)), kDstHost);
+      if (mixed) a.add(bits_ch, r.data + counts_b, static_cast<int64_t>(h_bits_ch.size()), kDstHost);
       PACK_HIP(stage_round_trip(a, dev, r, st, [&] {
         std::memcpy(h_counts.data(), r.data, h_counts.size() * sizeof(int32_t));
         if (mixed) std::memcpy(h_bits_ch.data(), r.data + counts_b, h_bits_ch.size());
@@ -1134,8 +1143,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       if (mixed) std::memcpy(tables, c->items_k.data(), n * sizeof(ItemK));
       if (n_chunks > 0) std::memcpy(tables + ik_b, c->chunks.data(), n_chunks * sizeof(Chunk));
       CopyArgs a{};
-      a.add(plan, d_idx_base, plan_b, true);
-      a.add(tables, c->d_block + o_ik, tables_b, true);
+      a.add(plan, d_idx_base, plan_b, kSrcHost);
+      a.add(tables, c->d_block + o_ik, tables_b, kSrcHost);
       a.fill(c->d_block + o_state, o_idx - o_state, 0u, 0u);     // appended tokens, arrival counters
       a.add(bits_tok, c->d_bits_tok, it.total_tokens);
       if (mixed) a.add(bits_ch, c->d_bits_ch, n * kHeadDim);
@@ -1634,17 +1643,18 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
   const size_t table_b = table.size() * sizeof(Chunk), items_b = items_sched.size() * sizeof(ItemK);
   StageRegion r;
   int dev = 0;
-  hipError_t e = stage_acquire(table_b + items_b, true, &r, &dev);
+  hipError_t e = stage_acquire(table_b + items_b, false, &r, &dev);
   if (e == hipSuccess) {
     if (table_b > 0) std::memcpy(r.data, table.data(), table_b);
     if (items_b > 0) std::memcpy(r.data + table_b, items_sched.data(), items_b);
     CopyArgs a{};
-    a.add(r.data, d_chunks, static_cast<int64_t>(table_b), true);
-    a.add(r.data + table_b, d_items_sched, static_cast<int64_t>(items_b), true);
+    a.add(r.data, d_chunks, static_cast<int64_t>(table_b), kSrcHost);
+    a.add(r.data + table_b, d_items_sched, static_cast<int64_t>(items_b), kSrcHost);
     a.fill(clear, clear_bytes, 0u, 0u);
     if (have_w) a.fill(w.arrive, static_cast<int64_t>(arrive_bytes), 0u, 0u);
-    e = stage_round_trip(a, dev, r, st, [] {});
+    e = stage_launch(a, r, true, st);
   }
+  if (e == hipSuccess) e = stage_stream_idle(st);
   if (e != hipSuccess) {
     al.put(d_chunks); al.put(d_items_sched);
     if (have_w) al.put(w.block);
@@ -1721,7 +1731,7 @@ rdkv_status rdkv_cache_tail_len_sync(rdkv_cache* c, void* stream, int32_t* out) 
     int dev = 0;
     RDKV_HIP(stage_acquire(sizeof(int32_t), true, &r, &dev));
     CopyArgs a{};
-    a.add(c->d_tail_len, r.data, sizeof(int32_t), true);
+    a.add(c->d_tail_len, r.data, sizeof(int32_t), kDstHost);
     RDKV_HIP(stage_round_trip(a, dev, r, st, [&] { std::memcpy(&c->tail_len, r.data, sizeof(int32_t)); }));
   }
   if (out) *out = c->tail_len;

@@ -59,27 +59,31 @@ struct ItemK {
   int16_t slot_ch[kMaxSlots];    // channel held by a slot, -1 for padding
 };
 
-// One launch of small copies (copy_kernels.hip).
+// One launch of small copies (copy_kernels.hip).  Segments with a side in staging memory are added first.
 constexpr int kStageWords = 16;        // completion words at the head of a staging region
+enum : int32_t { kSrcHost = 1, kDstHost = 2 };
 struct CopySeg {
   const void* src;                     // null: fill with the two words of `fill`
   void* dst;
   int64_t bytes;
   uint32_t fill[2];
-  int32_t host;                        // one side is staging memory: only the first host_blocks workgroups take part
+  int32_t side;                        // kSrcHost or kDstHost: that side is staging memory; 0: both are device memory
 };
 struct CopyArgs {
-  CopySeg seg[8];
-  int32_t n, host_blocks;
+  int32_t n;
+  int32_t first[9];                    // first workgroup of a segment (plan_copy)
   uint32_t* words;                     // completion words of the staging region, or null
   uint32_t seq;
-  void add(const void* src, void* dst, int64_t bytes, bool host = false) {
-    if (bytes > 0) seg[n++] = CopySeg{src, dst, bytes, {0u, 0u}, host ? 1 : 0};
+  int32_t host_blocks;                 // workgroups that set a word (plan_copy)
+  CopySeg seg[8];
+  void add(const void* src, void* dst, int64_t bytes, int32_t side = 0) {
+    if (bytes > 0) seg[n++] = CopySeg{src, dst, bytes, {0u, 0u}, side};
   }
   void fill(void* dst, int64_t bytes, uint32_t w0, uint32_t w1) {
     if (bytes > 0) seg[n++] = CopySeg{nullptr, dst, bytes, {w0, w1}, 0};
   }
 };
+void plan_copy(CopyArgs& a);           // after the last segment, before launch_copy
 hipError_t launch_copy(const CopyArgs& a, hipStream_t st);
 
 struct DenseArgs {

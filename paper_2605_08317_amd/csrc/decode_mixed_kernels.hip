@@ -43,9 +43,12 @@ struct LdsPlan {
   __host__ __device__ LdsPlan(int n_steps, int n_qsteps, int hs, int g, int kWaves) {
     qpre = 0;
     qraw = qpre + n_steps * hs * 32;
-    wtab = qraw + n_qsteps * hs * 32;
-    wtab_wave = (2 * n_qsteps + 1) * hs * 64;   // one entry of padding: the step loop reads one entry ahead
-    const int tables = wtab + kWaves * wtab_wave;
+    // the step loop reads entries in fours, aligned to the word index, and one four ahead: up to three entries in front of
+    // a table and seven behind it are read (never used)
+    wtab = (qraw + n_qsteps * hs * 32 + 63) / 64 * 64 + 3 * hs * 64;
+    wtab_wave = 2 * n_qsteps * hs * 64;
+    int tables = wtab + kWaves * wtab_wave + 8 * hs * 64;
+    if (tables < wtab + g * kHeadDim * 2) tables = wtab + g * kHeadDim * 2;     // the query rows, before there are tables
     const int merge = kWaves * 4 * hs * 2 * 4 + finish_lds_floats(kWaves, g) * 4;
     total = tables > merge ? tables : merge;
   }
@@ -139,20 +142,32 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
       if (sq < nqs) kmeta[it] = *reinterpret_cast<const uint4*>(km + sq * 16);
     }
   }
+  // Loads return in order: what the query operands are made of goes ahead of the tiles, and the query rows pass through LDS
+  // instead of being gathered from memory by the channel numbers once those have arrived (one round trip fewer).
+  const int n_elems = n_steps * HS * 4;
+  uint4 qrow = make_uint4(0, 0, 0, 0);
+  if (tid < g * (kHeadDim / 8)) qrow = *reinterpret_cast<const uint4*>(q + 8 * tid);
+  struct __attribute__((packed, aligned(2))) Slots { uint32_t x, y; };      // four channel numbers
+  Slots slots{0, 0};
+  if (tid < n_elems) slots = *reinterpret_cast<const Slots*>(ikp->slot_ch + 4 * (tid / (HS * 4)));
   if (wave < ntiles) {
     load_k(wave);
     load_v(wave);
   }
+  uint16_t* s_qrow = reinterpret_cast<uint16_t*>(smem + plan.wtab);
+  if (tid < g * (kHeadDim / 8)) *reinterpret_cast<uint4*>(s_qrow + 8 * tid) = qrow;
+  __syncthreads();
 
   // ---- query operands per step (once per workgroup) ---------------------------------------------------------
-  for (int e = tid; e < n_steps * HS * 4; e += kWG) {
+  for (int e = tid; e < n_elems; e += kWG) {
     const int s = e / (HS * 4), hs = (e >> 2) % HS, hj = e & 3;
     const int head = 4 * hs + hj;
+    if (e != tid) slots = *reinterpret_cast<const Slots*>(ikp->slot_ch + 4 * s);
     float v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int c = ikp->slot_ch[4 * s + k];
-      v[k] = (c >= 0 && head < g) ? __uint_as_float(static_cast<uint32_t>(q[head * kHeadDim + c]) << 16) : 0.f;
+      const int c = static_cast<int16_t>((k < 2 ? slots.x : slots.y) >> (16 * (k & 1)));
+      v[k] = (c >= 0 && head < g) ? __uint_as_float(static_cast<uint32_t>(s_qrow[head * kHeadDim + c]) << 16) : 0.f;
     }
     uint2 out;
     if (s < ns16) {   // raw bf16
@@ -240,8 +255,7 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
         kk += dpp_f32<0x4E>(ss);   // quad_perm [2, 3, 0, 1]
         kk += dpp_f32<0x124>(kk);  // row_ror:4
         kk += dpp_f32<0x128>(kk);  // row_ror:8
-        kk += __shfl_xor(kk, 16);
-        bias[hs] = kk;
+        bias[hs] = sum_xor16(kk);
       }
     }
     wave_lds_sync();
@@ -263,86 +277,97 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
       // evaluated ahead of the tile loop and kept in scalar registers (thousands of spills).
       int t16 = e16, t8 = e8, t4 = e4, t2 = e2;
       asm volatile("" : "+s"(t16), "+s"(t8), "+s"(t4), "+s"(t2));
+      // The scaled query is the A operand: the lanes of block b hold the entry of step b % 4 of a group of four steps, and a
+      // product broadcasts the block of its step over its four blocks (cbsz = 2; the token group of a lane half is its
+      // own).  One LDS read per lane serves four steps (read on the B side by every lane for every step, the reads and
+      // their waits made 30 of a tile's 450 instructions and most of a lone tile's latency).  Groups are aligned to the
+      // word index, which is a compile-time constant where it is used; the next group is read ahead.
       // table address of word w's first step = tier base + w * (steps per word) * HS * 64
-      const uint8_t* wt = s_wtab + G * nqs * HS * 64 + j * 16;
+      const uint8_t* wt = s_wtab + (G * nqs + (blk & 3)) * (HS * 64) + j * 16;
       const uint8_t* wt8 = wt - t16 * (HS * 64);
       const uint8_t* wt4 = wt + ((t8 - t16) - 2 * t8) * (HS * 64);
       const uint8_t* wt2 = wt + ((t8 - t16) + 2 * (t4 - t8) - 4 * t4) * (HS * 64);
-      // The quantized steps of a row (8-, 4-, then 2-bit words) are consecutive entries of the table.  With one
-      // head set every step asks for the next entry before its own products, so that they cover the LDS latency
-      // (the entry after the last step is padding); with two head sets those registers would spill.
-      constexpr bool kAhead = HS == 1;
-      uint4 bq[HS];
-      if constexpr (kAhead) {
+      uint4 cur[HS], nxt[HS];
 #pragma unroll
-        for (int hs = 0; hs < HS; ++hs) bq[hs] = *reinterpret_cast<const uint4*>(wt + hs * 64);
-      }
-      auto qstep = [&](const Pack4& a, const uint8_t* o) __attribute__((always_inline)) {
-        uint4 nx[HS];
+      for (int hs = 0; hs < HS; ++hs) cur[hs] = nxt[hs] = make_uint4(0, 0, 0, 0);
+      auto read_group = [&](uint4 (&dst)[HS], const uint8_t* o) __attribute__((always_inline)) {
 #pragma unroll
-        for (int hs = 0; hs < HS; ++hs) {
-          if constexpr (kAhead) nx[hs] = *reinterpret_cast<const uint4*>(o + (HS + hs) * 64);
-          else bq[hs] = *reinterpret_cast<const uint4*>(o + hs * 64);
-        }
+        for (int hs = 0; hs < HS; ++hs) dst[hs] = *reinterpret_cast<const uint4*>(o + hs * 64);
+      };
+      // before a tier's words [first, ..): spw steps per word, groups of wpg = 4 / spw words
+      auto enter_tier = [&](const uint8_t* t, int first, int spw) __attribute__((always_inline)) {
+        const int wpg = 4 / spw, fa = first & ~(wpg - 1);
+        if (spw != 4) read_group(cur, t + spw * fa * (HS * 64));
+        read_group(nxt, t + spw * (fa == first ? first : fa + wpg) * (HS * 64));
+      };
+      auto qstep = [&](const Pack4& b, auto ab) __attribute__((always_inline)) {
 #pragma unroll
         for (int hs = 0; hs < HS; ++hs) {
-          Pack4 bh, bl;
-          bh.u[0] = bq[hs].x; bh.u[1] = bq[hs].y;
-          bl.u[0] = bq[hs].z; bl.u[1] = bq[hs].w;
-          aqh[hs] = __builtin_amdgcn_mfma_f32_4x4x4f16(a.h, bh.h, aqh[hs], 0, 0, 0);
-          aql[hs] = __builtin_amdgcn_mfma_f32_4x4x4f16(a.h, bl.h, aql[hs], 0, 0, 0);
-        }
-        if constexpr (kAhead) {
-#pragma unroll
-          for (int hs = 0; hs < HS; ++hs) bq[hs] = nx[hs];
+          Pack4 ah, al;
+          ah.u[0] = cur[hs].x; ah.u[1] = cur[hs].y;
+          al.u[0] = cur[hs].z; al.u[1] = cur[hs].w;
+          aqh[hs] = __builtin_amdgcn_mfma_f32_4x4x4f16(ah.h, b.h, aqh[hs], 2, decltype(ab)::value, 0);
+          aql[hs] = __builtin_amdgcn_mfma_f32_4x4x4f16(al.h, b.h, aql[hs], 2, decltype(ab)::value, 0);
         }
       };
+      auto next_group = [&](const uint8_t* o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int hs = 0; hs < HS; ++hs) cur[hs] = nxt[hs];
+        read_group(nxt, o);
+      };
       // one word of each tier; the word index is a compile-time constant (registers cannot be indexed at run time)
+      uint2 q16[HS];
+#pragma unroll
+      for (int hs = 0; hs < HS; ++hs) q16[hs] = make_uint2(0, 0);
       auto body16 = [&](auto wc) __attribute__((always_inline)) {   // a 16-bit step = two words = four bf16
         constexpr int w = decltype(wc)::value;
         if constexpr ((w & 1) == 0 && w + 1 < NW) {
+          if constexpr ((w & 7) == 0) {
+#pragma unroll
+            for (int hs = 0; hs < HS; ++hs)
+              q16[hs] = *reinterpret_cast<const uint2*>(s_qpre + ((((w >> 1) + (blk & 3)) * HS + hs) * 4 + j) * 8);
+          }
           // the two words pass through an empty asm: read as one 8-byte vector straight from kw[], the pair would
           // keep the whole array out of registers (scalar replacement gives up on mixed-width accesses)
           uint32_t lo = kw[w], hi = kw[w + 1];
           asm("" : "+v"(lo), "+v"(hi));
-          const short4v a = bf4(lo, hi);
+          const short4v b = bf4(lo, hi);
 #pragma unroll
-          for (int hs = 0; hs < HS; ++hs) {
-            const uint2 braw = *reinterpret_cast<const uint2*>(s_qpre + (((w >> 1) * HS + hs) * 4 + j) * 8);
-            a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, bf4(braw.x, braw.y), a16[hs], 0, 0, 0);
-          }
+          for (int hs = 0; hs < HS; ++hs)
+            a16[hs] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(bf4(q16[hs].x, q16[hs].y), b, a16[hs], 2, (w >> 1) & 3, 0);
         }
       };
       auto body8 = [&](auto wc) __attribute__((always_inline)) {
         constexpr int w = decltype(wc)::value;
-        Pack4 a;
-        a.u[0] = __builtin_amdgcn_perm(0u, kw[w], 0x0C020C00u);
-        a.u[1] = __builtin_amdgcn_perm(0u, kw[w], 0x0C030C01u);
-        qstep(a, wt8 + w * (HS * 64));
+        if constexpr ((w & 3) == 0) next_group(wt8 + (w + 4) * (HS * 64));
+        Pack4 b;
+        b.u[0] = __builtin_amdgcn_perm(0u, kw[w], 0x0C020C00u);
+        b.u[1] = __builtin_amdgcn_perm(0u, kw[w], 0x0C030C01u);
+        qstep(b, GroupIndex<(w & 3)>{});
       };
       auto body4 = [&](auto wc) __attribute__((always_inline)) {
         constexpr int w = decltype(wc)::value;
+        if constexpr ((w & 1) == 0) next_group(wt4 + 2 * (w + 2) * (HS * 64));
         const uint32_t c0 = kw[w], c1 = c0 >> 8;
-        const uint8_t* o = wt4 + 2 * w * (HS * 64);
-        Pack4 a;
-        a.u[0] = c0 & 0x000F000Fu; a.u[1] = c0 & 0x00F000F0u;
-        qstep(a, o);
-        a.u[0] = c1 & 0x000F000Fu; a.u[1] = c1 & 0x00F000F0u;
-        qstep(a, o + HS * 64);
+        Pack4 b;
+        b.u[0] = c0 & 0x000F000Fu; b.u[1] = c0 & 0x00F000F0u;
+        qstep(b, GroupIndex<(2 * w & 3)>{});
+        b.u[0] = c1 & 0x000F000Fu; b.u[1] = c1 & 0x00F000F0u;
+        qstep(b, GroupIndex<(2 * w & 3) + 1>{});
       };
       auto body2 = [&](auto wc) __attribute__((always_inline)) {
         constexpr int w = decltype(wc)::value;
+        next_group(wt2 + 4 * (w + 1) * (HS * 64));
         const uint32_t c0 = kw[w], c1 = c0 >> 6, c2 = c0 >> 12;
-        const uint8_t* o = wt2 + 4 * w * (HS * 64);
-        Pack4 a;
-        a.u[0] = c0 & 0x00030003u; a.u[1] = c0 & 0x000C000Cu;     // fields 0, 1
-        qstep(a, o);
-        a.u[0] = c0 & 0x00300030u; a.u[1] = c1 & 0x00030003u;     // fields 2, 3
-        qstep(a, o + HS * 64);
-        a.u[0] = c1 & 0x000C000Cu; a.u[1] = c1 & 0x00300030u;     // fields 4, 5
-        qstep(a, o + 2 * HS * 64);
-        a.u[0] = c2 & 0x00030003u; a.u[1] = c2 & 0x000C000Cu;     // fields 6, 7
-        qstep(a, o + 3 * HS * 64);
+        Pack4 b;
+        b.u[0] = c0 & 0x00030003u; b.u[1] = c0 & 0x000C000Cu;     // fields 0, 1
+        qstep(b, GroupIndex<0>{});
+        b.u[0] = c0 & 0x00300030u; b.u[1] = c1 & 0x00030003u;     // fields 2, 3
+        qstep(b, GroupIndex<1>{});
+        b.u[0] = c1 & 0x000C000Cu; b.u[1] = c1 & 0x00300030u;     // fields 4, 5
+        qstep(b, GroupIndex<2>{});
+        b.u[0] = c2 & 0x00030003u; b.u[1] = c2 & 0x000C000Cu;     // fields 6, 7
+        qstep(b, GroupIndex<3>{});
       };
       // A tier is a run of consecutive words [first, end): jump to its first word and fall through word by word
       // until the end (one uniform comparison per word; a test of every word against every tier costs several
@@ -365,18 +390,32 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
     default: break;                                                                                           \
   }
       RDKV_K_TIER(body16, 0, t16)
-      RDKV_K_TIER(body8, t16, t8)
-      RDKV_K_TIER(body4, t8, t4)
-      RDKV_K_TIER(body2, t4, t2)
+      if (t16 < t8) {
+        enter_tier(wt8, t16, 1);
+        RDKV_K_TIER(body8, t16, t8)
+      }
+      if (t8 < t4) {
+        enter_tier(wt4, t8, 2);
+        RDKV_K_TIER(body4, t8, t4)
+      }
+      if (t4 < t2) {
+        enter_tier(wt2, t4, 4);
+        RDKV_K_TIER(body2, t4, t2)
+      }
 #undef RDKV_K_TIER
 #undef RDKV_K_CASE16
 #undef RDKV_K_CASE4
 #undef RDKV_K_CASE
+      float xt[HS][4];      // lane = token, i = head
 #pragma unroll
       for (int hs = 0; hs < HS; ++hs)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          x[hs][i] = __builtin_fmaf(a16[hs][i], kKUnit, aqh[hs][i] + aql[hs][i]) + bias[hs] * (1.0f / 16777216.0f);
+        for (int i = 0; i < 4; ++i) xt[hs][i] = __builtin_fmaf(a16[hs][i], kKUnit, aqh[hs][i] + aql[hs][i]);
+      to_head_lanes<HS>(xt, j, x);
+#pragma unroll
+      for (int hs = 0; hs < HS; ++hs)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[hs][i] += bias[hs] * (1.0f / 16777216.0f);
     }
     if (more) load_k(next);   // K registers are free again
 

@@ -901,26 +901,36 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     total_cost += item_cost[i];
     if (!mixed) cost16 += c->counts[i * 4] * row_cost(i, 16);
   }
-  // Small launches are bound by latencies, not bytes: the tiles that one SIMD goes through one after the other, and the
-  // partials of an item (arrivals queue on one counter, the merge reads them).  Rows per chunk of such a launch: the
-  // multiple of 256 (one tile per SIMD) with the least sum of the two, fitted to (microseconds per launch, caches cold; rows
-  // per item in parentheses, the rows per chunk chosen marked):
-  //   16 MB layer, 40 % 8-bit rows (10000)   256: 12.5   512: 10.7*  768: 11.3   1024: 12.5
-  //   12 MB layer, few 8-bit rows (13000)                512: 11.6   768: 11.2*  1024: 11.6
-  //   keep / 4 bit / evict (16000)                       512: 12.5   768: 11.4*  1024: 11.8
-  //   2 items (3200)                         256:  7.2*  512:  7.8   768:  8.3   1024:  9.2
-  //   8 query heads per KV head (13000)      256: 17.5   512: 14.6*  768: 14.6   1024: 15.2
+  // Small launches are bound by latencies, not bytes: the rounds of workgroups, the tiles that one SIMD goes through one
+  // after the other, and the partials of an item (arrivals queue on one counter, the merge reads them).  Rows per chunk of
+  // such a launch: the multiple of 256 (one tile per SIMD) with the least sum of the three, fitted to these times
+  // (microseconds per launch, caches cold; rows per item in parentheses, the rows per chunk chosen marked; "old": chunks of
+  // at least 96 KB, or 48):
+  //   16 MB layer, 40 % 8-bit rows (10000)   256: 12.5   512: 10.7*  768: 11.3   1024: 12.5               old: 11.1
+  //   12 MB layer, no 8-bit rows (13000)                 512: 11.6   768: 11.2*  1024: 11.6               old: 11.6
+  //   keep / 4 bit / evict (16000)                       512: 12.5   768: 11.4*  1024: 11.8               old: 11.8
+  //   2 items (3200)                         256:  7.2*  512:  7.8   768:  8.3   1024:  9.2               old:  9.2
+  //   8 query heads per KV head (13000)      256: 17.5   512: 14.6*  768: 14.6   1024: 15.2               old: 15.6
+  //   8 items (52000)                                    512: 25.1   768: 22.7   1024: 18.9  2048: 17.4*  old: 18.9
+  //   8 items (78000)                                    1024: 25.6  1536: 22.6  2048: 25.0  3072: 21.6*  old: 24.3
+  // Token-wise launches above that size are cut by bytes (below) unless they are a few long items of narrow rows: with
+  // many items or 8-bit rows the bytes' balance matters more (8 ragged sequences 16.4 us by bytes, 17.6 so).
   const int64_t floor_bytes = static_cast<int64_t>(wide ? 96 : 48) << 10;
   int64_t small_rows = 0;
-  if (total_cost > 0 && total_cost <= round_chunks * floor_bytes) {
-    int64_t rows8 = 0, rows_all = 0;
-    for (int64_t i = 0; i < n; ++i)
-      for (int ti = ti0; ti < 4; ++ti) (ti == 1 ? rows8 : rows_all) += c->counts[i * 4 + ti];
-    rows_all += rows8;
-    const double share8 = static_cast<double>(rows8) / static_cast<double>(rows_all);
+  // (eight-wavefront workgroups of the channel-wise kernel: one per compute unit, so that a few more than 256 double the
+  // time; 23 MB of one 64K sequence 512: 26.0, 768: 30.2, 1024: 19.0*, 1536: 21.4)
+  int64_t rows8 = 0, rows_all = 0;
+  for (int64_t i = 0; i < n; ++i)
+    for (int ti = ti0; ti < 4; ++ti) (ti == 1 ? rows8 : rows_all) += c->counts[i * 4 + ti];
+  rows_all += rows8;
+  const double share8 = static_cast<double>(rows8) / static_cast<double>(std::max<int64_t>(rows_all, 1));
+  if (total_cost > 0 && (mixed ? mixed_wide || total_cost <= round_chunks * floor_bytes
+                               : total_cost <= round_chunks * floor_bytes ||
+                                     (share8 < 0.2 && n <= 16 && total_cost < round_chunks * (192 << 10)))) {
     const double per_tile = mixed ? (g > 4 ? 6.0 : 3.0) : (g > 4 ? 1.6 : 1.3) + 1.6 * share8;
+    constexpr int kMostTiles = 16;
     double best = 0.0;
-    for (int k = 1; k <= 8; k += k < 4 ? 1 : 2) {
+    for (int k = 1; k <= kMostTiles; k += k < 4 ? 1 : k < 8 ? 2 : 4) {
       const uint32_t rows = 256u * static_cast<uint32_t>(k);
       int64_t n_wg = 0, most = 0;
       for (int64_t i = 0; i < n; ++i) {
@@ -929,9 +939,11 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
         n_wg += slots;
         most = std::max(most, slots);
       }
-      if (n_wg > 768 + 4 * n && k < 8) continue;      // more than any launch needs (and cache_max_table_bytes allows for)
-      const double t = per_tile * k * static_cast<double>((n_wg + 255) / 256) + 0.07 * static_cast<double>(most) +
-                       0.13 * static_cast<double>(std::max<int64_t>(0, most - 14));
+      if (n_wg > 768 + 4 * n && k < kMostTiles) continue;      // more than any launch needs (and cache_max_table_bytes allows for)
+      const double rounds = static_cast<double>((n_wg + round_chunks - 1) / round_chunks);
+      const double at_once = static_cast<double>(most) / rounds;
+      const double t = 6.5 * rounds + per_tile * k * static_cast<double>((n_wg + 255) / 256) + 0.07 * at_once +
+                       0.09 * std::max(0.0, at_once - 14.0);
       if (small_rows == 0 || t < best) { small_rows = rows; best = t; }
     }
   }

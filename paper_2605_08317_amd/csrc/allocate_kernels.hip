@@ -122,7 +122,7 @@ __host__ __device__ constexpr int hist_slot(int b) { return b + (b >> 5); }
 
 // Histogram over the fp32 patterns of the positive units, ascending; suffix[b] = units in buckets >= b,
 // suffix[BUCKETS] = 0.  bucket() is monotone in the unit.
-//   anchored: 256 buckets per factor of two below the largest unit's pattern (everything 2^-32 below it in bucket 0)
+// 256 buckets per factor of two below the largest unit's pattern (everything 2^-32 below it in bucket 0).
 struct Anchored {
   static constexpr int kBuckets = 8192, kShift = 15, kWords = (hist_slot(kBuckets) + 4) / 4 * 4;
   uint32_t top;                // pattern of the largest unit
@@ -139,16 +139,6 @@ struct Anchored {
     return d >= top ? 0u : top - d;
   }
 };
-//   full range: 64 buckets per factor of two
-struct FullRange {
-  static constexpr int kBuckets = 32768, kShift = 16, kWords = (hist_slot(kBuckets) + 4) / 4 * 4;
-  __device__ __forceinline__ int bucket(uint32_t u) const { return static_cast<int>(min(u, 0x7F7FFFFFu) >> kShift); }
-  __device__ __forceinline__ uint32_t lowest(int b) const { return static_cast<uint32_t>(b) << kShift; }
-  __device__ __forceinline__ uint32_t highest(int b) const {    // (infinity counts to the last bucket)
-    return b >= bucket(0x7F7FFFFFu) ? 0x7F800000u : ((static_cast<uint32_t>(b) + 1u) << kShift) - 1u;
-  }
-};
-
 // Steps of the search that the histogram decides, by one wavefront; returns with done set, max_iters reached or
 // standing before a step it cannot decide.
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
@@ -215,6 +205,25 @@ __device__ __forceinline__ void steps_on_histogram(const Problem& P, const Map& 
   }
 }
 
+// Where the search goes on after a step the histogram cannot decide, whichever way that step comes out: [lo, hi] contains
+// its multiplier and every later one the histogram cannot decide either; a later multiplier above hi is feasible (and not
+// inside the band), one below lo over budget.  A step can be undecided early, with a wide bracket, when its multiplier
+// happens to lie next to the final one; the buckets open to the whole bracket then hold thousands of units (a gather of
+// 13 us took 47), those open to [lo, hi] a few.
+struct Hull { double lo, hi; };
+__device__ __forceinline__ Hull bracket_of(const Search& S) { return Hull{S.lo, S.hi}; }
+template <class Map>
+__device__ __forceinline__ Hull narrow_hull(const Problem& P, const Map& map, const int* suffix, const Search& S) {
+  const double lam = (S.lo + S.hi) * 0.5;
+  Search over = S, feasible = S;
+  over.take(0, lam);
+  feasible.take(1, lam);
+  steps_on_histogram(P, map, suffix, over);
+  steps_on_histogram(P, map, suffix, feasible);
+  return Hull{feasible.lo, over.hi};
+}
+constexpr int kFewOpen = 1024;       // open units that a single wavefront takes the remaining steps on
+
 // In place: suffix[b] = sum of suffix[b ..]; suffix[BUCKETS] = 0.  All threads; barriers inside.
 template <int BUCKETS>
 __device__ __forceinline__ void suffix_sums(int* suffix, int* s_wave) {
@@ -246,19 +255,19 @@ __device__ __forceinline__ void suffix_sums(int* suffix, int* s_wave) {
   __syncthreads();
 }
 
-// The buckets that a threshold lam r_k can reach for lam in the bracket [lo, hi]: up to four disjoint ranges (rounded
+// The buckets that a threshold lam r_k can reach for lam in [h.lo, h.hi]: up to four disjoint ranges (rounded
 // products and the bucket are monotone).  Units of other buckets keep their side of every threshold.
 struct OpenBuckets {
   int a[kThr], b[kThr];            // range k: buckets a[k] .. b[k], empty when a[k] > b[k]
   __device__ __forceinline__ OpenBuckets() {}
   template <class Map>
-  __device__ __forceinline__ OpenBuckets(const Problem& P, const Map& map, double lo, double hi) {
+  __device__ __forceinline__ OpenBuckets(const Problem& P, const Map& map, const Hull& h) {
     int prev = -1;
 #pragma unroll
     for (int k = 0; k < kThr; ++k) {
       const bool used = k < P.nh - 1;
-      b[k] = used ? min(map.bucket(__float_as_uint(P.thr(hi, k))), Map::kBuckets - 1) : prev;
-      a[k] = used ? max(map.bucket(__float_as_uint(P.thr(lo, k))), prev + 1) : prev + 1;
+      b[k] = used ? min(map.bucket(__float_as_uint(P.thr(h.hi, k))), Map::kBuckets - 1) : prev;
+      a[k] = used ? max(map.bucket(__float_as_uint(P.thr(h.lo, k))), prev + 1) : prev + 1;
       prev = max(prev, b[k]);
     }
   }
@@ -307,11 +316,16 @@ struct OpenPatterns {
 
 // The remaining steps, exactly, on n undecided units in LDS beside the decided ones' bit sum `fixed`.
 // All threads; S is the same in all of them on entry and exit.  s_red: 2 kWaves ints.
-__device__ __forceinline__ void steps_on_list(const Problem& P, const float* list, int n, long long fixed, Search& S,
-                                              int* s_red) {
+__device__ __forceinline__ void steps_on_list(const Problem& P, const float* list, int n, long long fixed,
+                                              const Hull& h, Search& S, int* s_red) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int parity = 0;
   while (!S.done && S.it < P.max_iters) {
     const double lam = (S.lo + S.hi) * 0.5;
+    if (lam < h.lo || lam > h.hi) {      // uniform
+      S.take(lam > h.hi, lam);
+      continue;
+    }
     float t[kThr];
 #pragma unroll
     for (int k = 0; k < kThr; ++k) t[k] = P.thr(lam, k);
@@ -322,7 +336,8 @@ __device__ __forceinline__ void steps_on_list(const Problem& P, const float* lis
 #pragma unroll
       for (int k = 0; k < kThr; ++k) s += P.step_bits[k] * __popcll(__ballot(w > t[k]));
     }
-    int* slots = s_red + (S.it & 1) * kWaves;    // alternating, so that one barrier per step is enough
+    int* slots = s_red + parity * kWaves;        // alternating, so that one barrier per step is enough
+    parity ^= 1;
     if (lane == 0) slots[wave] = s;
     __syncthreads();
     int sum = 0;
@@ -333,9 +348,13 @@ __device__ __forceinline__ void steps_on_list(const Problem& P, const float* lis
 }
 // the same by one wavefront that holds up to 64 PER units in registers
 template <int PER>
-__device__ __forceinline__ void steps_in_wave(const Problem& P, const float (&w)[PER], long long fixed, Search& S) {
+__device__ __forceinline__ void steps_in_wave(const Problem& P, const float (&w)[PER], long long fixed, const Hull& h, Search& S) {
   while (!S.done && S.it < P.max_iters) {
     const double lam = (S.lo + S.hi) * 0.5;
+    if (lam < h.lo || lam > h.hi) {
+      S.take(lam > h.hi, lam);
+      continue;
+    }
     long long s = fixed;
 #pragma unroll
     for (int k = 0; k < kThr; ++k) {
@@ -407,6 +426,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   __shared__ int s_wave[kWaves], s_red[2 * kWaves], s_n;
   __shared__ float s_max[kWaves];
   __shared__ Search s_search;
+  __shared__ Hull s_hull;
   const int item = blockIdx.x;
   const int U = a.item_U[item];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -463,8 +483,19 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
       S = s_search;
       if (S.done || S.it >= P.max_iters) break;
       // the histogram cannot decide the next step
-      const OpenBuckets open(P, map, S.lo, S.hi);
-      const int n = open.count(s_hist);
+      Hull hull = bracket_of(S);
+      OpenBuckets open(P, map, hull);
+      int n = open.count(s_hist);
+      if (n > kFewOpen) {
+        if (wave == 0) {
+          hull = narrow_hull(P, map, s_hist, S);
+          if (lane == 0) s_hull = hull;
+        }
+        __syncthreads();
+        hull = s_hull;
+        open = OpenBuckets(P, map, hull);
+        n = open.count(s_hist);
+      }
       if (n <= kItemListCap) {
         const OpenPatterns pat(open, map);
         uint32_t mine = 0;                 // which of this thread's units
@@ -485,18 +516,18 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
           if ((mine >> j) & 1) *dst++ = v[j];
         __syncthreads();
         const long long fixed = open.fixed(P, s_hist);
-        if (n <= 1024) {
+        if (n <= kFewOpen) {
           if (wave == 0) {
             float u[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) u[i] = i * 64 + lane < n ? s_list[i * 64 + lane] : 0.f;
-            steps_in_wave<16>(P, u, fixed, S);
+            steps_in_wave<16>(P, u, fixed, hull, S);
             if (lane == 0) s_search = S;
           }
           __syncthreads();
           S = s_search;
         } else {
-          steps_on_list(P, s_list, n, fixed, S, s_red);
+          steps_on_list(P, s_list, n, fixed, hull, S, s_red);
         }
         break;
       }
@@ -576,7 +607,7 @@ constexpr int kItemUnits = 32 * kThreads;   // longest item of that kernel
 // ---- longer items: the passes over the units on many workgroups -------------------------------------------------
 // Beyond 32K units the registers of one compute unit no longer hold an item.  Measured, 8 items of 128K units: 98 to 255
 // us in six kernels -> 55 us in four; what is left is the latency of two hand-overs to the last workgroup and of the
-// dependent steps (22 + 20 us).
+// dependent steps.
 // An item's weights read as aligned 16-byte quads.  Quad q covers units 4 q - a .. 4 q - a + 3,
 // a = how many floats the item's first weight sits past a 16-byte boundary; units outside [0, U) read as 0 (never above
 // a threshold).  The first and the last quad are read element by element (their neighbours may lie outside the array).
@@ -605,18 +636,22 @@ struct Quads {
   }
 };
 
+constexpr int kMostSlices = 16;              // workgroups that share an item
 constexpr int kListCap = 24576;             // undecided units of an item (96 KB of LDS in the exact steps)
 struct SearchState {
   Search s;
+  Hull hull;
   long long fixed;                          // what the units outside the open buckets add to the bit sum
   int32_t open_a[kThr], open_b[kThr];       // the open buckets (OpenBuckets)
-  int32_t mx, n_open, n_list, arrive[2], fill;   // fill: >= 0: the tier of every unit
+  int32_t n_open, n_list, arrive[2], fill;  // fill: >= 0: the tier of every unit
+  uint32_t top;                             // pattern of the largest unit
 };
 struct MultiArgs {
   AllocArgs a;
   int32_t* hist;        // [items][kBuckets], zero on entry
   SearchState* state;   // [items], zero on entry
   float* list;          // [items][kListCap]
+  float* slice_max;     // [items][slices]
   int32_t slices;
 };
 
@@ -635,21 +670,47 @@ __device__ __forceinline__ T load_agent(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// every slice adds its units to the item's histogram and maximum; the last one takes the steps the histogram decides
-constexpr size_t kHistLds = FullRange::kWords * sizeof(int);
+// The largest unit of every slice, which anchors the histograms (over the full range of fp32 they had 32768 buckets at a
+// quarter of the resolution: hist_kernel 21 us, gather_kernel 20 at 8 x 128K units), and zeros for the next kernels.
+__global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, uint4* clear, int64_t n_clear) {
+  __shared__ float s_max[kWaves];
+  const int item = blockIdx.y, tid = threadIdx.x;
+  const Quads quads(m.a.w + m.a.item_off[item], m.a.item_U[item]);
+  int q0, q1;
+  quads.slice(m.slices, &q0, &q1);
+  const int64_t step = static_cast<int64_t>(gridDim.x) * gridDim.y * kThreads;
+  for (int64_t i = (static_cast<int64_t>(item) * gridDim.x + blockIdx.x) * kThreads + tid; i < n_clear; i += step)
+    clear[i] = make_uint4(0, 0, 0, 0);
+  float mx = 0.f;
+  for (int q = q0 + tid; q < q1; q += kThreads) {
+    float v[4];
+    quads.load(q, v);
+    mx = fmaxf(mx, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+  }
+  mx = wave_max(mx);
+  if ((tid & 63) == 0) s_max[tid >> 6] = mx;
+  __syncthreads();
+  if (tid < 64) {
+    mx = wave_max(tid < kWaves ? s_max[tid] : 0.f);
+    if (tid == 0) m.slice_max[item * m.slices + blockIdx.x] = mx;
+  }
+}
+
+// every slice adds its units to the item's histogram; the last one takes the steps the histogram decides
+constexpr size_t kHistLds = Anchored::kWords * sizeof(int);
 __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   extern __shared__ __align__(16) unsigned char smem[];
   int* s_hist = reinterpret_cast<int*>(smem);
   __shared__ int s_wave[kWaves], s_flag;
-  __shared__ float s_max[kWaves];
   const AllocArgs& a = m.a;
   const int item = blockIdx.y;
   const int U = a.item_U[item];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   SearchState& st = m.state[item];
   const Quads quads(a.w + a.item_off[item], U);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
+  float mx = lane < m.slices ? m.slice_max[item * m.slices + lane] : 0.f;      // (at most 32 slices)
   float wv[4] = {0.f, 0.f, 0.f, 0.f};
   if (q0 + tid < q1) quads.load(q0 + tid, wv);
   const Problem P(a, U, a.item_budget[item]);
@@ -662,31 +723,23 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
     }
     return;
   }
-  const FullRange map{};
-  for (int i = tid; i < FullRange::kWords / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
+  for (int i = tid; i < Anchored::kWords / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
+  mx = wave_max(mx);
+  const Anchored map{__float_as_uint(mx)};
   __syncthreads();
-  float mx = 0.f;
   for (int q = q0 + tid; q < q1;) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      mx = fmaxf(mx, wv[e]);
+    for (int e = 0; e < 4; ++e)
       if (wv[e] > 0.f) atomicAdd(&s_hist[hist_slot(map.bucket(__float_as_uint(wv[e])))], 1);
-    }
     q += kThreads;
     if (q < q1) quads.load(q, wv);
   }
-  mx = wave_max(mx);
-  if ((tid & 63) == 0) s_max[tid >> 6] = mx;
   __syncthreads();
-  int32_t* gh = m.hist + static_cast<int64_t>(item) * FullRange::kBuckets;
-  for (int i = tid; i < FullRange::kBuckets; i += kThreads)
+  int32_t* gh = m.hist + static_cast<int64_t>(item) * Anchored::kBuckets;
+  for (int i = tid; i < Anchored::kBuckets; i += kThreads)
     if (s_hist[hist_slot(i)] != 0) atomicAdd(gh + i, s_hist[hist_slot(i)]);
-  if (tid == 0) {
-    for (int i = 1; i < kWaves; ++i) mx = fmaxf(mx, s_max[i]);
-    if (mx > 0.f) atomicMax(&st.mx, __float_as_int(mx));     // positive: integer order is float order
-  }
   if (!last_to_arrive(&st.arrive[0], m.slices, &s_flag)) return;
-  constexpr int kPer = FullRange::kBuckets / kThreads;
+  constexpr int kPer = Anchored::kBuckets / kThreads;
   {
     int h[kPer];
 #pragma unroll
@@ -695,15 +748,22 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
     for (int k = 0; k < kPer; ++k) s_hist[hist_slot(tid + k * kThreads)] = h[k];
   }
   __syncthreads();
-  suffix_sums<FullRange::kBuckets>(s_hist, s_wave);
+  suffix_sums<Anchored::kBuckets>(s_hist, s_wave);
   if (tid < 64) {
-    Search S{0.0, static_cast<double>(__int_as_float(load_agent(&st.mx))), 0.0, 0, 0, 0};
+    Search S{0.0, static_cast<double>(mx), 0.0, 0, 0, 0};
     steps_on_histogram(P, map, s_hist, S);
     S.done = S.done || S.it >= P.max_iters;
-    const OpenBuckets open(P, map, S.lo, S.hi);
+    Hull hull = bracket_of(S);
+    OpenBuckets open(P, map, hull);
+    if (!S.done && open.count(s_hist) > kFewOpen) {
+      hull = narrow_hull(P, map, s_hist, S);
+      open = OpenBuckets(P, map, hull);
+    }
     if (tid == 0) {
       st.s = S;
+      st.hull = hull;
       st.fill = -1;
+      st.top = map.top;
       st.fixed = open.fixed(P, s_hist);
       st.n_open = open.count(s_hist);
 #pragma unroll
@@ -743,7 +803,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
       open.a[k] = st.open_a[k];
       open.b[k] = st.open_b[k];
     }
-    const OpenPatterns pat(open, FullRange{});
+    const OpenPatterns pat(open, Anchored{st.top});
     if (tid == 0) s_n = 0;
     __syncthreads();
     for (int qw = q0 + wave * 64; qw < q1; qw += kThreads) {
@@ -770,12 +830,13 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
     if (!last_to_arrive(&st.arrive[1], m.slices, &s_flag)) return;
     const Problem P(a, U, a.item_budget[item]);
     const long long fixed = st.fixed;
-    if (n <= 1024) {
+    const Hull hull = st.hull;
+    if (n <= kFewOpen) {
       if (wave == 0) {
         float u[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) u[i] = i * 64 + lane < n ? load_agent(gl + i * 64 + lane) : 0.f;
-        steps_in_wave<16>(P, u, fixed, S);
+        steps_in_wave<16>(P, u, fixed, hull, S);
         if (lane == 0) s_search = S;
       }
       __syncthreads();
@@ -783,7 +844,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
     } else {
       for (int i = tid; i < n; i += kThreads) s_list[i] = load_agent(gl + i);
       __syncthreads();
-      steps_on_list(P, s_list, n, fixed, S, s_red);
+      steps_on_list(P, s_list, n, fixed, hull, S, s_red);
     }
   } else {                                  // more than the list holds: every step on all units, one workgroup
     const Problem P(a, U, a.item_budget[item]);
@@ -871,12 +932,6 @@ __global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
   }
 }
 
-// hipMemsetAsync for memory that a captured graph may clear too
-__global__ __launch_bounds__(256) void clear_kernel(uint4* p, int64_t n) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * 256)
-    p[i] = make_uint4(0, 0, 0, 0);
-}
-
 // Stage 3 of Alg. 1: the K budget r_K * B_head of an item is spread over its retained tokens (bit-width above zero)
 // only: k_avg = min(16, 2 r_K avg_bits T / n_kept) average bits per channel unit, 0 if nothing is retained; rounded
 // to fp32 like every budget.  fp64 in this operation order (the file is compiled without contraction).  The map over
@@ -912,7 +967,7 @@ __global__ __launch_bounds__(64) void channel_allocate_kernel(ChannelArgs c) {
   float t[kThr];
   if (fill < 0) {
     S.hi = static_cast<double>(wave_max(fmaxf(fmaxf(v[0], v[1]), 0.f)));
-    steps_in_wave<2>(P, v, P.base, S);
+    steps_in_wave<2>(P, v, P.base, bracket_of(S), S);
 #pragma unroll
     for (int k = 0; k < kThr; ++k) t[k] = S.have ? P.thr(S.best, k) : INFINITY;
   }
@@ -943,7 +998,7 @@ hipError_t allow_lds(K kernel, size_t lds) {
                              static_cast<int>(lds));
 }
 
-size_t hist_bytes(int n_items) { return static_cast<size_t>(n_items) * FullRange::kBuckets * sizeof(int32_t); }
+size_t hist_bytes(int n_items) { return static_cast<size_t>(n_items) * Anchored::kBuckets * sizeof(int32_t); }
 size_t state_bytes(int n_items) { return (static_cast<size_t>(n_items) * sizeof(SearchState) + 255) / 256 * 256; }
 
 }  // namespace
@@ -951,7 +1006,7 @@ size_t state_bytes(int n_items) { return (static_cast<size_t>(n_items) * sizeof(
 // Device scratch launch_allocate needs for items of up to max_U units; 0 where one workgroup holds an item.
 size_t allocate_scratch_bytes(int n_items, int max_U) {
   if (max_U <= kItemUnits) return 0;
-  return hist_bytes(n_items) + state_bytes(n_items) + static_cast<size_t>(n_items) * kListCap * sizeof(float);
+  return hist_bytes(n_items) + state_bytes(n_items) + static_cast<size_t>(n_items) * (kListCap + kMostSlices) * sizeof(float);
 }
 
 // Token maps of all items.  blk_counts (with item_blk_off): what the packing stage needs, or null.
@@ -987,11 +1042,11 @@ hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int3
   m.hist = reinterpret_cast<int32_t*>(p);
   m.state = reinterpret_cast<SearchState*>(p + hist_bytes(n_items));
   m.list = reinterpret_cast<float*>(p + hist_bytes(n_items) + state_bytes(n_items));
-  m.slices = std::max(1, std::min(32, 256 / n_items));
+  m.slice_max = m.list + static_cast<size_t>(n_items) * kListCap;
+  m.slices = std::max(1, std::min(kMostSlices, 256 / n_items));
   const int64_t clear = static_cast<int64_t>((hist_bytes(n_items) + state_bytes(n_items)) / 16);
-  hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>(std::min<int64_t>(1024, (clear + 255) / 256))), dim3(256), 0, st,
-                     reinterpret_cast<uint4*>(p), clear);
   const dim3 wide(m.slices, n_items);
+  hipLaunchKernelGGL(slice_max_kernel, wide, block, 0, st, m, reinterpret_cast<uint4*>(p), clear);
   e = allow_lds(hist_kernel, kHistLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(hist_kernel, wide, block, kHistLds, st, m);

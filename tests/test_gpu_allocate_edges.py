@@ -70,3 +70,23 @@ def test_allocate_at_the_edges(seq_lens, kind, budgets, tiers, monkeypatch):
             assert np.isnan(lam[item]) if info["lam"] is None else lam[item] == info["lam"]
             off += T
             item += 1
+
+
+@pytest.mark.parametrize("T", [3000, 20000, 60000])
+@pytest.mark.parametrize("step", [3, 5])
+@pytest.mark.parametrize("off", [-40, -1, 0, 1, 40])
+def test_final_multiplier_next_to_an_early_one(T, step, off, monkeypatch):
+    """A budget within a few bits of what an early multiplier spends: that step is decided on the units themselves while
+    the bracket is still wide and most units lie in it."""
+    monkeypatch.setattr(O, "argmin_bits", lambda w, lam, tiers, eps: O.classify(w, lam, *O.hull_thresholds(tiers, eps)))
+    print(f"[case] {T} {step} {off}", flush=True)
+    b, table = B(), O.EPS_V_LLAMA31_8B
+    w = np.random.default_rng(T + step).random((1, T)).astype(np.float32)
+    lam = float(w.max()) * 0.5 ** step            # the step-th multiplier of a search that is within the budget so far
+    spent = int(O.classify(w[0], lam, *O.hull_thresholds(O.TIERS, table)).astype(np.int64).sum())
+    budget = np.float32((spent + off) / T)
+    cfg = b.Config([T], 1, 1, budget_bits=[float(budget)], eps_v=[np.float32(x) for x in table], rel_tol=1e-6)
+    bits, _, got, iters = b.rdkv_allocate_info(cfg, torch.from_numpy(w.reshape(-1)).cuda())
+    ref, info = O.mckp_bisect(w[0], budget, O.TIERS, table, rel_tol=np.float32(1e-6), return_info=True)
+    np.testing.assert_array_equal(bits.cpu().numpy(), ref)
+    assert iters.cpu().numpy()[0][0] == info["iters"] and got.cpu().numpy()[0][0] == info["lam"]

@@ -63,6 +63,21 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
 // four bytes of a bit map at any address
 struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 
+// Inclusive sum over the wavefront's lanes on the ALUs (rows of 16, then across rows; a shuffle per step goes through LDS)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t lanes_below(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += lanes_below<0x111, 0xF>(v);   // row_shr:1
+  v += lanes_below<0x112, 0xF>(v);
+  v += lanes_below<0x114, 0xF>(v);
+  v += lanes_below<0x118, 0xF>(v);
+  v += lanes_below<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += lanes_below<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // Writes the ascending position lists: tier_idx[item_base + tier_base + rank].  One workgroup = one block of 1024 tokens, a
 // thread = four consecutive ones; the ranks of all four tiers come from one prefix sum over 16-bit fields.
 __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __restrict__ bits,
@@ -92,11 +107,11 @@ __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __rest
     const int4 x = blk_counts[item_blk_off[item] + i];
     c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
   }
-  int before[4] = {c.x, c.y, c.z, c.w};
+  const int before[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    for (int o = 32; o > 0; o >>= 1) before[k] += __shfl_xor(before[k], o);
-    if (lane == 0) s_before[wave][k] = before[k];
+    const int sum = static_cast<int>(wave_scan(static_cast<uint32_t>(before[k])));
+    if (lane == 63) s_before[wave][k] = sum;
   }
   int slot[4];
   uint64_t mine = 0;                       // this thread's tokens per tier, 16 bits each
@@ -105,12 +120,8 @@ __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __rest
     slot[e] = tier_slot(static_cast<uint8_t>(four >> (8 * e)));
     mine += slot[e] >= 0 ? 1ull << (16 * slot[e]) : 0ull;
   }
-  uint64_t incl = mine;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t x = __shfl_up(incl, o);
-    if (lane >= o) incl += x;
-  }
+  const uint64_t incl = static_cast<uint64_t>(wave_scan(static_cast<uint32_t>(mine))) |
+                        static_cast<uint64_t>(wave_scan(static_cast<uint32_t>(mine >> 32))) << 32;   // (at most 256 each)
   if (lane == 63) s_wave[wave] = incl;
   __syncthreads();
   uint64_t rank = incl - mine;

@@ -517,21 +517,43 @@ __global__ __launch_bounds__(256) void row_lse_kernel(WeightArgs a) {
 }
 
 // AvgPool1d(kernel, stride 1, zero padding kernel/2, divisor kernel) along the keys of each item
+// (kernel odd, at most 15).  256 PER keys per workgroup; every load is issued before anything waits, and each key is read
+// once: with a thread per key and its neighbours read from memory 2.9M keys took 13.7 us.
+template <int PER>
 __global__ __launch_bounds__(256) void pool_kernel(const float* __restrict__ w_raw, float* __restrict__ w_out,
                                                    const int64_t* __restrict__ item_row_off,
                                                    const int32_t* __restrict__ item_T, int kernel) {
+  constexpr int kRows = 256 * PER, kMostRadius = 7;
+  __shared__ float s_w[kRows + 2 * kMostRadius];
   const int item = blockIdx.y;
   const int T = item_T[item];
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
+  const int t0 = blockIdx.x * kRows, tid = threadIdx.x;
+  if (t0 >= T) return;
   const float* w = w_raw + item_row_off[item];
-  const int r = kernel / 2;
-  float s = 0.f;
-  for (int k = -r; k <= r; ++k) {
-    const int u = t + k;
-    if (u >= 0 && u < T) s += w[u];
+  float* out = w_out + item_row_off[item];
+  const int r = kernel / 2, first = t0 - r;
+  float v[PER + 1];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int u = first + 256 * j + tid;
+    v[j] = u >= 0 && u < T ? w[u] : 0.f;
   }
-  w_out[item_row_off[item] + t] = s / static_cast<float>(kernel);
+  const int last = first + kRows + tid;
+  v[PER] = tid < 2 * r && last < T ? w[last] : 0.f;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) s_w[256 * j + tid] = v[j];
+  if (tid < 2 * r) s_w[kRows + tid] = v[PER];
+  __syncthreads();
+  float s[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) s[j] = 0.f;
+  for (int k = 0; k <= 2 * r; ++k)
+#pragma unroll
+    for (int j = 0; j < PER; ++j) s[j] += s_w[256 * j + tid + k];
+  const float count = static_cast<float>(kernel);
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (t0 + 256 * j + tid < T) out[t0 + 256 * j + tid] = s[j] / count;
 }
 
 // w_c = ||Q[:,c]|| ||K[:,c]|| / sqrt(d): finishes the K sums of squares and adds the probe's column norms; 8 threads per
@@ -613,8 +635,12 @@ hipError_t launch_weights(const rdkv_config& cfg, const int64_t* d_item_row_off,
   else launch_passes<2, 4>(a, w_ch != nullptr, st);
   const bool pooled = cfg.pool_kernel > 1;
   if (pooled) {
-    hipLaunchKernelGGL(pool_kernel, dim3((max_T + 255) / 256, static_cast<unsigned>(n_items)), dim3(256), 0, st,
-                       a.w_raw, w_tok, d_item_row_off, d_item_T, cfg.pool_kernel);
+    // enough workgroups for the chip first, then several keys per thread
+    const bool wide = n_items * ((max_T + 1023) / 1024) >= 1024;
+    const unsigned per_wg = wide ? 1024 : 256;
+    const dim3 grid((static_cast<unsigned>(max_T) + per_wg - 1) / per_wg, static_cast<unsigned>(n_items));
+    if (wide) hipLaunchKernelGGL(pool_kernel<4>, grid, dim3(256), 0, st, a.w_raw, w_tok, d_item_row_off, d_item_T, cfg.pool_kernel);
+    else hipLaunchKernelGGL(pool_kernel<1>, grid, dim3(256), 0, st, a.w_raw, w_tok, d_item_row_off, d_item_T, cfg.pool_kernel);
   } else {
     hipError_t e = hipMemcpyAsync(w_tok, a.w_raw, total_tokens * sizeof(float), hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return e;

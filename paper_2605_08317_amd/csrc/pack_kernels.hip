@@ -191,8 +191,8 @@ struct Quant {
   _Float16 sh, mh;
   bool finite;
   template <int BITS>
-  __device__ __forceinline__ void set(float mn, float mx) {
-    constexpr float Q = static_cast<float>((1 << BITS) - 1);
+  __device__ __forceinline__ void set(float mn, float mx) { set(mn, mx, static_cast<float>((1 << BITS) - 1)); }
+  __device__ __forceinline__ void set(float mn, float mx, float Q) {       // Q: the largest code
     mn = mn + 0.0f;            // canonical +0
     sh = static_cast<_Float16>((mx - mn) / Q);   // round to nearest even
     mh = static_cast<_Float16>(mn);
@@ -203,8 +203,9 @@ struct Quant {
   }
   // the code as a float; EXACT: by division
   template <int BITS, bool EXACT>
-  __device__ __forceinline__ float code(float x) const {
-    constexpr float Q = static_cast<float>((1 << BITS) - 1);
+  __device__ __forceinline__ float code(float x) const { return code<EXACT>(x, static_cast<float>((1 << BITS) - 1)); }
+  template <bool EXACT>
+  __device__ __forceinline__ float code(float x, float Q) const {
     const float d = x - m;
     float q;
     if constexpr (EXACT) {
@@ -214,7 +215,7 @@ struct Quant {
       q = __builtin_fmaf(__builtin_fmaf(-q0, s, d), y, q0);
     }
     const float t = fminf(fmaxf(rintf(q), 0.0f), Q);
-    return s == 0.0f ? 0.0f : t;
+    return EXACT && s == 0.0f ? 0.0f : t;        // (with a finite s = 0: y = 0, q = 0)
   }
 };
 
@@ -467,10 +468,50 @@ __global__ __launch_bounds__(256) void k_channel_range_kernel(PackArgs a) {
 // 16 (e % 2) + b (e / 2) + 2 b k; a 16-bit word holds its two slots in its halves.
 // Metadata: per token group G and quantized step sq (4 slots) 4 fp16 scales then 4 fp16 offsets at fp16 index
 // 8 (G n_qsteps + sq).
-__global__ __launch_bounds__(256) void pack_k_mixed_kernel(PackArgs a) {
+//
+// One thread = one slot of a word and one token group: its channel's 32 values in registers, quantized, the codes packed F
+// tokens to a register (F = 32 / b fields of a word).  The F lanes that hold a word's slots then exchange fields so that
+// lane f ends with the word of token f: a transposition of F x F fields in log2 F steps within a row of 16 lanes.  Every
+// tier starts at a row of lanes.  The words are staged in LDS and leave in 16-byte pieces.  Bound: instruction
+// issue; 160K rows 40 -> 32 us (a word put together field by field, each a channel number and a code out of LDS; and one
+// code path per width, of which a wavefront with slots of three tiers took all three).
+// what lane ^ J holds (J = 1, 2, 4, 8, inside a row of 16)
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (J == 1) return dpp_u<kQuadXor1>(v);
+  else if constexpr (J == 2) return dpp_u<kQuadXor2>(v);
+  else if constexpr (J == 8) return dpp_u<0x128>(v);                    // row_ror:8
+  else {
+    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x104, 0xF, 0x5, false);   // row_shl:4 into banks 0, 2
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(lo, static_cast<int>(v), 0x114, 0xF, 0xA, false));   // row_shr:4
+  }
+}
+// One step of the transposition: fields of B bits whose index differs in bit J swap places with lane ^ J.
+template <int B, int J>
+__device__ __forceinline__ uint32_t exchange_fields(uint32_t v, int f) {
+  uint32_t keep = 0;                   // fields with bit J clear
+#pragma unroll
+  for (int i = 0; i < 32 / B; ++i) keep |= (i & J) ? 0u : ((1u << B) - 1u) << (B * i);
+  const bool up = (f & J) != 0;
+  const uint32_t m = up ? ~keep : keep;
+  const uint32_t o = lane_xor<J>(v);
+  const uint32_t moved = __builtin_amdgcn_alignbit(o, o, up ? J * B : 32 - J * B);     // rotate right
+  return (v & m) | (moved & ~m);
+}
+template <int B>
+__device__ __forceinline__ uint32_t transpose_fields(uint32_t v, int f) {
+  if constexpr (B <= 2) v = exchange_fields<B, 8>(v, f);
+  if constexpr (B <= 4) v = exchange_fields<B, 4>(v, f);
+  if constexpr (B <= 8) v = exchange_fields<B, 2>(v, f);
+  return exchange_fields<B, 1>(v, f);
+}
+
+constexpr int kKThreads = 384;         // two token groups of at most 192 lanes
+__global__ __launch_bounds__(kKThreads) void pack_k_mixed_kernel(PackArgs a) {
   constexpr int kRows = kTile64;
   constexpr int kRowStride = kHeadDim + 8;
-  __shared__ __align__(16) uint16_t s_rows[kRows][kRowStride];   // bf16 rows, then the codes in their place
+  constexpr int kRowBytes = kRows * kRowStride * 2, kWordBytes = kRows * kMaxKRowWords * 4;
+  __shared__ __align__(16) uint8_t s_buf[kRowBytes > kWordBytes ? kRowBytes : kWordBytes];   // bf16 rows, then the tile's words
   __shared__ uint16_t s_sc[2][kHeadDim], s_of[2][kHeadDim];
   __shared__ ItemK s_ik;
   const int item = blockIdx.y;
@@ -479,101 +520,151 @@ __global__ __launch_bounds__(256) void pack_k_mixed_kernel(PackArgs a) {
   const int valid = min(kRows, t.n - t.tile * kRows);
   const int tid = threadIdx.x;
   const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + t.ti) * 4;
+  uint16_t* s_rows = reinterpret_cast<uint16_t*>(s_buf);
   {
-    const int lane = tid & 63, c16 = lane & 15, row0 = 16 * (tid >> 6) + 4 * (lane >> 4);
     const int32_t* idx = a.tier_idx + a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kRows;
     const int64_t item_row = a.item_row_off[item];
-    uint4 v[4];
+    constexpr int kPieces = kRows * 16, kLoads = (kPieces + kKThreads - 1) / kKThreads;      // 16 bytes each
+    uint4 v[kLoads];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kLoads; ++i) {
+      const int p = i * kKThreads + tid, row = p >> 4;
       v[i] = make_uint4(0, 0, 0, 0);
-      if (row0 + i < valid) v[i] = *reinterpret_cast<const uint4*>(a.K + (item_row + idx[row0 + i]) * kHeadDim + c16 * 8);
+      if (row < valid) v[i] = *reinterpret_cast<const uint4*>(a.K + (item_row + idx[row]) * kHeadDim + (p & 15) * 8);
     }
-    for (int i = tid; i < static_cast<int>(sizeof(ItemK) / 4); i += 256)
+    for (int i = tid; i < static_cast<int>(sizeof(ItemK) / 4); i += kKThreads)
       reinterpret_cast<uint32_t*>(&s_ik)[i] = reinterpret_cast<const uint32_t*>(a.items_k + item)[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(&s_rows[row0 + i][c16 * 8]) = v[i];
-  }
-  __syncthreads();
-  {  // one thread = one (token group, channel), its 32 values in registers
-    const int G = tid >> 7, c = tid & 127;
-    const int rb = kKTokenGroup * G, vg = min(max(valid - rb, 0), kKTokenGroup);
-    const int b = a.bits_ch[item * kHeadDim + c];
-    uint16_t sc = 0, of = 0;
-    const bool quantized = (b == 8 || b == 4 || b == 2) && vg > 0;
-    if (quantized) {
-      float x[kKTokenGroup];
-#pragma unroll
-      for (int r = 0; r < kKTokenGroup; ++r) x[r] = __uint_as_float(static_cast<uint32_t>(s_rows[rb + r][c]) << 16);
-      float mn, mx;
-      if (a.k_range) {   // the range of the whole unit
-        mn = ordered_to_float(a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2]);
-        mx = ordered_to_float(a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2 + 1]);
-      } else {
-        mn = x[0];
-        mx = x[0];
-#pragma unroll
-        for (int r = 1; r < kKTokenGroup; ++r) {
-          mn = r < vg ? fminf(mn, x[r]) : mn;
-          mx = r < vg ? fmaxf(mx, x[r]) : mx;
-        }
-      }
-      Quant g;
-      const auto run = [&](auto bits_c) __attribute__((always_inline)) {
-        constexpr int BITS = decltype(bits_c)::value;
-        g.set<BITS>(mn, mx);
-        if (g.finite) {
-#pragma unroll
-          for (int r = 0; r < kKTokenGroup; ++r)
-            s_rows[rb + r][c] = r < vg ? static_cast<uint16_t>(g.code<BITS, false>(x[r])) : uint16_t(0);
-        } else {
-#pragma unroll 1
-          for (int r = 0; r < kKTokenGroup; ++r) {
-            const float xr = __uint_as_float(static_cast<uint32_t>(s_rows[rb + r][c]) << 16);
-            s_rows[rb + r][c] = r < vg ? static_cast<uint16_t>(g.code<BITS, true>(xr)) : uint16_t(0);
-          }
-        }
-      };
-      if (b == 8) run(std::integral_constant<int, 8>{});
-      else if (b == 4) run(std::integral_constant<int, 4>{});
-      else run(std::integral_constant<int, 2>{});
-      sc = __builtin_bit_cast(unsigned short, g.sh);
-      of = __builtin_bit_cast(unsigned short, g.mh);
+    for (int i = 0; i < kLoads; ++i) {
+      const int p = i * kKThreads + tid;
+      if (p < kPieces) *reinterpret_cast<uint4*>(s_rows + (p >> 4) * kRowStride + (p & 15) * 8) = v[i];
     }
-    // (16-bit channels keep their bf16 values, rows past the last are zero; dropped channels are in no word)
-    s_sc[G][c] = sc;
-    s_of[G][c] = of;
   }
   __syncthreads();
 
+  // slots: lanes of a token group = words of a tier times slots of a word, tier by tier from a row of 16 on
   const int nwp = s_ik.n_words_padded, full = nwp & ~3;
-  uint32_t* dst = reinterpret_cast<uint32_t*>(a.arena + so[0] + static_cast<int64_t>(t.tile) * s_ik.kt_bytes);
-  for (int idx = tid; idx < kRows * nwp; idx += 256) {
-    int W, r;
-    if (idx < kRows * full) {
-      W = 4 * (idx >> 8) + (idx & 3);
-      r = (idx >> 2) & 63;
-    } else {
-      W = full + (idx & 1);
-      r = (idx - kRows * full) >> 1;
+  int start[5];
+  start[0] = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    start[k + 1] = start[k] + (((s_ik.word_end[k] - (k > 0 ? s_ik.word_end[k - 1] : 0)) * (2 << k) + 15) & ~15);
+  const int lanes = start[4];            // at most 192
+  const bool active = tid < 2 * lanes;
+  const int G = tid >= lanes ? 1 : 0, l = tid - G * lanes;
+  int tier = 0, local = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (l >= start[k] && l < start[k + 1]) {
+      tier = k;
+      local = l - start[k];
     }
-    uint32_t out = 0;
-    if (W < s_ik.n_words) {
-      int tier = 0;
-      while (W >= s_ik.word_end[tier]) ++tier;
-      const int b = 16 >> tier, per_word = 32 / b;
-      const int lw = W - (tier > 0 ? s_ik.word_end[tier - 1] : 0);
-      const int16_t* sl = s_ik.slot_ch + s_ik.slot_base[tier] + lw * per_word;
-      for (int jj = 0; jj < per_word; ++jj) {
-        const int c = sl[jj];
-        if (c < 0) continue;
-        const int k = jj >> 2, e = jj & 3;
-        const int bit = b == 16 ? 16 * jj : 16 * (e & 1) + b * (e >> 1) + 2 * b * k;
-        out |= static_cast<uint32_t>(s_rows[r][c]) << bit;
-      }
-    }
-    dst[idx] = out;
+  const int rb = kKTokenGroup * G, vg = min(max(valid - rb, 0), kKTokenGroup);
+  const int per_word = 2 << tier, f = local & (per_word - 1);
+  const int first_word = tier > 0 ? s_ik.word_end[tier - 1] : 0, W = first_word + (local >> (tier + 1));
+  const bool writes = active && W < s_ik.word_end[tier];
+  int c = -1;                            // the slot's channel
+  if (writes) {
+    // slot 4 k + e of a word sits at bit 16 (e % 2) + b (e / 2) + 2 b k: field (F / 2) (e % 2) + e / 2 + 2 k
+    const int half = per_word >> 1, e = 2 * (f & 1) + f / half, k4 = (f & (half - 1)) >> 1;
+    c = s_ik.slot_ch[s_ik.slot_base[tier] + (W - first_word) * per_word + (tier == 0 ? f : 4 * k4 + e)];
   }
+  float x[kKTokenGroup];                 // the channel's values, then their codes
+#pragma unroll
+  for (int r = 0; r < kKTokenGroup; ++r) x[r] = 0.f;
+  if (c >= 0) {
+#pragma unroll
+    for (int r = 0; r < kKTokenGroup; ++r) x[r] = __uint_as_float(static_cast<uint32_t>(s_rows[(rb + r) * kRowStride + c]) << 16);
+    if (tier > 0) {                      // one path for all widths: a wavefront holds slots of several tiers
+      uint16_t sc = 0, of = 0;
+      if (vg > 0) {
+        const float most = static_cast<float>((1 << (16 >> tier)) - 1);
+        float mn, mx;
+        if (a.k_range) {   // the range of the whole unit
+          mn = ordered_to_float(a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2]);
+          mx = ordered_to_float(a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2 + 1]);
+        } else {
+          mn = x[0];
+          mx = x[0];
+          if (vg == kKTokenGroup) {
+#pragma unroll
+            for (int r = 1; r < kKTokenGroup; ++r) {
+              mn = fminf(mn, x[r]);
+              mx = fmaxf(mx, x[r]);
+            }
+          } else {
+#pragma unroll
+            for (int r = 1; r < kKTokenGroup; ++r) {
+              mn = r < vg ? fminf(mn, x[r]) : mn;
+              mx = r < vg ? fmaxf(mx, x[r]) : mx;
+            }
+          }
+        }
+        Quant g;
+        g.set(mn, mx, most);
+        if (g.finite) {
+#pragma unroll
+          for (int r = 0; r < kKTokenGroup; ++r) x[r] = g.code<false>(x[r], most);
+        } else {
+#pragma unroll
+          for (int r = 0; r < kKTokenGroup; ++r) x[r] = g.code<true>(x[r], most);
+        }
+        if (vg < kKTokenGroup) {
+#pragma unroll
+          for (int r = 0; r < kKTokenGroup; ++r) x[r] = r < vg ? x[r] : 0.f;
+        }
+        sc = __builtin_bit_cast(unsigned short, g.sh);
+        of = __builtin_bit_cast(unsigned short, g.mh);
+      } else {
+#pragma unroll
+        for (int r = 0; r < kKTokenGroup; ++r) x[r] = 0.f;
+      }
+      s_sc[G][c] = sc;
+      s_of[G][c] = of;
+    }
+  }
+  uint32_t out[16];                      // words of tokens rb + F q + f
+  const auto pack = [&](auto bits_c) __attribute__((always_inline)) {
+    constexpr int B = decltype(bits_c)::value, F = 32 / B;
+#pragma unroll
+    for (int q = 0; q < kKTokenGroup / F; ++q) {
+      uint32_t v = 0;
+      if constexpr (B == 16) {
+        v = (__float_as_uint(x[2 * q]) >> 16) | (__float_as_uint(x[2 * q + 1]) & 0xFFFF0000u);
+      } else {
+#pragma unroll
+        for (int i = 0; i < F; i += 2)   // two codes to a conversion
+          v |= static_cast<uint32_t>(__builtin_fmaf(x[q * F + i + 1], static_cast<float>(1 << B), x[q * F + i])) << (B * i);
+      }
+      out[q] = transpose_fields<B>(v, f);
+    }
+  };
+  if (active) {
+    if (tier == 3) pack(std::integral_constant<int, 2>{});
+    else if (tier == 2) pack(std::integral_constant<int, 4>{});
+    else if (tier == 1) pack(std::integral_constant<int, 8>{});
+    else pack(std::integral_constant<int, 16>{});
+  }
+  __syncthreads();                       // the rows are used up: their memory takes the words
+  uint32_t* s_words = reinterpret_cast<uint32_t*>(s_buf);
+  const auto word_at = [&](int w, int r) __attribute__((always_inline)) {
+    return w < full ? 256 * (w >> 2) + 4 * r + (w & 3) : kRows * full + 2 * r + (w - full);
+  };
+  if (writes) {
+    const auto put = [&](auto bits_c) __attribute__((always_inline)) {
+      constexpr int F = 32 / decltype(bits_c)::value;
+#pragma unroll
+      for (int q = 0; q < kKTokenGroup / F; ++q) s_words[word_at(W, rb + F * q + f)] = out[q];
+    };
+    if (tier == 3) put(std::integral_constant<int, 2>{});
+    else if (tier == 2) put(std::integral_constant<int, 4>{});
+    else if (tier == 1) put(std::integral_constant<int, 8>{});
+    else put(std::integral_constant<int, 16>{});
+  }
+  if (nwp > s_ik.n_words && tid < kRows) s_words[word_at(s_ik.n_words, tid)] = 0;
+  __syncthreads();
+  uint4* dst = reinterpret_cast<uint4*>(a.arena + so[0] + static_cast<int64_t>(t.tile) * s_ik.kt_bytes);
+  for (int idx = tid; idx < 16 * nwp; idx += kKThreads) dst[idx] = reinterpret_cast<const uint4*>(s_words)[idx];
   // metadata; the segment's last tile also clears the bytes up to the next segment's alignment
   const int nqs = s_ik.n_qsteps, n_tiles = (t.n + kRows - 1) / kRows;
   const bool last = t.tile == n_tiles - 1;
@@ -581,7 +672,7 @@ __global__ __launch_bounds__(256) void pack_k_mixed_kernel(PackArgs a) {
     uint16_t* meta1 = reinterpret_cast<uint16_t*>(a.arena + so[1]);
     const int words = 8 * nqs, padded = (2 * words + kSegAlign - 1) / kSegAlign * (kSegAlign / 2);
     if (t.tile == 0)
-      for (int idx = tid; idx < padded; idx += 256) {
+      for (int idx = tid; idx < padded; idx += kKThreads) {
         uint16_t v = 0;
         if (idx < words) {
           const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * (idx >> 3) + (idx & 3)];
@@ -594,7 +685,7 @@ __global__ __launch_bounds__(256) void pack_k_mixed_kernel(PackArgs a) {
   uint16_t* meta = reinterpret_cast<uint16_t*>(a.arena + so[1] + static_cast<int64_t>(t.tile) * s_ik.km_bytes);
   const int64_t end = static_cast<int64_t>(n_tiles) * s_ik.km_bytes;
   const int pad = last ? static_cast<int>((kSegAlign - end % kSegAlign) % kSegAlign) / 2 : 0;
-  for (int idx = tid; idx < 16 * nqs + pad; idx += 256) {
+  for (int idx = tid; idx < 16 * nqs + pad; idx += kKThreads) {
     uint16_t v = 0;
     if (idx < 16 * nqs) {
       const int G = idx / (8 * nqs), rem = idx - G * 8 * nqs;
@@ -643,7 +734,7 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
   }
   // k_range must hold (0xFFFFFFFF, 0) pairs on entry
   if (k_range) hipLaunchKernelGGL(k_channel_range_kernel, dim3(64, n_items), block, 0, st, a);
-  hipLaunchKernelGGL(pack_k_mixed_kernel, grid, block, 0, st, a);
+  hipLaunchKernelGGL(pack_k_mixed_kernel, grid, dim3(kKThreads), 0, st, a);
   hipLaunchKernelGGL(pack_tile_kernel<true>, grid, block, 0, st, a);
   return hipGetLastError();
 }

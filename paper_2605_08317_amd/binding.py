@@ -365,14 +365,14 @@ def rdkv_decode_bf16_workspace_bytes(seq_lens, hq, hkv, head_dim=128):
 
 
 def rdkv_decode_attn_bf16(K, V, seq_lens, hq, hkv, q, head_dim=128, out=None, lse=None, workspace=None):
-    arr = (ctypes.c_int32 * len(seq_lens))(*[int(x) for x in seq_lens])
+    arr = (ctypes.c_int32 * len(seq_lens))(*map(int, seq_lens))
     if workspace is None:
         n = lib.rdkv_decode_bf16_workspace_bytes(arr, len(seq_lens), hq, hkv, head_dim)
         workspace = torch.empty(max(n, 16), dtype=torch.uint8, device=q.device)
     if out is None:
-        out = torch.empty((len(seq_lens), hq, head_dim), dtype=torch.float32, device=q.device)
+        out = _empty_f32((len(seq_lens), hq, head_dim), (hq * head_dim, head_dim, 1), q.device)
     if lse is None:
-        lse = torch.empty((len(seq_lens), hq), dtype=torch.float32, device=q.device)
+        lse = _empty_f32((len(seq_lens), hq), (hq, 1), q.device)
     _check(lib.rdkv_decode_attn_bf16(_ptr(K), _ptr(V), arr, len(seq_lens), hq, hkv, head_dim, _ptr(q), _ptr(out),
                                      _ptr(lse), _ptr(workspace), workspace.numel(), _stream()))
     return out, lse

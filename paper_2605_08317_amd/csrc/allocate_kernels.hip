@@ -992,12 +992,6 @@ AllocArgs make_args(const float* w, int n_hull, const int* hull_tiers, const dou
   return a;
 }
 
-template <class K>
-hipError_t allow_lds(K kernel, size_t lds) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             static_cast<int>(lds));
-}
-
 size_t hist_bytes(int n_items) { return static_cast<size_t>(n_items) * Anchored::kBuckets * sizeof(int32_t); }
 size_t state_bytes(int n_items) { return (static_cast<size_t>(n_items) * sizeof(SearchState) + 255) / 256 * 256; }
 
@@ -1025,7 +1019,7 @@ hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int3
   if (max_U <= kItemUnits) {
 #define RDKV_ITEMS(REG_)                                                                               \
   {                                                                                                    \
-    e = allow_lds(allocate_item_kernel<REG_>, kItemLds);                                               \
+    e = RDKV_ALLOW_LDS((allocate_item_kernel<REG_>), kItemLds);                                              \
     if (e != hipSuccess) return e;                                                                     \
     hipLaunchKernelGGL(allocate_item_kernel<REG_>, dim3(n_items), block, kItemLds, st, a);             \
   }
@@ -1047,10 +1041,10 @@ hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int3
   const int64_t clear = static_cast<int64_t>((hist_bytes(n_items) + state_bytes(n_items)) / 16);
   const dim3 wide(m.slices, n_items);
   hipLaunchKernelGGL(slice_max_kernel, wide, block, 0, st, m, reinterpret_cast<uint4*>(p), clear);
-  e = allow_lds(hist_kernel, kHistLds);
+  e = RDKV_ALLOW_LDS(hist_kernel, kHistLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(hist_kernel, wide, block, kHistLds, st, m);
-  e = allow_lds(gather_kernel, kGatherLds);
+  e = RDKV_ALLOW_LDS(gather_kernel, kGatherLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(gather_kernel, wide, block, kGatherLds, st, m);
   hipLaunchKernelGGL(write_kernel, dim3((max_U + kBlockUnits - 1) / kBlockUnits, n_items), dim3(256), 0, st, m);

@@ -25,7 +25,7 @@
 // power of two of the field is folded into the query operand (K side) or into p (V side, per lane).
 // Everything a tile needs is loaded straight into registers in its final form; LDS holds only the merge of the wavefronts
 // of a workgroup.
-#include "decode_tile_common.h"
+#include "decode_rows.h"
 
 namespace rdkv {
 
@@ -230,6 +230,13 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
                                   ch.rows, g, qp, run);                                                           \
     finish_chunk<HS, false, NWV>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                                  \
   }
+    if constexpr (ROOMY) {
+      if (ch.tier == 16) {      // (launches without 16-bit chunks get less LDS)
+        process_rows_mfma<HS, true, NWV>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
+                                         nullptr, nullptr, &ma, &co);
+        return;
+      }
+    }
     switch (ch.tier) {
       case 8: RDKV_ONE(8) break;
       case 4: RDKV_ONE(4) break;
@@ -263,9 +270,16 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
 }
 
 template <int HS, int NWV, bool MULTI, bool ROOMY>
-hipError_t launch_tiles(const Chunk* chunks, int first, int n_chunks, const uint8_t* arena, const uint16_t* q,
+hipError_t launch_tiles(const Chunk* chunks, int first, int n_chunks, bool rows16, const uint8_t* arena, const uint16_t* q,
                         const MergeArgs& ma, const int32_t* tail_len, hipStream_t st) {
-  const size_t lds = (NWV * 4 * HS * 2 + finish_lds_floats(NWV, ma.g)) * sizeof(float);
+  size_t lds = (NWV * 4 * HS * 2 + finish_lds_floats(NWV, ma.g)) * sizeof(float);
+  if constexpr (ROOMY)
+    if (rows16) {
+      constexpr size_t kRows = rows_lds_bytes<HS, NWV>();
+      hipError_t e = RDKV_ALLOW_LDS((decode_tiles_kernel<HS, NWV, MULTI, ROOMY>), kRows);
+      if (e != hipSuccess) return e;
+      lds = lds > kRows ? lds : kRows;
+    }
   hipLaunchKernelGGL((decode_tiles_kernel<HS, NWV, MULTI, ROOMY>), dim3(n_chunks), dim3(NWV * 64), lds, st, chunks, arena, q,
                      tail_len, first, ma.g, ma);
   return hipGetLastError();
@@ -273,15 +287,19 @@ hipError_t launch_tiles(const Chunk* chunks, int first, int n_chunks, const uint
 
 }  // namespace
 
-hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, bool multi, const uint8_t* arena,
+bool decode_tiles_take_rows(int n_chunks, bool multi) { return !multi && n_chunks <= 256; }
+
+// `rows16`: the range starts with chunks of the 16-bit tier (allowed when decode_tiles_take_rows says so)
+hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, bool rows16, bool multi, const uint8_t* arena,
                                const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, hipStream_t st) {
   if (n_chunks == 0) return hipSuccess;
+  if (rows16 && !decode_tiles_take_rows(n_chunks, multi)) return hipErrorInvalidValue;
   // up to 4 query heads per KV head: one head set, workgroups of eight wavefronts; 8 heads: two head sets, workgroups of
   // four
-#define RDKV_TILES(HS_, NWV_)                                                                                         \
-  if (multi) return launch_tiles<HS_, NWV_, true, false>(chunks, first, n_chunks, arena, q, ma, tail_len, st);        \
-  if (n_chunks > 256) return launch_tiles<HS_, NWV_, false, false>(chunks, first, n_chunks, arena, q, ma, tail_len, st); \
-  return launch_tiles<HS_, NWV_, false, true>(chunks, first, n_chunks, arena, q, ma, tail_len, st);
+#define RDKV_TILES(HS_, NWV_)                                                                                              \
+  if (multi) return launch_tiles<HS_, NWV_, true, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st);      \
+  if (n_chunks > 256) return launch_tiles<HS_, NWV_, false, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st); \
+  return launch_tiles<HS_, NWV_, false, true>(chunks, first, n_chunks, rows16, arena, q, ma, tail_len, st);
   if (ma.g > 4) {
     RDKV_TILES(2, 4)
   }

@@ -504,8 +504,7 @@ hipError_t launch_one(const Chunk* chunks, int n_chunks, const uint8_t* arena, c
                       hipStream_t st) {
   const size_t lds = static_cast<size_t>(LdsPlan(lds_steps, lds_qsteps, HS, ma.g, NWV).total);
   if (lds > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_mixed_kernel<NW, HS, NWV>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    hipError_t e = RDKV_ALLOW_LDS((decode_mixed_kernel<NW, HS, NWV>), 160 * 1024);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((decode_mixed_kernel<NW, HS, NWV>), dim3(n_chunks), dim3(NWV * 64), lds, st, chunks, arena,

@@ -924,18 +924,17 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     for (int ti = ti0; ti < 4; ++ti) (ti == 1 ? rows8 : rows_all) += c->counts[i * 4 + ti];
   rows_all += rows8;
   const double share8 = static_cast<double>(rows8) / static_cast<double>(std::max<int64_t>(rows_all, 1));
-  if (total_cost > 0 && (mixed ? mixed_wide || total_cost <= round_chunks * floor_bytes
-                               : total_cost <= round_chunks * floor_bytes ||
-                                     (share8 < 0.2 && n <= 16 && total_cost < round_chunks * (192 << 10)))) {
-    const double per_tile = mixed ? (g > 4 ? 6.0 : 3.0) : (g > 4 ? 1.6 : 1.3) + 1.6 * share8;
+  // rows per chunk for the tiers from ti_first on, and the number of chunks that gives
+  auto latency_model = [&](int ti_first, double per_tile, int64_t* n_chunks) {
     constexpr int kMostTiles = 16;
     double best = 0.0;
+    int64_t best_rows = 0;
     for (int k = 1; k <= kMostTiles; k += k < 4 ? 1 : k < 8 ? 2 : 4) {
       const uint32_t rows = 256u * static_cast<uint32_t>(k);
       int64_t n_wg = 0, most = 0;
       for (int64_t i = 0; i < n; ++i) {
         int64_t slots = 0;
-        for (int ti = ti0; ti < 4; ++ti) slots += (static_cast<uint32_t>(c->counts[i * 4 + ti]) + rows - 1) / rows;
+        for (int ti = ti_first; ti < 4; ++ti) slots += (static_cast<uint32_t>(c->counts[i * 4 + ti]) + rows - 1) / rows;
         n_wg += slots;
         most = std::max(most, slots);
       }
@@ -944,8 +943,26 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       const double at_once = static_cast<double>(most) / rounds;
       const double t = 6.5 * rounds + per_tile * k * static_cast<double>((n_wg + 255) / 256) + 0.07 * at_once +
                        0.09 * std::max(0.0, at_once - 14.0);
-      if (small_rows == 0 || t < best) { small_rows = rows; best = t; }
+      if (best_rows == 0 || t < best) { best_rows = rows; best = t; *n_chunks = n_wg; }
     }
+    return best_rows;
+  };
+  const double per_tile = mixed ? (g > 4 ? 6.0 : 3.0) : (g > 4 ? 1.6 : 1.3) + 1.6 * share8;
+  // A token-wise launch of at most 256 chunks takes the 16-bit rows along (decode_tiles_take_rows): one launch instead of
+  // two that follow each other (three short sequences of keep / 4 bit / evict 11.7 -> 8 us).
+  bool rows16_along = false;
+  if (cost16 > 0 && total_cost + cost16 <= round_chunks * floor_bytes) {
+    int64_t n_wg = 0;
+    small_rows = latency_model(0, (g > 4 ? 1.6 : 1.3) + 1.6, &n_wg);
+    rows16_along = decode_tiles_take_rows(static_cast<int>(n_wg), false);
+    if (!rows16_along) small_rows = 0;
+  }
+  if (small_rows == 0 && total_cost > 0 &&
+      (mixed ? mixed_wide || total_cost <= round_chunks * floor_bytes
+             : total_cost <= round_chunks * floor_bytes ||
+                   (share8 < 0.2 && n <= 16 && total_cost < round_chunks * (192 << 10)))) {
+    int64_t n_wg = 0;
+    small_rows = latency_model(ti0, per_tile, &n_wg);
   }
   // Number of chunks a chunk cost of cb gives, and the largest chunk's cost.  Chunks of less than an eighth of cb (a
   // tier with a handful of rows) do not count: they finish at once and leave their workgroup slot to the next chunk
@@ -1027,7 +1044,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       if (cnt == 0) continue;
       const int64_t per_row = row_cost(i, bits);
       int64_t want = std::max<int64_t>(64, (!mixed && bits == 16 ? chunk_bytes16 : chunk_bytes) / per_row);
-      if (small_rows > 0 && (mixed || bits != 16)) want = small_rows;
+      if (small_rows > 0 && (mixed || bits != 16 || rows16_along)) want = small_rows;
       const int64_t nch = (cnt + want - 1) / want;
       const int64_t rows_per = round_up((cnt + nch - 1) / nch, 64);
       for (int64_t r0 = 0; r0 < cnt; r0 += rows_per) {
@@ -1524,12 +1541,16 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
                                  st));
     return RDKV_OK;
   }
-  // the workgroups of both kernels announce themselves on the same counters: whichever finishes an item merges it
-  RDKV_HIP(launch_decode_tiered_split(c->d_chunks, n16, c->d_arena, static_cast<const uint16_t*>(q), ma, st));
   bool multi = c->n_cont > 0;      // some workgroup goes through more than one tier of its item
   for (const rdkv_cache* child : c->absorbed) multi = multi || child->n_cont > 0;
-  RDKV_HIP(launch_decode_tiles(c->d_chunks, n16, nrest, multi, c->d_arena, static_cast<const uint16_t*>(q), ma,
-                               c->d_tail_len, st));
+  const uint16_t* qp = static_cast<const uint16_t*>(q);
+  if (n16 > 0 && decode_tiles_take_rows(n16 + nrest, multi)) {     // one launch for all tiers
+    RDKV_HIP(launch_decode_tiles(c->d_chunks, 0, n16 + nrest, true, multi, c->d_arena, qp, ma, c->d_tail_len, st));
+    return RDKV_OK;
+  }
+  // the workgroups of both kernels announce themselves on the same counters: whichever finishes an item merges it
+  RDKV_HIP(launch_decode_tiered_split(c->d_chunks, n16, c->d_arena, qp, ma, st));
+  RDKV_HIP(launch_decode_tiles(c->d_chunks, n16, nrest, false, multi, c->d_arena, qp, ma, c->d_tail_len, st));
   return RDKV_OK;
 }
 

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -59,6 +60,26 @@ struct ItemK {
   int16_t slot_ch[kMaxSlots];    // channel held by a slot, -1 for padding
 };
 
+// Lets a kernel use more dynamic LDS than the runtime grants by default; asked once per kernel and device (a call costs
+// 0.5 us).
+template <class K>
+inline hipError_t allow_lds(K kernel, size_t lds, std::atomic<uint64_t>* asked) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (asked->load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  if (e == hipSuccess) asked->fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
+// `most`: the most the kernel is ever launched with
+#define RDKV_ALLOW_LDS(kernel, most)                        \
+  [&]() -> hipError_t {                                     \
+    static std::atomic<uint64_t> asked{0};                  \
+    return rdkv::allow_lds(kernel, most, &asked);           \
+  }()
+
 // One launch of small copies (copy_kernels.hip).  Segments with a side in staging memory are added first.
 constexpr int kStageWords = 16;        // completion words at the head of a staging region
 enum : int32_t { kSrcHost = 1, kDstHost = 2 };
@@ -114,7 +135,8 @@ hipError_t launch_gather_tail_rows(const uint8_t* tail, int64_t n_items, int32_t
 
 // chunks: the whole chunk table; workgroup b starts with chunks[first + b] and, if `multi`, follows Chunk::next.
 // tail_len: device word holding the appended tokens that exist so far (chunks of tier kTierTail end there)
-hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, bool multi, const uint8_t* arena,
+bool decode_tiles_take_rows(int n_chunks, bool multi);
+hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, bool rows16, bool multi, const uint8_t* arena,
                                const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, hipStream_t st);
 // one object per head-set count (hs1: up to 4 query heads per KV head, hs2: 8)
 // One object per head-set count (hs1: up to 4 query heads per KV head, hs2: 8) and row length class (long0: K rows

@@ -148,15 +148,10 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 }
 template <class Map>
 __device__ __forceinline__ void steps_on_histogram(const Problem& P, const Map& map, const int* suffix, Search& S) {
-  const int node = max(1, static_cast<int>(threadIdx.x & 63));
+  const int lane = threadIdx.x & 63, node = max(1, lane);
   const int depth = 31 - __clz(node);
-  while (!S.done && S.it < P.max_iters) {
-    double lo = S.lo, hi = S.hi;                 // the bracket the search has at this lane's node
-    for (int d = depth - 1; d >= 0; --d) {       // child 2 i: over budget (lo rises), child 2 i + 1: feasible (hi falls)
-      const double mid = (lo + hi) * 0.5;
-      if ((node >> d) & 1) hi = mid; else lo = mid;
-    }
-    const double lam = (lo + hi) * 0.5;
+  // bounds of the bit sum at lam: 0: over budget, 1: feasible, 2: feasible and inside the band, 3: cannot be decided here
+  const auto judge = [&](double lam) __attribute__((always_inline)) {
     long long s_min = P.base, s_max = P.base;
 #pragma unroll
     for (int k = 0; k < kThr; ++k) {
@@ -165,10 +160,36 @@ __device__ __forceinline__ void steps_on_histogram(const Problem& P, const Map& 
       s_min += P.gain(k, suffix[hist_slot(min(b + 1, Map::kBuckets))]);
       s_max += P.gain(k, suffix[hist_slot(b)]);
     }
-    const bool over = s_min > P.B_int;
-    const bool stop = !over && s_max <= P.B_int && s_min >= P.need;
-    const unsigned long long m_over = __ballot(over), m_stop = __ballot(stop);
-    const unsigned long long m_open = __ballot(!over && !stop && !(s_max < P.need));     // cannot be decided here
+    if (s_min > P.B_int) return 0;
+    if (s_max <= P.B_int && s_min >= P.need) return 2;
+    return s_max < P.need ? 1 : 3;
+  };
+  if (S.lo == 0.0 && !S.done && S.it < P.max_iters) {
+    // nothing was over budget so far: while that lasts the multipliers are hi / 2, hi / 4, ... (exact halves), a lane each
+    const double lam = ldexp(S.hi, -(lane + 1));
+    const int v = judge(lam);
+    const unsigned long long other = __ballot(v != 1);
+    const int run = min(other ? __ffsll(other) - 1 : 64, P.max_iters - S.it);    // feasible steps in a row
+    if (run > 0) {
+      S.it += run;
+      S.have = 1;
+      S.best = S.hi = readlane_f64(lam, run - 1);
+    }
+    if (run < 64 && S.it < P.max_iters) {
+      const int next = __builtin_amdgcn_readlane(v, run);
+      if (next == 3) return;
+      S.take(next, readlane_f64(lam, run));
+    }
+  }
+  while (!S.done && S.it < P.max_iters) {
+    double lo = S.lo, hi = S.hi;                 // the bracket the search has at this lane's node
+    for (int d = depth - 1; d >= 0; --d) {       // child 2 i: over budget (lo rises), child 2 i + 1: feasible (hi falls)
+      const double mid = (lo + hi) * 0.5;
+      if ((node >> d) & 1) hi = mid; else lo = mid;
+    }
+    const double lam = (lo + hi) * 0.5;
+    const int v = judge(lam);
+    const unsigned long long m_over = __ballot(v == 0), m_stop = __ballot(v == 2), m_open = __ballot(v == 3);
     int cur = 1, feasible = 0, it = S.it;        // feasible: the last node on the way with a feasible verdict
     bool open = false, done = false;
     while (cur < 64 && it < P.max_iters && !open && !done) {

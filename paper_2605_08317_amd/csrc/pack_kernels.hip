@@ -26,42 +26,47 @@ __device__ __forceinline__ int tier_slot(uint8_t b) {   // 16,8,4,2 -> 0..3 ; el
 }
 
 // counts of each stored tier inside every block of 1024 tokens of every item
+// four bytes of a bit map at any address
+struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
+
 __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restrict__ bits,
                                                          const int64_t* __restrict__ item_tok_off,
                                                          const int32_t* __restrict__ item_T,
                                                          const int32_t* __restrict__ item_blk_off,
-                                                         int32_t* __restrict__ blk_counts,
-                                                         int32_t* __restrict__ invalid) {
+                                                         int4* __restrict__ blk_counts) {
+  __shared__ int s_cnt[4][5];
   const int item = blockIdx.y;
   const int T = item_T[item];
   const int t0 = blockIdx.x * kPartBlock;
   if (t0 >= T) return;
-  const uint8_t* b = bits + item_tok_off[item];
-  int c[4] = {0, 0, 0, 0};
-  bool bad = false;
-  for (int t = t0 + threadIdx.x; t < min(T, t0 + kPartBlock); t += 256) {
-    const int s = tier_slot(b[t]);
-    bad |= s < 0 && b[t] != 0;           // neither a stored tier nor 0 (evicted)
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const uint8_t* b = bits + item_tok_off[item] + t0;
+  const int n = min(kPartBlock, T - t0), u = 4 * tid;
+  uint32_t four = 0;
+  if (u + 3 < n) four = reinterpret_cast<const Bytes4*>(b + u)->v;
+  else
+    for (int e = 0; e < 4; ++e)
+      if (u + e < n) four |= static_cast<uint32_t>(b[u + e]) << (8 * e);
+  int c[5] = {0, 0, 0, 0, 0};            // the four tiers, and what is neither a tier nor 0 (evicted)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) c[k] += (s == k);
-  }
-  if (bad) atomicOr(invalid, 1);
-  __shared__ int sm[4][4];
+  for (int e = 0; e < 4; ++e) {
+    const uint8_t v = static_cast<uint8_t>(four >> (8 * e));
+    const int s = tier_slot(v);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    int v = c[k];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6][k] = v;
+    for (int k = 0; k < 4; ++k) c[k] += __popcll(__ballot(s == k));
+    c[4] += __popcll(__ballot(s < 0 && v != 0));
   }
+  if ((tid & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) s_cnt[wave][k] = c[k];
   __syncthreads();
-  if (threadIdx.x < 4) {
-    const int k = threadIdx.x;
-    blk_counts[(item_blk_off[item] + blockIdx.x) * 4 + k] = sm[0][k] + sm[1][k] + sm[2][k] + sm[3][k];
+  if (tid == 0) {
+    int sum[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) sum[k] = s_cnt[0][k] + s_cnt[1][k] + s_cnt[2][k] + s_cnt[3][k];
+    blk_counts[item_blk_off[item] + blockIdx.x] = make_int4(sum[4] > 0 ? -1 : sum[0], sum[1], sum[2], sum[3]);
   }
 }
-
-// four bytes of a bit map at any address
-struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 
 // Inclusive sum over the wavefront's lanes on the ALUs (rows of 16, then across rows; a shuffle per step goes through LDS)
 template <int CTRL, int ROWS>
@@ -699,13 +704,12 @@ __global__ __launch_bounds__(kKThreads) void pack_k_mixed_kernel(PackArgs a) {
 }  // namespace
 
 hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                             const int32_t* item_blk_off, int32_t* blk_counts, int32_t* invalid,
-                             int n_items, int max_T, hipStream_t st) {
+                             const int32_t* item_blk_off, int32_t* blk_counts, int n_items, int max_T, hipStream_t st) {
   const int max_blk = (max_T + kPartBlock - 1) / kPartBlock;
   if (n_items == 0 || max_blk == 0) return hipSuccess;
   // `invalid` (zero on entry) is set when the map holds a value that is no bit-width of the method
   hipLaunchKernelGGL(tier_count_kernel, dim3(max_blk, n_items), dim3(256), 0, st, bits, item_tok_off, item_T,
-                     item_blk_off, blk_counts, invalid);
+                     item_blk_off, reinterpret_cast<int4*>(blk_counts));
   return hipGetLastError();
 }
 

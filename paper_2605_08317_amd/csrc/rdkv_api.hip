@@ -18,7 +18,7 @@
 
 namespace rdkv {
 hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                             const int32_t* item_blk_off, int32_t* blk_counts, int32_t* invalid, int n_items, int max_T, hipStream_t st);
+                             const int32_t* item_blk_off, int32_t* blk_counts, int n_items, int max_T, hipStream_t st);
 hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
                                const int32_t* item_blk_off, const int32_t* blk_counts, const int64_t* idx_base,
                                int32_t* tier_idx, int n_items, int max_T, hipStream_t st);
@@ -752,9 +752,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   c->counts.assign(n * 4, 0);
   c->seg_off.assign(n * 16, 0);
   const size_t n1 = static_cast<size_t>(std::max<int64_t>(n, 1));
-  // tier counts of every block of the bit map: the allocation's own, or counted here (then the invalid-value flag)
+  // tier counts of every block of the bit map: the allocation's own, or counted here
   const bool counted = d_blk_counts != nullptr;
-  const int64_t n_counts = it.n_blocks * 4 + (counted ? 0 : 1);
+  const int64_t n_counts = it.n_blocks * 4;
   if (!counted) d_blk_counts = tmp.get<int32_t>(n_counts);
   // [items][4] kept-position bases, [items][16] segment offsets, [items][4] rows per tier
   int64_t* d_idx_base = tmp.get<int64_t>(n1 * 22);
@@ -771,12 +771,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     // memory and the host watches for them (a copy to host memory and a wait for the stream: 25 us more).
     if (!counted) {
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
-      CopyArgs clear{};
-      clear.fill(d_blk_counts + it.n_blocks * 4, sizeof(int32_t), 0u, 0u);
-      plan_copy(clear);
-      PACK_HIP(launch_copy(clear, st));
-      PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_blk_counts + it.n_blocks * 4,
-                                 static_cast<int>(n), it.max_T, st));
+      PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, static_cast<int>(n), it.max_T, st));
     }
     std::vector<int32_t> h_counts(n_counts, 0);
     std::vector<uint8_t> h_bits_ch(mixed ? n * kHeadDim : 0);
@@ -793,8 +788,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
         if (mixed) std::memcpy(h_bits_ch.data(), r.data + counts_b, h_bits_ch.size());
       }));
     }
-    if (!counted && h_counts[it.n_blocks * 4] != 0)
-      return bail(fail(RDKV_ERR_INVALID_ARG, "bits_tok holds a value outside {0, 2, 4, 8, 16}"));
+    if (!counted)
+      for (int64_t b = 0; b < it.n_blocks; ++b)      // (a block with any other value says so in its first count)
+        if (h_counts[b * 4] < 0) return bail(fail(RDKV_ERR_INVALID_ARG, "bits_tok holds a value outside {0, 2, 4, 8, 16}"));
     for (int64_t i = 0; i < n; ++i) {
       const int64_t b1 = i + 1 < n ? it.blk_off[i + 1] : it.n_blocks;
       for (int64_t b = it.blk_off[i]; b < b1; ++b)

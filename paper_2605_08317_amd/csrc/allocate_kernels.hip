@@ -23,8 +23,10 @@
 // workgroup that finishes an item's pass last runs the steps that follow it.
 // Channel maps (128 units) take one wavefront (channel_allocate_kernel).
 #include <algorithm>
+#include <type_traits>
 
 #include "rdkv_internal.h"
+#include "wave_ops.h"
 
 namespace rdkv {
 
@@ -233,16 +235,14 @@ __device__ __forceinline__ void steps_on_histogram(const Problem& P, const Map& 
 // 13 us took 47), those open to [lo, hi] a few.
 struct Hull { double lo, hi; };
 __device__ __forceinline__ Hull bracket_of(const Search& S) { return Hull{S.lo, S.hi}; }
+// (by one wavefront per outcome: `feasible` says which; gives lo or hi)
 template <class Map>
-__device__ __forceinline__ Hull narrow_hull(const Problem& P, const Map& map, const int* suffix, const Search& S) {
-  const double lam = (S.lo + S.hi) * 0.5;
-  Search over = S, feasible = S;
-  over.take(0, lam);
-  feasible.take(1, lam);
-  steps_on_histogram(P, map, suffix, over);
-  steps_on_histogram(P, map, suffix, feasible);
-  return Hull{feasible.lo, over.hi};
+__device__ __forceinline__ double narrow_hull(const Problem& P, const Map& map, const int* suffix, Search S, bool feasible) {
+  S.take(feasible, (S.lo + S.hi) * 0.5);
+  steps_on_histogram(P, map, suffix, S);
+  return feasible ? S.lo : S.hi;
 }
+constexpr int kManyOpen = 4096;      // open units from which that pays
 constexpr int kFewOpen = 1024;       // open units that a single wavefront takes the remaining steps on
 
 // In place: suffix[b] = sum of suffix[b ..]; suffix[BUCKETS] = 0.  All threads; barriers inside.
@@ -256,12 +256,8 @@ __device__ __forceinline__ void suffix_sums(int* suffix, int* s_wave) {
     v[i] = suffix[hist_slot(tid * kPer + i)];
     local += v[i];
   }
-  int incl = local;                      // sum over this lane and the higher ones
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_down(incl, o);
-    if (lane + o < 64) incl += t;
-  }
+  const int below = static_cast<int>(wave_scan(static_cast<uint32_t>(local)));
+  const int incl = __builtin_amdgcn_readlane(below, 63) - below + local;      // sum over this lane and the higher ones
   if (lane == 0) s_wave[wave] = incl;
   __syncthreads();
   int run = incl - local;
@@ -389,9 +385,26 @@ __device__ __forceinline__ void steps_in_wave(const Problem& P, const float (&w)
   }
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
+// ... and the registers that n <= kFewOpen units take (a step compares all of them with every threshold)
+template <class Unit>
+__device__ __forceinline__ void steps_on_few(const Problem& P, int n, long long fixed, const Hull& h, Search& S, Unit&& unit) {
+  const int lane = threadIdx.x & 63;
+  const auto run = [&](auto& u, auto per) __attribute__((always_inline)) {
+    constexpr int PER = decltype(per)::value;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) u[i] = i * 64 + lane < n ? unit(i * 64 + lane) : 0.f;
+    steps_in_wave<PER>(P, u, fixed, h, S);
+  };
+  if (n <= 64) {
+    float u[1];
+    run(u, std::integral_constant<int, 1>{});
+  } else if (n <= 256) {
+    float u[4];
+    run(u, std::integral_constant<int, 4>{});
+  } else {
+    float u[16];
+    run(u, std::integral_constant<int, 16>{});
+  }
 }
 
 __device__ __forceinline__ void report(const AllocArgs& a, int item, bool searched, const Search& S) {
@@ -507,10 +520,10 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
       Hull hull = bracket_of(S);
       OpenBuckets open(P, map, hull);
       int n = open.count(s_hist);
-      if (n > kFewOpen) {
-        if (wave == 0) {
-          hull = narrow_hull(P, map, s_hist, S);
-          if (lane == 0) s_hull = hull;
+      if (n > kManyOpen) {
+        if (wave < 2) {
+          const double end = narrow_hull(P, map, s_hist, S, wave == 0);
+          if (lane == 0) (wave == 0 ? s_hull.lo : s_hull.hi) = end;
         }
         __syncthreads();
         hull = s_hull;
@@ -522,13 +535,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
         uint32_t mine = 0;                 // which of this thread's units
 #pragma unroll
         for (int j = 0; j < REG; ++j) mine |= pat.contains(v[j]) ? 1u << j : 0u;
-        int incl = __popc(mine);
-        const int own = incl;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int x = __shfl_up(incl, o);
-          if (lane >= o) incl += x;
-        }
+        const int own = __popc(mine), incl = static_cast<int>(wave_scan(static_cast<uint32_t>(own)));
         int base = 0;
         if (lane == 63) base = atomicAdd(&s_n, incl);
         float* dst = s_list + __builtin_amdgcn_readlane(base, 63) + incl - own;
@@ -539,10 +546,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
         const long long fixed = open.fixed(P, s_hist);
         if (n <= kFewOpen) {
           if (wave == 0) {
-            float u[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) u[i] = i * 64 + lane < n ? s_list[i * 64 + lane] : 0.f;
-            steps_in_wave<16>(P, u, fixed, hull, S);
+            steps_on_few(P, n, fixed, hull, S, [&](int i) { return s_list[i]; });
             if (lane == 0) s_search = S;
           }
           __syncthreads();
@@ -722,7 +726,9 @@ constexpr size_t kHistLds = Anchored::kWords * sizeof(int);
 __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   extern __shared__ __align__(16) unsigned char smem[];
   int* s_hist = reinterpret_cast<int*>(smem);
-  __shared__ int s_wave[kWaves], s_flag;
+  __shared__ int s_wave[kWaves], s_flag, s_many;
+  __shared__ Hull s_hull;
+  __shared__ Search s_search;
   const AllocArgs& a = m.a;
   const int item = blockIdx.y;
   const int U = a.item_U[item];
@@ -770,16 +776,25 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   }
   __syncthreads();
   suffix_sums<Anchored::kBuckets>(s_hist, s_wave);
-  if (tid < 64) {
+  if (tid < 128) {                       // two wavefronts, the same steps
     Search S{0.0, static_cast<double>(mx), 0.0, 0, 0, 0};
     steps_on_histogram(P, map, s_hist, S);
     S.done = S.done || S.it >= P.max_iters;
     Hull hull = bracket_of(S);
     OpenBuckets open(P, map, hull);
-    if (!S.done && open.count(s_hist) > kFewOpen) {
-      hull = narrow_hull(P, map, s_hist, S);
-      open = OpenBuckets(P, map, hull);
+    const bool many = !S.done && open.count(s_hist) > kManyOpen;
+    if (many) {
+      const double end = narrow_hull(P, map, s_hist, S, tid < 64);
+      if (lane == 0) (tid < 64 ? s_hull.lo : s_hull.hi) = end;
     }
+    if (tid == 0) s_many = many;
+    if (tid == 0) s_search = S;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const Search S = s_search;
+    const Hull hull = s_many ? s_hull : bracket_of(S);
+    const OpenBuckets open(P, map, hull);
     if (tid == 0) {
       st.s = S;
       st.hull = hull;
@@ -854,10 +869,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
     const Hull hull = st.hull;
     if (n <= kFewOpen) {
       if (wave == 0) {
-        float u[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) u[i] = i * 64 + lane < n ? load_agent(gl + i * 64 + lane) : 0.f;
-        steps_in_wave<16>(P, u, fixed, hull, S);
+        steps_on_few(P, n, fixed, hull, S, [&](int i) { return load_agent(gl + i); });
         if (lane == 0) s_search = S;
       }
       __syncthreads();

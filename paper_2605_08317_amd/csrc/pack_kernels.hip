@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "rdkv_internal.h"
+#include "wave_ops.h"
 
 namespace rdkv {
 
@@ -66,21 +67,6 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
     for (int k = 0; k < 5; ++k) sum[k] = s_cnt[0][k] + s_cnt[1][k] + s_cnt[2][k] + s_cnt[3][k];
     blk_counts[item_blk_off[item] + blockIdx.x] = make_int4(sum[4] > 0 ? -1 : sum[0], sum[1], sum[2], sum[3]);
   }
-}
-
-// Inclusive sum over the wavefront's lanes on the ALUs (rows of 16, then across rows; a shuffle per step goes through LDS)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t lanes_below(uint32_t v) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
-}
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
-  v += lanes_below<0x111, 0xF>(v);   // row_shr:1
-  v += lanes_below<0x112, 0xF>(v);
-  v += lanes_below<0x114, 0xF>(v);
-  v += lanes_below<0x118, 0xF>(v);
-  v += lanes_below<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-  v += lanes_below<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-  return v;
 }
 
 // Writes the ascending position lists: tier_idx[item_base + tier_base + rank].  One workgroup = one block of 1024 tokens, a

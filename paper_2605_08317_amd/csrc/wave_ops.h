@@ -1,0 +1,36 @@
+// Sums and maxima over the lanes of a wavefront on the ALUs: row shifts inside rows of 16 lanes, then across the rows.  (A
+// shuffle per step goes through LDS, 100 cycles each where nothing covers them.)
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace rdkv {
+
+// v of the lane CTRL names, 0 where there is none (rows outside the row mask ROWS included)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t lanes_below(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
+}
+// inclusive sum over this lane and the lower ones
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += lanes_below<0x111, 0xF>(v);   // row_shr:1
+  v += lanes_below<0x112, 0xF>(v);
+  v += lanes_below<0x114, 0xF>(v);
+  v += lanes_below<0x118, 0xF>(v);
+  v += lanes_below<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += lanes_below<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+// maximum of numbers >= 0 (NaN is ignored), in every lane
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, 0.f);
+  v = fmaxf(v, __uint_as_float(lanes_below<0x111, 0xF>(__float_as_uint(v))));
+  v = fmaxf(v, __uint_as_float(lanes_below<0x112, 0xF>(__float_as_uint(v))));
+  v = fmaxf(v, __uint_as_float(lanes_below<0x114, 0xF>(__float_as_uint(v))));
+  v = fmaxf(v, __uint_as_float(lanes_below<0x118, 0xF>(__float_as_uint(v))));
+  v = fmaxf(v, __uint_as_float(lanes_below<0x142, 0xA>(__float_as_uint(v))));
+  v = fmaxf(v, __uint_as_float(lanes_below<0x143, 0xC>(__float_as_uint(v))));
+  return __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(v)), 63)));
+}
+
+}  // namespace rdkv

@@ -10,7 +10,7 @@
 //           (cbsz = 4);  B = K codes: lane = token (64 per tile), 4 channels per step;  D: lane = token, four heads.
 //           Eight steps cover a quantization group of 32 channels; the group's scale, the lane's own, multiplies the
 //           partial product (fusion identity of App. B) and the offsets go through one more product with the group
-//           sums of q.  Products with unit vectors then turn each block, so that lane (block b, head j) holds tokens
+//           sums of q.  Exchanges inside the quads then turn each block, so that lane (block b, head j) holds tokens
 //           4b..4b+3.  With the query on the B side instead the result needed no turning, but every operand of it came
 //           from LDS and every scale through four cross-lane moves: 16 ragged sequences with 8 query heads per KV head
 //           45.4 -> 44.1 us, a layer of 16 MB 11.0 -> 10.7 us.

@@ -121,16 +121,27 @@ __device__ __forceinline__ uint4 load_query(const uint16_t* __restrict__ q, int 
 }
 
 // The K products leave lane = token with the four heads of a set in its registers; the softmax and P V want lane (block,
-// head) with the block's four tokens: a 4x4 transposition per block, which products with unit vectors do exactly.
+// head) with the block's four tokens: a 4x4 transposition inside each quad of lanes, in two steps that exchange registers
+// with lane ^ 1 and lane ^ 2.  Moves only, so that a head whose logits are not finite stays by itself (products with
+// unit vectors, which take the same time -- a 70B-shaped batch 44.1 and 44.2 us -- spread its NaN over the set: 0 x NaN).
 template <int HS>
 __device__ __forceinline__ void to_head_lanes(const float (&xt)[HS][4], int j, float (&x)[HS][4]) {
+  const bool odd = (j & 1) != 0, high = (j & 2) != 0;
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) {
-    floatx4 t = {0.f, 0.f, 0.f, 0.f};
+    float t[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) t = __builtin_amdgcn_mfma_f32_4x4x1f32(xt[hs][k], j == k ? 1.0f : 0.0f, t, 0, 0, 0);
+    for (int k = 0; k < 4; k += 2) {
+      const float from1 = dpp_f32<0xB1>(xt[hs][k + 1]), from0 = dpp_f32<0xB1>(xt[hs][k]);   // quad_perm [1, 0, 3, 2]
+      t[k] = odd ? from1 : xt[hs][k];
+      t[k + 1] = odd ? xt[hs][k + 1] : from0;
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[hs][i] = t[i];
+    for (int k = 0; k < 2; ++k) {
+      const float from2 = dpp_f32<0x4E>(t[k + 2]), from0 = dpp_f32<0x4E>(t[k]);             // quad_perm [2, 3, 0, 1]
+      x[hs][k] = high ? from2 : t[k];
+      x[hs][k + 2] = high ? t[k + 2] : from0;
+    }
   }
 }
 

@@ -19,6 +19,11 @@
  *    the schedule), rdkv_calibrate_eps, rdkv_cache_stats and rdkv_cache_export
  *    (host results) wait for the stream.  rdkv_weights, rdkv_allocate,
  *    rdkv_decode_attn, rdkv_decode_attn_bf16 and rdkv_cache_append never wait.
+ *  - Under graph capture the calls that never wait may be recorded and replayed (what
+ *    rdkv_decode_attn shares then is said there; rdkv_weights and rdkv_allocate record
+ *    their lengths and budgets by value and take their scratch as always).  A call that
+ *    waits for a stream under capture is refused with RDKV_ERR_HIP before anything is
+ *    recorded.
  *  - Every function returns an rdkv_status and never throws or aborts; host-side
  *    arguments are validated before anything is launched (what only the device can
  *    see -- the values inside a device bit map -- is reported after the one wait of

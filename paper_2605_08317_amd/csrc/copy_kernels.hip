@@ -6,6 +6,9 @@
 // What bounds it is latency: a read over PCIe takes 1.5 us, so every piece has workgroups of its own (pieces one after the
 // other in each workgroup: 7 us a launch) and nothing is flushed: what goes to host memory goes past the caches, and a wait
 // for the workgroup's own accesses stands in front of the completion word (a system-scope release writes back all of L2).
+#include <algorithm>
+#include <cstring>
+
 #include "rdkv_internal.h"
 
 namespace rdkv {
@@ -66,6 +69,16 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
   }
 }
 
+// Bytes that come with the launch: of a graph's node, which keeps its arguments.
+struct ValueArgs {
+  uint8_t* dst;
+  int32_t bytes;
+  uint8_t data[3072];                  // (a launch carries up to 4 KB of arguments)
+};
+__global__ __launch_bounds__(kCopyThreads) void copy_value_kernel(ValueArgs a) {
+  for (int i = threadIdx.x; i < a.bytes; i += kCopyThreads) a.dst[i] = a.data[i];
+}
+
 }  // namespace
 
 void plan_copy(CopyArgs& a) {
@@ -94,6 +107,24 @@ hipError_t launch_copy(const CopyArgs& a, hipStream_t st) {
   const int blocks = a.n == 0 ? 1 : a.first[a.n];
   hipLaunchKernelGGL(copy_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kCopyThreads), 0, st, a);
   return hipGetLastError();
+}
+
+hipError_t launch_copy_by_value(const CopyArgs& a, hipStream_t st) {
+  for (int k = 0; k < a.n; ++k)
+    if (a.seg[k].side != kSrcHost) return hipErrorStreamCaptureUnsupported;
+  for (int k = 0; k < a.n; ++k) {
+    const CopySeg& s = a.seg[k];
+    ValueArgs v{};
+    for (int64_t at = 0; at < s.bytes; at += v.bytes) {
+      v.dst = static_cast<uint8_t*>(s.dst) + at;
+      v.bytes = static_cast<int32_t>(std::min<int64_t>(s.bytes - at, sizeof(v.data)));
+      std::memcpy(v.data, static_cast<const uint8_t*>(s.src) + at, v.bytes);
+      hipLaunchKernelGGL(copy_value_kernel, dim3(1), dim3(kCopyThreads), 0, st, v);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+  }
+  return hipSuccess;
 }
 
 }  // namespace rdkv

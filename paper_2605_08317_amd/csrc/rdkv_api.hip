@@ -164,7 +164,8 @@ struct StageRegion {
   uint8_t* data = nullptr;        // pinned: what the host fills (or reads)
   uint32_t* words = nullptr;
   uint32_t seq = 0;
-  void* own = nullptr;            // not of the ring: an allocation of its own, given back by release()
+  void* own = nullptr;            // not of the ring: an allocation of its own
+  bool recorded = false;          // the stream is under capture: `own` is ordinary memory that no kernel ever sees
   bool done() const {
     for (int i = 0; i < kStageWords; ++i)
       if (__atomic_load_n(words + i, __ATOMIC_ACQUIRE) != seq) return false;
@@ -272,32 +273,53 @@ class Staging {
 };
 Staging g_staging[kMaxDevices];
 
-hipError_t stage_acquire(size_t bytes, bool held, StageRegion* out, int* device) {
+// A region for a launch on `st`.  Under capture the bytes travel in the recorded launches' arguments: a replay comes when
+// a region of the ring is long somebody else's.
+hipError_t stage_acquire(size_t bytes, bool held, hipStream_t st, StageRegion* out, int* device) {
   hipError_t e = hipGetDevice(device);
   if (e != hipSuccess) return e;
   if (*device < 0 || *device >= kMaxDevices) return hipErrorInvalidDevice;
-  return g_staging[*device].acquire(bytes, held, out);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  e = hipStreamIsCapturing(st, &cap);
+  if (e != hipSuccess) return e;
+  if (cap == hipStreamCaptureStatusNone) return g_staging[*device].acquire(bytes, held, out);
+  if (held) return hipErrorStreamCaptureUnsupported;      // (the host would wait)
+  StageRegion r;
+  r.recorded = true;
+  r.own = std::malloc(std::max<size_t>(bytes, 1));
+  if (!r.own) return hipErrorOutOfMemory;
+  r.data = static_cast<uint8_t*>(r.own);
+  *out = r;
+  return hipSuccess;
 }
 
 // Launches a copy to or from a region.  `last`: the region's only launch and not read by the host; memory that is not of
 // the ring is given back then (after the kernel; the ring looks after itself).
 hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_t st) {
+  if (r.recorded) {
+    const hipError_t e = launch_copy_by_value(a, st);
+    std::free(r.own);
+    return e;
+  }
   plan_copy(a);
   a.words = r.words;
   a.seq = r.seq;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(st, &cap);
-  const bool captured = cap != hipStreamCaptureStatusNone;
-  if (e == hipSuccess && captured && (!last || r.own)) e = hipErrorStreamCaptureUnsupported;   // the host waits for it
   for (int i = a.host_blocks; i < kStageWords; ++i) __atomic_store_n(r.words + i, r.seq, __ATOMIC_RELAXED);   // nobody's
-  if (e == hipSuccess) e = launch_copy(a, st);
-  // a captured copy reads the ring at its replay, if ever: nothing to wait for before the bytes are used again
-  if (e != hipSuccess || captured) r.mark_done();
+  hipError_t e = launch_copy(a, st);
+  if (e != hipSuccess) r.mark_done();
   if (last && r.own) {
     if (e == hipSuccess) e = stage_wait(r, st);
     (void)hipHostFree(r.own);
   }
   return e;
+}
+
+// For the calls that wait for the stream: refuses a stream under capture before anything is recorded.
+rdkv_status refuse_capture(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  RDKV_HIP(hipStreamIsCapturing(st, &cap));
+  if (cap == hipStreamCaptureStatusNone) return RDKV_OK;
+  return fail(RDKV_ERR_HIP, "the call waits for the stream, which is under capture: %s", hipGetErrorString(hipErrorStreamCaptureUnsupported));
 }
 
 // Launches a copy, waits for it -- and so for everything queued on the stream before it -- and hands the region to `read`.
@@ -316,7 +338,7 @@ hipError_t stage_round_trip(CopyArgs& a, int device, const StageRegion& r, hipSt
 hipError_t stage_stream_idle(hipStream_t st) {
   StageRegion r;
   int dev = 0;
-  const hipError_t e = stage_acquire(0, true, &r, &dev);
+  const hipError_t e = stage_acquire(0, true, st, &r, &dev);
   if (e != hipSuccess) return e;
   CopyArgs a{};
   return stage_round_trip(a, dev, r, st, [] {});
@@ -327,7 +349,7 @@ hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t st) {
   if (bytes == 0) return hipSuccess;
   StageRegion r;
   int dev = 0;
-  hipError_t e = stage_acquire(bytes, false, &r, &dev);
+  hipError_t e = stage_acquire(bytes, false, st, &r, &dev);
   if (e != hipSuccess) return e;
   std::memcpy(r.data, src, bytes);
   CopyArgs a{};
@@ -641,7 +663,7 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
   if (!d) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   StageRegion region;
   int dev = 0;
-  RDKV_HIP(stage_acquire(bytes, false, &region, &dev));
+  RDKV_HIP(stage_acquire(bytes, false, st, &region, &dev));
   uint8_t* blob = region.data;
   std::memset(blob, 0, bytes);
   int64_t* tok_off = reinterpret_cast<int64_t*>(blob);
@@ -779,7 +801,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       const int64_t counts_b = round_up(n_counts * static_cast<int64_t>(sizeof(int32_t)), 16);
       StageRegion r;
       int dev = 0;
-      PACK_HIP(stage_acquire(static_cast<size_t>(counts_b) + h_bits_ch.size(), true, &r, &dev));
+      PACK_HIP(stage_acquire(static_cast<size_t>(counts_b) + h_bits_ch.size(), true, st, &r, &dev));
       CopyArgs a{};
       a.add(d_blk_counts, r.data, n_counts * static_cast<int64_t>(sizeof(int32_t)), kDstHost);
       if (mixed) a.add(bits_ch, r.data + counts_b, static_cast<int64_t>(h_bits_ch.size()), kDstHost);
@@ -1159,7 +1181,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       }
       StageRegion r;
       int dev = 0;
-      PACK_HIP(stage_acquire(static_cast<size_t>(plan_b + tables_b), false, &r, &dev));
+      PACK_HIP(stage_acquire(static_cast<size_t>(plan_b + tables_b), false, st, &r, &dev));
       int64_t* plan = reinterpret_cast<int64_t*>(r.data);
       std::memcpy(plan, idx_base.data(), n * 4 * sizeof(int64_t));
       std::memcpy(plan + n1 * 4, c->seg_off.data(), n * 16 * sizeof(int64_t));
@@ -1314,6 +1336,8 @@ rdkv_status rdkv_calibrate_eps(const rdkv_config* cfg, const void* K, const void
     if (cfg->seq_lens[b] < 1) return fail(RDKV_ERR_SHAPE, "seq_lens[%d] = %d: calibration needs at least one token", b, cfg->seq_lens[b]);
   hipStream_t st = static_cast<hipStream_t>(stream);
   Allocator al{cfg->alloc, cfg->free_, cfg->alloc_user};
+  s = refuse_capture(st);
+  if (s != RDKV_OK) return s;
   Temp tmp(al, st);
   Items it = make_items(cfg->seq_lens, cfg->batch, cfg->hkv);
   const size_t n = static_cast<size_t>(it.n_items);
@@ -1391,6 +1415,7 @@ rdkv_status rdkv_pack(const rdkv_config* cfg, const void* K, const void* V, cons
     return fail(RDKV_ERR_INVALID_ARG, "K, V and bits_tok must not be null");
   if (mixed && it.n_items > 0 && !bits_ch)
     return fail(RDKV_ERR_INVALID_ARG, "bits_ch must not be null in channel-wise mode");
+  if (it.n_items > 0 && (s = refuse_capture(st)) != RDKV_OK) return s;
   Temp tmp(al, st);
   Tables tb;
   s = make_tables(cfg, it, false, tmp, st, &tb);
@@ -1409,6 +1434,7 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   Allocator al{cfg->alloc, cfg->free_, cfg->alloc_user};
   Items it = make_items(cfg->seq_lens, cfg->batch, cfg->hkv);
   if (it.total_tokens > 0 && (!K || !V || !Q_obs)) return fail(RDKV_ERR_INVALID_ARG, "K, V and Q_obs must not be null");
+  if (it.n_items > 0 && (s = refuse_capture(st)) != RDKV_OK) return s;
   Temp tmp(al, st);
   const size_t nt = static_cast<size_t>(std::max<int64_t>(it.total_tokens, 1));
   const size_t ni = static_cast<size_t>(std::max<int64_t>(it.n_items, 1));
@@ -1672,7 +1698,7 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
   const size_t table_b = table.size() * sizeof(Chunk), items_b = items_sched.size() * sizeof(ItemK);
   StageRegion r;
   int dev = 0;
-  hipError_t e = stage_acquire(table_b + items_b, false, &r, &dev);
+  hipError_t e = stage_acquire(table_b + items_b, false, st, &r, &dev);
   if (e == hipSuccess) {
     if (table_b > 0) std::memcpy(r.data, table.data(), table_b);
     if (items_b > 0) std::memcpy(r.data + table_b, items_sched.data(), items_b);
@@ -1720,6 +1746,8 @@ rdkv_status rdkv_cache_reserve_tail(rdkv_cache* c, int32_t max_new_tokens, void*
   if (c->tail_cap != 0) return fail(RDKV_ERR_INVALID_ARG, "the tail of this cache is already reserved (%d tokens)", c->tail_cap);
   if (c->n_items == 0) { c->tail_cap = max_new_tokens; return RDKV_OK; }
   hipStream_t st = static_cast<hipStream_t>(stream);
+  rdkv_status s = refuse_capture(st);
+  if (s != RDKV_OK) return s;
   Allocator al{c->alloc, c->free_, c->alloc_user};
   const int64_t tail_tiles = (max_new_tokens + kTile64 - 1) / kTile64, tile_bytes = kTile64 * kHeadDim * 2;
   const int64_t side = c->n_items * tail_tiles * tile_bytes;     // K tiles of all items, then V tiles
@@ -1728,7 +1756,7 @@ rdkv_status rdkv_cache_reserve_tail(rdkv_cache* c, int32_t max_new_tokens, void*
   c->d_tail = d_tail;
   c->tail_cap = max_new_tokens;
   c->tail_len = 0;
-  const rdkv_status s = rebuild_schedule(c, d_tail, 2 * side, st);     // rows not yet appended must read as zeros
+  s = rebuild_schedule(c, d_tail, 2 * side, st);     // rows not yet appended must read as zeros
   if (s != RDKV_OK) {
     c->d_tail = nullptr;
     c->tail_cap = 0;
@@ -1756,9 +1784,11 @@ rdkv_status rdkv_cache_tail_len_sync(rdkv_cache* c, void* stream, int32_t* out) 
   if (!c) return fail(RDKV_ERR_INVALID_ARG, "cache is null");
   if (c->n_items > 0 && c->d_tail_len) {
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const rdkv_status s = refuse_capture(st);
+    if (s != RDKV_OK) return s;
     StageRegion r;
     int dev = 0;
-    RDKV_HIP(stage_acquire(sizeof(int32_t), true, &r, &dev));
+    RDKV_HIP(stage_acquire(sizeof(int32_t), true, st, &r, &dev));
     CopyArgs a{};
     a.add(c->d_tail_len, r.data, sizeof(int32_t), kDstHost);
     RDKV_HIP(stage_round_trip(a, dev, r, st, [&] { std::memcpy(&c->tail_len, r.data, sizeof(int32_t)); }));

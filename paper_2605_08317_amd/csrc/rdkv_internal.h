@@ -106,6 +106,8 @@ struct CopyArgs {
 };
 void plan_copy(CopyArgs& a);           // after the last segment, before launch_copy
 hipError_t launch_copy(const CopyArgs& a, hipStream_t st);
+// The same for a stream under capture: segments out of host memory only, whose bytes the recorded launches carry themselves.
+hipError_t launch_copy_by_value(const CopyArgs& a, hipStream_t st);
 
 struct DenseArgs {
   const uint16_t* K;

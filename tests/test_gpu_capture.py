@@ -1,0 +1,100 @@
+"""The staged calls recorded in a HIP graph: their host tables go with the graph, so that a replay neither depends on the
+staging memory the call used at capture nor touches it, and the calls that wait for the stream record nothing."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import B
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(batch, hkv, T, s_obs, seed):
+    rng = torch.Generator().manual_seed(seed)
+    K = torch.randn(batch * hkv * T * 128, generator=rng).to(torch.bfloat16).cuda()
+    Q = torch.randn((batch, hkv, s_obs, 128), generator=rng).to(torch.bfloat16).cuda()
+    return K, Q
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("batch,T", [(2, 700), (90, 64), (4000, 33)])   # a table of one launch, of several, larger than the ring
+def test_replays_of_the_staged_calls(batch, T, mixed):
+    b, hkv = B(), 8
+    print(f"[case] captured weights and allocation, {batch} x {T}, channel-wise {mixed}", flush=True)
+    K, Q = _batch(batch, hkv, T, 32, batch)
+    budgets = [0.5 + s % 4 for s in range(batch)]
+    cfg = b.Config([T] * batch, hkv, hkv, budget_bits=budgets, s_obs=32, **b.torch_allocator_hooks(),
+                   **({"k_mode": b.RDKV_K_CHANNELWISE} if mixed else {}))
+    # unrelated work whose tables go once round the ring between two replays
+    other_batch = 1100
+    oK, oQ = _batch(other_batch, hkv, 40, 32, 7)
+    other = b.Config([40] * other_batch, hkv, hkv, budget_bits=[2.0] * other_batch, s_obs=32, **b.torch_allocator_hooks())
+    oq = oQ[:, :, 0].contiguous()
+
+    def unrelated():
+        outs = []
+        for _ in range(3):
+            cache = b.rdkv_compress(other, oK, oK, oQ)
+            outs.append(b.rdkv_decode_attn(cache, oq)[0].clone())
+            torch.cuda.synchronize()
+            cache.free()
+        return outs
+
+    def staged():
+        w_tok, w_ch = b.rdkv_weights(cfg, K, Q, want_channel=mixed)
+        bits_tok, bits_ch = b.rdkv_allocate(cfg, w_tok, w_ch)
+        return [x for x in (w_tok, w_ch, bits_tok, bits_ch) if x is not None]
+
+    eager, expected = staged(), unrelated()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        recorded = staged()
+    for _ in range(4):
+        for x in recorded:
+            x.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        got = unrelated()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(recorded, eager))
+        assert all(torch.equal(x, y) for x, y in zip(got, expected))
+
+
+def test_calls_that_wait_are_refused_under_capture():
+    b, hkv, T = B(), 2, 300
+    K, Q = _batch(1, hkv, T, 32, 1)
+    cfg = b.Config([T], hkv, hkv, budget_bits=[2.0], s_obs=32, **b.torch_allocator_hooks())
+    bits = torch.from_numpy(np.random.default_rng(1).choice(np.array([0, 2, 4], np.uint8), size=hkv * T)).cuda()
+    q = Q[:, :, 0].contiguous()
+    cache, tailed = b.rdkv_pack(cfg, K, K, bits), b.rdkv_pack(cfg, K, K, bits)
+    b.rdkv_cache_reserve_tail(tailed, 64)
+    row = K[:hkv * 128].view(1, hkv, 128)
+    for _ in range(40):
+        b.rdkv_cache_append(tailed, row, row)
+    before, _ = b.rdkv_decode_attn(tailed, q)
+    out, lse = torch.empty_like(before), torch.empty_like(before[..., 0])
+    tail_cfg = b.Config([40], hkv, hkv, budget_bits=[2.0], s_obs=32, **b.torch_allocator_hooks())
+    calls = [lambda: b.rdkv_pack(cfg, K, K, bits), lambda: b.rdkv_compress(cfg, K, K, Q), lambda: b.rdkv_calibrate_eps(cfg, K, K),
+             lambda: b.rdkv_cache_reserve_tail(cache, 8), lambda: b.rdkv_cache_tail_len_sync(tailed),
+             lambda: b.rdkv_cache_rebudget_tail(tailed, tail_cfg, Q)]
+    status = []
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for call in calls:
+            try:
+                call()
+                status.append(0)
+            except b.RdkvError as e:
+                status.append(e.status)
+        b.rdkv_decode_attn(tailed, q, out, lse)          # the capture goes on
+    assert status == [5] * len(calls)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, before)
+    for call in calls:                                   # and outside of one they all still run
+        call()
+    torch.cuda.synchronize()

@@ -54,6 +54,8 @@ struct AllocArgs {
   int32_t* iters_out;          // [items] or null: bisection steps taken
   const int32_t* item_blk_off; // [items]: first 1024-unit block of the item, or null (no counts wanted)
   int4* blk_counts;            // [blocks] out: units of the block in tiers 16, 8, 4, 2
+  const int32_t* order;        // the items of this launch, or null: all of them as they stand
+  __device__ __forceinline__ int item_of(int slot) const { return order ? order[slot] : slot; }
 };
 
 // largest fp32 number not above t (t >= 0): for fp32 w, (double) w > t exactly when w > below(t)
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   __shared__ float s_max[kWaves];
   __shared__ Search s_search;
   __shared__ Hull s_hull;
-  const int item = blockIdx.x;
+  const int item = a.item_of(blockIdx.x);
   const int U = a.item_U[item];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* __restrict__ w = a.w + a.item_off[item];
@@ -673,10 +675,11 @@ struct SearchState {
 };
 struct MultiArgs {
   AllocArgs a;
-  int32_t* hist;        // [items][kBuckets], zero on entry
-  SearchState* state;   // [items], zero on entry
-  float* list;          // [items][kListCap]
-  float* slice_max;     // [items][slices]
+  // per item of the launch (grid row), not of the batch
+  int32_t* hist;        // [rows][kBuckets], zero on entry
+  SearchState* state;   // [rows], zero on entry
+  float* list;          // [rows][kListCap]
+  float* slice_max;     // [rows][slices]
   int32_t slices;
 };
 
@@ -699,12 +702,12 @@ __device__ __forceinline__ T load_agent(const T* p) {
 // quarter of the resolution: hist_kernel 21 us, gather_kernel 20 at 8 x 128K units), and zeros for the next kernels.
 __global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, uint4* clear, int64_t n_clear) {
   __shared__ float s_max[kWaves];
-  const int item = blockIdx.y, tid = threadIdx.x;
+  const int row = blockIdx.y, item = m.a.item_of(row), tid = threadIdx.x;
   const Quads quads(m.a.w + m.a.item_off[item], m.a.item_U[item]);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
   const int64_t step = static_cast<int64_t>(gridDim.x) * gridDim.y * kThreads;
-  for (int64_t i = (static_cast<int64_t>(item) * gridDim.x + blockIdx.x) * kThreads + tid; i < n_clear; i += step)
+  for (int64_t i = (static_cast<int64_t>(row) * gridDim.x + blockIdx.x) * kThreads + tid; i < n_clear; i += step)
     clear[i] = make_uint4(0, 0, 0, 0);
   float mx = 0.f;
   for (int q = q0 + tid; q < q1; q += kThreads) {
@@ -717,7 +720,7 @@ __global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, uint4*
   __syncthreads();
   if (tid < 64) {
     mx = wave_max(tid < kWaves ? s_max[tid] : 0.f);
-    if (tid == 0) m.slice_max[item * m.slices + blockIdx.x] = mx;
+    if (tid == 0) m.slice_max[row * m.slices + blockIdx.x] = mx;
   }
 }
 
@@ -730,14 +733,14 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   __shared__ Hull s_hull;
   __shared__ Search s_search;
   const AllocArgs& a = m.a;
-  const int item = blockIdx.y;
+  const int row = blockIdx.y, item = a.item_of(row);
   const int U = a.item_U[item];
   const int tid = threadIdx.x, lane = tid & 63;
-  SearchState& st = m.state[item];
+  SearchState& st = m.state[row];
   const Quads quads(a.w + a.item_off[item], U);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
-  float mx = lane < m.slices ? m.slice_max[item * m.slices + lane] : 0.f;      // (at most 32 slices)
+  float mx = lane < m.slices ? m.slice_max[row * m.slices + lane] : 0.f;       // (at most 16 slices)
   float wv[4] = {0.f, 0.f, 0.f, 0.f};
   if (q0 + tid < q1) quads.load(q0 + tid, wv);
   const Problem P(a, U, a.item_budget[item]);
@@ -762,7 +765,7 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
     if (q < q1) quads.load(q, wv);
   }
   __syncthreads();
-  int32_t* gh = m.hist + static_cast<int64_t>(item) * Anchored::kBuckets;
+  int32_t* gh = m.hist + static_cast<int64_t>(row) * Anchored::kBuckets;
   for (int i = tid; i < Anchored::kBuckets; i += kThreads)
     if (s_hist[hist_slot(i)] != 0) atomicAdd(gh + i, s_hist[hist_slot(i)]);
   if (!last_to_arrive(&st.arrive[0], m.slices, &s_flag)) return;
@@ -820,8 +823,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   __shared__ int s_n, s_base, s_above[kThr], s_flag, s_red[2 * kWaves];
   __shared__ Search s_search;
   const AllocArgs& a = m.a;
-  const int item = blockIdx.y;
-  SearchState& st = m.state[item];
+  const int row = blockIdx.y, item = a.item_of(row);
+  SearchState& st = m.state[row];
   if (st.s.done) return;                    // written by the previous kernel
   const int n = st.n_open;
   if (n > kListCap && blockIdx.x != 0) return;
@@ -832,7 +835,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   quads.slice(m.slices, &q0, &q1);
   Search S = st.s;
   if (n <= kListCap) {
-    float* gl = m.list + static_cast<int64_t>(item) * kListCap;
+    float* gl = m.list + static_cast<int64_t>(row) * kListCap;
     OpenBuckets open;
 #pragma unroll
     for (int k = 0; k < kThr; ++k) {
@@ -879,7 +882,9 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
       __syncthreads();
       steps_on_list(P, s_list, n, fixed, hull, S, s_red);
     }
-  } else {                                  // more than the list holds: every step on all units, one workgroup
+  } else {
+    // More than the list holds (weights all alike, or in a band of a few ulp): every step on all units, one workgroup.
+    // 8 items of 128K units, one value, 64 steps: 820 us (with fp64 comparisons 1470); a band of 1e-3, 20 steps: 190 (440).
     const Problem P(a, U, a.item_budget[item]);
     while (!S.done && S.it < P.max_iters) {
       const double lam = (S.lo + S.hi) * 0.5;
@@ -920,11 +925,11 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
 __global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
   __shared__ int4 s_cnt[4];
   const AllocArgs& a = m.a;
-  const int item = blockIdx.y;
+  const int row = blockIdx.y, item = a.item_of(row);
   const int U = a.item_U[item];
   const int u0 = blockIdx.x * kBlockUnits, tid = threadIdx.x;
   if (u0 >= U) return;
-  const SearchState& st = m.state[item];
+  const SearchState& st = m.state[row];
   const float* __restrict__ w = a.w + a.item_off[item];
   uint8_t* __restrict__ bits = a.bits + a.item_off[item];
   float v[4];
@@ -1028,41 +1033,25 @@ AllocArgs make_args(const float* w, int n_hull, const int* hull_tiers, const dou
 size_t hist_bytes(int n_items) { return static_cast<size_t>(n_items) * Anchored::kBuckets * sizeof(int32_t); }
 size_t state_bytes(int n_items) { return (static_cast<size_t>(n_items) * sizeof(SearchState) + 255) / 256 * 256; }
 
-}  // namespace
+// Items that the many-workgroup form takes at once: 130 KB of scratch each, 67 MB in all.
+constexpr int kMostTogether = 512;
 
-// Device scratch launch_allocate needs for items of up to max_U units; 0 where one workgroup holds an item.
-size_t allocate_scratch_bytes(int n_items, int max_U) {
-  if (max_U <= kItemUnits) return 0;
-  return hist_bytes(n_items) + state_bytes(n_items) + static_cast<size_t>(n_items) * (kListCap + kMostSlices) * sizeof(float);
+hipError_t launch_short_items(const AllocArgs& a, int n_items, int max_U, hipStream_t st) {
+  const dim3 grid(n_items), block(kThreads);
+#define RDKV_ITEMS(REG_)                                                              \
+  {                                                                                   \
+    const hipError_t e = RDKV_ALLOW_LDS((allocate_item_kernel<REG_>), kItemLds);      \
+    if (e != hipSuccess) return e;                                                    \
+    hipLaunchKernelGGL(allocate_item_kernel<REG_>, grid, block, kItemLds, st, a);     \
+  }
+  if (max_U <= 4 * kThreads) RDKV_ITEMS(4)
+  else if (max_U <= 16 * kThreads) RDKV_ITEMS(16)
+  else RDKV_ITEMS(32)
+#undef RDKV_ITEMS
+  return hipGetLastError();
 }
 
-// Token maps of all items.  blk_counts (with item_blk_off): what the packing stage needs, or null.
-hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
-                           const double* d_item_budget, int n_items, int max_U, int n_hull, const int* hull_tiers,
-                           const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
-                           int32_t* iters_out, const int32_t* d_item_blk_off, int32_t* blk_counts, void* scratch,
-                           hipStream_t st) {
-  if (n_items == 0) return hipSuccess;
-  if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
-  AllocArgs a = make_args(w, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits, lam_out, iters_out);
-  a.item_off = d_item_off; a.item_U = d_item_U; a.item_budget = d_item_budget;
-  a.item_blk_off = d_item_blk_off; a.blk_counts = reinterpret_cast<int4*>(blk_counts);
-  hipError_t e = hipSuccess;
-  const dim3 block(kThreads);
-  if (max_U <= kItemUnits) {
-#define RDKV_ITEMS(REG_)                                                                               \
-  {                                                                                                    \
-    e = RDKV_ALLOW_LDS((allocate_item_kernel<REG_>), kItemLds);                                              \
-    if (e != hipSuccess) return e;                                                                     \
-    hipLaunchKernelGGL(allocate_item_kernel<REG_>, dim3(n_items), block, kItemLds, st, a);             \
-  }
-    if (max_U <= 4 * kThreads) RDKV_ITEMS(4)
-    else if (max_U <= 16 * kThreads) RDKV_ITEMS(16)
-    else RDKV_ITEMS(32)
-#undef RDKV_ITEMS
-    return hipGetLastError();
-  }
-  if (!scratch) return hipErrorInvalidValue;
+hipError_t launch_items_together(const AllocArgs& a, int n_items, int max_U, void* scratch, hipStream_t st) {
   MultiArgs m;
   m.a = a;
   uint8_t* p = static_cast<uint8_t*>(scratch);
@@ -1072,9 +1061,9 @@ hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int3
   m.slice_max = m.list + static_cast<size_t>(n_items) * kListCap;
   m.slices = std::max(1, std::min(kMostSlices, 256 / n_items));
   const int64_t clear = static_cast<int64_t>((hist_bytes(n_items) + state_bytes(n_items)) / 16);
-  const dim3 wide(m.slices, n_items);
+  const dim3 wide(m.slices, n_items), block(kThreads);
   hipLaunchKernelGGL(slice_max_kernel, wide, block, 0, st, m, reinterpret_cast<uint4*>(p), clear);
-  e = RDKV_ALLOW_LDS(hist_kernel, kHistLds);
+  hipError_t e = RDKV_ALLOW_LDS(hist_kernel, kHistLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(hist_kernel, wide, block, kHistLds, st, m);
   e = RDKV_ALLOW_LDS(gather_kernel, kGatherLds);
@@ -1082,6 +1071,46 @@ hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int3
   hipLaunchKernelGGL(gather_kernel, wide, block, kGatherLds, st, m);
   hipLaunchKernelGGL(write_kernel, dim3((max_U + kBlockUnits - 1) / kBlockUnits, n_items), dim3(256), 0, st, m);
   return hipGetLastError();
+}
+
+}  // namespace
+
+// How a batch is searched.  Up to 32K units per item: one launch, a workgroup per item.  Longer ones and up to 512 items:
+// all of them in the many-workgroup form (8 items of 128K units and 8 of 20K: 38 us).  More items: those beyond 32K units in
+// groups of 512, so that the scratch has a bound, and the others in the launch of their own.
+bool allocate_needs_order(int n_items, int max_U) { return max_U > kItemUnits && n_items > kMostTogether; }
+int allocate_short_units() { return kItemUnits; }
+
+// Device scratch launch_allocate needs for items of up to max_U units; 0 where one workgroup holds an item.
+size_t allocate_scratch_bytes(int n_items, int max_U) {
+  if (max_U <= kItemUnits) return 0;
+  const int n = std::min(n_items, kMostTogether);
+  return hist_bytes(n) + state_bytes(n) + static_cast<size_t>(n) * (kListCap + kMostSlices) * sizeof(float);
+}
+
+// Token maps of all items.  d_order (where allocate_needs_order): the items, the n_long of more than allocate_short_units()
+// first, the others with up to max_short units.  blk_counts (with item_blk_off): what the packing stage needs, or null.
+hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
+                           const double* d_item_budget, int n_items, int max_U, const int32_t* d_order, int n_long,
+                           int max_short, int n_hull, const int* hull_tiers,
+                           const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
+                           int32_t* iters_out, const int32_t* d_item_blk_off, int32_t* blk_counts, void* scratch,
+                           hipStream_t st) {
+  if (n_items == 0) return hipSuccess;
+  if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
+  AllocArgs a = make_args(w, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits, lam_out, iters_out);
+  a.item_off = d_item_off; a.item_U = d_item_U; a.item_budget = d_item_budget;
+  a.item_blk_off = d_item_blk_off; a.blk_counts = reinterpret_cast<int4*>(blk_counts);
+  if (max_U <= kItemUnits) return launch_short_items(a, n_items, max_U, st);
+  if (!scratch || (!d_order && n_items > kMostTogether)) return hipErrorInvalidValue;
+  if (!d_order) return launch_items_together(a, n_items, max_U, scratch, st);
+  for (int first = 0; first < n_long; first += kMostTogether) {
+    a.order = d_order + first;
+    const hipError_t e = launch_items_together(a, std::min(kMostTogether, n_long - first), max_U, scratch, st);
+    if (e != hipSuccess) return e;
+  }
+  a.order = d_order + n_long;
+  return n_items > n_long ? launch_short_items(a, n_items - n_long, max_short, st) : hipSuccess;
 }
 
 // Stage 3: the channel maps, from the kept tokens launch_allocate has counted.

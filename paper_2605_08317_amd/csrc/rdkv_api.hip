@@ -35,8 +35,11 @@ hipError_t launch_weights(const rdkv_config& cfg, const int64_t* d_item_row_off,
                           int max_T, const uint16_t* K, const uint16_t* Q_obs, float* w_tok, float* w_ch,
                           float* scratch, hipStream_t st);
 size_t allocate_scratch_bytes(int n_items, int max_U);
+bool allocate_needs_order(int n_items, int max_U);
+int allocate_short_units();
 hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
-                           const double* d_item_budget, int n_items, int max_U, int n_hull, const int* hull_tiers,
+                           const double* d_item_budget, int n_items, int max_U, const int32_t* d_order, int n_long,
+                           int max_short, int n_hull, const int* hull_tiers,
                            const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
                            int32_t* iters_out, const int32_t* d_item_blk_off, int32_t* blk_counts, void* scratch,
                            hipStream_t st);
@@ -734,8 +737,24 @@ rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables&
     blk_counts = tmp.get<int32_t>(static_cast<size_t>(std::max<int64_t>(it.n_blocks, 1)) * 4);
     if (!blk_counts) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   }
+  int32_t* d_order = nullptr;
+  int n_long = 0, max_short = 0;
+  if (allocate_needs_order(n, it.max_T)) {
+    std::vector<int32_t> order(it.T.size());
+    const auto is_long = [&](int32_t i) { return it.T[i] > allocate_short_units(); };
+    for (int32_t i = 0; i < n; ++i)
+      if (is_long(i)) order[n_long++] = i;
+    for (int32_t i = 0, at = n_long; i < n; ++i)
+      if (!is_long(i)) {
+        order[at++] = i;
+        max_short = std::max(max_short, it.T[i]);
+      }
+    d_order = tmp.get<int32_t>(order.size());
+    if (!d_order) return fail(RDKV_ERR_ALLOC, "device allocation failed");
+    RDKV_HIP(upload(d_order, order.data(), order.size() * sizeof(int32_t), st));
+  }
   TimedScope ts(RDKV_TIME_ALLOCATE, st);      // every kernel of the stage
-  RDKV_HIP(launch_allocate(w_tok, tb.tok_off, tb.T, tb.budget, n, it.max_T, static_cast<int>(ht.size()), ht.data(), hr.data(),
+  RDKV_HIP(launch_allocate(w_tok, tb.tok_off, tb.T, tb.budget, n, it.max_T, d_order, n_long, max_short, static_cast<int>(ht.size()), ht.data(), hr.data(),
                            1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_tok, lam, iters, tb.blk_off,
                            blk_counts, scratch, st));
   if (!mixed) return RDKV_OK;
@@ -1447,6 +1466,7 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
                  weights_scratch_floats(n_wblk, it.n_items, it.total_tokens, R, mixed) * sizeof(float),
                  static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t), ni * 22 * sizeof(int64_t), ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),
                  allocate_scratch_bytes(static_cast<int>(it.n_items), it.max_T),
+                 allocate_needs_order(static_cast<int>(it.n_items), it.max_T) ? ni * sizeof(int32_t) : 0,
                  mixed && cfg->k_scale_per_channel ? nc * 2 * sizeof(uint32_t) : 0});
   }
   Tables tb;

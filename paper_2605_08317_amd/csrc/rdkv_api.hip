@@ -283,10 +283,9 @@ hipError_t stage_acquire(size_t bytes, bool held, hipStream_t st, StageRegion* o
   if (e != hipSuccess) return e;
   if (*device < 0 || *device >= kMaxDevices) return hipErrorInvalidDevice;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  e = hipStreamIsCapturing(st, &cap);
+  if (!held) e = hipStreamIsCapturing(st, &cap);          // (the calls that wait have asked: refuse_capture)
   if (e != hipSuccess) return e;
   if (cap == hipStreamCaptureStatusNone) return g_staging[*device].acquire(bytes, held, out);
-  if (held) return hipErrorStreamCaptureUnsupported;      // (the host would wait)
   StageRegion r;
   r.recorded = true;
   r.own = std::malloc(std::max<size_t>(bytes, 1));

@@ -34,8 +34,11 @@
  *    like a stream-ordered caching allocator used on the call's stream (memory
  *    given back may be handed out again only to work enqueued later on that stream,
  *    or after that stream has drained; PyTorch's caching allocator does this).
- *    Without hooks, scratch comes from hipMallocAsync / hipFreeAsync on the call's
- *    stream and what a cache owns from hipMalloc / hipFree.
+ *    Without hooks, scratch comes from a pool of the library's own, whose blocks (at
+ *    most 512 MiB per device; unused ones go back when a cache is freed) are used again
+ *    in stream order.  Scratch that does not fit there, and that of a call under graph
+ *    capture, comes from hipMallocAsync / hipFreeAsync on the call's stream, which may
+ *    wait for the stream.  What a cache owns comes from hipMalloc / hipFree.
  *  - Shapes: head_dim must be 128, hq a multiple of hkv with hq/hkv in
  *    {1,2,4,8}, quantization group size 32 or 128.
  *  - Ragged batch layout: K, V (and per-token arrays) hold, per sequence s in

@@ -92,10 +92,87 @@ struct KernelTiming {
 };
 KernelTiming g_timing;
 
+constexpr int kMaxDevices = 64;
+
+// Scratch of calls without allocator hooks: blocks that outlive the call, one pool per device.  (hipFreeAsync waits for the
+// stream when the block was handed out again before its previous hipFreeAsync had come up on it: the second of two staged
+// calls behind a quarter of a second of queued work took 242 ms to return, now 0.02.)
+// A block given back carries an event of its last stream; it goes out again to that stream, or to another one once the event
+// has passed.  At most kBytes per device; what does not fit comes from the runtime's pool and may wait.  Blocks that were not
+// used for a while go back when a cache is freed, which waits for the device anyway.
+class ScratchPool {
+  struct Block { void* p; size_t bytes; hipEvent_t ev; hipStream_t st; bool idle; uint64_t used; };
+  std::mutex mu_;
+  std::vector<Block> blocks_;
+  size_t total_ = 0;
+  uint64_t calls_ = 0;
+  static constexpr size_t kBytes = static_cast<size_t>(512) << 20;
+  static constexpr uint64_t kKeepCalls = 64;
+  // sizes in quarter steps of a power of two, so that a program's largest call leaves few blocks behind
+  static size_t rounded(size_t bytes) {
+    size_t step = static_cast<size_t>(64) << 10;
+    while (8 * step <= bytes) step *= 2;
+    return (bytes + step - 1) / step * step;
+  }
+
+ public:
+  void* get(size_t bytes, hipStream_t st) {
+    std::lock_guard<std::mutex> lk(mu_);
+    ++calls_;
+    Block* best = nullptr;
+    for (Block& b : blocks_)
+      if (b.idle && b.bytes >= bytes && (!best || b.bytes < best->bytes) && (b.st == st || hipEventQuery(b.ev) == hipSuccess)) best = &b;
+    if (best) {
+      if (hipEventQuery(best->ev) != hipSuccess && hipStreamWaitEvent(st, best->ev, 0) != hipSuccess) return nullptr;
+      best->idle = false;
+      best->used = calls_;
+      return best->p;
+    }
+    Block b{nullptr, rounded(bytes), nullptr, st, false, calls_};
+    if (total_ + b.bytes > kBytes) return nullptr;
+    if (hipEventCreateWithFlags(&b.ev, hipEventDisableTiming) != hipSuccess) return nullptr;
+    if (hipMalloc(&b.p, b.bytes) != hipSuccess) {
+      (void)hipEventDestroy(b.ev);
+      return nullptr;
+    }
+    blocks_.push_back(b);
+    total_ += b.bytes;
+    return b.p;
+  }
+  bool put(void* p, hipStream_t st) {      // false: not of this pool
+    std::lock_guard<std::mutex> lk(mu_);
+    for (Block& b : blocks_)
+      if (b.p == p) {
+        if (hipEventRecord(b.ev, st) != hipSuccess) (void)hipStreamSynchronize(st);
+        b.st = st;
+        b.idle = true;
+        return true;
+      }
+    return false;
+  }
+  void give_back() {
+    std::lock_guard<std::mutex> lk(mu_);
+    for (size_t k = 0; k < blocks_.size();) {
+      Block& b = blocks_[k];
+      if (!b.idle || calls_ - b.used < kKeepCalls || hipEventQuery(b.ev) != hipSuccess) { ++k; continue; }
+      (void)hipFree(b.p);
+      (void)hipEventDestroy(b.ev);
+      total_ -= b.bytes;
+      b = blocks_.back();
+      blocks_.pop_back();
+    }
+  }
+};
+ScratchPool g_scratch_pool[kMaxDevices];
+ScratchPool* scratch_pool() {
+  int dev = -1;
+  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices ? &g_scratch_pool[dev] : nullptr;
+}
+
 // Device memory of the library.  What a cache owns lives until rdkv_cache_free and comes from alloc() / hipMalloc.
 // Scratch of a single call is released when the call returns, while its kernels may still be queued: the release is
 // stream-ordered (the caller's hooks must behave like a stream-ordered caching allocator on the call's stream; without
-// hooks hipMallocAsync / hipFreeAsync on that stream).
+// hooks the pool above, or hipMallocAsync / hipFreeAsync on that stream when it is under capture).
 struct Allocator {
   rdkv_alloc_fn alloc = nullptr;
   rdkv_free_fn free_ = nullptr;
@@ -113,12 +190,18 @@ struct Allocator {
   void* get_scratch(size_t bytes, hipStream_t st) const {
     if (bytes == 0) bytes = 16;
     if (alloc) return alloc(bytes, user);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+      if (ScratchPool* pool = scratch_pool())
+        if (void* p = pool->get(bytes, st)) return p;
     void* p = nullptr;
     return hipMallocAsync(&p, bytes, st) == hipSuccess ? p : nullptr;
   }
   void put_scratch(void* p, hipStream_t st) const {
     if (!p) return;
-    if (free_) free_(p, user); else (void)hipFreeAsync(p, st);
+    if (free_) { free_(p, user); return; }
+    ScratchPool* pool = scratch_pool();
+    if (!pool || !pool->put(p, st)) (void)hipFreeAsync(p, st);
   }
 };
 
@@ -160,7 +243,6 @@ struct Temp {
 // kernels read and write directly (launch_copy): no copy of the runtime, no event, no wait for the stream.  A region starts
 // with completion words that the kernel sets to the region's number when it is done with it; the ring's bytes are reused
 // once it has.
-constexpr int kMaxDevices = 64;
 constexpr size_t kStageHead = kStageWords * sizeof(uint32_t);
 
 struct StageRegion {
@@ -2068,6 +2150,8 @@ rdkv_status rdkv_cache_export(const rdkv_cache* c, int what, void* dst, size_t b
 void rdkv_cache_free(rdkv_cache* c) {
   if (!c) return;
   free_cache_buffers(c);
+  if (!c->alloc)
+    if (ScratchPool* pool = scratch_pool()) pool->give_back();
   delete c;
 }
 

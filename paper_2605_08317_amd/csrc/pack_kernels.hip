@@ -173,10 +173,11 @@ struct TileOf {
 };
 
 // The quantizer of one group: scale, offset and codes.  The correctly rounded quotient d / s without the division
-// sequence: q0 = d * y with y the hardware reciprocal of s (within one unit in the last place), remainder r = d - q0 s
-// exact in one fused multiply-add, q = q0 + r y.  On the CPU the result equals the IEEE quotient for every fp16 s, also with
-// y one unit off, over 457 million (d, s) around half-integers, dense ranges and differences of bf16 numbers.  A group
-// with a scale or offset that is not finite takes the division.
+// sequence, by Markstein's scheme (IBM J. Res. Dev. 34, 1990): q0 = d * y with y the hardware reciprocal of s, remainder
+// r = d - q0 s exact in one fused multiply-add, q = q0 + r y.  The reciprocal is within one unit in the last place, not
+// correctly rounded as the theorem asks; tests/test_quotient.py finds the IEEE quotient all the same for every fp16 s and
+// all three y, at 128 million numerators around the half-integers and of differences of bf16 numbers.  A group with a scale
+// or offset that is not finite takes the division.
 struct Quant {
   float m, s, y;
   _Float16 sh, mh;

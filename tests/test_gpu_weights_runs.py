@@ -52,5 +52,7 @@ def test_weights_over_row_and_tile_edges(seq_lens, hq, hkv, s_obs, causal, spike
         got = w_tok[off:off + hkv * T].reshape(hkv, T)
         off += hkv * T
         err = np.abs(got - ref) / (np.abs(ref) + 1e-6 * ref.max())
-        assert err.max() <= WEIGHT_RTOL * (5 if spike else 1), f"sequence {s}: {err.max():.2e}"
+        # (spiked logits of 145 powers of two: the log-sum-exp is rounded to 1.5e-5 / 2 there, 5e-6 of a weight; over these
+        # and other seeds and spikes of 20 to 120 at most 2.4e-6 came out, 1.3e-6 with a running maximum in every tile)
+        assert err.max() <= WEIGHT_RTOL, f"sequence {s}: {err.max():.2e}"
         np.testing.assert_allclose(w_ch[s * hkv:(s + 1) * hkv], O.channel_weights(Ks, _np(Q[s])), rtol=1e-5)

@@ -65,7 +65,7 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 // 16 bytes per lane from global memory straight into LDS: lane i's bytes, base + offset, land at lds_base + 16 i (base
 // and lds_base are uniform).  The compiler does not see the copy, so the reader waits for it by hand (tile_barrier).
 __device__ __forceinline__ void copy_to_lds(const void* base, uint32_t offset, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_base) : "memory");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 // Barrier of the workgroup after this wavefront's vector memory operations but the last PENDING have completed.
 template <int PENDING>

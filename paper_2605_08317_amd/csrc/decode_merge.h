@@ -40,10 +40,6 @@ __device__ __forceinline__ void store_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ float load_agent(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Every thread calls this after its last store_agent of the partial and before the workgroup barrier that precedes
 // arrive_and_merge(): agent-scope stores are written through to memory, so once the wave's store counter has drained
 // they are visible to every XCD.  (A release fence would add a write-back of the whole L2, which has nothing of

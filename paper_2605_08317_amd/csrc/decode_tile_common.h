@@ -10,6 +10,7 @@
 #pragma once
 #include "decode_merge.h"
 #include "rdkv_internal.h"
+#include "wave_ops.h"
 
 namespace rdkv {
 namespace tile {
@@ -62,22 +63,6 @@ union Pack4 {
   uint32_t u[2];
 };
 
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __builtin_bit_cast(float, dpp_u32<CTRL>(__builtin_bit_cast(uint32_t, v)));
-}
-// Row and half exchanges (the wait states they need after a write to their operands stand in front of them): rows 1 and 3
-// of a swapped with rows 0 and 2 of b; the upper half of a with the lower half of b.
-__device__ __forceinline__ void swap_rows(float& a, float& b) {
-  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-__device__ __forceinline__ void swap_halves(float& a, float& b) {
-  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
 __device__ __forceinline__ float sum_xor16(float v) {
   float o = v;
   swap_rows(v, o);
@@ -344,12 +329,6 @@ __device__ __forceinline__ void pv_tile(const uint4 (&vraw)[TIER], const uint4& 
 struct ChunkOut {
   int item, slot, slot0, nslots;   // the chunk's item and partial slot; the item's first slot and slot count
 };
-
-// Sum of the wavefront's two halves: of a in lanes 0..31, of b in lanes 32..63.
-__device__ __forceinline__ float halves_sum(float a, float b) {
-  swap_halves(a, b);
-  return a + b;
-}
 
 // Floats of LDS the end of a chunk needs behind s_ml: the wavefronts' sums, later the merge of the item.
 __host__ __device__ constexpr int finish_lds_floats(int waves, int g) {

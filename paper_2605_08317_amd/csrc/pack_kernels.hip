@@ -26,10 +26,11 @@ __device__ __forceinline__ int tier_slot(uint8_t b) {   // 16,8,4,2 -> 0..3 ; el
   return b == 16 ? 0 : b == 8 ? 1 : b == 4 ? 2 : b == 2 ? 3 : -1;
 }
 
-// counts of each stored tier inside every block of 1024 tokens of every item
 // four bytes of a bit map at any address
 struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 
+// Counts of each stored tier inside every block of 1024 tokens of every item; a first count of -1: the block holds a value
+// that is no bit-width.
 __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restrict__ bits,
                                                          const int64_t* __restrict__ item_tok_off,
                                                          const int32_t* __restrict__ item_T,
@@ -140,7 +141,6 @@ struct PackArgs {
   const int64_t* item_row_off; // [items]: first row of the item's [T][d] block in K / V
   uint8_t* arena;
   const ItemK* items_k;        // [items] (mixed mode)
-  const uint8_t* bits_ch;      // [items][128] (mixed mode)
   uint32_t* k_range;           // [items][128][2]: ordered-integer images of a channel's minimum and maximum over all
                                // retained tokens (one scale per channel, App. B), or null (groups of 32 tokens)
   int32_t row_wide;            // token rows: one scale and offset per row (App. B's per-token format), repeated in
@@ -211,12 +211,6 @@ struct Quant {
   }
 };
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kRowMirror = 0x140;
 
 __device__ __forceinline__ void unpack8(const uint4& v, float (&x)[8]) {
@@ -236,15 +230,15 @@ __device__ __forceinline__ void quantize_row(const uint4& raw, int row_wide, Qua
   unpack8(raw, x);
   float mn = fminf(fminf(fminf(x[0], x[1]), fminf(x[2], x[3])), fminf(fminf(x[4], x[5]), fminf(x[6], x[7])));
   float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-  mn = fminf(mn, dpp_f<kQuadXor1>(mn));
-  mx = fmaxf(mx, dpp_f<kQuadXor1>(mx));
-  mn = fminf(mn, dpp_f<kQuadXor2>(mn));
-  mx = fmaxf(mx, dpp_f<kQuadXor2>(mx));
+  mn = fminf(mn, dpp_f32<kQuadXor1>(mn));
+  mx = fmaxf(mx, dpp_f32<kQuadXor1>(mx));
+  mn = fminf(mn, dpp_f32<kQuadXor2>(mn));
+  mx = fmaxf(mx, dpp_f32<kQuadXor2>(mx));
   if (row_wide) {
-    mn = fminf(mn, dpp_f<kHalfMirror>(mn));
-    mx = fmaxf(mx, dpp_f<kHalfMirror>(mx));
-    mn = fminf(mn, dpp_f<kRowMirror>(mn));
-    mx = fmaxf(mx, dpp_f<kRowMirror>(mx));
+    mn = fminf(mn, dpp_f32<kHalfMirror>(mn));
+    mx = fmaxf(mx, dpp_f32<kHalfMirror>(mx));
+    mn = fminf(mn, dpp_f32<kRowMirror>(mn));
+    mx = fmaxf(mx, dpp_f32<kRowMirror>(mx));
   }
   g.set<BITS>(mn, mx);
   if (__all(g.finite)) {
@@ -278,16 +272,16 @@ __device__ __forceinline__ void store_k_words(const float (&c)[8], uint8_t* tile
     const int sh = 8 * (p & 1);
     w.x <<= sh;
     w.y <<= sh;
-    w.x |= dpp_u<kQuadXor1>(w.x);
-    w.y |= dpp_u<kQuadXor1>(w.y);
+    w.x |= dpp_u32<kQuadXor1>(w.x);
+    w.y |= dpp_u32<kQuadXor1>(w.y);
   } else if constexpr (BITS == 2) {        // fields 2 p, 2 p + 1 of the group's only word pair
     const int sh = 4 * p;
     w.x <<= sh;
     w.y <<= sh;
-    w.x |= dpp_u<kQuadXor1>(w.x);
-    w.y |= dpp_u<kQuadXor1>(w.y);
-    w.x |= dpp_u<kQuadXor2>(w.x);
-    w.y |= dpp_u<kQuadXor2>(w.y);
+    w.x |= dpp_u32<kQuadXor1>(w.x);
+    w.y |= dpp_u32<kQuadXor1>(w.y);
+    w.x |= dpp_u32<kQuadXor2>(w.x);
+    w.y |= dpp_u32<kQuadXor2>(w.y);
   }
   const int W = BITS * grp + (BITS == 8 ? 2 * p : BITS == 4 ? (p & 2) : 0);
   if (BITS == 8 || (BITS == 4 && (p & 1) == 0) || (BITS == 2 && p == 0))
@@ -470,9 +464,9 @@ __global__ __launch_bounds__(256) void k_channel_range_kernel(PackArgs a) {
 // what lane ^ J holds (J = 1, 2, 4, 8, inside a row of 16)
 template <int J>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
-  if constexpr (J == 1) return dpp_u<kQuadXor1>(v);
-  else if constexpr (J == 2) return dpp_u<kQuadXor2>(v);
-  else if constexpr (J == 8) return dpp_u<0x128>(v);                    // row_ror:8
+  if constexpr (J == 1) return dpp_u32<kQuadXor1>(v);
+  else if constexpr (J == 2) return dpp_u32<kQuadXor2>(v);
+  else if constexpr (J == 8) return dpp_u32<0x128>(v);                    // row_ror:8
   else {
     const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x104, 0xF, 0x5, false);   // row_shl:4 into banks 0, 2
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(lo, static_cast<int>(v), 0x114, 0xF, 0xA, false));   // row_shr:4
@@ -694,7 +688,6 @@ hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, c
                              const int32_t* item_blk_off, int32_t* blk_counts, int n_items, int max_T, hipStream_t st) {
   const int max_blk = (max_T + kPartBlock - 1) / kPartBlock;
   if (n_items == 0 || max_blk == 0) return hipSuccess;
-  // `invalid` (zero on entry) is set when the map holds a value that is no bit-width of the method
   hipLaunchKernelGGL(tier_count_kernel, dim3(max_blk, n_items), dim3(256), 0, st, bits, item_tok_off, item_T,
                      item_blk_off, reinterpret_cast<int4*>(blk_counts));
   return hipGetLastError();
@@ -714,10 +707,9 @@ hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off,
 hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx,
                              const int64_t* idx_base, const int32_t* counts, const int64_t* seg_off,
                              const int64_t* item_row_off, uint8_t* arena, int n_items,
-                             int max_tiles, const ItemK* items_k, const uint8_t* bits_ch,
-                             uint32_t* k_range, int row_wide, hipStream_t st) {
+                             int max_tiles, const ItemK* items_k, uint32_t* k_range, int row_wide, hipStream_t st) {
   if (n_items == 0 || max_tiles == 0) return hipSuccess;
-  const PackArgs a{K, V, tier_idx, idx_base, counts, seg_off, item_row_off, arena, items_k, bits_ch, k_range, row_wide};
+  const PackArgs a{K, V, tier_idx, idx_base, counts, seg_off, item_row_off, arena, items_k, k_range, row_wide};
   const dim3 grid(max_tiles, n_items), block(256);
   if (items_k == nullptr) {
     hipLaunchKernelGGL(pack_tile_kernel<false>, grid, block, 0, st, a);

@@ -25,8 +25,7 @@ hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off,
 hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx,
                              const int64_t* idx_base, const int32_t* counts, const int64_t* seg_off,
                              const int64_t* item_row_off, uint8_t* arena, int n_items,
-                             int max_tiles, const ItemK* items_k, const uint8_t* bits_ch,
-                             uint32_t* k_range, int row_wide, hipStream_t st);
+                             int max_tiles, const ItemK* items_k, uint32_t* k_range, int row_wide, hipStream_t st);
 int partition_block();
 int weights_key_tile();
 size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_tokens, int R, bool want_ch);
@@ -1320,7 +1319,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
                                    static_cast<int>(n), it.max_T, st));
       PACK_HIP(launch_quant_pack(static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), c->d_tier_idx,
                                  d_idx_base, d_counts, d_seg_off, d_tok_off, c->d_arena, static_cast<int>(n),
-                                 max_tiles, mixed ? c->d_items_k : nullptr, mixed ? c->d_bits_ch : nullptr, d_krange,
+                                 max_tiles, mixed ? c->d_items_k : nullptr, d_krange,
                                  c->group_size == kHeadDim ? 1 : 0, st));
     }
   }

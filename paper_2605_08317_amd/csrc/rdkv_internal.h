@@ -167,8 +167,6 @@ struct TimedScope {
   ~TimedScope() { timing_end(kind, st); }
 };
 
-struct PackItemDesc;   // compress_kernels
-
 }  // namespace rdkv
 
 // The opaque handle of the C ABI.

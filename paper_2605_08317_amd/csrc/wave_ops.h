@@ -1,11 +1,33 @@
-// Sums and maxima over the lanes of a wavefront on the ALUs: row shifts inside rows of 16 lanes, then across the rows.  (A
-// shuffle per step goes through LDS, 100 cycles each where nothing covers them.)
+// Moves between the lanes of a wavefront, sums and maxima over them, on the ALUs: row shifts inside rows of 16 lanes, then
+// across the rows.  (A shuffle per step goes through LDS, 100 cycles each where nothing covers them.)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace rdkv {
 
+// v of the lane CTRL names; every lane has one
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __builtin_bit_cast(float, dpp_u32<CTRL>(__builtin_bit_cast(uint32_t, v)));
+}
+// Row and half exchanges in place (the wait states they need after a write to their operands stand in front of them): rows 1
+// and 3 of a swapped with rows 0 and 2 of b; the upper half of a with the lower half of b.
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+// Sum of the wavefront's two halves: of a in lanes 0..31, of b in lanes 32..63.
+__device__ __forceinline__ float halves_sum(float a, float b) {
+  const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(v[0]) + __uint_as_float(v[1]);
+}
 // v of the lane CTRL names, 0 where there is none (rows outside the row mask ROWS included)
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t lanes_below(uint32_t v) {

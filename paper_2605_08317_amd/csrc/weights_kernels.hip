@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "rdkv_internal.h"
+#include "wave_ops.h"
 
 namespace rdkv {
 
@@ -91,12 +92,6 @@ __device__ __forceinline__ int item_slots(const WeightArgs& a, int item, int* fi
   const int w0 = owner_of(t0, a.workgroups, a.n_tiles), w1 = owner_of(t1 - 1, a.workgroups, a.n_tiles);
   *first = w0 + item;
   return w1 - w0 + 1;
-}
-
-// v of this lane and of the lane 32 away, added (a swap returns both halves, whichever lane holds which)
-__device__ __forceinline__ float halves_sum(float v) {
-  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
 // One workgroup = one run of key tiles against all window rows of their items.
@@ -283,7 +278,7 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
       if constexpr (PASS == 1) {
         l[kRt] += sum;
       } else if constexpr (kRt == NRT - 1) {
-        const float c = halves_sum((part[0] + part[1]) + (part[2] + part[3]));
+        const float own = (part[0] + part[1]) + (part[2] + part[3]), c = halves_sum(own, own);
         if (half == 0) s_sum[t % kSumTiles][rgi][step * 32 + l32] = c;
       }
       if constexpr (kMultiply) acc = nxt;
@@ -415,7 +410,7 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
           }
         }
         if constexpr (PASS == 2) {
-          c = halves_sum(c);
+          c = halves_sum(c, c);
           if (half == 0) s_sum[t % kSumTiles][rgi][step * 32 + l32] = c;
         }
       }
@@ -432,7 +427,7 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
 #pragma unroll
       for (int rt = 0; rt < NRT; ++rt) {
         const float mm = fmaxf(m[rt], __shfl_xor(m[rt], 32));
-        const float ll = halves_sum(l[rt] * fast_exp2(m[rt] - mm));
+        const float own = l[rt] * fast_exp2(m[rt] - mm), ll = halves_sum(own, own);
         if (half == 0) {
           float* p = s_ml + ((ks * RGW + rgi) * 32 * NRT + rt * 32 + l32) * 2;
           p[0] = mm;

@@ -130,7 +130,7 @@ class ScratchPool {
     Block b{nullptr, rounded(bytes), nullptr, st, false, calls_};
     if (total_ + b.bytes > kBytes) return nullptr;
     if (hipEventCreateWithFlags(&b.ev, hipEventDisableTiming) != hipSuccess) return nullptr;
-    if (hipMalloc(&b.p, b.bytes) != hipSuccess) {
+    if (hipMallocAsync(&b.p, b.bytes, st) != hipSuccess) {      // (hipMalloc would end another thread's graph capture)
       (void)hipEventDestroy(b.ev);
       return nullptr;
     }
@@ -154,7 +154,7 @@ class ScratchPool {
     for (size_t k = 0; k < blocks_.size();) {
       Block& b = blocks_[k];
       if (!b.idle || calls_ - b.used < kKeepCalls || hipEventQuery(b.ev) != hipSuccess) { ++k; continue; }
-      (void)hipFree(b.p);
+      (void)hipFreeAsync(b.p, nullptr);
       (void)hipEventDestroy(b.ev);
       total_ -= b.bytes;
       b = blocks_.back();

@@ -1,5 +1,8 @@
 """The staged calls recorded in a HIP graph: their host tables go with the graph, so that a replay neither depends on the
 staging memory the call used at capture nor touches it, and the calls that wait for the stream record nothing."""
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -98,3 +101,41 @@ def test_calls_that_wait_are_refused_under_capture():
     for call in calls:                                   # and outside of one they all still run
         call()
     torch.cuda.synchronize()
+
+
+def test_another_thread_calls_while_this_one_captures():
+    """A staged call without allocator hooks, whose scratch is larger than what the library holds so far, on a stream and a
+    thread of its own beside a capture: neither disturbs the other."""
+    b, hkv = B(), 2
+    K, Q = _batch(1, hkv, 300, 32, 1)
+    cfg = b.Config([300], hkv, hkv, budget_bits=[2.0], s_obs=32)
+    cache = b.rdkv_compress(cfg, K, K, Q)
+    q = Q[:, :, 0].contiguous()
+    expected, _ = b.rdkv_decode_attn(cache, q)
+    T = 40000
+    big_K, big_Q = _batch(4, 8, T, 32, 2)
+    big = b.Config([T] * 4, 8, 8, budget_bits=[1.0] * 4, s_obs=32)
+    w = torch.empty(4 * 8 * T, dtype=torch.float32, device="cuda")
+    out, lse = torch.empty_like(expected), torch.empty_like(expected[..., 0])
+    side, status = torch.cuda.Stream(), []
+
+    def call():
+        status.append(b.lib.rdkv_weights(big.ref(), big_K.data_ptr(), big_Q.data_ptr(), w.data_ptr(), None,
+                                         ctypes.c_void_p(side.cuda_stream)))
+
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b.rdkv_decode_attn(cache, q, out, lse)
+        thread = threading.Thread(target=call)
+        thread.start()
+        thread.join()
+    torch.cuda.synchronize()
+    assert status == [0]
+    assert torch.equal(w, b.rdkv_weights(big, big_K, big_Q)[0])
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, expected)
+    cache.free()

@@ -177,7 +177,7 @@ __device__ __forceinline__ void process_tiles(const uint8_t* __restrict__ kd, co
     if constexpr (kShare) load_v(r, tile);   // the K codes are used up: their registers take this tile's V codes
     else if (more) load_k(r, next);          // K registers are free again
 
-    to_head_lanes<HS>(xt, j, x);
+    to_head_lanes<HS, HS == 2>(xt, j, x);
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
     softmax_tile<HS>(x, run, p, lk);

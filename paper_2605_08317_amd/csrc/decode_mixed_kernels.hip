@@ -411,7 +411,7 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
       for (int hs = 0; hs < HS; ++hs)
 #pragma unroll
         for (int i = 0; i < 4; ++i) xt[hs][i] = __builtin_fmaf(a16[hs][i], kKUnit, aqh[hs][i] + aql[hs][i]);
-      to_head_lanes<HS>(xt, j, x);
+      to_head_lanes<HS, false>(xt, j, x);
 #pragma unroll
       for (int hs = 0; hs < HS; ++hs)
 #pragma unroll

@@ -119,7 +119,7 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
     for (int hs = 0; hs < HS; ++hs)
 #pragma unroll
       for (int i = 0; i < 4; ++i) xt[hs][i] = a16[hs][i] * kKUnit;
-    to_head_lanes<HS>(xt, j, x);
+    to_head_lanes<HS, HS == 2>(xt, j, x);
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
     softmax_tile<HS>(x, run, p);

@@ -107,28 +107,54 @@ __device__ __forceinline__ uint4 load_query(const uint16_t* __restrict__ q, int 
 
 // The K products leave lane = token with the four heads of a set in its registers; the softmax and P V want lane (block,
 // head) with the block's four tokens: a 4x4 transposition inside each quad of lanes, in two steps that exchange registers
-// with lane ^ 1 and lane ^ 2.  Moves only, so that a head whose logits are not finite stays by itself (products with
-// unit vectors, which take the same time -- a 70B-shaped batch 44.1 and 44.2 us -- spread its NaN over the set: 0 x NaN).
-template <int HS>
+// with lane ^ 1 and lane ^ 2.  Moves only, so that a head whose logits are not finite stays by itself: products with unit
+// vectors, which turn the block as well, spread its NaN over the set (0 x NaN).
+// Two forms.  Written plainly it becomes eight moves and eight selections, which the compiler spreads over the code around.
+// A selection that takes one side from another lane is one instruction: half as many, in one piece (FEW).  That is better
+// where the vector issue is full, with two head sets over token rows (16 ragged sequences with 8 query heads 44.1 us with
+// the products, 44.3 plainly, 44.1 so), and worse elsewhere (one channel-wise 64K sequence, 4 query heads 16.9, 16.2, 17.1; a
+// batch of 16, 8 query heads, 32K tokens 97.1, 97.5, 99.0).
+// (A selection of that kind reads its mask, the lanes that keep their own register, from vcc.  Two wait states stand between
+// a write to a register and its use by another lane.)
+#define RDKV_TURN_MASK(M_) "s_mov_b32 vcc_lo, " #M_ "\n\ts_mov_b32 vcc_hi, " #M_ "\n\t"
+#define RDKV_TURN_1(D_, OTHER_, OWN_) "v_cndmask_b32_dpp " D_ ", " OTHER_ ", " OWN_ ", vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+#define RDKV_TURN_2(D_, OTHER_, OWN_) "v_cndmask_b32_dpp " D_ ", " OTHER_ ", " OWN_ ", vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+template <int HS, bool FEW>
 __device__ __forceinline__ void to_head_lanes(const float (&xt)[HS][4], int j, float (&x)[HS][4]) {
   const bool odd = (j & 1) != 0, high = (j & 2) != 0;
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) {
     float t[4];
+    if constexpr (FEW) {
 #pragma unroll
-    for (int k = 0; k < 4; k += 2) {
-      const float from1 = dpp_f32<0xB1>(xt[hs][k + 1]), from0 = dpp_f32<0xB1>(xt[hs][k]);   // quad_perm [1, 0, 3, 2]
-      t[k] = odd ? from1 : xt[hs][k];
-      t[k + 1] = odd ? xt[hs][k + 1] : from0;
-    }
+      for (int i = 0; i < 4; ++i) x[hs][i] = xt[hs][i];
+      asm("s_nop 1\n\t"
+          RDKV_TURN_MASK(0x55555555) RDKV_TURN_1("%4", "%1", "%0") RDKV_TURN_1("%6", "%3", "%2")
+          RDKV_TURN_MASK(0xaaaaaaaa) RDKV_TURN_1("%5", "%0", "%1") RDKV_TURN_1("%7", "%2", "%3")
+          RDKV_TURN_MASK(0x33333333) RDKV_TURN_2("%0", "%6", "%4") RDKV_TURN_2("%1", "%7", "%5")
+          RDKV_TURN_MASK(0xcccccccc) RDKV_TURN_2("%2", "%4", "%6") RDKV_TURN_2("%3", "%5", "%7")
+          : "+v"(x[hs][0]), "+v"(x[hs][1]), "+v"(x[hs][2]), "+v"(x[hs][3]), "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
+          :
+          : "vcc");
+    } else {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const float from2 = dpp_f32<0x4E>(t[k + 2]), from0 = dpp_f32<0x4E>(t[k]);             // quad_perm [2, 3, 0, 1]
-      x[hs][k] = high ? from2 : t[k];
-      x[hs][k + 2] = high ? t[k + 2] : from0;
+      for (int k = 0; k < 4; k += 2) {
+        const float from1 = dpp_f32<0xB1>(xt[hs][k + 1]), from0 = dpp_f32<0xB1>(xt[hs][k]);   // quad_perm [1, 0, 3, 2]
+        t[k] = odd ? from1 : xt[hs][k];
+        t[k + 1] = odd ? xt[hs][k + 1] : from0;
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const float from2 = dpp_f32<0x4E>(t[k + 2]), from0 = dpp_f32<0x4E>(t[k]);             // quad_perm [2, 3, 0, 1]
+        x[hs][k] = high ? from2 : t[k];
+        x[hs][k + 2] = high ? t[k + 2] : from0;
+      }
     }
   }
 }
+#undef RDKV_TURN_2
+#undef RDKV_TURN_1
+#undef RDKV_TURN_MASK
 
 // Field position of step s inside a 16-bit half, which right-shifted copy of the word it is read from, and the bit
 // offset that remains after that shift (the code then reads as code * 2^fb * 2^-24).
@@ -475,7 +501,7 @@ __device__ __forceinline__ void process_tail_tiles(const uint8_t* __restrict__ k
     for (int hs = 0; hs < HS; ++hs)
 #pragma unroll
       for (int i = 0; i < 4; ++i) xt[hs][i] = a16[hs][i] * kKUnit;
-    to_head_lanes<HS>(xt, j, x);
+    to_head_lanes<HS, HS == 2>(xt, j, x);
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
     softmax_tile<HS>(x, run, p);

@@ -1031,7 +1031,10 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   //   8 items (52000)                                    512: 25.1   768: 22.7   1024: 18.9  2048: 17.4*  old: 18.9
   //   8 items (78000)                                    1024: 25.6  1536: 22.6  2048: 25.0  3072: 21.6*  old: 24.3
   // Token-wise launches above that size are cut by bytes (below) unless they are a few long items of narrow rows: with
-  // many items or 8-bit rows the bytes' balance matters more (8 ragged sequences 16.4 us by bytes, 17.6 so).
+  // many items or 8-bit rows the bytes' balance matters more (8 ragged sequences 16.4 us by bytes, 17.6 so).  Of 120 other
+  // launches (8 to 32 items, up to half 8-bit rows, 42 to 151 MB) the line picks the better way, or one within 5 %, in 89; it
+  // is off the most just above the floor with 8 query heads (42 MB, 16 items, 30 % 8-bit rows: 25.4 us by bytes, 16.2 so) and
+  // just below the upper limit with 4 (96 MB, 16 items, 10 %: 23.2 us by bytes, 27.5 so).
   const int64_t floor_bytes = static_cast<int64_t>(wide ? 96 : 48) << 10;
   int64_t small_rows = 0;
   // (eight-wavefront workgroups of the channel-wise kernel: one per compute unit, so that a few more than 256 double the

@@ -13,11 +13,12 @@
 // fetched once per run and two tiles of keys are in flight during the arithmetic on a third.  The products of a step are
 // issued between the exponentials of the step before: a logit costs the plain ALUs a multiply-add, an exponential (8
 // cycles per wavefront) and an addition beside the matrix core.  Measured: 8 heads x 128K keys x 256 rows 109 + 102 us
-// -> 85 + 92 us for the two passes, 128 heads x 20K keys x 256 rows 256 + 239 -> 190 + 210 us (keys stationary and rows
-// staged through LDS before).  What bounds them: three resources near their limits at once.  The products alone are
-// 69 GFLOP per pass of the first shape, 55 us at the rate a large library product reaches on this card (its clock drops
-// under matrix work on random data); without them the pass takes 51 us (HBM, 5.3 TB/s), without exponentials 71 us,
-// without fetching keys 73 us; tile shapes, occupancy (2 or 3 wavefronts per SIMD) and deeper prefetch change nothing.
+// -> 76 + 78 us for the two passes (kernel trace; 85 + 92 among other work), 128 heads x 20K keys x 256 rows 256 + 239 ->
+// 179 + 184 us (keys stationary and rows staged through LDS before).  What bounds them: matrix core and plain ALUs together.
+// The products alone are 69 GFLOP per pass of the first shape, 58 us at the rate a large library product reaches on this card
+// (1.18 PFLOP/s; its clock drops under matrix work on random data).  By the counters two wavefronts per SIMD fill two thirds
+// of the vector issue, keep the matrix core busy 53 to 55 % of their time and wait 20 to 24 % of it; keys arrive at 3.4 TB/s.
+// Tile shapes, occupancy (2 or 3 wavefronts per SIMD) and deeper prefetch change nothing.
 #include <algorithm>
 #include <type_traits>
 

@@ -107,8 +107,8 @@ typedef struct rdkv_config {
   float eps_k[RDKV_MAX_TIERS];     /* distortion table eps_K(b) */
   float rel_tol;            /* bisection tolerance delta (App. B: 1e-2) */
   int32_t max_iters;        /* bisection steps I (App. B: 64) */
-  rdkv_alloc_fn alloc;      /* NULL: hipMalloc */
-  rdkv_free_fn free_;       /* NULL: hipFree */
+  rdkv_alloc_fn alloc;      /* NULL: the library's own (general rules above) */
+  rdkv_free_fn free_;       /* NULL with alloc */
   void* alloc_user;
 } rdkv_config;
 
@@ -237,8 +237,8 @@ size_t rdkv_cache_max_table_bytes(const rdkv_config* cfg);
  *   out  DEVICE fp32 [batch][hq][d]
  *   lse  DEVICE fp32 [batch][hq] or NULL: natural-log sum of exp of the logits
  * An item with no retained token gives out = 0, lse = -inf.  One launch (two when a token-wise cache holds 16-bit
- * rows): the workgroup that finishes an item's last chunk merges the item's split partials.  A cache keeps one
- * split workspace per stream it is decoded on, so steps on different streams may overlap (steps on one stream are
+ * rows and has more than 256 chunks): the workgroup that finishes an item's last chunk merges the item's split
+ * partials.  A cache keeps one split workspace per stream it is decoded on, so steps on different streams may overlap (steps on one stream are
  * serialised by the stream).  The workspace of the stream that built the cache (or last rebuilt its schedule:
  * rdkv_cache_reserve_tail, rdkv_cache_rebudget_tail) exists from the start; the first step on any other stream
  * allocates that stream's workspace through the cache's allocator.  A step issued while its stream is under graph
@@ -283,7 +283,7 @@ rdkv_status rdkv_decode_attn_bf16_noalloc(const void* K, const void* V, const in
  * rdkv_decode_attn (merge included), the split-K kernel of rdkv_decode_attn_bf16,
  * every kernel of rdkv_weights, every kernel of rdkv_allocate, and the kernels of
  * rdkv_pack in two brackets (tier counts before the call's one wait; position
- * lists, quantize and pack after it; the arena's clearing is not inside).
+ * lists, quantize and pack after it; the copies of tables and counts are not inside).
  * rdkv_kernel_timing_read waits for the recorded events, returns the number of
  * brackets of one kind and their summed duration in milliseconds, and clears that
  * kind.  Not for use under graph capture.

@@ -1,25 +1,43 @@
 // Log-sum-exp merge of the split partials of a decode step (the last step of Eq. 7's evaluation as a split-K
-// flash-decode) inside the decode kernels themselves: every workgroup stores its chunk's partial result, announces
-// it on the item's arrival counter, and the workgroup that arrives last merges all partials of the item and writes
-// the output rows.  One launch per decode step instead of a split launch and a merge launch.
+// flash-decode) inside the decode launch itself: one launch per step instead of a split launch and a merge launch.
 //
-// Memory ordering across the chip's eight L2 caches: partials are written and read with agent-scope accesses (they
-// go through to memory instead of staying in one XCD's L2), every thread waits for its stores to drain before the
-// workgroup's barrier, and one thread then bumps the counter with an agent-scope atomic.  The merging workgroup resets the
-// counter, so a cache's workspace is ready for the next step on the same stream.  The merge has a fixed summation
-// order (slot order), so results do not depend on which workgroup happens to arrive last.
+// Memory across the chip's eight L2 caches: partials are written and read with agent-scope accesses, which go through to
+// memory instead of staying in one XCD's L2.  Either way of merging has a fixed summation order (slot order), so results do
+// not depend on which chunk happens to end last.
+//
+// Large launches count (arrive_and_merge): every workgroup stores its chunk's partial, waits until the stores have drained,
+// announces it on the item's arrival counter, and the workgroup that completes an item merges its partials and resets the
+// counter.
+//
+// Small launches look (merge_part): behind the chunks they have workgroups that only merge, each some of an item's output
+// channels.  A word of a partial is its own arrival flag: between steps every word of the workspace holds kAbsent, a NaN that a
+// partial never holds (`present`), and the merging wavefront puts it back once it has read a word.  Nothing is ordered
+// against anything, so no store is waited for and there is no counter.  What that saves is two memory round trips after
+// a chunk's last store (drain, counter; 20 arrivals at once queue for 1.4 us) and a merge in one workgroup per item with eight
+// slots per thread: from the last partial's store to the end of the launch 4.3 us counted, 1.7 so (time stamps, 164 chunks).
+// Launches of 30, 164 and 178 chunks with 2 to 8 items 7.0 -> 5.1, 9.5 -> 6.7 and 10.7 -> 9.2 us, 208 channel-wise ones
+// 15.2 -> 12.3 (replayed from a graph).
+// In large launches the merging workgroups come too late, one behind the other in what slots the chunks leave (16 ragged
+// sequences with 8 query heads 43.7 us counted, 46.8 looked at; 16 channel-wise ones 77.6, 77.8).
+//
+// Why the wait ends: the merging workgroups are the last of the grid, workgroups are dispatched in the order of the grid on
+// each XCD, and only merging workgroups wait; so whatever a merging workgroup waits for is running or done, however many
+// other launches share the chip.  Should two steps use one workspace at a time, which the interface forbids, the wait still
+// ends after kMostTries looks (seconds).
 #pragma once
 #include "rdkv_internal.h"
+#include "wave_ops.h"
 
 namespace rdkv {
 
 struct MergeArgs {
-  float* part_acc;     // [slots][g][128] unnormalised partial outputs
-  float* part_ml;      // [slots][g][2]   running maximum (log2 domain) and sum of each partial
-  int32_t* arrive;     // [items] arrival counters, zero between steps
+  float* part_acc;     // [slots][g][128] unnormalised partial outputs; launches that look: [slots][g] look records
+  float* part_ml;      // [slots][g][2]   running maximum (log2 domain) and sum of each partial (launches that count)
+  int32_t* arrive;     // [items] arrival counters, zero between steps (launches that count)
   float* out;          // [batch][hq][128]
   float* lse;          // [batch][hq] or null
   int32_t g;           // query heads per KV head: item i (sequence x KV head) owns output rows i g .. i g + g - 1
+  int32_t parts;       // merging workgroups of an item, 8 g / parts blocks each
 };
 
 inline hipError_t launch_decode_mixed(const Chunk* chunks, int n_chunks, const uint8_t* arena, const ItemK* items_k,
@@ -36,8 +54,32 @@ namespace merge {
 
 constexpr float kNegBig = -1.0e30f;
 
+constexpr uint32_t kAbsent = 0xFFFFFFFFu;
+constexpr int kMostTries = 1 << 23;
+constexpr int kSc1 = 16;                  // cache policy of the buffer accesses: agent scope
+
+using uint4v = __attribute__((ext_vector_type(4))) unsigned;
+using uint2v = __attribute__((ext_vector_type(2))) unsigned;
+
+// v, with another NaN in place of kAbsent
+__device__ __forceinline__ float present(float v) {
+  return __float_as_uint(v) == kAbsent ? __uint_as_float(0x7FC00000u) : v;
+}
 __device__ __forceinline__ void store_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_agent2(float* p, float v0, float v1) {     // (p: a multiple of eight bytes)
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p),
+                     static_cast<uint64_t>(__float_as_uint(v0)) | (static_cast<uint64_t>(__float_as_uint(v1)) << 32),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A look record: the partial of a slot and head in kBlocks blocks of 16 channels, which have a reading wavefront each.  A block
+// is a line of 128 bytes: [16] accumulators, running maximum, sum, "ends soon", nothing; so that every word has one reader
+// and a reader's loads of a block are one request.
+constexpr int kBlocks = 8, kBlockFloats = 32, kRecordFloats = kBlocks * kBlockFloats;
+__device__ __forceinline__ float* look_record(const MergeArgs& ma, int slot, int head, int block) {
+  return ma.part_acc + (static_cast<int64_t>(slot) * ma.g + head) * kRecordFloats + block * kBlockFloats;
 }
 
 // Every thread calls this after its last store_agent of the partial and before the workgroup barrier that precedes
@@ -51,8 +93,6 @@ __device__ __forceinline__ void partial_stores_done() { asm volatile("s_waitcnt 
 // reduces its slots with running maxima, and the SG groups are combined through LDS.  Sixteen bytes of a partial and one
 // (maximum, sum) pair per load -- with one channel and all heads per thread (96 loads instead of 16 at g = 4) the merge of
 // 21 slots took 2.75 us of a 12.3 us launch.
-constexpr int kSc1 = 16;                  // cache policy of the buffer accesses: agent scope
-
 template <int NT, int G>
 __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int slot0, int nslots, float* smem) {
   constexpr int kCols = G * kHeadDim / 4;
@@ -69,8 +109,6 @@ __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int sl
                                                           nslots * G * kHeadDim * 4, 0x00027000);
   const auto ml_rsrc = __builtin_amdgcn_make_buffer_rsrc(ma.part_ml + static_cast<int64_t>(slot0) * G * 2, 0,
                                                          nslots * G * 8, 0x00027000);
-  using uint4v = __attribute__((ext_vector_type(4))) unsigned;
-  using uint2v = __attribute__((ext_vector_type(2))) unsigned;
   float m_run = kNegBig, l_run = 0.f, o_run[4] = {0.f, 0.f, 0.f, 0.f};
   for (int s0 = sg; s0 < nslots; s0 += SG * kBatch) {
     uint4v a[kBatch];
@@ -159,7 +197,161 @@ __device__ __forceinline__ void arrive_and_merge(const MergeArgs& ma, int item, 
   if (tid == 0) __hip_atomic_store(ma.arrive + item, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// LDS floats arrive_and_merge needs for NT threads (the flag, SG * G <= NT / 32 maxima and sums, four sums per thread)
+// A wavefront of a merging workgroup: C blocks of 16 channels, block0 + k block_step counted over the heads of the item.
+// lane = (slot group of sixteen, four neighbouring channels); BATCH slots of a lane at a time, all loads of a batch in flight
+// together and repeated until none of their words is absent; then the slot groups are added across the lanes.  No LDS and no
+// barrier: what a workgroup's wavefronts exchange they would wait for (a slot group per half wavefront and the rest through
+// LDS took 1.2 us from the last word's arrival, this 0.5).  What bounds it then are requests: two per slot and block, eight
+// wavefronts of 32 workgroups, made 16 MB layers 10.8 us; a line per block and 64 workgroups 9.3, 128 of them 9.2.
+template <int C, int BATCH>
+__device__ __forceinline__ void merge_blocks(const MergeArgs& ma, int item, int slot0, int nslots, int block0, int block_step) {
+  constexpr int SG = 16;
+  const int lane = threadIdx.x & 63, sg = lane >> 2, col = lane & 3;
+  const int step = ma.g * kRecordFloats * 4;      // bytes from slot to slot
+  // loads past the last slot return zeros, stores there are dropped (the buffer's bounds)
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(ma.part_acc + static_cast<int64_t>(slot0) * ma.g * kRecordFloats, 0,
+                                                      nslots * step, 0x00027000);
+  const auto ml_at = [&](int c) { return (block0 + c * block_step) * (kBlockFloats * 4) + 64; };
+  const auto acc_at = [&](int c) { return (block0 + c * block_step) * (kBlockFloats * 4) + col * 16; };
+  int tries = 0;
+  // "Ends soon" first, until all slots of the first batch say so: the loads of whole partials would take their bandwidth from
+  // the chunks.  (It takes a chunk 1 us from there to its stores, and the news a little less to come here.)
+  for (;;) {
+    uint32_t soon[BATCH], most = 0;
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u)               // (past the last slot: zero)
+      soon[u] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (u * SG + sg) * step + ml_at(0) + 8, 0, kSc1);
+    asm volatile("" ::: "memory");                // (load again next time)
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) most = max(most, soon[u]);
+    if (!__any(most == kAbsent) || ++tries >= kMostTries) break;
+  }
+  float m_run[C], l_run[C], o_run[C][4];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    m_run[c] = kNegBig;
+    l_run[c] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o_run[c][k] = 0.f;
+  }
+  struct Slots {
+    uint4v a[C][BATCH];
+    uint2v ml[C][BATCH];
+  };
+  Slots x, y;                                     // two looks under way, half a round trip apart
+  for (int base = 0; base < nslots; base += SG * BATCH) {
+    const auto load = [&](Slots& v) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          const int s = (base + u * SG + sg) * step;
+          v.ml[c][u] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, s + ml_at(c), 0, kSc1);
+          v.a[c][u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, s + acc_at(c), 0, kSc1);
+        }
+      asm volatile("" ::: "memory");
+    };
+    const auto complete = [&](const Slots& v) __attribute__((always_inline)) {
+      uint32_t most = 0;                          // kAbsent is the largest word
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          most = max(max(most, v.ml[c][u].x), v.ml[c][u].y);
+          most = max(max(most, v.a[c][u].x), v.a[c][u].y);
+          most = max(max(most, v.a[c][u].z), v.a[c][u].w);
+        }
+      return !__any(most == kAbsent) || ++tries >= kMostTries;
+    };
+    Slots z;
+    load(x);
+    for (;;) {
+      load(y);
+      if (complete(x)) { z = x; break; }
+      load(x);
+      if (complete(y)) { z = y; break; }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const int s = (base + u * SG + sg) * step;
+        const uint4v absent = {kAbsent, kAbsent, kAbsent, kAbsent};
+        __builtin_amdgcn_raw_buffer_store_b128(absent, rsrc, s + acc_at(c), 0, kSc1);
+        if (col == 0) __builtin_amdgcn_raw_buffer_store_b128(absent, rsrc, s + ml_at(c), 0, kSc1);
+      }
+      float mb = m_run[c], mv[BATCH];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        mv[u] = base + u * SG + sg < nslots ? __uint_as_float(z.ml[c][u].x) : kNegBig;
+        mb = fmaxf(mb, mv[u]);
+      }
+      const float f0 = __builtin_amdgcn_exp2f(m_run[c] - mb);
+      l_run[c] *= f0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o_run[c][k] *= f0;
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const float f = __builtin_amdgcn_exp2f(mv[u] - mb);
+        l_run[c] = __builtin_fmaf(__uint_as_float(z.ml[c][u].y), f, l_run[c]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o_run[c][k] = __builtin_fmaf(__uint_as_float(z.a[c][u][k]), f, o_run[c][k]);
+      }
+      m_run[c] = mb;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const float mm = head_max(m_run[c]);
+    const float f = __builtin_amdgcn_exp2f(m_run[c] - mm);
+    const float l = head_sum(l_run[c] * f);
+    // the sums over the slot groups, the four channels turned into the four rows of lanes on the way
+    float o[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = o_run[c][k] * f;
+    swap_rows(o[0], o[1]);
+    swap_rows(o[2], o[3]);
+    float lo = o[0] + o[1], hi = o[2] + o[3];
+    swap_halves(lo, hi);
+    float v = lo + hi;
+    v += dpp_f32<0x124>(v);
+    v += dpp_f32<0x128>(v);
+    const int block = block0 + c * block_step;
+    if ((lane & 12) == 0)
+      ma.out[static_cast<int64_t>(item) * ma.g * kHeadDim + block * 16 + 4 * col + (lane >> 4)] = l > 0.f ? v / l : 0.f;
+    if (lane == 0 && block % kBlocks == 0 && ma.lse != nullptr)
+      ma.lse[static_cast<int64_t>(item) * ma.g + block / kBlocks] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
+  }
+  // The look that was not needed is still on its way: its registers must not be used for anything before (that would wait for
+  // it: 0.8 us).
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) asm volatile("" ::"v"(x.a[c][u]), "v"(x.ml[c][u]), "v"(y.a[c][u]), "v"(y.ml[c][u]));
+}
+
+// A merging workgroup of NWV wavefronts (a chunk of tier kTierMerge): part ch.row0 of the item's blocks.
+template <int NWV>
+__device__ __forceinline__ void merge_part(const MergeArgs& ma, const Chunk& ch) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blocks = ma.g * kBlocks / ma.parts, block0 = ch.row0 * blocks + wave;
+  if (wave >= blocks) return;
+  // (merge_parts keeps a workgroup to four heads)
+  switch (blocks / NWV) {
+    case 0:
+    case 1:
+      if (ch.nslots <= 32) return merge_blocks<1, 2>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
+      return merge_blocks<1, 4>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
+    case 2:
+      if (ch.nslots <= 16) return merge_blocks<2, 1>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
+      return merge_blocks<2, 2>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
+    case 4: return merge_blocks<4, 1>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
+    default:
+      if constexpr (NWV < 8) return merge_blocks<8, 1>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
+  }
+}
+
+// LDS floats arrive_and_merge needs for NT threads (a flag, at most NT / 32 maxima and sums, four sums per thread)
 __host__ __device__ constexpr int merge_lds_floats(int nt) { return 16 + 2 * (nt / 32) + nt * 4; }
 
 }  // namespace merge

@@ -214,11 +214,17 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
   const int n_tail = *tail_len;      // with the chunk, not after it
   const uint16_t* qp = q + static_cast<int64_t>(ch.item) * g * kHeadDim;     // item = sequence x KV head
   const ChunkOut co{ch.item, ch.slot, ch.slot0, ch.nslots};
-  float* s_ml = reinterpret_cast<float*>(smem);   // [NWV][4 HS][2]
-  float* s_acc = s_ml + NWV * 4 * HS * 2;           // finish_lds_floats(NWV, g)
+  float* s_ml = reinterpret_cast<float*>(smem);
+  float* s_acc = s_ml + ml_lds_floats(NWV, HS);     // finish_lds_floats(NWV, g)
+  if constexpr (ROOMY) {
+    if (ch.tier == kTierMerge) {
+      merge::merge_part<NWV>(ma, ch);
+      return;
+    }
+  }
   if (ch.tier == kTierTail) {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
     const int rows = max(0, min(ch.rows, n_tail - ch.row0));
-    process_tail_tiles<HS, false, NWV>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, s_ml, s_acc, ma, co);
+    process_tail_tiles<HS, false, NWV, ROOMY>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, s_ml, s_acc, ma, co);
     return;
   }
   if constexpr (!MULTI) {
@@ -228,11 +234,11 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
     run.init();                                                                                                   \
     process_tiles<TIER_, HS, NWV, ROOMY>(arena + ch.k_data, arena + ch.k_meta, arena + ch.v_data, arena + ch.v_meta,     \
                                   ch.rows, g, qp, run);                                                           \
-    finish_chunk<HS, false, NWV>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                                  \
+    finish_chunk<HS, false, NWV, ROOMY>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                                  \
   }
     if constexpr (ROOMY) {
       if (ch.tier == 16) {      // (launches without 16-bit chunks get less LDS)
-        process_rows_mfma<HS, true, NWV>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
+        process_rows_mfma<HS, true, NWV, true>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
                                          nullptr, nullptr, &ma, &co);
         return;
       }
@@ -266,13 +272,13 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
   RDKV_PIECE(8)
 #undef RDKV_PIECE
   // ---- undo the subnormal unit, add the offsets, merge the wavefronts, hand the partial over -------------------
-  finish_chunk<HS, false, NWV>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);
+  finish_chunk<HS, false, NWV, ROOMY>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);
 }
 
 template <int HS, int NWV, bool MULTI, bool ROOMY>
-hipError_t launch_tiles(const Chunk* chunks, int first, int n_chunks, bool rows16, const uint8_t* arena, const uint16_t* q,
+hipError_t launch_tiles(const Chunk* chunks, int first, int n_blocks, bool rows16, const uint8_t* arena, const uint16_t* q,
                         const MergeArgs& ma, const int32_t* tail_len, hipStream_t st) {
-  size_t lds = (NWV * 4 * HS * 2 + finish_lds_floats(NWV, ma.g)) * sizeof(float);
+  size_t lds = (ml_lds_floats(NWV, HS) + finish_lds_floats(NWV, ma.g)) * sizeof(float);
   if constexpr (ROOMY)
     if (rows16) {
       constexpr size_t kRows = rows_lds_bytes<HS, NWV>();
@@ -280,7 +286,7 @@ hipError_t launch_tiles(const Chunk* chunks, int first, int n_chunks, bool rows1
       if (e != hipSuccess) return e;
       lds = lds > kRows ? lds : kRows;
     }
-  hipLaunchKernelGGL((decode_tiles_kernel<HS, NWV, MULTI, ROOMY>), dim3(n_chunks), dim3(NWV * 64), lds, st, chunks, arena, q,
+  hipLaunchKernelGGL((decode_tiles_kernel<HS, NWV, MULTI, ROOMY>), dim3(n_blocks), dim3(NWV * 64), lds, st, chunks, arena, q,
                      tail_len, first, ma.g, ma);
   return hipGetLastError();
 }
@@ -289,17 +295,19 @@ hipError_t launch_tiles(const Chunk* chunks, int first, int n_chunks, bool rows1
 
 bool decode_tiles_take_rows(int n_chunks, bool multi) { return !multi && n_chunks <= 256; }
 
-// `rows16`: the range starts with chunks of the 16-bit tier (allowed when decode_tiles_take_rows says so)
-hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, bool rows16, bool multi, const uint8_t* arena,
-                               const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, hipStream_t st) {
+hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, int n_merge, bool rows16, bool multi,
+                               const uint8_t* arena, const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len,
+                               hipStream_t st) {
   if (n_chunks == 0) return hipSuccess;
-  if (rows16 && !decode_tiles_take_rows(n_chunks, multi)) return hipErrorInvalidValue;
+  const bool look = n_merge >= 0;
+  if (look && !decode_tiles_take_rows(n_chunks, multi)) return hipErrorInvalidValue;
+  if (rows16 && !look) return hipErrorInvalidValue;
   // up to 4 query heads per KV head: one head set, workgroups of eight wavefronts; 8 heads: two head sets, workgroups of
   // four
-#define RDKV_TILES(HS_, NWV_)                                                                                              \
+#define RDKV_TILES(HS_, NWV_)                                                                                             \
+  if (look) return launch_tiles<HS_, NWV_, false, true>(chunks, first, n_chunks + n_merge, rows16, arena, q, ma, tail_len, st); \
   if (multi) return launch_tiles<HS_, NWV_, true, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st);      \
-  if (n_chunks > 256) return launch_tiles<HS_, NWV_, false, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st); \
-  return launch_tiles<HS_, NWV_, false, true>(chunks, first, n_chunks, rows16, arena, q, ma, tail_len, st);
+  return launch_tiles<HS_, NWV_, false, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st);
   if (ma.g > 4) {
     RDKV_TILES(2, 4)
   }

@@ -49,7 +49,7 @@ struct LdsPlan {
     wtab_wave = 2 * n_qsteps * hs * 64;
     int tables = wtab + kWaves * wtab_wave + 8 * hs * 64;
     if (tables < wtab + g * kHeadDim * 2) tables = wtab + g * kHeadDim * 2;     // the query rows, before there are tables
-    const int merge = kWaves * 4 * hs * 2 * 4 + finish_lds_floats(kWaves, g) * 4;
+    const int merge = (ml_lds_floats(kWaves, hs) + finish_lds_floats(kWaves, g)) * 4;
     total = tables > merge ? tables : merge;
   }
 };
@@ -470,8 +470,8 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
     }
   }
 
-  finish_chunk<HS, true, NWV>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
-                                 reinterpret_cast<float*>(smem) + kWaves * 4 * HS * 2, ma, co);
+  finish_chunk<HS, true, NWV, NWV == 8>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
+                                 reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
 }
 
 template <int NW, int HS, int NWV>
@@ -487,10 +487,13 @@ __global__ __launch_bounds__(NWV * 64, (NW <= 32 && HS == 1) ? 3 : 2) void decod
   switch (ch.tier) {
     case kTierTail: {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
       const int rows = max(0, min(ch.rows, *tail_len - ch.row0));
-      process_tail_tiles<HS, true, NWV>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, reinterpret_cast<float*>(smem),
-                                        reinterpret_cast<float*>(smem) + NWV * 4 * HS * 2, ma, co);
+      process_tail_tiles<HS, true, NWV, NWV == 8>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, reinterpret_cast<float*>(smem),
+                                        reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
       break;
     }
+    case kTierMerge:
+      if constexpr (NWV == 8) merge::merge_part<NWV>(ma, ch);
+      break;
     case 16: process_mixed<16, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
     case 8: process_mixed<8, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
     case 4: process_mixed<4, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;

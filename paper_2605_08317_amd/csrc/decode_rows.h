@@ -26,9 +26,9 @@ constexpr int kRowStride = 272;                       // bytes per token row in 
 constexpr int kStageBytes = kTile * kRowStride;       // one wavefront's staging region
 template <int HS, int NWV>
 constexpr int rows_lds_bytes() {
-  // the wavefronts' staging regions, [waves][4 HS][m, l] floats;
+  // the wavefronts' staging regions, their maxima and sums;
   // the end-of-chunk areas (per-wavefront accumulators [waves][g][128] floats, then the merge) reuse the staging
-  return NWV * kStageBytes + NWV * 4 * HS * 2 * 4;
+  return NWV * kStageBytes + ml_lds_floats(NWV, HS) * 4;
 }
 
 __device__ __forceinline__ uint4 load_row_chunk(const uint8_t* __restrict__ base, int row, int c16) {
@@ -59,9 +59,9 @@ __device__ __forceinline__ void pv_steps(const uint8_t* s_stage, int lane, const
   (pv_step<A, HS>(s_stage, lane, phi, plo, run), ...);
 }
 
-// TIERED: the chunk's partial goes to the split workspace with agent-scope stores and the workgroup announces it
-// (the item's last workgroup merges); otherwise plain stores for a merge kernel that follows.
-template <int HS, bool TIERED, int NWV>
+// TIERED: the chunk's partial goes to the split workspace for the launch's merging workgroups (LOOK) or is announced
+// (store_partial); otherwise plain stores for a merge kernel that follows.
+template <int HS, bool TIERED, int NWV, bool LOOK = false>
 __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
                                                   int rows, int g, const uint16_t* __restrict__ q, uint8_t* smem,
                                                   float* __restrict__ part_acc, float* __restrict__ part_ml,
@@ -139,12 +139,13 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
   // ---- end of the chunk: merge the workgroup's wavefronts, store the partial ---------------------------------------
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) run.l[hs] = head_sum(run.l[hs]);
+  if constexpr (TIERED) ends_soon<LOOK>(g, *ma, *co);
   __syncthreads();                      // the staging regions become the accumulator area
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) {
-    if (lane < 4)
-      *reinterpret_cast<float2*>(s_ml + ((wave * HS + hs) * 4 + lane) * 2) =
-          make_float2(run.m[hs] * kXScale - kPExp, run.l[hs]);      // log2 domain from here on
+    if (lane < 16)        // (block, j) -> group block of head j; log2 domain from here on
+      *reinterpret_cast<float4*>(s_ml + ml_at<HS>(wave, 4 * hs + (lane & 3), lane >> 2)) =
+          make_float4(run.m[hs] * kXScale - kPExp, run.l[hs], 0.f, 0.f);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int head = 4 * hs + i;
@@ -154,7 +155,7 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
     }
   }
   if constexpr (TIERED) {
-    store_partial<HS, NWV>(g, s_ml, s_acc, *ma, *co);
+    store_partial<HS, NWV, LOOK>(1.0f, g, s_ml, s_acc, *ma, *co);
   } else {
     __syncthreads();
     for (int idx = tid; idx < g * kHeadDim; idx += NWV * 64) {
@@ -162,14 +163,14 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
       float m[NWV], mm = kNegBig, v = 0.f, ll = 0.f;
 #pragma unroll
       for (int w = 0; w < NWV; ++w) {
-        m[w] = s_ml[(w * HS * 4 + head) * 2];
+        m[w] = s_ml[ml_at<HS>(w, head, 0)];
         mm = fmaxf(mm, m[w]);
       }
 #pragma unroll
       for (int w = 0; w < NWV; ++w) {
         const float f = fast_exp2(m[w] - mm);
         v = __builtin_fmaf(s_acc[w * g * kHeadDim + idx], f, v);
-        ll = __builtin_fmaf(s_ml[(w * HS * 4 + head) * 2 + 1], f, ll);
+        ll = __builtin_fmaf(s_ml[ml_at<HS>(w, head, 0) + 1], f, ll);
       }
       part_acc[idx] = v;
       if ((idx & 127) == 0) {

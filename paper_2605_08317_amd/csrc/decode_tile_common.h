@@ -63,30 +63,6 @@ union Pack4 {
   uint32_t u[2];
 };
 
-__device__ __forceinline__ float sum_xor16(float v) {
-  float o = v;
-  swap_rows(v, o);
-  return v + o;
-}
-// Reduction over the 16 lanes that hold the same head (lane % 4): lanes 4 apart inside a row of 16, then the rows.  No
-// step goes through LDS: with two or three wavefronts per SIMD nothing covers the 100 cycles of a ds_bpermute (a chunk's
-// five sums took 0.65 us).
-__device__ __forceinline__ float head_max(float v) {
-  v = fmaxf(v, dpp_f32<0x124>(v));   // row_ror:4
-  v = fmaxf(v, dpp_f32<0x128>(v));   // row_ror:8
-  float o = v;
-  swap_rows(v, o);
-  o = v = fmaxf(v, o);
-  swap_halves(v, o);
-  return fmaxf(v, o);
-}
-__device__ __forceinline__ float head_sum(float v) {
-  v += dpp_f32<0x124>(v);
-  v += dpp_f32<0x128>(v);
-  float o = v = sum_xor16(v);
-  swap_halves(v, o);
-  return v + o;
-}
 // value held by lane i of this lane's quad
 template <int I>
 __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) { return dpp_u32<I * 0x55>(v); }
@@ -356,96 +332,123 @@ struct ChunkOut {
   int item, slot, slot0, nslots;   // the chunk's item and partial slot; the item's first slot and slot count
 };
 
-// Floats of LDS the end of a chunk needs behind s_ml: the wavefronts' sums, later the merge of the item.
+// Floats of LDS the end of a chunk needs behind s_ml for the wavefronts' sums (launches that count: later the merge's).
 __host__ __device__ constexpr int finish_lds_floats(int waves, int g) {
   return waves * g * kHeadDim > merge::merge_lds_floats(waves * 64) ? waves * g * kHeadDim : merge::merge_lds_floats(waves * 64);
 }
+// Floats of s_ml: per wavefront, head and channel group the maximum, the sum, the group's offset sum and a free word.
+__host__ __device__ constexpr int ml_lds_floats(int waves, int hs) { return waves * hs * 4 * kGroupsPerRow * 4; }
+template <int HS>
+__device__ __forceinline__ constexpr int ml_at(int wave, int head, int group) {
+  return ((wave * HS * 4 + head) * kGroupsPerRow + group) * 4;
+}
 
-// Last part of a chunk's end, after s_ml ([NWV][4 HS heads] of maximum, sum) and s_acc ([NWV][g][128] unnormalised sums,
-// each relative to its wavefront's own maximum) are written: one barrier, then every thread weighs and adds the NWV
-// wavefronts' values of its (head, channel).  An item of a single chunk is finished here; otherwise the partial result is
-// stored and announced, and the workgroup that completes its item merges the item's partials (arrive_and_merge).
-template <int HS, int NWV>
-__device__ __forceinline__ void store_partial(int g, const float* s_ml, float* s_acc, const MergeArgs& ma, const ChunkOut& co) {
-  constexpr int NT = NWV * 64;
-  const int tid = threadIdx.x;
-  float* __restrict__ part_acc = ma.part_acc + static_cast<int64_t>(co.slot) * g * kHeadDim;
-  float* __restrict__ part_ml = ma.part_ml + static_cast<int64_t>(co.slot) * g * 2;
+// Last part of a chunk's end, after s_ml and s_acc ([NWV][g][128] unnormalised sums times 1 / acc_scale, offset sums not
+// included, each relative to its wavefront's own maximum) are written: one barrier, then a wavefront per head weighs and adds
+// the NWV wavefronts' values, two channels a lane.  The weights are made once, lane w of each row of lanes that of wavefront
+// w (by every lane for itself they were eight exponentials and eight more reads of LDS).  An item of a single chunk is finished
+// here; otherwise the partial result is stored, for the item's merging workgroups (LOOK) or announced (decode_merge.h).
+template <int HS, int NWV, bool LOOK>
+__device__ __forceinline__ void store_partial(float acc_scale, int g, const float* s_ml, float* s_acc, const MergeArgs& ma,
+                                              const ChunkOut& co) {
+  const int lane = threadIdx.x & 63, ch = 2 * lane;
   const bool single = co.nslots == 1;
   const int64_t qh0 = static_cast<int64_t>(co.item) * g;
   __syncthreads();
-  for (int idx = tid; idx < g * kHeadDim; idx += NT) {
-    const int head = idx >> 7;
-    float2 ml[NWV];
-    float a[NWV], mm = kNegBig;
+  for (int head = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); head < g; head += NWV) {
+    // row of lanes = channel group, which is that of the lane's two channels
+    const float2 ml = *reinterpret_cast<const float2*>(s_ml + ml_at<HS>(lane & (NWV - 1), head, lane >> 4));
+    float2 a[NWV];
+    float off[NWV];      // (added wavefront by wavefront: the two terms of an output nearly cancel)
 #pragma unroll
     for (int w = 0; w < NWV; ++w) {
-      ml[w] = *reinterpret_cast<const float2*>(s_ml + (w * HS * 4 + head) * 2);
-      a[w] = s_acc[w * g * kHeadDim + idx];
+      a[w] = *reinterpret_cast<const float2*>(s_acc + (w * g + head) * kHeadDim + ch);
+      off[w] = s_ml[ml_at<HS>(w, head, lane >> 4) + 2];
     }
-#pragma unroll
-    for (int w = 0; w < NWV; ++w) mm = fmaxf(mm, ml[w].x);
-    float v = 0.f, l = 0.f;
+    const float mm = row_max(ml.x);
+    const float f = fast_exp2(ml.x - mm);
+    const bool own = (lane & 15) < NWV;      // (the other lanes repeat one)
+    const float l = row_sum(own ? ml.y * f : 0.f);
+    float v0 = 0.f, v1 = 0.f;
 #pragma unroll
     for (int w = 0; w < NWV; ++w) {
-      const float f = fast_exp2(ml[w].x - mm);
-      l = __builtin_fmaf(ml[w].y, f, l);
-      v = __builtin_fmaf(a[w], f, v);
+      const float fw = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), w));
+      v0 = __builtin_fmaf(__builtin_fmaf(a[w].x, acc_scale, off[w]), fw, v0);
+      v1 = __builtin_fmaf(__builtin_fmaf(a[w].y, acc_scale, off[w]), fw, v1);
     }
     if (single) {
-      ma.out[qh0 * kHeadDim + idx] = l > 0.f ? v / l : 0.f;
-      if ((idx & 127) == 0 && ma.lse != nullptr)
-        ma.lse[qh0 + head] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
+      float* o = ma.out + (qh0 + head) * kHeadDim + ch;
+      o[0] = l > 0.f ? v0 / l : 0.f;
+      o[1] = l > 0.f ? v1 / l : 0.f;
+      if (lane == 0 && ma.lse != nullptr) ma.lse[qh0 + head] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
+    } else if constexpr (LOOK) {
+      float* rec = merge::look_record(ma, co.slot, head, ch >> 4);
+      merge::store_agent2(rec + (ch & 15), merge::present(v0), merge::present(v1));
+      if ((ch & 15) == 0) merge::store_agent2(rec + 16, merge::present(mm), merge::present(l));
     } else {
-      merge::store_agent(part_acc + idx, v);
-      if ((idx & 127) == 0) {
-        merge::store_agent(part_ml + head * 2, mm);
-        merge::store_agent(part_ml + head * 2 + 1, l);
-      }
+      merge::store_agent2(ma.part_acc + (static_cast<int64_t>(co.slot) * g + head) * kHeadDim + ch, v0, v1);
+      if (lane == 0) merge::store_agent2(ma.part_ml + (static_cast<int64_t>(co.slot) * g + head) * 2, mm, l);
     }
   }
-  if (single) return;
-  merge::partial_stores_done();
-  __syncthreads();     // every partial store has landed, and nobody reads s_ml / s_acc any more
-  merge::arrive_and_merge<NT, 4 * HS>(ma, co.item, co.slot0, co.nslots, g, s_acc);
+  if constexpr (!LOOK) {
+    if (single) return;
+    merge::partial_stores_done();
+    __syncthreads();     // every partial store has landed, and nobody reads s_ml / s_acc any more
+    merge::arrive_and_merge<NWV * 64, 4 * HS>(ma, co.item, co.slot0, co.nslots, g, s_acc);
+  }
 }
 
-// End of a chunk: scale the accumulators back (acc_scale = 2^24 where the V codes entered as fp16 subnormals),
-// take the lane's factor kappa = 2^lk out of the running sums, add the offset sums and the two token halves, and merge
-// the workgroup's NWV wavefronts through LDS (store_partial).
-// s_ml: [NWV][4 HS heads][m, l] floats; s_acc: finish_lds_floats(NWV, g) floats.  ALIAS: the two areas overlap LDS that
+// A chunk's first wavefront is through with its tiles: the item's merging workgroups start to look at whole partials.
+template <bool LOOK>
+__device__ __forceinline__ void ends_soon(int g, const MergeArgs& ma, const ChunkOut& co) {
+  if constexpr (LOOK)
+    if (threadIdx.x < g * merge::kBlocks && co.nslots > 1)
+      merge::store_agent(merge::look_record(ma, co.slot, threadIdx.x / merge::kBlocks, threadIdx.x % merge::kBlocks) + 18, 0.f);
+}
+
+// End of a chunk: take the lane's factor kappa = 2^lk out of the running sums, add the token halves of the accumulators and
+// the blocks' offset sums, and merge the workgroup's NWV wavefronts through LDS (store_partial; acc_scale = 2^24 where the V
+// codes entered as fp16 subnormals).
+// s_ml: ml_lds_floats(NWV, HS); s_acc: finish_lds_floats(NWV, g) floats.  ALIAS: the two areas overlap LDS that
 // the tile loop used, so a barrier separates the two uses.
-template <int HS, bool ALIAS, int NWV>
+template <int HS, bool ALIAS, int NWV, bool LOOK>
 __device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, float lk, int g, float* s_ml,
                                              float* s_acc, const MergeArgs& ma, const ChunkOut& co) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool upper = lane >= 32;
   const float inv_kappa = __builtin_ldexpf(1.0f, static_cast<int>(-lk));   // lk is a small integer
+  ends_soon<LOOK>(g, ma, co);
   if constexpr (ALIAS) __syncthreads();
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) {
     run.l[hs] = head_sum(run.l[hs] * inv_kappa);
-    if (lane < 4)
-      *reinterpret_cast<float2*>(s_ml + ((wave * HS + hs) * 4 + lane) * 2) =
-          make_float2(run.m[hs] * kXScale - kPExp, run.l[hs]);      // log2 domain from here on
+    // lanes (block, j) hold head i's sum_t p m of channel group j over the block's tokens.  The sums over the blocks, the
+    // four heads turned into the four rows of lanes on the way
+    float o[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = run.offv[hs][i] * inv_kappa;
+    swap_rows(o[0], o[1]);
+    swap_rows(o[2], o[3]);
+    float lo = o[0] + o[1], hi = o[2] + o[3];
+    swap_halves(lo, hi);
+    float off = lo + hi;
+    off += dpp_f32<0x124>(off);
+    off += dpp_f32<0x128>(off);
+    if (lane < 16)        // (block, j) -> group block of head j; log2 domain from here on
+      *reinterpret_cast<float2*>(s_ml + ml_at<HS>(wave, 4 * hs + (lane & 3), lane >> 2)) =
+          make_float2(run.m[hs] * kXScale - kPExp, run.l[hs]);
+    if ((lane & 12) == 0) s_ml[ml_at<HS>(wave, 4 * hs + (lane >> 4), lane & 3) + 2] = off;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int head = 4 * hs + i;
-      // lanes (block, j) hold head i's sum_t p m of channel group j over the block's tokens: all blocks, then to the
-      // lanes of every group
-      const uint32_t ou = __builtin_bit_cast(uint32_t, head_sum(run.offv[hs][i] * inv_kappa));
-      const float o0 = __builtin_bit_cast(float, quad_bcast<0>(ou)), o1 = __builtin_bit_cast(float, quad_bcast<1>(ou));
-      const float o2 = __builtin_bit_cast(float, quad_bcast<2>(ou)), o3 = __builtin_bit_cast(float, quad_bcast<3>(ou));
-      const float v0 = __builtin_fmaf(halves_sum(run.acc[hs][0][i], run.acc[hs][1][i]), acc_scale, upper ? o1 : o0);
-      const float v1 = __builtin_fmaf(halves_sum(run.acc[hs][2][i], run.acc[hs][3][i]), acc_scale, upper ? o3 : o2);
+      const float v0 = halves_sum(run.acc[hs][0][i], run.acc[hs][1][i]), v1 = halves_sum(run.acc[hs][2][i], run.acc[hs][3][i]);
       if (head < g) {
         s_acc[(wave * g + head) * kHeadDim + lane] = v0;
         s_acc[(wave * g + head) * kHeadDim + 64 + lane] = v1;
       }
     }
   }
-  store_partial<HS, NWV>(g, s_ml, s_acc, ma, co);
+  store_partial<HS, NWV, LOOK>(acc_scale, g, s_ml, s_acc, ma, co);
 }
 
 // A chunk of appended tokens (Sec. 3.3 Zone C: bf16 rows kept after the compression pass) on the same instruction
@@ -453,7 +456,7 @@ __device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, floa
 // bf16 channels 2W, 2W+1) of token r at byte 1024 (W / 4) + 16 r + 4 (W % 4), so a lane (= token) reads its row
 // with sixteen coalesced 16-byte loads; V tile = 16 KiB in the layout of the 16-bit V tiles of mixed mode (lane
 // 32 (r / 32) + c % 32 holds channel c, eight tokens per 16-byte unit u = 4 (c / 32) + (r % 32) / 8 at 1024 u).
-template <int HS, bool ALIAS, int NWV>
+template <int HS, bool ALIAS, int NWV, bool LOOK>
 __device__ __forceinline__ void process_tail_tiles(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
                                                    int rows, int g, const uint16_t* __restrict__ q,
                                                    float* s_ml, float* s_acc, const MergeArgs& ma,
@@ -532,7 +535,7 @@ __device__ __forceinline__ void process_tail_tiles(const uint8_t* __restrict__ k
 #undef RDKV_TAIL_GROUP
 #undef RDKV_TAIL_STEP
   }
-  finish_chunk<HS, ALIAS, NWV>(run, 1.0f, 0.f, g, s_ml, s_acc, ma, co);
+  finish_chunk<HS, ALIAS, NWV, LOOK>(run, 1.0f, 0.f, g, s_ml, s_acc, ma, co);
 }
 
 }  // namespace tile

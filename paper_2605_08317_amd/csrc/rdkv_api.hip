@@ -577,14 +577,16 @@ void free_cache_buffers(rdkv_cache* c) {
   c->absorbed.clear();
 }
 
-// Memory of a split workspace for n_slots partials; the caller clears the arrival counters.
-bool make_workspace(const rdkv_cache* c, hipStream_t st, int64_t n_slots, rdkv_cache::Workspace* w, size_t* arrive_bytes) {
+// Memory of a split workspace for n_slots partials; the caller sets its first *absent bytes to merge::kAbsent, for a
+// launch that looks, and the *arrive bytes at w->arrive to zero.
+bool make_workspace(const rdkv_cache* c, hipStream_t st, int64_t n_slots, rdkv_cache::Workspace* w, size_t* absent, size_t* arrive) {
   Allocator al{c->alloc, c->free_, c->alloc_user};
   const int g = c->hq / c->hkv;
   const size_t slots = static_cast<size_t>(std::max<int64_t>(n_slots, 1));
-  const size_t acc_b = slots * g * kHeadDim * sizeof(float), ml_b = (slots * g * 2 * sizeof(float) + 255) / 256 * 256;
-  *arrive_bytes = static_cast<size_t>(std::max<int64_t>(c->n_items, 1)) * sizeof(int32_t);
-  uint8_t* block = static_cast<uint8_t*>(al.get(acc_b + ml_b + *arrive_bytes));
+  const size_t acc_b = slots * g * merge::kRecordFloats * sizeof(float), ml_b = slots * g * 2 * sizeof(float);
+  *absent = acc_b;
+  *arrive = static_cast<size_t>(std::max<int64_t>(c->n_items, 1)) * sizeof(int32_t);
+  uint8_t* block = static_cast<uint8_t*>(al.get(acc_b + ml_b + *arrive));
   if (!block) return false;
   *w = rdkv_cache::Workspace{st, reinterpret_cast<float*>(block), reinterpret_cast<float*>(block + acc_b),
                              reinterpret_cast<int32_t*>(block + acc_b + ml_b), block};
@@ -607,9 +609,10 @@ rdkv_status workspace_for(const rdkv_cache* c, hipStream_t st, rdkv_cache::Works
     }
   }
   rdkv_cache::Workspace w;
-  size_t arrive_bytes = 0;
-  if (!make_workspace(c, st, c->n_slots, &w, &arrive_bytes)) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
-  const hipError_t e = hipMemsetAsync(w.arrive, 0, arrive_bytes, st);     // counters start at zero; the kernels keep them so
+  size_t absent = 0, arrive = 0;
+  if (!make_workspace(c, st, c->n_slots, &w, &absent, &arrive)) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
+  hipError_t e = hipMemsetAsync(w.arrive, 0, arrive, st);     // (the kernels keep both so)
+  if (e == hipSuccess && c->n_merge > 0) e = hipMemsetAsync(w.block, 0xFF, absent, st);
   if (e != hipSuccess) {
     Allocator{c->alloc, c->free_, c->alloc_user}.put(w.block);
     return fail(RDKV_ERR_HIP, "clearing a split workspace: %s", hipGetErrorString(e));
@@ -661,6 +664,32 @@ void order_chunks(std::vector<Chunk>::iterator first, std::vector<Chunk>::iterat
         if (begin[i] + rank < begin[i + 1]) sorted[out++] = first[key[begin[i] + rank].second];
   }
   std::copy(sorted.begin(), sorted.end(), first);
+}
+
+// Workgroups that merge an item's partials, 8 g / parts blocks of 16 channels each: four per query head while a launch has at
+// most 128 of them, half of what the chip holds beside its chunks, and at least one for every four heads.
+int merge_parts(int g, int64_t n_items) {
+  int parts = 4 * g;
+  while (parts > 1 && 4 * parts > g && parts * n_items > 128) parts /= 2;
+  return parts;
+}
+// their entries of the chunk table: none for items whose only chunk writes the output rows itself
+std::vector<Chunk> merge_chunks(const std::vector<int32_t>& slot_begin, const std::vector<int32_t>& slot_count, int64_t n_items, int g) {
+  std::vector<Chunk> table;
+  const int parts = merge_parts(g, n_items);
+  for (int part = 0; part < parts; ++part)
+    for (int64_t i = 0; i < n_items; ++i) {
+      if (slot_count[i] <= 1) continue;
+      Chunk ch{};
+      ch.tier = kTierMerge;
+      ch.item = static_cast<int32_t>(i);
+      ch.slot0 = slot_begin[i];
+      ch.nslots = slot_count[i];
+      ch.row0 = part;
+      ch.next = -1;
+      table.push_back(ch);
+    }
+  return table;
 }
 
 // every chunk learns its item's first partial slot and slot count (the merge inside the decode kernels needs them)
@@ -985,8 +1014,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   c->stored_bytes = stored;
 
   // byte-balanced chunks: every workgroup streams about the same number of stored bytes.  Every chunk costs its
-  // workgroup a hand-over at the end (partial stores that go through to memory, an arrival atomic whose answer the
-  // workgroup waits for) and its item one more partial to merge, so a launch wants exactly one round of workgroups:
+  // workgroup a hand-over at the end (partial stores that go through to memory and, in larger launches, an arrival atomic
+  // whose answer the workgroup waits for) and its item one more partial to merge, so a launch wants exactly one round of workgroups:
   // as many chunks as the chip keeps resident (256 compute units x 2 workgroups of eight wavefronts = 512), never a
   // few more (measured on 4 x 128K tokens of 2-bit rows: 512 chunks 4.9 TB/s, 608 chunks 4.4, 2048 chunks 4.2).
   // Small launches are bound by latencies instead and want fewer, larger chunks still: at least 96 KB (measured on a
@@ -1240,7 +1269,12 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     for (Chunk& ch : conts) if (ch.next >= 0) ch.next += base;
     c->chunks.insert(c->chunks.end(), conts.begin(), conts.end());
   }
-  const int64_t n_chunks = static_cast<int64_t>(c->chunks.size());
+  // merging workgroups where the decode kernel looks for partials (see decode_merge.h)
+  std::vector<Chunk> mergers;
+  if (mixed ? c->mixed_waves == 8 : decode_tiles_take_rows(static_cast<int>(c->sched16 + c->schedq), c->n_cont > 0))
+    mergers = merge_chunks(slot_begin, slot_count, n, g);
+  c->n_merge = static_cast<int64_t>(mergers.size());
+  const int64_t n_chunks = static_cast<int64_t>(c->chunks.size()), n_table = n_chunks + c->n_merge;
   c->own_slot_count.assign(slot_count.begin(), slot_count.begin() + n);
 
   // ---- allocate what the cache owns: one block --------------------------------------------
@@ -1253,9 +1287,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     const int64_t o_bt = o_idx + up(kept * 4), o_bc = o_bt + up(it.total_tokens);
     const int64_t o_ik = o_bc + (mixed ? up(n * kHeadDim) : 0);
     const int64_t ik_b = mixed ? round_up(n * static_cast<int64_t>(sizeof(ItemK)), 8) : 0;
-    const int64_t o_acc = o_ik + up(ik_b + n_chunks * static_cast<int64_t>(sizeof(Chunk)));
-    const int64_t o_ml = o_acc + up(std::max<int64_t>(n_chunks, 1) * g * kHeadDim * 4);
-    const int64_t o_lam = o_ml + up(std::max<int64_t>(n_chunks, 1) * g * 2 * 4);
+    const int64_t o_acc = o_ik + up(ik_b + n_table * static_cast<int64_t>(sizeof(Chunk)));
+    const int64_t o_ml = o_acc + up(std::max<int64_t>(c->n_slots, 1) * g * (c->n_merge > 0 ? merge::kRecordFloats : kHeadDim) * 4);
+    const int64_t o_lam = o_ml + up(std::max<int64_t>(c->n_slots, 1) * g * 2 * 4);
     const int maps = mixed ? 2 : 1;
     const int64_t o_it = o_lam + (lam ? up(maps * n * 8) : 0);
     const int64_t total = o_it + (iters ? up(maps * n * 4) : 0);
@@ -1276,7 +1310,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     if (n > 0) {
       // one launch: the tables out of pinned memory, what the block keeps of the pass's scratch, the words that start at
       // zero (the pack kernels write every byte of the arena)
-      const int64_t plan_b = static_cast<int64_t>(n1) * 22 * 8, tables_b = ik_b + n_chunks * static_cast<int64_t>(sizeof(Chunk));
+      const int64_t plan_b = static_cast<int64_t>(n1) * 22 * 8, tables_b = ik_b + n_table * static_cast<int64_t>(sizeof(Chunk));
       if (c->k_per_unit) {
         d_krange = tmp.get<uint32_t>(n * kHeadDim * 2);
         if (!d_krange) return bail(fail(RDKV_ERR_ALLOC, "device allocation failed"));
@@ -1290,11 +1324,20 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       std::memcpy(plan + n1 * 20, c->counts.data(), n * 4 * sizeof(int32_t));
       uint8_t* tables = r.data + plan_b;
       if (mixed) std::memcpy(tables, c->items_k.data(), n * sizeof(ItemK));
-      if (n_chunks > 0) std::memcpy(tables + ik_b, c->chunks.data(), n_chunks * sizeof(Chunk));
+      {   // [launched chunks | merging workgroups | continuation pieces]
+        Chunk* t = reinterpret_cast<Chunk*>(tables + ik_b);
+        const int64_t launched = n_chunks - c->n_cont;
+        std::copy(c->chunks.begin(), c->chunks.begin() + launched, t);
+        std::copy(mergers.begin(), mergers.end(), t + launched);
+        std::copy(c->chunks.begin() + launched, c->chunks.end(), t + launched + c->n_merge);
+        for (int64_t k = 0; k < n_table; ++k)
+          if (t[k].next >= 0) t[k].next += static_cast<int32_t>(c->n_merge);
+      }
       CopyArgs a{};
       a.add(plan, d_idx_base, plan_b, kSrcHost);
       a.add(tables, c->d_block + o_ik, tables_b, kSrcHost);
       a.fill(c->d_block + o_state, o_idx - o_state, 0u, 0u);     // appended tokens, arrival counters
+      if (c->n_merge > 0) a.fill(c->d_block + o_acc, o_ml - o_acc, merge::kAbsent, merge::kAbsent);
       a.add(bits_tok, c->d_bits_tok, it.total_tokens);
       if (mixed) a.add(bits_ch, c->d_bits_ch, n * kHeadDim);
       if (lam) a.add(lam, c->d_block + o_lam, maps * n * 8);
@@ -1613,8 +1656,8 @@ static size_t cache_max_bytes(const rdkv_config* cfg) {
 }
 
 // The same for everything else in the cache's block: kept positions (4 bytes each), the bit maps, the K row layouts,
-// the chunk table and the first split workspace (at most two rounds of chunks and four per item, 80 bytes and
-// g x 130 floats each), lambda and step counts, and the alignment of the parts.
+// the chunk table and the first split workspace (at most two rounds of chunks and four per item, g x 162 floats each, and
+// the merging workgroups), lambda and step counts, and the alignment of the parts.
 static size_t cache_max_table_bytes(const rdkv_config* cfg) {
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
   const int g = cfg->hq / cfg->hkv;
@@ -1631,7 +1674,8 @@ static size_t cache_max_table_bytes(const rdkv_config* cfg) {
   const double items = static_cast<double>(cfg->batch) * cfg->hkv;
   const double chunks = 2.0 * 768.0 + 8.0 * items;
   return static_cast<size_t>(4.0 * kept + tokens + items * (kHeadDim + sizeof(ItemK) + 8 + 2 * 12) +
-                             chunks * (sizeof(Chunk) + g * (kHeadDim + 2) * 4.0) + 16.0 * 256);
+                             chunks * (sizeof(Chunk) + g * (merge::kRecordFloats + 2) * 4.0) + std::max(128.0, 2.0 * items) * sizeof(Chunk) +
+                             16.0 * 256);
 }
 
 size_t rdkv_cache_max_bytes(const rdkv_config* cfg) {
@@ -1644,6 +1688,18 @@ size_t rdkv_cache_max_table_bytes(const rdkv_config* cfg) {
   return cache_max_table_bytes(cfg);
 }
 
+// Wavefronts per workgroup of a channel-wise schedule whose longest K row over all generations has sched_k_words words
+// (0: there is one generation).
+static int sched_mixed_waves(const rdkv_cache* c, int32_t sched_k_words) {
+  return std::max(c->max_k_words, sched_k_words) <= 32 && c->hq / c->hkv <= 4 ? c->mixed_waves : 4;
+}
+// Some workgroup of a token-wise schedule goes through more than one tier of its item.
+static bool sched_multi(const rdkv_cache* c) {
+  bool multi = c->n_cont > 0;
+  for (const rdkv_cache* child : c->absorbed) multi = multi || child->n_cont > 0;
+  return multi;
+}
+
 rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, float* lse, void* stream) {
   if (!c) return fail(RDKV_ERR_INVALID_ARG, "cache must not be null");
   if (c->n_items == 0) return RDKV_OK;       // nothing to compute (and q / out of an empty batch may be null)
@@ -1652,30 +1708,29 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
   rdkv_cache::Workspace w;
   const rdkv_status ws = workspace_for(c, st, &w);
   if (ws != RDKV_OK) return ws;
-  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, c->hq / c->hkv};
+  const int g = c->hq / c->hkv;
+  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, g, merge_parts(g, c->n_items)};
   // every chunk of the schedule is launched, the tail's included: chunks of tail rows that do not exist yet find
   // the current length in the cache's device word and contribute an empty partial
   const int n16 = static_cast<int>(c->sched16), nrest = static_cast<int>(c->schedq + c->n_tail_chunks);
+  const int n_merge = static_cast<int>(c->n_merge);
   TimedScope ts(RDKV_TIME_DECODE_TIERED, st);
   if (c->k_mode == RDKV_K_CHANNELWISE) {
-    RDKV_HIP(launch_decode_mixed(c->d_chunks, n16 + nrest, c->d_arena, c->d_items_sched ? c->d_items_sched : c->d_items_k,
+    RDKV_HIP(launch_decode_mixed(c->d_chunks, n16 + nrest + n_merge, c->d_arena, c->d_items_sched ? c->d_items_sched : c->d_items_k,
                                  std::max(c->max_k_words, c->sched_k_words), std::max(c->max_k_steps, c->sched_k_steps),
                                  std::max(c->max_k_qsteps, c->sched_k_qsteps), static_cast<const uint16_t*>(q), ma,
-                                 c->d_tail_len, c->k_per_unit,
-                                 std::max(c->max_k_words, c->sched_k_words) <= 32 && c->hq / c->hkv <= 4 ? c->mixed_waves : 4,
-                                 st));
+                                 c->d_tail_len, c->k_per_unit, sched_mixed_waves(c, c->sched_k_words), st));
     return RDKV_OK;
   }
-  bool multi = c->n_cont > 0;      // some workgroup goes through more than one tier of its item
-  for (const rdkv_cache* child : c->absorbed) multi = multi || child->n_cont > 0;
+  const bool multi = sched_multi(c);
   const uint16_t* qp = static_cast<const uint16_t*>(q);
-  if (n16 > 0 && decode_tiles_take_rows(n16 + nrest, multi)) {     // one launch for all tiers
-    RDKV_HIP(launch_decode_tiles(c->d_chunks, 0, n16 + nrest, true, multi, c->d_arena, qp, ma, c->d_tail_len, st));
+  if (decode_tiles_take_rows(n16 + nrest, multi)) {     // one launch for all tiers
+    RDKV_HIP(launch_decode_tiles(c->d_chunks, 0, n16 + nrest, n_merge, n16 > 0, multi, c->d_arena, qp, ma, c->d_tail_len, st));
     return RDKV_OK;
   }
   // the workgroups of both kernels announce themselves on the same counters: whichever finishes an item merges it
   RDKV_HIP(launch_decode_tiered_split(c->d_chunks, n16, c->d_arena, qp, ma, st));
-  RDKV_HIP(launch_decode_tiles(c->d_chunks, n16, nrest, false, multi, c->d_arena, qp, ma, c->d_tail_len, st));
+  RDKV_HIP(launch_decode_tiles(c->d_chunks, n16, nrest, -1, false, multi, c->d_arena, qp, ma, c->d_tail_len, st));
   return RDKV_OK;
 }
 
@@ -1705,7 +1760,8 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
     n_slots += nc[i];
   }
   // table = [16-bit chunks of every generation | launched quantized chunks of every generation | tail chunks |
-  //          continuation pieces of every generation]; a generation's own vector is [16-bit | launched | continuations]
+  //          merging workgroups | continuation pieces of every generation];
+  // a generation's own vector is [16-bit | launched | continuations]
   int64_t n_cont_total = 0;
   std::vector<int64_t> cont_off(gens.size());
   for (size_t k = 0; k < gens.size(); ++k) {
@@ -1713,7 +1769,23 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
     cont_off[k] = n_cont_total;
     n_cont_total += gens[k]->n_cont;
   }
-  const int64_t cont_base = n_gen_chunks + n * npi;      // where the continuation pieces start in the new table
+  // channel-wise K: every (generation, item) has its own sorted-channel row layout
+  const bool mixed = c->k_mode == RDKV_K_CHANNELWISE;
+  std::vector<ItemK> items_sched;
+  int32_t kw = 0, ks = 0, kq = 0;
+  if (mixed && gens.size() > 1) {
+    for (const rdkv_cache* gc : gens) {
+      items_sched.insert(items_sched.end(), gc->items_k.begin(), gc->items_k.end());
+      kw = std::max(kw, gc->max_k_words);
+      ks = std::max(ks, gc->max_k_steps);
+      kq = std::max(kq, gc->max_k_qsteps);
+    }
+  }
+  std::vector<Chunk> mergers;      // where the decode kernel looks for partials
+  if (mixed ? sched_mixed_waves(c, kw) == 8 : decode_tiles_take_rows(static_cast<int>(n_gen_chunks + n * npi), sched_multi(c)))
+    mergers = merge_chunks(nb, nc, n, c->hq / c->hkv);
+  const int64_t n_merge = static_cast<int64_t>(mergers.size());
+  const int64_t cont_base = n_gen_chunks + n * npi + n_merge;      // where the continuation pieces start in the new table
   std::vector<Chunk> table;
   table.reserve(static_cast<size_t>(cont_base + n_cont_total));
   std::vector<Chunk> own = c->chunks;   // this cache's chunks with their new slot numbers
@@ -1762,6 +1834,7 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
       ch.next = -1;
       table.push_back(ch);
     }
+  table.insert(table.end(), mergers.begin(), mergers.end());
   for (size_t k = 0; k < gens.size(); ++k) {
     const rdkv_cache* gc = gens[k];
     for (size_t j = gc->chunks.size() - static_cast<size_t>(gc->n_cont); j < gc->chunks.size(); ++j)
@@ -1773,18 +1846,8 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
   stamp_slots(table, nb, nc);
   stamp_slots(own, nb, nc);
   const int64_t n_table = static_cast<int64_t>(table.size());
-  // channel-wise K: every (generation, item) has its own sorted-channel row layout
-  const bool mixed = c->k_mode == RDKV_K_CHANNELWISE;
-  std::vector<ItemK> items_sched;
   ItemK* d_items_sched = nullptr;
-  int32_t kw = 0, ks = 0, kq = 0;
-  if (mixed && gens.size() > 1) {
-    for (const rdkv_cache* gc : gens) {
-      items_sched.insert(items_sched.end(), gc->items_k.begin(), gc->items_k.end());
-      kw = std::max(kw, gc->max_k_words);
-      ks = std::max(ks, gc->max_k_steps);
-      kq = std::max(kq, gc->max_k_qsteps);
-    }
+  if (!items_sched.empty()) {
     d_items_sched = static_cast<ItemK*>(al.get(items_sched.size() * sizeof(ItemK)));
     if (!d_items_sched) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   }
@@ -1794,9 +1857,9 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
     return fail(RDKV_ERR_ALLOC, "device allocation failed");
   }
   rdkv_cache::Workspace w;   // this stream's workspace right away: a decode under graph capture then allocates nothing
-  size_t arrive_bytes = 0;
-  const bool have_w = make_workspace(c, st, n_slots, &w, &arrive_bytes);   // (a failure is reported by the decode call that needs it)
-  // tables up, counters and the caller's memory cleared in one launch; the stream must be idle before the old tables and
+  size_t absent = 0, arrive = 0;
+  const bool have_w = make_workspace(c, st, n_slots, &w, &absent, &arrive);   // (a failure is reported by the decode call that needs it)
+  // tables up, the workspace and the caller's memory set in one launch; the stream must be idle before the old tables and
   // workspaces go: a decode step may still be reading them
   const size_t table_b = table.size() * sizeof(Chunk), items_b = items_sched.size() * sizeof(ItemK);
   StageRegion r;
@@ -1809,7 +1872,8 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
     a.add(r.data, d_chunks, static_cast<int64_t>(table_b), kSrcHost);
     a.add(r.data + table_b, d_items_sched, static_cast<int64_t>(items_b), kSrcHost);
     a.fill(clear, clear_bytes, 0u, 0u);
-    if (have_w) a.fill(w.arrive, static_cast<int64_t>(arrive_bytes), 0u, 0u);
+    if (have_w) a.fill(w.arrive, static_cast<int64_t>(arrive), 0u, 0u);
+    if (have_w && n_merge > 0) a.fill(w.block, static_cast<int64_t>(absent), merge::kAbsent, merge::kAbsent);
     e = stage_launch(a, r, true, st);
   }
   if (e == hipSuccess) e = stage_stream_idle(st);
@@ -1833,6 +1897,7 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
   c->sched16 = n16;
   c->schedq = n_gen_chunks - n16;
   c->n_tail_chunks = n * npi;
+  c->n_merge = n_merge;
   c->chunks.swap(own);
   c->slot_begin.swap(nb);
   c->slot_count.swap(nc);

@@ -29,11 +29,12 @@ __host__ __device__ inline int tier_meta_bytes(int bits) { return bits == 16 ? 0
 struct Chunk {
   int64_t k_data, k_meta, v_data, v_meta;   // byte offsets into the arena
   int32_t rows;                             // valid rows in this chunk
-  int32_t tier;                             // 16, 8, 4, 2
+  int32_t tier;                             // 16, 8, 4, 2, kTierTail, kTierMerge
   int32_t item;                             // sequence * hkv + kv head
   int32_t slot;                             // partial-result slot
   int16_t k_word_end[4];                    // mixed mode: ItemK::word_end of the item (the shape of its K rows)
-  int32_t row0;                             // appended-token zone: first row of the chunk inside the item's tail
+  int32_t row0;                             // appended-token zone: first row of the chunk inside the item's tail;
+                                            // kTierMerge: which part of the item's query heads
   int32_t reserved;                         // mixed mode: index of the chunk's ItemK in the schedule's table
                                             // (generation * items + item)
   int32_t slot0, nslots;                    // the item's first partial slot and its number of slots (= chunks)
@@ -43,6 +44,7 @@ struct Chunk {
 };
 constexpr int kTailChunkRows = 256;         // appended tokens per decode work item
 constexpr int kTierTail = 17;               // Chunk::tier of a chunk of appended tokens (64-token tiles of bf16 rows)
+constexpr int kTierMerge = 18;              // Chunk::tier of a workgroup that merges an item's partials (decode_merge.h)
 
 // Channel-wise K (mixed mode): how one item's K tiles are laid out.  Channels are sorted by bit-width into
 // slots: tiers 16, 8, 4, 2 in this order.  A retained token's K row is a run of 32-bit words (a 16-bit word holds
@@ -81,6 +83,7 @@ inline hipError_t allow_lds(K kernel, size_t lds, std::atomic<uint64_t>* asked) 
   }()
 
 // One launch of small copies (copy_kernels.hip).  Segments with a side in staging memory are added first.
+constexpr int kCopySegs = 9;
 constexpr int kStageWords = 16;        // completion words at the head of a staging region
 enum : int32_t { kSrcHost = 1, kDstHost = 2 };
 struct CopySeg {
@@ -92,11 +95,11 @@ struct CopySeg {
 };
 struct CopyArgs {
   int32_t n;
-  int32_t first[9];                    // first workgroup of a segment (plan_copy)
+  int32_t first[kCopySegs + 1];        // first workgroup of a segment (plan_copy)
   uint32_t* words;                     // completion words of the staging region, or null
   uint32_t seq;
   int32_t host_blocks;                 // workgroups that set a word (plan_copy)
-  CopySeg seg[8];
+  CopySeg seg[kCopySegs];
   void add(const void* src, void* dst, int64_t bytes, int32_t side = 0) {
     if (bytes > 0) seg[n++] = CopySeg{src, dst, bytes, {0u, 0u}, side};
   }
@@ -136,10 +139,12 @@ hipError_t launch_gather_tail_rows(const uint8_t* tail, int64_t n_items, int32_t
                                    uint16_t* k_rows, uint16_t* v_rows, hipStream_t st);
 
 // chunks: the whole chunk table; workgroup b starts with chunks[first + b] and, if `multi`, follows Chunk::next.
+// n_merge >= 0: the partials are looked for by the n_merge entries of tier kTierMerge behind the n_chunks, and the range may
+// start with chunks of the 16-bit tier (rows16), both only where decode_tiles_take_rows says so; -1: arrivals are counted.
 // tail_len: device word holding the appended tokens that exist so far (chunks of tier kTierTail end there)
 bool decode_tiles_take_rows(int n_chunks, bool multi);
-hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, bool rows16, bool multi, const uint8_t* arena,
-                               const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, hipStream_t st);
+hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, int n_merge, bool rows16, bool multi,
+                               const uint8_t* arena, const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, hipStream_t st);
 // one object per head-set count (hs1: up to 4 query heads per KV head, hs2: 8)
 // One object per head-set count (hs1: up to 4 query heads per KV head, hs2: 8) and row length class (long0: K rows
 // of up to 32 words, long1: up to 68).  waves: wavefronts per workgroup, 4 or 8 (8 only in hs1 / long0).
@@ -191,8 +196,7 @@ struct rdkv_cache {
   uint8_t* d_arena = nullptr;
   int32_t* d_tier_idx = nullptr;        // [kept_total]
   rdkv::Chunk* d_chunks = nullptr;
-  // split workspaces, one per stream that has decoded from this cache: partial results [slots][g][128 + 2] floats and
-  // the items' arrival counters (zero between steps)
+  // split workspaces, one per stream that has decoded from this cache: partial results (decode_merge.h) and the items' arrival counters (zero between steps)
   struct Workspace {
     hipStream_t stream;
     float* part_acc;
@@ -214,6 +218,8 @@ struct rdkv_cache {
   // for V, in one allocation (zero-filled: rows not yet appended read as zeros)
   std::vector<int32_t> slot_begin, slot_count;   // host copies of the partial-slot tables
   uint8_t* d_tail = nullptr;
+  int64_t n_merge = 0;                  // merging workgroups of the schedule, behind the launched chunks in d_chunks: none
+                                        // where the decode kernel counts arrivals (decode_merge.h)
   int64_t n_tail_chunks = 0;            // chunks of the tail, appended to d_chunks in (chunk index, item) order:
                                         // the first ceil(tail_len / 256) * items of them are live
   int32_t tail_cap = 0, tail_len = 0;

@@ -28,6 +28,43 @@ __device__ __forceinline__ float halves_sum(float a, float b) {
   const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float(v[0]) + __uint_as_float(v[1]);
 }
+// maximum and sum over the 16 lanes of a row, in each of them
+__device__ __forceinline__ float row_max(float v) {
+  v = fmaxf(v, dpp_f32<0x128>(v));   // row_ror:8
+  v = fmaxf(v, dpp_f32<0x124>(v));
+  v = fmaxf(v, dpp_f32<0x122>(v));
+  return fmaxf(v, dpp_f32<0x121>(v));
+}
+__device__ __forceinline__ float row_sum(float v) {
+  v += dpp_f32<0x128>(v);
+  v += dpp_f32<0x124>(v);
+  v += dpp_f32<0x122>(v);
+  return v + dpp_f32<0x121>(v);
+}
+__device__ __forceinline__ float sum_xor16(float v) {
+  float o = v;
+  swap_rows(v, o);
+  return v + o;
+}
+// Reduction over the 16 lanes that hold the same head (lane % 4): lanes 4 apart inside a row of 16, then the rows.  No
+// step goes through LDS: with two or three wavefronts per SIMD nothing covers the 100 cycles of a ds_bpermute (a chunk's
+// five sums took 0.65 us).
+__device__ __forceinline__ float head_max(float v) {
+  v = fmaxf(v, dpp_f32<0x124>(v));   // row_ror:4
+  v = fmaxf(v, dpp_f32<0x128>(v));   // row_ror:8
+  float o = v;
+  swap_rows(v, o);
+  o = v = fmaxf(v, o);
+  swap_halves(v, o);
+  return fmaxf(v, o);
+}
+__device__ __forceinline__ float head_sum(float v) {
+  v += dpp_f32<0x124>(v);
+  v += dpp_f32<0x128>(v);
+  float o = v = sum_xor16(v);
+  swap_halves(v, o);
+  return v + o;
+}
 // v of the lane CTRL names, 0 where there is none (rows outside the row mask ROWS included)
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t lanes_below(uint32_t v) {

@@ -1,0 +1,57 @@
+"""The merging workgroups of small decode launches: slots per item on both sides of a batch of loads, every number of blocks
+per wavefront (which follows the number of items and of query heads), channel-wise keys, and a workspace that every step leaves
+as it found it."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import rdkv_oracle as O
+from paper_2605_08317_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(b, seq_lens, hkv, g, widths, mixed=False):
+    wl = W.scaled(W.CONFIGS["tiny"], batch=len(seq_lens), seq_lens=tuple(seq_lens), hq=g * hkv, hkv=hkv)
+    inp = W.make_inputs(wl, device="cpu")
+    rng = np.random.default_rng(sum(seq_lens) + g)
+    bits = [rng.choice(np.asarray(widths, np.uint8), size=(hkv, T)) for T in seq_lens]
+    bits_ch = [rng.choice(np.asarray([2, 4], np.uint8), size=(hkv, 128)) for _ in seq_lens] if mixed else None
+    flat = lambda m: torch.from_numpy(np.concatenate([x.reshape(-1) for x in m])).cuda()
+    cfg = b.Config(seq_lens, wl.hq, hkv, budget_bits=[2.0] * len(seq_lens), s_obs=wl.s_obs,
+                   k_mode=b.RDKV_K_CHANNELWISE if mixed else b.RDKV_K_TOKENWISE)
+    cache = b.rdkv_pack(cfg, inp["K"].cuda(), inp["V"].cuda(), flat(bits), flat(bits_ch) if mixed else None)
+    print(f"[case] {len(seq_lens)} x {hkv} items, g {g}, {cache.stats()['n_chunks']} chunks", flush=True)
+    q = inp["q"].cuda()
+    out, lse = b.rdkv_decode_attn(cache, q)
+    for _ in range(3):
+        again, again_lse = b.rdkv_decode_attn(cache, q)
+        assert torch.equal(again, out) and torch.equal(again_lse, lse)
+    split = lambda x: [y.float().numpy() for y in W.split_sequences(x, seq_lens, hkv, 128)]
+    build = O.build_cache_mixed if mixed else O.build_cache_tokenwise
+    ref_out, ref_lse = O.decode(build(split(inp["K"]), split(inp["V"]), bits, *([bits_ch] if mixed else [])), inp["q"].float().numpy())
+    err = np.abs(out.cpu().numpy() - ref_out).max(-1) / np.abs(ref_out).max(-1)
+    assert err.max() <= 2e-3          # as in the other decode tests: fp16 products of probability and scale
+    np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, rtol=1e-4, atol=1e-4)
+    cache.free()
+
+
+@pytest.mark.parametrize("T", [513, 4096, 4097, 8449, 30000, 150001])
+@pytest.mark.parametrize("g", [1, 4, 8])
+def test_slots_of_one_item(T, g):
+    from paper_2605_08317_amd import binding as b
+    _check(b, [T], 1, g, [2])
+
+
+@pytest.mark.parametrize("batch,hkv", [(1, 3), (2, 8), (17, 2), (33, 1), (9, 8), (25, 4)])
+@pytest.mark.parametrize("g", [1, 2, 4, 8])
+def test_numbers_of_items(batch, hkv, g):
+    from paper_2605_08317_amd import binding as b
+    _check(b, [700 - 3 * s for s in range(batch)], hkv, g, [8, 2])
+
+
+@pytest.mark.parametrize("T", [600, 9001])
+@pytest.mark.parametrize("g", [2, 4])
+def test_channelwise(T, g):
+    from paper_2605_08317_amd import binding as b
+    _check(b, [T], 2, g, [8, 4, 2, 0], mixed=True)

@@ -178,40 +178,56 @@ struct TileOf {
 // correctly rounded as the theorem asks; tests/test_quotient.py finds the IEEE quotient all the same for every fp16 s and
 // all three y, at 128 million numerators around the half-integers and of differences of bf16 numbers.  A group with a scale
 // or offset that is not finite takes the division.
+// The scale's division by the largest code Q goes the same way with the correctly rounded 1 / Q, which is the theorem's case.
 struct Quant {
   float m, s, y;
   _Float16 sh, mh;
   bool finite;
-  template <int BITS>
-  __device__ __forceinline__ void set(float mn, float mx) { set(mn, mx, static_cast<float>((1 << BITS) - 1)); }
-  __device__ __forceinline__ void set(float mn, float mx, float Q) {       // Q: the largest code
+  // Q: the largest code, inv_q: 1 / Q; EXACT: by division
+  template <bool EXACT = false>
+  __device__ __forceinline__ void set(float mn, float mx, float Q, float inv_q) {
     mn = mn + 0.0f;            // canonical +0
-    sh = static_cast<_Float16>((mx - mn) / Q);   // round to nearest even
+    const float range = mx - mn;
+    float q;
+    if constexpr (EXACT) {
+      q = range / Q;
+    } else {
+      const float q0 = range * inv_q;
+      q = __builtin_fmaf(__builtin_fmaf(-q0, Q, range), inv_q, q0);
+      q = __builtin_copysignf(q, range);         // (-0 of a group of -0)
+      asm("" : "+v"(q));       // rounded to fp32 before it is rounded to fp16 (else one instruction does both)
+    }
+    sh = static_cast<_Float16>(q);               // round to nearest even
     mh = static_cast<_Float16>(mn);
     s = static_cast<float>(sh);
     m = static_cast<float>(mh);
     finite = fabsf(s) < INFINITY && fabsf(m) < INFINITY;     // (false for NaN)
     y = s == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(s);
   }
-  // the code as a float; EXACT: by division
-  template <int BITS, bool EXACT>
-  __device__ __forceinline__ float code(float x) const { return code<EXACT>(x, static_cast<float>((1 << BITS) - 1)); }
+  // The code: the low 16 bits of what comes back (rounded to an integer by the addition of 1.5 x 2^23, whose low half is
+  // zero; clamped before, which is the same as after).  EXACT: by division
   template <bool EXACT>
-  __device__ __forceinline__ float code(float x, float Q) const {
+  __device__ __forceinline__ uint32_t code(float x, float Q) const {
     const float d = x - m;
     float q;
     if constexpr (EXACT) {
       q = d / s;
-    } else {
+    } else {                   // (with a finite s = 0: y = 0, q = 0)
       const float q0 = d * y;
       q = __builtin_fmaf(__builtin_fmaf(-q0, s, d), y, q0);
     }
-    const float t = fminf(fmaxf(rintf(q), 0.0f), Q);
-    return EXACT && s == 0.0f ? 0.0f : t;        // (with a finite s = 0: y = 0, q = 0)
+    const float t = fminf(fmaxf(q, 0.0f), Q);
+    return __float_as_uint((EXACT && s == 0.0f ? 0.0f : t) + 12582912.0f);
   }
 };
+// two codes as the halves of a word; four as its bytes, one after the other
+__device__ __forceinline__ uint32_t code_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x05040100u); }
+template <int I>
+__device__ __forceinline__ uint32_t code_byte(uint32_t word, uint32_t code) {      // code in byte I, zeros above it
+  return __builtin_amdgcn_perm(code, word, I == 1 ? 0x0C0C0400u : I == 2 ? 0x0C040100u : 0x04020100u);
+}
 
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kRowMirror = 0x140;
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;
 
 __device__ __forceinline__ void unpack8(const uint4& v, float (&x)[8]) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -222,31 +238,44 @@ __device__ __forceinline__ void unpack8(const uint4& v, float (&x)[8]) {
   }
 }
 
+// Minimum and maximum over a quad of lanes, over rows of 16.  (A minimum that reads another lane is one instruction; out of
+// fminf the compiler makes three, because it cannot tell that what comes from another lane is no signalling NaN.  Two wait
+// states stand between a write to a register and its use by another lane.)
+__device__ __forceinline__ void quad_range(float& mn, float& mx) {
+  asm("s_nop 1\n\t"
+      "v_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+      : "+v"(mn), "+v"(mx));
+}
+__device__ __forceinline__ void row_range(float& mn, float& mx) {      // after quad_range
+  asm("s_nop 1\n\t"
+      "v_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf"
+      : "+v"(mn), "+v"(mx));
+}
+
 // Quantizes the 8 channels this lane holds of a token row (the 16 lanes of a row hold it in order, four lanes a group of
-// 32 channels); codes as floats.
-template <int BITS>
-__device__ __forceinline__ void quantize_row(const uint4& raw, int row_wide, Quant& g, float (&c)[8]) {
+// 32 channels); codes as Quant::code gives them.
+template <int BITS, bool EXACT>
+__device__ __forceinline__ void quantize_row(const uint4& raw, int row_wide, Quant& g, uint32_t (&c)[8]) {
+  constexpr float kMost = static_cast<float>((1 << BITS) - 1), kInvMost = 1.0f / kMost;
   float x[8];
   unpack8(raw, x);
   float mn = fminf(fminf(fminf(x[0], x[1]), fminf(x[2], x[3])), fminf(fminf(x[4], x[5]), fminf(x[6], x[7])));
   float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-  mn = fminf(mn, dpp_f32<kQuadXor1>(mn));
-  mx = fmaxf(mx, dpp_f32<kQuadXor1>(mx));
-  mn = fminf(mn, dpp_f32<kQuadXor2>(mn));
-  mx = fmaxf(mx, dpp_f32<kQuadXor2>(mx));
-  if (row_wide) {
-    mn = fminf(mn, dpp_f32<kHalfMirror>(mn));
-    mx = fmaxf(mx, dpp_f32<kHalfMirror>(mx));
-    mn = fminf(mn, dpp_f32<kRowMirror>(mn));
-    mx = fmaxf(mx, dpp_f32<kRowMirror>(mx));
-  }
-  g.set<BITS>(mn, mx);
-  if (__all(g.finite)) {
+  quad_range(mn, mx);
+  if (row_wide) row_range(mn, mx);
+  g.set<EXACT>(mn, mx, kMost, kInvMost);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) c[j] = g.code<BITS, false>(x[j]);
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) c[j] = g.code<BITS, true>(x[j]);
+  for (int j = 0; j < 8; ++j) {
+    if constexpr (EXACT) __builtin_amdgcn_sched_barrier(0);      // (eight divisions side by side take 40 registers)
+    c[j] = g.code<EXACT>(x[j], kMost);
   }
 }
 
@@ -258,14 +287,17 @@ __device__ __forceinline__ void quantize_row(const uint4& raw, int row_wide, Qua
 //   V: lane = 32*(r/32) + c % 32; group = c / 32; r % 32 = 4*step + k   (a lane holds one channel for 32 tokens)
 // Metadata tile = 1024 bytes: K row-major per token [4 scales][4 offsets]; V per block of 4 tokens 4 groups x 16
 // bytes: the group's scales of the 4 tokens, then its offsets.
-// K words: this lane's two steps of its group; the lanes of a group OR their fields together.
+// K words: this lane's two steps of its group; the lanes of a group OR their fields together.  dst: k_words_at of the row's
+// tile, plus 16 bytes per row.
 template <int BITS>
-__device__ __forceinline__ void store_k_words(const float (&c)[8], uint8_t* tile, int r, int grp, int p) {
-  constexpr float kField = static_cast<float>(1 << BITS);
+__device__ __forceinline__ int k_words_at(int grp, int p) {
+  const int W = BITS * grp + (BITS == 8 ? 2 * p : BITS == 4 ? (p & 2) : 0);
+  return 1024 * (W >> 2) + 4 * (W & 3);
+}
+template <int BITS>
+__device__ __forceinline__ void store_k_words(const uint32_t (&c)[8], uint8_t* dst, int p) {
   const auto word = [&](int k) __attribute__((always_inline)) {     // codes k, k + 1 of steps 2 p and 2 p + 1
-    const uint32_t lo = static_cast<uint32_t>(__builtin_fmaf(c[4 + k], kField, c[k]));
-    const uint32_t hi = static_cast<uint32_t>(__builtin_fmaf(c[5 + k], kField, c[k + 1]));
-    return lo | (hi << 16);
+    return code_halves(c[k], c[k + 1]) | (code_halves(c[4 + k], c[5 + k]) << BITS);
   };
   uint2 w = make_uint2(word(0), word(2));
   if constexpr (BITS == 4) {               // fields 2 (p % 2), 2 (p % 2) + 1 of word pair p / 2
@@ -283,9 +315,7 @@ __device__ __forceinline__ void store_k_words(const float (&c)[8], uint8_t* tile
     w.x |= dpp_u32<kQuadXor2>(w.x);
     w.y |= dpp_u32<kQuadXor2>(w.y);
   }
-  const int W = BITS * grp + (BITS == 8 ? 2 * p : BITS == 4 ? (p & 2) : 0);
-  if (BITS == 8 || (BITS == 4 && (p & 1) == 0) || (BITS == 2 && p == 0))
-    *reinterpret_cast<uint2*>(tile + 1024 * (W >> 2) + 16 * r + 4 * (W & 3)) = w;
+  if (BITS == 8 || (BITS == 4 && (p & 1) == 0) || (BITS == 2 && p == 0)) *reinterpret_cast<uint2*>(dst) = w;
 }
 
 // V codes go through LDS: s_vc[channel][token] bytes, 68 bytes per channel (four tokens of a channel are one word of a
@@ -318,11 +348,13 @@ __device__ __forceinline__ void store_v_words(const uint8_t* s_vc, uint8_t* tile
 // One workgroup = one tile of 64 kept rows of any tier, K and V (V_ONLY: V, K of a channel-wise cache is packed by
 // pack_k_mixed_kernel); rows past the segment's last are zero rows, so a tile is always written whole.  A wavefront gathers
 // 16 rows, 16 lanes a row (whole 256-byte rows per load), a lane the same 8 channels of four consecutive tokens, which is
-// what a step of the V layout takes; codes are made in registers and only V passes through LDS, as bytes.  Bound: HBM (the
-// gather); 128 items x 20K tokens, mostly 2- and 4-bit rows: 298 us in three launches and 24 us for clearing the arena
-// -> 219 us (1.2 GB, 5.5 TB/s); a 128K-token layer 37 + 5 -> 21 us.
+// what a step of the V layout takes; codes are made in registers and only V passes through LDS, as bytes.  Bound: HBM and
+// plain ALUs (the gather: 0.94 GB at 5.3 TB/s, half reads of whole rows; 14 instructions per element).  128 items x 20K
+// tokens, mostly 2- and 4-bit rows: 216 -> 172 us; a 128K-token layer 20.4 -> 16.6 us; V alone of 8 x 50K 17.3 -> 13.6.  Before,
+// positions were loaded row by row, codes were converted one by one, and the division path, inlined beside every row, took the
+// registers of a fifth workgroup.
 template <bool V_ONLY>
-__global__ __launch_bounds__(256) void pack_tile_kernel(PackArgs a) {
+__global__ __launch_bounds__(256, 5) void pack_tile_kernel(PackArgs a) {
   __shared__ __align__(16) uint8_t s_buf[kTile64 * (kHeadDim + 8) * 2];   // V codes, or bf16 V rows of the 16-bit tier
   __shared__ __align__(16) uint16_t s_km[kTile64][8];                     // K metadata
   const int item = blockIdx.y;
@@ -335,15 +367,28 @@ __global__ __launch_bounds__(256) void pack_tile_kernel(PackArgs a) {
   const int32_t* idx = a.tier_idx + a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kTile64;
   const int64_t item_row = a.item_row_off[item];
   uint4 kq[4], vq[4];
+  // All positions, then all rows, without a branch (with one per row every position was waited for behind the rows before
+  // it: four round trips instead of two).  Rows past the segment's last repeat it and become zeros.
+  const auto gather = [&](int first) __attribute__((always_inline)) {
+    int pos[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    kq[i] = vq[i] = make_uint4(0, 0, 0, 0);
-    if (row0 + i < valid) {
-      const int64_t src = (item_row + idx[row0 + i]) * kHeadDim + c16 * 8;
+    for (int i = 0; i < 4; ++i) pos[i] = idx[min(first + i, valid - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t src = (item_row + pos[i]) * kHeadDim + c16 * 8;
       if constexpr (!V_ONLY) kq[i] = *reinterpret_cast<const uint4*>(a.K + src);
       vq[i] = *reinterpret_cast<const uint4*>(a.V + src);
     }
-  }
+    if (valid < kTile64) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (first + i >= valid) {
+          if constexpr (!V_ONLY) kq[i] = make_uint4(0, 0, 0, 0);
+          vq[i] = make_uint4(0, 0, 0, 0);
+        }
+    }
+  };
+  gather(row0);
   const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + t.ti) * 4;
   const int bits = 16 >> t.ti;
   uint8_t* kd = a.arena + so[0] + static_cast<int64_t>(t.tile) * (kTile64 * kHeadDim / 8) * bits;
@@ -375,15 +420,21 @@ __global__ __launch_bounds__(256) void pack_tile_kernel(PackArgs a) {
   }
   uint8_t* km = a.arena + so[1] + static_cast<int64_t>(t.tile) * 1024;
   uint8_t* vm = a.arena + so[3] + static_cast<int64_t>(t.tile) * 1024;
-  const auto quantize = [&](auto bits_c) __attribute__((always_inline)) {
+  // this wavefront's rows; false: some group's scale or offset is not finite, and everything has to be done again by division
+  const auto quantize = [&](auto bits_c, auto exact_c) __attribute__((always_inline)) {
     constexpr int BITS = decltype(bits_c)::value;
+    constexpr bool kExact = decltype(exact_c)::value;
+    uint64_t odd = 0;
     if constexpr (!V_ONLY) {
+      uint8_t* kw = kd + k_words_at<BITS>(grp, p) + 16 * row0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         Quant g;
-        float c[8];
-        quantize_row<BITS>(kq[i], a.row_wide, g, c);
-        store_k_words<BITS>(c, kd, row0 + i, grp, p);
+        uint32_t c[8];
+        __builtin_amdgcn_sched_barrier(0);     // row by row: registers decide how many workgroups are resident
+        quantize_row<BITS, kExact>(kq[i], a.row_wide, g, c);
+        odd |= __builtin_amdgcn_ballot_w64(!g.finite);
+        store_k_words<BITS>(c, kw + 16 * i, p);
         if (p == 0) {
           s_km[row0 + i][grp] = __builtin_bit_cast(unsigned short, g.sh);
           s_km[row0 + i][4 + grp] = __builtin_bit_cast(unsigned short, g.mh);
@@ -391,30 +442,44 @@ __global__ __launch_bounds__(256) void pack_tile_kernel(PackArgs a) {
       }
     }
     uint32_t sc[4], of[4], packed[8];      // packed: the four tokens' codes of a channel, one byte each
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    const auto row = [&](auto ic) __attribute__((always_inline)) {
+      constexpr int I = decltype(ic)::value;
       Quant g;
-      float c[8];
-      quantize_row<BITS>(vq[i], a.row_wide, g, c);
-      sc[i] = __builtin_bit_cast(unsigned short, g.sh);
-      of[i] = __builtin_bit_cast(unsigned short, g.mh);
+      uint32_t c[8];
+      __builtin_amdgcn_sched_barrier(0);
+      quantize_row<BITS, kExact>(vq[I], a.row_wide, g, c);
+      odd |= __builtin_amdgcn_ballot_w64(!g.finite);
+      sc[I] = __builtin_bit_cast(unsigned short, g.sh);
+      of[I] = __builtin_bit_cast(unsigned short, g.mh);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const uint32_t u = static_cast<uint32_t>(c[j]);
-        packed[j] = i == 0 ? u : packed[j] | (u << (8 * i));
+        if constexpr (I == 0) packed[j] = c[j]; else packed[j] = code_byte<I>(packed[j], c[j]);
       }
-    }
+    };
+    row(std::integral_constant<int, 0>{});
+    row(std::integral_constant<int, 1>{});
+    row(std::integral_constant<int, 2>{});
+    row(std::integral_constant<int, 3>{});
 #pragma unroll
     for (int j = 0; j < 8; ++j) *reinterpret_cast<uint32_t*>(s_buf + (c16 * 8 + j) * kVcStride + row0) = packed[j];
     if (p == 0)                            // block row0 / 4 of the tile, group grp
       *reinterpret_cast<uint4*>(vm + 16 * row0 + 16 * grp) =
           make_uint4(sc[0] | (sc[1] << 16), sc[2] | (sc[3] << 16), of[0] | (of[1] << 16), of[2] | (of[3] << 16));
-    __syncthreads();
-    store_v_words<BITS>(s_buf, vd);
+    return odd == 0;
   };
-  if (t.ti == 1) quantize(std::integral_constant<int, 8>{});
-  else if (t.ti == 2) quantize(std::integral_constant<int, 4>{});
-  else quantize(std::integral_constant<int, 2>{});
+  const auto tile = [&](auto bits_c) __attribute__((always_inline)) {
+    if (!quantize(bits_c, std::false_type{})) {
+      int again = row0;
+      asm("" : "+v"(again));               // (or the addresses would be kept for it)
+      gather(again);
+      quantize(bits_c, std::true_type{});
+    }
+    __syncthreads();
+    store_v_words<decltype(bits_c)::value>(s_buf, vd);
+  };
+  if (t.ti == 1) tile(std::integral_constant<int, 8>{});
+  else if (t.ti == 2) tile(std::integral_constant<int, 4>{});
+  else tile(std::integral_constant<int, 2>{});
   if constexpr (!V_ONLY) {
     if (tid < kTile64) *reinterpret_cast<uint4*>(km + 16 * tid) = *reinterpret_cast<const uint4*>(&s_km[tid][0]);
   }
@@ -460,7 +525,8 @@ __global__ __launch_bounds__(256) void k_channel_range_kernel(PackArgs a) {
 // lane f ends with the word of token f: a transposition of F x F fields in log2 F steps within a row of 16 lanes.  Every
 // tier starts at a row of lanes.  The words are staged in LDS and leave in 16-byte pieces.  Bound: instruction
 // issue; 160K rows 40 -> 32 us (a word put together field by field, each a channel number and a code out of LDS; and one
-// code path per width, of which a wavefront with slots of three tiers took all three).
+// code path per width, of which a wavefront with slots of three tiers took all three) -> 30 (codes without conversions, all
+// positions loaded before the rows).
 // what lane ^ J holds (J = 1, 2, 4, 8, inside a row of 16)
 template <int J>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
@@ -493,7 +559,7 @@ __device__ __forceinline__ uint32_t transpose_fields(uint32_t v, int f) {
 }
 
 constexpr int kKThreads = 384;         // two token groups of at most 192 lanes
-__global__ __launch_bounds__(kKThreads) void pack_k_mixed_kernel(PackArgs a) {
+__global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) {
   constexpr int kRows = kTile64;
   constexpr int kRowStride = kHeadDim + 8;
   constexpr int kRowBytes = kRows * kRowStride * 2, kWordBytes = kRows * kMaxKRowWords * 4;
@@ -512,18 +578,19 @@ __global__ __launch_bounds__(kKThreads) void pack_k_mixed_kernel(PackArgs a) {
     const int64_t item_row = a.item_row_off[item];
     constexpr int kPieces = kRows * 16, kLoads = (kPieces + kKThreads - 1) / kKThreads;      // 16 bytes each
     uint4 v[kLoads];
+    int pos[kLoads];                     // all positions, then all rows (rows past the last repeat it and become zeros)
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const int p = i * kKThreads + tid, row = p >> 4;
-      v[i] = make_uint4(0, 0, 0, 0);
-      if (row < valid) v[i] = *reinterpret_cast<const uint4*>(a.K + (item_row + idx[row]) * kHeadDim + (p & 15) * 8);
-    }
+    for (int i = 0; i < kLoads; ++i) pos[i] = idx[min((i * kKThreads + tid) >> 4, valid - 1)];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)
+      v[i] = *reinterpret_cast<const uint4*>(a.K + (item_row + pos[i]) * kHeadDim + (tid & 15) * 8);
     for (int i = tid; i < static_cast<int>(sizeof(ItemK) / 4); i += kKThreads)
       reinterpret_cast<uint32_t*>(&s_ik)[i] = reinterpret_cast<const uint32_t*>(a.items_k + item)[i];
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int p = i * kKThreads + tid;
-      if (p < kPieces) *reinterpret_cast<uint4*>(s_rows + (p >> 4) * kRowStride + (p & 15) * 8) = v[i];
+      if (p < kPieces)
+        *reinterpret_cast<uint4*>(s_rows + (p >> 4) * kRowStride + (p & 15) * 8) = (p >> 4) < valid ? v[i] : make_uint4(0, 0, 0, 0);
     }
   }
   __syncthreads();
@@ -565,6 +632,7 @@ __global__ __launch_bounds__(kKThreads) void pack_k_mixed_kernel(PackArgs a) {
       uint16_t sc = 0, of = 0;
       if (vg > 0) {
         const float most = static_cast<float>((1 << (16 >> tier)) - 1);
+        const float inv_most = tier == 1 ? 1.0f / 255.0f : tier == 2 ? 1.0f / 15.0f : 1.0f / 3.0f;
         float mn, mx;
         if (a.k_range) {   // the range of the whole unit
           mn = ordered_to_float(a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2]);
@@ -587,13 +655,14 @@ __global__ __launch_bounds__(kKThreads) void pack_k_mixed_kernel(PackArgs a) {
           }
         }
         Quant g;
-        g.set(mn, mx, most);
+        g.set(mn, mx, most, inv_most);
         if (g.finite) {
 #pragma unroll
-          for (int r = 0; r < kKTokenGroup; ++r) x[r] = g.code<false>(x[r], most);
+          for (int r = 0; r < kKTokenGroup; ++r) x[r] = __uint_as_float(g.code<false>(x[r], most));
         } else {
+          g.set<true>(mn, mx, most, inv_most);
 #pragma unroll
-          for (int r = 0; r < kKTokenGroup; ++r) x[r] = g.code<true>(x[r], most);
+          for (int r = 0; r < kKTokenGroup; ++r) x[r] = __uint_as_float(g.code<true>(x[r], most));
         }
         if (vg < kKTokenGroup) {
 #pragma unroll
@@ -618,9 +687,10 @@ __global__ __launch_bounds__(kKThreads) void pack_k_mixed_kernel(PackArgs a) {
       if constexpr (B == 16) {
         v = (__float_as_uint(x[2 * q]) >> 16) | (__float_as_uint(x[2 * q + 1]) & 0xFFFF0000u);
       } else {
+        // codes F / 2 apart stand in the two halves of a word
 #pragma unroll
-        for (int i = 0; i < F; i += 2)   // two codes to a conversion
-          v |= static_cast<uint32_t>(__builtin_fmaf(x[q * F + i + 1], static_cast<float>(1 << B), x[q * F + i])) << (B * i);
+        for (int i = 0; i < F / 2; ++i)
+          v |= code_halves(__float_as_uint(x[q * F + i]), __float_as_uint(x[q * F + F / 2 + i])) << (B * i);
       }
       out[q] = transpose_fields<B>(v, f);
     }

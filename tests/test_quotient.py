@@ -3,7 +3,8 @@ reciprocal of the scale and one exact remainder, the scheme of P. W. Markstein, 
 IBM RISC System/6000 processor" (1990).  His theorem asks for a correctly rounded reciprocal; the hardware's is within one
 unit in the last place, so the result is compared with the IEEE quotient here: for every positive fp16 scale, with the
 correctly rounded reciprocal and both its neighbours, at the numerators where a code changes (half-integers times the scale,
-two numbers on either side) and at differences of bf16 numbers."""
+two numbers on either side) and at differences of bf16 numbers.  The scale's own quotient, a group's range by the largest code,
+goes the same way with the correctly rounded reciprocal: all numerators of two binades, and the sign of a zero."""
 import shutil
 import subprocess
 
@@ -14,6 +15,7 @@ PROGRAM = r"""
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 static float from_bits(uint32_t u) { float f; std::memcpy(&f, &u, 4); return f; }
 static float half_value(uint32_t h) {                 // positive, finite
   const int e = h >> 10, m = h & 1023;
@@ -42,6 +44,14 @@ int main() {
         const float d = from_bits([](float f) { uint32_t u; std::memcpy(&u, &f, 4); return u & 0xFFFF0000u; }(x)) - m;
         if (d >= 0.0f && d <= 256.0f * s) check(d, s, y);
       }
+    }
+  }
+  for (const float Q : {3.0f, 15.0f, 255.0f}) {
+    const float inv = 1.0f / Q;
+    for (uint32_t u = 0x3F800000u; u < 0x40800000u; ++u) check(from_bits(u), Q, inv);
+    for (const float zero : {0.0f, -0.0f}) {
+      const float q0 = zero * inv, q = std::copysign(std::fma(std::fma(-q0, Q, zero), inv, q0), zero), want = zero / Q;
+      bad += std::memcmp(&q, &want, 4) != 0;
     }
   }
   std::printf("%ld quotients, %ld differ\n", n, bad);

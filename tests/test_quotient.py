@@ -68,3 +68,10 @@ def test_quotient_from_reciprocal_and_remainder_is_the_ieee_quotient(tmp_path):
     p = subprocess.run([tmp_path / "quotient"], capture_output=True, text=True)
     print(p.stdout)
     assert p.returncode == 0, p.stdout
+
+
+def test_window_row_by_a_product_is_the_remainder():
+    """limit_of in weights_kernels.hip: row % s_obs from row * (65536 / s_obs + 1) / 65536, for every window length."""
+    for s in range(1, 65):
+        for row in range(768):
+            assert row - (row * (65536 // s + 1) >> 16) * s == row % s

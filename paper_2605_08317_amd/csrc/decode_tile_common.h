@@ -236,7 +236,7 @@ template <int HS>
 __device__ __forceinline__ void softmax_tile(const float (&x)[HS][4], Run<HS>& run, float (&p)[HS][4], float lk = 0.f) {
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) {
-    const float mt = head_max(fmaxf(fmaxf(x[hs][0], x[hs][1]), fmaxf(x[hs][2], x[hs][3])));
+    const float mt = head_max(max_of_four(x[hs][0], x[hs][1], x[hs][2], x[hs][3]));
     const float m_new = fmaxf(run.m[hs], mt);
     if (__any(m_new != run.m[hs])) {
       const float alpha = fast_exp2((run.m[hs] - m_new) * kXScale);

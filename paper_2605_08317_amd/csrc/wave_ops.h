@@ -49,14 +49,33 @@ __device__ __forceinline__ float sum_xor16(float v) {
 // Reduction over the 16 lanes that hold the same head (lane % 4): lanes 4 apart inside a row of 16, then the rows.  No
 // step goes through LDS: with two or three wavefronts per SIMD nothing covers the 100 cycles of a ds_bpermute (a chunk's
 // five sums took 0.65 us).
+// (A maximum that reads another lane is one instruction; out of fmaxf the compiler makes three, because it cannot tell that
+// what comes from another lane is no signalling NaN.  Two wait states stand between a write to a register and its use by
+// another lane.)  v: no signalling NaN
 __device__ __forceinline__ float head_max(float v) {
-  v = fmaxf(v, dpp_f32<0x124>(v));   // row_ror:4
-  v = fmaxf(v, dpp_f32<0x128>(v));   // row_ror:8
-  float o = v;
-  swap_rows(v, o);
-  o = v = fmaxf(v, o);
-  swap_halves(v, o);
-  return fmaxf(v, o);
+  float o;
+  asm("s_nop 1\n\t"
+      "v_max_f32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\t"
+      "v_max_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_mov_b32 %1, %0\n\t"
+      "s_nop 1\n\t"
+      "v_permlane16_swap_b32 %0, %1\n\t"
+      "s_nop 0\n\t"
+      "v_max_f32 %0, %0, %1\n\t"
+      "v_mov_b32 %1, %0\n\t"
+      "s_nop 1\n\t"
+      "v_permlane32_swap_b32 %0, %1\n\t"
+      "s_nop 0\n\t"
+      "v_max_f32 %0, %0, %1"
+      : "+v"(v), "=&v"(o));
+  return v;
+}
+// the larger of four, none a signalling NaN
+__device__ __forceinline__ float max_of_four(float a, float b, float c, float d) {
+  float m;
+  asm("v_max3_f32 %0, %1, %2, %3\n\tv_max_f32 %0, %0, %4" : "=&v"(m) : "v"(a), "v"(b), "v"(c), "v"(d));
+  return m;
 }
 __device__ __forceinline__ float head_sum(float v) {
   v += dpp_f32<0x124>(v);

@@ -1047,71 +1047,93 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     total_cost += item_cost[i];
     if (!mixed) cost16 += c->counts[i * 4] * row_cost(i, 16);
   }
-  // Small launches are bound by latencies, not bytes: the rounds of workgroups, the tiles that one SIMD goes through one
-  // after the other, and the partials of an item (arrivals queue on one counter, the merge reads them).  Rows per chunk of
-  // such a launch: the multiple of 256 (one tile per SIMD) with the least sum of the three, fitted to these times
-  // (microseconds per launch, caches cold; rows per item in parentheses, the rows per chunk chosen marked; "old": chunks of
-  // at least 96 KB, or 48):
-  //   16 MB layer, 40 % 8-bit rows (10000)   256: 12.5   512: 10.7*  768: 11.3   1024: 12.5               old: 11.1
-  //   12 MB layer, no 8-bit rows (13000)                 512: 11.6   768: 11.2*  1024: 11.6               old: 11.6
-  //   keep / 4 bit / evict (16000)                       512: 12.5   768: 11.4*  1024: 11.8               old: 11.8
-  //   2 items (3200)                         256:  7.2*  512:  7.8   768:  8.3   1024:  9.2               old:  9.2
-  //   8 query heads per KV head (13000)      256: 17.5   512: 14.6*  768: 14.6   1024: 15.2               old: 15.6
-  //   8 items (52000)                                    512: 25.1   768: 22.7   1024: 18.9  2048: 17.4*  old: 18.9
-  //   8 items (78000)                                    1024: 25.6  1536: 22.6  2048: 25.0  3072: 21.6*  old: 24.3
-  // Token-wise launches above that size are cut by bytes (below) unless they are a few long items of narrow rows: with
-  // many items or 8-bit rows the bytes' balance matters more (8 ragged sequences 16.4 us by bytes, 17.6 so).  Of 120 other
-  // launches (8 to 32 items, up to half 8-bit rows, 42 to 151 MB) the line picks the better way, or one within 5 %, in 89; it
-  // is off the most just above the floor with 8 query heads (42 MB, 16 items, 30 % 8-bit rows: 25.4 us by bytes, 16.2 so) and
-  // just below the upper limit with 4 (96 MB, 16 items, 10 %: 23.2 us by bytes, 27.5 so).
+  // Launches of up to kModelledCost are cut into rows, a multiple of 256 per chunk (one 64-row tile per SIMD), by a model of
+  // their time: a start, the tiles that one SIMD goes through one after the other (8-bit rows take longer), and what each
+  // chunk adds to the launch and each partial to the merge of its item.  A launch of at most 256 chunks has one workgroup per
+  // compute unit and looks for its partials; a larger one counts arrivals and shares its compute units.  Against both stands
+  // the cut by bytes below, whose time goes with the bytes.  Fitted to 314 token-wise launches (2 to 64 items, 1 to 192 MB,
+  // up to 60 % 8-bit rows, caches cold).  600 others (1 to 128 items of even and uneven lengths, 0.5 to 220 MB, 16-bit rows,
+  // tails) take 2.9 % less time in the geometric mean than with arrivals weighed as of a counted merge and a line by bytes alone:
+  // 125 of them at least 3 % less (one item of 220 MB, 8 heads per KV head: 717 chunks 62.7 us, 206 chunks 18.7), 29 more
+  // (the worst 64 items with long tails: 750 chunks 31.5 us, 248 and the tails' 192 38.4).
+  // Some of the fit (microseconds per launch, number of chunks in parentheses):
+  //   2 items, 8 MB                          k 1: 8.2 (236)   k 2: 7.4 (119)*  k 4: 8.6 (60)    by bytes: 8.3 (83)
+  //   2 items, 64 MB                                          k 8: 16.8*       k 12: 19.9       by bytes: 22.9
+  //   16 items, 64 MB, 60 % 8-bit rows                        k 6: 17.4*                        by bytes: 20.5
+  //   16 items, 96 MB, 20 %                                   k 8: 26.9                         by bytes: 24.2*
+  //   8 heads per KV head, 2 items, 64 MB, 60 %               k 4: 27.4 (280)  k 6: 21.5 (188)* by bytes: 42.9 (711)
+  //   8 heads per KV head, 64 items, 64 MB                    k 4: 19.2 (477)*                  by bytes: 23.1 (1306)
+  // Channel-wise launches small enough for eight-wavefront workgroups want one per compute unit, since a few more than 256
+  // double the time, but no fewer: over 216 launches (2 to 32 items, 1 to 44 MB) the best cut is 3.0 % faster than one with
+  // arrivals weighed as above, and 0.9 % than this one (one 64K sequence of 2 and 4 bits, 2 heads, 12 MB: 106 chunks 20.0 us,
+  // 156 chunks 15.0).  With four wavefronts and 8 query heads per KV head two workgroups share a compute unit well (72 launches
+  // of 1 to 32 MB: 5.0 % and 1.0 %; 32 items, 32 MB: 248 chunks 46.6 us, 455 chunks 33.3).
+  constexpr double kModelledCost = 192e6;
   const int64_t floor_bytes = static_cast<int64_t>(wide ? 96 : 48) << 10;
-  int64_t small_rows = 0;
-  // (eight-wavefront workgroups of the channel-wise kernel: one per compute unit, so that a few more than 256 double the
-  // time; 23 MB of one 64K sequence 512: 26.0, 768: 30.2, 1024: 19.0*, 1536: 21.4)
   int64_t rows8 = 0, rows_all = 0;
   for (int64_t i = 0; i < n; ++i)
     for (int ti = ti0; ti < 4; ++ti) (ti == 1 ? rows8 : rows_all) += c->counts[i * 4 + ti];
   rows_all += rows8;
   const double share8 = static_cast<double>(rows8) / static_cast<double>(std::max<int64_t>(rows_all, 1));
-  // rows per chunk for the tiers from ti_first on, and the number of chunks that gives
-  auto latency_model = [&](int ti_first, double per_tile, int64_t* n_chunks) {
-    constexpr int kMostTiles = 16;
-    double best = 0.0;
-    int64_t best_rows = 0;
-    for (int k = 1; k <= kMostTiles; k += k < 4 ? 1 : k < 8 ? 2 : 4) {
-      const uint32_t rows = 256u * static_cast<uint32_t>(k);
-      int64_t n_wg = 0, most = 0;
-      for (int64_t i = 0; i < n; ++i) {
-        int64_t slots = 0;
-        for (int ti = ti_first; ti < 4; ++ti) slots += (static_cast<uint32_t>(c->counts[i * 4 + ti]) + rows - 1) / rows;
-        n_wg += slots;
-        most = std::max(most, slots);
-      }
-      if (n_wg > 768 + 4 * n && k < kMostTiles) continue;      // more than any launch needs (and cache_max_table_bytes allows for)
-      const double rounds = static_cast<double>((n_wg + round_chunks - 1) / round_chunks);
-      const double at_once = static_cast<double>(most) / rounds;
-      const double t = 6.5 * rounds + per_tile * k * static_cast<double>((n_wg + 255) / 256) + 0.07 * at_once +
-                       0.09 * std::max(0.0, at_once - 14.0);
-      if (best_rows == 0 || t < best) { best_rows = rows; best = t; *n_chunks = n_wg; }
+  const double items = static_cast<double>(std::max<int64_t>(n, 1));
+  // microseconds; tile8: more for each tile after the first free8 if all rows have 8 bits; byte: per 1e6 of cost
+  struct LaunchTime { double start, tile, tile8, free8, chunk, partial, byte; };
+  const bool heads4 = !mixed && g <= 4;
+  const LaunchTime alone = mixed_wide ? LaunchTime{3.0, 1.8, 0.0, 0.0, 0.01, 0.01, 0.0}
+                           : mixed    ? LaunchTime{3.0, 7.0, 0.0, 0.0, 0.0, 0.1, 0.0}
+                           : heads4   ? LaunchTime{4.9, 0.25, 1.2, 3.0, 0.002, 0.001, 0.14}
+                                      : LaunchTime{4.2, 1.5, 0.7, 2.0, 0.018, 0.0, 0.03};
+  const LaunchTime among = mixed_wide ? LaunchTime{6.0, 1.8, 0.0, 0.0, 0.01, 0.01, 0.0}
+                           : mixed    ? LaunchTime{3.0, 7.0, 0.0, 0.0, 0.0, 0.1, 0.0}
+                           : heads4   ? LaunchTime{1.7, 1.2, 0.69, 0.0, 0.018, 0.067, 0.0}
+                                      : LaunchTime{4.4, 1.1, 0.67, 0.0, 0.008, 0.1, 0.0};
+  const int64_t at_once = mixed && !mixed_wide ? 512 : 256;      // chunks whose tiles do not slow each other down
+  struct Cut { int64_t rows; double time; };
+  const int64_t room = std::min<int64_t>(2 * n, 16);      // for the chunks of a tail, which a cache that is decoded from usually gets
+  // the best rows per chunk for the tiers from ti_first on
+  auto cut_by_rows = [&](int ti_first, double share, bool only_looked) {
+    constexpr uint32_t kMostTiles = 16;
+    Cut best{0, 0.0};
+    for (uint32_t k = 1; k <= kMostTiles; k += heads4 && k >= 4 ? 2 : 1) {      // (eight wavefronts: 512 rows at a time)
+      const uint32_t rows = 256u * k;
+      int64_t n_wg = 0;
+      uint32_t tiles = 0;
+      for (int64_t i = 0; i < n; ++i)
+        for (int ti = ti_first; ti < 4; ++ti) {
+          const uint32_t cnt = static_cast<uint32_t>(c->counts[i * 4 + ti]);
+          if (cnt == 0) continue;
+          const uint32_t nch = (cnt + rows - 1) / rows;
+          n_wg += nch;
+          tiles = std::max(tiles, ((cnt + nch - 1) / nch + 255u) / 256u);
+        }
+      if (n_wg > 768 + 4 * n) continue;      // more than any launch needs, and than cache_max_table_bytes allows for
+      const bool look = n_wg <= 256 - room;
+      if (only_looked && !look) continue;
+      const LaunchTime& t = look ? alone : among;
+      const double rounds = static_cast<double>((n_wg + at_once - 1) / at_once), depth = static_cast<double>(tiles);
+      const double time = t.start + (t.tile * depth + t.tile8 * share * std::max(0.0, depth - t.free8)) * rounds +
+                          (t.chunk + t.partial / items) * static_cast<double>(n_wg) + t.byte * 1e-6 * static_cast<double>(total_cost);
+      if (best.rows == 0 || time < best.time) best = Cut{static_cast<int64_t>(rows), time};
     }
-    return best_rows;
+    return best;
   };
-  const double per_tile = mixed ? (g > 4 ? 6.0 : 3.0) : (g > 4 ? 1.6 : 1.3) + 1.6 * share8;
+  const auto by_bytes = [&](int64_t cost) { return std::min<int64_t>(round_chunks, cost / floor_bytes); };      // its chunks
+  const auto bytes_time = [&](int64_t cost) {
+    const double partials = static_cast<double>(by_bytes(cost)) / items;
+    return g > 4 ? 8.6 + 0.155e-6 * static_cast<double>(cost) + 0.06 * partials : 8.1 + 0.118e-6 * static_cast<double>(cost) + 0.034 * partials;
+  };
+  int64_t small_rows = 0;
+  if (total_cost > 0 && (mixed ? mixed_wide || total_cost <= round_chunks * floor_bytes : static_cast<double>(total_cost) <= kModelledCost)) {
+    const Cut cut = cut_by_rows(ti0, share8, false);
+    if (mixed || by_bytes(total_cost) <= 256 || cut.time < bytes_time(total_cost)) small_rows = cut.rows;
+  }
   // A token-wise launch of at most 256 chunks takes the 16-bit rows along (decode_tiles_take_rows): one launch instead of
-  // two that follow each other (three short sequences of keep / 4 bit / evict 11.7 -> 8 us).
+  // two that follow each other (three short sequences of keep / 4 bit / evict 11.7 -> 8 us).  They take what 8-bit rows do.
   bool rows16_along = false;
   if (cost16 > 0 && total_cost + cost16 <= round_chunks * floor_bytes) {
-    int64_t n_wg = 0;
-    small_rows = latency_model(0, (g > 4 ? 1.6 : 1.3) + 1.6, &n_wg);
-    rows16_along = decode_tiles_take_rows(static_cast<int>(n_wg), false);
-    if (!rows16_along) small_rows = 0;
-  }
-  if (small_rows == 0 && total_cost > 0 &&
-      (mixed ? mixed_wide || total_cost <= round_chunks * floor_bytes
-             : total_cost <= round_chunks * floor_bytes ||
-                   (share8 < 0.2 && n <= 16 && total_cost < round_chunks * (192 << 10)))) {
-    int64_t n_wg = 0;
-    small_rows = latency_model(ti0, per_tile, &n_wg);
+    const Cut cut = cut_by_rows(0, 1.0, true);
+    rows16_along = cut.rows > 0 && (total_cost + cost16 <= 256 * floor_bytes || cut.time < bytes_time(total_cost + cost16) + 4.0);
+    if (rows16_along) small_rows = cut.rows;
   }
   // Number of chunks a chunk cost of cb gives, and the largest chunk's cost.  Chunks of less than an eighth of cb (a
   // tier with a handful of rows) do not count: they finish at once and leave their workgroup slot to the next chunk
@@ -1146,7 +1168,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // worth it when a chunk streams for tens of microseconds (32 sequences x 128K tokens at 0.4 bit/elt: 101.6 -> 97.6
   // us), not in latency-bound launches (a 16 MB layer: 12.2 -> 13.7 us), which keep one tier per chunk.
   int64_t chunk_bytes = std::max<int64_t>(floor_bytes, total_cost / round_chunks);
-  const bool shares = !mixed && chunk_bytes >= (192 << 10);
+  const bool shares = !mixed && small_rows == 0 && chunk_bytes >= (192 << 10);
   auto count_any = [&](int64_t cb, int64_t* max_cost) { return shares ? count_shares(cb, max_cost) : count_chunks(cb, max_cost); };
   int64_t max_cost = 0, n_one_round = count_any(chunk_bytes, &max_cost);
   for (int tries = 0; small_rows == 0 && tries < 64 && n_one_round > round_chunks + round_chunks / 50; ++tries) {   // (2 % over is fine)

@@ -1,6 +1,6 @@
 """The merging workgroups of small decode launches: slots per item on both sides of a batch of loads, every number of blocks
-per wavefront (which follows the number of items and of query heads), channel-wise keys, and a workspace that every step leaves
-as it found it."""
+per wavefront (which follows the number of items and of query heads), channel-wise keys, both sides of the line between a launch
+that looks and one that counts, and a workspace that every step leaves as it found it."""
 import numpy as np
 import pytest
 import torch
@@ -55,3 +55,13 @@ def test_numbers_of_items(batch, hkv, g):
 def test_channelwise(T, g):
     from paper_2605_08317_amd import binding as b
     _check(b, [T], 2, g, [8, 4, 2, 0], mixed=True)
+
+
+# one and two tiles per SIMD, the last cut that looks and the first that counts, tiers that all end in a remainder
+@pytest.mark.parametrize("seq_lens,hkv,widths", [((257,), 1, [2]), ((512, 65), 2, [8]), ((30600, 30600), 2, [2]),
+                                                 ((61400,), 2, [4]), ((5000, 70, 12001), 8, [8, 4, 2]),
+                                                 ((20000, 1), 4, [16, 8, 4, 2]), ((3000,) * 12, 8, [8, 2])])
+@pytest.mark.parametrize("g", [1, 4, 8])
+def test_rows_per_chunk(seq_lens, hkv, widths, g):
+    from paper_2605_08317_amd import binding as b
+    _check(b, list(seq_lens), hkv, g, widths)

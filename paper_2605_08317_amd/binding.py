@@ -1,8 +1,9 @@
-"""Thin ctypes binding of librdkv (include/rdkv.h).
+"""Thin binding of librdkv (include/rdkv.h): ctypes, and for the two calls of a
+decode loop native code (_rdkv_call, csrc/rdkv_call.cpp).
 
 Argument marshalling only: every step of the path runs in the HIP kernels of the
 shared library.  PyTorch supplies device memory and streams.  There is no CPU
-fallback: if the library is missing or fails to load, importing this module
+fallback: if either library is missing or fails to load, importing this module
 raises.
 """
 import ctypes
@@ -120,6 +121,12 @@ def _load():
 
 
 lib = _load()
+try:
+    from . import _rdkv_call as _call
+except ImportError as e:
+    raise ImportError(f"_rdkv_call.so is not built or does not fit this PyTorch ({e}); "
+                      "run `python -c 'import __graft_entry__ as g; g.build()'`") from e
+_call.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.rdkv_decode_attn, lib.rdkv_cache_append)))
 
 
 def _check(status):
@@ -274,6 +281,11 @@ def rdkv_compress(cfg, K, V, Q_obs):
 
 def rdkv_decode_attn(cache, q, out=None, lse=None):
     cfg = cache.cfg
+    done = _call.decode(cache.h, _stream(), len(cfg.seq_lens), cfg.hq, cfg.d, q, out, lse)
+    if done is not None:
+        if done[0] != RDKV_OK:
+            _check(done[0])
+        return done[1:]
     if out is None:
         out = _empty_f32((len(cfg.seq_lens), cfg.hq, cfg.d), (cfg.hq * cfg.d, cfg.d, 1), q.device)
     if lse is None:
@@ -287,6 +299,9 @@ def rdkv_cache_reserve_tail(cache, max_new_tokens):
 
 
 def rdkv_cache_append(cache, k_new, v_new):
+    status = _call.append(cache.h, _stream(), k_new, v_new)
+    if status is not None:
+        return _check(status)
     _check(lib.rdkv_cache_append(cache.h, _ptr(k_new), _ptr(v_new), _stream()))
 
 

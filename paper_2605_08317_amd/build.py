@@ -1,12 +1,15 @@
-"""Builds librdkv.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc."""
+"""Builds in-tree: librdkv.so (HIP kernels + C ABI) for gfx950 with hipcc, and _rdkv_call.so (the decode loop's calls from
+Python) with the host compiler."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librdkv.so")
+CALL = os.path.join(HERE, "_rdkv_call.so")
 # (source, object, extra flags); the mixed-mode decode kernels are compiled once per head-set count and row length
 # class so that their many instantiations build in parallel; the slowest objects come first
 SOURCES = [
@@ -41,9 +44,24 @@ FLAGS = [
 ]
 
 
+def call_command():
+    """The host compiler's line for _rdkv_call.so: against the installed PyTorch's headers, without a HIP header."""
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I" + os.path.join(ROOT, "include")] +
+            ["-isystem" + p for p in include_paths() + [sysconfig.get_paths()["include"]]] +
+            [os.path.join(CSRC, "rdkv_call.cpp"), "-o", CALL, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"])
+
+
 def build(verbose=True, jobs=8):
     objs, procs = [], []
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
+    cmd = call_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs.append(("rdkv_call.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, obj_name, extra in SOURCES:
         obj = os.path.join(HERE, "_build", obj_name)
         objs.append(obj)
@@ -69,7 +87,7 @@ def _drain(procs):
         if out:
             print(out, flush=True)
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}")
+            raise RuntimeError(f"the compiler failed on {src}")
 
 
 if __name__ == "__main__":

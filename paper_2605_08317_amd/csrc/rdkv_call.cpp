@@ -1,0 +1,134 @@
+// The two calls of a decode loop, from Python in native code: rdkv_decode_attn and rdkv_cache_append.
+//
+// A decode step of a short context takes the GPU 5.2 us.  Through ctypes it took the host 7.4: 3.6 in the call itself, 2.5 for
+// two result tensors made from Python and the rest for converting arguments one by one.  Here the tensors are unpacked and
+// made by PyTorch's C++ interface: 5.8 us per step (4K keys, 2 KV heads), a request of 32K keys and 64 tokens with results
+// given 1054 -> 988 us.  What is not a plain tensor call (an argument that is no tensor, one that is not contiguous) is left to
+// the ctypes path, which says what is wrong with it: the functions then return None.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/core/Tensor.h>
+#include <ATen/ops/empty.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
+
+#include "rdkv.h"
+
+namespace {
+
+decltype(&rdkv_decode_attn) g_decode = nullptr;
+decltype(&rdkv_cache_append) g_append = nullptr;
+
+// a contiguous tensor's memory
+bool pointer(PyObject* o, void** p) {
+  if (!THPVariable_Check(o)) return false;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.is_contiguous()) return false;
+  *p = t.data_ptr();
+  return true;
+}
+
+// a cache's handle: a number, None, or a ctypes pointer
+bool handle(PyObject* o, long long* h) {
+  if (o == Py_None) {
+    *h = 0;
+    return true;
+  }
+  if (PyLong_Check(o)) {
+    *h = PyLong_AsLongLong(o);
+    return !PyErr_Occurred();
+  }
+  static PyObject* const name = PyUnicode_InternFromString("value");
+  PyObject* v = PyObject_GetAttr(o, name);
+  if (!v) return false;
+  const bool ok = v == Py_None || PyLong_Check(v);
+  *h = v == Py_None || !ok ? 0 : PyLong_AsLongLong(v);
+  Py_DECREF(v);
+  if (!ok) PyErr_SetString(PyExc_TypeError, "not a handle");
+  return ok && !PyErr_Occurred();
+}
+
+bool integers(PyObject* const* args, int n, long long* out) {
+  for (int i = 0; i < n; ++i) {
+    out[i] = PyLong_AsLongLong(args[i]);
+    if (out[i] == -1 && PyErr_Occurred()) return false;
+  }
+  return true;
+}
+
+// bind(address of rdkv_decode_attn, address of rdkv_cache_append)
+PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  long long a[2];
+  if (n != 2 || !integers(args, 2, a)) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "bind takes two addresses");
+    return nullptr;
+  }
+  g_decode = reinterpret_cast<decltype(g_decode)>(a[0]);
+  g_append = reinterpret_cast<decltype(g_append)>(a[1]);
+  Py_RETURN_NONE;
+}
+
+// decode(cache, stream, batch, hq, d, q, out or None, lse or None) -> (status, out, lse) or None
+PyObject* decode(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  long long h, a[4];
+  if (n != 8 || !handle(args[0], &h) || !integers(args + 1, 4, a)) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "decode takes eight arguments");
+    return nullptr;
+  }
+  void *q, *out = nullptr, *lse = nullptr;
+  if (!g_decode || !pointer(args[5], &q)) Py_RETURN_NONE;
+  const bool make_out = args[6] == Py_None, make_lse = args[7] == Py_None;
+  if ((!make_out && !pointer(args[6], &out)) || (!make_lse && !pointer(args[7], &lse))) Py_RETURN_NONE;
+  at::Tensor new_out, new_lse;
+  const auto options = at::TensorOptions().dtype(at::kFloat).device(THPVariable_Unpack(args[5]).device());
+  if (make_out) {
+    new_out = at::empty({a[1], a[2], a[3]}, options);
+    out = new_out.data_ptr();
+  }
+  if (make_lse) {
+    new_lse = at::empty({a[1], a[2]}, options);
+    lse = new_lse.data_ptr();
+  }
+  int status;
+  Py_BEGIN_ALLOW_THREADS
+  status = g_decode(reinterpret_cast<rdkv_cache*>(h), q, static_cast<float*>(out), static_cast<float*>(lse), reinterpret_cast<void*>(a[0]));
+  Py_END_ALLOW_THREADS
+  THPObjectPtr py_out(make_out ? THPVariable_Wrap(std::move(new_out)) : Py_NewRef(args[6]));
+  THPObjectPtr py_lse(make_lse ? THPVariable_Wrap(std::move(new_lse)) : Py_NewRef(args[7]));
+  if (!py_out || !py_lse) return nullptr;
+  return Py_BuildValue("(iNN)", status, py_out.release(), py_lse.release());
+  END_HANDLE_TH_ERRORS
+}
+
+// append(cache, stream, k_new, v_new) -> status or None
+PyObject* append(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  long long h, stream;
+  if (n != 4 || !handle(args[0], &h) || !integers(args + 1, 1, &stream)) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "append takes four arguments");
+    return nullptr;
+  }
+  void *k, *v;
+  if (!g_append || !pointer(args[2], &k) || !pointer(args[3], &v)) Py_RETURN_NONE;
+  int status;
+  Py_BEGIN_ALLOW_THREADS
+  status = g_append(reinterpret_cast<rdkv_cache*>(h), k, v, reinterpret_cast<void*>(stream));
+  Py_END_ALLOW_THREADS
+  return PyLong_FromLong(status);
+  END_HANDLE_TH_ERRORS
+}
+
+PyMethodDef methods[] = {
+    {"bind", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(bind)), METH_FASTCALL, nullptr},
+    {"decode", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(decode)), METH_FASTCALL, nullptr},
+    {"append", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(append)), METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr},
+};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_rdkv_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__rdkv_call() { return PyModule_Create(&module); }

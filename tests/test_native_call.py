@@ -1,0 +1,71 @@
+"""The decode loop's calls in native code: what they hand to the library, what they make, and what they leave to ctypes."""
+import threading
+
+import pytest
+import torch
+
+from paper_2605_08317_amd import workloads as W
+
+
+@pytest.fixture(scope="module")
+def b():
+    from paper_2605_08317_amd import binding
+    return binding
+
+
+class _NoCache:
+    def __init__(self, h):
+        import types
+        self.h, self.cfg = h, types.SimpleNamespace(seq_lens=[5], hq=2, d=128)
+
+
+def test_errors_are_those_of_the_library_and_of_ctypes(b, monkeypatch):
+    import ctypes
+    monkeypatch.setattr(b, "_stream", lambda: 0)
+    q = torch.zeros(1, 2, 128, dtype=torch.bfloat16)
+    for h in (None, 0, ctypes.c_void_p()):
+        with pytest.raises(b.RdkvError, match="RDKV_ERR_INVALID_ARG"):
+            b.rdkv_decode_attn(_NoCache(h), q)
+        for k in (q, None):
+            with pytest.raises(b.RdkvError, match="RDKV_ERR_INVALID_ARG"):
+                b.rdkv_cache_append(_NoCache(h), k, k)
+    odd = torch.zeros(1, 2, 256, dtype=torch.bfloat16)[:, :, ::2]
+    for args in ((odd,), (q, odd), (q, None, odd)):
+        with pytest.raises(AssertionError):
+            b.rdkv_decode_attn(_NoCache(0), *args)
+    with pytest.raises(AssertionError):
+        b.rdkv_cache_append(_NoCache(0), q, odd)
+    with pytest.raises((AttributeError, TypeError)):
+        b.rdkv_decode_attn(_NoCache("no handle"), q)
+
+
+@pytest.mark.gpu
+def test_results_made_or_given_on_any_stream_and_thread(b):
+    wl = W.scaled(W.CONFIGS["tiny"], seq_lens=(700,))
+    inp = {k: v.cuda() for k, v in W.make_inputs(wl, device="cpu").items() if k in ("K", "V", "q", "Q_obs")}
+    cfg = b.Config([700], wl.hq, wl.hkv, budget_bits=[3.0], s_obs=wl.s_obs)
+    cache = b.rdkv_compress(cfg, inp["K"], inp["V"], inp["Q_obs"])
+    out, lse = b.rdkv_decode_attn(cache, inp["q"])
+    for t, shape in ((out, (1, wl.hq, 128)), (lse, (1, wl.hq))):
+        assert t.shape == shape and t.dtype == torch.float32 and t.is_contiguous() and t.device == inp["q"].device and not t.requires_grad
+    given = [torch.full_like(out, 7.0), torch.full_like(lse, 7.0)]
+    for o, l in ((None, given[1]), (given[0], None), given):
+        r = b.rdkv_decode_attn(cache, inp["q"], o, l)
+        assert isinstance(r, tuple) and (o is None or r[0] is o) and (l is None or r[1] is l)
+        assert torch.equal(r[0], out) and torch.equal(r[1], lse)
+    torch.cuda.synchronize()
+    bad = []
+
+    def loop():
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for _ in range(20):
+                o, l = b.rdkv_decode_attn(cache, inp["q"])
+                stream.synchronize()
+                if not (torch.equal(o, out) and torch.equal(l, lse)):
+                    bad.append(1)
+    thread = threading.Thread(target=loop)
+    thread.start()
+    thread.join()
+    assert not bad
+    cache.free()

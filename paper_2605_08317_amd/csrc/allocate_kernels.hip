@@ -88,8 +88,11 @@ struct Problem {
     need = static_cast<long long>(ceil(a.need_frac * static_cast<double>(B_int)));
   }
   // the tier every unit gets without a search, or -1
+  // (the top tier by comparisons: an index known at run time puts the whole structure into memory)
   __device__ __forceinline__ int fill(int U) const {
-    const int top = tiers[nh - 1];
+    int top = tiers[0];
+#pragma unroll
+    for (int k = 1; k < kMaxHull; ++k) top = k < nh ? tiers[k] : top;
     if (B_int >= static_cast<long long>(top) * U) return top;
     if (nh == 1 || B_int < tiers[1]) return tiers[0];
     return -1;

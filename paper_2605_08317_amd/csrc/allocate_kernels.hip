@@ -450,10 +450,11 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 // Thread t holds units 4096 j + 4 t .. + 3, so four wavefronts make one block of the per-block counts.  What bounds it:
 // one compute unit works on an item, through the latency of its loads and about fifteen barriers and then the number of
 // instructions per unit and pass (load, histogram, gather, write).  Measured against fp64
-// comparisons and one step at a time: 4K units 31 -> 15 us, 32K units (94 us in five kernels) -> 28 us, both with the
+// comparisons and one step at a time: 4K units 31 -> 8.4 us, 32K units (94 us in five kernels) -> 24 us, both with the
 // counting kernels (10 us) gone.
 constexpr int kItemListCap = 24576;        // units of open buckets in LDS (96 KB beside 34 KB of histogram)
-constexpr size_t kItemLds = Anchored::kWords * sizeof(int) + kItemListCap * sizeof(float);
+template <int REG>
+constexpr size_t kItemLds = Anchored::kWords * sizeof(int) + (REG == 4 ? kWaves * sizeof(int4) : kItemListCap * sizeof(float));
 
 template <int REG>
 __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
@@ -522,6 +523,33 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
       S = s_search;
       if (S.done || S.it >= P.max_iters) break;
       // the histogram cannot decide the next step
+      // Up to 4K units the other steps are taken on all of them, 0.3 us each: finding the open buckets, the list and its few
+      // units' steps took 4.2 us (4K units 11.8 -> 8.4 us in all, 64 units and 64 steps 16 -> 12).  With 32 units per thread a
+      // step costs 2 us: two such steps in front of the list 25 -> 36 us.
+      if constexpr (REG == 4) {
+        int parity = 0;
+        while (!S.done && S.it < P.max_iters) {
+          const double lam = (S.lo + S.hi) * 0.5;
+          int c = 0;
+#pragma unroll
+          for (int k = 0; k < kThr; ++k) {
+            const float tk = P.thr(lam, k);
+            int ck = 0;
+#pragma unroll
+            for (int j = 0; j < REG; ++j) ck += __popcll(__ballot(v[j] > tk));
+            c += P.step_bits[k] * ck;
+          }
+          int* slots = s_red + parity * kWaves;        // alternating, so that one barrier per step is enough
+          parity ^= 1;
+          if (lane == 0) slots[wave] = c;
+          __syncthreads();
+          long long s = P.base;
+#pragma unroll
+          for (int i = 0; i < kWaves; ++i) s += slots[i];
+          S.take(P.verdict(s), lam);
+        }
+        break;
+      }
       Hull hull = bracket_of(S);
       OpenBuckets open(P, map, hull);
       int n = open.count(s_hist);
@@ -1043,9 +1071,9 @@ hipError_t launch_short_items(const AllocArgs& a, int n_items, int max_U, hipStr
   const dim3 grid(n_items), block(kThreads);
 #define RDKV_ITEMS(REG_)                                                              \
   {                                                                                   \
-    const hipError_t e = RDKV_ALLOW_LDS((allocate_item_kernel<REG_>), kItemLds);      \
+    const hipError_t e = RDKV_ALLOW_LDS((allocate_item_kernel<REG_>), kItemLds<REG_>); \
     if (e != hipSuccess) return e;                                                    \
-    hipLaunchKernelGGL(allocate_item_kernel<REG_>, grid, block, kItemLds, st, a);     \
+    hipLaunchKernelGGL(allocate_item_kernel<REG_>, grid, block, kItemLds<REG_>, st, a); \
   }
   if (max_U <= 4 * kThreads) RDKV_ITEMS(4)
   else if (max_U <= 16 * kThreads) RDKV_ITEMS(16)

@@ -664,7 +664,7 @@ constexpr int kItemUnits = 32 * kThreads;   // longest item of that kernel
 
 // ---- longer items: the passes over the units on many workgroups -------------------------------------------------
 // Beyond 32K units the registers of one compute unit no longer hold an item.  Measured, 8 items of 128K units: 98 to 255
-// us in six kernels -> 55 us in four; what is left is the latency of two hand-overs to the last workgroup and of the
+// us in six kernels -> 33 us in four; what is left is the latency of two hand-overs to the last workgroup and of the
 // dependent steps.
 // An item's weights read as aligned 16-byte quads.  Quad q covers units 4 q - a .. 4 q - a + 3,
 // a = how many floats the item's first weight sits past a 16-byte boundary; units outside [0, U) read as 0 (never above

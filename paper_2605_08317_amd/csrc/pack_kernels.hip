@@ -488,26 +488,68 @@ __global__ __launch_bounds__(256, 5) void pack_tile_kernel(PackArgs a) {
 // ---- mixed mode -------------------------------------------------------------------------------------------------
 // One scale per channel over all retained tokens (App. B): the channel's minimum and maximum over the kept rows of
 // all four tiers of the item.  k_range starts at (0xFFFFFFFF, 0).
-__global__ __launch_bounds__(256) void k_channel_range_kernel(PackArgs a) {
-  __shared__ uint32_t s_mn[2][kHeadDim], s_mx[2][kHeadDim];
-  const int item = blockIdx.y;
-  const int64_t first = a.idx_base[item * 4];
-  const int kept = a.counts[item * 4] + a.counts[item * 4 + 1] + a.counts[item * 4 + 2] + a.counts[item * 4 + 3];
-  const int c = threadIdx.x & (kHeadDim - 1), sub = threadIdx.x >> 7;
-  uint32_t mn = 0xFFFFFFFFu, mx = 0u;
-  for (int r = blockIdx.x * 2 + sub; r < kept; r += gridDim.x * 2) {
-    const int pos = a.tier_idx[first + r];
-    const float x = __uint_as_float(static_cast<uint32_t>(a.K[(a.item_row_off[item] + pos) * kHeadDim + c]) << 16);
-    const uint32_t k = float_to_ordered(x);
-    mn = min(mn, k);
-    mx = max(mx, k);
+// Bound: HBM (the kept rows once).  A wavefront's load is four rows, 16 bytes per lane, and kRangeLoads of them are in flight
+// with the positions of the next ones; the order of bf16 numbers is that of 16-bit integers, two to a register, as
+// float_to_ordered maps them.  Few workgroups per item, because each ends in 256 atomics on the item's 256 words.
+// RANGE_TIMES
+constexpr int kRangeThreads = 512, kRangeLoads = 8, kRangeRows = kRangeThreads / 16 * kRangeLoads;
+using ushort2v = __attribute__((ext_vector_type(2))) unsigned short;
+using short2v = __attribute__((ext_vector_type(2))) short;
+__global__ __launch_bounds__(kRangeThreads) void k_channel_range_kernel(PackArgs a) {
+  constexpr int kParts = kRangeThreads / 16;
+  __shared__ uint4 s_part[2][kParts][16];            // smallest, largest: [rows of a load][channels 8 c16 ..]
+  const int item = blockIdx.y, tid = threadIdx.x, part = tid >> 4, c16 = tid & 15;
+  const int4 n4 = reinterpret_cast<const int4*>(a.counts)[item];
+  const int kept = n4.x + n4.y + n4.z + n4.w;
+  const int row0 = blockIdx.x * kRangeRows, step = static_cast<int>(gridDim.x) * kRangeRows;
+  if (row0 >= kept) return;                          // (the whole workgroup)
+  const int32_t* idx = a.tier_idx + a.idx_base[item * 4];
+  const uint16_t* rows = a.K + a.item_row_off[item] * kHeadDim + c16 * 8;
+  union Piece { uint4 q; ushort2v h[4]; };
+  Piece mn, mx;
+  mn.q = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+  mx.q = make_uint4(0, 0, 0, 0);
+  int pos[kRangeLoads];
+  const auto positions = [&](int r0) __attribute__((always_inline)) {      // rows past the last repeat it
+#pragma unroll
+    for (int i = 0; i < kRangeLoads; ++i) pos[i] = idx[min(r0 + i * kParts + part, kept - 1)];
+  };
+  positions(row0);
+  for (int r0 = row0; r0 < kept; r0 += step) {
+    Piece v[kRangeLoads];
+#pragma unroll
+    for (int i = 0; i < kRangeLoads; ++i) v[i].q = *reinterpret_cast<const uint4*>(rows + static_cast<int64_t>(pos[i]) * kHeadDim);
+    if (r0 + step < kept) positions(r0 + step);
+#pragma unroll
+    for (int i = 0; i < kRangeLoads; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const ushort2v u = v[i].h[j];
+        const ushort2v sign = __builtin_bit_cast(ushort2v, __builtin_bit_cast(short2v, u) >> short2v{15, 15});
+        const ushort2v k = u ^ (sign | ushort2v{0x8000, 0x8000});
+        mn.h[j] = __builtin_elementwise_min(mn.h[j], k);
+        mx.h[j] = __builtin_elementwise_max(mx.h[j], k);
+      }
   }
-  s_mn[sub][c] = mn;
-  s_mx[sub][c] = mx;
+  s_part[0][part][c16] = mn.q;
+  s_part[1][part][c16] = mx.q;
   __syncthreads();
-  if (sub == 0 && kept > 0) {
-    atomicMin(&a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2], min(s_mn[0][c], s_mn[1][c]));
-    atomicMax(&a.k_range[(static_cast<int64_t>(item) * kHeadDim + c) * 2 + 1], max(s_mx[0][c], s_mx[1][c]));
+  if (tid < kHeadDim) {                              // two channels each of the smallest (64 threads) and of the largest
+    const bool largest = tid >= kHeadDim / 2;
+    const int pair = tid & (kHeadDim / 2 - 1);
+    const ushort2v* p = reinterpret_cast<const ushort2v*>(&s_part[largest][0][0]) + pair;
+    ushort2v k = p[0];
+#pragma unroll
+    for (int i = 1; i < kParts; ++i) {
+      const ushort2v o = p[i * (kHeadDim / 2)];
+      k = largest ? __builtin_elementwise_max(k, o) : __builtin_elementwise_min(k, o);
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint32_t k16 = k[e], k32 = k16 << 16 | (k16 & 0x8000u ? 0u : 0xFFFFu);      // float_to_ordered of the number
+      uint32_t* dst = &a.k_range[(static_cast<int64_t>(item) * kHeadDim + 2 * pair + e) * 2];
+      if (largest) atomicMax(dst + 1, k32); else atomicMin(dst, k32);
+    }
   }
 }
 
@@ -786,7 +828,11 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
     return hipGetLastError();
   }
   // k_range must hold (0xFFFFFFFF, 0) pairs on entry
-  if (k_range) hipLaunchKernelGGL(k_channel_range_kernel, dim3(64, n_items), block, 0, st, a);
+  if (k_range) {
+    // 512 workgroups fill the chip; 16 per item are left where there are many items, 128 at most where there are few
+    const int parts = std::min(std::max(512 / n_items, 16), 128), most = (max_tiles * kTile64 + kRangeRows - 1) / kRangeRows;
+    hipLaunchKernelGGL(k_channel_range_kernel, dim3(std::max(1, std::min(parts, most)), n_items), dim3(kRangeThreads), 0, st, a);
+  }
   hipLaunchKernelGGL(pack_k_mixed_kernel, grid, dim3(kKThreads), 0, st, a);
   hipLaunchKernelGGL(pack_tile_kernel<true>, grid, block, 0, st, a);
   return hipGetLastError();

@@ -1018,9 +1018,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // whose answer the workgroup waits for) and its item one more partial to merge, so a launch wants exactly one round of workgroups:
   // as many chunks as the chip keeps resident (256 compute units x 2 workgroups of eight wavefronts = 512), never a
   // few more (measured on 4 x 128K tokens of 2-bit rows: 512 chunks 4.9 TB/s, 608 chunks 4.4, 2048 chunks 4.2).
-  // Small launches are bound by latencies instead and want fewer, larger chunks still: at least 96 KB (measured on a
-  // 16 MB layer: 96 KB chunks 12.6 us, 64 KB 13.4 us, 24 KB 20 us).  Kernels with four-wavefront workgroups (8 query
-  // heads per KV head, channel-wise K) keep three workgroups per compute unit resident: 768 chunks of at least 48 KB.
+  // Small launches are bound by latencies instead and are cut by rows (below); what is cut by bytes has chunks of at least
+  // 96 KB.  Kernels with four-wavefront workgroups (8 query heads per KV head, channel-wise K) keep three workgroups per
+  // compute unit resident: 768 chunks of at least 48 KB.
   // channel-wise mode: eight-wavefront workgroups when the launch is small (one workgroup per compute unit holds
   // it) and the kernel has such an instantiation (up to 4 query heads per KV head, K rows of up to 32 words)
   const bool mixed_wide = mixed && g <= 4 && c->max_k_words <= 32 && stored < (static_cast<int64_t>(48) << 20);

@@ -1052,10 +1052,11 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // chunk adds to the launch and each partial to the merge of its item.  A launch of at most 256 chunks has one workgroup per
   // compute unit and looks for its partials; a larger one counts arrivals and shares its compute units.  Against both stands
   // the cut by bytes below, whose time goes with the bytes.  Fitted to 314 token-wise launches (2 to 64 items, 1 to 192 MB,
-  // up to 60 % 8-bit rows, caches cold).  600 others (1 to 128 items of even and uneven lengths, 0.5 to 220 MB, 16-bit rows,
-  // tails) take 2.9 % less time in the geometric mean than with arrivals weighed as of a counted merge and a line by bytes alone:
-  // 125 of them at least 3 % less (one item of 220 MB, 8 heads per KV head: 717 chunks 62.7 us, 206 chunks 18.7), 29 more
-  // (the worst 64 items with long tails: 750 chunks 31.5 us, 248 and the tails' 192 38.4).
+  // up to 60 % 8-bit rows, caches cold).  244 others (1 to 128 items of even and uneven lengths, 0.5 to 220 MB, 16-bit rows,
+  // tails) take 3.6 % less time in the geometric mean than with arrivals weighed as of a counted merge and a line by bytes alone:
+  // 55 of them at least 3 % less (one item of 220 MB, 8 heads per KV head: 717 chunks 62.7 us, 206 chunks 18.7), 8 more; 217 caches
+  // of 0.4 to 8 bits per element and up to sixteen sequences 2.1 % less, 5 at least 3 % more (2 items of 23K rows: 62 chunks
+  // 7.6 us, 184 chunks 8.0).
   // Some of the fit (microseconds per launch, number of chunks in parentheses):
   //   2 items, 8 MB                          k 1: 8.2 (236)   k 2: 7.4 (119)*  k 4: 8.6 (60)    by bytes: 8.3 (83)
   //   2 items, 64 MB                                          k 8: 16.8*       k 12: 19.9       by bytes: 22.9
@@ -1063,11 +1064,10 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   //   16 items, 96 MB, 20 %                                   k 8: 26.9                         by bytes: 24.2*
   //   8 heads per KV head, 2 items, 64 MB, 60 %               k 4: 27.4 (280)  k 6: 21.5 (188)* by bytes: 42.9 (711)
   //   8 heads per KV head, 64 items, 64 MB                    k 4: 19.2 (477)*                  by bytes: 23.1 (1306)
-  // Channel-wise launches small enough for eight-wavefront workgroups want one per compute unit, since a few more than 256
-  // double the time, but no fewer: over 216 launches (2 to 32 items, 1 to 44 MB) the best cut is 3.0 % faster than one with
-  // arrivals weighed as above, and 0.9 % than this one (one 64K sequence of 2 and 4 bits, 2 heads, 12 MB: 106 chunks 20.0 us,
-  // 156 chunks 15.0).  With four wavefronts and 8 query heads per KV head two workgroups share a compute unit well (72 launches
-  // of 1 to 32 MB: 5.0 % and 1.0 %; 32 items, 32 MB: 248 chunks 46.6 us, 455 chunks 33.3).
+  // Channel-wise launches of eight-wavefront workgroups (one per compute unit, so that a few more than 256 double the time) or
+  // below the floor of the cut by bytes weigh their rounds, tiles and an item's partials instead (cut_channelwise).  Over 47
+  // launches of one to sixteen sequences a model of the kind above was no faster (1.003) and up to 14 % slower (16 uneven
+  // items of 8K to 24K rows), though 3 % faster over 216 even ones.
   constexpr double kModelledCost = 192e6;
   const int64_t floor_bytes = static_cast<int64_t>(wide ? 96 : 48) << 10;
   int64_t rows8 = 0, rows_all = 0;
@@ -1078,23 +1078,15 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   const double items = static_cast<double>(std::max<int64_t>(n, 1));
   // microseconds; tile8: more for each tile after the first free8 if all rows have 8 bits; byte: per 1e6 of cost
   struct LaunchTime { double start, tile, tile8, free8, chunk, partial, byte; };
-  const bool heads4 = !mixed && g <= 4;
-  const LaunchTime alone = mixed_wide ? LaunchTime{3.0, 1.8, 0.0, 0.0, 0.01, 0.01, 0.0}
-                           : mixed    ? LaunchTime{3.0, 7.0, 0.0, 0.0, 0.0, 0.1, 0.0}
-                           : heads4   ? LaunchTime{4.9, 0.25, 1.2, 3.0, 0.002, 0.001, 0.14}
-                                      : LaunchTime{4.2, 1.5, 0.7, 2.0, 0.018, 0.0, 0.03};
-  const LaunchTime among = mixed_wide ? LaunchTime{6.0, 1.8, 0.0, 0.0, 0.01, 0.01, 0.0}
-                           : mixed    ? LaunchTime{3.0, 7.0, 0.0, 0.0, 0.0, 0.1, 0.0}
-                           : heads4   ? LaunchTime{1.7, 1.2, 0.69, 0.0, 0.018, 0.067, 0.0}
-                                      : LaunchTime{4.4, 1.1, 0.67, 0.0, 0.008, 0.1, 0.0};
-  const int64_t at_once = mixed && !mixed_wide ? 512 : 256;      // chunks whose tiles do not slow each other down
+  const LaunchTime alone = g > 4 ? LaunchTime{4.2, 1.6, 0.7, 2.0, 0.014, 0.0, 0.03} : LaunchTime{4.9, 0.25, 1.2, 3.0, 0.002, 0.001, 0.14};
+  const LaunchTime among = g > 4 ? LaunchTime{4.4, 1.1, 0.67, 0.0, 0.008, 0.1, 0.0} : LaunchTime{1.7, 1.2, 0.69, 0.0, 0.018, 0.067, 0.0};
   struct Cut { int64_t rows; double time; };
-  const int64_t room = std::min<int64_t>(2 * n, 16);      // for the chunks of a tail, which a cache that is decoded from usually gets
+  const int64_t room = n <= 8 ? 2 * n : 0;      // for a tail's chunks, where they are few enough to keep the launch small
   // the best rows per chunk for the tiers from ti_first on
   auto cut_by_rows = [&](int ti_first, double share, bool only_looked) {
     constexpr uint32_t kMostTiles = 16;
     Cut best{0, 0.0};
-    for (uint32_t k = 1; k <= kMostTiles; k += heads4 && k >= 4 ? 2 : 1) {      // (eight wavefronts: 512 rows at a time)
+    for (uint32_t k = 1; k <= kMostTiles; k += g <= 4 && k >= 4 ? 2 : 1) {      // (eight wavefronts: 512 rows at a time)
       const uint32_t rows = 256u * k;
       int64_t n_wg = 0;
       uint32_t tiles = 0;
@@ -1110,9 +1102,28 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       const bool look = n_wg <= 256 - room;
       if (only_looked && !look) continue;
       const LaunchTime& t = look ? alone : among;
-      const double rounds = static_cast<double>((n_wg + at_once - 1) / at_once), depth = static_cast<double>(tiles);
+      const double rounds = static_cast<double>((n_wg + 255) / 256), depth = static_cast<double>(tiles);
       const double time = t.start + (t.tile * depth + t.tile8 * share * std::max(0.0, depth - t.free8)) * rounds +
                           (t.chunk + t.partial / items) * static_cast<double>(n_wg) + t.byte * 1e-6 * static_cast<double>(total_cost);
+      if (best.rows == 0 || time < best.time) best = Cut{static_cast<int64_t>(rows), time};
+    }
+    return best;
+  };
+  const auto cut_channelwise = [&]() {
+    Cut best{0, 0.0};
+    for (uint32_t k = 1; k <= 16; k += k < 4 ? 1 : k < 8 ? 2 : 4) {
+      const uint32_t rows = 256u * k;
+      int64_t n_wg = 0, most = 0;
+      for (int64_t i = 0; i < n; ++i) {
+        int64_t slots = 0;
+        for (int ti = 0; ti < 4; ++ti) slots += (static_cast<uint32_t>(c->counts[i * 4 + ti]) + rows - 1) / rows;
+        n_wg += slots;
+        most = std::max(most, slots);
+      }
+      if (n_wg > 768 + 4 * n && k < 16) continue;
+      const double rounds = static_cast<double>((n_wg + round_chunks - 1) / round_chunks), at_once = static_cast<double>(most) / rounds;
+      const double time = 6.5 * rounds + (g > 4 ? 6.0 : 3.0) * k * static_cast<double>((n_wg + 255) / 256) + 0.07 * at_once +
+                          0.09 * std::max(0.0, at_once - 14.0);
       if (best.rows == 0 || time < best.time) best = Cut{static_cast<int64_t>(rows), time};
     }
     return best;
@@ -1120,12 +1131,14 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   const auto by_bytes = [&](int64_t cost) { return std::min<int64_t>(round_chunks, cost / floor_bytes); };      // its chunks
   const auto bytes_time = [&](int64_t cost) {
     const double partials = static_cast<double>(by_bytes(cost)) / items;
-    return g > 4 ? 8.6 + 0.155e-6 * static_cast<double>(cost) + 0.06 * partials : 8.1 + 0.118e-6 * static_cast<double>(cost) + 0.034 * partials;
+    return g > 4 ? 10.0 + 0.16e-6 * static_cast<double>(cost) + 0.06 * partials : 8.1 + 0.118e-6 * static_cast<double>(cost) + 0.034 * partials;
   };
   int64_t small_rows = 0;
-  if (total_cost > 0 && (mixed ? mixed_wide || total_cost <= round_chunks * floor_bytes : static_cast<double>(total_cost) <= kModelledCost)) {
+  if (mixed) {
+    if (total_cost > 0 && (mixed_wide || total_cost <= round_chunks * floor_bytes)) small_rows = cut_channelwise().rows;
+  } else if (total_cost > 0 && static_cast<double>(total_cost) <= kModelledCost) {
     const Cut cut = cut_by_rows(ti0, share8, false);
-    if (mixed || by_bytes(total_cost) <= 256 || cut.time < bytes_time(total_cost)) small_rows = cut.rows;
+    if (by_bytes(total_cost) <= 256 || cut.time < bytes_time(total_cost)) small_rows = cut.rows;
   }
   // A token-wise launch of at most 256 chunks takes the 16-bit rows along (decode_tiles_take_rows): one launch instead of
   // two that follow each other (three short sequences of keep / 4 bit / evict 11.7 -> 8 us).  They take what 8-bit rows do.

@@ -237,9 +237,9 @@ size_t rdkv_cache_max_table_bytes(const rdkv_config* cfg);
  *   out  DEVICE fp32 [batch][hq][d]
  *   lse  DEVICE fp32 [batch][hq] or NULL: natural-log sum of exp of the logits
  * An item with no retained token gives out = 0, lse = -inf.  One launch (two when a token-wise cache holds 16-bit
- * rows and has more than 256 chunks): the workgroup that finishes an item's last chunk merges the item's split
- * partials.  A cache keeps one split workspace per stream it is decoded on, so steps on different streams may
- * overlap (steps on one stream are serialised by the stream).  The workspace of the stream that built the cache
+ * rows and has more than 256 chunks), in which the items' split partials are merged as well.  A cache keeps one split
+ * workspace per stream it is decoded on, so steps on different streams may overlap, whatever shares the device (no step
+ * waits for a workgroup that has no place yet for longer than a moment; steps on one stream are serialised by the stream).  The workspace of the stream that built the cache
  * (or last rebuilt its schedule: rdkv_cache_reserve_tail, rdkv_cache_rebudget_tail) exists from the start; the
  * first step on any other stream allocates that stream's workspace through the cache's allocator.  A step issued
  * while its stream is under graph capture allocates nothing and uses that first workspace whatever the stream:

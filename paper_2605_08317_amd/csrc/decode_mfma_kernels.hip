@@ -218,39 +218,38 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
   float* s_acc = s_ml + ml_lds_floats(NWV, HS);     // finish_lds_floats(NWV, g)
   if constexpr (ROOMY) {
     if (ch.tier == kTierMerge) {
-      merge::merge_part<NWV>(ma, ch);
+      merge::merge_left<NWV>(ma, ch.item, ch.slot0, ch.nslots, merge::merge_part<NWV>(ma, ch));
       return;
     }
   }
+  uint32_t state = merge::kAbsent;
   if (ch.tier == kTierTail) {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
     const int rows = max(0, min(ch.rows, n_tail - ch.row0));
-    process_tail_tiles<HS, false, NWV, ROOMY>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, s_ml, s_acc, ma, co);
-    return;
-  }
-  if constexpr (!MULTI) {
+    state = process_tail_tiles<HS, false, NWV, ROOMY>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, s_ml, s_acc, ma, co);
+    if constexpr (!ROOMY) return;
+  } else if constexpr (!MULTI) {
 #define RDKV_ONE(TIER_)                                                                                           \
   {                                                                                                               \
     Run<HS> run;                                                                                                  \
     run.init();                                                                                                   \
     process_tiles<TIER_, HS, NWV, ROOMY>(arena + ch.k_data, arena + ch.k_meta, arena + ch.v_data, arena + ch.v_meta,     \
                                   ch.rows, g, qp, run);                                                           \
-    finish_chunk<HS, false, NWV, ROOMY>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                                  \
+    state = finish_chunk<HS, false, NWV, ROOMY>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                          \
   }
-    if constexpr (ROOMY) {
-      if (ch.tier == 16) {      // (launches without 16-bit chunks get less LDS)
-        process_rows_mfma<HS, true, NWV, true>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
-                                         nullptr, nullptr, &ma, &co);
-        return;
-      }
-    }
     switch (ch.tier) {
+      case 16:                  // (launches without 16-bit chunks get less LDS)
+        if constexpr (ROOMY)
+          state = process_rows_mfma<HS, true, NWV, true>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
+                                                         nullptr, nullptr, &ma, &co);
+        break;
       case 8: RDKV_ONE(8) break;
       case 4: RDKV_ONE(4) break;
       default: RDKV_ONE(2) break;
     }
 #undef RDKV_ONE
-    return;
   }
+  if constexpr (ROOMY) merge::merge_left<NWV>(ma, co.item, co.slot0, co.nslots, merge::blocks_left<NWV>(ma, co.slot0, state));
+  if constexpr (!MULTI) return;
   // The workgroup's pieces: runs of rows of the item's quantized tiers on one softmax state.  A share of an item's
   // work goes through the tiers in the order 2, 4, 8 bits, so the chain is at most three pieces long and the three
   // tier bodies follow each other in a straight line (a loop around a switch made the compiler spill the state).

@@ -58,7 +58,7 @@ struct LdsPlan {
 __device__ __forceinline__ int field_fb(int b, int f) { return b == 2 ? 2 * (f % 3) : b == 4 ? 4 * (f % 2) : 0; }
 
 template <int VT, int NW, int HS, int NWV>
-__device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __restrict__ arena,
+__device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t* __restrict__ arena,
                                               const ItemK* __restrict__ ikp, int g, const uint16_t* __restrict__ q,
                                               const MergeArgs& ma, const ChunkOut& co,
                                               uint8_t* smem, int lds_steps, int lds_qsteps, bool per_unit) {
@@ -470,7 +470,7 @@ __device__ __forceinline__ void process_mixed(const Chunk& ch, const uint8_t* __
     }
   }
 
-  finish_chunk<HS, true, NWV, NWV == 8>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
+  return finish_chunk<HS, true, NWV, NWV == 8>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
                                  reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
 }
 
@@ -484,21 +484,23 @@ __global__ __launch_bounds__(NWV * 64, (NW <= 32 && HS == 1) ? 3 : 2) void decod
   const uint16_t* qp = q + static_cast<int64_t>(ch.item) * g * kHeadDim;     // item = sequence x KV head
   const ChunkOut co{ch.item, ch.slot, ch.slot0, ch.nslots};
   const ItemK* ikp = items_k + ch.reserved;   // the K row layout of this chunk's (generation, item)
+  uint32_t state = merge::kAbsent;
   switch (ch.tier) {
     case kTierTail: {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
       const int rows = max(0, min(ch.rows, *tail_len - ch.row0));
-      process_tail_tiles<HS, true, NWV, NWV == 8>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, reinterpret_cast<float*>(smem),
+      state = process_tail_tiles<HS, true, NWV, NWV == 8>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, reinterpret_cast<float*>(smem),
                                         reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
       break;
     }
     case kTierMerge:
-      if constexpr (NWV == 8) merge::merge_part<NWV>(ma, ch);
-      break;
-    case 16: process_mixed<16, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
-    case 8: process_mixed<8, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
-    case 4: process_mixed<4, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
-    default: process_mixed<2, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+      if constexpr (NWV == 8) merge::merge_left<NWV>(ma, ch.item, ch.slot0, ch.nslots, merge::merge_part<NWV>(ma, ch));
+      return;
+    case 16: state = process_mixed<16, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+    case 8: state = process_mixed<8, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+    case 4: state = process_mixed<4, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+    default: state = process_mixed<2, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
   }
+  if constexpr (NWV == 8) merge::merge_left<NWV>(ma, co.item, co.slot0, co.nslots, merge::blocks_left<NWV>(ma, co.slot0, state));
 }
 
 template <int NW, int HS, int NWV>

@@ -62,7 +62,7 @@ __device__ __forceinline__ void pv_steps(const uint8_t* s_stage, int lane, const
 // TIERED: the chunk's partial goes to the split workspace for the launch's merging workgroups (LOOK) or is announced
 // (store_partial); otherwise plain stores for a merge kernel that follows.
 template <int HS, bool TIERED, int NWV, bool LOOK = false>
-__device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
+__device__ __forceinline__ uint32_t process_rows_mfma(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
                                                   int rows, int g, const uint16_t* __restrict__ q, uint8_t* smem,
                                                   float* __restrict__ part_acc, float* __restrict__ part_ml,
                                                   const MergeArgs* ma, const ChunkOut* co) {
@@ -139,7 +139,8 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
   // ---- end of the chunk: merge the workgroup's wavefronts, store the partial ---------------------------------------
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) run.l[hs] = head_sum(run.l[hs]);
-  if constexpr (TIERED) ends_soon<LOOK>(g, *ma, *co);
+  uint32_t state = merge::kAbsent;
+  if constexpr (TIERED) state = ends_soon<LOOK, NWV>(g, *ma, *co);
   __syncthreads();                      // the staging regions become the accumulator area
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) {
@@ -179,6 +180,7 @@ __device__ __forceinline__ void process_rows_mfma(const uint8_t* __restrict__ kd
       }
     }
   }
+  return state;
 }
 
 }  // namespace tile

@@ -343,6 +343,18 @@ __device__ __forceinline__ constexpr int ml_at(int wave, int head, int group) {
   return ((wave * HS * 4 + head) * kGroupsPerRow + group) * 4;
 }
 
+// A wavefront is through with its tiles: the merging wavefronts of its heads start to look at whole partials.  The state words
+// (decode_merge.h) come back, lane by lane; nothing waits for them here.
+template <bool LOOK, int NWV>
+__device__ __forceinline__ uint32_t ends_soon(int g, const MergeArgs& ma, const ChunkOut& co) {
+  uint32_t state = merge::kAbsent;
+  if constexpr (LOOK) {
+    const int block = merge::own_block<NWV>();
+    if (block < g * merge::kBlocks && co.nslots > 1) state = merge::clear_state(ma, co.slot, block, merge::kEndsSoon);
+  }
+  return state;
+}
+
 // Last part of a chunk's end, after s_ml and s_acc ([NWV][g][128] unnormalised sums times 1 / acc_scale, offset sums not
 // included, each relative to its wavefront's own maximum) are written: one barrier, then a wavefront per head weighs and adds
 // the NWV wavefronts' values, two channels a lane.  The weights are made once, lane w of each row of lanes that of wavefront
@@ -355,7 +367,12 @@ __device__ __forceinline__ void store_partial(float acc_scale, int g, const floa
   const bool single = co.nslots == 1;
   const int64_t qh0 = static_cast<int64_t>(co.item) * g;
   __syncthreads();
-  for (int head = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); head < g; head += NWV) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kHeads = (4 * HS + NWV - 1) / NWV;
+#pragma unroll
+  for (int k = 0; k < kHeads; ++k) {      // (in a loop that is one, the answer of ends_soon would be waited for in front of it)
+    const int head = wave + k * NWV;
+    if (head >= g) break;
     // row of lanes = channel group, which is that of the lane's two channels
     const float2 ml = *reinterpret_cast<const float2*>(s_ml + ml_at<HS>(lane & (NWV - 1), head, lane >> 4));
     float2 a[NWV];
@@ -398,26 +415,18 @@ __device__ __forceinline__ void store_partial(float acc_scale, int g, const floa
   }
 }
 
-// A chunk's first wavefront is through with its tiles: the item's merging workgroups start to look at whole partials.
-template <bool LOOK>
-__device__ __forceinline__ void ends_soon(int g, const MergeArgs& ma, const ChunkOut& co) {
-  if constexpr (LOOK)
-    if (threadIdx.x < g * merge::kBlocks && co.nslots > 1)
-      merge::store_agent(merge::look_record(ma, co.slot, threadIdx.x / merge::kBlocks, threadIdx.x % merge::kBlocks) + 18, 0.f);
-}
-
 // End of a chunk: take the lane's factor kappa = 2^lk out of the running sums, add the token halves of the accumulators and
 // the blocks' offset sums, and merge the workgroup's NWV wavefronts through LDS (store_partial; acc_scale = 2^24 where the V
 // codes entered as fp16 subnormals).
 // s_ml: ml_lds_floats(NWV, HS); s_acc: finish_lds_floats(NWV, g) floats.  ALIAS: the two areas overlap LDS that
 // the tile loop used, so a barrier separates the two uses.
 template <int HS, bool ALIAS, int NWV, bool LOOK>
-__device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, float lk, int g, float* s_ml,
-                                             float* s_acc, const MergeArgs& ma, const ChunkOut& co) {
+__device__ __forceinline__ uint32_t finish_chunk(Run<HS>& run, float acc_scale, float lk, int g, float* s_ml,
+                                                 float* s_acc, const MergeArgs& ma, const ChunkOut& co) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const float inv_kappa = __builtin_ldexpf(1.0f, static_cast<int>(-lk));   // lk is a small integer
-  ends_soon<LOOK>(g, ma, co);
+  const uint32_t state = ends_soon<LOOK, NWV>(g, ma, co);
   if constexpr (ALIAS) __syncthreads();
 #pragma unroll
   for (int hs = 0; hs < HS; ++hs) {
@@ -449,6 +458,7 @@ __device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, floa
     }
   }
   store_partial<HS, NWV, LOOK>(acc_scale, g, s_ml, s_acc, ma, co);
+  return state;
 }
 
 // A chunk of appended tokens (Sec. 3.3 Zone C: bf16 rows kept after the compression pass) on the same instruction
@@ -457,7 +467,7 @@ __device__ __forceinline__ void finish_chunk(Run<HS>& run, float acc_scale, floa
 // with sixteen coalesced 16-byte loads; V tile = 16 KiB in the layout of the 16-bit V tiles of mixed mode (lane
 // 32 (r / 32) + c % 32 holds channel c, eight tokens per 16-byte unit u = 4 (c / 32) + (r % 32) / 8 at 1024 u).
 template <int HS, bool ALIAS, int NWV, bool LOOK>
-__device__ __forceinline__ void process_tail_tiles(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
+__device__ __forceinline__ uint32_t process_tail_tiles(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
                                                    int rows, int g, const uint16_t* __restrict__ q,
                                                    float* s_ml, float* s_acc, const MergeArgs& ma,
                                                    const ChunkOut& co) {
@@ -535,7 +545,7 @@ __device__ __forceinline__ void process_tail_tiles(const uint8_t* __restrict__ k
 #undef RDKV_TAIL_GROUP
 #undef RDKV_TAIL_STEP
   }
-  finish_chunk<HS, ALIAS, NWV, LOOK>(run, 1.0f, 0.f, g, s_ml, s_acc, ma, co);
+  return finish_chunk<HS, ALIAS, NWV, LOOK>(run, 1.0f, 0.f, g, s_ml, s_acc, ma, co);
 }
 
 }  // namespace tile

@@ -1744,7 +1744,7 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
   const rdkv_status ws = workspace_for(c, st, &w);
   if (ws != RDKV_OK) return ws;
   const int g = c->hq / c->hkv;
-  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, g, merge_parts(g, c->n_items)};
+  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, g, merge_parts(g, c->n_items), c->looks};
   // every chunk of the schedule is launched, the tail's included: chunks of tail rows that do not exist yet find
   // the current length in the cache's device word and contribute an empty partial
   const int n16 = static_cast<int>(c->sched16), nrest = static_cast<int>(c->schedq + c->n_tail_chunks);
@@ -2212,6 +2212,10 @@ int32_t rdkv_k_row_words(const uint8_t* bits_ch) {
 }
 
 int32_t rdkv_k_row_words_max(void) { return kMaxKRowWords; }
+
+// Not part of the interface: how often the merging workgroups of this cache's decode launches look before they leave their
+// blocks to the chunks.  A test's way to have them give up at once.
+void rdkv_cache_set_looks(rdkv_cache* c, int32_t looks) { c->looks = looks; }
 
 size_t rdkv_cache_export_bytes(const rdkv_cache* c, int what) {
   if (!c) return 0;

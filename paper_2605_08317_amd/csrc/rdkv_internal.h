@@ -220,6 +220,7 @@ struct rdkv_cache {
   uint8_t* d_tail = nullptr;
   int64_t n_merge = 0;                  // merging workgroups of the schedule, behind the launched chunks in d_chunks: none
                                         // where the decode kernel counts arrivals (decode_merge.h)
+  int32_t looks = 256;                  // MergeArgs::looks: a look takes 1 us, a launch that looks at most 50
   int64_t n_tail_chunks = 0;            // chunks of the tail, appended to d_chunks in (chunk index, item) order:
                                         // the first ceil(tail_len / 256) * items of them are live
   int32_t tail_cap = 0, tail_len = 0;

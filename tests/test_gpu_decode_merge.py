@@ -1,6 +1,8 @@
 """The merging workgroups of small decode launches: slots per item on both sides of a batch of loads, every number of blocks
 per wavefront (which follows the number of items and of query heads), channel-wise keys, both sides of the line between a launch
 that looks and one that counts, and a workspace that every step leaves as it found it."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -65,3 +67,37 @@ def test_channelwise(T, g):
 def test_rows_per_chunk(seq_lens, hkv, widths, g):
     from paper_2605_08317_amd import binding as b
     _check(b, list(seq_lens), hkv, g, widths)
+
+
+# Merging workgroups that do not wait: whatever they find incomplete they leave to the wavefronts that store the partials.  Bits
+# and workspace are those of a launch whose merging workgroups wait, whoever merges (two queries in turn: a word that was not
+# put back would be the other query's).
+@pytest.mark.parametrize("seq_lens,hkv,g,widths,mixed", [
+    ((600,), 2, 4, [2], False), ((4097,), 1, 8, [2], False), ((30000,), 1, 4, [2], False), ((30600, 30600), 2, 4, [2], False),
+    ((150001,), 1, 1, [2], False), ((150001,), 1, 8, [8, 2], False), ((700,) * 25, 4, 2, [8, 2], False), ((700,) * 17, 2, 8, [8, 2], False),
+    ((3000, 20000), 4, 4, [16, 8, 4, 2], False), ((600, 9001), 2, 4, [8, 4, 2], True), ((700,) * 25, 4, 4, [8, 4, 2], True)])
+@pytest.mark.parametrize("looks", [0, 3])
+def test_merging_workgroups_that_give_up(seq_lens, hkv, g, widths, mixed, looks):
+    from paper_2605_08317_amd import binding as b
+    wl = W.scaled(W.CONFIGS["tiny"], batch=len(seq_lens), seq_lens=tuple(seq_lens), hq=g * hkv, hkv=hkv)
+    inp = W.make_inputs(wl, device="cpu")
+    rng = np.random.default_rng(sum(seq_lens) + g)
+    bits = torch.from_numpy(rng.choice(np.asarray(widths, np.uint8), size=sum(seq_lens) * hkv)).cuda()
+    bits_ch = torch.from_numpy(rng.choice(np.asarray([2, 4], np.uint8), size=len(seq_lens) * hkv * 128)).cuda() if mixed else None
+    cfg = b.Config(seq_lens, wl.hq, hkv, budget_bits=[2.0] * len(seq_lens), s_obs=wl.s_obs,
+                   k_mode=b.RDKV_K_CHANNELWISE if mixed else b.RDKV_K_TOKENWISE)
+    cache = b.rdkv_pack(cfg, inp["K"].cuda(), inp["V"].cuda(), bits, bits_ch)
+    print(f"[case] {len(seq_lens)} x {hkv} items, g {g}, looks {looks}, {cache.stats()['n_chunks']} chunks", flush=True)
+    assert mixed or cache.stats()["n_chunks"] <= 256
+    qs = [inp["q"].cuda(), -inp["q"].cuda()]
+    set_looks = b.lib.rdkv_cache_set_looks
+    set_looks.argtypes, set_looks.restype = [ctypes.c_void_p, ctypes.c_int32], None
+    want = [b.rdkv_decode_attn(cache, q) for q in qs]
+    assert not torch.equal(want[0][0], want[1][0])
+    for n in (looks, looks, 256):
+        set_looks(cache.h, n)
+        for _ in range(3):
+            for q, (out, lse) in zip(qs, want):
+                again, again_lse = b.rdkv_decode_attn(cache, q)
+                assert torch.equal(again, out) and torch.equal(again_lse, lse)
+    cache.free()

@@ -1,13 +1,15 @@
 """Thin binding of librdkv (include/rdkv.h): ctypes, and for the two calls of a
-decode loop native code (_rdkv_call, csrc/rdkv_call.cpp).
+decode loop native code (_rdkv_call, csrc/rdkv_call.cpp), which makes the same calls
+for less host time; where it does not load, ctypes makes them and a warning says so.
 
 Argument marshalling only: every step of the path runs in the HIP kernels of the
 shared library.  PyTorch supplies device memory and streams.  There is no CPU
-fallback: if either library is missing or fails to load, importing this module
+fallback: if the library is missing or fails to load, importing this module
 raises.
 """
 import ctypes
 import os
+import warnings
 
 import numpy as np
 import torch
@@ -123,10 +125,11 @@ def _load():
 lib = _load()
 try:
     from . import _rdkv_call as _call
+    _call.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.rdkv_decode_attn, lib.rdkv_cache_append)))
 except ImportError as e:
-    raise ImportError(f"_rdkv_call.so is not built or does not fit this PyTorch ({e}); "
-                      "run `python -c 'import __graft_entry__ as g; g.build()'`") from e
-_call.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.rdkv_decode_attn, lib.rdkv_cache_append)))
+    _call = None
+    warnings.warn(f"_rdkv_call.so is not built or does not fit this PyTorch ({e}): a decode step takes the host 2 us more; "
+                  "run `python -c 'import __graft_entry__ as g; g.build()'`")
 
 
 def _check(status):
@@ -281,7 +284,7 @@ def rdkv_compress(cfg, K, V, Q_obs):
 
 def rdkv_decode_attn(cache, q, out=None, lse=None):
     cfg = cache.cfg
-    done = _call.decode(cache.h, _stream(), len(cfg.seq_lens), cfg.hq, cfg.d, q, out, lse)
+    done = _call and _call.decode(cache.h, _stream(), len(cfg.seq_lens), cfg.hq, cfg.d, q, out, lse)
     if done is not None:
         if done[0] != RDKV_OK:
             _check(done[0])
@@ -299,7 +302,7 @@ def rdkv_cache_reserve_tail(cache, max_new_tokens):
 
 
 def rdkv_cache_append(cache, k_new, v_new):
-    status = _call.append(cache.h, _stream(), k_new, v_new)
+    status = _call and _call.append(cache.h, _stream(), k_new, v_new)
     if status is not None:
         return _check(status)
     _check(lib.rdkv_cache_append(cache.h, _ptr(k_new), _ptr(v_new), _stream()))

@@ -1,10 +1,15 @@
 """The decode loop's calls in native code: what they hand to the library, what they make, and what they leave to ctypes."""
+import os
+import subprocess
+import sys
 import threading
 
 import pytest
 import torch
 
 from paper_2605_08317_amd import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(scope="module")
@@ -69,3 +74,28 @@ def test_results_made_or_given_on_any_stream_and_thread(b):
     thread.join()
     assert not bad
     cache.free()
+
+
+def test_ctypes_serves_where_the_native_calls_do_not_load():
+    """The same errors, and a warning, without _rdkv_call: a missing or unfit one is not needed to import the binding."""
+    code = """
+import sys, types, warnings
+sys.modules["paper_2605_08317_amd._rdkv_call"] = None
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    from paper_2605_08317_amd import binding as b
+assert any("_rdkv_call" in str(x.message) for x in w), w
+import torch
+b._stream = lambda: 0
+q = torch.zeros(1, 2, 128, dtype=torch.bfloat16)
+cache = types.SimpleNamespace(h=None, cfg=types.SimpleNamespace(seq_lens=[5], hq=2, d=128))
+for call in (lambda: b.rdkv_decode_attn(cache, q), lambda: b.rdkv_cache_append(cache, q, q)):
+    try:
+        call()
+    except b.RdkvError as e:
+        assert e.status == 1
+    else:
+        raise SystemExit("no error")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr

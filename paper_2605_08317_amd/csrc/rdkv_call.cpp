@@ -3,8 +3,8 @@
 // A decode step of a short context takes the GPU 5.2 us.  Through ctypes it took the host 7.4: 3.6 in the call itself, 2.5 for
 // two result tensors made from Python and the rest for converting arguments one by one.  Here the tensors are unpacked and
 // made by PyTorch's C++ interface: 5.8 us per step (4K keys, 2 KV heads), a request of 32K keys and 64 tokens with results
-// given 1054 -> 988 us.  What is not a plain tensor call (an argument that is no tensor, one that is not contiguous) is left to
-// the ctypes path, which says what is wrong with it: the functions then return None.
+// given 1054 -> 988 us.  What is not a plain tensor call (an argument that is no tensor, one of a subclass, one that is not
+// contiguous) is left to the ctypes path, which says what is wrong with it: the functions then return None.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -23,7 +23,7 @@ decltype(&rdkv_cache_append) g_append = nullptr;
 
 // a contiguous tensor's memory
 bool pointer(PyObject* o, void** p) {
-  if (!THPVariable_Check(o)) return false;
+  if (!THPVariable_CheckExact(o)) return false;      // (a subclass has methods of its own)
   const at::Tensor& t = THPVariable_Unpack(o);
   if (!t.is_contiguous()) return false;
   *p = t.data_ptr();

@@ -44,6 +44,23 @@ def test_errors_are_those_of_the_library_and_of_ctypes(b, monkeypatch):
         b.rdkv_decode_attn(_NoCache("no handle"), q)
 
 
+def test_a_subclass_is_asked_for_its_memory(b, monkeypatch):
+    asked = []
+
+    class Own(torch.Tensor):
+        def data_ptr(self):
+            asked.append(1)
+            return super().data_ptr()
+    monkeypatch.setattr(b, "_stream", lambda: 0)
+    q = torch.zeros(1, 2, 128, dtype=torch.bfloat16)
+    for args in ((q.as_subclass(Own),), (q, q.float().as_subclass(Own)), (q, None, q.float().as_subclass(Own))):
+        with pytest.raises(b.RdkvError):
+            b.rdkv_decode_attn(_NoCache(None), *args)
+    with pytest.raises(b.RdkvError):
+        b.rdkv_cache_append(_NoCache(None), q, q.as_subclass(Own))
+    assert len(asked) == 4
+
+
 @pytest.mark.gpu
 def test_results_made_or_given_on_any_stream_and_thread(b):
     wl = W.scaled(W.CONFIGS["tiny"], seq_lens=(700,))

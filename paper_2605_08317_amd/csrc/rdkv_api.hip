@@ -577,14 +577,15 @@ void free_cache_buffers(rdkv_cache* c) {
   c->absorbed.clear();
 }
 
-// Memory of a split workspace for n_slots partials; the caller sets its first *absent bytes to merge::kAbsent, for a
-// launch that looks, and the *arrive bytes at w->arrive to zero.
-bool make_workspace(const rdkv_cache* c, hipStream_t st, int64_t n_slots, rdkv_cache::Workspace* w, size_t* absent, size_t* arrive) {
+// Memory of a split workspace for n_slots partials of a launch that looks for them or counts; the caller sets its first
+// *absent bytes to merge::kAbsent, for a launch that looks, and the *arrive bytes at w->arrive to zero.
+bool make_workspace(const rdkv_cache* c, hipStream_t st, int64_t n_slots, bool look, rdkv_cache::Workspace* w, size_t* absent,
+                    size_t* arrive) {
   Allocator al{c->alloc, c->free_, c->alloc_user};
   const int g = c->hq / c->hkv;
   const size_t slots = static_cast<size_t>(std::max<int64_t>(n_slots, 1));
-  const size_t acc_b = slots * g * merge::kRecordFloats * sizeof(float), ml_b = slots * g * 2 * sizeof(float);
-  *absent = acc_b;
+  const size_t acc_b = slots * g * (look ? merge::kRecordFloats : kHeadDim) * sizeof(float), ml_b = slots * g * 2 * sizeof(float);
+  *absent = look ? acc_b : 0;
   *arrive = static_cast<size_t>(std::max<int64_t>(c->n_items, 1)) * sizeof(int32_t);
   uint8_t* block = static_cast<uint8_t*>(al.get(acc_b + ml_b + *arrive));
   if (!block) return false;
@@ -610,9 +611,9 @@ rdkv_status workspace_for(const rdkv_cache* c, hipStream_t st, rdkv_cache::Works
   }
   rdkv_cache::Workspace w;
   size_t absent = 0, arrive = 0;
-  if (!make_workspace(c, st, c->n_slots, &w, &absent, &arrive)) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
+  if (!make_workspace(c, st, c->n_slots, c->n_merge > 0, &w, &absent, &arrive)) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
   hipError_t e = hipMemsetAsync(w.arrive, 0, arrive, st);     // (the kernels keep both so)
-  if (e == hipSuccess && c->n_merge > 0) e = hipMemsetAsync(w.block, 0xFF, absent, st);
+  if (e == hipSuccess && absent > 0) e = hipMemsetAsync(w.block, 0xFF, absent, st);
   if (e != hipSuccess) {
     Allocator{c->alloc, c->free_, c->alloc_user}.put(w.block);
     return fail(RDKV_ERR_HIP, "clearing a split workspace: %s", hipGetErrorString(e));
@@ -1893,7 +1894,7 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
   }
   rdkv_cache::Workspace w;   // this stream's workspace right away: a decode under graph capture then allocates nothing
   size_t absent = 0, arrive = 0;
-  const bool have_w = make_workspace(c, st, n_slots, &w, &absent, &arrive);   // (a failure is reported by the decode call that needs it)
+  const bool have_w = make_workspace(c, st, n_slots, n_merge > 0, &w, &absent, &arrive);   // (a failure is reported by the decode call that needs it)
   // tables up, the workspace and the caller's memory set in one launch; the stream must be idle before the old tables and
   // workspaces go: a decode step may still be reading them
   const size_t table_b = table.size() * sizeof(Chunk), items_b = items_sched.size() * sizeof(ItemK);
@@ -1908,7 +1909,7 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
     a.add(r.data + table_b, d_items_sched, static_cast<int64_t>(items_b), kSrcHost);
     a.fill(clear, clear_bytes, 0u, 0u);
     if (have_w) a.fill(w.arrive, static_cast<int64_t>(arrive), 0u, 0u);
-    if (have_w && n_merge > 0) a.fill(w.block, static_cast<int64_t>(absent), merge::kAbsent, merge::kAbsent);
+    if (have_w) a.fill(w.block, static_cast<int64_t>(absent), merge::kAbsent, merge::kAbsent);
     e = stage_launch(a, r, true, st);
   }
   if (e == hipSuccess) e = stage_stream_idle(st);

@@ -49,3 +49,51 @@ def test_allocator_hooks_round_trip():
         assert len(live) == 0                   # temporaries and the cache's buffers all came back
     assert np.array_equal(outs[0][0], outs[1][0])
     assert torch.equal(outs[0][1], outs[1][1]) and torch.equal(outs[0][2], outs[1][2])
+
+
+# a workspace of another stream and that of a rebuilt schedule, for launches that look for their partials (128-byte lines) and for
+# launches that count (512 bytes per slot and head; two numbers each and a counter per item)
+@pytest.mark.parametrize("T,hkv,looks", [(4000, 2, True), (100000, 8, False)])
+def test_a_workspace_holds_what_its_launch_needs(T, hkv, looks):
+    b = B()
+    sizes, live = [], {}
+
+    @b._ALLOC_FN
+    def alloc(nbytes, user):
+        p = torch.cuda.caching_allocator_alloc(nbytes)
+        live[p] = nbytes
+        sizes.append(nbytes)
+        return p
+
+    @b._FREE_FN
+    def free(ptr, user):
+        del live[ptr]
+        torch.cuda.caching_allocator_delete(ptr)
+
+    g = 8
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    K = torch.randn((hkv * T, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    bits = torch.full((hkv * T,), 8, dtype=torch.uint8, device="cuda")
+    cfg = b.Config([T], g * hkv, hkv, budget_bits=[8.0], alloc=alloc, free_=free)
+    cache = b.rdkv_pack(cfg, K, K, bits, None)
+    assert (cache.stats()["n_chunks"] <= 256) == looks
+    q = torch.randn((1, g * hkv, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    out, lse = b.rdkv_decode_attn(cache, q)
+    per_slot = g * ((256 if looks else 128) + 2) * 4
+    for tail in (0, 100):
+        if tail:
+            sizes.clear()
+            b.rdkv_cache_reserve_tail(cache, tail)       # the tail, the table, the workspace
+            slots = cache.stats()["n_chunks"] + hkv
+            assert slots * per_slot + 4 * hkv in sizes, (slots, sizes)
+        sizes.clear()
+        stream = torch.cuda.Stream()
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            again, again_lse = b.rdkv_decode_attn(cache, q)
+        stream.synchronize()
+        slots = cache.stats()["n_chunks"] + (hkv if tail else 0)
+        assert sizes == [slots * per_slot + 4 * hkv]
+        assert tail or (torch.equal(again, out) and torch.equal(again_lse, lse))
+    cache.free()
+    assert not live

@@ -1,6 +1,7 @@
 """The merging workgroups of small decode launches: slots per item on both sides of a batch of loads, every number of blocks
 per wavefront (which follows the number of items and of query heads), channel-wise keys, both sides of the line between a launch
-that looks and one that counts, and a workspace that every step leaves as it found it."""
+that looks and one that counts, and a workspace that every step leaves as it found it.  (Channel-wise launches of eight-wavefront
+workgroups look whatever their number of chunks.)"""
 import ctypes
 
 import numpy as np
@@ -13,7 +14,7 @@ from paper_2605_08317_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def _check(b, seq_lens, hkv, g, widths, mixed=False):
+def _check(b, seq_lens, hkv, g, widths, mixed=False, few=None):
     wl = W.scaled(W.CONFIGS["tiny"], batch=len(seq_lens), seq_lens=tuple(seq_lens), hq=g * hkv, hkv=hkv)
     inp = W.make_inputs(wl, device="cpu")
     rng = np.random.default_rng(sum(seq_lens) + g)
@@ -23,18 +24,24 @@ def _check(b, seq_lens, hkv, g, widths, mixed=False):
     cfg = b.Config(seq_lens, wl.hq, hkv, budget_bits=[2.0] * len(seq_lens), s_obs=wl.s_obs,
                    k_mode=b.RDKV_K_CHANNELWISE if mixed else b.RDKV_K_TOKENWISE)
     cache = b.rdkv_pack(cfg, inp["K"].cuda(), inp["V"].cuda(), flat(bits), flat(bits_ch) if mixed else None)
-    print(f"[case] {len(seq_lens)} x {hkv} items, g {g}, {cache.stats()['n_chunks']} chunks", flush=True)
-    q = inp["q"].cuda()
-    out, lse = b.rdkv_decode_attn(cache, q)
+    chunks = cache.stats()["n_chunks"]
+    print(f"[case] {len(seq_lens)} x {hkv} items, g {g}, {chunks} chunks", flush=True)
+    assert few is None or (chunks <= 256) == few
+    # two queries in turn: what a step left behind would be the other query's partials
+    qs = [inp["q"].cuda(), -inp["q"].cuda()]
+    want = [b.rdkv_decode_attn(cache, q) for q in qs]
     for _ in range(3):
-        again, again_lse = b.rdkv_decode_attn(cache, q)
-        assert torch.equal(again, out) and torch.equal(again_lse, lse)
+        for q, (out, lse) in zip(qs, want):
+            again, again_lse = b.rdkv_decode_attn(cache, q)
+            assert torch.equal(again, out) and torch.equal(again_lse, lse)
     split = lambda x: [y.float().numpy() for y in W.split_sequences(x, seq_lens, hkv, 128)]
     build = O.build_cache_mixed if mixed else O.build_cache_tokenwise
-    ref_out, ref_lse = O.decode(build(split(inp["K"]), split(inp["V"]), bits, *([bits_ch] if mixed else [])), inp["q"].float().numpy())
-    err = np.abs(out.cpu().numpy() - ref_out).max(-1) / np.abs(ref_out).max(-1)
-    assert err.max() <= 2e-3          # as in the other decode tests: fp16 products of probability and scale
-    np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, rtol=1e-4, atol=1e-4)
+    ref = build(split(inp["K"]), split(inp["V"]), bits, *([bits_ch] if mixed else []))
+    for q, (out, lse) in zip(qs, want):
+        ref_out, ref_lse = O.decode(ref, q.cpu().float().numpy())
+        err = np.abs(out.cpu().numpy() - ref_out).max(-1) / np.abs(ref_out).max(-1)
+        assert err.max() <= 2e-3          # as in the other decode tests: fp16 products of probability and scale
+        np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, rtol=1e-4, atol=1e-4)
     cache.free()
 
 
@@ -45,11 +52,13 @@ def test_slots_of_one_item(T, g):
     _check(b, [T], 1, g, [2])
 
 
-@pytest.mark.parametrize("batch,hkv", [(1, 3), (2, 8), (17, 2), (33, 1), (9, 8), (25, 4)])
+# two chunks per item: the last number of items whose launch looks and the first whose launch counts among them
+@pytest.mark.parametrize("batch,hkv,few", [(1, 3, True), (2, 8, True), (17, 2, True), (33, 1, True), (9, 8, True), (25, 4, True),
+                                           (16, 8, True), (43, 3, False)])
 @pytest.mark.parametrize("g", [1, 2, 4, 8])
-def test_numbers_of_items(batch, hkv, g):
+def test_numbers_of_items(batch, hkv, few, g):
     from paper_2605_08317_amd import binding as b
-    _check(b, [700 - 3 * s for s in range(batch)], hkv, g, [8, 2])
+    _check(b, [700 - 3 * s for s in range(batch)], hkv, g, [8, 2], few=few)
 
 
 @pytest.mark.parametrize("T", [600, 9001])
@@ -59,14 +68,22 @@ def test_channelwise(T, g):
     _check(b, [T], 2, g, [8, 4, 2, 0], mixed=True)
 
 
-# one and two tiles per SIMD, the last cut that looks and the first that counts, tiers that all end in a remainder
-@pytest.mark.parametrize("seq_lens,hkv,widths", [((257,), 1, [2]), ((512, 65), 2, [8]), ((30600, 30600), 2, [2]),
-                                                 ((61400,), 2, [4]), ((5000, 70, 12001), 8, [8, 4, 2]),
-                                                 ((20000, 1), 4, [16, 8, 4, 2]), ((3000,) * 12, 8, [8, 2])])
-@pytest.mark.parametrize("g", [1, 4, 8])
-def test_rows_per_chunk(seq_lens, hkv, widths, g):
+# more chunks, and more items with merging workgroups, than the chip has places
+@pytest.mark.parametrize("batch,hkv,T", [(33, 8, 300), (13, 8, 1100)])
+def test_channelwise_with_many_items(batch, hkv, T):
     from paper_2605_08317_amd import binding as b
-    _check(b, list(seq_lens), hkv, g, widths)
+    _check(b, [T - s for s in range(batch)], hkv, 4, [8, 4, 2], mixed=True, few=False)
+
+
+# one and two tiles per SIMD, as many chunks as a launch that looks has beside room for a tail, a launch that counts, tiers that
+# all end in a remainder
+@pytest.mark.parametrize("seq_lens,hkv,widths,few", [
+    ((257,), 1, [2], True), ((512, 65), 2, [8], True), ((30600, 30600), 2, [2], True), ((61400,), 2, [4], True),
+    ((5000, 70, 12001), 8, [8, 4, 2], True), ((20000, 1), 4, [16, 8, 4, 2], True), ((3000,) * 12, 8, [8, 2], False)])
+@pytest.mark.parametrize("g", [1, 4, 8])
+def test_rows_per_chunk(seq_lens, hkv, widths, few, g):
+    from paper_2605_08317_amd import binding as b
+    _check(b, list(seq_lens), hkv, g, widths, few=few)
 
 
 # Merging workgroups that do not wait: whatever they find incomplete they leave to the wavefronts that store the partials.  Bits

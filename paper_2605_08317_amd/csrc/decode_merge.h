@@ -22,18 +22,18 @@
 //
 // What bounds the wait of a merging workgroup.  Workgroups are dispatched in the order of the grid on each XCD, but an item's
 // chunks are on all of them, and launches on other streams and of other processes share them: merging workgroups of several
-// launches could hold all places of the XCDs that each other's chunks need.  So a merging wavefront waits for a chunk that has
-// no place yet for a while only (MergeArgs::looks), then hands its blocks over (give_up), and holds no place any more.
+// launches could hold all places of the XCDs that each other's chunks need.  So a merging wavefront waits for chunks that may
+// have no place yet for a while only (MergeArgs::looks), then hands its block over (give_up), and holds no place any more.
 //   Each line has a state word, of which either side clears a bit of its own in one atomic that returns what the other has
 // cleared: a chunk's wavefront when it is through with its tiles (that is also the news that it ends soon; the answer is there
-// by the time that its partial is stored, and costs the launch nothing), a merging wavefront when it gives up.  Where the chunk
-// came first, its workgroup runs and waits for nothing, and the merging wavefront waits for its partial.  Then it sets
-// the block's hand-over word and looks once more.  Where the merging wavefront came first, the chunk's wavefront finds it out,
-// waits until its own stores have landed, reads the hand-over word, and if it is set looks once.  Of all these take the one
-// whose partial landed last: if it read the word before it was set, all partials had landed by then, and the merging wavefront's
-// last look finds them; otherwise its own look does.  Who finds all of them takes the block by a compare-and-exchange on the
-// hand-over word, and only the taker puts words back and writes the output.  A partial is complete only with its chunk's bit
-// cleared, so no atomic is under way when words are put back.
+// by the time that its partial is stored), a merging wavefront when it gives up.  Where the chunk came first, its workgroup runs
+// and waits for nothing, and a merging wavefront may wait for its partial: it does so once all chunks of the item have come, and,
+// after it has given up, for those that had.  Then it sets the block's hand-over word and looks once more.  Where the merging
+// wavefront came first, the chunk's wavefront finds it out, waits until its own stores have landed, reads the hand-over word, and
+// if it is set looks once.  Of all these take the one whose partial landed last: if it read the word before it was set, all
+// partials had landed by then, and the merging wavefront's last look finds them; otherwise its own look does.  Who finds all of
+// them takes the block by a compare-and-exchange on the hand-over word, and only the taker puts words back and writes the
+// output.  No words are put back before every chunk's bit is cleared, so no atomic is under way then.
 #pragma once
 #include "rdkv_internal.h"
 #include "wave_ops.h"
@@ -47,7 +47,7 @@ struct MergeArgs {
   float* out;          // [batch][hq][128]
   float* lse;          // [batch][hq] or null
   int32_t g;           // query heads per KV head: item i (sequence x KV head) owns output rows i g .. i g + g - 1
-  int32_t parts;       // merging workgroups of an item, 8 g / parts blocks each
+  int32_t parts;       // merging workgroups of an item, 8 g / parts blocks each, a wavefront each; 0: the launch counts
   int32_t looks;       // how often they look before they leave their blocks to the chunks (rdkv_cache::looks)
 };
 
@@ -71,11 +71,10 @@ constexpr uint32_t kAbsent = 0xFFFFFFFFu;
 constexpr uint32_t kEndsSoon = 1, kGivenUp = 2;
 constexpr uint32_t kReady = 0;
 constexpr int kStateWord = 18, kHandOverWord = 19;
-constexpr int kMostLooks = 1 << 20;       // of give_up at a running chunk, seconds: should two steps use one workspace at a time
+constexpr int kMostLooks = 1 << 20;       // at chunks that run (seconds): should two steps share a workspace, which is not allowed
 constexpr int kSc1 = 16;                  // cache policy of the buffer accesses: agent scope
 
 using uint4v = __attribute__((ext_vector_type(4))) unsigned;
-using uint3v = __attribute__((ext_vector_type(3))) unsigned;
 using uint2v = __attribute__((ext_vector_type(2))) unsigned;
 
 // v, with another NaN in place of kAbsent
@@ -106,8 +105,6 @@ __device__ __forceinline__ uint32_t* look_word(const MergeArgs& ma, int slot, in
 __device__ __forceinline__ uint32_t clear_state(const MergeArgs& ma, int slot, int block, uint32_t bit) {
   return __hip_atomic_fetch_and(look_word(ma, slot, block, kStateWord), ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// kAbsent as long as the chunk has not said that it ends soon
-__device__ __forceinline__ uint32_t ends_soon_or_absent(uint32_t state) { return state | ~kEndsSoon; }
 __device__ __forceinline__ bool take_block(const MergeArgs& ma, int slot0, int block) {
   uint32_t ready = kReady;
   bool mine = false;
@@ -232,168 +229,156 @@ __device__ __forceinline__ void arrive_and_merge(const MergeArgs& ma, int item, 
   if (tid == 0) __hip_atomic_store(ma.arrive + item, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One wavefront: C blocks of 16 channels, block0 + k block_step counted over the heads of the item.
+// All chunks of an item say that they end soon, in the lines of a block.  ONCE: at the first look; otherwise after at most looks
+// of them.
+template <bool ONCE>
+__device__ __forceinline__ bool all_end_soon(const MergeArgs& ma, int slot0, int nslots, int block) {
+  constexpr int kLoads = 4;
+  const int step = ma.g * kRecordFloats * 4;      // bytes from slot to slot
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(ma.part_acc + static_cast<int64_t>(slot0) * ma.g * kRecordFloats, 0,
+                                                      nslots * step, 0x00027000);
+  const int at = (threadIdx.x & 63) * step + (block * kBlockFloats + kStateWord) * 4;
+  int tries = 0;
+  for (int base = 0; base < nslots; base += 64 * kLoads)
+    for (;;) {
+      uint32_t state[kLoads], most = 0;
+#pragma unroll
+      for (int u = 0; u < kLoads; ++u)            // (past the last slot: zero)
+        state[u] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (base + u * 64) * step + at, 0, kSc1);
+      asm volatile("" ::: "memory");              // (load again next time)
+#pragma unroll
+      for (int u = 0; u < kLoads; ++u) most = max(most, state[u] | ~kEndsSoon);
+      if (!__any(most == kAbsent)) break;
+      if (ONCE || ++tries >= ma.looks) return false;
+    }
+  return true;
+}
+
+// One wavefront, after all_end_soon: a block of 16 channels, counted over the heads of the item.
 // lane = (slot group of sixteen, four neighbouring channels); BATCH slots of a lane at a time, all loads of a batch in flight
 // together and repeated until none of their words is absent; then the slot groups are added across the lanes.  No LDS and no
 // barrier: what a workgroup's wavefronts exchange they would wait for (a slot group per half wavefront and the rest through
 // LDS took 1.2 us from the last word's arrival, this 0.5).  What bounds it then are requests: two per slot and block, eight
 // wavefronts of 32 workgroups, made 16 MB layers 10.8 us; a line per block and 64 workgroups 9.3, 128 of them 9.2.
-// False, and nothing is changed in memory: words are still absent after ma.looks looks, or (ONCE: one look at a block that a
-// merging wavefront left) after that look, or another wavefront has taken the block.
-template <int C, int BATCH, bool ONCE>
-__device__ __forceinline__ bool merge_blocks(const MergeArgs& ma, int item, int slot0, int nslots, int block0, int block_step) {
-  static_assert(!ONCE || C == 1, "blocks are taken one by one");
+// ONCE: one look at a block that its merging wavefront left to the chunks; nothing happens if words are still absent, or if
+// another wavefront has taken the block.
+template <int BATCH, bool ONCE>
+__device__ __forceinline__ void merge_block(const MergeArgs& ma, int item, int slot0, int nslots, int block) {
   constexpr int SG = 16;
   const int lane = threadIdx.x & 63, sg = lane >> 2, col = lane & 3;
   const int step = ma.g * kRecordFloats * 4;      // bytes from slot to slot
   // loads past the last slot return zeros, stores there are dropped (the buffer's bounds)
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(ma.part_acc + static_cast<int64_t>(slot0) * ma.g * kRecordFloats, 0,
                                                       nslots * step, 0x00027000);
-  const auto ml_at = [&](int c) { return (block0 + c * block_step) * (kBlockFloats * 4) + 64; };
-  const auto acc_at = [&](int c) { return (block0 + c * block_step) * (kBlockFloats * 4) + col * 16; };
-  int tries = 0;
-  // "Ends soon" first, until all slots of the first batch say so: the loads of whole partials would take their bandwidth from
-  // the chunks.  (It takes a chunk 1 us from there to its stores, and the news a little less to come here.)
-  if constexpr (!ONCE) {
-    for (;;) {
-      uint32_t soon[BATCH], most = 0;
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u)             // (past the last slot: zero)
-        soon[u] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (u * SG + sg) * step + ml_at(0) + 8, 0, kSc1);
-      asm volatile("" ::: "memory");              // (load again next time)
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) most = max(most, ends_soon_or_absent(soon[u]));
-      if (!__any(most == kAbsent)) break;
-      if (++tries >= ma.looks) return false;
-    }
-  }
-  float m_run[C], l_run[C], o_run[C][4];
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    m_run[c] = kNegBig;
-    l_run[c] = 0.f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o_run[c][k] = 0.f;
-  }
-  struct Slots {
-    uint4v a[C][BATCH];
-    uint3v ml[C][BATCH];
-  };
-  // All words of the blocks absent again, once the last of them has been read: what gives up between two batches must leave
-  // the first one to others.
-  const auto put_back = [&]() __attribute__((always_inline)) {
+  const int ml_at = block * (kBlockFloats * 4) + 64, acc_at = block * (kBlockFloats * 4) + col * 16;
+  const auto put_back = [&](int base) __attribute__((always_inline)) {
     const uint4v absent = {kAbsent, kAbsent, kAbsent, kAbsent};
-    for (int s = sg * step; s - sg * step < nslots * step; s += SG * step)
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        __builtin_amdgcn_raw_buffer_store_b128(absent, rsrc, s + acc_at(c), 0, kSc1);
-        if (col == 0) __builtin_amdgcn_raw_buffer_store_b128(absent, rsrc, s + ml_at(c), 0, kSc1);
-      }
+    for (int u = 0; u < BATCH; ++u) {
+      const int s = (base + u * SG + sg) * step;
+      __builtin_amdgcn_raw_buffer_store_b128(absent, rsrc, s + acc_at, 0, kSc1);
+      if (col == 0) __builtin_amdgcn_raw_buffer_store_b128(absent, rsrc, s + ml_at, 0, kSc1);
+    }
+  };
+  struct Slots {
+    uint4v a[BATCH];
+    uint2v ml[BATCH];
   };
   Slots x, y;                                     // two looks under way, half a round trip apart
+  float m_run = kNegBig, l_run = 0.f, o_run[4] = {0.f, 0.f, 0.f, 0.f};
+  int tries = 0;
   for (int base = 0; base < nslots; base += SG * BATCH) {
     const auto load = [&](Slots& v) __attribute__((always_inline)) {
 #pragma unroll
-      for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-          const int s = (base + u * SG + sg) * step;
-          v.ml[c][u] = __builtin_amdgcn_raw_buffer_load_b96(rsrc, s + ml_at(c), 0, kSc1);
-          v.a[c][u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, s + acc_at(c), 0, kSc1);
-        }
+      for (int u = 0; u < BATCH; ++u) {
+        const int s = (base + u * SG + sg) * step;
+        v.ml[u] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, s + ml_at, 0, kSc1);
+        v.a[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, s + acc_at, 0, kSc1);
+      }
       asm volatile("" ::: "memory");
     };
     const auto complete = [&](const Slots& v) __attribute__((always_inline)) {
       uint32_t most = 0;                          // kAbsent is the largest word
 #pragma unroll
-      for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-          most = max(max(max(most, v.ml[c][u].x), v.ml[c][u].y), ends_soon_or_absent(v.ml[c][u].z));
-          most = max(max(most, v.a[c][u].x), v.a[c][u].y);
-          most = max(max(most, v.a[c][u].z), v.a[c][u].w);
-        }
+      for (int u = 0; u < BATCH; ++u) {
+        most = max(max(most, v.ml[u].x), v.ml[u].y);
+        most = max(max(most, v.a[u].x), v.a[u].y);
+        most = max(max(most, v.a[u].z), v.a[u].w);
+      }
       return !__any(most == kAbsent);
     };
     Slots z;
     load(x);
     if constexpr (ONCE) {
-      if (!complete(x)) return false;
+      if (!complete(x)) return;
       z = x;
     } else {
       for (;;) {
         load(y);
-        if (complete(x)) { z = x; break; }
+        if (complete(x) || ++tries >= kMostLooks) { z = x; break; }
         load(x);
-        if (complete(y)) { z = y; break; }
-        if ((tries += 2) >= ma.looks) return false;
+        if (complete(y) || ++tries >= kMostLooks) { z = y; break; }
       }
-      if (base + SG * BATCH >= nslots) put_back();
+      put_back(base);
     }
+    float mb = m_run, mv[BATCH];
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      float mb = m_run[c], mv[BATCH];
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        mv[u] = base + u * SG + sg < nslots ? __uint_as_float(z.ml[c][u].x) : kNegBig;
-        mb = fmaxf(mb, mv[u]);
-      }
-      const float f0 = __builtin_amdgcn_exp2f(m_run[c] - mb);
-      l_run[c] *= f0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o_run[c][k] *= f0;
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const float f = __builtin_amdgcn_exp2f(mv[u] - mb);
-        l_run[c] = __builtin_fmaf(__uint_as_float(z.ml[c][u].y), f, l_run[c]);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o_run[c][k] = __builtin_fmaf(__uint_as_float(z.a[c][u][k]), f, o_run[c][k]);
-      }
-      m_run[c] = mb;
+    for (int u = 0; u < BATCH; ++u) {
+      mv[u] = base + u * SG + sg < nslots ? __uint_as_float(z.ml[u].x) : kNegBig;
+      mb = fmaxf(mb, mv[u]);
     }
+    const float f0 = __builtin_amdgcn_exp2f(m_run - mb);
+    l_run *= f0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o_run[k] *= f0;
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const float f = __builtin_amdgcn_exp2f(mv[u] - mb);
+      l_run = __builtin_fmaf(__uint_as_float(z.ml[u].y), f, l_run);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o_run[k] = __builtin_fmaf(__uint_as_float(z.a[u][k]), f, o_run[k]);
+    }
+    m_run = mb;
   }
   if constexpr (ONCE) {
-    if (!take_block(ma, slot0, block0)) return false;
-    put_back();
+    if (!take_block(ma, slot0, block)) return;
+    for (int base = 0; base < nslots; base += SG * BATCH) put_back(base);
   }
+  const float mm = head_max(m_run);
+  const float f = __builtin_amdgcn_exp2f(m_run - mm);
+  const float l = head_sum(l_run * f);
+  // the sums over the slot groups, the four channels turned into the four rows of lanes on the way
+  float o[4];
 #pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const float mm = head_max(m_run[c]);
-    const float f = __builtin_amdgcn_exp2f(m_run[c] - mm);
-    const float l = head_sum(l_run[c] * f);
-    // the sums over the slot groups, the four channels turned into the four rows of lanes on the way
-    float o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = o_run[c][k] * f;
-    swap_rows(o[0], o[1]);
-    swap_rows(o[2], o[3]);
-    float lo = o[0] + o[1], hi = o[2] + o[3];
-    swap_halves(lo, hi);
-    float v = lo + hi;
-    v += dpp_f32<0x124>(v);
-    v += dpp_f32<0x128>(v);
-    const int block = block0 + c * block_step;
-    if ((lane & 12) == 0)
-      ma.out[static_cast<int64_t>(item) * ma.g * kHeadDim + block * 16 + 4 * col + (lane >> 4)] = l > 0.f ? v / l : 0.f;
-    if (lane == 0 && block % kBlocks == 0 && ma.lse != nullptr)
-      ma.lse[static_cast<int64_t>(item) * ma.g + block / kBlocks] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
-  }
+  for (int k = 0; k < 4; ++k) o[k] = o_run[k] * f;
+  swap_rows(o[0], o[1]);
+  swap_rows(o[2], o[3]);
+  float lo = o[0] + o[1], hi = o[2] + o[3];
+  swap_halves(lo, hi);
+  float v = lo + hi;
+  v += dpp_f32<0x124>(v);
+  v += dpp_f32<0x128>(v);
+  if ((lane & 12) == 0)
+    ma.out[static_cast<int64_t>(item) * ma.g * kHeadDim + block * 16 + 4 * col + (lane >> 4)] = l > 0.f ? v / l : 0.f;
+  if (lane == 0 && block % kBlocks == 0 && ma.lse != nullptr)
+    ma.lse[static_cast<int64_t>(item) * ma.g + block / kBlocks] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
   // The look that was not needed is still on its way: its registers must not be used for anything before (that would wait for
   // it: 0.8 us).
   if constexpr (!ONCE) {
 #pragma unroll
-    for (int c = 0; c < C; ++c)
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) asm volatile("" ::"v"(x.a[c][u]), "v"(x.ml[c][u]), "v"(y.a[c][u]), "v"(y.ml[c][u]));
+    for (int u = 0; u < BATCH; ++u) asm volatile("" ::"v"(x.a[u]), "v"(x.ml[u]), "v"(y.a[u]), "v"(y.ml[u]));
   }
-  return true;
 }
 
-template <int NWV>
-__device__ __forceinline__ int blocks_per_wave(const MergeArgs& ma) { return max(1, ma.g * kBlocks / ma.parts / NWV); }
 // slots of a lane at a time: the same whoever merges, since the order of the sums depends on it
-__device__ __forceinline__ int batch_of(int per_wave, int nslots) {
-  return per_wave == 1 ? (nslots <= 32 ? 2 : 4) : per_wave == 2 ? (nslots <= 16 ? 1 : 2) : 1;
+template <bool ONCE>
+__device__ __forceinline__ void merge_block(const MergeArgs& ma, int item, int slot0, int nslots, int block) {
+  if (nslots <= 32) merge_block<2, ONCE>(ma, item, slot0, nslots, block);
+  else merge_block<4, ONCE>(ma, item, slot0, nslots, block);
+}
+// (a look at the state words as well: no atomic of a chunk may be under way when words are put back)
+__device__ __forceinline__ void merge_if_complete(const MergeArgs& ma, int item, int slot0, int nslots, int block) {
+  if (all_end_soon<true>(ma, slot0, nslots, block)) merge_block<true>(ma, item, slot0, nslots, block);
 }
 
 // lane -> a block of the heads whose partials this wavefront stores (heads wave, wave + NWV, ..; from 8 g on: none)
@@ -403,81 +388,52 @@ __device__ __forceinline__ int own_block() {
   return (static_cast<int>(threadIdx.x >> 6) + lane / kBlocks * NWV) * kBlocks + lane % kBlocks;
 }
 
-// A merging wavefront leaves its blocks to the chunks, except for what it need not be afraid of waiting for: the slots whose
-// workgroups are through with their tiles.  The blocks, one bit each.
-__device__ __forceinline__ uint64_t give_up(const MergeArgs& ma, int slot0, int nslots, int block0, int block_step, int n) {
+// A merging wavefront leaves its block to the chunks, except for what it need not be afraid of waiting for: the slots whose
+// workgroups are through with their tiles.
+__device__ __forceinline__ void give_up(const MergeArgs& ma, int slot0, int nslots, int block) {
   const int lane = threadIdx.x & 63;
-  uint64_t blocks = 0;
-  for (int k = 0; k < n; ++k) {
-    const int block = block0 + k * block_step;
-    blocks |= 1ull << block;
-    for (int s = lane; s < nslots; s += 64) {
-      if (clear_state(ma, slot0 + s, block, kGivenUp) & kEndsSoon) continue;
-      for (int tries = 0; tries < kMostLooks; ++tries) {
-        uint32_t most = 0;
-        for (int w = 0; w < kStateWord; ++w)
-          most = max(most, __hip_atomic_load(look_word(ma, slot0 + s, block, w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if (most != kAbsent) break;
-      }
+  for (int s = lane; s < nslots; s += 64) {
+    if (clear_state(ma, slot0 + s, block, kGivenUp) & kEndsSoon) continue;
+    for (int tries = 0; tries < kMostLooks; ++tries) {
+      uint32_t most = 0;
+      for (int w = 0; w < kStateWord; ++w)
+        most = max(most, __hip_atomic_load(look_word(ma, slot0 + s, block, w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      if (most != kAbsent) break;
     }
   }
-  if ((blocks >> lane) & 1)
-    __hip_atomic_store(look_word(ma, slot0, lane, kHandOverWord), kReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane == 0)
+    __hip_atomic_store(look_word(ma, slot0, block, kHandOverWord), kReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   partial_stores_done();
-  return blocks;
 }
 
-// A merging workgroup of NWV wavefronts (a chunk of tier kTierMerge): part ch.row0 of the item's blocks.  What comes back are
-// the blocks of this wavefront, one bit each, that it has given up (merge_left).
+// A merging workgroup of NWV wavefronts (a chunk of tier kTierMerge): part ch.row0 of the item's blocks, one a wavefront.
 template <int NWV>
-__device__ __forceinline__ uint64_t merge_part(const MergeArgs& ma, const Chunk& ch) {
+__device__ __forceinline__ void merge_part(const MergeArgs& ma, const Chunk& ch) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int blocks = ma.g * kBlocks / ma.parts, block0 = ch.row0 * blocks + wave;
-  if (wave >= blocks) return 0;
-  // (merge_parts keeps a workgroup to four heads)
-  const int per_wave = blocks_per_wave<NWV>(ma), batch = batch_of(per_wave, ch.nslots);
-  bool done = true;
-  switch (per_wave) {
-    case 1:
-      done = batch == 2 ? merge_blocks<1, 2, false>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV)
-                        : merge_blocks<1, 4, false>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
-      break;
-    case 2:
-      done = batch == 1 ? merge_blocks<2, 1, false>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV)
-                        : merge_blocks<2, 2, false>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
-      break;
-    case 4: done = merge_blocks<4, 1, false>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV); break;
-    default:
-      if constexpr (NWV < 8) done = merge_blocks<8, 1, false>(ma, ch.item, ch.slot0, ch.nslots, block0, NWV);
+  const int blocks = ma.g * kBlocks / ma.parts, block = ch.row0 * blocks + wave;
+  if (wave >= blocks) return;
+  // "Ends soon" first: the loads of whole partials would take their bandwidth from the chunks.  (It takes a chunk 1 us from
+  // there to its stores, and the news a little less to come here.)
+  if (all_end_soon<false>(ma, ch.slot0, ch.nslots, block)) {
+    merge_block<false>(ma, ch.item, ch.slot0, ch.nslots, block);
+  } else {
+    give_up(ma, ch.slot0, ch.nslots, block);
+    merge_if_complete(ma, ch.item, ch.slot0, ch.nslots, block);
   }
-  if (done) return 0;
-  return give_up(ma, ch.slot0, ch.nslots, block0, NWV, per_wave);
 }
 
-// What a wavefront's heads' blocks have come to, of those whose partials it stores (store_partial), from the state words that it
-// cleared a bit of when it was through with its tiles: the blocks that it has to look at, for merge_left.
+// The end of a chunk's wavefront in a launch that looks, after store_partial.  state: of its heads' blocks, which it cleared a
+// bit of when it was through with its tiles (ends_soon).  One look at each block that its merging wavefront had left by then.
 template <int NWV>
-__device__ __forceinline__ uint64_t blocks_left(const MergeArgs& ma, int slot0, uint32_t state) {
-  if (!__any((state & kGivenUp) == 0)) return 0;
+__device__ __forceinline__ void merge_left(const MergeArgs& ma, int item, int slot0, int nslots, uint32_t state) {
+  if (__builtin_expect(!__any((state & kGivenUp) == 0), true)) return;
   partial_stores_done();
+  const int block = own_block<NWV>();
   uint32_t word = kAbsent;
   if ((state & kGivenUp) == 0)
-    word = __hip_atomic_load(look_word(ma, slot0, own_block<NWV>(), kHandOverWord), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  uint64_t blocks = 0;
-  for (uint64_t m = __ballot(word == kReady); m != 0; m &= m - 1) blocks |= 1ull << __builtin_amdgcn_readlane(own_block<NWV>(), __builtin_ctzll(m));
-  return blocks;
-}
-
-// One look at each of these blocks; those whose words are all there are merged by whoever takes them first.
-template <int NWV>
-__device__ __forceinline__ void merge_left(const MergeArgs& ma, int item, int slot0, int nslots, uint64_t blocks) {
-  const int batch = batch_of(blocks_per_wave<NWV>(ma), nslots);
-  for (; blocks != 0; blocks &= blocks - 1) {
-    const int block = __builtin_ctzll(blocks);
-    if (batch == 1) merge_blocks<1, 1, true>(ma, item, slot0, nslots, block, 0);
-    else if (batch == 2) merge_blocks<1, 2, true>(ma, item, slot0, nslots, block, 0);
-    else merge_blocks<1, 4, true>(ma, item, slot0, nslots, block, 0);
-  }
+    word = __hip_atomic_load(look_word(ma, slot0, block, kHandOverWord), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (uint64_t lanes = __ballot(word == kReady); lanes != 0; lanes &= lanes - 1)
+    merge_if_complete(ma, item, slot0, nslots, __builtin_amdgcn_readlane(block, __builtin_ctzll(lanes)));
 }
 
 // LDS floats arrive_and_merge needs for NT threads (a flag, at most NT / 32 maxima and sums, four sums per thread)

@@ -205,7 +205,7 @@ __device__ __forceinline__ void process_tiles(const uint8_t* __restrict__ kd, co
 
 // MULTI: workgroups may go through several tiers of their item (Chunk::next); without it every chunk is one tier and
 // the tier's body ends in its own copy of the chunk's end, which saves a latency-bound launch 0.3 us.
-template <int HS, int NWV, bool MULTI, bool ROOMY>
+template <int HS, int NWV, bool MULTI, bool ROOMY, bool LOOK>
 __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_tiles_kernel(
     const Chunk* __restrict__ chunks, const uint8_t* __restrict__ arena, const uint16_t* __restrict__ q,
     const int32_t* __restrict__ tail_len, int first, int g, MergeArgs ma) {
@@ -216,17 +216,17 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
   const ChunkOut co{ch.item, ch.slot, ch.slot0, ch.nslots};
   float* s_ml = reinterpret_cast<float*>(smem);
   float* s_acc = s_ml + ml_lds_floats(NWV, HS);     // finish_lds_floats(NWV, g)
-  if constexpr (ROOMY) {
+  if constexpr (LOOK) {
     if (ch.tier == kTierMerge) {
-      merge::merge_left<NWV>(ma, ch.item, ch.slot0, ch.nslots, merge::merge_part<NWV>(ma, ch));
+      merge::merge_part<NWV>(ma, ch);
       return;
     }
   }
   uint32_t state = merge::kAbsent;
   if (ch.tier == kTierTail) {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
     const int rows = max(0, min(ch.rows, n_tail - ch.row0));
-    state = process_tail_tiles<HS, false, NWV, ROOMY>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, s_ml, s_acc, ma, co);
-    if constexpr (!ROOMY) return;
+    state = process_tail_tiles<HS, false, NWV, LOOK>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, s_ml, s_acc, ma, co);
+    if constexpr (MULTI) return;
   } else if constexpr (!MULTI) {
 #define RDKV_ONE(TIER_)                                                                                           \
   {                                                                                                               \
@@ -234,12 +234,12 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
     run.init();                                                                                                   \
     process_tiles<TIER_, HS, NWV, ROOMY>(arena + ch.k_data, arena + ch.k_meta, arena + ch.v_data, arena + ch.v_meta,     \
                                   ch.rows, g, qp, run);                                                           \
-    state = finish_chunk<HS, false, NWV, ROOMY>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                          \
+    state = finish_chunk<HS, false, NWV, LOOK>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                           \
   }
     switch (ch.tier) {
       case 16:                  // (launches without 16-bit chunks get less LDS)
         if constexpr (ROOMY)
-          state = process_rows_mfma<HS, true, NWV, true>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
+          state = process_rows_mfma<HS, true, NWV, LOOK>(arena + ch.k_data, arena + ch.v_data, ch.rows, g, qp, smem,
                                                          nullptr, nullptr, &ma, &co);
         break;
       case 8: RDKV_ONE(8) break;
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
     }
 #undef RDKV_ONE
   }
-  if constexpr (ROOMY) merge::merge_left<NWV>(ma, co.item, co.slot0, co.nslots, merge::blocks_left<NWV>(ma, co.slot0, state));
+  if constexpr (LOOK) merge::merge_left<NWV>(ma, co.item, co.slot0, co.nslots, state);
   if constexpr (!MULTI) return;
   // The workgroup's pieces: runs of rows of the item's quantized tiers on one softmax state.  A share of an item's
   // work goes through the tiers in the order 2, 4, 8 bits, so the chain is at most three pieces long and the three
@@ -271,21 +271,21 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
   RDKV_PIECE(8)
 #undef RDKV_PIECE
   // ---- undo the subnormal unit, add the offsets, merge the wavefronts, hand the partial over -------------------
-  finish_chunk<HS, false, NWV, ROOMY>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);
+  finish_chunk<HS, false, NWV, LOOK>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);
 }
 
-template <int HS, int NWV, bool MULTI, bool ROOMY>
+template <int HS, int NWV, bool MULTI, bool ROOMY, bool LOOK>
 hipError_t launch_tiles(const Chunk* chunks, int first, int n_blocks, bool rows16, const uint8_t* arena, const uint16_t* q,
                         const MergeArgs& ma, const int32_t* tail_len, hipStream_t st) {
   size_t lds = (ml_lds_floats(NWV, HS) + finish_lds_floats(NWV, ma.g)) * sizeof(float);
   if constexpr (ROOMY)
     if (rows16) {
       constexpr size_t kRows = rows_lds_bytes<HS, NWV>();
-      hipError_t e = RDKV_ALLOW_LDS((decode_tiles_kernel<HS, NWV, MULTI, ROOMY>), kRows);
+      hipError_t e = RDKV_ALLOW_LDS((decode_tiles_kernel<HS, NWV, MULTI, ROOMY, LOOK>), kRows);
       if (e != hipSuccess) return e;
       lds = lds > kRows ? lds : kRows;
     }
-  hipLaunchKernelGGL((decode_tiles_kernel<HS, NWV, MULTI, ROOMY>), dim3(n_blocks), dim3(NWV * 64), lds, st, chunks, arena, q,
+  hipLaunchKernelGGL((decode_tiles_kernel<HS, NWV, MULTI, ROOMY, LOOK>), dim3(n_blocks), dim3(NWV * 64), lds, st, chunks, arena, q,
                      tail_len, first, ma.g, ma);
   return hipGetLastError();
 }
@@ -298,15 +298,15 @@ hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, int
                                const uint8_t* arena, const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len,
                                hipStream_t st) {
   if (n_chunks == 0) return hipSuccess;
-  const bool look = n_merge >= 0;
-  if (look && !decode_tiles_take_rows(n_chunks, multi)) return hipErrorInvalidValue;
-  if (rows16 && !look) return hipErrorInvalidValue;
+  const bool look = ma.parts > 0, roomy = decode_tiles_take_rows(n_chunks, multi);
+  if ((look || rows16) && !roomy) return hipErrorInvalidValue;
   // up to 4 query heads per KV head: one head set, workgroups of eight wavefronts; 8 heads: two head sets, workgroups of
   // four
 #define RDKV_TILES(HS_, NWV_)                                                                                             \
-  if (look) return launch_tiles<HS_, NWV_, false, true>(chunks, first, n_chunks + n_merge, rows16, arena, q, ma, tail_len, st); \
-  if (multi) return launch_tiles<HS_, NWV_, true, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st);      \
-  return launch_tiles<HS_, NWV_, false, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st);
+  if (look) return launch_tiles<HS_, NWV_, false, true, true>(chunks, first, n_chunks + n_merge, rows16, arena, q, ma, tail_len, st); \
+  if (roomy) return launch_tiles<HS_, NWV_, false, true, false>(chunks, first, n_chunks, rows16, arena, q, ma, tail_len, st);         \
+  if (multi) return launch_tiles<HS_, NWV_, true, false, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st); \
+  return launch_tiles<HS_, NWV_, false, false, false>(chunks, first, n_chunks, false, arena, q, ma, tail_len, st);
   if (ma.g > 4) {
     RDKV_TILES(2, 4)
   }

@@ -57,7 +57,7 @@ struct LdsPlan {
 // bit offset left after the copy shift of field f of a 16-bit half (tier b): the code reads as code * 2^fb * 2^-24
 __device__ __forceinline__ int field_fb(int b, int f) { return b == 2 ? 2 * (f % 3) : b == 4 ? 4 * (f % 2) : 0; }
 
-template <int VT, int NW, int HS, int NWV>
+template <int VT, int NW, int HS, int NWV, bool LOOK>
 __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t* __restrict__ arena,
                                               const ItemK* __restrict__ ikp, int g, const uint16_t* __restrict__ q,
                                               const MergeArgs& ma, const ChunkOut& co,
@@ -470,11 +470,11 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
     }
   }
 
-  return finish_chunk<HS, true, NWV, NWV == 8>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
+  return finish_chunk<HS, true, NWV, LOOK>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
                                  reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
 }
 
-template <int NW, int HS, int NWV>
+template <int NW, int HS, int NWV, bool LOOK>
 __global__ __launch_bounds__(NWV * 64, (NW <= 32 && HS == 1) ? 3 : 2) void decode_mixed_kernel(
     const Chunk* __restrict__ chunks, const uint8_t* __restrict__ arena, const ItemK* __restrict__ items_k,
     const uint16_t* __restrict__ q, const int32_t* __restrict__ tail_len, int lds_steps, int lds_qsteps, int per_unit,
@@ -488,31 +488,31 @@ __global__ __launch_bounds__(NWV * 64, (NW <= 32 && HS == 1) ? 3 : 2) void decod
   switch (ch.tier) {
     case kTierTail: {   // appended tokens: 64-token tiles of bf16 rows, as many rows as exist so far
       const int rows = max(0, min(ch.rows, *tail_len - ch.row0));
-      state = process_tail_tiles<HS, true, NWV, NWV == 8>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, reinterpret_cast<float*>(smem),
+      state = process_tail_tiles<HS, true, NWV, LOOK>(arena + ch.k_data, arena + ch.v_data, rows, g, qp, reinterpret_cast<float*>(smem),
                                         reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
       break;
     }
     case kTierMerge:
-      if constexpr (NWV == 8) merge::merge_left<NWV>(ma, ch.item, ch.slot0, ch.nslots, merge::merge_part<NWV>(ma, ch));
+      if constexpr (LOOK) merge::merge_part<NWV>(ma, ch);
       return;
-    case 16: state = process_mixed<16, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
-    case 8: state = process_mixed<8, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
-    case 4: state = process_mixed<4, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
-    default: state = process_mixed<2, NW, HS, NWV>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+    case 16: state = process_mixed<16, NW, HS, NWV, LOOK>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+    case 8: state = process_mixed<8, NW, HS, NWV, LOOK>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+    case 4: state = process_mixed<4, NW, HS, NWV, LOOK>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
+    default: state = process_mixed<2, NW, HS, NWV, LOOK>(ch, arena, ikp, g, qp, ma, co, smem, lds_steps, lds_qsteps, per_unit != 0); break;
   }
-  if constexpr (NWV == 8) merge::merge_left<NWV>(ma, co.item, co.slot0, co.nslots, merge::blocks_left<NWV>(ma, co.slot0, state));
+  if constexpr (LOOK) merge::merge_left<NWV>(ma, co.item, co.slot0, co.nslots, state);
 }
 
-template <int NW, int HS, int NWV>
+template <int NW, int HS, int NWV, bool LOOK>
 hipError_t launch_one(const Chunk* chunks, int n_chunks, const uint8_t* arena, const ItemK* items_k, int lds_steps,
                       int lds_qsteps, const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, int per_unit,
                       hipStream_t st) {
   const size_t lds = static_cast<size_t>(LdsPlan(lds_steps, lds_qsteps, HS, ma.g, NWV).total);
   if (lds > 48 * 1024) {
-    hipError_t e = RDKV_ALLOW_LDS((decode_mixed_kernel<NW, HS, NWV>), 160 * 1024);
+    hipError_t e = RDKV_ALLOW_LDS((decode_mixed_kernel<NW, HS, NWV, LOOK>), 160 * 1024);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((decode_mixed_kernel<NW, HS, NWV>), dim3(n_chunks), dim3(NWV * 64), lds, st, chunks, arena,
+  hipLaunchKernelGGL((decode_mixed_kernel<NW, HS, NWV, LOOK>), dim3(n_chunks), dim3(NWV * 64), lds, st, chunks, arena,
                      items_k, q, tail_len, lds_steps, lds_qsteps, per_unit, ma.g, ma);
   return hipGetLastError();
 }
@@ -526,8 +526,8 @@ hipError_t RDKV_MIXED_NAME(launch_decode_mixed_hs, RDKV_MIXED_HS, _long, RDKV_MI
     int max_qsteps, const uint16_t* q, const MergeArgs& ma, const int32_t* tail_len, int per_unit, int waves,
     hipStream_t st) {
   if (n_chunks == 0) return hipSuccess;
-#define RDKV_MIXED_LAUNCH(NW_, NWV_)                                                                            \
-  return launch_one<NW_, RDKV_MIXED_HS, NWV_>(chunks, n_chunks, arena, items_k, max_steps, max_qsteps, q, ma,   \
+#define RDKV_MIXED_LAUNCH(NW_, NWV_, LOOK_)                                                                     \
+  return launch_one<NW_, RDKV_MIXED_HS, NWV_, LOOK_>(chunks, n_chunks, arena, items_k, max_steps, max_qsteps, q, ma,   \
                                               tail_len, per_unit, st)
   // kMaxKRowWords = 68 is the longest row a channel bit map can give (125 channels at 16 bits and one each at 8, 4
   // and 2 bits: 64 + 1 + 1 + 1 words, padded to an even count); the host refuses anything longer
@@ -537,15 +537,19 @@ hipError_t RDKV_MIXED_NAME(launch_decode_mixed_hs, RDKV_MIXED_HS, _long, RDKV_MI
 #if RDKV_MIXED_LONG == 0
 #if RDKV_MIXED_HS == 1
   // eight-wavefront workgroups exist for up to four query heads per KV head and rows of up to 32 words
-  if (waves == 8 && max_words <= 16) RDKV_MIXED_LAUNCH(16, 8);
-  if (waves == 8 && max_words <= 32) RDKV_MIXED_LAUNCH(32, 8);
+  if (waves == 8 && ma.parts > 0) {
+    if (max_words <= 16) RDKV_MIXED_LAUNCH(16, 8, true);
+    if (max_words <= 32) RDKV_MIXED_LAUNCH(32, 8, true);
+  }
+  if (waves == 8 && max_words <= 16) RDKV_MIXED_LAUNCH(16, 8, false);
+  if (waves == 8 && max_words <= 32) RDKV_MIXED_LAUNCH(32, 8, false);
 #endif
-  if (max_words <= 16) RDKV_MIXED_LAUNCH(16, 4);
-  if (max_words <= 32) RDKV_MIXED_LAUNCH(32, 4);
+  if (max_words <= 16) RDKV_MIXED_LAUNCH(16, 4, false);
+  if (max_words <= 32) RDKV_MIXED_LAUNCH(32, 4, false);
   return hipErrorInvalidValue;
 #else
-  if (max_words <= 64) RDKV_MIXED_LAUNCH(64, 4);
-  RDKV_MIXED_LAUNCH(68, 4);
+  if (max_words <= 64) RDKV_MIXED_LAUNCH(64, 4, false);
+  RDKV_MIXED_LAUNCH(68, 4, false);
 #endif
 #undef RDKV_MIXED_LAUNCH
 }

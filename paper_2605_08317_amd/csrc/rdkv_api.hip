@@ -611,7 +611,7 @@ rdkv_status workspace_for(const rdkv_cache* c, hipStream_t st, rdkv_cache::Works
   }
   rdkv_cache::Workspace w;
   size_t absent = 0, arrive = 0;
-  if (!make_workspace(c, st, c->n_slots, c->n_merge > 0, &w, &absent, &arrive)) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
+  if (!make_workspace(c, st, c->n_slots, c->merge_parts > 0, &w, &absent, &arrive)) return fail(RDKV_ERR_ALLOC, "device allocation of a split workspace failed");
   hipError_t e = hipMemsetAsync(w.arrive, 0, arrive, st);     // (the kernels keep both so)
   if (e == hipSuccess && absent > 0) e = hipMemsetAsync(w.block, 0xFF, absent, st);
   if (e != hipSuccess) {
@@ -667,17 +667,28 @@ void order_chunks(std::vector<Chunk>::iterator first, std::vector<Chunk>::iterat
   std::copy(sorted.begin(), sorted.end(), first);
 }
 
-// Workgroups that merge an item's partials, 8 g / parts blocks of 16 channels each: four per query head while a launch has at
-// most 128 of them, half of what the chip holds beside its chunks, and at least one for every four heads.
+// Merging workgroups of an item in a launch that looks for its partials (8 g / parts blocks of 16 channels each, a wavefront
+// each): four per query head while a launch has at most 128 of them; 0, the launch counts, where that takes more than 128
+// or wavefronts with more than one block, i.e. from 129 query heads on (8 heads per KV head, four wavefronts a workgroup: 65).
+// The places that chunks leave beside them (a compute unit holds one workgroup of these kernels, two with four wavefronts)
+// are no line: 64 or 32 workgroups, or as many as there are places left, took 0 to 3 us more in launches of 175 to 241 chunks.
+// Time looked for / time counted, caches cold, 4 to 1024 items of 300 to 20000 keys (lowest, geometric mean, highest; number of
+// launches).  Token-wise launches of at most 256 chunks, 1 to 4 query heads per KV head:
+//   up to 128 query heads  0.74 0.88 1.01  (148)     above  0.93 1.06 1.20  (26)
+// 8 per KV head:
+//   up to 64               0.82 0.93 1.05  (16)      above  0.95 1.19 1.46  (27)
+// Channel-wise launches of eight-wavefront workgroups, whatever their number of chunks:
+//   up to 128              0.84 0.94 1.06  (100)     above  0.97 1.03 1.11  (44)
 int merge_parts(int g, int64_t n_items) {
+  const int least = g > 4 ? 2 * g : g;
+  if (least * n_items > 128) return 0;
   int parts = 4 * g;
-  while (parts > 1 && 4 * parts > g && parts * n_items > 128) parts /= 2;
+  while (parts > least && parts * n_items > 128) parts /= 2;
   return parts;
 }
 // their entries of the chunk table: none for items whose only chunk writes the output rows itself
-std::vector<Chunk> merge_chunks(const std::vector<int32_t>& slot_begin, const std::vector<int32_t>& slot_count, int64_t n_items, int g) {
+std::vector<Chunk> merge_chunks(const std::vector<int32_t>& slot_begin, const std::vector<int32_t>& slot_count, int64_t n_items, int parts) {
   std::vector<Chunk> table;
-  const int parts = merge_parts(g, n_items);
   for (int part = 0; part < parts; ++part)
     for (int64_t i = 0; i < n_items; ++i) {
       if (slot_count[i] <= 1) continue;
@@ -1051,9 +1062,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // Launches of up to kModelledCost are cut into rows, a multiple of 256 per chunk (one 64-row tile per SIMD), by a model of
   // their time: a start, the tiles that one SIMD goes through one after the other (8-bit rows take longer), and what each
   // chunk adds to the launch and each partial to the merge of its item.  A launch of at most 256 chunks has one workgroup per
-  // compute unit and looks for its partials; a larger one counts arrivals and shares its compute units.  Against both stands
-  // the cut by bytes below, whose time goes with the bytes.  Fitted to 314 token-wise launches (2 to 64 items, 1 to 192 MB,
-  // up to 60 % 8-bit rows, caches cold).  244 others (1 to 128 items of even and uneven lengths, 0.5 to 220 MB, 16-bit rows,
+  // compute unit and looks for its partials (or, with many query heads, counts: merge_parts); a larger one counts arrivals and
+  // shares its compute units.  Against both stands the cut by bytes below, whose time goes with the bytes.  Fitted to 314
+  // token-wise launches (2 to 64 items, 1 to 192 MB, up to 60 % 8-bit rows, caches cold).  244 others (1 to 128 items of even and uneven lengths, 0.5 to 220 MB, 16-bit rows,
   // tails) take 3.6 % less time in the geometric mean than with arrivals weighed as of a counted merge and a line by bytes alone:
   // 55 of them at least 3 % less (one item of 220 MB, 8 heads per KV head: 717 chunks 62.7 us, 206 chunks 18.7), 8 more; 217 caches
   // of 0.4 to 8 bits per element and up to sixteen sequences 2.1 % less, 5 at least 3 % more (2 items of 23K rows: 62 chunks
@@ -1308,7 +1319,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // merging workgroups where the decode kernel looks for partials (see decode_merge.h)
   std::vector<Chunk> mergers;
   if (mixed ? c->mixed_waves == 8 : decode_tiles_take_rows(static_cast<int>(c->sched16 + c->schedq), c->n_cont > 0))
-    mergers = merge_chunks(slot_begin, slot_count, n, g);
+    c->merge_parts = merge_parts(g, n);
+  mergers = merge_chunks(slot_begin, slot_count, n, c->merge_parts);
   c->n_merge = static_cast<int64_t>(mergers.size());
   const int64_t n_chunks = static_cast<int64_t>(c->chunks.size()), n_table = n_chunks + c->n_merge;
   c->own_slot_count.assign(slot_count.begin(), slot_count.begin() + n);
@@ -1324,7 +1336,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     const int64_t o_ik = o_bc + (mixed ? up(n * kHeadDim) : 0);
     const int64_t ik_b = mixed ? round_up(n * static_cast<int64_t>(sizeof(ItemK)), 8) : 0;
     const int64_t o_acc = o_ik + up(ik_b + n_table * static_cast<int64_t>(sizeof(Chunk)));
-    const int64_t o_ml = o_acc + up(std::max<int64_t>(c->n_slots, 1) * g * (c->n_merge > 0 ? merge::kRecordFloats : kHeadDim) * 4);
+    const int64_t o_ml = o_acc + up(std::max<int64_t>(c->n_slots, 1) * g * (c->merge_parts > 0 ? merge::kRecordFloats : kHeadDim) * 4);
     const int64_t o_lam = o_ml + up(std::max<int64_t>(c->n_slots, 1) * g * 2 * 4);
     const int maps = mixed ? 2 : 1;
     const int64_t o_it = o_lam + (lam ? up(maps * n * 8) : 0);
@@ -1373,7 +1385,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       a.add(plan, d_idx_base, plan_b, kSrcHost);
       a.add(tables, c->d_block + o_ik, tables_b, kSrcHost);
       a.fill(c->d_block + o_state, o_idx - o_state, 0u, 0u);     // appended tokens, arrival counters
-      if (c->n_merge > 0) a.fill(c->d_block + o_acc, o_ml - o_acc, merge::kAbsent, merge::kAbsent);
+      if (c->merge_parts > 0) a.fill(c->d_block + o_acc, o_ml - o_acc, merge::kAbsent, merge::kAbsent);
       a.add(bits_tok, c->d_bits_tok, it.total_tokens);
       if (mixed) a.add(bits_ch, c->d_bits_ch, n * kHeadDim);
       if (lam) a.add(lam, c->d_block + o_lam, maps * n * 8);
@@ -1692,7 +1704,7 @@ static size_t cache_max_bytes(const rdkv_config* cfg) {
 }
 
 // The same for everything else in the cache's block: kept positions (4 bytes each), the bit maps, the K row layouts,
-// the chunk table and the first split workspace (at most two rounds of chunks and four per item, g x 162 floats each, and
+// the chunk table and the first split workspace (at most two rounds of chunks and eight per item, g x 258 floats each, and
 // the merging workgroups), lambda and step counts, and the alignment of the parts.
 static size_t cache_max_table_bytes(const rdkv_config* cfg) {
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
@@ -1710,7 +1722,7 @@ static size_t cache_max_table_bytes(const rdkv_config* cfg) {
   const double items = static_cast<double>(cfg->batch) * cfg->hkv;
   const double chunks = 2.0 * 768.0 + 8.0 * items;
   return static_cast<size_t>(4.0 * kept + tokens + items * (kHeadDim + sizeof(ItemK) + 8 + 2 * 12) +
-                             chunks * (sizeof(Chunk) + g * (merge::kRecordFloats + 2) * 4.0) + std::max(128.0, 2.0 * items) * sizeof(Chunk) +
+                             chunks * (sizeof(Chunk) + g * (merge::kRecordFloats + 2) * 4.0) + 128.0 * sizeof(Chunk) +
                              16.0 * 256);
 }
 
@@ -1745,7 +1757,7 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
   const rdkv_status ws = workspace_for(c, st, &w);
   if (ws != RDKV_OK) return ws;
   const int g = c->hq / c->hkv;
-  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, g, merge_parts(g, c->n_items), c->looks};
+  const MergeArgs ma{w.part_acc, w.part_ml, w.arrive, out, lse, g, c->merge_parts, c->looks};
   // every chunk of the schedule is launched, the tail's included: chunks of tail rows that do not exist yet find
   // the current length in the cache's device word and contribute an empty partial
   const int n16 = static_cast<int>(c->sched16), nrest = static_cast<int>(c->schedq + c->n_tail_chunks);
@@ -1766,7 +1778,7 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* c, const void* q, float* out, flo
   }
   // the workgroups of both kernels announce themselves on the same counters: whichever finishes an item merges it
   RDKV_HIP(launch_decode_tiered_split(c->d_chunks, n16, c->d_arena, qp, ma, st));
-  RDKV_HIP(launch_decode_tiles(c->d_chunks, n16, nrest, -1, false, multi, c->d_arena, qp, ma, c->d_tail_len, st));
+  RDKV_HIP(launch_decode_tiles(c->d_chunks, n16, nrest, 0, false, multi, c->d_arena, qp, ma, c->d_tail_len, st));
   return RDKV_OK;
 }
 
@@ -1818,8 +1830,10 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
     }
   }
   std::vector<Chunk> mergers;      // where the decode kernel looks for partials
+  int parts = 0;
   if (mixed ? sched_mixed_waves(c, kw) == 8 : decode_tiles_take_rows(static_cast<int>(n_gen_chunks + n * npi), sched_multi(c)))
-    mergers = merge_chunks(nb, nc, n, c->hq / c->hkv);
+    parts = merge_parts(c->hq / c->hkv, n);
+  mergers = merge_chunks(nb, nc, n, parts);
   const int64_t n_merge = static_cast<int64_t>(mergers.size());
   const int64_t cont_base = n_gen_chunks + n * npi + n_merge;      // where the continuation pieces start in the new table
   std::vector<Chunk> table;
@@ -1894,7 +1908,7 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
   }
   rdkv_cache::Workspace w;   // this stream's workspace right away: a decode under graph capture then allocates nothing
   size_t absent = 0, arrive = 0;
-  const bool have_w = make_workspace(c, st, n_slots, n_merge > 0, &w, &absent, &arrive);   // (a failure is reported by the decode call that needs it)
+  const bool have_w = make_workspace(c, st, n_slots, parts > 0, &w, &absent, &arrive);   // (a failure is reported by the decode call that needs it)
   // tables up, the workspace and the caller's memory set in one launch; the stream must be idle before the old tables and
   // workspaces go: a decode step may still be reading them
   const size_t table_b = table.size() * sizeof(Chunk), items_b = items_sched.size() * sizeof(ItemK);
@@ -1934,6 +1948,7 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
   c->schedq = n_gen_chunks - n16;
   c->n_tail_chunks = n * npi;
   c->n_merge = n_merge;
+  c->merge_parts = parts;
   c->chunks.swap(own);
   c->slot_begin.swap(nb);
   c->slot_count.swap(nc);

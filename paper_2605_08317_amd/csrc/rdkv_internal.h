@@ -34,7 +34,7 @@ struct Chunk {
   int32_t slot;                             // partial-result slot
   int16_t k_word_end[4];                    // mixed mode: ItemK::word_end of the item (the shape of its K rows)
   int32_t row0;                             // appended-token zone: first row of the chunk inside the item's tail;
-                                            // kTierMerge: which part of the item's query heads
+                                            // kTierMerge: which of the item's merging workgroups
   int32_t reserved;                         // mixed mode: index of the chunk's ItemK in the schedule's table
                                             // (generation * items + item)
   int32_t slot0, nslots;                    // the item's first partial slot and its number of slots (= chunks)
@@ -139,8 +139,9 @@ hipError_t launch_gather_tail_rows(const uint8_t* tail, int64_t n_items, int32_t
                                    uint16_t* k_rows, uint16_t* v_rows, hipStream_t st);
 
 // chunks: the whole chunk table; workgroup b starts with chunks[first + b] and, if `multi`, follows Chunk::next.
-// n_merge >= 0: the partials are looked for by the n_merge entries of tier kTierMerge behind the n_chunks, and the range may
-// start with chunks of the 16-bit tier (rows16), both only where decode_tiles_take_rows says so; -1: arrivals are counted.
+// ma.parts > 0: the partials are looked for, by the n_merge entries of tier kTierMerge behind the n_chunks; otherwise arrivals
+// are counted.  The former, and a range that starts with chunks of the 16-bit tier (rows16), only where decode_tiles_take_rows
+// says so.
 // tail_len: device word holding the appended tokens that exist so far (chunks of tier kTierTail end there)
 bool decode_tiles_take_rows(int n_chunks, bool multi);
 hipError_t launch_decode_tiles(const Chunk* chunks, int first, int n_chunks, int n_merge, bool rows16, bool multi,
@@ -218,8 +219,8 @@ struct rdkv_cache {
   // for V, in one allocation (zero-filled: rows not yet appended read as zeros)
   std::vector<int32_t> slot_begin, slot_count;   // host copies of the partial-slot tables
   uint8_t* d_tail = nullptr;
-  int64_t n_merge = 0;                  // merging workgroups of the schedule, behind the launched chunks in d_chunks: none
-                                        // where the decode kernel counts arrivals (decode_merge.h)
+  int64_t n_merge = 0;                  // merging workgroups of the schedule, behind the launched chunks in d_chunks
+  int32_t merge_parts = 0;              // MergeArgs::parts
   int32_t looks = 256;                  // MergeArgs::looks: a look takes 1 us, a launch that looks at most 50
   int64_t n_tail_chunks = 0;            // chunks of the tail, appended to d_chunks in (chunk index, item) order:
                                         // the first ceil(tail_len / 256) * items of them are live

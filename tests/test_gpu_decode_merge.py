@@ -1,7 +1,6 @@
-"""The merging workgroups of small decode launches: slots per item on both sides of a batch of loads, every number of blocks
-per wavefront (which follows the number of items and of query heads), channel-wise keys, both sides of the line between a launch
-that looks and one that counts, and a workspace that every step leaves as it found it.  (Channel-wise launches of eight-wavefront
-workgroups look whatever their number of chunks.)"""
+"""The merging workgroups of small decode launches: slots per item on both sides of a batch of loads, every number of merging
+workgroups per item (which follows the number of items and of query heads), channel-wise keys, both sides of the line between a launch
+that looks and one that counts, and a workspace that every step leaves as it found it."""
 import ctypes
 
 import numpy as np
@@ -52,9 +51,11 @@ def test_slots_of_one_item(T, g):
     _check(b, [T], 1, g, [2])
 
 
-# two chunks per item: the last number of items whose launch looks and the first whose launch counts among them
-@pytest.mark.parametrize("batch,hkv,few", [(1, 3, True), (2, 8, True), (17, 2, True), (33, 1, True), (9, 8, True), (25, 4, True),
-                                           (16, 8, True), (43, 3, False)])
+# two chunks per item, 8, 9, 32, 33, 64, 65, 128 and 129 items among them: the last number whose launch looks and the first whose
+# launch counts for 8, 4, 2 and 1 query heads per KV head
+@pytest.mark.parametrize("batch,hkv,few", [(1, 3, True), (1, 8, True), (9, 1, True), (2, 8, True), (4, 8, True), (17, 2, True),
+                                           (33, 1, True), (8, 8, True), (13, 5, True), (9, 8, True), (25, 4, True), (16, 8, True),
+                                           (43, 3, False)])
 @pytest.mark.parametrize("g", [1, 2, 4, 8])
 def test_numbers_of_items(batch, hkv, few, g):
     from paper_2605_08317_amd import binding as b
@@ -68,11 +69,11 @@ def test_channelwise(T, g):
     _check(b, [T], 2, g, [8, 4, 2, 0], mixed=True)
 
 
-# more chunks, and more items with merging workgroups, than the chip has places
-@pytest.mark.parametrize("batch,hkv,T", [(33, 8, 300), (13, 8, 1100)])
-def test_channelwise_with_many_items(batch, hkv, T):
+# more chunks than the chip has places: merging workgroups behind them (the last two), arrivals counted
+@pytest.mark.parametrize("batch,hkv,g,T", [(33, 8, 4, 300), (13, 8, 4, 1100), (16, 8, 1, 1100), (12, 8, 1, 300)])
+def test_channelwise_with_many_items(batch, hkv, g, T):
     from paper_2605_08317_amd import binding as b
-    _check(b, [T - s for s in range(batch)], hkv, 4, [8, 4, 2], mixed=True, few=False)
+    _check(b, [T - s for s in range(batch)], hkv, g, [8, 4, 2], mixed=True, few=False)
 
 
 # one and two tiles per SIMD, as many chunks as a launch that looks has beside room for a tail, a launch that counts, tiers that
@@ -91,8 +92,8 @@ def test_rows_per_chunk(seq_lens, hkv, widths, few, g):
 # put back would be the other query's).
 @pytest.mark.parametrize("seq_lens,hkv,g,widths,mixed", [
     ((600,), 2, 4, [2], False), ((4097,), 1, 8, [2], False), ((30000,), 1, 4, [2], False), ((30600, 30600), 2, 4, [2], False),
-    ((150001,), 1, 1, [2], False), ((150001,), 1, 8, [8, 2], False), ((700,) * 25, 4, 2, [8, 2], False), ((700,) * 17, 2, 8, [8, 2], False),
-    ((3000, 20000), 4, 4, [16, 8, 4, 2], False), ((600, 9001), 2, 4, [8, 4, 2], True), ((700,) * 25, 4, 4, [8, 4, 2], True)])
+    ((150001,), 1, 1, [2], False), ((150001,), 1, 8, [8, 2], False), ((700,) * 16, 4, 2, [8, 2], False), ((700,) * 4, 2, 8, [8, 2], False),
+    ((3000, 20000), 4, 4, [16, 8, 4, 2], False), ((600, 9001), 2, 4, [8, 4, 2], True), ((700,) * 8, 4, 4, [8, 4, 2], True)])
 @pytest.mark.parametrize("looks", [0, 3])
 def test_merging_workgroups_that_give_up(seq_lens, hkv, g, widths, mixed, looks):
     from paper_2605_08317_amd import binding as b

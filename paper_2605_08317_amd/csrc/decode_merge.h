@@ -9,15 +9,15 @@
 // announces it on the item's arrival counter, and the workgroup that completes an item merges its partials and resets the
 // counter.
 //
-// Small launches look (merge_part): behind the chunks they have workgroups that only merge, each some of an item's output
-// channels.  A word of a partial is its own arrival flag: between steps every word of the workspace holds kAbsent, a NaN that a
-// partial never holds (`present`), and the merging wavefront puts it back once it has read a word.  What that saves is two
-// memory round trips between a chunk's last store and the merge (drain, counter; 20 arrivals at once queue for 1.4 us) and a
-// merge in one workgroup per item with eight slots per thread: from the last partial's store to the end of the launch 4.3 us
-// counted, 1.7 so (time stamps, 164 chunks).
+// Small launches with up to 128 query heads look (merge_part; merge_parts in rdkv_api.hip says where the line lies): behind the
+// chunks they have workgroups that only merge, each some of an item's output channels.  A word of a partial is its own arrival
+// flag: between steps every word of the workspace holds kAbsent, a NaN that a partial never holds (`present`), and the merging
+// wavefront puts it back once it has read a word.  What that saves is two memory round trips between a chunk's last store and
+// the merge (drain, counter; 20 arrivals at once queue for 1.4 us) and a merge in one workgroup per item with eight slots per
+// thread: from the last partial's store to the end of the launch 4.3 us counted, 1.7 so (time stamps, 164 chunks).
 // Launches of 30, 164 and 178 chunks with 2 to 8 items 7.0 -> 5.1, 9.5 -> 6.7 and 10.7 -> 9.2 us, 208 channel-wise ones
 // 15.2 -> 12.3 (replayed from a graph).
-// In large launches the merging workgroups come too late, one behind the other in what slots the chunks leave (16 ragged
+// In larger launches the merging workgroups come too late, one behind the other in what slots the chunks leave (16 ragged
 // sequences with 8 query heads 43.7 us counted, 46.8 looked at; 16 channel-wise ones 77.6, 77.8).
 //
 // What bounds the wait of a merging workgroup.  Workgroups are dispatched in the order of the grid on each XCD, but an item's

@@ -1093,7 +1093,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   const LaunchTime alone = g > 4 ? LaunchTime{4.2, 1.6, 0.7, 2.0, 0.014, 0.0, 0.03} : LaunchTime{4.9, 0.25, 1.2, 3.0, 0.002, 0.001, 0.14};
   const LaunchTime among = g > 4 ? LaunchTime{4.4, 1.1, 0.67, 0.0, 0.008, 0.1, 0.0} : LaunchTime{1.7, 1.2, 0.69, 0.0, 0.018, 0.067, 0.0};
   struct Cut { int64_t rows; double time; };
-  const int64_t room = n <= 8 ? 2 * n : 0;      // for a tail's chunks, where they are few enough to keep the launch small
+  // Room for a tail's chunks, where they are few, so that the launch goes on looking: 8 items of 30K 4-bit rows in 240 chunks
+  // 12.2 us, with a tail reserved 12.0.  (16 items of 8K in 256 chunks 9.5, with a tail's 16 more, counted, 11.7.)
+  const int64_t room = n <= 8 ? 2 * n : 0;
   // the best rows per chunk for the tiers from ti_first on
   auto cut_by_rows = [&](int ti_first, double share, bool only_looked) {
     constexpr uint32_t kMostTiles = 16;

@@ -686,22 +686,24 @@ int merge_parts(int g, int64_t n_items) {
   while (parts > least && parts * n_items > 128) parts /= 2;
   return parts;
 }
-// their entries of the chunk table: none for items whose only chunk writes the output rows itself
-std::vector<Chunk> merge_chunks(const std::vector<int32_t>& slot_begin, const std::vector<int32_t>& slot_count, int64_t n_items, int parts) {
-  std::vector<Chunk> table;
+// Their entries of the chunk table, written to where the table is put together (none for items whose only chunk writes the
+// output rows itself).
+int64_t count_merge_chunks(const std::vector<int32_t>& slot_count, int64_t n_items, int parts) {
+  return parts * std::count_if(slot_count.begin(), slot_count.begin() + n_items, [](int32_t c) { return c > 1; });
+}
+void merge_chunks(const std::vector<int32_t>& slot_begin, const std::vector<int32_t>& slot_count, int64_t n_items, int parts, Chunk* to) {
+  Chunk ch{};
+  ch.tier = kTierMerge;
+  ch.next = -1;
   for (int part = 0; part < parts; ++part)
     for (int64_t i = 0; i < n_items; ++i) {
       if (slot_count[i] <= 1) continue;
-      Chunk ch{};
-      ch.tier = kTierMerge;
       ch.item = static_cast<int32_t>(i);
       ch.slot0 = slot_begin[i];
       ch.nslots = slot_count[i];
       ch.row0 = part;
-      ch.next = -1;
-      table.push_back(ch);
+      *to++ = ch;
     }
-  return table;
 }
 
 // every chunk learns its item's first partial slot and slot count (the merge inside the decode kernels needs them)
@@ -1097,21 +1099,24 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // 12.2 us, with a tail reserved 12.0.  (16 items of 8K in 256 chunks 9.5, with a tail's 16 more, counted, 11.7.)
   const int64_t room = n <= 8 ? 2 * n : 0;
   // the best rows per chunk for the tiers from ti_first on
+  std::vector<uint32_t> segs;
+  segs.reserve(static_cast<size_t>(n) * 4);
   auto cut_by_rows = [&](int ti_first, double share, bool only_looked) {
     constexpr uint32_t kMostTiles = 16;
     Cut best{0, 0.0};
+    segs.clear();      // the 256 rows of each item and tier
+    for (int64_t i = 0; i < n; ++i)
+      for (int ti = ti_first; ti < 4; ++ti)
+        if (c->counts[i * 4 + ti] > 0) segs.push_back((static_cast<uint32_t>(c->counts[i * 4 + ti]) + 255u) / 256u);
     for (uint32_t k = 1; k <= kMostTiles; k += g <= 4 && k >= 4 ? 2 : 1) {      // (eight wavefronts: 512 rows at a time)
       const uint32_t rows = 256u * k;
       int64_t n_wg = 0;
-      uint32_t tiles = 0;
-      for (int64_t i = 0; i < n; ++i)
-        for (int ti = ti_first; ti < 4; ++ti) {
-          const uint32_t cnt = static_cast<uint32_t>(c->counts[i * 4 + ti]);
-          if (cnt == 0) continue;
-          const uint32_t nch = (cnt + rows - 1) / rows;
-          n_wg += nch;
-          tiles = std::max(tiles, ((cnt + nch - 1) / nch + 255u) / 256u);
-        }
+      uint32_t tiles = 0;      // of the largest chunk
+      for (const uint32_t seg : segs) {
+        const uint32_t nch = seg <= k ? 1u : (seg + k - 1) / k;
+        n_wg += nch;
+        if (tiles < std::min(seg, k)) tiles = std::max(tiles, (seg + nch - 1) / nch);
+      }
       if (n_wg > 768 + 4 * n) continue;      // more than any launch needs, and than cache_max_table_bytes allows for
       const bool look = n_wg <= 256 - room;
       if (only_looked && !look) continue;
@@ -1319,11 +1324,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     c->chunks.insert(c->chunks.end(), conts.begin(), conts.end());
   }
   // merging workgroups where the decode kernel looks for partials (see decode_merge.h)
-  std::vector<Chunk> mergers;
   if (mixed ? c->mixed_waves == 8 : decode_tiles_take_rows(static_cast<int>(c->sched16 + c->schedq), c->n_cont > 0))
     c->merge_parts = merge_parts(g, n);
-  mergers = merge_chunks(slot_begin, slot_count, n, c->merge_parts);
-  c->n_merge = static_cast<int64_t>(mergers.size());
+  c->n_merge = count_merge_chunks(slot_count, n, c->merge_parts);
   const int64_t n_chunks = static_cast<int64_t>(c->chunks.size()), n_table = n_chunks + c->n_merge;
   c->own_slot_count.assign(slot_count.begin(), slot_count.begin() + n);
 
@@ -1376,12 +1379,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       if (mixed) std::memcpy(tables, c->items_k.data(), n * sizeof(ItemK));
       {   // [launched chunks | merging workgroups | continuation pieces]
         Chunk* t = reinterpret_cast<Chunk*>(tables + ik_b);
-        const int64_t launched = n_chunks - c->n_cont;
-        std::copy(c->chunks.begin(), c->chunks.begin() + launched, t);
-        std::copy(mergers.begin(), mergers.end(), t + launched);
-        std::copy(c->chunks.begin() + launched, c->chunks.end(), t + launched + c->n_merge);
-        for (int64_t k = 0; k < n_table; ++k)
-          if (t[k].next >= 0) t[k].next += static_cast<int32_t>(c->n_merge);
+        std::copy(c->chunks.begin(), c->chunks.end(), t);       // (a schedule has one of the two last)
+        merge_chunks(slot_begin, slot_count, n, c->merge_parts, t + n_chunks);
       }
       CopyArgs a{};
       a.add(plan, d_idx_base, plan_b, kSrcHost);
@@ -1831,12 +1830,10 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
       kq = std::max(kq, gc->max_k_qsteps);
     }
   }
-  std::vector<Chunk> mergers;      // where the decode kernel looks for partials
-  int parts = 0;
+  int parts = 0;      // where the decode kernel looks for partials
   if (mixed ? sched_mixed_waves(c, kw) == 8 : decode_tiles_take_rows(static_cast<int>(n_gen_chunks + n * npi), sched_multi(c)))
     parts = merge_parts(c->hq / c->hkv, n);
-  mergers = merge_chunks(nb, nc, n, parts);
-  const int64_t n_merge = static_cast<int64_t>(mergers.size());
+  const int64_t n_merge = count_merge_chunks(nc, n, parts);
   const int64_t cont_base = n_gen_chunks + n * npi + n_merge;      // where the continuation pieces start in the new table
   std::vector<Chunk> table;
   table.reserve(static_cast<size_t>(cont_base + n_cont_total));
@@ -1886,7 +1883,8 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
       ch.next = -1;
       table.push_back(ch);
     }
-  table.insert(table.end(), mergers.begin(), mergers.end());
+  table.resize(table.size() + static_cast<size_t>(n_merge));
+  merge_chunks(nb, nc, n, parts, table.data() + (table.size() - static_cast<size_t>(n_merge)));
   for (size_t k = 0; k < gens.size(); ++k) {
     const rdkv_cache* gc = gens[k];
     for (size_t j = gc->chunks.size() - static_cast<size_t>(gc->n_cont); j < gc->chunks.size(); ++j)

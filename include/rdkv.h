@@ -282,8 +282,9 @@ rdkv_status rdkv_decode_attn_bf16_noalloc(const void* K, const void* V, const in
  * kernels with HIP events on the call's own stream: the decode launch of
  * rdkv_decode_attn (merge included), the split-K kernel of rdkv_decode_attn_bf16,
  * every kernel of rdkv_weights, every kernel of rdkv_allocate, and the kernels of
- * rdkv_pack in two brackets (tier counts before the call's one wait; position
- * lists, quantize and pack after it; the copies of tables and counts are not inside).
+ * rdkv_pack in two or three brackets (tier counts, where the allocation has not
+ * counted, and position lists before the call's one wait; quantize and pack after it;
+ * the copies of tables and counts go along in these launches).
  * rdkv_kernel_timing_read waits for the recorded events, returns the number of
  * brackets of one kind and their summed duration in milliseconds, and clears that
  * kind.  Not for use under graph capture.

@@ -11,9 +11,10 @@
 //   code = clamp(rint((x - m) / s), 0, Q), all zero when s == 0; the quotient is the correctly rounded one, from the
 //          hardware reciprocal of s and one exact remainder (see Quant::code)
 // Codes occupy b-bit fields of little-endian words (App. B: fields at bit offsets 0,2,4,6 / 0,4 of a byte).
+#include <algorithm>
 #include <type_traits>
 
-#include "rdkv_internal.h"
+#include "copy_device.h"
 #include "wave_ops.h"
 
 namespace rdkv {
@@ -70,40 +71,218 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
   }
 }
 
-// Writes the ascending position lists: tier_idx[item_base + tier_base + rank].  One workgroup = one block of 1024 tokens, a
-// thread = four consecutive ones; the ranks of all four tiers come from one prefix sum over 16-bit fields.
-__global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __restrict__ bits,
-                                                           const int64_t* __restrict__ item_tok_off,
-                                                           const int32_t* __restrict__ item_T,
-                                                           const int32_t* __restrict__ item_blk_off,
-                                                           const int4* __restrict__ blk_counts,
-                                                           const int64_t* __restrict__ idx_base /* [items][4] */,
-                                                           int32_t* __restrict__ tier_idx) {
+// One launch between the bit map and the host's wait for its counts; nothing in it needs the host:
+//   - the ascending position lists of every tier, item by item in scratch: item's first token + kept tokens of the higher
+//     tiers + rank (one workgroup = one block of 1024 tokens, a thread = four consecutive ones; the ranks of all four tiers
+//     come from one prefix sum over 16-bit fields)
+//   - the counts' way to the host, and what else is copied or filled then (copy_part)
+//   - the arena's plan (plan_part), by one workgroup
+//   - channel-wise K: the row layout of every item (layout_part), by the item's first workgroup
+// What bounds it is latency: two round trips to memory and the launch (4.4 us for two items of 4K tokens, 11.6 for 128 of 20K).
+// With the counts copied by a launch in front of the wait, and the tables and then the lists in two launches behind it,
+// compressing two heads of 4K keys took 58.0 us, eight of 128K 242; now 53.2 and 234.
+struct ScatterArgs {
+  const uint8_t* bits;
+  const int64_t* item_tok_off;
+  const int32_t* item_T;
+  const int32_t* item_blk_off;
+  const int4* blk_counts;
+  int32_t* tier_idx;
+  int32_t extra;                 // leading workgroups of every grid row that do other things
+  PlanArgs plan;
+  CopyArgs copy;
+};
+
+// counts of a block; one that holds a value that is no bit-width (the host refuses the map) counts as empty there
+__device__ __forceinline__ int4 block_counts(const int4* blk_counts, int b) {
+  int4 c = blk_counts[b];
+  c.x = max(c.x, 0);
+  return c;
+}
+
+// Sum over groups of 2^k consecutive lanes, in each of them.
+__device__ __forceinline__ uint32_t group_sum(uint32_t v, int lanes) {
+  for (int d = 1; d < lanes; d <<= 1) v += __shfl_xor(v, d);
+  return v;
+}
+__device__ __forceinline__ uint64_t inclusive_sum(uint64_t v) {
+  const int lane = threadIdx.x & 63;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t o = __shfl_up(v, d);
+    v += lane >= d ? o : 0ull;
+  }
+  return v;
+}
+
+// Where every tier segment of the arena starts, where an item's kept positions do, and the rows of every tier: the plan that
+// the host makes for the chunk table when it has the counts (pack_impl), here for the packing kernels, so that they wait for
+// no table.  One workgroup; 2^k lanes add up an item's counts, and the items are a prefix sum apart.
+__device__ __forceinline__ void plan_part(const ScatterArgs& a) {
+  __shared__ uint64_t s_sum[2][4];
+  const PlanArgs& p = a.plan;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int lanes = 64;                          // per item
+  while (lanes > 1 && static_cast<int64_t>(lanes) * p.n_items > 256) lanes >>= 1;
+  const int per_round = 256 / lanes, sub = tid & (lanes - 1);
+  uint64_t units0 = 0, kept0 = 0;          // of the earlier rounds' items
+  for (int i0 = 0; i0 < p.n_items; i0 += per_round) {
+    const int item = i0 + tid / lanes;
+    const bool in = item < p.n_items;
+    const int nb = in ? (a.item_T[item] + kPartBlock - 1) / kPartBlock : 0, first = in ? a.item_blk_off[item] : 0;
+    uint32_t cnt[4] = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int b = sub; b < nb; b += lanes) {
+      const int4 c = block_counts(a.blk_counts, first + b);
+      cnt[0] += c.x; cnt[1] += c.y; cnt[2] += c.z; cnt[3] += c.w;
+    }
+    uint32_t words = 0, steps = 0;         // channel-wise: 32-bit words of a K row, its quantized steps
+    if (p.bits_ch) {
+      uint32_t ch = 0;                     // channels of every tier, eight bits each (at most 128)
+      if (in)
+#pragma unroll 8
+        for (int w = sub; w < kHeadDim / 4; w += lanes) {
+          const uint32_t four = reinterpret_cast<const Bytes4*>(p.bits_ch + static_cast<int64_t>(item) * kHeadDim)[w].v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int s = tier_slot(static_cast<uint8_t>(four >> (8 * e)));
+            ch += s >= 0 ? 1u << (8 * s) : 0u;
+          }
+        }
+      ch = group_sum(ch, lanes);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t slots = k_tier_slots(k, (ch >> (8 * k)) & 0xFF);
+        words += slots * (16 >> k) / 32;
+        if (k > 0) steps += slots / 4;
+      }
+      words = (words + 1) & ~1u;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cnt[k] = group_sum(cnt[k], lanes);
+    // segments K data, K metadata, V data, V metadata, in units of kSegAlign bytes
+    static_assert(kSegAlign == 256, "a 64-row tile of b-bit rows takes 4 b units, its metadata 4, a tile of channel-wise K a word per unit");
+    uint64_t size[4][4], units = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t tiles = (cnt[k] + kTile64 - 1) / kTile64;
+      size[k][2] = tiles * (4u * (16 >> k));
+      size[k][3] = k == 0 ? 0ull : tiles * 4u;
+      size[k][0] = p.bits_ch ? tiles * words : size[k][2];
+      const uint64_t meta = p.per_unit ? (cnt[k] > 0 ? 16u * steps : 0u) : tiles * (32u * steps);
+      size[k][1] = p.bits_ch ? (meta + kSegAlign - 1) / kSegAlign : size[k][3];
+      units += (size[k][0] + size[k][1]) + (size[k][2] + size[k][3]);
+    }
+    const uint32_t kept = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+    const uint64_t own_u = in && sub == 0 ? units : 0ull, own_k = in && sub == 0 ? kept : 0ull;
+    const uint64_t inc_u = inclusive_sum(own_u), inc_k = inclusive_sum(own_k);
+    __syncthreads();                       // (the sums of the round before are used up)
+    if (lane == 63) {
+      s_sum[0][wave] = inc_u;
+      s_sum[1][wave] = inc_k;
+    }
+    __syncthreads();
+    uint64_t u = units0 + inc_u - own_u, at = kept0 + inc_k - own_k;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) { u += s_sum[0][w]; at += s_sum[1][w]; }
+      units0 += s_sum[0][w];
+      kept0 += s_sum[1][w];
+    }
+    if (in && sub == 0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        p.counts[item * 4 + k] = static_cast<int32_t>(cnt[k]);
+        p.idx_base[item * 4 + k] = static_cast<int64_t>(at);
+        at += cnt[k];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          p.seg_off[(static_cast<int64_t>(item) * 4 + k) * 4 + g] = static_cast<int64_t>(u * kSegAlign);
+          u += size[k][g];
+        }
+      }
+    }
+  }
+}
+
+// Row layout of an item's channel-wise K tiles (make_item_k is the host's) by the first wavefront: two channels per lane.
+__device__ __forceinline__ void layout_part(const PlanArgs& p, int item) {
+  const int lane = threadIdx.x;
+  ItemK* out = p.items_k + item;
+  int tier[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) tier[h] = tier_slot(p.bits_ch[static_cast<int64_t>(item) * kHeadDim + 64 * h + lane]);
+  const uint64_t below = (1ull << lane) - 1ull;
+  uint32_t slot = 0, words = 0, steps = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint64_t lo = __ballot(tier[0] == k), hi = __ballot(tier[1] == k);
+    const uint32_t n_lo = __popcll(lo), n = n_lo + __popcll(hi), slots = k_tier_slots(k, n);
+    if (tier[0] == k) out->slot_ch[slot + __popcll(lo & below)] = static_cast<int16_t>(lane);
+    if (tier[1] == k) out->slot_ch[slot + n_lo + __popcll(hi & below)] = static_cast<int16_t>(64 + lane);
+    if (lane < slots - n) out->slot_ch[slot + n + lane] = -1;
+    words += slots * (16 >> k) / 32;
+    if (lane == 0) {
+      out->slot_base[k] = static_cast<int16_t>(slot);
+      out->word_end[k] = static_cast<int16_t>(words);
+      if (k == 0) out->n_steps16 = static_cast<int16_t>(slots / 4);
+    }
+    if (k > 0) steps += slots / 4;
+    slot += slots;
+  }
+  for (int j = slot + lane; j < kMaxSlots; j += 64) out->slot_ch[j] = -1;
+  if (lane == 0) {
+    out->n_slots = static_cast<int16_t>(slot);
+    out->n_words = static_cast<int16_t>(words);
+    out->n_words_padded = static_cast<int16_t>((words + 1) & ~1u);
+    out->n_qsteps = static_cast<int16_t>(steps);
+    out->kt_bytes = 256 * static_cast<int32_t>((words + 1) & ~1u);
+    out->km_bytes = 32 * static_cast<int32_t>(steps);
+  }
+}
+
+__global__ __launch_bounds__(256) void tier_scatter_kernel(ScatterArgs a) {
   static_assert(kPartBlock == 1024, "256 threads of four tokens");
-  __shared__ int s_before[4][4];
+  static_assert(kCopyThreads == 256, "copies in workgroups of this kernel");
+  __shared__ int s_before[4][4], s_all[4][4];
   __shared__ uint64_t s_wave[4];
-  const int item = blockIdx.y;
-  const int T = item_T[item];
-  const int t0 = blockIdx.x * kPartBlock;
+  if (static_cast<int>(blockIdx.x) < a.extra) {
+    const int b = static_cast<int>(blockIdx.y) * a.extra + static_cast<int>(blockIdx.x), copies = a.copy.first[a.copy.n];
+    if (b == 0) plan_part(a);
+    else if (b <= copies) copy_part(a.copy, b - 1);
+    return;
+  }
+  const int item = blockIdx.y, block = static_cast<int>(blockIdx.x) - a.extra;
+  const int T = a.item_T[item];
+  const int t0 = block * kPartBlock;
   if (t0 >= T) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint8_t* b = bits + item_tok_off[item] + t0;
+  const int64_t tok_off = a.item_tok_off[item];
+  const uint8_t* b = a.bits + tok_off + t0;
   const int n = min(kPartBlock, T - t0), u = 4 * tid;
   uint32_t four = 0;                       // tokens past the end: evicted
   if (u + 3 < n) four = reinterpret_cast<const Bytes4*>(b + u)->v;
   else
     for (int e = 0; e < 4; ++e)
       if (u + e < n) four |= static_cast<uint32_t>(b[u + e]) << (8 * e);
-  int4 c = make_int4(0, 0, 0, 0);          // kept tokens of the item's earlier blocks
-  for (int i = tid; i < static_cast<int>(blockIdx.x); i += 256) {
-    const int4 x = blk_counts[item_blk_off[item] + i];
-    c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
+  int before[4] = {0, 0, 0, 0}, all[4] = {0, 0, 0, 0};      // kept tokens of the item's earlier blocks, of all of them
+  const int n_blocks = (T + kPartBlock - 1) / kPartBlock;
+  for (int i = tid; i < n_blocks; i += 256) {
+    const int4 x = block_counts(a.blk_counts, a.item_blk_off[item] + i);
+    const int c[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      all[k] += c[k];
+      before[k] += i < block ? c[k] : 0;
+    }
   }
-  const int before[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int sum = static_cast<int>(wave_scan(static_cast<uint32_t>(before[k])));
-    if (lane == 63) s_before[wave][k] = sum;
+    const int total = static_cast<int>(wave_scan(static_cast<uint32_t>(all[k])));
+    if (lane == 63) {
+      s_before[wave][k] = sum;
+      s_all[wave][k] = total;
+    }
   }
   int slot[4];
   uint64_t mine = 0;                       // this thread's tokens per tier, 16 bits each
@@ -116,14 +295,22 @@ __global__ __launch_bounds__(256) void tier_scatter_kernel(const uint8_t* __rest
                         static_cast<uint64_t>(wave_scan(static_cast<uint32_t>(mine >> 32))) << 32;   // (at most 256 each)
   if (lane == 63) s_wave[wave] = incl;
   __syncthreads();
+  if (wave == 0 && block == 0 && a.plan.bits_ch) layout_part(a.plan, item);
   uint64_t rank = incl - mine;
   for (int w = 0; w < wave; ++w) rank += s_wave[w];
+  int first[4], higher = 0;                // first of the block in its tier's list
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    first[k] = higher + s_before[0][k] + s_before[1][k] + s_before[2][k] + s_before[3][k];
+    higher += s_all[0][k] + s_all[1][k] + s_all[2][k] + s_all[3][k];
+  }
 #pragma unroll
   for (int e = 0; e < 4; ++e)
     if (slot[e] >= 0) {
       const int k = slot[e];
-      const int first = s_before[0][k] + s_before[1][k] + s_before[2][k] + s_before[3][k];
-      tier_idx[idx_base[item * 4 + k] + first + static_cast<int>((rank >> (16 * k)) & 0xFFFF)] = t0 + u + e;
+      const int base = k == 0 ? first[0] : k == 1 ? first[1] : k == 2 ? first[2] : first[3];
+      const int at = base + static_cast<int>((rank >> (16 * k)) & 0xFFFF);
+      if (at < T) a.tier_idx[tok_off + at] = t0 + u + e;      // (a map that will be refused has blocks that were not counted)
       rank += 1ull << (16 * k);
     }
 }
@@ -134,7 +321,8 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 struct PackArgs {
   const uint16_t* K;
   const uint16_t* V;
-  const int32_t* tier_idx;
+  const int32_t* tier_idx;     // scratch: an item's kept positions from its first token's place on, tier after tier
+  int32_t* tier_idx_out;       // the same without gaps: a tier's from idx_base on
   const int64_t* idx_base;     // [items][4]
   const int32_t* counts;       // [items][4]
   const int64_t* seg_off;      // [items][4][4]
@@ -145,6 +333,8 @@ struct PackArgs {
                                // retained tokens (one scale per channel, App. B), or null (groups of 32 tokens)
   int32_t row_wide;            // token rows: one scale and offset per row (App. B's per-token format), repeated in
                                // the row's four metadata slots, instead of one per group of 32 channels
+  int32_t extra;               // pack_tile_kernel: leading workgroups of every grid row that copy
+  CopyArgs copy;
 };
 
 // monotone map float -> uint32 (and back), so that integer atomic min / max order floats
@@ -158,15 +348,20 @@ __device__ __forceinline__ float ordered_to_float(uint32_t k) {
 
 // The tile of a workgroup: the tiles of an item stand in the order of its tiers, 16, 8, 4, 2 (blockIdx.x counts them).
 struct TileOf {
-  int ti, n, tile;             // tier, rows of the segment, tile inside the segment; ti = 4: past the item's last
-  __device__ __forceinline__ TileOf(const PackArgs& a, int item, int b) : ti(4), n(0), tile(0) {
+  int ti, n, tile, before;     // tier, rows of the segment, tile inside the segment, rows of the higher tiers; ti = 4: past the item's last
+  __device__ __forceinline__ TileOf(const PackArgs& a, int item, int b) : ti(4), n(0), tile(0), before(0) {
     const int4 c = reinterpret_cast<const int4*>(a.counts)[item];
     const int rows[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int t = (rows[k] + kTile64 - 1) / kTile64;
       if (ti == 4) {
-        if (b < t) { ti = k; n = rows[k]; tile = b; } else b -= t;
+        if (b < t) {
+          ti = k; n = rows[k]; tile = b;
+        } else {
+          b -= t;
+          before += rows[k];
+        }
       }
     }
   }
@@ -357,15 +552,22 @@ template <bool V_ONLY>
 __global__ __launch_bounds__(256, 5) void pack_tile_kernel(PackArgs a) {
   __shared__ __align__(16) uint8_t s_buf[kTile64 * (kHeadDim + 8) * 2];   // V codes, or bf16 V rows of the 16-bit tier
   __shared__ __align__(16) uint16_t s_km[kTile64][8];                     // K metadata
+  static_assert(kCopyThreads == 256, "copies in workgroups of this kernel");
   const int item = blockIdx.y;
-  const TileOf t(a, item, blockIdx.x);
+  if (static_cast<int>(blockIdx.x) < a.extra) {
+    const int b = item * a.extra + static_cast<int>(blockIdx.x);
+    if (b < a.copy.first[a.copy.n]) copy_part(a.copy, b);
+    return;
+  }
+  const TileOf t(a, item, static_cast<int>(blockIdx.x) - a.extra);
   if (t.ti == 4) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, c16 = lane & 15, grp = c16 >> 2, p = c16 & 3;
   const int row0 = 16 * wave + 4 * lr;     // this lane's rows row0 .. row0 + 3 of the tile
   const int valid = min(kTile64, t.n - t.tile * kTile64);
-  const int32_t* idx = a.tier_idx + a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kTile64;
   const int64_t item_row = a.item_row_off[item];
+  const int32_t* idx = a.tier_idx + item_row + t.before + static_cast<int64_t>(t.tile) * kTile64;
+  if (tid < valid) a.tier_idx_out[a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kTile64 + tid] = idx[tid];
   uint4 kq[4], vq[4];
   // All positions, then all rows, without a branch (with one per row every position was waited for behind the rows before
   // it: four round trips instead of two).  Rows past the segment's last repeat it and become zeros.
@@ -504,7 +706,7 @@ __global__ __launch_bounds__(kRangeThreads) void k_channel_range_kernel(PackArgs
   const int kept = n4.x + n4.y + n4.z + n4.w;
   const int row0 = blockIdx.x * kRangeRows, step = static_cast<int>(gridDim.x) * kRangeRows;
   if (row0 >= kept) return;                          // (the whole workgroup)
-  const int32_t* idx = a.tier_idx + a.idx_base[item * 4];
+  const int32_t* idx = a.tier_idx + a.item_row_off[item];
   const uint16_t* rows = a.K + a.item_row_off[item] * kHeadDim + c16 * 8;
   union Piece { uint4 q; ushort2v h[4]; };
   Piece mn, mx;
@@ -617,8 +819,8 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
   const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + t.ti) * 4;
   uint16_t* s_rows = reinterpret_cast<uint16_t*>(s_buf);
   {
-    const int32_t* idx = a.tier_idx + a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kRows;
     const int64_t item_row = a.item_row_off[item];
+    const int32_t* idx = a.tier_idx + item_row + t.before + static_cast<int64_t>(t.tile) * kRows;
     constexpr int kPieces = kRows * 16, kLoads = (kPieces + kKThreads - 1) / kKThreads;      // 16 bytes each
     uint4 v[kLoads];
     int pos[kLoads];                     // all positions, then all rows (rows past the last repeat it and become zeros)
@@ -806,36 +1008,37 @@ hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, c
   return hipGetLastError();
 }
 
+// The position lists, the plan and what `copy` holds (planned; at least the counts on their way to the host), in one launch.
 hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                               const int32_t* item_blk_off, const int32_t* blk_counts, const int64_t* idx_base,
-                               int32_t* tier_idx, int n_items, int max_T, hipStream_t st) {
-  const int max_blk = (max_T + kPartBlock - 1) / kPartBlock;
-  if (n_items == 0 || max_blk == 0) return hipSuccess;
-  hipLaunchKernelGGL(tier_scatter_kernel, dim3(max_blk, n_items), dim3(256), 0, st, bits, item_tok_off, item_T,
-                     item_blk_off, reinterpret_cast<const int4*>(blk_counts), idx_base, tier_idx);
+                               const int32_t* item_blk_off, const int32_t* blk_counts, int32_t* tier_idx, const PlanArgs& plan,
+                               int max_T, const CopyArgs& copy, hipStream_t st) {
+  const int max_blk = (max_T + kPartBlock - 1) / kPartBlock, others = copy.first[copy.n] + 1;
+  const ScatterArgs a{bits, item_tok_off, item_T, item_blk_off, reinterpret_cast<const int4*>(blk_counts), tier_idx,
+                      (others + plan.n_items - 1) / plan.n_items, plan, copy};
+  hipLaunchKernelGGL(tier_scatter_kernel, dim3(max_blk + a.extra, plan.n_items), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-// max_tiles: the most 64-row tiles any item has over its tiers
-hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx,
-                             const int64_t* idx_base, const int32_t* counts, const int64_t* seg_off,
-                             const int64_t* item_row_off, uint8_t* arena, int n_items,
-                             int max_tiles, const ItemK* items_k, uint32_t* k_range, int row_wide, hipStream_t st) {
-  if (n_items == 0 || max_tiles == 0) return hipSuccess;
-  const PackArgs a{K, V, tier_idx, idx_base, counts, seg_off, item_row_off, arena, items_k, k_range, row_wide};
-  const dim3 grid(max_tiles, n_items), block(256);
-  if (items_k == nullptr) {
-    hipLaunchKernelGGL(pack_tile_kernel<false>, grid, block, 0, st, a);
+// max_tiles: the most 64-row tiles any item has over its tiers (at least one); k_range must hold (0xFFFFFFFF, 0) pairs on entry.
+// `copy` (planned) goes along.
+hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx, int32_t* tier_idx_out,
+                             const PlanArgs& plan, const int64_t* item_row_off, uint8_t* arena, int max_tiles,
+                             uint32_t* k_range, int row_wide, const CopyArgs& copy, hipStream_t st) {
+  const int n_items = plan.n_items, extra = (copy.first[copy.n] + n_items - 1) / n_items;
+  const PackArgs a{K, V, tier_idx, tier_idx_out, plan.idx_base, plan.counts, plan.seg_off, item_row_off, arena, plan.items_k,
+                   k_range, row_wide, extra, copy};
+  const dim3 grid(max_tiles, n_items), with_copies(max_tiles + extra, n_items), block(256);
+  if (plan.items_k == nullptr) {
+    hipLaunchKernelGGL(pack_tile_kernel<false>, with_copies, block, 0, st, a);
     return hipGetLastError();
   }
-  // k_range must hold (0xFFFFFFFF, 0) pairs on entry
   if (k_range) {
     // 512 workgroups fill the chip; 16 per item are left where there are many items, 128 at most where there are few
     const int parts = std::min(std::max(512 / n_items, 16), 128), most = (max_tiles * kTile64 + kRangeRows - 1) / kRangeRows;
     hipLaunchKernelGGL(k_channel_range_kernel, dim3(std::max(1, std::min(parts, most)), n_items), dim3(kRangeThreads), 0, st, a);
   }
   hipLaunchKernelGGL(pack_k_mixed_kernel, grid, dim3(kKThreads), 0, st, a);
-  hipLaunchKernelGGL(pack_tile_kernel<true>, grid, block, 0, st, a);
+  hipLaunchKernelGGL(pack_tile_kernel<true>, with_copies, block, 0, st, a);
   return hipGetLastError();
 }
 

@@ -20,12 +20,11 @@ namespace rdkv {
 hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
                              const int32_t* item_blk_off, int32_t* blk_counts, int n_items, int max_T, hipStream_t st);
 hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                               const int32_t* item_blk_off, const int32_t* blk_counts, const int64_t* idx_base,
-                               int32_t* tier_idx, int n_items, int max_T, hipStream_t st);
-hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx,
-                             const int64_t* idx_base, const int32_t* counts, const int64_t* seg_off,
-                             const int64_t* item_row_off, uint8_t* arena, int n_items,
-                             int max_tiles, const ItemK* items_k, uint32_t* k_range, int row_wide, hipStream_t st);
+                               const int32_t* item_blk_off, const int32_t* blk_counts, int32_t* tier_idx, const PlanArgs& plan,
+                               int max_T, const CopyArgs& copy, hipStream_t st);
+hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx, int32_t* tier_idx_out,
+                             const PlanArgs& plan, const int64_t* item_row_off, uint8_t* arena, int max_tiles,
+                             uint32_t* k_range, int row_wide, const CopyArgs& copy, hipStream_t st);
 int partition_block();
 int weights_key_tile();
 size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_tokens, int R, bool want_ch);
@@ -377,8 +376,10 @@ hipError_t stage_acquire(size_t bytes, bool held, hipStream_t st, StageRegion* o
 }
 
 // Launches a copy to or from a region.  `last`: the region's only launch and not read by the host; memory that is not of
-// the ring is given back then (after the kernel; the ring looks after itself).
-hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_t st) {
+// the ring is given back then (after the kernel; the ring looks after itself).  `launch`: the kernel that takes the planned copy
+// along (not under capture).
+template <class Launch>
+hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_t st, Launch&& launch) {
   if (r.recorded) {
     const hipError_t e = launch_copy_by_value(a, st);
     std::free(r.own);
@@ -388,13 +389,16 @@ hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_
   a.words = r.words;
   a.seq = r.seq;
   for (int i = a.host_blocks; i < kStageWords; ++i) __atomic_store_n(r.words + i, r.seq, __ATOMIC_RELAXED);   // nobody's
-  hipError_t e = launch_copy(a, st);
+  hipError_t e = launch(a);
   if (e != hipSuccess) r.mark_done();
   if (last && r.own) {
     if (e == hipSuccess) e = stage_wait(r, st);
     (void)hipHostFree(r.own);
   }
   return e;
+}
+hipError_t stage_launch(CopyArgs& a, const StageRegion& r, bool last, hipStream_t st) {
+  return stage_launch(a, r, last, st, [&](const CopyArgs& c) { return launch_copy(c, st); });
 }
 
 // For the calls that wait for the stream: refuses a stream under capture before anything is recorded.
@@ -407,14 +411,18 @@ rdkv_status refuse_capture(hipStream_t st) {
 
 // Launches a copy, waits for it -- and so for everything queued on the stream before it -- and hands the region to `read`.
 // (A copy to pageable memory and a wait for the stream: 25-35 us beyond the work; so 3-5.)
-template <class Read>
-hipError_t stage_round_trip(CopyArgs& a, int device, const StageRegion& r, hipStream_t st, Read&& read) {
-  hipError_t e = stage_launch(a, r, false, st);
+template <class Read, class Launch>
+hipError_t stage_round_trip(CopyArgs& a, int device, const StageRegion& r, hipStream_t st, Read&& read, Launch&& launch) {
+  hipError_t e = stage_launch(a, r, false, st, launch);
   if (e == hipSuccess) e = stage_wait(r, st);
   if (e == hipSuccess) read();
   g_staging[device].release(r);
   if (r.own) (void)hipHostFree(r.own);
   return e;
+}
+template <class Read>
+hipError_t stage_round_trip(CopyArgs& a, int device, const StageRegion& r, hipStream_t st, Read&& read) {
+  return stage_round_trip(a, device, r, st, read, [&](const CopyArgs& c) { return launch_copy(c, st); });
 }
 
 // Waits until everything queued on the stream is done, the caches' write-backs included: a launch that comes after it.
@@ -721,12 +729,11 @@ ItemK make_item_k(const uint8_t* bits_ch) {
   int slot = 0, words = 0, qsteps = 0;
   for (int ti = 0; ti < 4; ++ti) {
     const int b = pack_tier_bits(ti);
-    const int pad = ti == 0 ? 4 : 32 / b;            // whole word pairs (16-bit) / whole words
     k.slot_base[ti] = static_cast<int16_t>(slot);
     int cnt = 0;
     for (int c = 0; c < kHeadDim; ++c)
       if (bits_ch[c] == b) k.slot_ch[slot + cnt++] = static_cast<int16_t>(c);
-    const int npad = (cnt + pad - 1) / pad * pad;
+    const int npad = static_cast<int>(k_tier_slots(ti, static_cast<uint32_t>(cnt)));
     for (int j = cnt; j < npad; ++j) k.slot_ch[slot + j] = -1;
     slot += npad;
     words += npad * b / 32;
@@ -890,9 +897,11 @@ rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables&
   return RDKV_OK;
 }
 
+// d_blk_counts: the tier counts of every block of the bit map when the allocation has left them, or null; d_positions: scratch
+// of a word per token when the caller has some, or null.
 rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const void* K, const void* V,
-                      const uint8_t* bits_tok, const uint8_t* bits_ch, int32_t* d_blk_counts, double* lam,
-                      int32_t* iters, Temp& tmp, hipStream_t st, rdkv_cache** out) {
+                      const uint8_t* bits_tok, const uint8_t* bits_ch, int32_t* d_blk_counts, int32_t* d_positions,
+                      double* lam, int32_t* iters, Temp& tmp, hipStream_t st, rdkv_cache** out) {
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
   Allocator al{cfg->alloc, cfg->free_, cfg->alloc_user};
   const int g = cfg->hq / cfg->hkv;
@@ -920,11 +929,13 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   const bool counted = d_blk_counts != nullptr;
   const int64_t n_counts = it.n_blocks * 4;
   if (!counted) d_blk_counts = tmp.get<int32_t>(n_counts);
-  // [items][4] kept-position bases, [items][16] segment offsets, [items][4] rows per tier
-  int64_t* d_idx_base = tmp.get<int64_t>(n1 * 22);
-  int64_t* d_seg_off = d_idx_base ? d_idx_base + n1 * 4 : nullptr;
-  int32_t* d_counts = d_idx_base ? reinterpret_cast<int32_t*>(d_idx_base + n1 * 20) : nullptr;
-  if (!d_blk_counts || !d_idx_base)
+  if (!d_positions) d_positions = tmp.get<int32_t>(it.total_tokens);
+  PlanArgs plan{tmp.get<int64_t>(n1 * 4), tmp.get<int64_t>(n1 * 16), tmp.get<int32_t>(n1 * 4), mixed ? bits_ch : nullptr,
+                mixed ? tmp.get<ItemK>(n1) : nullptr, static_cast<int32_t>(n), c->k_per_unit};
+  // per-channel (minimum, maximum) over all retained tokens, as ordered integers
+  uint32_t* d_krange = c->k_per_unit ? tmp.get<uint32_t>(n1 * kHeadDim * 2) : nullptr;
+  if (!d_blk_counts || !d_positions || !plan.idx_base || !plan.seg_off || !plan.counts || (mixed && !plan.items_k) ||
+      (c->k_per_unit && !d_krange))
     return bail(fail(RDKV_ERR_ALLOC, "device allocation failed"));
   const int64_t* d_tok_off = tb.tok_off;
   const int32_t* d_T = tb.T;
@@ -932,7 +943,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
 
   if (n > 0) {
     // the one wait of the pass: the tier counts size the arena and the split schedule.  A kernel writes them into pinned
-    // memory and the host watches for them (a copy to host memory and a wait for the stream: 25 us more).
+    // memory and the host watches for them (a copy to host memory and a wait for the stream: 25 us more).  It is the launch
+    // that makes the position lists and the packing kernels' tables, which need nothing from here.
     if (!counted) {
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
       PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, static_cast<int>(n), it.max_T, st));
@@ -947,9 +959,15 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       CopyArgs a{};
       a.add(d_blk_counts, r.data, n_counts * static_cast<int64_t>(sizeof(int32_t)), kDstHost);
       if (mixed) a.add(bits_ch, r.data + counts_b, static_cast<int64_t>(h_bits_ch.size()), kDstHost);
-      PACK_HIP(stage_round_trip(a, dev, r, st, [&] {
+      if (d_krange) a.fill(d_krange, n * kHeadDim * 2 * static_cast<int64_t>(sizeof(uint32_t)), 0xFFFFFFFFu, 0u);
+      const auto read = [&] {
         std::memcpy(h_counts.data(), r.data, h_counts.size() * sizeof(int32_t));
         if (mixed) std::memcpy(h_bits_ch.data(), r.data + counts_b, h_bits_ch.size());
+      };
+      PACK_HIP(stage_round_trip(a, dev, r, st, read, [&](const CopyArgs& ca) {
+        if (it.max_T == 0) return launch_copy(ca, st);      // no tokens, no lists
+        TimedScope ts(RDKV_TIME_PACK, st);
+        return launch_tier_scatter(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_positions, plan, it.max_T, ca, st);
       }));
     }
     if (!counted)
@@ -1333,7 +1351,6 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // ---- allocate what the cache owns: one block --------------------------------------------
   // [arena | appended tokens per item | arrival counters of this stream's workspace]  (cleared together)
   // [kept positions | token bit map | channel bit map | K row layouts, chunk table (one copy) | partials | lambda, steps]
-  uint32_t* d_krange = nullptr;
   {
     auto up = [](int64_t b) { return round_up(std::max<int64_t>(b, 16), 256); };
     const int64_t o_state = c->arena_bytes, o_arrive = o_state + up(n * 4), o_idx = o_arrive + up(n * 4);
@@ -1361,39 +1378,32 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     c->d_chunks = reinterpret_cast<Chunk*>(c->d_block + o_ik + ik_b);
     c->index_bytes = total - c->arena_bytes;     // everything else in the block
     if (n > 0) {
-      // one launch: the tables out of pinned memory, what the block keeps of the pass's scratch, the words that start at
-      // zero (the pack kernels write every byte of the arena)
-      const int64_t plan_b = static_cast<int64_t>(n1) * 22 * 8, tables_b = ik_b + n_table * static_cast<int64_t>(sizeof(Chunk));
-      if (c->k_per_unit) {
-        d_krange = tmp.get<uint32_t>(n * kHeadDim * 2);
-        if (!d_krange) return bail(fail(RDKV_ERR_ALLOC, "device allocation failed"));
-      }
+      // the tables out of pinned memory, what the block keeps of the pass's scratch, the words that start at zero (the pack
+      // kernels write every byte of the arena): in workgroups of the packing launch
+      const int64_t tables_b = ik_b + n_table * static_cast<int64_t>(sizeof(Chunk));
       StageRegion r;
       int dev = 0;
-      PACK_HIP(stage_acquire(static_cast<size_t>(plan_b + tables_b), false, st, &r, &dev));
-      int64_t* plan = reinterpret_cast<int64_t*>(r.data);
-      std::memcpy(plan, idx_base.data(), n * 4 * sizeof(int64_t));
-      std::memcpy(plan + n1 * 4, c->seg_off.data(), n * 16 * sizeof(int64_t));
-      std::memcpy(plan + n1 * 20, c->counts.data(), n * 4 * sizeof(int32_t));
-      uint8_t* tables = r.data + plan_b;
-      if (mixed) std::memcpy(tables, c->items_k.data(), n * sizeof(ItemK));
+      PACK_HIP(stage_acquire(static_cast<size_t>(tables_b), false, st, &r, &dev));
+      if (mixed) std::memcpy(r.data, c->items_k.data(), n * sizeof(ItemK));
       {   // [launched chunks | merging workgroups | continuation pieces]
-        Chunk* t = reinterpret_cast<Chunk*>(tables + ik_b);
+        Chunk* t = reinterpret_cast<Chunk*>(r.data + ik_b);
         std::copy(c->chunks.begin(), c->chunks.end(), t);       // (a schedule has one of the two last)
         merge_chunks(slot_begin, slot_count, n, c->merge_parts, t + n_chunks);
       }
       CopyArgs a{};
-      a.add(plan, d_idx_base, plan_b, kSrcHost);
-      a.add(tables, c->d_block + o_ik, tables_b, kSrcHost);
+      a.add(r.data, c->d_block + o_ik, tables_b, kSrcHost);
       a.fill(c->d_block + o_state, o_idx - o_state, 0u, 0u);     // appended tokens, arrival counters
       if (c->merge_parts > 0) a.fill(c->d_block + o_acc, o_ml - o_acc, merge::kAbsent, merge::kAbsent);
       a.add(bits_tok, c->d_bits_tok, it.total_tokens);
       if (mixed) a.add(bits_ch, c->d_bits_ch, n * kHeadDim);
       if (lam) a.add(lam, c->d_block + o_lam, maps * n * 8);
       if (iters) a.add(iters, c->d_block + o_it, maps * n * 4);
-      // per-channel (minimum, maximum) over all retained tokens, as ordered integers
-      if (d_krange) a.fill(d_krange, n * kHeadDim * 2 * static_cast<int64_t>(sizeof(uint32_t)), 0xFFFFFFFFu, 0u);
-      PACK_HIP(stage_launch(a, r, true, st));
+      PACK_HIP(stage_launch(a, r, true, st, [&](const CopyArgs& ca) {
+        if (kept == 0) return launch_copy(ca, st);
+        TimedScope ts(RDKV_TIME_PACK, st);
+        return launch_quant_pack(static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), d_positions, c->d_tier_idx, plan,
+                                 d_tok_off, c->d_arena, max_tiles, d_krange, c->group_size == kHeadDim ? 1 : 0, ca, st);
+      }));
       c->slot_begin = slot_begin;
       c->slot_count = slot_count;
       {   // the split workspace of this stream lives in the block: a first decode under graph capture allocates nothing
@@ -1407,17 +1417,6 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
     if (iters) c->d_iters = reinterpret_cast<int32_t*>(c->d_block + o_it);
   }
 
-  if (n > 0) {
-    if (kept > 0) {
-      TimedScope ts(RDKV_TIME_PACK, st);      // second half: kept-position lists, quantize and pack
-      PACK_HIP(launch_tier_scatter(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_idx_base, c->d_tier_idx,
-                                   static_cast<int>(n), it.max_T, st));
-      PACK_HIP(launch_quant_pack(static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), c->d_tier_idx,
-                                 d_idx_base, d_counts, d_seg_off, d_tok_off, c->d_arena, static_cast<int>(n),
-                                 max_tiles, mixed ? c->d_items_k : nullptr, d_krange,
-                                 c->group_size == kHeadDim ? 1 : 0, st));
-    }
-  }
 #undef PACK_HIP
   *out = c;
   return RDKV_OK;
@@ -1614,7 +1613,7 @@ rdkv_status rdkv_pack(const rdkv_config* cfg, const void* K, const void* V, cons
   Tables tb;
   s = make_tables(cfg, it, false, tmp, st, &tb);
   if (s != RDKV_OK) return s;
-  return pack_impl(cfg, it, tb, K, V, bits_tok, bits_ch, nullptr, nullptr, nullptr, tmp, st, out);
+  return pack_impl(cfg, it, tb, K, V, bits_tok, bits_ch, nullptr, nullptr, nullptr, nullptr, tmp, st, out);
 }
 
 rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, const void* Q_obs, void* stream,
@@ -1639,7 +1638,8 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
     for (int64_t i = 0; i < it.n_items; ++i) n_wblk += (it.T[i] + key_tile - 1) / key_tile;
     tmp.reserve({36 * ni + 16, nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
                  weights_scratch_floats(n_wblk, it.n_items, it.total_tokens, R, mixed) * sizeof(float),
-                 static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t), ni * 22 * sizeof(int64_t), ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),
+                 static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t), ni * 4 * sizeof(int64_t), ni * 16 * sizeof(int64_t),
+                 ni * 4 * sizeof(int32_t), mixed ? ni * sizeof(ItemK) : 0, ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),
                  allocate_scratch_bytes(static_cast<int>(it.n_items), it.max_T),
                  allocate_needs_order(static_cast<int>(it.n_items), it.max_T) ? ni * sizeof(int32_t) : 0,
                  mixed && cfg->k_scale_per_channel ? nc * 2 * sizeof(uint32_t) : 0});
@@ -1652,7 +1652,7 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   float* w_ch = mixed ? tmp.get<float>(nc) : nullptr;
   uint8_t* bits_ch = mixed ? tmp.get<uint8_t>(nc) : nullptr;
   if (!w || !bits || (mixed && (!w_ch || !bits_ch))) return fail(RDKV_ERR_ALLOC, "device allocation failed");
-  if (it.n_items == 0) return pack_impl(cfg, it, tb, K, V, bits, bits_ch, nullptr, nullptr, nullptr, tmp, st, out);
+  if (it.n_items == 0) return pack_impl(cfg, it, tb, K, V, bits, bits_ch, nullptr, nullptr, nullptr, nullptr, tmp, st, out);
   // the multiplier and the step count of every item's search stay with the cache (rdkv_cache_stats / export): the
   // pack stage copies them into the cache's block
   const int maps = mixed ? 2 : 1;
@@ -1665,7 +1665,8 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   if (!blk_counts) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   s = allocate_impl(cfg, it, tb, w, w_ch, bits, bits_ch, lam, iters, blk_counts, tmp, st);
   if (s != RDKV_OK) return s;
-  return pack_impl(cfg, it, tb, K, V, bits, bits_ch, blk_counts, lam, iters, tmp, st, out);
+  // (the weights are used up: their memory takes the kept positions)
+  return pack_impl(cfg, it, tb, K, V, bits, bits_ch, blk_counts, reinterpret_cast<int32_t*>(w), lam, iters, tmp, st, out);
 }
 
 // A-priori bound on the packed arena from the budget alone (Sec. 3.2: sum of bit-widths <= floor(avg * units)).

@@ -62,6 +62,22 @@ struct ItemK {
   int16_t slot_ch[kMaxSlots];    // channel held by a slot, -1 for padding
 };
 
+// Slots of a tier of a K row with n channels (ItemK): whole word pairs of 16-bit slots, whole words of the others.
+__host__ __device__ inline uint32_t k_tier_slots(int ti, uint32_t n) {
+  const uint32_t pad = ti == 0 ? 4u : 2u << ti;
+  return (n + pad - 1u) & ~(pad - 1u);
+}
+// Device tables that one workgroup of the launch with the position lists makes for the packing kernels, so that these wait for
+// nothing that the host makes.
+struct PlanArgs {
+  int64_t* idx_base;             // [items][4]: first of a tier's kept positions
+  int64_t* seg_off;              // [items][4][4]: arena offsets
+  int32_t* counts;               // [items][4]: rows per tier
+  const uint8_t* bits_ch;        // [items][128] channel-wise K, or null
+  ItemK* items_k;                // [items] channel-wise K, or null
+  int32_t n_items, per_unit;     // per_unit: one K scale per channel
+};
+
 // Lets a kernel use more dynamic LDS than the runtime grants by default; asked once per kernel and device (a call costs
 // 0.5 us).
 template <class K>

@@ -36,14 +36,11 @@ constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxHull = 5;
 constexpr int kThr = kMaxHull - 1;
-constexpr int kBlockUnits = 1024;   // units per block of the per-block tier counts (the packing stage's partition block)
+constexpr int kBlockUnits = kPartBlock;   // units per block of the per-block tier counts
 static_assert(kBlockUnits == kThreads, "a quarter of a round of allocate_item_kernel is one block");
 
 struct AllocArgs {
   const float* w;
-  const int64_t* item_off;
-  const int32_t* item_U;
-  const double* item_budget;   // average bits per unit
   uint8_t* bits;
   double r[kMaxHull];          // r[k-1]: threshold ratio into hull tier k
   int32_t tiers[kMaxHull];
@@ -52,10 +49,10 @@ struct AllocArgs {
   double need_frac;            // 1 - rel_tol
   double* lam_out;             // [items] or null: the multiplier of the returned allocation (NaN: no search ran)
   int32_t* iters_out;          // [items] or null: bisection steps taken
-  const int32_t* item_blk_off; // [items]: first 1024-unit block of the item, or null (no counts wanted)
-  int4* blk_counts;            // [blocks] out: units of the block in tiers 16, 8, 4, 2
+  int4* blk_counts;            // [blocks] out: units of the block in tiers 16, 8, 4, 2; or null
   const int32_t* order;        // the items of this launch, or null: all of them as they stand
-  __device__ __forceinline__ int item_of(int slot) const { return order ? order[slot] : slot; }
+  Batch batch;
+  __device__ __forceinline__ int item_of(int slot) const { return order ? __builtin_amdgcn_readfirstlane(order[slot]) : slot; }
 };
 
 // largest fp32 number not above t (t >= 0): for fp32 w, (double) w > t exactly when w > below(t)
@@ -468,10 +465,11 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   __shared__ Search s_search;
   __shared__ Hull s_hull;
   const int item = a.item_of(blockIdx.x);
-  const int U = a.item_U[item];
+  const ItemOf it(a.batch, item);
+  const int U = it.T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float* __restrict__ w = a.w + a.item_off[item];
-  uint8_t* __restrict__ bits = a.bits + a.item_off[item];
+  const float* __restrict__ w = a.w + it.off;
+  uint8_t* __restrict__ bits = a.bits + it.off;
   float v[REG];                            // units past the end read as 0: never above a threshold
 #pragma unroll
   for (int j = 0; j < kQ; ++j) {
@@ -486,7 +484,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
     }
   }
   for (int i = tid; i < Anchored::kWords / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
-  const Problem P(a, U, a.item_budget[item]);
+  const Problem P(a, U, it.budget);
   const int fill = U > 0 ? P.fill(U) : P.tiers[0];
   Search S{0.0, 0.0, 0.0, 0, 0, 0};
   float t[kThr];
@@ -618,7 +616,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
     for (int u = tid; u < U; u += kThreads) bits[u] = static_cast<uint8_t>(fill);
     if (a.blk_counts && tid < nblk) {
       const int n = min(kBlockUnits, U - tid * kBlockUnits);
-      a.blk_counts[a.item_blk_off[item] + tid] =
+      a.blk_counts[it.blk0 + tid] =
           make_int4(fill == 16 ? n : 0, fill == 8 ? n : 0, fill == 4 ? n : 0, fill == 2 ? n : 0);
     }
     return;
@@ -656,7 +654,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
         const int4 x = s_cnt[4 * tid + i];
         c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
       }
-      a.blk_counts[a.item_blk_off[item] + tid] = tier_counts(P, min(kBlockUnits, U - tid * kBlockUnits), c);
+      a.blk_counts[it.blk0 + tid] = tier_counts(P, min(kBlockUnits, U - tid * kBlockUnits), c);
     }
   }
 }
@@ -733,8 +731,9 @@ __device__ __forceinline__ T load_agent(const T* p) {
 // quarter of the resolution: hist_kernel 21 us, gather_kernel 20 at 8 x 128K units), and zeros for the next kernels.
 __global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, uint4* clear, int64_t n_clear) {
   __shared__ float s_max[kWaves];
-  const int row = blockIdx.y, item = m.a.item_of(row), tid = threadIdx.x;
-  const Quads quads(m.a.w + m.a.item_off[item], m.a.item_U[item]);
+  const int row = blockIdx.y, tid = threadIdx.x;
+  const ItemOf it(m.a.batch, m.a.item_of(row));
+  const Quads quads(m.a.w + it.off, it.T);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
   const int64_t step = static_cast<int64_t>(gridDim.x) * gridDim.y * kThreads;
@@ -765,16 +764,17 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   __shared__ Search s_search;
   const AllocArgs& a = m.a;
   const int row = blockIdx.y, item = a.item_of(row);
-  const int U = a.item_U[item];
+  const ItemOf it(a.batch, item);
+  const int U = it.T;
   const int tid = threadIdx.x, lane = tid & 63;
   SearchState& st = m.state[row];
-  const Quads quads(a.w + a.item_off[item], U);
+  const Quads quads(a.w + it.off, U);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
   float mx = lane < m.slices ? m.slice_max[row * m.slices + lane] : 0.f;       // (at most 16 slices)
   float wv[4] = {0.f, 0.f, 0.f, 0.f};
   if (q0 + tid < q1) quads.load(q0 + tid, wv);
-  const Problem P(a, U, a.item_budget[item]);
+  const Problem P(a, U, it.budget);
   const int fill = U > 0 ? P.fill(U) : P.tiers[0];
   if (fill >= 0) {
     if (blockIdx.x == 0 && tid == 0) {
@@ -859,9 +859,10 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   if (st.s.done) return;                    // written by the previous kernel
   const int n = st.n_open;
   if (n > kListCap && blockIdx.x != 0) return;
-  const int U = a.item_U[item];
+  const ItemOf it(a.batch, item);
+  const int U = it.T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const Quads quads(a.w + a.item_off[item], U);
+  const Quads quads(a.w + it.off, U);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
   Search S = st.s;
@@ -898,7 +899,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
     for (int i = tid; i < mine; i += kThreads)
       __hip_atomic_store(gl + s_base + i, s_list[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!last_to_arrive(&st.arrive[1], m.slices, &s_flag)) return;
-    const Problem P(a, U, a.item_budget[item]);
+    const Problem P(a, U, it.budget);
     const long long fixed = st.fixed;
     const Hull hull = st.hull;
     if (n <= kFewOpen) {
@@ -916,7 +917,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   } else {
     // More than the list holds (weights all alike, or in a band of a few ulp): every step on all units, one workgroup.
     // 8 items of 128K units, one value, 64 steps: 820 us (with fp64 comparisons 1470); a band of 1e-3, 20 steps: 190 (440).
-    const Problem P(a, U, a.item_budget[item]);
+    const Problem P(a, U, it.budget);
     while (!S.done && S.it < P.max_iters) {
       const double lam = (S.lo + S.hi) * 0.5;
       float t[kThr];
@@ -957,16 +958,17 @@ __global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
   __shared__ int4 s_cnt[4];
   const AllocArgs& a = m.a;
   const int row = blockIdx.y, item = a.item_of(row);
-  const int U = a.item_U[item];
+  const ItemOf it(a.batch, item);
+  const int U = it.T;
   const int u0 = blockIdx.x * kBlockUnits, tid = threadIdx.x;
   if (u0 >= U) return;
   const SearchState& st = m.state[row];
-  const float* __restrict__ w = a.w + a.item_off[item];
-  uint8_t* __restrict__ bits = a.bits + a.item_off[item];
+  const float* __restrict__ w = a.w + it.off;
+  uint8_t* __restrict__ bits = a.bits + it.off;
   float v[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) v[j] = u0 + 256 * j + tid < U ? w[u0 + 256 * j + tid] : 0.f;
-  const Problem P(a, U, a.item_budget[item]);
+  const Problem P(a, U, it.budget);
   const int n = min(kBlockUnits, U - u0);
   const int fill = st.fill >= 0 ? st.fill : (st.s.have ? -1 : P.tiers[0]);
   if (fill >= 0) {
@@ -974,7 +976,7 @@ __global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
     for (int j = 0; j < 4; ++j)
       if (u0 + 256 * j + tid < U) bits[u0 + 256 * j + tid] = static_cast<uint8_t>(fill);
     if (a.blk_counts && tid == 0)
-      a.blk_counts[a.item_blk_off[item] + blockIdx.x] =
+      a.blk_counts[it.blk0 + blockIdx.x] =
           make_int4(fill == 16 ? n : 0, fill == 8 ? n : 0, fill == 4 ? n : 0, fill == 2 ? n : 0);
     return;
   }
@@ -997,7 +999,7 @@ __global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
     int4 x = s_cnt[0];
 #pragma unroll
     for (int i = 1; i < 4; ++i) { x.x += s_cnt[i].x; x.y += s_cnt[i].y; x.z += s_cnt[i].z; x.w += s_cnt[i].w; }
-    a.blk_counts[a.item_blk_off[item] + blockIdx.x] = tier_counts(P, n, x);
+    a.blk_counts[it.blk0 + blockIdx.x] = tier_counts(P, n, x);
   }
 }
 
@@ -1006,11 +1008,8 @@ __global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
 // to fp32 like every budget.  fp64 in this operation order (the file is compiled without contraction).  The map over
 // the item's 128 channels is then searched by one wavefront, two channels per lane.
 struct ChannelArgs {
-  AllocArgs a;                 // w, bits: the channel weights and map [items][128]; item_off, item_U, item_budget unused
+  AllocArgs a;                 // w, bits: the channel weights and map [items][128]
   const int4* blk_counts;      // [blocks] of the token maps: kept tokens per tier
-  const int32_t* item_blk_off;
-  const int32_t* item_T;
-  const double* item_avg;      // average bits per cache element of the item's sequence
   double rk;
 };
 __global__ __launch_bounds__(64) void channel_allocate_kernel(ChannelArgs c) {
@@ -1018,8 +1017,9 @@ __global__ __launch_bounds__(64) void channel_allocate_kernel(ChannelArgs c) {
   const int item = blockIdx.x, lane = threadIdx.x;
   const float* w = a.w + static_cast<int64_t>(item) * kHeadDim;
   const float v[2] = {w[lane], w[64 + lane]};
-  const int4* bc = c.blk_counts + c.item_blk_off[item];
-  const int nblk = (c.item_T[item] + kBlockUnits - 1) / kBlockUnits;
+  const ItemOf it(a.batch, item);
+  const int4* bc = c.blk_counts + it.blk0;
+  const int nblk = (it.T + kBlockUnits - 1) / kBlockUnits;
   int kept = 0;
   for (int i = lane; i < nblk; i += 64) {
     const int4 n = bc[i];
@@ -1028,7 +1028,7 @@ __global__ __launch_bounds__(64) void channel_allocate_kernel(ChannelArgs c) {
   for (int o = 32; o > 0; o >>= 1) kept += __shfl_xor(kept, o);
   double k_avg = 0.0;
   if (kept > 0)
-    k_avg = fmin(16.0, 2.0 * c.rk * c.item_avg[item] * static_cast<double>(c.item_T[item]) / static_cast<double>(kept));
+    k_avg = fmin(16.0, 2.0 * c.rk * it.avg * static_cast<double>(it.T) / static_cast<double>(kept));
   const Problem P(a, kHeadDim, static_cast<double>(static_cast<float>(k_avg)));
   uint8_t* bits = a.bits + static_cast<int64_t>(item) * kHeadDim;
   const int fill = P.fill(kHeadDim);
@@ -1048,10 +1048,10 @@ __global__ __launch_bounds__(64) void channel_allocate_kernel(ChannelArgs c) {
   if (lane == 0) report(a, item, fill < 0, S);
 }
 
-AllocArgs make_args(const float* w, int n_hull, const int* hull_tiers, const double* hull_r, double need_frac,
+AllocArgs make_args(const float* w, const Batch& batch, int n_hull, const int* hull_tiers, const double* hull_r, double need_frac,
                     int max_iters, uint8_t* bits, double* lam_out, int32_t* iters_out) {
   AllocArgs a{};
-  a.w = w; a.bits = bits;
+  a.w = w; a.bits = bits; a.batch = batch;
   for (int k = 0; k < kMaxHull; ++k) {
     a.tiers[k] = k < n_hull ? hull_tiers[k] : 0;
     a.r[k] = k < n_hull - 1 ? hull_r[k] : 0.0;
@@ -1120,18 +1120,16 @@ size_t allocate_scratch_bytes(int n_items, int max_U) {
 }
 
 // Token maps of all items.  d_order (where allocate_needs_order): the items, the n_long of more than allocate_short_units()
-// first, the others with up to max_short units.  blk_counts (with item_blk_off): what the packing stage needs, or null.
-hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
-                           const double* d_item_budget, int n_items, int max_U, const int32_t* d_order, int n_long,
+// first, the others with up to max_short units.  blk_counts: what the packing stage needs, or null.
+hipError_t launch_allocate(const float* w, const Batch& batch, int max_U, const int32_t* d_order, int n_long,
                            int max_short, int n_hull, const int* hull_tiers,
                            const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
-                           int32_t* iters_out, const int32_t* d_item_blk_off, int32_t* blk_counts, void* scratch,
-                           hipStream_t st) {
+                           int32_t* iters_out, int32_t* blk_counts, void* scratch, hipStream_t st) {
+  const int n_items = batch.n_seqs * batch.hkv;
   if (n_items == 0) return hipSuccess;
   if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
-  AllocArgs a = make_args(w, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits, lam_out, iters_out);
-  a.item_off = d_item_off; a.item_U = d_item_U; a.item_budget = d_item_budget;
-  a.item_blk_off = d_item_blk_off; a.blk_counts = reinterpret_cast<int4*>(blk_counts);
+  AllocArgs a = make_args(w, batch, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits, lam_out, iters_out);
+  a.blk_counts = reinterpret_cast<int4*>(blk_counts);
   if (max_U <= kItemUnits) return launch_short_items(a, n_items, max_U, st);
   if (!scratch || (!d_order && n_items > kMostTogether)) return hipErrorInvalidValue;
   if (!d_order) return launch_items_together(a, n_items, max_U, scratch, st);
@@ -1145,16 +1143,16 @@ hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int3
 }
 
 // Stage 3: the channel maps, from the kept tokens launch_allocate has counted.
-hipError_t launch_allocate_channels(const float* w_ch, const int32_t* blk_counts, const int32_t* d_item_blk_off,
-                                    const int32_t* d_item_T,
-                                    const double* d_item_avg, double rk, int n_items, int n_hull, const int* hull_tiers,
+hipError_t launch_allocate_channels(const float* w_ch, const Batch& batch, const int32_t* blk_counts, double rk, int n_hull,
+                                    const int* hull_tiers,
                                     const double* hull_r, double need_frac, int max_iters, uint8_t* bits_ch,
                                     double* lam_out, int32_t* iters_out, hipStream_t st) {
+  const int n_items = batch.n_seqs * batch.hkv;
   if (n_items == 0) return hipSuccess;
   if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
   ChannelArgs c;
-  c.a = make_args(w_ch, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits_ch, lam_out, iters_out);
-  c.blk_counts = reinterpret_cast<const int4*>(blk_counts); c.item_blk_off = d_item_blk_off; c.item_T = d_item_T; c.item_avg = d_item_avg; c.rk = rk;
+  c.a = make_args(w_ch, batch, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits_ch, lam_out, iters_out);
+  c.blk_counts = reinterpret_cast<const int4*>(blk_counts); c.rk = rk;
   hipLaunchKernelGGL(channel_allocate_kernel, dim3(n_items), dim3(64), 0, st, c);
   return hipGetLastError();
 }

@@ -21,8 +21,6 @@ namespace rdkv {
 
 namespace {
 
-constexpr int kPartBlock = 1024;   // tokens per partition block
-
 __device__ __forceinline__ int tier_slot(uint8_t b) {   // 16,8,4,2 -> 0..3 ; else -1
   return b == 16 ? 0 : b == 8 ? 1 : b == 4 ? 2 : b == 2 ? 3 : -1;
 }
@@ -32,18 +30,15 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 
 // Counts of each stored tier inside every block of 1024 tokens of every item; a first count of -1: the block holds a value
 // that is no bit-width.
-__global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restrict__ bits,
-                                                         const int64_t* __restrict__ item_tok_off,
-                                                         const int32_t* __restrict__ item_T,
-                                                         const int32_t* __restrict__ item_blk_off,
-                                                         int4* __restrict__ blk_counts) {
+__global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restrict__ bits, int4* __restrict__ blk_counts,
+                                                         Batch batch) {
   __shared__ int s_cnt[4][5];
-  const int item = blockIdx.y;
-  const int T = item_T[item];
+  const ItemOf it(batch, blockIdx.y);
+  const int T = it.T;
   const int t0 = blockIdx.x * kPartBlock;
   if (t0 >= T) return;
   const int tid = threadIdx.x, wave = tid >> 6;
-  const uint8_t* b = bits + item_tok_off[item] + t0;
+  const uint8_t* b = bits + it.off + t0;
   const int n = min(kPartBlock, T - t0), u = 4 * tid;
   uint32_t four = 0;
   if (u + 3 < n) four = reinterpret_cast<const Bytes4*>(b + u)->v;
@@ -67,7 +62,7 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
     int sum[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) sum[k] = s_cnt[0][k] + s_cnt[1][k] + s_cnt[2][k] + s_cnt[3][k];
-    blk_counts[item_blk_off[item] + blockIdx.x] = make_int4(sum[4] > 0 ? -1 : sum[0], sum[1], sum[2], sum[3]);
+    blk_counts[it.blk0 + blockIdx.x] = make_int4(sum[4] > 0 ? -1 : sum[0], sum[1], sum[2], sum[3]);
   }
 }
 
@@ -83,14 +78,12 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
 // compressing two heads of 4K keys took 58.0 us, eight of 128K 242; now 53.2 and 234.
 struct ScatterArgs {
   const uint8_t* bits;
-  const int64_t* item_tok_off;
-  const int32_t* item_T;
-  const int32_t* item_blk_off;
   const int4* blk_counts;
   int32_t* tier_idx;
   int32_t extra;                 // leading workgroups of every grid row that do other things
   PlanArgs plan;
   CopyArgs copy;
+  Batch batch;
 };
 
 // counts of a block; one that holds a value that is no bit-width (the host refuses the map) counts as empty there
@@ -128,7 +121,8 @@ __device__ __forceinline__ void plan_part(const ScatterArgs& a) {
   for (int i0 = 0; i0 < p.n_items; i0 += per_round) {
     const int item = i0 + tid / lanes;
     const bool in = item < p.n_items;
-    const int nb = in ? (a.item_T[item] + kPartBlock - 1) / kPartBlock : 0, first = in ? a.item_blk_off[item] : 0;
+    const ItemOf it(a.batch, in ? item : 0);
+    const int nb = in ? (it.T + kPartBlock - 1) / kPartBlock : 0, first = it.blk0;
     uint32_t cnt[4] = {0, 0, 0, 0};
 #pragma unroll 4
     for (int b = sub; b < nb; b += lanes) {
@@ -252,11 +246,12 @@ __global__ __launch_bounds__(256) void tier_scatter_kernel(ScatterArgs a) {
     return;
   }
   const int item = blockIdx.y, block = static_cast<int>(blockIdx.x) - a.extra;
-  const int T = a.item_T[item];
+  const ItemOf it(a.batch, item);
+  const int T = it.T;
   const int t0 = block * kPartBlock;
   if (t0 >= T) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t tok_off = a.item_tok_off[item];
+  const int64_t tok_off = it.off;
   const uint8_t* b = a.bits + tok_off + t0;
   const int n = min(kPartBlock, T - t0), u = 4 * tid;
   uint32_t four = 0;                       // tokens past the end: evicted
@@ -267,7 +262,7 @@ __global__ __launch_bounds__(256) void tier_scatter_kernel(ScatterArgs a) {
   int before[4] = {0, 0, 0, 0}, all[4] = {0, 0, 0, 0};      // kept tokens of the item's earlier blocks, of all of them
   const int n_blocks = (T + kPartBlock - 1) / kPartBlock;
   for (int i = tid; i < n_blocks; i += 256) {
-    const int4 x = block_counts(a.blk_counts, a.item_blk_off[item] + i);
+    const int4 x = block_counts(a.blk_counts, it.blk0 + i);
     const int c[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -326,7 +321,6 @@ struct PackArgs {
   const int64_t* idx_base;     // [items][4]
   const int32_t* counts;       // [items][4]
   const int64_t* seg_off;      // [items][4][4]
-  const int64_t* item_row_off; // [items]: first row of the item's [T][d] block in K / V
   uint8_t* arena;
   const ItemK* items_k;        // [items] (mixed mode)
   uint32_t* k_range;           // [items][128][2]: ordered-integer images of a channel's minimum and maximum over all
@@ -335,6 +329,7 @@ struct PackArgs {
                                // the row's four metadata slots, instead of one per group of 32 channels
   int32_t extra;               // pack_tile_kernel: leading workgroups of every grid row that copy
   CopyArgs copy;
+  Batch batch;
 };
 
 // monotone map float -> uint32 (and back), so that integer atomic min / max order floats
@@ -565,7 +560,7 @@ __global__ __launch_bounds__(256, 5) void pack_tile_kernel(PackArgs a) {
   const int lr = lane >> 4, c16 = lane & 15, grp = c16 >> 2, p = c16 & 3;
   const int row0 = 16 * wave + 4 * lr;     // this lane's rows row0 .. row0 + 3 of the tile
   const int valid = min(kTile64, t.n - t.tile * kTile64);
-  const int64_t item_row = a.item_row_off[item];
+  const int64_t item_row = ItemOf(a.batch, item).off;
   const int32_t* idx = a.tier_idx + item_row + t.before + static_cast<int64_t>(t.tile) * kTile64;
   if (tid < valid) a.tier_idx_out[a.idx_base[item * 4 + t.ti] + static_cast<int64_t>(t.tile) * kTile64 + tid] = idx[tid];
   uint4 kq[4], vq[4];
@@ -706,8 +701,9 @@ __global__ __launch_bounds__(kRangeThreads) void k_channel_range_kernel(PackArgs
   const int kept = n4.x + n4.y + n4.z + n4.w;
   const int row0 = blockIdx.x * kRangeRows, step = static_cast<int>(gridDim.x) * kRangeRows;
   if (row0 >= kept) return;                          // (the whole workgroup)
-  const int32_t* idx = a.tier_idx + a.item_row_off[item];
-  const uint16_t* rows = a.K + a.item_row_off[item] * kHeadDim + c16 * 8;
+  const int64_t item_row = ItemOf(a.batch, item).off;
+  const int32_t* idx = a.tier_idx + item_row;
+  const uint16_t* rows = a.K + item_row * kHeadDim + c16 * 8;
   union Piece { uint4 q; ushort2v h[4]; };
   Piece mn, mx;
   mn.q = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
@@ -819,7 +815,7 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
   const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + t.ti) * 4;
   uint16_t* s_rows = reinterpret_cast<uint16_t*>(s_buf);
   {
-    const int64_t item_row = a.item_row_off[item];
+    const int64_t item_row = ItemOf(a.batch, item).off;
     const int32_t* idx = a.tier_idx + item_row + t.before + static_cast<int64_t>(t.tile) * kRows;
     constexpr int kPieces = kRows * 16, kLoads = (kPieces + kKThreads - 1) / kKThreads;      // 16 bytes each
     uint4 v[kLoads];
@@ -999,22 +995,18 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
 
 }  // namespace
 
-hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                             const int32_t* item_blk_off, int32_t* blk_counts, int n_items, int max_T, hipStream_t st) {
-  const int max_blk = (max_T + kPartBlock - 1) / kPartBlock;
+hipError_t launch_tier_count(const uint8_t* bits, const Batch& batch, int32_t* blk_counts, int max_T, hipStream_t st) {
+  const int max_blk = (max_T + kPartBlock - 1) / kPartBlock, n_items = batch.n_seqs * batch.hkv;
   if (n_items == 0 || max_blk == 0) return hipSuccess;
-  hipLaunchKernelGGL(tier_count_kernel, dim3(max_blk, n_items), dim3(256), 0, st, bits, item_tok_off, item_T,
-                     item_blk_off, reinterpret_cast<int4*>(blk_counts));
+  hipLaunchKernelGGL(tier_count_kernel, dim3(max_blk, n_items), dim3(256), 0, st, bits, reinterpret_cast<int4*>(blk_counts), batch);
   return hipGetLastError();
 }
 
 // The position lists, the plan and what `copy` holds (planned; at least the counts on their way to the host), in one launch.
-hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                               const int32_t* item_blk_off, const int32_t* blk_counts, int32_t* tier_idx, const PlanArgs& plan,
-                               int max_T, const CopyArgs& copy, hipStream_t st) {
+hipError_t launch_tier_scatter(const uint8_t* bits, const Batch& batch, const int32_t* blk_counts, int32_t* tier_idx,
+                               const PlanArgs& plan, int max_T, const CopyArgs& copy, hipStream_t st) {
   const int max_blk = (max_T + kPartBlock - 1) / kPartBlock, others = copy.first[copy.n] + 1;
-  const ScatterArgs a{bits, item_tok_off, item_T, item_blk_off, reinterpret_cast<const int4*>(blk_counts), tier_idx,
-                      (others + plan.n_items - 1) / plan.n_items, plan, copy};
+  const ScatterArgs a{bits, reinterpret_cast<const int4*>(blk_counts), tier_idx, (others + plan.n_items - 1) / plan.n_items, plan, copy, batch};
   hipLaunchKernelGGL(tier_scatter_kernel, dim3(max_blk + a.extra, plan.n_items), dim3(256), 0, st, a);
   return hipGetLastError();
 }
@@ -1022,11 +1014,11 @@ hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off,
 // max_tiles: the most 64-row tiles any item has over its tiers (at least one); k_range must hold (0xFFFFFFFF, 0) pairs on entry.
 // `copy` (planned) goes along.
 hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx, int32_t* tier_idx_out,
-                             const PlanArgs& plan, const int64_t* item_row_off, uint8_t* arena, int max_tiles,
+                             const PlanArgs& plan, const Batch& batch, uint8_t* arena, int max_tiles,
                              uint32_t* k_range, int row_wide, const CopyArgs& copy, hipStream_t st) {
   const int n_items = plan.n_items, extra = (copy.first[copy.n] + n_items - 1) / n_items;
-  const PackArgs a{K, V, tier_idx, tier_idx_out, plan.idx_base, plan.counts, plan.seg_off, item_row_off, arena, plan.items_k,
-                   k_range, row_wide, extra, copy};
+  const PackArgs a{K, V, tier_idx, tier_idx_out, plan.idx_base, plan.counts, plan.seg_off, arena, plan.items_k,
+                   k_range, row_wide, extra, copy, batch};
   const dim3 grid(max_tiles, n_items), with_copies(max_tiles + extra, n_items), block(256);
   if (plan.items_k == nullptr) {
     hipLaunchKernelGGL(pack_tile_kernel<false>, with_copies, block, 0, st, a);
@@ -1041,7 +1033,5 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
   hipLaunchKernelGGL(pack_tile_kernel<true>, with_copies, block, 0, st, a);
   return hipGetLastError();
 }
-
-int partition_block() { return kPartBlock; }
 
 }  // namespace rdkv

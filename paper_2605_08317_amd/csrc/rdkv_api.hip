@@ -17,33 +17,25 @@
 #include "rdkv_internal.h"
 
 namespace rdkv {
-hipError_t launch_tier_count(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                             const int32_t* item_blk_off, int32_t* blk_counts, int n_items, int max_T, hipStream_t st);
-hipError_t launch_tier_scatter(const uint8_t* bits, const int64_t* item_tok_off, const int32_t* item_T,
-                               const int32_t* item_blk_off, const int32_t* blk_counts, int32_t* tier_idx, const PlanArgs& plan,
-                               int max_T, const CopyArgs& copy, hipStream_t st);
+hipError_t launch_tier_count(const uint8_t* bits, const Batch& batch, int32_t* blk_counts, int max_T, hipStream_t st);
+hipError_t launch_tier_scatter(const uint8_t* bits, const Batch& batch, const int32_t* blk_counts, int32_t* tier_idx,
+                               const PlanArgs& plan, int max_T, const CopyArgs& copy, hipStream_t st);
 hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t* tier_idx, int32_t* tier_idx_out,
-                             const PlanArgs& plan, const int64_t* item_row_off, uint8_t* arena, int max_tiles,
+                             const PlanArgs& plan, const Batch& batch, uint8_t* arena, int max_tiles,
                              uint32_t* k_range, int row_wide, const CopyArgs& copy, hipStream_t st);
-int partition_block();
-int weights_key_tile();
 size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_tokens, int R, bool want_ch);
-hipError_t launch_weights(const rdkv_config& cfg, const int64_t* d_item_row_off, const int32_t* d_item_T,
-                          const int32_t* d_item_tile_off, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
+hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
                           int max_T, const uint16_t* K, const uint16_t* Q_obs, float* w_tok, float* w_ch,
                           float* scratch, hipStream_t st);
 size_t allocate_scratch_bytes(int n_items, int max_U);
 bool allocate_needs_order(int n_items, int max_U);
 int allocate_short_units();
-hipError_t launch_allocate(const float* w, const int64_t* d_item_off, const int32_t* d_item_U,
-                           const double* d_item_budget, int n_items, int max_U, const int32_t* d_order, int n_long,
+hipError_t launch_allocate(const float* w, const Batch& batch, int max_U, const int32_t* d_order, int n_long,
                            int max_short, int n_hull, const int* hull_tiers,
                            const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
-                           int32_t* iters_out, const int32_t* d_item_blk_off, int32_t* blk_counts, void* scratch,
-                           hipStream_t st);
-hipError_t launch_allocate_channels(const float* w_ch, const int32_t* blk_counts, const int32_t* d_item_blk_off,
-                                    const int32_t* d_item_T,
-                                    const double* d_item_avg, double rk, int n_items, int n_hull, const int* hull_tiers,
+                           int32_t* iters_out, int32_t* blk_counts, void* scratch, hipStream_t st);
+hipError_t launch_allocate_channels(const float* w_ch, const Batch& batch, const int32_t* blk_counts, double rk, int n_hull,
+                                    const int* hull_tiers,
                                     const double* hull_r, double need_frac, int max_iters, uint8_t* bits_ch,
                                     double* lam_out, int32_t* iters_out, hipStream_t st);
 hipError_t launch_calibrate(const uint16_t* K, const uint16_t* V, const int64_t* item_row_off, const int32_t* item_T,
@@ -460,7 +452,6 @@ struct Items {
 
 Items make_items(const int32_t* seq_lens, int batch, int hkv) {
   Items it;
-  const int pb = partition_block();
   int64_t off = 0;
   int64_t blk = 0;
   for (int s = 0; s < batch; ++s) {
@@ -471,7 +462,7 @@ Items make_items(const int32_t* seq_lens, int batch, int hkv) {
       it.tok_off.push_back(off);
       it.blk_off.push_back(static_cast<int32_t>(blk));
       off += T;
-      blk += (T + pb - 1) / pb;
+      blk += (T + kPartBlock - 1) / kPartBlock;
     }
   }
   it.n_items = static_cast<int64_t>(batch) * hkv;
@@ -776,62 +767,58 @@ void hull_thresholds(const rdkv_config* cfg, const float* eps, std::vector<int>*
 }
 
 
-// Device tables of one pass over a ragged batch (one entry per item), sent in a single copy.
+// What the kernels of one pass over a ragged batch read about it.  Up to kSeqsAlong sequences travel with the launches, a
+// table of more goes to the device first.
 struct Tables {
-  int64_t* tok_off = nullptr;    // first token of the item in ragged [hkv][T_s] arrays
-  double* budget = nullptr;      // average bits of the token map (channel-wise mode: the V share)
-  double* avg = nullptr;         // average bits per cache element of the item's sequence
-  int32_t* T = nullptr;
-  int32_t* wblk_off = nullptr;   // [items + 1]: first key tile of the item in the weights kernels
-  int32_t* blk_off = nullptr;    // first partition block of the item
-  int64_t n_wblk = 0;
+  Batch batch;
+  int64_t n_tiles = 0;           // key tiles of all items
 };
 
-rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budget, Temp& tmp, hipStream_t st,
-                        Tables* out) {
-  const size_t n = static_cast<size_t>(std::max<int64_t>(it.n_items, 1));
+size_t table_bytes(int32_t n_seqs) { return n_seqs <= kSeqsAlong ? 0 : static_cast<size_t>(n_seqs) * sizeof(SeqEntry); }
+
+rdkv_status make_tables(const rdkv_config* cfg, bool with_budget, Temp& tmp, hipStream_t st, Tables* out) {
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
-  const size_t bytes = 36 * n + 16;
-  uint8_t* d = tmp.get<uint8_t>(bytes);
-  if (!d) return fail(RDKV_ERR_ALLOC, "device allocation failed");
+  Batch& b = out->batch;
+  std::memset(&b, 0, sizeof(b));
+  b.n_seqs = cfg->batch;
+  b.hkv = cfg->hkv;
+  b.inv_hkv = cfg->hkv == 1 ? 0xFFFFFFFFu : static_cast<uint32_t>(((1ull << 32) + cfg->hkv - 1) / static_cast<uint64_t>(cfg->hkv));
   StageRegion region;
   int dev = 0;
-  RDKV_HIP(stage_acquire(bytes, false, st, &region, &dev));
-  uint8_t* blob = region.data;
-  std::memset(blob, 0, bytes);
-  int64_t* tok_off = reinterpret_cast<int64_t*>(blob);
-  double* budget = reinterpret_cast<double*>(blob + 8 * n);
-  double* avg = reinterpret_cast<double*>(blob + 16 * n);
-  int32_t* T = reinterpret_cast<int32_t*>(blob + 24 * n);
-  int32_t* blk = T + n;
-  int32_t* wblk = T + 2 * n;      // n + 1 entries
-  const int key_tile = weights_key_tile();
-  int64_t n_wblk = 0;
-  for (int64_t i = 0; i < it.n_items; ++i) {
-    tok_off[i] = it.tok_off[i];
-    T[i] = it.T[i];
-    blk[i] = it.blk_off[i];
-    wblk[i] = static_cast<int32_t>(n_wblk);
-    n_wblk += (it.T[i] + key_tile - 1) / key_tile;
+  SeqEntry *entries = b.own, *d_table = nullptr;
+  const size_t bytes = table_bytes(cfg->batch);
+  if (bytes > 0) {
+    d_table = tmp.get<SeqEntry>(static_cast<size_t>(cfg->batch));
+    if (!d_table) return fail(RDKV_ERR_ALLOC, "device allocation failed");
+    RDKV_HIP(stage_acquire(bytes, false, st, &region, &dev));
+    entries = reinterpret_cast<SeqEntry*>(region.data);
+  }
+  int64_t row = 0, tile = 0, blk = 0;
+  for (int s = 0; s < cfg->batch; ++s) {
+    SeqEntry e{};
+    e.row0 = row;
+    e.T = cfg->seq_lens[s];
+    e.tile0 = static_cast<int32_t>(tile);
+    e.blk0 = static_cast<int32_t>(blk);
     if (with_budget) {
       // Stage 2.  Token-wise mode: the sequence's average serves K and V alike.  Channel-wise mode: V gets the share
       // 1 - r_K of the head budget, i.e. 2 (1 - r_K) avg_bits per token unit (rounded to fp32 like every budget).
-      const double a = static_cast<double>(cfg->budget_bits[i / cfg->hkv]);
-      avg[i] = a;
-      budget[i] = mixed ? static_cast<double>(static_cast<float>(2.0 * (1.0 - static_cast<double>(cfg->kv_split_rk)) * a)) : a;
+      e.avg = cfg->budget_bits[s];
+      e.budget = mixed ? static_cast<float>(2.0 * (1.0 - static_cast<double>(cfg->kv_split_rk)) * static_cast<double>(e.avg)) : e.avg;
     }
+    entries[s] = e;
+    const int64_t T = e.T;
+    row += cfg->hkv * T;
+    tile += cfg->hkv * ((T + kKeyTile - 1) / kKeyTile);
+    blk += cfg->hkv * ((T + kPartBlock - 1) / kPartBlock);
   }
-  wblk[it.n_items] = static_cast<int32_t>(n_wblk);
-  CopyArgs ca{};
-  ca.add(blob, d, static_cast<int64_t>(bytes), kSrcHost);
-  RDKV_HIP(stage_launch(ca, region, true, st));
-  out->tok_off = reinterpret_cast<int64_t*>(d);
-  out->budget = reinterpret_cast<double*>(d + 8 * n);
-  out->avg = reinterpret_cast<double*>(d + 16 * n);
-  out->T = reinterpret_cast<int32_t*>(d + 24 * n);
-  out->blk_off = out->T + n;
-  out->wblk_off = out->T + 2 * n;
-  out->n_wblk = n_wblk;
+  out->n_tiles = tile;
+  if (bytes > 0) {
+    CopyArgs ca{};
+    ca.add(region.data, d_table, static_cast<int64_t>(bytes), kSrcHost);
+    RDKV_HIP(stage_launch(ca, region, true, st));
+    b.table = d_table;
+  }
   return RDKV_OK;
 }
 
@@ -839,11 +826,11 @@ rdkv_status make_tables(const rdkv_config* cfg, const Items& it, bool with_budge
 rdkv_status weights_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const void* K, const void* Q_obs,
                          float* w_tok, float* w_ch, Temp& tmp, hipStream_t st) {
   const int R = cfg->hq / cfg->hkv * cfg->s_obs;
-  const size_t nscr = weights_scratch_floats(tb.n_wblk, it.n_items, it.total_tokens, R, w_ch != nullptr);
+  const size_t nscr = weights_scratch_floats(tb.n_tiles, it.n_items, it.total_tokens, R, w_ch != nullptr);
   float* scratch = tmp.get<float>(nscr);
   if (!scratch) return fail(RDKV_ERR_ALLOC, "device allocation failed");
   TimedScope ts(RDKV_TIME_WEIGHTS, st);
-  RDKV_HIP(launch_weights(*cfg, tb.tok_off, tb.T, tb.wblk_off, tb.n_wblk, it.n_items, it.total_tokens, it.max_T,
+  RDKV_HIP(launch_weights(*cfg, tb.batch, tb.n_tiles, it.n_items, it.total_tokens, it.max_T,
                           static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(Q_obs), w_tok, w_ch, scratch,
                           st));
   return RDKV_OK;
@@ -884,13 +871,13 @@ rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables&
     RDKV_HIP(upload(d_order, order.data(), order.size() * sizeof(int32_t), st));
   }
   TimedScope ts(RDKV_TIME_ALLOCATE, st);      // every kernel of the stage
-  RDKV_HIP(launch_allocate(w_tok, tb.tok_off, tb.T, tb.budget, n, it.max_T, d_order, n_long, max_short, static_cast<int>(ht.size()), ht.data(), hr.data(),
-                           1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_tok, lam, iters, tb.blk_off,
+  RDKV_HIP(launch_allocate(w_tok, tb.batch, it.max_T, d_order, n_long, max_short, static_cast<int>(ht.size()), ht.data(), hr.data(),
+                           1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_tok, lam, iters,
                            blk_counts, scratch, st));
   if (!mixed) return RDKV_OK;
   // Stage 3, on the device: k_avg = min(16, 2 r_K avg_bits T / n_kept) over the retained tokens just counted
   hull_thresholds(cfg, cfg->eps_k, &ht, &hr);
-  RDKV_HIP(launch_allocate_channels(w_ch, blk_counts, tb.blk_off, tb.T, tb.avg, static_cast<double>(cfg->kv_split_rk), n,
+  RDKV_HIP(launch_allocate_channels(w_ch, tb.batch, blk_counts, static_cast<double>(cfg->kv_split_rk),
                                     static_cast<int>(ht.size()), ht.data(), hr.data(),
                                     1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_ch,
                                     lam ? lam + n : nullptr, iters ? iters + n : nullptr, st));
@@ -937,17 +924,13 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   if (!d_blk_counts || !d_positions || !plan.idx_base || !plan.seg_off || !plan.counts || (mixed && !plan.items_k) ||
       (c->k_per_unit && !d_krange))
     return bail(fail(RDKV_ERR_ALLOC, "device allocation failed"));
-  const int64_t* d_tok_off = tb.tok_off;
-  const int32_t* d_T = tb.T;
-  const int32_t* d_blk_off = tb.blk_off;
-
   if (n > 0) {
     // the one wait of the pass: the tier counts size the arena and the split schedule.  A kernel writes them into pinned
     // memory and the host watches for them (a copy to host memory and a wait for the stream: 25 us more).  It is the launch
     // that makes the position lists and the packing kernels' tables, which need nothing from here.
     if (!counted) {
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
-      PACK_HIP(launch_tier_count(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, static_cast<int>(n), it.max_T, st));
+      PACK_HIP(launch_tier_count(bits_tok, tb.batch, d_blk_counts, it.max_T, st));
     }
     std::vector<int32_t> h_counts(n_counts, 0);
     std::vector<uint8_t> h_bits_ch(mixed ? n * kHeadDim : 0);
@@ -967,7 +950,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       PACK_HIP(stage_round_trip(a, dev, r, st, read, [&](const CopyArgs& ca) {
         if (it.max_T == 0) return launch_copy(ca, st);      // no tokens, no lists
         TimedScope ts(RDKV_TIME_PACK, st);
-        return launch_tier_scatter(bits_tok, d_tok_off, d_T, d_blk_off, d_blk_counts, d_positions, plan, it.max_T, ca, st);
+        return launch_tier_scatter(bits_tok, tb.batch, d_blk_counts, d_positions, plan, it.max_T, ca, st);
       }));
     }
     if (!counted)
@@ -1402,7 +1385,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
         if (kept == 0) return launch_copy(ca, st);
         TimedScope ts(RDKV_TIME_PACK, st);
         return launch_quant_pack(static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), d_positions, c->d_tier_idx, plan,
-                                 d_tok_off, c->d_arena, max_tiles, d_krange, c->group_size == kHeadDim ? 1 : 0, ca, st);
+                                 tb.batch, c->d_arena, max_tiles, d_krange, c->group_size == kHeadDim ? 1 : 0, ca, st);
       }));
       c->slot_begin = slot_begin;
       c->slot_count = slot_count;
@@ -1509,7 +1492,7 @@ rdkv_status rdkv_weights(const rdkv_config* cfg, const void* K, const void* Q_ob
   Temp tmp(al, st);
   Items it = make_items(cfg->seq_lens, cfg->batch, cfg->hkv);
   Tables tb;
-  s = make_tables(cfg, it, false, tmp, st, &tb);
+  s = make_tables(cfg, false, tmp, st, &tb);
   if (s != RDKV_OK) return s;
   return weights_impl(cfg, it, tb, K, Q_obs, w_tok, w_ch, tmp, st);
 }
@@ -1584,7 +1567,7 @@ rdkv_status rdkv_allocate_info(const rdkv_config* cfg, const float* w_tok, const
   Temp tmp(al, st);
   Items it = make_items(cfg->seq_lens, cfg->batch, cfg->hkv);
   Tables tb;
-  s = make_tables(cfg, it, true, tmp, st, &tb);
+  s = make_tables(cfg, true, tmp, st, &tb);
   if (s != RDKV_OK) return s;
   return allocate_impl(cfg, it, tb, w_tok, w_ch, bits_tok, bits_ch, lambda_out, iterations_out, nullptr, tmp, st);
 }
@@ -1611,7 +1594,7 @@ rdkv_status rdkv_pack(const rdkv_config* cfg, const void* K, const void* V, cons
   if (it.n_items > 0 && (s = refuse_capture(st)) != RDKV_OK) return s;
   Temp tmp(al, st);
   Tables tb;
-  s = make_tables(cfg, it, false, tmp, st, &tb);
+  s = make_tables(cfg, false, tmp, st, &tb);
   if (s != RDKV_OK) return s;
   return pack_impl(cfg, it, tb, K, V, bits_tok, bits_ch, nullptr, nullptr, nullptr, nullptr, tmp, st, out);
 }
@@ -1633,11 +1616,11 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   const size_t ni = static_cast<size_t>(std::max<int64_t>(it.n_items, 1));
   const size_t nc = ni * kHeadDim;
   {
-    const int R = cfg->hq / cfg->hkv * cfg->s_obs, key_tile = weights_key_tile();
-    int64_t n_wblk = 0;
-    for (int64_t i = 0; i < it.n_items; ++i) n_wblk += (it.T[i] + key_tile - 1) / key_tile;
-    tmp.reserve({36 * ni + 16, nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
-                 weights_scratch_floats(n_wblk, it.n_items, it.total_tokens, R, mixed) * sizeof(float),
+    const int R = cfg->hq / cfg->hkv * cfg->s_obs;
+    int64_t n_tiles = 0;
+    for (int64_t i = 0; i < it.n_items; ++i) n_tiles += (it.T[i] + kKeyTile - 1) / kKeyTile;
+    tmp.reserve({table_bytes(cfg->batch), nt * sizeof(float), nt, mixed ? nc * sizeof(float) : 0, mixed ? nc : 0,
+                 weights_scratch_floats(n_tiles, it.n_items, it.total_tokens, R, mixed) * sizeof(float),
                  static_cast<size_t>(std::max<int64_t>(it.n_blocks * 4, 1)) * sizeof(int32_t), ni * 4 * sizeof(int64_t), ni * 16 * sizeof(int64_t),
                  ni * 4 * sizeof(int32_t), mixed ? ni * sizeof(ItemK) : 0, ni * 2 * sizeof(double), ni * 2 * sizeof(int32_t),
                  allocate_scratch_bytes(static_cast<int>(it.n_items), it.max_T),
@@ -1645,7 +1628,7 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
                  mixed && cfg->k_scale_per_channel ? nc * 2 * sizeof(uint32_t) : 0});
   }
   Tables tb;
-  s = make_tables(cfg, it, true, tmp, st, &tb);
+  s = make_tables(cfg, true, tmp, st, &tb);
   if (s != RDKV_OK) return s;
   float* w = tmp.get<float>(nt);
   uint8_t* bits = tmp.get<uint8_t>(nt);

@@ -17,6 +17,8 @@ constexpr int kGroup = 32;             // quantization group (channels)
 constexpr int kGroupsPerRow = kHeadDim / kGroup;
 constexpr int kTile64 = 64;            // tier segments are padded to whole 64-row tiles
 constexpr int kKTokenGroup = 32;       // mixed mode: a K channel's group = 32 consecutive retained tokens of a segment
+constexpr int kPartBlock = 1024;       // tokens per block of the tier counts
+constexpr int kKeyTile = 64;           // keys per tile of the weights kernels
 constexpr int kSegAlign = 256;         // byte alignment of arena segments
 constexpr int kNumPackTiers = 4;       // stored tiers, order 16, 8, 4, 2
 constexpr int kDenseMaxSeqs = 64;      // sequences per dense-decode launch (kernel-argument table)
@@ -60,6 +62,57 @@ struct ItemK {
   int16_t n_slots, n_words, n_words_padded;
   int16_t n_steps16, n_qsteps;   // steps of the 16-bit tier; steps of the quantized tiers
   int16_t slot_ch[kMaxSlots];    // channel held by a slot, -1 for padding
+};
+
+// What the kernels of a compression pass need to know about a batch, an entry per sequence.  Up to kSeqsAlong of them come
+// with every launch, in its arguments: no launch has to bring a table to the device first, and a kernel's first loads wait for
+// the entries alone.  More of them are a table in device memory.  (1 KB of arguments costs the host 0.1 us a launch, a launch that
+// copies a table 2.4 and the device 3.3: staged calls on 50K keys 196.5 -> 189.5 us, compressing 4K keys 54.4 -> 52.6.)
+struct SeqEntry {
+  int64_t row0;                  // first token of the sequence in ragged [hkv][T] arrays
+  int32_t T, tile0, blk0;        // tokens; first key tile and first block of the bit map of the sequence's items
+  float avg, budget;             // average bits per cache element, and of the token map (channel-wise mode: the V share)
+  int32_t pad_;
+};
+constexpr int kSeqsAlong = 32;
+struct Batch {
+  const SeqEntry* table;         // device memory, or null: own
+  int32_t n_seqs, hkv;
+  uint32_t inv_hkv;              // 2^32 / hkv, rounded up (2^32 - 1 for one head)
+  SeqEntry own[kSeqsAlong];
+  // (constant address space, as the arguments' is: one scalar load whichever of the two it comes from)
+  typedef const __attribute__((address_space(4))) SeqEntry* ConstEntries;
+  __device__ __forceinline__ SeqEntry seq(int s) const {
+    if (!table) return own[s];
+    const ConstEntries t = (ConstEntries)(table) + s;
+    return SeqEntry{t->row0, t->T, t->tile0, t->blk0, t->avg, t->budget, 0};
+  }
+  __device__ __forceinline__ int tile0(int s) const { return table ? table[s].tile0 : own[s].tile0; }
+};
+// one item = (sequence, KV head)
+struct ItemOf {
+  int seq, head, T, tile0, blk0;
+  int64_t off;                   // first token
+  double avg, budget;
+  __device__ __forceinline__ ItemOf(const Batch& b, int item) {
+    seq = static_cast<int>(__umulhi(static_cast<uint32_t>(item), b.inv_hkv));      // off by one at most
+    head = item - seq * b.hkv;
+    if (head < 0) {
+      --seq;
+      head += b.hkv;
+    } else if (head >= b.hkv) {
+      ++seq;
+      head -= b.hkv;
+    }
+    const SeqEntry e = b.seq(seq);
+    T = e.T;
+    off = e.row0 + static_cast<int64_t>(head) * e.T;
+    tile0 = e.tile0 + head * tiles();
+    blk0 = e.blk0 + head * ((e.T + kPartBlock - 1) / kPartBlock);
+    avg = static_cast<double>(e.avg);
+    budget = static_cast<double>(e.budget);
+  }
+  __device__ __forceinline__ int tiles() const { return (T + kKeyTile - 1) / kKeyTile; }
 };
 
 // Slots of a tier of a K row with n channels (ItemK): whole word pairs of 16-bit slots, whole words of the others.

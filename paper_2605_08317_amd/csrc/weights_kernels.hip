@@ -32,8 +32,7 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
-constexpr int kKeyTile = 64;                // keys per LDS buffer
-constexpr int kKeyTileBytes = kKeyTile * kHeadDim * 2;
+constexpr int kKeyTileBytes = kKeyTile * kHeadDim * 2;   // an LDS buffer
 constexpr int kBuffers = 3;                 // two tiles in flight while one is computed
 constexpr int kSumTiles = 16;               // tiles whose column sums pass 2 keeps in LDS
 constexpr int kPass1PerCu = 2, kPass2PerCu = 2;   // workgroups a compute unit keeps resident (registers)
@@ -43,9 +42,6 @@ constexpr float kLogitScale = 1.4426950408889634f * 0.08838834764831845f;   // l
 struct WeightArgs {
   const uint16_t* K;
   const uint16_t* Q;             // [batch][hq][s_obs][d]
-  const int64_t* item_row_off;   // [items]
-  const int32_t* item_T;         // [items]
-  const int32_t* item_tile_off;  // [items + 1] first key tile of the item
   float* row_part;               // [workgroups + items][row_slots][2]  (m, l) in the log2 domain
   float* lse;                    // [items][row_slots]
   float* w_raw;                  // [total tokens] unpooled weights
@@ -53,6 +49,7 @@ struct WeightArgs {
   int32_t hq, hkv, g, s_obs, R, row_slots, causal;   // row_slots: R in whole sweeps of row groups
   int32_t n_items, n_tiles;      // items, key tiles of all of them
   int32_t workgroups;            // pass 1
+  Batch batch;
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -87,7 +84,8 @@ __device__ __forceinline__ int owner_of(int tile, int workgroups, int n_tiles) {
 }
 // slots of an item: [*first, *first + return value)
 __device__ __forceinline__ int item_slots(const WeightArgs& a, int item, int* first) {
-  const int t0 = a.item_tile_off[item], t1 = a.item_tile_off[item + 1];
+  const ItemOf it(a.batch, item);
+  const int t0 = it.tile0, t1 = t0 + it.tiles();
   *first = 0;
   if (t1 <= t0) return 0;
   const int w0 = owner_of(t0, a.workgroups, a.n_tiles), w1 = owner_of(t1 - 1, a.workgroups, a.n_tiles);
@@ -124,20 +122,28 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
   const int prow = tid >> 4, piece = (tid & 15) ^ (prow & 15);   // this thread's key rows prow + 16 k and piece of the key
 
   const int run0 = first_tile(blockIdx.x, gridDim.x, a.n_tiles), run1 = first_tile(blockIdx.x + 1, gridDim.x, a.n_tiles);
-  int item = 0;                            // the item of tile run0: the last one that starts at or before it
-  for (int hi = a.n_items; hi - item > 1;) {
-    const int mid = (item + hi) >> 1;
-    if (uniform(a.item_tile_off[mid]) <= run0) item = mid; else hi = mid;
+  int seq = 0;                             // the sequence of tile run0: the last one that starts at or before it
+  for (int s0 = 0; s0 < a.batch.n_seqs && a.batch.n_seqs > 1; s0 += 64) {
+    const int s = s0 + lane;
+    const uint64_t before = __ballot(s < a.batch.n_seqs && a.batch.tile0(min(s, a.batch.n_seqs - 1)) <= run0);
+    if (before == 0) break;
+    seq = s0 + 63 - __clzll(static_cast<long long>(before));
   }
-  for (int tile0 = run0; tile0 < run1; ++item) {
-  const int item0 = uniform(a.item_tile_off[item]);
-  const int ntile = min(run1, uniform(a.item_tile_off[item + 1])) - tile0;   // this run's tiles of the item
+  int head = -1;                           // (not known yet)
+  for (int tile0 = run0; tile0 < run1; ++head) {
+  if (head == a.hkv) {
+    head = 0;
+    ++seq;
+  }
+  const SeqEntry entry = a.batch.seq(seq);
+  const int T = uniform(entry.T), tiles = (T + kKeyTile - 1) / kKeyTile;
+  if (head < 0) head = (tile0 - uniform(entry.tile0)) / tiles;      // (the sequence has the tile, so it has keys)
+  const int item = seq * a.hkv + head, item0 = uniform(entry.tile0) + head * tiles;
+  const int ntile = min(run1, item0 + tiles) - tile0;   // this run's tiles of the item
   if (ntile <= 0) continue;                // an item without keys
-  const int T = uniform(a.item_T[item]);
-  const int64_t row_off = uniform64(a.item_row_off[item]);
+  const int64_t row_off = uniform64(entry.row0) + static_cast<int64_t>(head) * T;
   const int key0 = (tile0 - item0) * kKeyTile, key1 = min(T, key0 + ntile * kKeyTile);
   tile0 += ntile;
-  const int seq = item / a.hkv, head = item % a.hkv;
   const int per_s_obs = 65536 / a.s_obs + 1;
   const uint16_t* Qg = a.Q + (static_cast<int64_t>(seq) * a.hq + head * a.g) * a.s_obs * kHeadDim;
   const uint16_t* Kh = a.K + row_off * kHeadDim;
@@ -522,16 +528,15 @@ __global__ __launch_bounds__(256) void row_lse_kernel(WeightArgs a) {
 // once: with a thread per key and its neighbours read from memory 2.9M keys took 13.7 us.
 template <int PER>
 __global__ __launch_bounds__(256) void pool_kernel(const float* __restrict__ w_raw, float* __restrict__ w_out,
-                                                   const int64_t* __restrict__ item_row_off,
-                                                   const int32_t* __restrict__ item_T, int kernel) {
+                                                   int kernel, Batch batch) {
   constexpr int kRows = 256 * PER, kMostRadius = 7;
   __shared__ float s_w[kRows + 2 * kMostRadius];
-  const int item = blockIdx.y;
-  const int T = item_T[item];
+  const ItemOf it(batch, blockIdx.y);
+  const int T = it.T;
   const int t0 = blockIdx.x * kRows, tid = threadIdx.x;
   if (t0 >= T) return;
-  const float* w = w_raw + item_row_off[item];
-  float* out = w_out + item_row_off[item];
+  const float* w = w_raw + it.off;
+  float* out = w_out + it.off;
   const int r = kernel / 2, first = t0 - r;
   float v[PER + 1];
 #pragma unroll
@@ -606,8 +611,6 @@ void launch_passes(const WeightArgs& a, bool want_ch, hipStream_t st) {
 
 }  // namespace
 
-int weights_key_tile() { return kKeyTile; }
-
 // scratch layout (floats): row_part | lse | w_raw | ksq_part
 size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_tokens, int R, bool want_ch) {
   const size_t slots = static_cast<size_t>(workgroups_of(n_tiles, kPass1PerCu)) + n_items;
@@ -615,13 +618,12 @@ size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_to
          (want_ch ? slots * kHeadDim : 0) + 64;
 }
 
-hipError_t launch_weights(const rdkv_config& cfg, const int64_t* d_item_row_off, const int32_t* d_item_T,
-                          const int32_t* d_item_tile_off, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
+hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
                           int max_T, const uint16_t* K, const uint16_t* Q_obs, float* w_tok, float* w_ch,
                           float* scratch, hipStream_t st) {
   if (n_items == 0 || max_T == 0) return hipSuccess;
   WeightArgs a;
-  a.K = K; a.Q = Q_obs; a.item_row_off = d_item_row_off; a.item_T = d_item_T; a.item_tile_off = d_item_tile_off;
+  a.K = K; a.Q = Q_obs; a.batch = batch;
   a.hq = cfg.hq; a.hkv = cfg.hkv; a.g = cfg.hq / cfg.hkv; a.s_obs = cfg.s_obs;
   a.R = a.g * cfg.s_obs; a.row_slots = row_slots_of(a.R); a.causal = cfg.causal ? 1 : 0;
   a.n_items = static_cast<int32_t>(n_items); a.n_tiles = static_cast<int32_t>(n_tiles);
@@ -640,8 +642,8 @@ hipError_t launch_weights(const rdkv_config& cfg, const int64_t* d_item_row_off,
     const bool wide = n_items * ((max_T + 1023) / 1024) >= 1024;
     const unsigned per_wg = wide ? 1024 : 256;
     const dim3 grid((static_cast<unsigned>(max_T) + per_wg - 1) / per_wg, static_cast<unsigned>(n_items));
-    if (wide) hipLaunchKernelGGL(pool_kernel<4>, grid, dim3(256), 0, st, a.w_raw, w_tok, d_item_row_off, d_item_T, cfg.pool_kernel);
-    else hipLaunchKernelGGL(pool_kernel<1>, grid, dim3(256), 0, st, a.w_raw, w_tok, d_item_row_off, d_item_T, cfg.pool_kernel);
+    if (wide) hipLaunchKernelGGL(pool_kernel<4>, grid, dim3(256), 0, st, a.w_raw, w_tok, cfg.pool_kernel, batch);
+    else hipLaunchKernelGGL(pool_kernel<1>, grid, dim3(256), 0, st, a.w_raw, w_tok, cfg.pool_kernel, batch);
   } else {
     hipError_t e = hipMemcpyAsync(w_tok, a.w_raw, total_tokens * sizeof(float), hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return e;

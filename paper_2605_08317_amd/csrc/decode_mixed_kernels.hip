@@ -128,9 +128,9 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
     dst[1] = *reinterpret_cast<const uint4*>(p + 1024);
   };
   auto load_v = [&](int t) __attribute__((always_inline)) {
+    if constexpr (VT != 16) vmeta = *reinterpret_cast<const uint4*>(vm + static_cast<int64_t>(t) * 1024 + lane * 16);   // (used first)
     if constexpr (kStream) load_v_piece(t, 0, vraw[0]);
     else load_tile_side<VT>(vraw[0], vd, t, lane);
-    if constexpr (VT != 16) vmeta = *reinterpret_cast<const uint4*>(vm + static_cast<int64_t>(t) * 1024 + lane * 16);
   };
 #pragma unroll
   for (int w = 0; w < NW; ++w) kw[w] = 0;
@@ -421,7 +421,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
 
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
-    softmax_tile<HS>(x, run, p, lk);
+    softmax_tile<HS, VT != 16>(x, run, p, lk, VT != 16 && wide_scales(vmeta));
 
     // ---- P V ------------------------------------------------------------------------------------------------
     if constexpr (VT == 16) {
@@ -470,7 +470,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
     }
   }
 
-  return finish_chunk<HS, true, NWV, LOOK>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
+  return finish_chunk<HS, true, NWV, LOOK, VT != 16>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
                                  reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
 }
 

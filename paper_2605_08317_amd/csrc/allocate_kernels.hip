@@ -41,6 +41,9 @@ static_assert(kBlockUnits == kThreads, "a quarter of a round of allocate_item_ke
 
 struct AllocArgs {
   const float* w;
+  const float* raw;            // the weights before the pooling, which the search's first launch then does; or null
+  int32_t pool;                // keys of a pooling window (odd, at most 15)
+  float pool_inv;              // 1 / pool
   uint8_t* bits;
   double r[kMaxHull];          // r[k-1]: threshold ratio into hull tier k
   int32_t tiers[kMaxHull];
@@ -443,6 +446,34 @@ __device__ __forceinline__ int4 tier_counts(const Problem& P, int n, const int4&
 struct __attribute__((packed, aligned(4))) Units4 { float v[4]; };
 struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 
+// AvgPool1d(pool, stride 1, zero padding pool / 2, divisor pool) of raw weights in LDS (pool_kernel in the weights' file is the
+// launch of its own), added in the same order and divided to the same bits: the correctly rounded quotient from the correctly
+// rounded reciprocal and one exact remainder (Markstein, IBM J. Res. Dev. 34, 1990), by division where the remainder could
+// underflow or is none.
+constexpr int kMostRadius = 7;
+__device__ __forceinline__ float pool_quotient(const AllocArgs& a, float s) {
+  const float n = static_cast<float>(a.pool), q0 = s * a.pool_inv;
+  float q = __builtin_fmaf(__builtin_fmaf(-q0, n, s), a.pool_inv, q0);
+  if (!(s > 1e-25f && s < 1e30f)) q = s == 0.f ? 0.f : s / n;
+  return q;
+}
+// four units whose window starts at w[0], 16-byte aligned
+__device__ __forceinline__ void pool_four(const AllocArgs& a, const float* w, float (&v)[4]) {
+  if (a.pool == 5) {                       // (uniform)
+    const float4 x = *reinterpret_cast<const float4*>(w), y = *reinterpret_cast<const float4*>(w + 4);
+    const float t[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = pool_quotient(a, (((t[e] + t[e + 1]) + t[e + 2]) + t[e + 3]) + t[e + 4]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float s = 0.f;
+      for (int k = 0; k < a.pool; ++k) s += w[e + k];
+      v[e] = pool_quotient(a, s);
+    }
+  }
+}
+
 // ---- one workgroup per item: up to 1024 REG units in registers ------------------------------------------------------
 // Thread t holds units 4096 j + 4 t .. + 3, so four wavefronts make one block of the per-block counts.  What bounds it:
 // one compute unit works on an item, through the latency of its loads and about fifteen barriers and then the number of
@@ -468,9 +499,10 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   const ItemOf it(a.batch, item);
   const int U = it.T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float* __restrict__ w = a.w + it.off;
+  const float* w = a.w + it.off;
   uint8_t* __restrict__ bits = a.bits + it.off;
   float v[REG];                            // units past the end read as 0: never above a threshold
+  if (a.raw) w = a.raw + it.off;
 #pragma unroll
   for (int j = 0; j < kQ; ++j) {
     const int u0 = 4 * (j * kThreads + tid);
@@ -482,6 +514,32 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[4 * j + e] = u0 + e < U ? w[u0 + e] : 0.f;
     }
+  }
+  if (a.raw) {
+    // through LDS, which nothing else uses yet: unit u at s_raw[u + radius], zeros around them
+    static_assert(kItemLds<REG> >= (REG * kThreads + 2 * kMostRadius) * sizeof(float), "an item and its window's ends");
+    float* s_raw = reinterpret_cast<float*>(smem);
+    const int radius = a.pool / 2;
+    if (tid < radius) s_raw[tid] = 0.f;
+    if (tid < radius) s_raw[radius + min(REG * kThreads, (U + 3) / 4 * 4) + tid] = 0.f;
+#pragma unroll
+    for (int j = 0; j < kQ; ++j) {
+      const int u0 = 4 * (j * kThreads + tid);
+      if (u0 < U) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s_raw[radius + u0 + e] = v[4 * j + e];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kQ; ++j) {
+      const int u0 = 4 * (j * kThreads + tid);
+      float x[4] = {0.f, 0.f, 0.f, 0.f};
+      if (u0 < U) pool_four(a, s_raw + u0, x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * j + e] = u0 + e < U ? x[e] : 0.f;
+    }
+    __syncthreads();
   }
   for (int i = tid; i < Anchored::kWords / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
   const Problem P(a, U, it.budget);
@@ -693,6 +751,8 @@ struct Quads {
 };
 
 constexpr int kMostSlices = 16;              // workgroups that share an item
+constexpr int kMostMaxima = 2 * kMostSlices; // workgroups that share its first pass
+static_assert(kMostMaxima <= 64, "a lane each");
 constexpr int kListCap = 24576;             // undecided units of an item (96 KB of LDS in the exact steps)
 struct SearchState {
   Search s;
@@ -708,8 +768,8 @@ struct MultiArgs {
   int32_t* hist;        // [rows][kBuckets], zero on entry
   SearchState* state;   // [rows], zero on entry
   float* list;          // [rows][kListCap]
-  float* slice_max;     // [rows][slices]
-  int32_t slices;
+  float* slice_max;     // [rows][maxima]
+  int32_t slices, maxima;
 };
 
 // Called by all threads of a workgroup after their stores and atomics of a pass: true in the workgroup that is the last
@@ -729,28 +789,69 @@ __device__ __forceinline__ T load_agent(const T* p) {
 
 // The largest unit of every slice, which anchors the histograms (over the full range of fp32 they had 32768 buckets at a
 // quarter of the resolution: hist_kernel 21 us, gather_kernel 20 at 8 x 128K units), and zeros for the next kernels.
-__global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, uint4* clear, int64_t n_clear) {
+// POOL: raw weights are pooled on the way and written for the next kernels (8 x 128K units: TODO).
+template <bool POOL>
+__global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, float* pooled, uint4* clear, int64_t n_clear) {
+  constexpr int kRound = 4 * kThreads;
+  __shared__ __align__(16) float s_raw[POOL ? kRound + 2 * kMostRadius + 2 : 4];
   __shared__ float s_max[kWaves];
   const int row = blockIdx.y, tid = threadIdx.x;
   const ItemOf it(m.a.batch, m.a.item_of(row));
-  const Quads quads(m.a.w + it.off, it.T);
-  int q0, q1;
-  quads.slice(m.slices, &q0, &q1);
   const int64_t step = static_cast<int64_t>(gridDim.x) * gridDim.y * kThreads;
   for (int64_t i = (static_cast<int64_t>(row) * gridDim.x + blockIdx.x) * kThreads + tid; i < n_clear; i += step)
     clear[i] = make_uint4(0, 0, 0, 0);
+  // whole rounds per workgroup, so that a slice starts at a multiple of four
+  const int rounds = (it.T + kRound - 1) / kRound, per = (rounds + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
+  const int u_first = min(it.T, static_cast<int>(blockIdx.x) * per * kRound), u_last = min(it.T, u_first + per * kRound);
   float mx = 0.f;
-  for (int q = q0 + tid; q < q1; q += kThreads) {
-    float v[4];
-    quads.load(q, v);
-    mx = fmaxf(mx, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+  if constexpr (POOL) {
+    const float* raw = m.a.raw + it.off;
+    float* out = pooled + it.off;
+    const int radius = m.a.pool / 2;
+    for (int u0 = u_first; u0 < u_last; u0 += kRound) {
+      float v[5];
+#pragma unroll
+      for (int j = 0; j < 5; ++j) {
+        const int u = u0 - radius + j * kThreads + tid;
+        v[j] = (j < 4 || tid < 2 * radius) && u >= 0 && u < it.T ? raw[u] : 0.f;
+      }
+      __syncthreads();                     // the round before is used up
+#pragma unroll
+      for (int j = 0; j < 5; ++j)
+        if (j < 4 || tid < 2 * radius) s_raw[j * kThreads + tid] = v[j];
+      __syncthreads();
+      float x[4];
+      pool_four(m.a, s_raw + 4 * tid, x);
+      const int u = u0 + 4 * tid;
+      if (u + 3 < u_last) {
+        *reinterpret_cast<Units4*>(out + u) = Units4{{x[0], x[1], x[2], x[3]}};
+        mx = fmaxf(mx, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (u + e < u_last) {
+            out[u + e] = x[e];
+            mx = fmaxf(mx, x[e]);
+          }
+      }
+    }
+  } else {
+    const float* w = m.a.w + it.off;
+    for (int u = u_first + 4 * tid; u < u_last; u += kRound) {
+      if (u + 3 < u_last) {
+        const Units4 x = *reinterpret_cast<const Units4*>(w + u);
+        mx = fmaxf(mx, fmaxf(fmaxf(x.v[0], x.v[1]), fmaxf(x.v[2], x.v[3])));
+      } else {
+        for (int e = 0; u + e < u_last; ++e) mx = fmaxf(mx, w[u + e]);
+      }
+    }
   }
   mx = wave_max(mx);
   if ((tid & 63) == 0) s_max[tid >> 6] = mx;
   __syncthreads();
   if (tid < 64) {
     mx = wave_max(tid < kWaves ? s_max[tid] : 0.f);
-    if (tid == 0) m.slice_max[row * m.slices + blockIdx.x] = mx;
+    if (tid == 0) m.slice_max[row * m.maxima + blockIdx.x] = mx;
   }
 }
 
@@ -771,7 +872,7 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   const Quads quads(a.w + it.off, U);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
-  float mx = lane < m.slices ? m.slice_max[row * m.slices + lane] : 0.f;       // (at most 16 slices)
+  float mx = lane < m.maxima ? m.slice_max[row * m.maxima + lane] : 0.f;
   float wv[4] = {0.f, 0.f, 0.f, 0.f};
   if (q0 + tid < q1) quads.load(q0 + tid, wv);
   const Problem P(a, U, it.budget);
@@ -1091,9 +1192,12 @@ hipError_t launch_items_together(const AllocArgs& a, int n_items, int max_U, voi
   m.list = reinterpret_cast<float*>(p + hist_bytes(n_items) + state_bytes(n_items));
   m.slice_max = m.list + static_cast<size_t>(n_items) * kListCap;
   m.slices = std::max(1, std::min(kMostSlices, 256 / n_items));
+  m.maxima = std::max(1, std::min(kMostMaxima, 512 / n_items));
   const int64_t clear = static_cast<int64_t>((hist_bytes(n_items) + state_bytes(n_items)) / 16);
   const dim3 wide(m.slices, n_items), block(kThreads);
-  hipLaunchKernelGGL(slice_max_kernel, wide, block, 0, st, m, reinterpret_cast<uint4*>(p), clear);
+  const dim3 first(m.maxima, n_items);
+  if (a.raw) hipLaunchKernelGGL(slice_max_kernel<true>, first, block, 0, st, m, const_cast<float*>(a.w), reinterpret_cast<uint4*>(p), clear);
+  else hipLaunchKernelGGL(slice_max_kernel<false>, first, block, 0, st, m, nullptr, reinterpret_cast<uint4*>(p), clear);
   hipError_t e = RDKV_ALLOW_LDS(hist_kernel, kHistLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(hist_kernel, wide, block, kHistLds, st, m);
@@ -1116,12 +1220,13 @@ int allocate_short_units() { return kItemUnits; }
 size_t allocate_scratch_bytes(int n_items, int max_U) {
   if (max_U <= kItemUnits) return 0;
   const int n = std::min(n_items, kMostTogether);
-  return hist_bytes(n) + state_bytes(n) + static_cast<size_t>(n) * (kListCap + kMostSlices) * sizeof(float);
+  return hist_bytes(n) + state_bytes(n) + static_cast<size_t>(n) * (kListCap + kMostMaxima) * sizeof(float);
 }
 
 // Token maps of all items.  d_order (where allocate_needs_order): the items, the n_long of more than allocate_short_units()
 // first, the others with up to max_short units.  blk_counts: what the packing stage needs, or null.
-hipError_t launch_allocate(const float* w, const Batch& batch, int max_U, const int32_t* d_order, int n_long,
+// raw: the weights before the pooling (window pool > 1), which the search then does itself; w is memory for the pooled ones.
+hipError_t launch_allocate(const float* raw, int pool, float* w, const Batch& batch, int max_U, const int32_t* d_order, int n_long,
                            int max_short, int n_hull, const int* hull_tiers,
                            const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
                            int32_t* iters_out, int32_t* blk_counts, void* scratch, hipStream_t st) {
@@ -1130,6 +1235,11 @@ hipError_t launch_allocate(const float* w, const Batch& batch, int max_U, const 
   if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
   AllocArgs a = make_args(w, batch, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits, lam_out, iters_out);
   a.blk_counts = reinterpret_cast<int4*>(blk_counts);
+  if (pool > 1) {
+    a.raw = raw;
+    a.pool = pool;
+    a.pool_inv = 1.0f / static_cast<float>(pool);
+  }
   if (max_U <= kItemUnits) return launch_short_items(a, n_items, max_U, st);
   if (!scratch || (!d_order && n_items > kMostTogether)) return hipErrorInvalidValue;
   if (!d_order) return launch_items_together(a, n_items, max_U, scratch, st);

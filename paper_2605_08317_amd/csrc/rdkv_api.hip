@@ -26,11 +26,11 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
 size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_tokens, int R, bool want_ch);
 hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
                           int max_T, const uint16_t* K, const uint16_t* Q_obs, float* w_tok, float* w_ch,
-                          float* scratch, hipStream_t st);
+                          float* scratch, const float** raw, hipStream_t st);
 size_t allocate_scratch_bytes(int n_items, int max_U);
 bool allocate_needs_order(int n_items, int max_U);
 int allocate_short_units();
-hipError_t launch_allocate(const float* w, const Batch& batch, int max_U, const int32_t* d_order, int n_long,
+hipError_t launch_allocate(const float* raw, int pool, float* w, const Batch& batch, int max_U, const int32_t* d_order, int n_long,
                            int max_short, int n_hull, const int* hull_tiers,
                            const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
                            int32_t* iters_out, int32_t* blk_counts, void* scratch, hipStream_t st);
@@ -822,9 +822,9 @@ rdkv_status make_tables(const rdkv_config* cfg, bool with_budget, Temp& tmp, hip
   return RDKV_OK;
 }
 
-// Stage 1 of Alg. 1; everything is enqueued on st, nothing waits.
+// Stage 1 of Alg. 1; everything is enqueued on st, nothing waits.  raw: see launch_weights.
 rdkv_status weights_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const void* K, const void* Q_obs,
-                         float* w_tok, float* w_ch, Temp& tmp, hipStream_t st) {
+                         float* w_tok, float* w_ch, const float** raw, Temp& tmp, hipStream_t st) {
   const int R = cfg->hq / cfg->hkv * cfg->s_obs;
   const size_t nscr = weights_scratch_floats(tb.n_tiles, it.n_items, it.total_tokens, R, w_ch != nullptr);
   float* scratch = tmp.get<float>(nscr);
@@ -832,14 +832,14 @@ rdkv_status weights_impl(const rdkv_config* cfg, const Items& it, const Tables& 
   TimedScope ts(RDKV_TIME_WEIGHTS, st);
   RDKV_HIP(launch_weights(*cfg, tb.batch, tb.n_tiles, it.n_items, it.total_tokens, it.max_T,
                           static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(Q_obs), w_tok, w_ch, scratch,
-                          st));
+                          raw, st));
   return RDKV_OK;
 }
 
-// Stages 2-3 of Alg. 1; everything is enqueued on st, nothing waits.  lam / iters: device [items] (token map), in
+// Stages 2-3 of Alg. 1; everything is enqueued on st, nothing waits.  raw: weights that are still to be pooled into w_tok, or null.  lam / iters: device [items] (token map), in
 // channel-wise mode followed by [items] for the channel map; or null.  blk_counts: device [blocks][4] for the packing
 // stage (kept tokens of every block of an item per tier), or null.
-rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const float* w_tok,
+rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const float* raw, float* w_tok,
                           const float* w_ch, uint8_t* bits_tok, uint8_t* bits_ch, double* lam, int32_t* iters,
                           int32_t* blk_counts, Temp& tmp, hipStream_t st) {
   const bool mixed = cfg->k_mode == RDKV_K_CHANNELWISE;
@@ -871,7 +871,7 @@ rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables&
     RDKV_HIP(upload(d_order, order.data(), order.size() * sizeof(int32_t), st));
   }
   TimedScope ts(RDKV_TIME_ALLOCATE, st);      // every kernel of the stage
-  RDKV_HIP(launch_allocate(w_tok, tb.batch, it.max_T, d_order, n_long, max_short, static_cast<int>(ht.size()), ht.data(), hr.data(),
+  RDKV_HIP(launch_allocate(raw, raw ? cfg->pool_kernel : 1, w_tok, tb.batch, it.max_T, d_order, n_long, max_short, static_cast<int>(ht.size()), ht.data(), hr.data(),
                            1.0 - static_cast<double>(cfg->rel_tol), cfg->max_iters, bits_tok, lam, iters,
                            blk_counts, scratch, st));
   if (!mixed) return RDKV_OK;
@@ -1494,7 +1494,7 @@ rdkv_status rdkv_weights(const rdkv_config* cfg, const void* K, const void* Q_ob
   Tables tb;
   s = make_tables(cfg, false, tmp, st, &tb);
   if (s != RDKV_OK) return s;
-  return weights_impl(cfg, it, tb, K, Q_obs, w_tok, w_ch, tmp, st);
+  return weights_impl(cfg, it, tb, K, Q_obs, w_tok, w_ch, nullptr, tmp, st);
 }
 
 rdkv_status rdkv_calibrate_eps(const rdkv_config* cfg, const void* K, const void* V, double* eps_k, double* eps_v,
@@ -1569,7 +1569,7 @@ rdkv_status rdkv_allocate_info(const rdkv_config* cfg, const float* w_tok, const
   Tables tb;
   s = make_tables(cfg, true, tmp, st, &tb);
   if (s != RDKV_OK) return s;
-  return allocate_impl(cfg, it, tb, w_tok, w_ch, bits_tok, bits_ch, lambda_out, iterations_out, nullptr, tmp, st);
+  return allocate_impl(cfg, it, tb, nullptr, const_cast<float*>(w_tok), w_ch, bits_tok, bits_ch, lambda_out, iterations_out, nullptr, tmp, st);
 }
 
 rdkv_status rdkv_allocate(const rdkv_config* cfg, const float* w_tok, const float* w_ch, uint8_t* bits_tok,
@@ -1642,11 +1642,12 @@ rdkv_status rdkv_compress(const rdkv_config* cfg, const void* K, const void* V, 
   double* lam = tmp.get<double>(maps * ni);
   int32_t* iters = tmp.get<int32_t>(maps * ni);
   if (!lam || !iters) return fail(RDKV_ERR_ALLOC, "device allocation failed");
-  s = weights_impl(cfg, it, tb, K, Q_obs, w, w_ch, tmp, st);
+  const float* raw = nullptr;
+  s = weights_impl(cfg, it, tb, K, Q_obs, w, w_ch, &raw, tmp, st);
   if (s != RDKV_OK) return s;
   int32_t* blk_counts = tmp.get<int32_t>(static_cast<size_t>(std::max<int64_t>(it.n_blocks, 1)) * 4);
   if (!blk_counts) return fail(RDKV_ERR_ALLOC, "device allocation failed");
-  s = allocate_impl(cfg, it, tb, w, w_ch, bits, bits_ch, lam, iters, blk_counts, tmp, st);
+  s = allocate_impl(cfg, it, tb, cfg->pool_kernel > 1 ? raw : nullptr, cfg->pool_kernel > 1 ? w : const_cast<float*>(raw), w_ch, bits, bits_ch, lam, iters, blk_counts, tmp, st);
   if (s != RDKV_OK) return s;
   // (the weights are used up: their memory takes the kept positions)
   return pack_impl(cfg, it, tb, K, V, bits, bits_ch, blk_counts, reinterpret_cast<int32_t*>(w), lam, iters, tmp, st, out);

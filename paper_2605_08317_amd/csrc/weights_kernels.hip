@@ -618,9 +618,10 @@ size_t weights_scratch_floats(int64_t n_tiles, int64_t n_items, int64_t total_to
          (want_ch ? slots * kHeadDim : 0) + 64;
 }
 
+// raw: where the weights before the pooling are (scratch), for a caller that pools them; w_tok is left alone then.
 hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_tiles, int64_t n_items, int64_t total_tokens,
                           int max_T, const uint16_t* K, const uint16_t* Q_obs, float* w_tok, float* w_ch,
-                          float* scratch, hipStream_t st) {
+                          float* scratch, const float** raw, hipStream_t st) {
   if (n_items == 0 || max_T == 0) return hipSuccess;
   WeightArgs a;
   a.K = K; a.Q = Q_obs; a.batch = batch;
@@ -636,8 +637,9 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   if (a.R <= 64) launch_passes<1, 2>(a, w_ch != nullptr, st);
   else if (a.R <= 128) launch_passes<2, 2>(a, w_ch != nullptr, st);
   else launch_passes<2, 4>(a, w_ch != nullptr, st);
-  const bool pooled = cfg.pool_kernel > 1;
-  if (pooled) {
+  if (raw) {
+    *raw = a.w_raw;
+  } else if (cfg.pool_kernel > 1) {
     // enough workgroups for the chip first, then several keys per thread
     const bool wide = n_items * ((max_T + 1023) / 1024) >= 1024;
     const unsigned per_wg = wide ? 1024 : 256;

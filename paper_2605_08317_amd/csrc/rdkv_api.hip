@@ -634,22 +634,24 @@ void drop_workspaces(rdkv_cache* c) {
 // (measured 4-5 % faster on a mixed-tier batch than plain size order).  Launches that fit the chip in one round:
 // round-robin over the items, so that with the usual round-robin placement of workgroups on the eight XCDs the
 // chunks of an item share an L2 (which then also holds the partials their merge reads); only speed depends on it.
-void order_chunks(std::vector<Chunk>::iterator first, std::vector<Chunk>::iterator last, int64_t n_items) {
+template <class T>      // Chunk or Piece
+void order_chunks(typename std::vector<T>::iterator first, typename std::vector<T>::iterator last, int64_t n_items) {
   const int64_t count = last - first;
   if (count < 2) return;
   // (tier, size) in one key and the position behind it: a stable order without moving chunks about
   using Key = std::pair<uint64_t, int32_t>;
   auto key_of = [&](int64_t k) {
-    const Chunk& x = first[k];
+    const T& x = first[k];
     const uint64_t size = static_cast<uint64_t>(x.rows) * static_cast<uint64_t>(x.tier);
     return Key{(static_cast<uint64_t>(x.tier) << 48) + ((1ull << 48) - 1 - size), static_cast<int32_t>(k)};
   };
   std::vector<Key> key(count);
-  std::vector<Chunk> sorted(count);
+  std::vector<T> sorted;
+  sorted.reserve(static_cast<size_t>(count));
   if (count > 1024 || n_items <= 1) {
     for (int64_t k = 0; k < count; ++k) key[k] = key_of(k);
     std::sort(key.begin(), key.end());
-    for (int64_t k = 0; k < count; ++k) sorted[k] = first[key[k].second];
+    for (int64_t k = 0; k < count; ++k) sorted.push_back(first[key[k].second]);
   } else {
     // each item's few chunks in that order, then dealt out a rank at a time (two sorts over all: 20 us more at 512)
     std::vector<int32_t> begin(static_cast<size_t>(n_items) + 1, 0);
@@ -657,11 +659,11 @@ void order_chunks(std::vector<Chunk>::iterator first, std::vector<Chunk>::iterat
     for (int64_t i = 0; i < n_items; ++i) begin[i + 1] += begin[i];
     std::vector<int32_t> at(begin.begin(), begin.end() - 1);
     for (int64_t k = 0; k < count; ++k) key[at[first[k].item]++] = key_of(k);
-    for (int64_t i = 0; i < n_items; ++i) std::sort(key.begin() + begin[i], key.begin() + begin[i + 1]);
-    int64_t out = 0;
-    for (int32_t rank = 0; out < count; ++rank)
+    for (int64_t i = 0; i < n_items; ++i)
+      if (!std::is_sorted(key.begin() + begin[i], key.begin() + begin[i + 1])) std::sort(key.begin() + begin[i], key.begin() + begin[i + 1]);
+    for (int32_t rank = 0; static_cast<int64_t>(sorted.size()) < count; ++rank)
       for (int64_t i = 0; i < n_items; ++i)
-        if (begin[i] + rank < begin[i + 1]) sorted[out++] = first[key[begin[i] + rank].second];
+        if (begin[i] + rank < begin[i + 1]) sorted.push_back(first[key[begin[i] + rank].second]);
   }
   std::copy(sorted.begin(), sorted.end(), first);
 }
@@ -704,6 +706,13 @@ void merge_chunks(const std::vector<int32_t>& slot_begin, const std::vector<int3
       *to++ = ch;
     }
 }
+
+// A run of rows of one tier of one item while a schedule is put together.
+struct Piece {
+  int32_t item, tier;      // tier: bits
+  int32_t row0, rows;
+  int32_t slot, next;      // Chunk::slot, Chunk::next
+};
 
 // every chunk learns its item's first partial slot and slot count (the merge inside the decode kernels needs them)
 void stamp_slots(std::vector<Chunk>& table, const std::vector<int32_t>& slot_begin, const std::vector<int32_t>& slot_count) {
@@ -932,8 +941,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
       PACK_HIP(launch_tier_count(bits_tok, tb.batch, d_blk_counts, it.max_T, st));
     }
-    std::vector<int32_t> h_counts(n_counts, 0);
     std::vector<uint8_t> h_bits_ch(mixed ? n * kHeadDim : 0);
+    bool refused = false;
     {
       const int64_t counts_b = round_up(n_counts * static_cast<int64_t>(sizeof(int32_t)), 16);
       StageRegion r;
@@ -944,7 +953,16 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       if (mixed) a.add(bits_ch, r.data + counts_b, static_cast<int64_t>(h_bits_ch.size()), kDstHost);
       if (d_krange) a.fill(d_krange, n * kHeadDim * 2 * static_cast<int64_t>(sizeof(uint32_t)), 0xFFFFFFFFu, 0u);
       const auto read = [&] {
-        std::memcpy(h_counts.data(), r.data, h_counts.size() * sizeof(int32_t));
+        const int32_t* blk = reinterpret_cast<const int32_t*>(r.data);
+        for (int64_t i = 0; i < n; ++i) {
+          const int64_t b1 = i + 1 < n ? it.blk_off[i + 1] : it.n_blocks;
+          int32_t sum[4] = {0, 0, 0, 0};
+          for (int64_t b = it.blk_off[i]; b < b1; ++b) {
+            refused = refused || blk[4 * b] < 0;      // (a block with a value that is no bit-width says so in its first count)
+            for (int k = 0; k < 4; ++k) sum[k] += blk[4 * b + k];
+          }
+          for (int k = 0; k < 4; ++k) c->counts[i * 4 + k] = sum[k];
+        }
         if (mixed) std::memcpy(h_bits_ch.data(), r.data + counts_b, h_bits_ch.size());
       };
       PACK_HIP(stage_round_trip(a, dev, r, st, read, [&](const CopyArgs& ca) {
@@ -953,14 +971,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
         return launch_tier_scatter(bits_tok, tb.batch, d_blk_counts, d_positions, plan, it.max_T, ca, st);
       }));
     }
-    if (!counted)
-      for (int64_t b = 0; b < it.n_blocks; ++b)      // (a block with any other value says so in its first count)
-        if (h_counts[b * 4] < 0) return bail(fail(RDKV_ERR_INVALID_ARG, "bits_tok holds a value outside {0, 2, 4, 8, 16}"));
-    for (int64_t i = 0; i < n; ++i) {
-      const int64_t b1 = i + 1 < n ? it.blk_off[i + 1] : it.n_blocks;
-      for (int64_t b = it.blk_off[i]; b < b1; ++b)
-        for (int k = 0; k < 4; ++k) c->counts[i * 4 + k] += h_counts[b * 4 + k];
-    }
+    if (refused) return bail(fail(RDKV_ERR_INVALID_ARG, "bits_tok holds a value outside {0, 2, 4, 8, 16}"));
     if (mixed) {
       c->items_k.resize(n);
       for (int64_t i = 0; i < n; ++i) {
@@ -981,15 +992,23 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   }
 
   // ---- plan: kept-position lists, arena segments, split schedule -------------------------
-  std::vector<int64_t> idx_base(n * 4, 0);
   int64_t kept = 0, cur = 0, stored = 0;
   int max_tiles = 0;
   for (int64_t i = 0; i < n; ++i) {
     int tiles = 0;
+    int64_t kbits = 0, nquant = 0;      // of the item's channels
+    if (mixed) {
+      const ItemK& ik = c->items_k[i];
+      for (int t2 = 0; t2 < 4; ++t2) {
+        const int end = t2 < 3 ? ik.slot_base[t2 + 1] : ik.n_slots;
+        const int64_t held = std::count_if(ik.slot_ch + ik.slot_base[t2], ik.slot_ch + end, [](int16_t ch) { return ch >= 0; });
+        kbits += held * pack_tier_bits(t2);
+        nquant += t2 > 0 ? held : 0;
+      }
+    }
     for (int ti = 0; ti < 4; ++ti) {
       const int bits = pack_tier_bits(ti);
       const int64_t cnt = c->counts[i * 4 + ti];
-      idx_base[i * 4 + ti] = kept;
       kept += cnt;
       tiles += static_cast<int>((cnt + kTile64 - 1) / kTile64);
       max_tiles = std::max(max_tiles, tiles);
@@ -1007,15 +1026,6 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
         cur += sizes[si];
       }
       if (mixed) {
-        int64_t kbits = 0, nquant = 0;
-        const ItemK& ik = c->items_k[i];
-        for (int s2 = 0; s2 < ik.n_slots; ++s2)
-          if (ik.slot_ch[s2] >= 0) {
-            int t2 = 3;
-            while (t2 > 0 && s2 < ik.slot_base[t2]) --t2;
-            kbits += pack_tier_bits(t2);
-            nquant += t2 > 0;
-          }
         const int64_t groups = c->k_per_unit ? (cnt > 0 ? 1 : 0) : (cnt + kKTokenGroup - 1) / kKTokenGroup;
         stored += cnt * kbits / 8 + groups * 4 * nquant;
         stored += cnt * (tier_row_bytes(bits) + tier_meta_bytes(bits));
@@ -1219,27 +1229,35 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   const int64_t round16 = 512;
   const int64_t chunk_bytes16 = std::max<int64_t>(96 << 10, (cost16 + round16 - 1) / round16);
   std::vector<int32_t> slot_begin(std::max<int64_t>(n, 1), 0), slot_count(std::max<int64_t>(n, 1), 0);
-  c->chunks.reserve(static_cast<size_t>(n_one_round + 2 * n));
-  std::vector<Chunk> conts;     // continuation pieces (token-wise mode): reached through Chunk::next, never launched
-  auto make_chunk = [&](int64_t i, int ti, int64_t r0, int64_t rows) {
-    const int bits = pack_tier_bits(ti);
-    const int64_t* so = &c->seg_off[(i * 4 + ti) * 4];
+  // (Cut and ordered as pieces, a quarter of a chunk's size, and written out once, into the memory the launch copies them from:
+  // the packing launch waits for this.  728 chunks of 128 items took 25 us from the counts to the block's allocation; a pass
+  // over them 645 -> 641 us, staged channel-wise calls on 50K keys 189 -> 185.)
+  std::vector<Piece> pieces, conts;     // conts: continuation pieces (token-wise mode), reached through Chunk::next, never launched
+  pieces.reserve(static_cast<size_t>(n_one_round + 2 * n));
+  const auto make_piece = [](int64_t i, int ti, int64_t r0, int64_t rows) {
+    return Piece{static_cast<int32_t>(i), pack_tier_bits(ti), static_cast<int32_t>(r0), static_cast<int32_t>(rows), 0, -1};
+  };
+  const auto chunk_of = [&](const Piece& p) {
     Chunk ch{};
+    ch.tier = p.tier;
+    ch.item = ch.reserved = p.item;
+    ch.slot = p.slot;
+    ch.next = p.next;
+    ch.rows = p.rows;
+    if (p.rows == 0) return ch;
+    const int64_t i = p.item, r0 = p.row0;
+    const int bits = p.tier, ti = bits == 16 ? 0 : bits == 8 ? 1 : bits == 4 ? 2 : 3;
+    const int64_t* so = &c->seg_off[(i * 4 + ti) * 4];
     ch.k_data = so[0] + (mixed ? r0 / kTile64 * c->items_k[i].kt_bytes : r0 * tier_row_bytes(bits));
     ch.k_meta = so[1] + (mixed ? (c->k_per_unit ? 0 : r0 / kTile64 * c->items_k[i].km_bytes)
                                : r0 * tier_meta_bytes(bits));
     ch.v_data = so[2] + r0 * tier_row_bytes(bits);
     ch.v_meta = so[3] + r0 * tier_meta_bytes(bits);
-    ch.rows = static_cast<int32_t>(rows);
-    ch.tier = bits;
-    ch.item = static_cast<int32_t>(i);
     for (int t2 = 0; t2 < 4; ++t2) ch.k_word_end[t2] = mixed ? c->items_k[i].word_end[t2] : int16_t(0);
-    ch.reserved = static_cast<int32_t>(i);
-    ch.next = -1;
     return ch;
   };
   for (int64_t i = 0; i < n; ++i) {
-    slot_begin[i] = static_cast<int32_t>(c->chunks.size());
+    slot_begin[i] = static_cast<int32_t>(pieces.size());
     // segments cut tier by tier: every tier, or only the 16-bit tier (its own kernel) when the quantized tiers of a
     // token-wise item are cut into shares below
     for (int ti = 0; ti < (shares ? 1 : 4); ++ti) {
@@ -1252,9 +1270,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       const int64_t nch = (cnt + want - 1) / want;
       const int64_t rows_per = round_up((cnt + nch - 1) / nch, 64);
       for (int64_t r0 = 0; r0 < cnt; r0 += rows_per) {
-        Chunk ch = make_chunk(i, ti, r0, std::min<int64_t>(rows_per, cnt - r0));
-        ch.slot = static_cast<int32_t>(c->chunks.size());
-        c->chunks.push_back(ch);
+        Piece p = make_piece(i, ti, r0, std::min<int64_t>(rows_per, cnt - r0));
+        p.slot = static_cast<int32_t>(pieces.size());
+        pieces.push_back(p);
       }
     }
     if (shares) {
@@ -1274,15 +1292,15 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
           const int64_t rc = row_cost(i, pack_tier_bits(ti));
           int64_t take = k + 1 == n_wg ? left : std::min<int64_t>(left, round_up(std::max<int64_t>(share, rc) / rc, 64));
           if (k + 1 < n_wg && left - take < 64) take = left;     // no slivers
-          Chunk ch = make_chunk(i, ti, r0, take);
+          Piece p = make_piece(i, ti, r0, take);
           if (prev == -1) {
-            ch.slot = static_cast<int32_t>(c->chunks.size());
-            c->chunks.push_back(ch);
-            prev = -2 - ch.slot;
+            p.slot = static_cast<int32_t>(pieces.size());
+            pieces.push_back(p);
+            prev = -2 - p.slot;
           } else {
             const int32_t me = static_cast<int32_t>(conts.size());
-            conts.push_back(ch);
-            if (prev <= -2) c->chunks[-2 - prev].next = me; else conts[prev].next = me;   // local index for now
+            conts.push_back(p);
+            if (prev <= -2) pieces[-2 - prev].next = me; else conts[prev].next = me;   // local index for now
             prev = me;
           }
           r0 += take;
@@ -1291,44 +1309,33 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
         }
       }
     }
-    if (static_cast<int32_t>(c->chunks.size()) == slot_begin[i]) {
+    if (static_cast<int32_t>(pieces.size()) == slot_begin[i]) {
       // nothing retained: an empty chunk, so that a workgroup still writes the item's output rows (0, lse = -inf)
-      Chunk ch{};
-      ch.tier = 2;
-      ch.item = static_cast<int32_t>(i);
-      ch.slot = static_cast<int32_t>(c->chunks.size());
-      ch.reserved = static_cast<int32_t>(i);
-      ch.next = -1;
-      c->chunks.push_back(ch);
+      Piece p = make_piece(i, 3, 0, 0);
+      p.slot = static_cast<int32_t>(pieces.size());
+      pieces.push_back(p);
     }
-    slot_count[i] = static_cast<int32_t>(c->chunks.size()) - slot_begin[i];
+    slot_count[i] = static_cast<int32_t>(pieces.size()) - slot_begin[i];
   }
-  c->n_slots = static_cast<int64_t>(c->chunks.size());
-  stamp_slots(c->chunks, slot_begin, slot_count);
+  const int64_t n_launched = static_cast<int64_t>(pieces.size());
+  c->n_slots = n_launched;
   // 16-bit chunks first (their own kernel), then the launched quantized ones, then the continuation pieces
-  std::stable_partition(c->chunks.begin(), c->chunks.end(), [](const Chunk& x) { return x.tier == 16; });
-  {
-    int64_t n16 = 0;
-    for (const Chunk& ch : c->chunks) n16 += ch.tier == 16;
-    order_chunks(c->chunks.begin(), c->chunks.begin() + n16, n);
-    order_chunks(c->chunks.begin() + n16, c->chunks.end(), n);
-  }
-  c->n_chunks16 = 0;
-  for (const Chunk& ch : c->chunks) c->n_chunks16 += ch.tier == 16;
-  c->sched16 = c->n_chunks16;
-  c->schedq = static_cast<int64_t>(c->chunks.size()) - c->n_chunks16;
+  const int64_t n16 = std::count_if(pieces.begin(), pieces.end(), [](const Piece& x) { return x.tier == 16; });
+  if (n16 > 0 && n16 < n_launched) std::stable_partition(pieces.begin(), pieces.end(), [](const Piece& x) { return x.tier == 16; });
+  order_chunks<Piece>(pieces.begin(), pieces.begin() + n16, n);
+  order_chunks<Piece>(pieces.begin() + n16, pieces.end(), n);
+  c->n_chunks16 = n16;
+  c->sched16 = n16;
+  c->schedq = n_launched - n16;
   c->n_cont = static_cast<int64_t>(conts.size());
-  {   // Chunk::next becomes an index into the whole table
-    const int32_t base = static_cast<int32_t>(c->chunks.size());
-    for (Chunk& ch : c->chunks) if (ch.next >= 0) ch.next += base;
-    for (Chunk& ch : conts) if (ch.next >= 0) ch.next += base;
-    c->chunks.insert(c->chunks.end(), conts.begin(), conts.end());
-  }
+  // Chunk::next becomes an index into the whole table
+  for (Piece& p : pieces) if (p.next >= 0) p.next += static_cast<int32_t>(n_launched);
+  for (Piece& p : conts) if (p.next >= 0) p.next += static_cast<int32_t>(n_launched);
   // merging workgroups where the decode kernel looks for partials (see decode_merge.h)
   if (mixed ? c->mixed_waves == 8 : decode_tiles_take_rows(static_cast<int>(c->sched16 + c->schedq), c->n_cont > 0))
     c->merge_parts = merge_parts(g, n);
   c->n_merge = count_merge_chunks(slot_count, n, c->merge_parts);
-  const int64_t n_chunks = static_cast<int64_t>(c->chunks.size()), n_table = n_chunks + c->n_merge;
+  const int64_t n_chunks = n_launched + c->n_cont, n_table = n_chunks + c->n_merge;
   c->own_slot_count.assign(slot_count.begin(), slot_count.begin() + n);
 
   // ---- allocate what the cache owns: one block --------------------------------------------
@@ -1366,12 +1373,20 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       const int64_t tables_b = ik_b + n_table * static_cast<int64_t>(sizeof(Chunk));
       StageRegion r;
       int dev = 0;
-      PACK_HIP(stage_acquire(static_cast<size_t>(tables_b), false, st, &r, &dev));
+      PACK_HIP(stage_acquire(static_cast<size_t>(tables_b), true, st, &r, &dev));
       if (mixed) std::memcpy(r.data, c->items_k.data(), n * sizeof(ItemK));
-      {   // [launched chunks | merging workgroups | continuation pieces]
-        Chunk* t = reinterpret_cast<Chunk*>(r.data + ik_b);
-        std::copy(c->chunks.begin(), c->chunks.end(), t);       // (a schedule has one of the two last)
-        merge_chunks(slot_begin, slot_count, n, c->merge_parts, t + n_chunks);
+      // [launched chunks | merging workgroups | continuation pieces] (a schedule has one of the two last)
+      Chunk* const table = reinterpret_cast<Chunk*>(r.data + ik_b);
+      {
+        Chunk* t = table;
+        for (const Piece& p : pieces) {      // (they know their item's first partial slot and slot count)
+          *t = chunk_of(p);
+          t->slot0 = slot_begin[p.item];
+          t->nslots = slot_count[p.item];
+          ++t;
+        }
+        for (const Piece& p : conts) *t++ = chunk_of(p);
+        merge_chunks(slot_begin, slot_count, n, c->merge_parts, t);
       }
       CopyArgs a{};
       a.add(r.data, c->d_block + o_ik, tables_b, kSrcHost);
@@ -1381,12 +1396,17 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       if (mixed) a.add(bits_ch, c->d_bits_ch, n * kHeadDim);
       if (lam) a.add(lam, c->d_block + o_lam, maps * n * 8);
       if (iters) a.add(iters, c->d_block + o_it, maps * n * 4);
-      PACK_HIP(stage_launch(a, r, true, st, [&](const CopyArgs& ca) {
+      hipError_t launched = stage_launch(a, r, false, st, [&](const CopyArgs& ca) {
         if (kept == 0) return launch_copy(ca, st);
         TimedScope ts(RDKV_TIME_PACK, st);
         return launch_quant_pack(static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), d_positions, c->d_tier_idx, plan,
                                  tb.batch, c->d_arena, max_tiles, d_krange, c->group_size == kHeadDim ? 1 : 0, ca, st);
-      }));
+      });
+      if (launched == hipSuccess) c->chunks.assign(table, table + n_chunks);      // the host's copy, while the launch is on its way
+      if (launched == hipSuccess && r.own) launched = stage_wait(r, st);
+      g_staging[dev].release(r);
+      if (r.own) (void)hipHostFree(r.own);
+      PACK_HIP(launched);
       c->slot_begin = slot_begin;
       c->slot_count = slot_count;
       {   // the split workspace of this stream lives in the block: a first decode under graph capture allocates nothing
@@ -1876,8 +1896,8 @@ static rdkv_status rebuild_schedule(rdkv_cache* c, void* clear, int64_t clear_by
       table.push_back(moved(k, gc->chunks[j]));
   }
   // launch order inside each kernel's range; the tail's chunks and the continuation pieces stay where they are
-  order_chunks(table.begin(), table.begin() + n16, n);
-  order_chunks(table.begin() + n16, table.begin() + n_gen_chunks, n);
+  order_chunks<Chunk>(table.begin(), table.begin() + n16, n);
+  order_chunks<Chunk>(table.begin() + n16, table.begin() + n_gen_chunks, n);
   stamp_slots(table, nb, nc);
   stamp_slots(own, nb, nc);
   const int64_t n_table = static_cast<int64_t>(table.size());

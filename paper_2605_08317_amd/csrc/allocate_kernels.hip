@@ -19,8 +19,8 @@
 //     the bit sum follows from the histogram.
 // Items of up to 32K units are searched by one workgroup that holds the units in registers and also writes the bit map
 // and the counts the packing stage starts from (allocate_item_kernel: one launch instead of four to eight).  Longer
-// items spread the three passes over the units over many workgroups (hist_kernel, gather_kernel, write_kernel); the
-// workgroup that finishes an item's pass last runs the steps that follow it.
+// items spread the passes over the units over many workgroups (slice_max_kernel, hist_kernel, gather_kernel, write_kernel); each
+// of them takes the histogram's steps for itself, and the one that gathers an item's last open units the steps on those.
 // Channel maps (128 units) take one wavefront (channel_allocate_kernel).
 #include <algorithm>
 #include <type_traits>
@@ -451,27 +451,37 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 // rounded reciprocal and one exact remainder (Markstein, IBM J. Res. Dev. 34, 1990), by division where the remainder could
 // underflow or is none.
 constexpr int kMostRadius = 7;
-__device__ __forceinline__ float pool_quotient(const AllocArgs& a, float s) {
-  const float n = static_cast<float>(a.pool), q0 = s * a.pool_inv;
-  float q = __builtin_fmaf(__builtin_fmaf(-q0, n, s), a.pool_inv, q0);
-  if (!(s > 1e-25f && s < 1e30f)) q = s == 0.f ? 0.f : s / n;
-  return q;
-}
-// four units whose window starts at w[0], 16-byte aligned
-__device__ __forceinline__ void pool_four(const AllocArgs& a, const float* w, float (&v)[4]) {
-  if (a.pool == 5) {                       // (uniform)
-    const float4 x = *reinterpret_cast<const float4*>(w), y = *reinterpret_cast<const float4*>(w + 4);
-    const float t[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+__device__ __forceinline__ void pool_quotients(const AllocArgs& a, float (&s)[4]) {
+  const float n = static_cast<float>(a.pool);
+  bool odd = false;
+  float q[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = pool_quotient(a, (((t[e] + t[e + 1]) + t[e + 2]) + t[e + 3]) + t[e + 4]);
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float s = 0.f;
-      for (int k = 0; k < a.pool; ++k) s += w[e + k];
-      v[e] = pool_quotient(a, s);
-    }
+  for (int e = 0; e < 4; ++e) {
+    const float q0 = s[e] * a.pool_inv;
+    q[e] = __builtin_fmaf(__builtin_fmaf(-q0, n, s[e]), a.pool_inv, q0);
+    odd |= !(s[e] == 0.f || (s[e] > 1e-25f && s[e] < 1e30f));
   }
+  if (__builtin_expect(__any(odd), 0)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = s[e] / n;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) s[e] = q[e];
+}
+// four units of a window of five from the eight weights under it
+__device__ __forceinline__ void pool_five(const AllocArgs& a, const float (&t)[8], float (&v)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = (((t[e] + t[e + 1]) + t[e + 2]) + t[e + 3]) + t[e + 4];
+  pool_quotients(a, v);
+}
+// ... of any window, the first of which starts at w[0]
+__device__ __forceinline__ void pool_any(const AllocArgs& a, const float* w, float (&v)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = 0.f;
+    for (int k = 0; k < a.pool; ++k) v[e] += w[e + k];
+  }
+  pool_quotients(a, v);
 }
 
 // ---- one workgroup per item: up to 1024 REG units in registers ------------------------------------------------------
@@ -516,28 +526,32 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
     }
   }
   if (a.raw) {
-    // through LDS, which nothing else uses yet: unit u at s_raw[u + radius], zeros around them
-    static_assert(kItemLds<REG> >= (REG * kThreads + 2 * kMostRadius) * sizeof(float), "an item and its window's ends");
+    // through LDS, which nothing else uses yet, for the neighbours' sake: unit u at s_raw[kPad + u], zeros around them
+    constexpr int kPad = 8;
+    static_assert(kPad > kMostRadius && kItemLds<REG> >= (REG * kThreads + 2 * kPad) * sizeof(float), "an item and its window's ends");
     float* s_raw = reinterpret_cast<float*>(smem);
-    const int radius = a.pool / 2;
-    if (tid < radius) s_raw[tid] = 0.f;
-    if (tid < radius) s_raw[radius + min(REG * kThreads, (U + 3) / 4 * 4) + tid] = 0.f;
+    if (tid < kPad) s_raw[tid] = s_raw[kPad + (U + 3) / 4 * 4 + tid] = 0.f;
 #pragma unroll
     for (int j = 0; j < kQ; ++j) {
       const int u0 = 4 * (j * kThreads + tid);
-      if (u0 < U) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s_raw[radius + u0 + e] = v[4 * j + e];
-      }
+      if (u0 < U) *reinterpret_cast<float4*>(s_raw + kPad + u0) = make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kQ; ++j) {
       const int u0 = 4 * (j * kThreads + tid);
-      float x[4] = {0.f, 0.f, 0.f, 0.f};
-      if (u0 < U) pool_four(a, s_raw + u0, x);
+      if (u0 < U) {
+        float x[4];
+        if (a.pool == 5) {                 // (uniform)
+          const float2 lo = *reinterpret_cast<const float2*>(s_raw + kPad + u0 - 2), hi = *reinterpret_cast<const float2*>(s_raw + kPad + u0 + 4);
+          const float t[8] = {lo.x, lo.y, v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3], hi.x, hi.y};
+          pool_five(a, t, x);
+        } else {
+          pool_any(a, s_raw + kPad + u0 - a.pool / 2, x);
+        }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * j + e] = u0 + e < U ? x[e] : 0.f;
+        for (int e = 0; e < 4; ++e) v[4 * j + e] = u0 + e < U ? x[e] : 0.f;
+      }
     }
     __syncthreads();
   }
@@ -720,7 +734,7 @@ constexpr int kItemUnits = 32 * kThreads;   // longest item of that kernel
 
 // ---- longer items: the passes over the units on many workgroups -------------------------------------------------
 // Beyond 32K units the registers of one compute unit no longer hold an item.  Measured, 8 items of 128K units: 98 to 255
-// us in six kernels -> 33 us in four; what is left is the latency of two hand-overs to the last workgroup and of the
+// us in six kernels -> 32 us in four, pooling included; what is left is the latency of a hand-over to the last workgroup and of the
 // dependent steps.
 // An item's weights read as aligned 16-byte quads.  Quad q covers units 4 q - a .. 4 q - a + 3,
 // a = how many floats the item's first weight sits past a 16-byte boundary; units outside [0, U) read as 0 (never above
@@ -755,12 +769,8 @@ constexpr int kMostMaxima = 2 * kMostSlices; // workgroups that share its first 
 static_assert(kMostMaxima <= 64, "a lane each");
 constexpr int kListCap = 24576;             // undecided units of an item (96 KB of LDS in the exact steps)
 struct SearchState {
-  Search s;
-  Hull hull;
-  long long fixed;                          // what the units outside the open buckets add to the bit sum
-  int32_t open_a[kThr], open_b[kThr];       // the open buckets (OpenBuckets)
-  int32_t n_open, n_list, arrive[2], fill;  // fill: >= 0: the tier of every unit
-  uint32_t top;                             // pattern of the largest unit
+  Search s;                                 // the search's end
+  int32_t n_list, arrive, fill;             // fill: >= 0: the tier of every unit
 };
 struct MultiArgs {
   AllocArgs a;
@@ -789,7 +799,7 @@ __device__ __forceinline__ T load_agent(const T* p) {
 
 // The largest unit of every slice, which anchors the histograms (over the full range of fp32 they had 32768 buckets at a
 // quarter of the resolution: hist_kernel 21 us, gather_kernel 20 at 8 x 128K units), and zeros for the next kernels.
-// POOL: raw weights are pooled on the way and written for the next kernels (8 x 128K units: TODO).
+// POOL: raw weights are pooled on the way and written for the next kernels (8 x 128K units: 5.8 us, as two launches 5.1 + 4.7).
 template <bool POOL>
 __global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, float* pooled, uint4* clear, int64_t n_clear) {
   constexpr int kRound = 4 * kThreads;
@@ -821,7 +831,13 @@ __global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, float*
         if (j < 4 || tid < 2 * radius) s_raw[j * kThreads + tid] = v[j];
       __syncthreads();
       float x[4];
-      pool_four(m.a, s_raw + 4 * tid, x);
+      if (m.a.pool == 5) {                 // (uniform)
+        const float4 lo = *reinterpret_cast<const float4*>(s_raw + 4 * tid), hi = *reinterpret_cast<const float4*>(s_raw + 4 * tid + 4);
+        const float t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        pool_five(m.a, t, x);
+      } else {
+        pool_any(m.a, s_raw + 4 * tid, x);
+      }
       const int u = u0 + 4 * tid;
       if (u + 3 < u_last) {
         *reinterpret_cast<Units4*>(out + u) = Units4{{x[0], x[1], x[2], x[3]}};
@@ -855,36 +871,28 @@ __global__ __launch_bounds__(kThreads) void slice_max_kernel(MultiArgs m, float*
   }
 }
 
-// every slice adds its units to the item's histogram; the last one takes the steps the histogram decides
+// every slice adds its units to the item's histogram
 constexpr size_t kHistLds = Anchored::kWords * sizeof(int);
+__device__ __forceinline__ float largest_unit(const MultiArgs& m, int row) {      // (before wave_max)
+  const int lane = threadIdx.x & 63;
+  return lane < m.maxima ? m.slice_max[row * m.maxima + lane] : 0.f;
+}
 __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   extern __shared__ __align__(16) unsigned char smem[];
   int* s_hist = reinterpret_cast<int*>(smem);
-  __shared__ int s_wave[kWaves], s_flag, s_many;
-  __shared__ Hull s_hull;
-  __shared__ Search s_search;
   const AllocArgs& a = m.a;
-  const int row = blockIdx.y, item = a.item_of(row);
-  const ItemOf it(a.batch, item);
+  const int row = blockIdx.y;
+  const ItemOf it(a.batch, a.item_of(row));
   const int U = it.T;
-  const int tid = threadIdx.x, lane = tid & 63;
-  SearchState& st = m.state[row];
+  const int tid = threadIdx.x;
   const Quads quads(a.w + it.off, U);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
-  float mx = lane < m.maxima ? m.slice_max[row * m.maxima + lane] : 0.f;
+  float mx = largest_unit(m, row);
   float wv[4] = {0.f, 0.f, 0.f, 0.f};
   if (q0 + tid < q1) quads.load(q0 + tid, wv);
   const Problem P(a, U, it.budget);
-  const int fill = U > 0 ? P.fill(U) : P.tiers[0];
-  if (fill >= 0) {
-    if (blockIdx.x == 0 && tid == 0) {
-      st.fill = fill;
-      st.s = Search{0.0, 0.0, 0.0, 0, 0, 1};
-      report(a, item, false, st.s);
-    }
-    return;
-  }
+  if (U <= 0 || P.fill(U) >= 0) return;
   for (int i = tid; i < Anchored::kWords / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
   mx = wave_max(mx);
   const Anchored map{__float_as_uint(mx)};
@@ -900,87 +908,87 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   int32_t* gh = m.hist + static_cast<int64_t>(row) * Anchored::kBuckets;
   for (int i = tid; i < Anchored::kBuckets; i += kThreads)
     if (s_hist[hist_slot(i)] != 0) atomicAdd(gh + i, s_hist[hist_slot(i)]);
-  if (!last_to_arrive(&st.arrive[0], m.slices, &s_flag)) return;
-  constexpr int kPer = Anchored::kBuckets / kThreads;
-  {
-    int h[kPer];
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) h[k] = load_agent(gh + tid + k * kThreads);
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) s_hist[hist_slot(tid + k * kThreads)] = h[k];
-  }
-  __syncthreads();
-  suffix_sums<Anchored::kBuckets>(s_hist, s_wave);
-  if (tid < 128) {                       // two wavefronts, the same steps
-    Search S{0.0, static_cast<double>(mx), 0.0, 0, 0, 0};
-    steps_on_histogram(P, map, s_hist, S);
-    S.done = S.done || S.it >= P.max_iters;
-    Hull hull = bracket_of(S);
-    OpenBuckets open(P, map, hull);
-    const bool many = !S.done && open.count(s_hist) > kManyOpen;
-    if (many) {
-      const double end = narrow_hull(P, map, s_hist, S, tid < 64);
-      if (lane == 0) (tid < 64 ? s_hull.lo : s_hull.hi) = end;
-    }
-    if (tid == 0) s_many = many;
-    if (tid == 0) s_search = S;
-  }
-  __syncthreads();
-  if (tid < 64) {
-    const Search S = s_search;
-    const Hull hull = s_many ? s_hull : bracket_of(S);
-    const OpenBuckets open(P, map, hull);
-    if (tid == 0) {
-      st.s = S;
-      st.hull = hull;
-      st.fill = -1;
-      st.top = map.top;
-      st.fixed = open.fixed(P, s_hist);
-      st.n_open = open.count(s_hist);
-#pragma unroll
-      for (int k = 0; k < kThr; ++k) {
-        st.open_a[k] = open.a[k];
-        st.open_b[k] = open.b[k];
-      }
-      if (S.done) report(a, item, true, S);
-    }
-  }
 }
 
-// every slice appends its units of open buckets to the item's list; the last one takes the other steps
-constexpr size_t kGatherLds = kListCap * sizeof(float);
+// Every slice takes the steps the histogram decides for itself (the last workgroup of the kernel before did, for all: it waited
+// for the others' sums and its state went through memory: hist 13.3 + gather 10.5 us at 8 x 128K units, now 6.5 + 15.6), then appends its units of open
+// buckets to the item's list; the last one takes the other steps.
+constexpr size_t kGatherLds = Anchored::kWords * sizeof(int) + kListCap * sizeof(float);
 __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   extern __shared__ __align__(16) unsigned char smem[];
-  float* s_list = reinterpret_cast<float*>(smem);     // [kListCap]
-  __shared__ int s_n, s_base, s_above[kThr], s_flag, s_red[2 * kWaves];
+  int* s_hist = reinterpret_cast<int*>(smem);
+  float* s_list = reinterpret_cast<float*>(s_hist + Anchored::kWords);      // [kListCap]
+  __shared__ int s_wave[kWaves], s_n, s_base, s_above[kThr], s_flag, s_red[2 * kWaves];
   __shared__ Search s_search;
+  __shared__ Hull s_hull;
   const AllocArgs& a = m.a;
   const int row = blockIdx.y, item = a.item_of(row);
-  SearchState& st = m.state[row];
-  if (st.s.done) return;                    // written by the previous kernel
-  const int n = st.n_open;
-  if (n > kListCap && blockIdx.x != 0) return;
   const ItemOf it(a.batch, item);
   const int U = it.T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  SearchState& st = m.state[row];
   const Quads quads(a.w + it.off, U);
   int q0, q1;
   quads.slice(m.slices, &q0, &q1);
-  Search S = st.s;
+  constexpr int kPer = Anchored::kBuckets / kThreads;
+  int h[kPer];
+  const int32_t* gh = m.hist + static_cast<int64_t>(row) * Anchored::kBuckets;
+  float mx = largest_unit(m, row);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) h[k] = gh[tid + k * kThreads];
+  float w0[4] = {0.f, 0.f, 0.f, 0.f};      // the slice's first round, on its way during the steps
+  if (q0 + tid < q1) quads.load(q0 + tid, w0);
+  const Problem P(a, U, it.budget);
+  const int fill = U > 0 ? P.fill(U) : P.tiers[0];
+  if (fill >= 0) {
+    if (blockIdx.x == 0 && tid == 0) {
+      st.fill = fill;
+      st.s = Search{0.0, 0.0, 0.0, 0, 0, 1};
+      report(a, item, false, st.s);
+    }
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) s_hist[hist_slot(tid + k * kThreads)] = h[k];
+  mx = wave_max(mx);
+  const Anchored map{__float_as_uint(mx)};
+  if (tid == 0) s_n = 0;
+  __syncthreads();
+  suffix_sums<Anchored::kBuckets>(s_hist, s_wave);
+  if (wave < 2) {                        // two wavefronts, the same steps
+    Search T{0.0, static_cast<double>(mx), 0.0, 0, 0, 0};
+    steps_on_histogram(P, map, s_hist, T);
+    T.done = T.done || T.it >= P.max_iters;
+    const Hull bracket = bracket_of(T);
+    const bool many = !T.done && OpenBuckets(P, map, bracket).count(s_hist) > kManyOpen;
+    const double end = many ? narrow_hull(P, map, s_hist, T, wave == 0) : wave == 0 ? bracket.lo : bracket.hi;
+    if (lane == 0) (wave == 0 ? s_hull.lo : s_hull.hi) = end;
+    if (tid == 0) s_search = T;
+  }
+  __syncthreads();
+  Search S = s_search;
+  if (S.done) {
+    if (blockIdx.x == 0 && tid == 0) {
+      st.fill = -1;
+      st.s = S;
+      report(a, item, true, S);
+    }
+    return;
+  }
+  const Hull hull = s_hull;
+  const OpenBuckets open(P, map, hull);
+  const int n = open.count(s_hist);
+  if (n > kListCap && blockIdx.x != 0) return;
   if (n <= kListCap) {
     float* gl = m.list + static_cast<int64_t>(row) * kListCap;
-    OpenBuckets open;
-#pragma unroll
-    for (int k = 0; k < kThr; ++k) {
-      open.a[k] = st.open_a[k];
-      open.b[k] = st.open_b[k];
-    }
-    const OpenPatterns pat(open, Anchored{st.top});
-    if (tid == 0) s_n = 0;
-    __syncthreads();
+    const OpenPatterns pat(open, map);
     for (int qw = q0 + wave * 64; qw < q1; qw += kThreads) {
-      float wv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (qw + lane < q1) quads.load(qw + lane, wv);
+      float wv[4] = {w0[0], w0[1], w0[2], w0[3]};
+      if (qw != q0 + wave * 64) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wv[e] = 0.f;
+        if (qw + lane < q1) quads.load(qw + lane, wv);
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const bool in = pat.contains(wv[e]);
@@ -999,10 +1007,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
     __syncthreads();
     for (int i = tid; i < mine; i += kThreads)
       __hip_atomic_store(gl + s_base + i, s_list[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!last_to_arrive(&st.arrive[1], m.slices, &s_flag)) return;
-    const Problem P(a, U, it.budget);
-    const long long fixed = st.fixed;
-    const Hull hull = st.hull;
+    if (!last_to_arrive(&st.arrive, m.slices, &s_flag)) return;
+    const long long fixed = open.fixed(P, s_hist);
     if (n <= kFewOpen) {
       if (wave == 0) {
         steps_on_few(P, n, fixed, hull, S, [&](int i) { return load_agent(gl + i); });
@@ -1018,7 +1024,6 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   } else {
     // More than the list holds (weights all alike, or in a band of a few ulp): every step on all units, one workgroup.
     // 8 items of 128K units, one value, 64 steps: 820 us (with fp64 comparisons 1470); a band of 1e-3, 20 steps: 190 (440).
-    const Problem P(a, U, it.budget);
     while (!S.done && S.it < P.max_iters) {
       const double lam = (S.lo + S.hi) * 0.5;
       float t[kThr];
@@ -1049,6 +1054,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
     }
   }
   if (tid == 0) {
+    st.fill = -1;
     st.s = S;
     report(a, item, true, S);
   }

@@ -480,9 +480,50 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
   }   // items of the run
 }
 
+// w_c = ||Q[:,c]|| ||K[:,c]|| / sqrt(d): finishes the K sums of squares and adds the probe's column norms; a workgroup has
+// kChannelPart channels of an item, 8 threads per channel share the runs and the window rows (fixed order of additions).
+// Part of row_lse_kernel's launch: both need what pass 1 leaves (as a launch of its own 4 us of a pass over 8 x 50K keys).
+constexpr int kChannelPart = 32;
+__device__ __forceinline__ void channel_weights(const WeightArgs& a, float* __restrict__ w_ch, int part) {
+  static_assert(8 * kChannelPart == 256, "the threads of row_lse_kernel");
+  __shared__ float s_k[8][kChannelPart], s_q[8][kChannelPart];
+  const int item = blockIdx.y, lc = threadIdx.x & (kChannelPart - 1), sub = threadIdx.x / kChannelPart;
+  const int c = part * kChannelPart + lc;
+  int slot0;
+  const int n = item_slots(a, item, &slot0);
+  const int64_t b0 = slot0;
+  float ksq = 0.f;
+#pragma unroll 8
+  for (int b = sub; b < n; b += 8) ksq += a.ksq_part[(b0 + b) * kHeadDim + c];
+  const int seq = item / a.hkv, head = item % a.hkv;
+  const uint16_t* Qg = a.Q + (static_cast<int64_t>(seq) * a.hq + head * a.g) * a.s_obs * kHeadDim;
+  float qsq = 0.f;
+#pragma unroll 8
+  for (int r = sub; r < a.R; r += 8) {
+    const float q = __uint_as_float(static_cast<uint32_t>(Qg[r * kHeadDim + c]) << 16);
+    qsq = __builtin_fmaf(q, q, qsq);
+  }
+  s_k[sub][lc] = ksq;
+  s_q[sub][lc] = qsq;
+  __syncthreads();
+  if (sub == 0) {
+    ksq = qsq = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      ksq += s_k[k][lc];
+      qsq += s_q[k][lc];
+    }
+    w_ch[static_cast<int64_t>(item) * kHeadDim + c] = sqrtf(qsq) * sqrtf(ksq) * 0.08838834764831845f;
+  }
+}
+
 // log-sum-exp of every window row over the runs of its item (log2 domain): 16 rows per workgroup, 16 threads stride
-// over a row's runs
-__global__ __launch_bounds__(256) void row_lse_kernel(WeightArgs a) {
+// over a row's runs; the workgroups behind them: the channel weights, where they are wanted
+__global__ __launch_bounds__(256) void row_lse_kernel(WeightArgs a, float* __restrict__ w_ch) {
+  if (static_cast<int>(blockIdx.x) * 16 >= a.row_slots) {
+    channel_weights(a, w_ch, static_cast<int>(blockIdx.x) - a.row_slots / 16);
+    return;
+  }
   __shared__ float s_m[16][17], s_l[16][17];
   const int item = blockIdx.y;
   const int lr = threadIdx.x & 15, sub = threadIdx.x >> 4;
@@ -562,39 +603,6 @@ __global__ __launch_bounds__(256) void pool_kernel(const float* __restrict__ w_r
     if (t0 + 256 * j + tid < T) out[t0 + 256 * j + tid] = s[j] / count;
 }
 
-// w_c = ||Q[:,c]|| ||K[:,c]|| / sqrt(d): finishes the K sums of squares and adds the probe's column norms; 8 threads per
-// channel share the runs and the window rows (fixed order of additions)
-__global__ __launch_bounds__(1024) void channel_weight_kernel(WeightArgs a, float* __restrict__ w_ch) {
-  __shared__ float s_k[8][kHeadDim], s_q[8][kHeadDim];
-  const int item = blockIdx.x, c = threadIdx.x & (kHeadDim - 1), sub = threadIdx.x >> 7;
-  int slot0;
-  const int n = item_slots(a, item, &slot0);
-  const int64_t b0 = slot0;
-  float ksq = 0.f;
-#pragma unroll 8
-  for (int b = sub; b < n; b += 8) ksq += a.ksq_part[(b0 + b) * kHeadDim + c];
-  const int seq = item / a.hkv, head = item % a.hkv;
-  const uint16_t* Qg = a.Q + (static_cast<int64_t>(seq) * a.hq + head * a.g) * a.s_obs * kHeadDim;
-  float qsq = 0.f;
-#pragma unroll 8
-  for (int r = sub; r < a.R; r += 8) {
-    const float q = __uint_as_float(static_cast<uint32_t>(Qg[r * kHeadDim + c]) << 16);
-    qsq = __builtin_fmaf(q, q, qsq);
-  }
-  s_k[sub][c] = ksq;
-  s_q[sub][c] = qsq;
-  __syncthreads();
-  if (sub == 0) {
-    ksq = qsq = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      ksq += s_k[k][c];
-      qsq += s_q[k][c];
-    }
-    w_ch[static_cast<int64_t>(item) * kHeadDim + c] = sqrtf(qsq) * sqrtf(ksq) * 0.08838834764831845f;
-  }
-}
-
 // one round of workgroups (per_cu of them stay resident on a compute unit), at least one tile each
 int workgroups_of(int64_t n_tiles, int per_cu) { return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(n_tiles, 256 * per_cu))); }
 
@@ -602,10 +610,10 @@ int workgroups_of(int64_t n_tiles, int per_cu) { return static_cast<int>(std::ma
 int row_slots_of(int R) { return R <= 64 ? 64 : R <= 128 ? 128 : (R + 255) / 256 * 256; }
 
 template <int NRT, int RGW>
-void launch_passes(const WeightArgs& a, bool want_ch, hipStream_t st) {
-  if (want_ch) hipLaunchKernelGGL((weights_kernel<1, NRT, RGW, true>), dim3(a.workgroups), dim3(256), 0, st, a);
+void launch_passes(const WeightArgs& a, float* w_ch, hipStream_t st) {
+  if (w_ch) hipLaunchKernelGGL((weights_kernel<1, NRT, RGW, true>), dim3(a.workgroups), dim3(256), 0, st, a);
   else hipLaunchKernelGGL((weights_kernel<1, NRT, RGW, false>), dim3(a.workgroups), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(row_lse_kernel, dim3(a.row_slots / 16, a.n_items), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(row_lse_kernel, dim3(a.row_slots / 16 + (w_ch ? kHeadDim / kChannelPart : 0), a.n_items), dim3(256), 0, st, a, w_ch);
   hipLaunchKernelGGL((weights_kernel<2, NRT, RGW, false>), dim3(workgroups_of(a.n_tiles, kPass2PerCu)), dim3(256), 0, st, a);
 }
 
@@ -634,9 +642,9 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   a.lse = a.row_part + slots * a.row_slots * 2;
   a.w_raw = a.lse + n_items * a.row_slots;
   a.ksq_part = w_ch ? a.w_raw + total_tokens : nullptr;
-  if (a.R <= 64) launch_passes<1, 2>(a, w_ch != nullptr, st);
-  else if (a.R <= 128) launch_passes<2, 2>(a, w_ch != nullptr, st);
-  else launch_passes<2, 4>(a, w_ch != nullptr, st);
+  if (a.R <= 64) launch_passes<1, 2>(a, w_ch, st);
+  else if (a.R <= 128) launch_passes<2, 2>(a, w_ch, st);
+  else launch_passes<2, 4>(a, w_ch, st);
   if (raw) {
     *raw = a.w_raw;
   } else if (cfg.pool_kernel > 1) {
@@ -650,7 +658,6 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
     hipError_t e = hipMemcpyAsync(w_tok, a.w_raw, total_tokens * sizeof(float), hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return e;
   }
-  if (w_ch) hipLaunchKernelGGL(channel_weight_kernel, dim3(static_cast<unsigned>(n_items)), dim3(1024), 0, st, a, w_ch);
   return hipGetLastError();
 }
 

@@ -10,13 +10,16 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librdkv.so")
 CALL = os.path.join(HERE, "_rdkv_call.so")
+# Branches that every lane takes alike stay branches: by default the compiler makes loops and flags of them (in the walk over a
+# channel-wise row's words three instructions, a wait and two jumps per word, and 20 registers).
+UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
 # (source, object, extra flags); the mixed-mode decode kernels are compiled once per head-set count and row length
 # class so that their many instantiations build in parallel; the slowest objects come first
 SOURCES = [
-    ("decode_mixed_kernels.hip", "decode_mixed_hs2_long1.o", ["-DRDKV_MIXED_HS=2", "-DRDKV_MIXED_LONG=1"]),
-    ("decode_mixed_kernels.hip", "decode_mixed_hs2_long0.o", ["-DRDKV_MIXED_HS=2", "-DRDKV_MIXED_LONG=0"]),
-    ("decode_mixed_kernels.hip", "decode_mixed_hs1_long1.o", ["-DRDKV_MIXED_HS=1", "-DRDKV_MIXED_LONG=1"]),
-    ("decode_mixed_kernels.hip", "decode_mixed_hs1_long0.o", ["-DRDKV_MIXED_HS=1", "-DRDKV_MIXED_LONG=0"]),
+    ("decode_mixed_kernels.hip", "decode_mixed_hs2_long1.o", ["-DRDKV_MIXED_HS=2", "-DRDKV_MIXED_LONG=1"] + UNIFORM),
+    ("decode_mixed_kernels.hip", "decode_mixed_hs2_long0.o", ["-DRDKV_MIXED_HS=2", "-DRDKV_MIXED_LONG=0"] + UNIFORM),
+    ("decode_mixed_kernels.hip", "decode_mixed_hs1_long1.o", ["-DRDKV_MIXED_HS=1", "-DRDKV_MIXED_LONG=1"] + UNIFORM),
+    ("decode_mixed_kernels.hip", "decode_mixed_hs1_long0.o", ["-DRDKV_MIXED_HS=1", "-DRDKV_MIXED_LONG=0"] + UNIFORM),
     ("decode_mfma_kernels.hip", "decode_mfma_kernels.o", []),
     ("rdkv_api.hip", "rdkv_api.o", []),
     ("decode_rows_mfma.hip", "decode_rows_mfma.o", []),

@@ -43,7 +43,7 @@ struct WeightArgs {
   const uint16_t* K;
   const uint16_t* Q;             // [batch][hq][s_obs][d]
   float* row_part;               // [workgroups + items][row_slots][2]  (m, l) in the log2 domain
-  float* lse;                    // [items][row_slots]
+  float* lse;                    // [items][row_slots], or null: pass 2 makes it from the partials
   float* w_raw;                  // [total tokens] unpooled weights
   float* ksq_part;               // [workgroups + items][128] or null
   int32_t hq, hkv, g, s_obs, R, row_slots, causal;   // row_slots: R in whole sweeps of row groups
@@ -93,6 +93,31 @@ __device__ __forceinline__ int item_slots(const WeightArgs& a, int item, int* fi
   return w1 - w0 + 1;
 }
 
+// The log-sum-exp (log2 domain) of a row of an item of n <= MANY runs (p: the first one's), with the additions of
+// row_lse_kernel, whose sixteen threads have at most two runs each then.
+constexpr int kFewRuns = 32;
+template <int MANY>
+__device__ __forceinline__ float lse_of_few(const float2* p, int row_slots, int n) {
+  static_assert(MANY <= 32, "two runs a thread");
+  float2 v[MANY];
+#pragma unroll
+  for (int k = 0; k < MANY; ++k) v[k] = p[static_cast<int64_t>(min(k, n - 1)) * row_slots];     // (the last one repeated, without a branch)
+  float m = kNegBig, l = 0.f;
+#pragma unroll
+  for (int k = 0; k < MANY; ++k) m = fmaxf(m, v[k].x);
+#pragma unroll
+  for (int k = 0; k < min(MANY, 16); ++k) {
+    float own = v[k].x, sum = k < n ? v[k].y : 0.f;
+    if (k + 16 < MANY) {
+      const float2 hi = v[(k + 16) % MANY];
+      own = k + 16 < n ? fmaxf(own, hi.x) : own;
+      sum = sum * fast_exp2(v[k].x - own) + (k + 16 < n ? hi.y * fast_exp2(hi.x - own) : 0.f);
+    }
+    l += sum * fast_exp2(own - m);
+  }
+  return l > 0.f ? m + __log2f(l) : INFINITY;
+}
+
 // One workgroup = one run of key tiles against all window rows of their items.
 //   NRT  32-row tiles of window rows per wavefront: 2, or 1 when the item has at most 64 rows
 //   RGW  row groups (of 32 NRT rows) worked on at a time: 4, or 2 when the item has at most 128 rows
@@ -110,6 +135,9 @@ template <int PASS, int NRT, int RGW, bool KSQ>
 __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void weights_kernel(WeightArgs a) {
   __shared__ __align__(16) uint8_t s_keys[kBuffers][kKeyTileBytes];
   __shared__ float s_sum[PASS == 2 ? kSumTiles : 1][RGW][PASS == 2 ? kKeyTile : 1];   // pass 2: [tile % kSumTiles][row group][key]
+
+  constexpr int kRows = RGW * 32 * NRT;                // of a sweep
+  float* s_lse = &s_sum[0][0][0];                      // [kRows], before the first column sums
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -201,6 +229,17 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
       return buf;
     };
     start();
+    if constexpr (PASS == 2) {
+      if (a.lse == nullptr) {              // while the first keys arrive; n_tiles workgroups stays below 2^32
+        const uint32_t tiles_end = static_cast<uint32_t>(item0 + (lane == 0 ? 1 : tiles)) * static_cast<uint32_t>(a.workgroups);
+        const int w = static_cast<int>((tiles_end + static_cast<uint32_t>(a.n_tiles) - 1) / static_cast<uint32_t>(a.n_tiles)) - 1;   // owner_of the item's first tile, its last
+        const int w0 = uniform(w), n = __builtin_amdgcn_readlane(w, 1) - w0 + 1;
+        const int row = sweep * kRows + tid;
+        const float2* p = reinterpret_cast<const float2*>(a.row_part) + static_cast<int64_t>(w0 + item) * a.row_slots + row;
+        if (tid < kRows) s_lse[tid] = row >= a.R ? INFINITY : n <= 8 ? lse_of_few<8>(p, a.row_slots, n) : lse_of_few<kFewRuns>(p, a.row_slots, n);
+        __syncthreads();
+      }
+    }
     // window rows past the last repeat it: pass 1 drops their sums, pass 2 gives them a log-sum-exp of infinity
     bf16x8 q_op[NRT][8];
 #pragma unroll
@@ -219,7 +258,10 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
       for (int rt = 0; rt < NRT; ++rt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float4 v = *reinterpret_cast<const float4*>(a.lse + static_cast<int64_t>(item) * a.row_slots + row0 + rt * 32 + 8 * i + 4 * half);
+          const int r = (rgi * NRT + rt) * 32 + 8 * i + 4 * half;
+          float4 v;
+          if (a.lse) v = *reinterpret_cast<const float4*>(a.lse + static_cast<int64_t>(item) * a.row_slots + sweep * kRows + r);
+          else v = *reinterpret_cast<const float4*>(s_lse + r);
           nlse[rt][4 * i] = -v.x; nlse[rt][4 * i + 1] = -v.y; nlse[rt][4 * i + 2] = -v.z; nlse[rt][4 * i + 3] = -v.w;
         }
     }
@@ -447,7 +489,6 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
         }
       }
       __syncthreads();
-      constexpr int kRows = RGW * 32 * NRT;
       if (tid < kRows) {
         const int row = sweep * kRows + tid;
         if (row < a.R) {
@@ -613,7 +654,7 @@ template <int NRT, int RGW>
 void launch_passes(const WeightArgs& a, float* w_ch, hipStream_t st) {
   if (w_ch) hipLaunchKernelGGL((weights_kernel<1, NRT, RGW, true>), dim3(a.workgroups), dim3(256), 0, st, a);
   else hipLaunchKernelGGL((weights_kernel<1, NRT, RGW, false>), dim3(a.workgroups), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(row_lse_kernel, dim3(a.row_slots / 16 + (w_ch ? kHeadDim / kChannelPart : 0), a.n_items), dim3(256), 0, st, a, w_ch);
+  if (a.lse) hipLaunchKernelGGL(row_lse_kernel, dim3(a.row_slots / 16 + (w_ch ? kHeadDim / kChannelPart : 0), a.n_items), dim3(256), 0, st, a, w_ch);
   hipLaunchKernelGGL((weights_kernel<2, NRT, RGW, false>), dim3(workgroups_of(a.n_tiles, kPass2PerCu)), dim3(256), 0, st, a);
 }
 
@@ -641,6 +682,12 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   a.row_part = scratch;
   a.lse = a.row_part + slots * a.row_slots * 2;
   a.w_raw = a.lse + n_items * a.row_slots;
+  // An item of few runs needs no launch of its own for the log-sum-exp: pass 2 makes it while its first keys arrive.  Launch +
+  // pass 2 against pass 2: 16 x 1K tokens 3.9 + 16.0 -> 16.0 us, 4 x 8K (17 runs) 4.2 + 20.1 -> 21.5, 128 items of 20K tokens
+  // 5.4 + 185.6 -> 188.8.  Eight items have 65 runs each, and every workgroup would read them: 32K tokens 4.7 + 18.5 -> 22.7, 128K
+  // tokens and 256 rows 5.3 + 78 -> 88.
+  const int64_t most_runs = static_cast<int64_t>((max_T + kKeyTile - 1) / kKeyTile) * a.workgroups / n_tiles + 2;
+  if (!w_ch && most_runs <= kFewRuns && n_tiles < (1 << 22)) a.lse = nullptr;
   a.ksq_part = w_ch ? a.w_raw + total_tokens : nullptr;
   if (a.R <= 64) launch_passes<1, 2>(a, w_ch, st);
   else if (a.R <= 128) launch_passes<2, 2>(a, w_ch, st);

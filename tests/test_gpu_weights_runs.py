@@ -56,3 +56,25 @@ def test_weights_over_row_and_tile_edges(seq_lens, hq, hkv, s_obs, causal, spike
         # and other seeds and spikes of 20 to 120 at most 2.4e-6 came out, 1.3e-6 with a running maximum in every tile)
         assert err.max() <= WEIGHT_RTOL, f"sequence {s}: {err.max():.2e}"
         np.testing.assert_allclose(w_ch[s * hkv:(s + 1) * hkv], O.channel_weights(Ks, _np(Q[s])), rtol=1e-5)
+
+
+# One launch fewer where no item has more than 30 runs (and the channel weights are not wanted): the same additions, so the same bits.
+@pytest.mark.parametrize("seq_lens,hq,hkv,s_obs", [
+    ((1,), 2, 2, 1),
+    ((1920, 33, 63, 64, 65, 1025), 2, 2, 32),    # 64 rows; 30 runs, 17
+    ((1024, 300), 8, 2, 32),                     # 128 rows; 16 runs
+    ((1921, 896), 8, 1, 32),                     # 256 rows; 31 runs: a launch of its own
+    ((1857, 896), 8, 1, 33),                     # 264 rows: a second sweep
+    ((500, 80), 16, 2, 64),                      # 512 rows
+    (tuple(7000 + 101 * k for k in range(8)), 8, 2, 32),      # 16 items that share 512 runs
+    (tuple(1500 + 101 * k for k in range(24)), 8, 2, 64),     # 48 items, runs that span two of them
+])
+def test_log_sum_exp_inside_the_second_pass(seq_lens, hq, hkv, s_obs):
+    print(f"[case] {seq_lens} hq {hq} hkv {hkv} s_obs {s_obs}", flush=True)
+    b, d = B(), 128
+    gen = torch.Generator().manual_seed(len(seq_lens) + hq)
+    K = torch.randn(sum(seq_lens) * hkv * d, generator=gen).to(torch.bfloat16).cuda()
+    Q = torch.randn((len(seq_lens), hq, s_obs, d), generator=gen).to(torch.bfloat16).cuda()
+    cfg = b.Config(seq_lens, hq, hkv, s_obs=s_obs)
+    w_tok, _ = b.rdkv_weights(cfg, K, Q)
+    assert torch.equal(w_tok, b.rdkv_weights(cfg, K, Q, want_channel=True)[0])

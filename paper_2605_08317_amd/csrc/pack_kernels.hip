@@ -761,13 +761,14 @@ __global__ __launch_bounds__(kRangeThreads) void k_channel_range_kernel(PackArgs
 // Metadata: per token group G and quantized step sq (4 slots) 4 fp16 scales then 4 fp16 offsets at fp16 index
 // 8 (G n_qsteps + sq).
 //
-// One thread = one slot of a word and one token group: its channel's 32 values in registers, quantized, the codes packed F
-// tokens to a register (F = 32 / b fields of a word).  The F lanes that hold a word's slots then exchange fields so that
-// lane f ends with the word of token f: a transposition of F x F fields in log2 F steps within a row of 16 lanes.  Every
-// tier starts at a row of lanes.  The words are staged in LDS and leave in 16-byte pieces.  Bound: instruction
-// issue; 160K rows 40 -> 32 us (a word put together field by field, each a channel number and a code out of LDS; and one
-// code path per width, of which a wavefront with slots of three tiers took all three) -> 30 (codes without conversions, all
-// positions loaded before the rows).
+// One workgroup = one token group of a tile, one thread = one slot of a word: its channel's 32 values in registers, quantized,
+// the codes packed F tokens to a register (F = 32 / b fields of a word).  The F lanes that hold a word's slots then exchange
+// fields so that lane f ends with the word of token f: a transposition of F x F fields in log2 F steps within a row of 16 lanes.
+// Every tier starts at a row of lanes.  The words are staged in LDS and leave in 16-byte pieces.  Bound: a workgroup's chain of
+// steps (rows, codes, words) and instruction issue; 160K rows 40 -> 32 us (a word put together field by field, each a channel
+// number and a code out of LDS; and one code path per width, of which a wavefront with slots of three tiers took all three) -> 30
+// (codes without conversions, all positions loaded before the rows) -> 24 (both groups of a tile in a workgroup before: half as
+// many to cover each other's chains; 8 % fewer vector instructions alone had changed nothing).
 // what lane ^ J holds (J = 1, 2, 4, 8, inside a row of 16)
 template <int J>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
@@ -799,29 +800,30 @@ __device__ __forceinline__ uint32_t transpose_fields(uint32_t v, int f) {
   return exchange_fields<B, 1>(v, f);
 }
 
-constexpr int kKThreads = 384;         // two token groups of at most 192 lanes
+constexpr int kKThreads = 192;         // the most lanes a token group has
 __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) {
-  constexpr int kRows = kTile64;
+  constexpr int kRows = kKTokenGroup;
   constexpr int kRowStride = kHeadDim + 8;
   constexpr int kRowBytes = kRows * kRowStride * 2, kWordBytes = kRows * kMaxKRowWords * 4;
-  __shared__ __align__(16) uint8_t s_buf[kRowBytes > kWordBytes ? kRowBytes : kWordBytes];   // bf16 rows, then the tile's words
-  __shared__ uint16_t s_sc[2][kHeadDim], s_of[2][kHeadDim];
+  static_assert(kTile64 == 2 * kRows, "two workgroups a tile");
+  __shared__ __align__(16) uint8_t s_buf[kRowBytes > kWordBytes ? kRowBytes : kWordBytes];   // bf16 rows, then the group's words
+  __shared__ uint16_t s_sc[kHeadDim], s_of[kHeadDim];
   __shared__ ItemK s_ik;
-  const int item = blockIdx.y;
-  const TileOf t(a, item, blockIdx.x);
+  const int item = blockIdx.y, G = blockIdx.x & 1;
+  const TileOf t(a, item, blockIdx.x >> 1);
   if (t.ti == 4) return;
-  const int valid = min(kRows, t.n - t.tile * kRows);
+  const int valid = min(kTile64, t.n - t.tile * kTile64), vg = min(max(valid - kRows * G, 0), kRows);     // rows of the tile, of the group
   const int tid = threadIdx.x;
   const int64_t* so = a.seg_off + (static_cast<int64_t>(item) * 4 + t.ti) * 4;
   uint16_t* s_rows = reinterpret_cast<uint16_t*>(s_buf);
   {
     const int64_t item_row = ItemOf(a.batch, item).off;
-    const int32_t* idx = a.tier_idx + item_row + t.before + static_cast<int64_t>(t.tile) * kRows;
+    const int32_t* idx = a.tier_idx + item_row + t.before + static_cast<int64_t>(t.tile) * kTile64;
     constexpr int kPieces = kRows * 16, kLoads = (kPieces + kKThreads - 1) / kKThreads;      // 16 bytes each
     uint4 v[kLoads];
-    int pos[kLoads];                     // all positions, then all rows (rows past the last repeat it and become zeros)
+    int pos[kLoads];                     // all positions, then all rows (rows past the segment's last repeat it and become zeros)
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) pos[i] = idx[min((i * kKThreads + tid) >> 4, valid - 1)];
+    for (int i = 0; i < kLoads; ++i) pos[i] = idx[min(kRows * G + ((i * kKThreads + tid) >> 4), valid - 1)];
 #pragma unroll
     for (int i = 0; i < kLoads; ++i)
       v[i] = *reinterpret_cast<const uint4*>(a.K + (item_row + pos[i]) * kHeadDim + (tid & 15) * 8);
@@ -831,7 +833,7 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
     for (int i = 0; i < kLoads; ++i) {
       const int p = i * kKThreads + tid;
       if (p < kPieces)
-        *reinterpret_cast<uint4*>(s_rows + (p >> 4) * kRowStride + (p & 15) * 8) = (p >> 4) < valid ? v[i] : make_uint4(0, 0, 0, 0);
+        *reinterpret_cast<uint4*>(s_rows + (p >> 4) * kRowStride + (p & 15) * 8) = (p >> 4) < vg ? v[i] : make_uint4(0, 0, 0, 0);
     }
   }
   __syncthreads();
@@ -844,16 +846,14 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
   for (int k = 0; k < 4; ++k)
     start[k + 1] = start[k] + (((s_ik.word_end[k] - (k > 0 ? s_ik.word_end[k - 1] : 0)) * (2 << k) + 15) & ~15);
   const int lanes = start[4];            // at most 192
-  const bool active = tid < 2 * lanes;
-  const int G = tid >= lanes ? 1 : 0, l = tid - G * lanes;
+  const bool active = tid < lanes;
   int tier = 0, local = 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k)
-    if (l >= start[k] && l < start[k + 1]) {
+    if (tid >= start[k] && tid < start[k + 1]) {
       tier = k;
-      local = l - start[k];
+      local = tid - start[k];
     }
-  const int rb = kKTokenGroup * G, vg = min(max(valid - rb, 0), kKTokenGroup);
   const int per_word = 2 << tier, f = local & (per_word - 1);
   const int first_word = tier > 0 ? s_ik.word_end[tier - 1] : 0, W = first_word + (local >> (tier + 1));
   const bool writes = active && W < s_ik.word_end[tier];
@@ -868,7 +868,7 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
   for (int r = 0; r < kKTokenGroup; ++r) x[r] = 0.f;
   if (c >= 0) {
 #pragma unroll
-    for (int r = 0; r < kKTokenGroup; ++r) x[r] = __uint_as_float(static_cast<uint32_t>(s_rows[(rb + r) * kRowStride + c]) << 16);
+    for (int r = 0; r < kKTokenGroup; ++r) x[r] = __uint_as_float(static_cast<uint32_t>(s_rows[r * kRowStride + c]) << 16);
     if (tier > 0) {                      // one path for all widths: a wavefront holds slots of several tiers
       uint16_t sc = 0, of = 0;
       if (vg > 0) {
@@ -915,11 +915,11 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
 #pragma unroll
         for (int r = 0; r < kKTokenGroup; ++r) x[r] = 0.f;
       }
-      s_sc[G][c] = sc;
-      s_of[G][c] = of;
+      s_sc[c] = sc;
+      s_of[c] = of;
     }
   }
-  uint32_t out[16];                      // words of tokens rb + F q + f
+  uint32_t out[16];                      // words of tokens F q + f
   const auto pack = [&](auto bits_c) __attribute__((always_inline)) {
     constexpr int B = decltype(bits_c)::value, F = 32 / B;
 #pragma unroll
@@ -945,13 +945,13 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
   __syncthreads();                       // the rows are used up: their memory takes the words
   uint32_t* s_words = reinterpret_cast<uint32_t*>(s_buf);
   const auto word_at = [&](int w, int r) __attribute__((always_inline)) {
-    return w < full ? 256 * (w >> 2) + 4 * r + (w & 3) : kRows * full + 2 * r + (w - full);
+    return w < full ? 4 * kRows * (w >> 2) + 4 * r + (w & 3) : kRows * full + 2 * r + (w - full);
   };
   if (writes) {
     const auto put = [&](auto bits_c) __attribute__((always_inline)) {
       constexpr int F = 32 / decltype(bits_c)::value;
 #pragma unroll
-      for (int q = 0; q < kKTokenGroup / F; ++q) s_words[word_at(W, rb + F * q + f)] = out[q];
+      for (int q = 0; q < kKTokenGroup / F; ++q) s_words[word_at(W, F * q + f)] = out[q];
     };
     if (tier == 3) put(std::integral_constant<int, 2>{});
     else if (tier == 2) put(std::integral_constant<int, 4>{});
@@ -961,33 +961,35 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
   if (nwp > s_ik.n_words && tid < kRows) s_words[word_at(s_ik.n_words, tid)] = 0;
   __syncthreads();
   uint4* dst = reinterpret_cast<uint4*>(a.arena + so[0] + static_cast<int64_t>(t.tile) * s_ik.kt_bytes);
-  for (int idx = tid; idx < 16 * nwp; idx += kKThreads) dst[idx] = reinterpret_cast<const uint4*>(s_words)[idx];
+  const int quads = kRows * (full >> 2);   // pieces of 16 bytes: a token's four words; behind them two tokens' last two
+  for (int idx = tid; idx < quads; idx += kKThreads)
+    dst[(idx / kRows) * kTile64 + kRows * G + idx % kRows] = reinterpret_cast<const uint4*>(s_words)[idx];
+  if (nwp > full && tid < kRows / 2) dst[2 * quads + (kRows / 2) * G + tid] = reinterpret_cast<const uint4*>(s_words)[quads + tid];
   // metadata; the segment's last tile also clears the bytes up to the next segment's alignment
-  const int nqs = s_ik.n_qsteps, n_tiles = (t.n + kRows - 1) / kRows;
+  const int nqs = s_ik.n_qsteps, n_tiles = (t.n + kTile64 - 1) / kTile64;
   const bool last = t.tile == n_tiles - 1;
   if (a.k_range) {   // one record for the whole segment, written by its first tile
     uint16_t* meta1 = reinterpret_cast<uint16_t*>(a.arena + so[1]);
     const int words = 8 * nqs, padded = (2 * words + kSegAlign - 1) / kSegAlign * (kSegAlign / 2);
-    if (t.tile == 0)
+    if (t.tile == 0 && G == 0)
       for (int idx = tid; idx < padded; idx += kKThreads) {
         uint16_t v = 0;
         if (idx < words) {
           const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * (idx >> 3) + (idx & 3)];
-          if (c >= 0) v = (idx >> 2) & 1 ? s_of[0][c] : s_sc[0][c];
+          if (c >= 0) v = (idx >> 2) & 1 ? s_of[c] : s_sc[c];
         }
         meta1[idx] = v;
       }
     return;
   }
-  uint16_t* meta = reinterpret_cast<uint16_t*>(a.arena + so[1] + static_cast<int64_t>(t.tile) * s_ik.km_bytes);
+  uint16_t* meta = reinterpret_cast<uint16_t*>(a.arena + so[1] + static_cast<int64_t>(t.tile) * s_ik.km_bytes) + 8 * nqs * G;
   const int64_t end = static_cast<int64_t>(n_tiles) * s_ik.km_bytes;
-  const int pad = last ? static_cast<int>((kSegAlign - end % kSegAlign) % kSegAlign) / 2 : 0;
-  for (int idx = tid; idx < 16 * nqs + pad; idx += kKThreads) {
+  const int pad = last && G == 1 ? static_cast<int>((kSegAlign - end % kSegAlign) % kSegAlign) / 2 : 0;
+  for (int idx = tid; idx < 8 * nqs + pad; idx += kKThreads) {
     uint16_t v = 0;
-    if (idx < 16 * nqs) {
-      const int G = idx / (8 * nqs), rem = idx - G * 8 * nqs;
-      const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * (rem >> 3) + (rem & 3)];
-      if (c >= 0) v = (rem >> 2) & 1 ? s_of[G][c] : s_sc[G][c];
+    if (idx < 8 * nqs) {
+      const int c = s_ik.slot_ch[s_ik.slot_base[1] + 4 * (idx >> 3) + (idx & 3)];
+      if (c >= 0) v = (idx >> 2) & 1 ? s_of[c] : s_sc[c];
     }
     meta[idx] = v;
   }
@@ -1019,7 +1021,7 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
   const int n_items = plan.n_items, extra = (copy.first[copy.n] + n_items - 1) / n_items;
   const PackArgs a{K, V, tier_idx, tier_idx_out, plan.idx_base, plan.counts, plan.seg_off, arena, plan.items_k,
                    k_range, row_wide, extra, copy, batch};
-  const dim3 grid(max_tiles, n_items), with_copies(max_tiles + extra, n_items), block(256);
+  const dim3 with_copies(max_tiles + extra, n_items), block(256);
   if (plan.items_k == nullptr) {
     hipLaunchKernelGGL(pack_tile_kernel<false>, with_copies, block, 0, st, a);
     return hipGetLastError();
@@ -1029,7 +1031,7 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
     const int parts = std::min(std::max(512 / n_items, 16), 128), most = (max_tiles * kTile64 + kRangeRows - 1) / kRangeRows;
     hipLaunchKernelGGL(k_channel_range_kernel, dim3(std::max(1, std::min(parts, most)), n_items), dim3(kRangeThreads), 0, st, a);
   }
-  hipLaunchKernelGGL(pack_k_mixed_kernel, grid, dim3(kKThreads), 0, st, a);
+  hipLaunchKernelGGL(pack_k_mixed_kernel, dim3(2 * max_tiles, n_items), dim3(kKThreads), 0, st, a);
   hipLaunchKernelGGL(pack_tile_kernel<true>, with_copies, block, 0, st, a);
   return hipGetLastError();
 }

@@ -234,3 +234,26 @@ def test_k_rows_longer_than_64_words(name, kw, counts):
     ref_out, ref_lse = O.decode(ref, _np(inp["q"]))
     _check_decode(out, lse, ref_out, ref_lse)
     cache.free()
+
+
+# A workgroup packs one of a tile's two token groups: segments that end at and around a group's and a tile's edge, rows of every
+# width with and without a last pair of words, in memory that held another cache (what is padding has to be cleared).
+@pytest.mark.parametrize("per_channel_scale", [False, True])
+@pytest.mark.parametrize("rows,channels", [(1, (3, 21, 40, 60)), (31, (0, 0, 43, 85)), (32, (0, 1, 0, 0)), (33, (128, 0, 0, 0)),
+                                           (63, (5, 0, 9, 100)), (64, (0, 0, 0, 128)), (65, (1, 30, 30, 67)), (97, (0, 128, 0, 0))])
+def test_token_groups_at_a_segments_end(rows, channels, per_channel_scale):
+    print(f"[case] rows {rows} channels {channels} per_channel_scale {per_channel_scale}", flush=True)
+    b = B()
+    wl, inp, dev = _inputs("tiny", seq_lens=(4 * rows + 70,))
+    rng = np.random.default_rng(rows)
+    T, hkv = inp["seq_lens"][0], wl.hkv
+    tok = np.zeros(T, np.uint8)
+    tok[:4 * rows] = np.repeat([16, 8, 4, 2], rows)
+    ch = np.zeros(128, np.uint8)
+    ch[:sum(channels)] = np.repeat([16, 8, 4, 2], channels)
+    bt = [np.stack([rng.permutation(tok) for _ in range(hkv)])]
+    bc = [np.stack([rng.permutation(ch) for _ in range(hkv)])]
+    other, _ = _pack_both_mixed(b, wl, inp, dev, [np.full_like(bt[0], 8)], [np.full_like(bc[0], 8)])
+    other.free()
+    cache, ref = _pack_both_mixed(b, wl, inp, dev, bt, bc, per_channel_scale)
+    _assert_cache_equal_mixed(b, cache, ref)

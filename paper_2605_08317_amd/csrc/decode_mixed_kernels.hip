@@ -287,20 +287,20 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
       const uint8_t* wt8 = wt - t16 * (HS * 64);
       const uint8_t* wt4 = wt + ((t8 - t16) - 2 * t8) * (HS * 64);
       const uint8_t* wt2 = wt + ((t8 - t16) + 2 * (t4 - t8) - 4 * t4) * (HS * 64);
-      uint4 cur[HS], nxt[HS];
+      uint4 wq[2][HS];      // group n in wq[n % 2], the next one on its way into the other
 #pragma unroll
-      for (int hs = 0; hs < HS; ++hs) cur[hs] = nxt[hs] = make_uint4(0, 0, 0, 0);
+      for (int hs = 0; hs < HS; ++hs) wq[0][hs] = wq[1][hs] = make_uint4(0, 0, 0, 0);
       auto read_group = [&](uint4 (&dst)[HS], const uint8_t* o) __attribute__((always_inline)) {
 #pragma unroll
         for (int hs = 0; hs < HS; ++hs) dst[hs] = *reinterpret_cast<const uint4*>(o + hs * 64);
       };
-      // before a tier's words [first, ..): spw steps per word, groups of wpg = 4 / spw words
-      auto enter_tier = [&](const uint8_t* t, int first, int spw) __attribute__((always_inline)) {
-        const int wpg = 4 / spw, fa = first & ~(wpg - 1);
-        if (spw != 4) read_group(cur, t + spw * fa * (HS * 64));
-        read_group(nxt, t + spw * (fa == first ? first : fa + wpg) * (HS * 64));
+      // before a tier's words [first, ..), wpg words per group: the first word's group and the one behind it
+      auto enter_tier = [&](const uint8_t* t, int first, int wpg) __attribute__((always_inline)) {
+        const int n = first / wpg;
+        read_group(wq[0], t + 4 * (n + (n & 1)) * (HS * 64));
+        read_group(wq[1], t + 4 * (n | 1) * (HS * 64));
       };
-      auto qstep = [&](const Pack4& b, auto ab) __attribute__((always_inline)) {
+      auto qstep = [&](const Pack4& b, const uint4 (&cur)[HS], auto ab) __attribute__((always_inline)) {
 #pragma unroll
         for (int hs = 0; hs < HS; ++hs) {
           Pack4 ah, al;
@@ -309,11 +309,6 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
           aqh[hs] = __builtin_amdgcn_mfma_f32_4x4x4f16(ah.h, b.h, aqh[hs], 2, decltype(ab)::value, 0);
           aql[hs] = __builtin_amdgcn_mfma_f32_4x4x4f16(al.h, b.h, aql[hs], 2, decltype(ab)::value, 0);
         }
-      };
-      auto next_group = [&](const uint8_t* o) __attribute__((always_inline)) {
-#pragma unroll
-        for (int hs = 0; hs < HS; ++hs) cur[hs] = nxt[hs];
-        read_group(nxt, o);
       };
       // one word of each tier; the word index is a compile-time constant (registers cannot be indexed at run time)
       uint2 q16[HS];
@@ -339,35 +334,38 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
       };
       auto body8 = [&](auto wc) __attribute__((always_inline)) {
         constexpr int w = decltype(wc)::value;
-        if constexpr ((w & 3) == 0) next_group(wt8 + (w + 4) * (HS * 64));
+        constexpr int n = (w >> 2) & 1;
+        if constexpr ((w & 3) == 0) read_group(wq[1 - n], wt8 + (w + 4) * (HS * 64));
         Pack4 b;
         b.u[0] = __builtin_amdgcn_perm(0u, kw[w], 0x0C020C00u);
         b.u[1] = __builtin_amdgcn_perm(0u, kw[w], 0x0C030C01u);
-        qstep(b, GroupIndex<(w & 3)>{});
+        qstep(b, wq[n], GroupIndex<(w & 3)>{});
       };
       auto body4 = [&](auto wc) __attribute__((always_inline)) {
         constexpr int w = decltype(wc)::value;
-        if constexpr ((w & 1) == 0) next_group(wt4 + 2 * (w + 2) * (HS * 64));
+        constexpr int n = (w >> 1) & 1;
+        if constexpr ((w & 1) == 0) read_group(wq[1 - n], wt4 + 2 * (w + 2) * (HS * 64));
         const uint32_t c0 = kw[w], c1 = c0 >> 8;
         Pack4 b;
         b.u[0] = c0 & 0x000F000Fu; b.u[1] = c0 & 0x00F000F0u;
-        qstep(b, GroupIndex<(2 * w & 3)>{});
+        qstep(b, wq[n], GroupIndex<(2 * w & 3)>{});
         b.u[0] = c1 & 0x000F000Fu; b.u[1] = c1 & 0x00F000F0u;
-        qstep(b, GroupIndex<(2 * w & 3) + 1>{});
+        qstep(b, wq[n], GroupIndex<(2 * w & 3) + 1>{});
       };
       auto body2 = [&](auto wc) __attribute__((always_inline)) {
         constexpr int w = decltype(wc)::value;
-        next_group(wt2 + 4 * (w + 1) * (HS * 64));
+        constexpr int n = w & 1;
+        read_group(wq[1 - n], wt2 + 4 * (w + 1) * (HS * 64));
         const uint32_t c0 = kw[w], c1 = c0 >> 6, c2 = c0 >> 12;
         Pack4 b;
         b.u[0] = c0 & 0x00030003u; b.u[1] = c0 & 0x000C000Cu;     // fields 0, 1
-        qstep(b, GroupIndex<0>{});
+        qstep(b, wq[n], GroupIndex<0>{});
         b.u[0] = c0 & 0x00300030u; b.u[1] = c1 & 0x00030003u;     // fields 2, 3
-        qstep(b, GroupIndex<1>{});
+        qstep(b, wq[n], GroupIndex<1>{});
         b.u[0] = c1 & 0x000C000Cu; b.u[1] = c1 & 0x00300030u;     // fields 4, 5
-        qstep(b, GroupIndex<2>{});
+        qstep(b, wq[n], GroupIndex<2>{});
         b.u[0] = c2 & 0x00030003u; b.u[1] = c2 & 0x000C000Cu;     // fields 6, 7
-        qstep(b, GroupIndex<3>{});
+        qstep(b, wq[n], GroupIndex<3>{});
       };
       // A tier is a run of consecutive words [first, end): jump to its first word and fall through word by word
       // until the end (one uniform comparison per word; a test of every word against every tier costs several
@@ -391,7 +389,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
   }
       RDKV_K_TIER(body16, 0, t16)
       if (t16 < t8) {
-        enter_tier(wt8, t16, 1);
+        enter_tier(wt8, t16, 4);
         RDKV_K_TIER(body8, t16, t8)
       }
       if (t8 < t4) {
@@ -399,7 +397,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
         RDKV_K_TIER(body4, t8, t4)
       }
       if (t4 < t2) {
-        enter_tier(wt2, t4, 4);
+        enter_tier(wt2, t4, 1);
         RDKV_K_TIER(body2, t4, t2)
       }
 #undef RDKV_K_TIER

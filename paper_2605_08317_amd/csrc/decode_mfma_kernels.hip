@@ -68,8 +68,7 @@ __device__ __forceinline__ void process_tiles(const uint8_t* __restrict__ kd, co
   auto load_k = [&](Regs& r, int t) __attribute__((always_inline)) {
     load_tile_side<TIER>(r.k, kd, t, lane);
     r.kmeta = *reinterpret_cast<const uint4*>(km + static_cast<int64_t>(t) * 1024 + lane * 16);
-    // lane (block, j) fetches group j's V scales and offsets of tokens 4 blk + 0..3; the quad shares them below.  (The softmax
-    // asks for them, so they go ahead of the V codes.)
+    // lane (block, j) fetches group j's V scales and offsets of tokens 4 blk + 0..3; the quad shares them below.
     if constexpr (kShare) r.vmeta = *reinterpret_cast<const uint4*>(vm + static_cast<int64_t>(t) * 1024 + lane * 16);
   };
   auto load_v = [&](Regs& r, int t) __attribute__((always_inline)) {
@@ -182,7 +181,7 @@ __device__ __forceinline__ void process_tiles(const uint8_t* __restrict__ kd, co
     to_head_lanes<HS, HS == 2>(xt, j, x);
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
-    softmax_tile<HS, true>(x, run, p, lk, wide_scales(r.vmeta));
+    softmax_tile<HS>(x, run, p, lk);
     if constexpr (kShare) pv_tile<TIER, HS>(r.k, r.vmeta, p, run); else pv_tile<TIER, HS>(r.v, r.vmeta, p, run);
     if (more) {               // V registers are free again
       if constexpr (kShare) load_k(r, next); else load_v(r, next);
@@ -236,7 +235,7 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
     run.init();                                                                                                   \
     process_tiles<TIER_, HS, NWV, ROOMY>(arena + ch.k_data, arena + ch.k_meta, arena + ch.v_data, arena + ch.v_meta,     \
                                   ch.rows, g, qp, run);                                                           \
-    state = finish_chunk<HS, false, NWV, LOOK, true>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                           \
+    state = finish_chunk<HS, false, NWV, LOOK>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);                           \
   }
     switch (ch.tier) {
       case 16:                  // (launches without 16-bit chunks get less LDS)
@@ -273,7 +272,7 @@ __global__ __launch_bounds__(NWV * 64, ROOMY ? 2 : HS == 1 ? 4 : 3) void decode_
   RDKV_PIECE(8)
 #undef RDKV_PIECE
   // ---- undo the subnormal unit, add the offsets, merge the wavefronts, hand the partial over -------------------
-  finish_chunk<HS, false, NWV, LOOK, true>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);
+  finish_chunk<HS, false, NWV, LOOK>(run, 16777216.0f, 0.f, g, s_ml, s_acc, ma, co);
 }
 
 template <int HS, int NWV, bool MULTI, bool ROOMY, bool LOOK>

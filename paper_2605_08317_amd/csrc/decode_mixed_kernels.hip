@@ -419,7 +419,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
 
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
-    softmax_tile<HS, VT != 16>(x, run, p, lk, VT != 16 && wide_scales(vmeta));
+    softmax_tile<HS>(x, run, p, lk);
 
     // ---- P V ------------------------------------------------------------------------------------------------
     if constexpr (VT == 16) {
@@ -468,7 +468,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
     }
   }
 
-  return finish_chunk<HS, true, NWV, LOOK, VT != 16>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
+  return finish_chunk<HS, true, NWV, LOOK>(run, VT == 16 ? 1.0f : 16777216.0f, lk, g, reinterpret_cast<float*>(smem),
                                  reinterpret_cast<float*>(smem) + ml_lds_floats(NWV, HS), ma, co);
 }
 

@@ -122,7 +122,7 @@ __device__ __forceinline__ uint32_t process_rows_mfma(const uint8_t* __restrict_
     to_head_lanes<HS, HS == 2>(xt, j, x);
     mask_rows<HS>(x, tile, rows, blk);
     float p[HS][4];
-    softmax_tile<HS, false>(x, run, p);
+    softmax_tile<HS>(x, run, p);
     short4v phi[HS], plo[HS];
 #pragma unroll
     for (int hs = 0; hs < HS; ++hs) split_bf16(p[hs], phi[hs], plo[hs]);
@@ -146,7 +146,7 @@ __device__ __forceinline__ uint32_t process_rows_mfma(const uint8_t* __restrict_
   for (int hs = 0; hs < HS; ++hs) {
     if (lane < 16)        // (block, j) -> group block of head j; log2 domain from here on
       *reinterpret_cast<float4*>(s_ml + ml_at<HS>(wave, 4 * hs + (lane & 3), lane >> 2)) =
-          make_float4(reported_max<false>(run.top[hs]), run.l[hs], 0.f, 0.f);
+          make_float4(run.m[hs] * kXScale - kPExp, run.l[hs], 0.f, 0.f);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int head = 4 * hs + i;

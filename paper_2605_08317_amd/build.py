@@ -10,14 +10,20 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librdkv.so")
 CALL = os.path.join(HERE, "_rdkv_call.so")
-# Branches that every lane takes alike stay branches: by default the compiler makes flags and flow blocks of them (in the walk over
-# a channel-wise row's words three instructions, a wait and two jumps per word, and 20 registers).  One 64K sequence channel-wise
-# 14.5 -> 13.1 us, 16 with one scale per channel 73.4 -> 70.0, a layer of 16 MB token-wise 9.3 -> 8.7, 16 ragged sequences with 8
-# query heads 43.0 -> 42.0, the search 0.4 % of a pass.  The other kernels gain nothing (rows, packing) or spill (weights).
-UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
-# The scheduler counts live registers by the target's own trackers: the second weights pass, which has all 256, no longer keeps
-# eight in memory across its loop (8 heads x 128K keys 79 -> 75.5 us, 128 heads x 20K keys 188 -> 178).  The other files' kernels
-# come out the same.
+# The decode kernels are a walk over tiers, words and pieces whose conditions are the same for all lanes: numbers of a chunk, the
+# grid's index, the wavefront's number.  By default the compiler's structurizer turns regions of such branches into flags and flow
+# blocks too (per word of a channel-wise row three instructions, a wait, two jumps, and 20 registers in all).  The first option
+# lets it leave a region as it is whose branches its uniformity analysis has proved uniform -- an analysis that takes a value it
+# cannot prove for divergent --, the second takes back the exception for regions around a divergent one: a region with a single
+# branch that lanes may take differently, at any depth, is structurized as ever.  (The outputs are
+# the same bit for bit without the options.  One 64K sequence channel-wise 13.8 -> 12.1 us, 16 with one scale per channel 74.9 ->
+# 68.6, 16 ragged ones token-wise 42.8 -> 41.6, 8 layers of 16K tokens 76.4 -> 75.0, launches bound by HBM 0 to 0.5 %.  The search
+# and the packing gain nothing, the weights spill.)
+UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions", "-mllvm", "-structurizecfg-relaxed-uniform-regions=false"]
+# The scheduler counts live registers by the target's own trackers (only an estimate of pressure: which instruction order it
+# prefers): the second weights pass, which has all 256, no longer keeps eight values in memory across its loop, for 32 instead of
+# 11 scalars in lanes of a vector register (8 heads x 128K keys 79.2 -> 77.4 us, 128 heads x 20K keys 199 -> 188).  The other files'
+# kernels come out the same.
 EXACT_PRESSURE = ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"]
 # (source, object, extra flags); the mixed-mode decode kernels are compiled once per head-set count and row length
 # class so that their many instantiations build in parallel; the slowest objects come first
@@ -32,7 +38,7 @@ SOURCES = [
     ("decode_kernels.hip", "decode_kernels.o", []),
     ("copy_kernels.hip", "copy_kernels.o", []),
     ("pack_kernels.hip", "pack_kernels.o", []),
-    ("allocate_kernels.hip", "allocate_kernels.o", UNIFORM),
+    ("allocate_kernels.hip", "allocate_kernels.o", []),
     # (its copies into LDS set m0, a reserved register, and say so)
     ("weights_kernels.hip", "weights_kernels.o", ["-Wno-inline-asm"] + EXACT_PRESSURE),
     ("calib_kernels.hip", "calib_kernels.o", []),

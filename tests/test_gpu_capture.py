@@ -20,18 +20,21 @@ def _batch(batch, hkv, T, s_obs, seed):
 
 
 @pytest.mark.parametrize("mixed", [False, True])
-@pytest.mark.parametrize("batch,T", [(2, 700), (90, 64), (4000, 33)])   # a table of one launch, of several, larger than the ring
-def test_replays_of_the_staged_calls(batch, T, mixed):
-    b, hkv = B(), 8
-    print(f"[case] captured weights and allocation, {batch} x {T}, channel-wise {mixed}", flush=True)
-    K, Q = _batch(batch, hkv, T, 32, batch)
+# 32 bytes a sequence: along with each launch up to 32 sequences; then a table, which a graph takes 3 KB a launch: one launch, three,
+# 42; and beyond half the staging ring (1 MB), where an eager call has memory of its own that it waits for and gives back
+@pytest.mark.parametrize("batch,hkv,T,s_obs", [(2, 8, 700, 32), (32, 2, 64, 32), (33, 2, 64, 32), (90, 8, 64, 32), (200, 2, 64, 32),
+                                               (4000, 8, 33, 32), (33000, 1, 9, 4)])
+def test_replays_of_the_staged_calls(batch, hkv, T, s_obs, mixed):
+    b = B()
+    print(f"[case] captured weights and allocation, {batch} x {T}, {hkv} heads, channel-wise {mixed}", flush=True)
+    K, Q = _batch(batch, hkv, T, s_obs, batch)
     budgets = [0.5 + s % 4 for s in range(batch)]
-    cfg = b.Config([T] * batch, hkv, hkv, budget_bits=budgets, s_obs=32, **b.torch_allocator_hooks(),
+    cfg = b.Config([T] * batch, hkv, hkv, budget_bits=budgets, s_obs=s_obs, **b.torch_allocator_hooks(),
                    **({"k_mode": b.RDKV_K_CHANNELWISE} if mixed else {}))
     # unrelated work whose tables go once round the ring between two replays
     other_batch = 1100
-    oK, oQ = _batch(other_batch, hkv, 40, 32, 7)
-    other = b.Config([40] * other_batch, hkv, hkv, budget_bits=[2.0] * other_batch, s_obs=32, **b.torch_allocator_hooks())
+    oK, oQ = _batch(other_batch, 8, 40, 32, 7)
+    other = b.Config([40] * other_batch, 8, 8, budget_bits=[2.0] * other_batch, s_obs=32, **b.torch_allocator_hooks())
     oq = oQ[:, :, 0].contiguous()
 
     def unrelated():

@@ -153,18 +153,12 @@ __device__ __forceinline__ void plan_part(const ScatterArgs& a) {
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) cnt[k] = group_sum(cnt[k], lanes);
-    // segments K data, K metadata, V data, V metadata, in units of kSegAlign bytes
-    static_assert(kSegAlign == 256, "a 64-row tile of b-bit rows takes 4 b units, its metadata 4, a tile of channel-wise K a word per unit");
-    uint64_t size[4][4], units = 0;
+    SegmentUnits size[4];
+    uint64_t units = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const uint64_t tiles = (cnt[k] + kTile64 - 1) / kTile64;
-      size[k][2] = tiles * (4u * (16 >> k));
-      size[k][3] = k == 0 ? 0ull : tiles * 4u;
-      size[k][0] = p.bits_ch ? tiles * words : size[k][2];
-      const uint64_t meta = p.per_unit ? (cnt[k] > 0 ? 16u * steps : 0u) : tiles * (32u * steps);
-      size[k][1] = p.bits_ch ? (meta + kSegAlign - 1) / kSegAlign : size[k][3];
-      units += (size[k][0] + size[k][1]) + (size[k][2] + size[k][3]);
+      size[k] = segment_units(k, cnt[k], p.bits_ch != nullptr, static_cast<int>(words), static_cast<int>(steps), p.per_unit != 0);
+      units += (size[k].k_data + size[k].k_meta) + (size[k].v_data + size[k].v_meta);
     }
     const uint32_t kept = cnt[0] + cnt[1] + cnt[2] + cnt[3];
     const uint64_t own_u = in && sub == 0 ? units : 0ull, own_k = in && sub == 0 ? kept : 0ull;
@@ -188,10 +182,11 @@ __device__ __forceinline__ void plan_part(const ScatterArgs& a) {
         p.counts[item * 4 + k] = static_cast<int32_t>(cnt[k]);
         p.idx_base[item * 4 + k] = static_cast<int64_t>(at);
         at += cnt[k];
+        const uint64_t own[4] = {size[k].k_data, size[k].k_meta, size[k].v_data, size[k].v_meta};
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           p.seg_off[(static_cast<int64_t>(item) * 4 + k) * 4 + g] = static_cast<int64_t>(u * kSegAlign);
-          u += size[k][g];
+          u += own[g];
         }
       }
     }
@@ -229,8 +224,8 @@ __device__ __forceinline__ void layout_part(const PlanArgs& p, int item) {
     out->n_words = static_cast<int16_t>(words);
     out->n_words_padded = static_cast<int16_t>((words + 1) & ~1u);
     out->n_qsteps = static_cast<int16_t>(steps);
-    out->kt_bytes = 256 * static_cast<int32_t>((words + 1) & ~1u);
-    out->km_bytes = 32 * static_cast<int32_t>(steps);
+    out->kt_bytes = k_tile_bytes(static_cast<int>((words + 1) & ~1u));
+    out->km_bytes = k_meta_bytes(static_cast<int>(steps));
   }
 }
 

@@ -744,8 +744,8 @@ ItemK make_item_k(const uint8_t* bits_ch) {
   k.n_qsteps = static_cast<int16_t>(qsteps);
   k.n_words = static_cast<int16_t>(words);
   k.n_words_padded = static_cast<int16_t>((words + 1) / 2 * 2);
-  k.kt_bytes = 256 * k.n_words_padded;
-  k.km_bytes = 32 * k.n_qsteps;
+  k.kt_bytes = k_tile_bytes(k.n_words_padded);
+  k.km_bytes = k_meta_bytes(k.n_qsteps);
   for (int j = slot; j < kMaxSlots; ++j) k.slot_ch[j] = -1;
   return k;
 }
@@ -1012,18 +1012,12 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       kept += cnt;
       tiles += static_cast<int>((cnt + kTile64 - 1) / kTile64);
       max_tiles = std::max(max_tiles, tiles);
-      const int64_t npad = round_up(cnt, kTile64);
-      int64_t sizes[4] = {npad * tier_row_bytes(bits), npad * tier_meta_bytes(bits),
-                          npad * tier_row_bytes(bits), npad * tier_meta_bytes(bits)};
-      if (mixed) {   // the K segments hold the channel-wise tiles of this tier's tokens
-        sizes[0] = npad / kTile64 * c->items_k[i].kt_bytes;
-        sizes[1] = c->k_per_unit ? (cnt > 0 ? c->items_k[i].km_bytes / 2 : 0)      // one record per segment
-                                 : npad / kTile64 * c->items_k[i].km_bytes;
-      }
+      const SegmentUnits u = mixed ? segment_units(ti, static_cast<uint64_t>(cnt), true, c->items_k[i].n_words_padded, c->items_k[i].n_qsteps, c->k_per_unit)
+                                   : segment_units(ti, static_cast<uint64_t>(cnt), false, 0, 0, false);
+      const uint64_t sizes[4] = {u.k_data, u.k_meta, u.v_data, u.v_meta};
       for (int si = 0; si < 4; ++si) {
-        cur = round_up(cur, kSegAlign);
         c->seg_off[(i * 4 + ti) * 4 + si] = cur;
-        cur += sizes[si];
+        cur += static_cast<int64_t>(sizes[si]) * kSegAlign;
       }
       if (mixed) {
         const int64_t groups = c->k_per_unit ? (cnt > 0 ? 1 : 0) : (cnt + kKTokenGroup - 1) / kKTokenGroup;
@@ -1034,7 +1028,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       }
     }
   }
-  c->arena_bytes = round_up(cur, kSegAlign);
+  c->arena_bytes = cur;
   c->kept_total = kept;
   c->stored_bytes = stored;
 

@@ -120,6 +120,33 @@ __host__ __device__ inline uint32_t k_tier_slots(int ti, uint32_t n) {
   const uint32_t pad = ti == 0 ? 4u : 2u << ti;
   return (n + pad - 1u) & ~(pad - 1u);
 }
+// Bytes of a 64-row tile of channel-wise K: its codes (words: of a row, padded to an even number), its scales and offsets (steps:
+// quantized steps of four slots; a record per group of kKTokenGroup rows).
+__host__ __device__ inline int32_t k_tile_bytes(int words) { return 4 * kTile64 * words; }
+__host__ __device__ inline int32_t k_meta_bytes(int steps) { return kTile64 / kKTokenGroup * 16 * steps; }
+// Sizes of the four segments of a tier of an item -- K codes, K scales and offsets, V codes, V scales and offsets, one behind the
+// other in the arena -- in units of kSegAlign bytes.  The host's plan (the chunk table, the arena's size) and the device's (where the
+// packing kernels write) both come from here.  words, steps: of a channel-wise K row; token-wise K: words 0.
+struct SegmentUnits { uint64_t k_data, k_meta, v_data, v_meta; };
+__host__ __device__ inline SegmentUnits segment_units(int ti, uint64_t rows, bool channelwise, int words, int steps, bool per_unit) {
+  const int bits = 16 >> ti;
+  const uint64_t tiles = (rows + kTile64 - 1) / kTile64;
+  static_assert(kTile64 * kHeadDim / 8 % kSegAlign == 0 && kTile64 * kGroupsPerRow * 4 % kSegAlign == 0 && 4 * kTile64 % kSegAlign == 0,
+                "whole units a tile");
+  SegmentUnits u;
+  u.v_data = tiles * static_cast<uint32_t>(kTile64 * tier_row_bytes(bits) / kSegAlign);
+  u.v_meta = tiles * static_cast<uint32_t>(kTile64 * tier_meta_bytes(bits) / kSegAlign);
+  if (!channelwise) {
+    u.k_data = u.v_data;
+    u.k_meta = u.v_meta;
+    return u;
+  }
+  u.k_data = tiles * static_cast<uint32_t>(k_tile_bytes(words) / kSegAlign);
+  const uint64_t meta = per_unit ? (rows > 0 ? static_cast<uint32_t>(k_meta_bytes(steps) / (kTile64 / kKTokenGroup)) : 0u)      // one record
+                                 : tiles * static_cast<uint32_t>(k_meta_bytes(steps));
+  u.k_meta = (meta + kSegAlign - 1) / kSegAlign;
+  return u;
+}
 // Device tables that one workgroup of the launch with the position lists makes for the packing kernels, so that these wait for
 // nothing that the host makes.
 struct PlanArgs {

@@ -487,9 +487,9 @@ __device__ __forceinline__ void pool_any(const AllocArgs& a, const float* w, flo
 // ---- one workgroup per item: up to 1024 REG units in registers ------------------------------------------------------
 // Thread t holds units 4096 j + 4 t .. + 3, so four wavefronts make one block of the per-block counts.  What bounds it:
 // one compute unit works on an item, through the latency of its loads and about fifteen barriers and then the number of
-// instructions per unit and pass (load, histogram, gather, write).  Measured against fp64
-// comparisons and one step at a time: 4K units 31 -> 8.4 us, 32K units (94 us in five kernels) -> 24 us, both with the
-// counting kernels (10 us) gone.
+// instructions per unit and pass (load, histogram, gather, write).  Measured against fp64 comparisons and one step at a time: 4K
+// units 31 -> 8.4 us, 32K units (94 us in five kernels) -> 24 us, both with the counting kernels (10 us) gone; with the pooling,
+// which had a launch of its own, 9.5 and 28.
 constexpr int kItemListCap = 24576;        // units of open buckets in LDS (96 KB beside 34 KB of histogram)
 template <int REG>
 constexpr size_t kItemLds = Anchored::kWords * sizeof(int) + (REG == 4 ? kWaves * sizeof(int4) : kItemListCap * sizeof(float));
@@ -594,7 +594,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
       if (S.done || S.it >= P.max_iters) break;
       // the histogram cannot decide the next step
       // Up to 4K units the other steps are taken on all of them, 0.3 us each: finding the open buckets, the list and its few
-      // units' steps took 4.2 us (4K units 11.8 -> 8.4 us in all, 64 units and 64 steps 16 -> 12).  With 32 units per thread a
+      // units' steps took 4.2 us (4K units without the pooling 11.8 -> 8.4 us in all, 64 units and 64 steps 16 -> 12).  With 32 units per thread a
       // step costs 2 us: two such steps in front of the list 25 -> 36 us.
       if constexpr (REG == 4) {
         int parity = 0;
@@ -910,9 +910,9 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
     if (s_hist[hist_slot(i)] != 0) atomicAdd(gh + i, s_hist[hist_slot(i)]);
 }
 
-// Every slice takes the steps the histogram decides for itself (the last workgroup of the kernel before did, for all: it waited
-// for the others' sums and its state went through memory: hist 13.3 + gather 10.5 us at 8 x 128K units, now 6.5 + 15.6), then appends its units of open
-// buckets to the item's list; the last one takes the other steps.
+// Every slice takes the steps the histogram decides for itself (the last workgroup of the kernel before did, for all: it waited for
+// the others' sums and its state went through memory: hist 13.3 + gather 10.5 us at 8 x 128K units, now 6.5 + 15.6), then appends
+// its units of open buckets to the item's list; the last one takes the other steps.
 constexpr size_t kGatherLds = Anchored::kWords * sizeof(int) + kListCap * sizeof(float);
 __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   extern __shared__ __align__(16) unsigned char smem[];

@@ -845,9 +845,9 @@ rdkv_status weights_impl(const rdkv_config* cfg, const Items& it, const Tables& 
   return RDKV_OK;
 }
 
-// Stages 2-3 of Alg. 1; everything is enqueued on st, nothing waits.  raw: weights that are still to be pooled into w_tok, or null.  lam / iters: device [items] (token map), in
-// channel-wise mode followed by [items] for the channel map; or null.  blk_counts: device [blocks][4] for the packing
-// stage (kept tokens of every block of an item per tier), or null.
+// Stages 2-3 of Alg. 1; everything is enqueued on st, nothing waits.  raw: weights that are still to be pooled into w_tok, or null.
+// lam / iters: device [items] (token map), in channel-wise mode followed by [items] for the channel map; or null.
+// blk_counts: device [blocks][4] for the packing stage (kept tokens of every block of an item per tier), or null.
 rdkv_status allocate_impl(const rdkv_config* cfg, const Items& it, const Tables& tb, const float* raw, float* w_tok,
                           const float* w_ch, uint8_t* bits_tok, uint8_t* bits_ch, double* lam, int32_t* iters,
                           int32_t* blk_counts, Temp& tmp, hipStream_t st) {
@@ -1038,8 +1038,11 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // as many chunks as the chip keeps resident (256 compute units x 2 workgroups of eight wavefronts = 512), never a
   // few more (measured on 4 x 128K tokens of 2-bit rows: 512 chunks 4.9 TB/s, 608 chunks 4.4, 2048 chunks 4.2).
   // Small launches are bound by latencies instead and are cut by rows (below); what is cut by bytes has chunks of at least
-  // 96 KB.  Kernels with four-wavefront workgroups (8 query heads per KV head, channel-wise K) keep three workgroups per
-  // compute unit resident: 768 chunks of at least 48 KB.
+  // 96 KB.  Four-wavefront workgroups (8 query heads per KV head, channel-wise K) are cut into 768 chunks of at least 48 KB, three per
+  // compute unit.  That is what the token-wise kernel keeps resident (157 registers).  Of the channel-wise ones, by their registers, a
+  // compute unit has room for four with K rows of up to 16 words and one head set (126; and for two of eight wavefronts, where 256
+  // in all are cut for), three up to 32 words (142), two with longer rows or two head sets (169 to 225); 768 was chosen when the first
+  // of these had room for three, and other numbers have not been measured since.
   // channel-wise mode: eight-wavefront workgroups when the launch is small (one workgroup per compute unit holds
   // it) and the kernel has such an instantiation (up to 4 query heads per KV head, K rows of up to 32 words)
   const bool mixed_wide = mixed && g <= 4 && c->max_k_words <= 32 && stored < (static_cast<int64_t>(48) << 20);
@@ -1071,8 +1074,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // chunk adds to the launch and each partial to the merge of its item.  A launch of at most 256 chunks has one workgroup per
   // compute unit and looks for its partials (or, with many query heads, counts: merge_parts); a larger one counts arrivals and
   // shares its compute units.  Against both stands the cut by bytes below, whose time goes with the bytes.  Fitted to 314
-  // token-wise launches (2 to 64 items, 1 to 192 MB, up to 60 % 8-bit rows, caches cold).  244 others (1 to 128 items of even and uneven lengths, 0.5 to 220 MB, 16-bit rows,
-  // tails) take 3.6 % less time in the geometric mean than with arrivals weighed as of a counted merge and a line by bytes alone:
+  // token-wise launches (2 to 64 items, 1 to 192 MB, up to 60 % 8-bit rows, caches cold).  244 others (1 to 128 items of even and
+  // uneven lengths, 0.5 to 220 MB, 16-bit rows, tails) take 3.6 % less time in the geometric mean than with arrivals weighed as of a counted merge and a line by bytes alone:
   // 55 of them at least 3 % less (one item of 220 MB, 8 heads per KV head: 717 chunks 62.7 us, 206 chunks 18.7), 8 more; 217 caches
   // of 0.4 to 8 bits per element and up to sixteen sequences 2.1 % less, 5 at least 3 % more (2 items of 23K rows: 62 chunks
   // 7.6 us, 184 chunks 8.0).
@@ -1083,7 +1086,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   //   16 items, 96 MB, 20 %                                   k 8: 26.9                         by bytes: 24.2*
   //   8 heads per KV head, 2 items, 64 MB, 60 %               k 4: 27.4 (280)  k 6: 21.5 (188)* by bytes: 42.9 (711)
   //   8 heads per KV head, 64 items, 64 MB                    k 4: 19.2 (477)*                  by bytes: 23.1 (1306)
-  // Channel-wise launches of eight-wavefront workgroups (one per compute unit, so that a few more than 256 double the time) or
+  // Channel-wise launches of eight-wavefront workgroups (cut for one per compute unit, what rows of 17 to 32 words have room for) or
   // below the floor of the cut by bytes weigh their rounds, tiles and an item's partials instead (cut_channelwise).  Over 47
   // launches of one to sixteen sequences a model of the kind above was no faster (1.003) and up to 14 % slower (16 uneven
   // items of 8K to 24K rows), though 3 % faster over 216 even ones.
@@ -1174,8 +1177,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   }
   // Number of chunks a chunk cost of cb gives, and the largest chunk's cost.  Chunks of less than an eighth of cb (a
   // tier with a handful of rows) do not count: they finish at once and leave their workgroup slot to the next chunk
-  // (16 channel-wise sequences of 64K tokens: six even chunks per item and one tiny one, 899 in all on 768 slots,
-  // take 108 us; five or seven per item 127-134 us).
+  // (16 channel-wise sequences of 64K tokens, when the launch was half as fast: six even chunks per item and one tiny one, 899 in all
+  // on 768 slots, took 108 us; five or seven per item 127-134 us).
   auto count_chunks = [&](int64_t cb, int64_t* max_cost) {
     int64_t total = 0;
     *max_cost = 0;
@@ -1369,7 +1372,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       int dev = 0;
       PACK_HIP(stage_acquire(static_cast<size_t>(tables_b), true, st, &r, &dev));
       if (mixed) std::memcpy(r.data, c->items_k.data(), n * sizeof(ItemK));
-      // [launched chunks | merging workgroups | continuation pieces] (a schedule has one of the two last)
+      // [launched chunks | continuation pieces | merging workgroups] (a schedule has one of the two last)
       Chunk* const table = reinterpret_cast<Chunk*>(r.data + ik_b);
       {
         Chunk* t = table;

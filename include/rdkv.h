@@ -19,9 +19,10 @@
  *    the schedule), rdkv_calibrate_eps, rdkv_cache_stats and rdkv_cache_export
  *    (host results) wait for the stream.  rdkv_weights, rdkv_allocate,
  *    rdkv_decode_attn, rdkv_decode_attn_bf16 and rdkv_cache_append never wait, but for
- *    one thing: the tables of rdkv_weights and rdkv_allocate (36 bytes per item) go
- *    through 2 MiB of staging memory per device, and a call whose tables take more than
- *    half of it, or that finds it full of those of queued calls, waits for them.
+ *    one thing: the tables of rdkv_weights and rdkv_allocate (32 bytes per sequence of a
+ *    batch of more than 32; 4 per item where rdkv_allocate puts more than 512 items in
+ *    order) go through 2 MiB of staging memory per device, and a call whose tables take
+ *    more than half of it, or that finds it full of those of queued calls, waits for them.
  *  - Under graph capture the calls that never wait may be recorded and replayed (what
  *    rdkv_decode_attn shares then is said there; rdkv_weights and rdkv_allocate record
  *    their lengths and budgets by value and take their scratch as always).  A call that

@@ -15,10 +15,10 @@ CALL = os.path.join(HERE, "_rdkv_call.so")
 # blocks too (per word of a channel-wise row three instructions, a wait, two jumps, and 20 registers in all).  The first option
 # lets it leave a region as it is whose branches its uniformity analysis has proved uniform -- an analysis that takes a value it
 # cannot prove for divergent --, the second takes back the exception for regions around a divergent one: a region with a single
-# branch that lanes may take differently, at any depth, is structurized as ever.  (The outputs are
-# the same bit for bit without the options.  One 64K sequence channel-wise 13.8 -> 12.1 us, 16 with one scale per channel 74.9 ->
-# 68.6, 16 ragged ones token-wise 42.8 -> 41.6, 8 layers of 16K tokens 76.4 -> 75.0, launches bound by HBM 0 to 0.5 %.  The search
-# and the packing gain nothing, the weights spill.)
+# branch that lanes may take differently, at any depth, is structurized as ever.  (The outputs are the same bit for bit without the
+# options.  One 64K sequence channel-wise 13.8 -> 12.1 us, 16 with one scale per channel 74.9 -> 68.6, 16 ragged ones token-wise
+# 42.8 -> 41.6, 8 layers of 16K tokens 76.4 -> 75.0, launches bound by HBM 0 to 0.5 %.  The search and the packing gain nothing, the
+# weights spill.)
 UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions", "-mllvm", "-structurizecfg-relaxed-uniform-regions=false"]
 # The scheduler counts live registers by the target's own trackers (only an estimate of pressure: which instruction order it
 # prefers): the second weights pass, which has all 256, no longer keeps eight values in memory across its loop, for 32 instead of

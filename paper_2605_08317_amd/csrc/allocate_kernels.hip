@@ -594,7 +594,8 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
       if (S.done || S.it >= P.max_iters) break;
       // the histogram cannot decide the next step
       // Up to 4K units the other steps are taken on all of them, 0.3 us each: finding the open buckets, the list and its few
-      // units' steps took 4.2 us (4K units without the pooling 11.8 -> 8.4 us in all, 64 units and 64 steps 16 -> 12).  With 32 units per thread a
+      // units' steps took 4.2 us (4K units without the pooling 11.8 -> 8.4 us in all, 64 units and 64 steps 16 -> 12).  With 32 units
+      // per thread a
       // step costs 2 us: two such steps in front of the list 25 -> 36 us.
       if constexpr (REG == 4) {
         int parity = 0;

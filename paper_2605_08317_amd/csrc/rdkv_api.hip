@@ -1075,7 +1075,8 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   // compute unit and looks for its partials (or, with many query heads, counts: merge_parts); a larger one counts arrivals and
   // shares its compute units.  Against both stands the cut by bytes below, whose time goes with the bytes.  Fitted to 314
   // token-wise launches (2 to 64 items, 1 to 192 MB, up to 60 % 8-bit rows, caches cold).  244 others (1 to 128 items of even and
-  // uneven lengths, 0.5 to 220 MB, 16-bit rows, tails) take 3.6 % less time in the geometric mean than with arrivals weighed as of a counted merge and a line by bytes alone:
+  // uneven lengths, 0.5 to 220 MB, 16-bit rows, tails) take 3.6 % less time in the geometric mean than with arrivals weighed as of a
+  // counted merge and a line by bytes alone:
   // 55 of them at least 3 % less (one item of 220 MB, 8 heads per KV head: 717 chunks 62.7 us, 206 chunks 18.7), 8 more; 217 caches
   // of 0.4 to 8 bits per element and up to sixteen sequences 2.1 % less, 5 at least 3 % more (2 items of 23K rows: 62 chunks
   // 7.6 us, 184 chunks 8.0).

@@ -96,54 +96,59 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
   constexpr int kVRegs = kStream ? 2 : VT;
   constexpr int kPieces = VT == 16 ? 8 : 4;          // pieces of a streamed tile
   uint4 vraw[kStream ? 2 : 1][kVRegs], vmeta;
+  // Past the chunk's last tile, past a row's last word and past the last step a load returns zeros and moves nothing (the buffers'
+  // bounds), so that every tile issues the same loads, whatever its row's length.  Behind branches the compiler does not know how
+  // many loads are under way, and P V waited not only for its V codes but also for the next tile's K row, issued right in
+  // front of the softmax: a memory latency per tile.  Registers came down too (two head sets: 169 to 158, a third wavefront per
+  // SIMD).  8 sequences of 30K tokens with 8 query heads per KV head 61.9 -> 48.2 us, 8 of 32K tokens at 8 bits per element
+  // 136.2 -> 124.2, at 2 bits 51.0 -> 49.7, 16 of 64K at 1 bit 82.6 -> 81.0, with one scale per channel 71.4 -> 70.1.
+  // Wavefronts of eight-wavefront workgroups have a tile or two each, and a load that moves nothing has to come back all the same
+  // before the chunk's end can use its registers: there the next tile's stay behind a branch (8K tokens 7.45 us, without it 7.70).
+  // (chunks have at most kMostChunkRows rows: every side is smaller than kNowhere)
+  constexpr bool kGuard = NWV == 8;
+  constexpr int kNowhere = 1 << 30;
+  constexpr int kSideBytes = kTile * 16 * VT;
+  const auto buffer = [&](const uint8_t* p, int bytes) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), 0, bytes, 0x00027000);
+  };
+  const auto kd_buf = buffer(kd, ntiles * kt_bytes), km_buf = buffer(km, per_unit ? 16 * nqs : ntiles * km_bytes);
+  const auto vd_buf = buffer(vd, ntiles * kSideBytes), vm_buf = buffer(vm, ntiles * 1024);
   auto load_k = [&](int t) __attribute__((always_inline)) {
-    const uint8_t* p = kd + static_cast<int64_t>(t) * kt_bytes;
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      // scales per group of 32 tokens: a record per tile and token group; one scale per channel over all retained tokens
+      // (App. B): a single record per segment, of which the first tile's load is the only one
+      const int sq = (lane & 31) + 32 * it;
+      const int record = !per_unit ? t * km_bytes + 16 * nqs * G : t == wave ? 0 : kNowhere / 2;
+      kmeta[it] = load_uint4(km_buf, sq < nqs ? record + 16 * sq : kNowhere);
+    }
 #pragma unroll
     for (int u = 0; u < NW / 4; ++u) {
-      // every word is assigned on every path (stores under the branches get merged into stores through a selected
-      // pointer, which keeps the array out of registers)
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (4 * u + 3 < nwp) {
-        v = *reinterpret_cast<const uint4*>(p + 1024 * u + 16 * lane);
-      } else if (4 * u + 1 < nwp) {   // the row's last two words
-        const uint2 t2 = *reinterpret_cast<const uint2*>(p + 1024 * u + 8 * lane);
-        v.x = t2.x;
-        v.y = t2.y;
-      }
+      // (where a row's last two words are a run of their own, a lane reads the next lane's beside them: nobody looks at those)
+      const int run = 4 * u + 3 < nwp ? 16 * lane : 4 * u + 1 < nwp ? 8 * lane : kNowhere;
+      const uint4 v = load_uint4(kd_buf, t * kt_bytes + 1024 * u + run);
       kw[4 * u] = v.x; kw[4 * u + 1] = v.y; kw[4 * u + 2] = v.z; kw[4 * u + 3] = v.w;
-    }
-    if (!per_unit) {   // scales per group of 32 tokens: a record per tile and token group
-      const uint8_t* pm = km + static_cast<int64_t>(t) * km_bytes;
-#pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        const int sq = (lane & 31) + 32 * it;
-        kmeta[it] = make_uint4(0, 0, 0, 0);
-        if (sq < nqs) kmeta[it] = *reinterpret_cast<const uint4*>(pm + (G * nqs + sq) * 16);
-      }
     }
   };
   auto load_v_piece = [&](int t, int piece, uint4 (&dst)[kVRegs]) __attribute__((always_inline)) {
-    const uint8_t* p = vd + static_cast<int64_t>(t) * (kTile * 16 * VT) + 2048 * piece + 16 * lane;
-    dst[0] = *reinterpret_cast<const uint4*>(p);
-    dst[1] = *reinterpret_cast<const uint4*>(p + 1024);
+    dst[0] = load_uint4(vd_buf, t * kSideBytes + 2048 * piece + 16 * lane);
+    dst[1] = load_uint4(vd_buf, t * kSideBytes + 2048 * piece + 16 * lane + 1024);
   };
+  auto load_vmeta = [&](int t) __attribute__((always_inline)) { vmeta = load_uint4(vm_buf, t * 1024 + lane * 16); };
   auto load_v = [&](int t) __attribute__((always_inline)) {
     // (ahead of the codes, which P V needs later: 8 sequences of 30K tokens, 8 query heads per KV head, 63.0 -> 59.4 us, one of 64K
     // tokens 13.0 -> 12.5, 16 of them with one scale per channel the same)
-    if constexpr (VT != 16) vmeta = *reinterpret_cast<const uint4*>(vm + static_cast<int64_t>(t) * 1024 + lane * 16);
-    if constexpr (kStream) load_v_piece(t, 0, vraw[0]);
-    else load_tile_side<VT>(vraw[0], vd, t, lane);
+    if constexpr (VT != 16) load_vmeta(t);
+    if constexpr (kStream) {
+      load_v_piece(t, 0, vraw[0]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < VT; ++i) vraw[0][i] = load_uint4(vd_buf, t * kSideBytes + lane * 16 + i * 1024);
+    }
   };
 #pragma unroll
   for (int w = 0; w < NW; ++w) kw[w] = 0;
   kmeta[0] = kmeta[1] = vmeta = make_uint4(0, 0, 0, 0);
-  if (per_unit) {      // one scale per channel over all retained tokens (App. B): a single record per segment
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const int sq = (lane & 31) + 32 * it;
-      if (sq < nqs) kmeta[it] = *reinterpret_cast<const uint4*>(km + sq * 16);
-    }
-  }
   // Loads return in order: what the query operands are made of goes ahead of the tiles, and the query rows pass through LDS
   // instead of being gathered from memory by the channel numbers once those have arrived (one round trip fewer).
   const int n_elems = n_steps * HS * 4;
@@ -152,10 +157,14 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
   struct __attribute__((packed, aligned(2))) Slots { uint32_t x, y; };      // four channel numbers
   Slots slots{0, 0};
   if (tid < n_elems) slots = *reinterpret_cast<const Slots*>(ikp->slot_ch + 4 * (tid / (HS * 4)));
-  if (wave < ntiles) {
+  // (in the order of the loop, which the waits in it rest on)
+  if constexpr (!kGuard) __builtin_amdgcn_sched_barrier(0);
+  if (!kGuard || wave < ntiles) {
     load_k(wave);
+    if constexpr (!kGuard) __builtin_amdgcn_sched_barrier(0);
     load_v(wave);
   }
+  if constexpr (!kGuard) __builtin_amdgcn_sched_barrier(0);
   uint16_t* s_qrow = reinterpret_cast<uint16_t*>(smem + plan.wtab);
   if (tid < g * (kHeadDim / 8)) *reinterpret_cast<uint4*>(s_qrow + 8 * tid) = qrow;
   __syncthreads();
@@ -266,7 +275,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
 
   for (int tile = wave; tile < ntiles; tile += kWaves) {
     const int next = tile + kWaves;
-    const bool more = next < ntiles;
+    const bool more = !kGuard || next < ntiles;
     if (!per_unit) prep();
 
     // ---- logits x[hs][i] of token 4 blk + i and head 4 hs + j, in units of kKUnit ----------------------------
@@ -463,7 +472,7 @@ __device__ __forceinline__ uint32_t process_mixed(const Chunk& ch, const uint8_t
             gw[0][4] = v[1].x; gw[0][5] = v[1].y; gw[0][6] = v[1].z; gw[0][7] = v[1].w;
           },
           vmeta, p, run);
-      if (more) vmeta = *reinterpret_cast<const uint4*>(vm + static_cast<int64_t>(next) * 1024 + lane * 16);
+      if (more) load_vmeta(next);
     } else {
       pv_tile<VT, HS>(vraw[0], vmeta, p, run);
       if (more) load_v(next);   // V registers are free again

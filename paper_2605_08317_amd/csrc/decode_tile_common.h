@@ -190,6 +190,13 @@ __device__ __forceinline__ void load_tile_side(uint4 (&raw)[TIER], const uint8_t
   for (int i = 0; i < TIER; ++i) raw[i] = *reinterpret_cast<const uint4*>(p + i * 1024);
 }
 
+// sixteen bytes of a buffer (a type the host's compiler does not know), zeros past its end
+template <class Buffer>
+__device__ __forceinline__ uint4 load_uint4(Buffer buf, int at) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b128(buf, at, 0, 0);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();

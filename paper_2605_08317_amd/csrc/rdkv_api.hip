@@ -1265,6 +1265,7 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
       const int64_t per_row = row_cost(i, bits);
       int64_t want = std::max<int64_t>(64, (!mixed && bits == 16 ? chunk_bytes16 : chunk_bytes) / per_row);
       if (small_rows > 0 && (mixed || bits != 16 || rows16_along)) want = small_rows;
+      want = std::min<int64_t>(want, kMostChunkRows);
       const int64_t nch = (cnt + want - 1) / want;
       const int64_t rows_per = round_up((cnt + nch - 1) / nch, 64);
       for (int64_t r0 = 0; r0 < cnt; r0 += rows_per) {

@@ -15,6 +15,7 @@ namespace rdkv {
 constexpr int kHeadDim = 128;
 constexpr int kGroup = 32;             // quantization group (channels)
 constexpr int kGroupsPerRow = kHeadDim / kGroup;
+constexpr int kMostChunkRows = 1 << 21;   // of a chunk of the decode schedule: a side of it is smaller than 2^30 bytes
 constexpr int kTile64 = 64;            // tier segments are padded to whole 64-row tiles
 constexpr int kKTokenGroup = 32;       // mixed mode: a K channel's group = 32 consecutive retained tokens of a segment
 constexpr int kPartBlock = 1024;       // tokens per block of the tier counts

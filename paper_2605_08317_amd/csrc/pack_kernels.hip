@@ -322,7 +322,7 @@ struct PackArgs {
                                // retained tokens (one scale per channel, App. B), or null (groups of 32 tokens)
   int32_t row_wide;            // token rows: one scale and offset per row (App. B's per-token format), repeated in
                                // the row's four metadata slots, instead of one per group of 32 channels
-  int32_t extra;               // pack_tile_kernel: leading workgroups of every grid row that copy
+  int32_t extra;               // leading workgroups of every grid row that copy
   CopyArgs copy;
   Batch batch;
 };
@@ -531,25 +531,18 @@ __device__ __forceinline__ void store_v_words(const uint8_t* s_vc, uint8_t* tile
 }
 
 // One workgroup = one tile of 64 kept rows of any tier, K and V (V_ONLY: V, K of a channel-wise cache is packed by
-// pack_k_mixed_kernel); rows past the segment's last are zero rows, so a tile is always written whole.  A wavefront gathers
+// pack_k_group); rows past the segment's last are zero rows, so a tile is always written whole.  A wavefront gathers
 // 16 rows, 16 lanes a row (whole 256-byte rows per load), a lane the same 8 channels of four consecutive tokens, which is
 // what a step of the V layout takes; codes are made in registers and only V passes through LDS, as bytes.  Bound: HBM and
 // plain ALUs (the gather: 0.94 GB at 5.3 TB/s, half reads of whole rows; 14 instructions per element).  128 items x 20K
 // tokens, mostly 2- and 4-bit rows: 216 -> 172 us; a 128K-token layer 20.4 -> 16.6 us; V alone of 8 x 50K 17.3 -> 13.6.  Before,
 // positions were loaded row by row, codes were converted one by one, and the division path, inlined beside every row, took the
 // registers of a fifth workgroup.
+constexpr int kTileLds = kTile64 * (kHeadDim + 8) * 2;
+// b: the tile's number in its item; s_buf: kTileLds bytes for V codes, or bf16 V rows of the 16-bit tier; s_km: K metadata
 template <bool V_ONLY>
-__global__ __launch_bounds__(256, 5) void pack_tile_kernel(PackArgs a) {
-  __shared__ __align__(16) uint8_t s_buf[kTile64 * (kHeadDim + 8) * 2];   // V codes, or bf16 V rows of the 16-bit tier
-  __shared__ __align__(16) uint16_t s_km[kTile64][8];                     // K metadata
-  static_assert(kCopyThreads == 256, "copies in workgroups of this kernel");
-  const int item = blockIdx.y;
-  if (static_cast<int>(blockIdx.x) < a.extra) {
-    const int b = item * a.extra + static_cast<int>(blockIdx.x);
-    if (b < a.copy.first[a.copy.n]) copy_part(a.copy, b);
-    return;
-  }
-  const TileOf t(a, item, static_cast<int>(blockIdx.x) - a.extra);
+__device__ __forceinline__ void pack_tile(const PackArgs& a, int item, int b, uint8_t* s_buf, uint16_t (*s_km)[8]) {
+  const TileOf t(a, item, b);
   if (t.ti == 4) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, c16 = lane & 15, grp = c16 >> 2, p = c16 & 3;
@@ -677,6 +670,23 @@ __global__ __launch_bounds__(256, 5) void pack_tile_kernel(PackArgs a) {
   }
 }
 
+// the copies that ride along: the leading workgroups of every grid row
+__device__ __forceinline__ bool copied_along(const PackArgs& a) {
+  static_assert(kCopyThreads == 256, "copies in workgroups of these kernels");
+  if (static_cast<int>(blockIdx.x) >= a.extra) return false;
+  const int b = static_cast<int>(blockIdx.y) * a.extra + static_cast<int>(blockIdx.x);
+  if (b < a.copy.first[a.copy.n]) copy_part(a.copy, b);
+  return true;
+}
+
+template <bool V_ONLY>
+__global__ __launch_bounds__(256, 5) void pack_tile_kernel(PackArgs a) {
+  __shared__ __align__(16) uint8_t s_buf[kTileLds];
+  __shared__ __align__(16) uint16_t s_km[V_ONLY ? 1 : kTile64][8];
+  if (copied_along(a)) return;
+  pack_tile<V_ONLY>(a, blockIdx.y, static_cast<int>(blockIdx.x) - a.extra, s_buf, s_km);
+}
+
 // ---- mixed mode -------------------------------------------------------------------------------------------------
 // One scale per channel over all retained tokens (App. B): the channel's minimum and maximum over the kept rows of
 // all four tiers of the item.  k_range starts at (0xFFFFFFFF, 0).
@@ -796,16 +806,22 @@ __device__ __forceinline__ uint32_t transpose_fields(uint32_t v, int f) {
 }
 
 constexpr int kKThreads = 192;         // the most lanes a token group has
-__global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) {
-  constexpr int kRows = kKTokenGroup;
-  constexpr int kRowStride = kHeadDim + 8;
-  constexpr int kRowBytes = kRows * kRowStride * 2, kWordBytes = kRows * kMaxKRowWords * 4;
+struct KGroupLds {
+  static constexpr int kRowStride = kHeadDim + 8;
+  static constexpr int kRowBytes = kKTokenGroup * kRowStride * 2, kWordBytes = kKTokenGroup * kMaxKRowWords * 4;
+  uint8_t buf[kRowBytes > kWordBytes ? kRowBytes : kWordBytes];      // bf16 rows, then the group's words
+  uint16_t sc[kHeadDim], of[kHeadDim];
+  ItemK ik;
+};
+// b: the tile's number in its item
+__device__ __forceinline__ void pack_k_group(const PackArgs& a, int item, int b, int G, KGroupLds& lds) {
+  constexpr int kRows = kKTokenGroup, kRowStride = KGroupLds::kRowStride;
   static_assert(kTile64 == 2 * kRows, "two workgroups a tile");
-  __shared__ __align__(16) uint8_t s_buf[kRowBytes > kWordBytes ? kRowBytes : kWordBytes];   // bf16 rows, then the group's words
-  __shared__ uint16_t s_sc[kHeadDim], s_of[kHeadDim];
-  __shared__ ItemK s_ik;
-  const int item = blockIdx.y, G = blockIdx.x & 1;
-  const TileOf t(a, item, blockIdx.x >> 1);
+  uint8_t* const s_buf = lds.buf;
+  uint16_t* const s_sc = lds.sc;
+  uint16_t* const s_of = lds.of;
+  ItemK& s_ik = lds.ik;
+  const TileOf t(a, item, b);
   if (t.ti == 4) return;
   const int valid = min(kTile64, t.n - t.tile * kTile64), vg = min(max(valid - kRows * G, 0), kRows);     // rows of the tile, of the group
   const int tid = threadIdx.x;
@@ -990,6 +1006,29 @@ __global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) 
   }
 }
 
+__global__ __launch_bounds__(kKThreads, 6) void pack_k_mixed_kernel(PackArgs a) {
+  __shared__ __align__(16) KGroupLds s;
+  pack_k_group(a, blockIdx.y, static_cast<int>(blockIdx.x) >> 1, blockIdx.x & 1, s);
+}
+
+// K and V of a channel-wise cache in one launch: k_groups workgroups per item for K, of three wavefronts (the fourth leaves at
+// once), the others for V.  A small cache saves a launch (launch_quant_pack says where); in a large one K pays for the registers
+// and the LDS of the V tiles.
+__global__ __launch_bounds__(256, 5) void pack_mixed_kernel(PackArgs a, int k_groups) {
+  __shared__ __align__(16) union {
+    uint8_t tile[kTileLds];
+    KGroupLds k;
+  } s;
+  if (copied_along(a)) return;
+  const int b = static_cast<int>(blockIdx.x) - a.extra;
+  if (b < k_groups) {
+    if (threadIdx.x >= kKThreads) return;
+    pack_k_group(a, blockIdx.y, b >> 1, b & 1, s.k);
+  } else {
+    pack_tile<true>(a, blockIdx.y, b - k_groups, s.tile, nullptr);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_tier_count(const uint8_t* bits, const Batch& batch, int32_t* blk_counts, int max_T, hipStream_t st) {
@@ -1025,6 +1064,15 @@ hipError_t launch_quant_pack(const uint16_t* K, const uint16_t* V, const int32_t
     // 512 workgroups fill the chip; 16 per item are left where there are many items, 128 at most where there are few
     const int parts = std::min(std::max(512 / n_items, 16), 128), most = (max_tiles * kTile64 + kRangeRows - 1) / kRangeRows;
     hipLaunchKernelGGL(k_channel_range_kernel, dim3(std::max(1, std::min(parts, most)), n_items), dim3(kRangeThreads), 0, st, a);
+  }
+  // One launch for K and V where they are few workgroups, the launch's own time counts and the slower workgroups do not: a whole pass
+  // over 1.7K to 6.7K tokens of 2 to 24 items (up to 2400 workgroups) 71.4 -> 67.6, 72.4 -> 69.6, 87.9 -> 84.4 and 109.2 -> 105.7 us, of
+  // 32 items of 4K (5800) 117.0 -> 116.7, of 8 items of 50K and 39K tokens (11K, 14K) 162.0 -> 166.1 and 173.2 -> 174.6, of 12 of 55K
+  // 304 -> 326.
+  constexpr int64_t kTogether = 4096;
+  if (static_cast<int64_t>(3 * max_tiles) * n_items <= kTogether) {
+    hipLaunchKernelGGL(pack_mixed_kernel, dim3(3 * max_tiles + extra, n_items), block, 0, st, a, 2 * max_tiles);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL(pack_k_mixed_kernel, dim3(2 * max_tiles, n_items), dim3(kKThreads), 0, st, a);
   hipLaunchKernelGGL(pack_tile_kernel<true>, with_copies, block, 0, st, a);

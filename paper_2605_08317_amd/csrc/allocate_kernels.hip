@@ -10,7 +10,7 @@
 //
 // Three things make a step cheap without changing a single verdict:
 //   - (double) w > t is w > below(t), the largest fp32 number not above t, so units are compared in fp32, one
-//     instruction per threshold, and counted by the scalar unit (population count of the comparison mask);
+//     instruction per threshold, and counted in the lanes by the comparison's carry;
 //   - a histogram over the leading bits of the fp32 pattern bounds the bit sum of any multiplier from both sides; while
 //     the two bounds agree, no unit is read.  One wavefront evaluates the 63 multipliers the next six steps can visit at
 //     once (a lane walks the midpoints to its node of the tree, so the multipliers are bit for bit those of Alg. 2);
@@ -53,6 +53,7 @@ struct AllocArgs {
   double* lam_out;             // [items] or null: the multiplier of the returned allocation (NaN: no search ran)
   int32_t* iters_out;          // [items] or null: bisection steps taken
   int4* blk_counts;            // [blocks] out: units of the block in tiers 16, 8, 4, 2; or null
+  int32_t direct;              // allocate_item_kernel: steps taken on all units before the open ones are listed
   const int32_t* order;        // the items of this launch, or null: all of them as they stand
   Batch batch;
   __device__ __forceinline__ int item_of(int slot) const { return order ? __builtin_amdgcn_readfirstlane(order[slot]) : slot; }
@@ -65,6 +66,13 @@ __device__ __forceinline__ float below(double t) {
 }
 
 __device__ __forceinline__ int tier_slot(int b) { return b == 16 ? 0 : b == 8 ? 1 : b == 4 ? 2 : b == 2 ? 3 : -1; }
+
+// c ? a : b of members of a structure (through the value: out of a plain selection the compiler makes one of two addresses, which puts
+// the structure into memory)
+__device__ __forceinline__ double either(bool c, double a, double b) {
+  asm("" : "+v"(a), "+v"(b));
+  return c ? a : b;
+}
 
 // ---- the search of one item ------------------------------------------------------------------------------------------
 struct Problem {
@@ -99,6 +107,12 @@ struct Problem {
   }
   // a unit is above threshold k of lam when it exceeds this
   __device__ __forceinline__ float thr(double lam, int k) const { return k < nh - 1 ? below(lam * r[k]) : INFINITY; }
+  // the ratio of threshold lane % 4
+  __device__ __forceinline__ double ratio_of_lane() const {
+    static_assert(kThr == 4, "two bits of the lane");
+    const bool odd = threadIdx.x & 1;
+    return either(threadIdx.x & 2, either(odd, r[3], r[2]), either(odd, r[1], r[0]));
+  }
   // bits of n units above threshold k
   __device__ __forceinline__ long long gain(int k, int n) const {
     return static_cast<long long>(static_cast<unsigned long long>(static_cast<unsigned>(step_bits[k])) * static_cast<unsigned>(n));
@@ -248,7 +262,7 @@ __device__ __forceinline__ double narrow_hull(const Problem& P, const Map& map, 
   return feasible ? S.lo : S.hi;
 }
 constexpr int kManyOpen = 4096;      // open units from which that pays
-constexpr int kFewOpen = 1024;       // open units that a single wavefront takes the remaining steps on
+constexpr int kFewOpen = 1024;       // open units that a wavefront holds for the remaining steps
 
 // In place: suffix[b] = sum of suffix[b ..]; suffix[BUCKETS] = 0.  All threads; barriers inside.
 template <int BUCKETS>
@@ -336,6 +350,57 @@ struct OpenPatterns {
   }
 };
 
+// Bits that a wavefront's units (N in each lane) gain above the thresholds, in every lane; n_units * 16 fits.  Counted in the lanes, two
+// instructions per unit and threshold, and added up once: population counts of the comparison masks go through the scalar unit
+// that the wavefronts of a SIMD share, and through scalar registers that 16 units and more do not have (one step on 8 units a
+// thread 1.3 us, on 16 2.4).
+// (as one block: a comparison's mask may be read two wait states after it, which the others' comparisons fill; out of additions of
+// 32 units' comparisons the compiler made trees of selects that spilled.  t is uniform, and read two wait states earlier at the latest.)
+__device__ __forceinline__ void count_above(float w, const float (&t)[4], int (&c)[4]) {
+  uint64_t m1, m2, m3;
+  asm volatile("v_cmp_lt_f32 vcc, %7, %11\n\t"
+      "v_cmp_lt_f32_e64 %4, %8, %11\n\t"
+      "v_cmp_lt_f32_e64 %5, %9, %11\n\t"
+      "v_cmp_lt_f32_e64 %6, %10, %11\n\t"
+      "v_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+      "v_addc_co_u32_e64 %1, %4, %1, 0, %4\n\t"
+      "v_addc_co_u32_e64 %2, %5, %2, 0, %5\n\t"
+      "v_addc_co_u32_e64 %3, %6, %3, 0, %6"
+      : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+      : "s"(t[0]), "s"(t[1]), "s"(t[2]), "s"(t[3]), "v"(w)
+      : "vcc");
+}
+// (used: how many of the N, in whole fours; uniform)
+template <int N>
+__device__ __forceinline__ int bits_above(const Problem& P, const float (&w)[N], const float (&t)[kThr], int used = N) {
+  static_assert(kThr == 4, "the thresholds of count_above");
+  // (a scalar that a lane was read into may be read two wait states later, which the compiler does not look after in a block)
+  asm volatile("s_nop 1" :: "s"(t[0]), "s"(t[1]), "s"(t[2]), "s"(t[3]));
+  __builtin_amdgcn_sched_barrier(0);
+  int c[kThr] = {0, 0, 0, 0}, s = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i > 0 && i % 4 == 0 && i >= used) break;
+    count_above(w[i], t, c);
+    __builtin_amdgcn_sched_barrier(0);     // (not all masks first: 32 units spilled)
+  }
+#pragma unroll
+  for (int k = 0; k < kThr; ++k) s += __mul24(P.step_bits[k], c[k]);
+  return __builtin_amdgcn_readlane(static_cast<int>(wave_scan(static_cast<uint32_t>(s))), 63);
+}
+// the thresholds of lam, a lane each (whole wavefronts)
+__device__ __forceinline__ void thresholds(const Problem& P, double lam, float (&t)[kThr]) {
+  const int own = __float_as_int(below(lam * P.ratio_of_lane()));
+#pragma unroll
+  for (int k = 0; k < kThr; ++k) t[k] = k < P.nh - 1 ? __int_as_float(__builtin_amdgcn_readlane(own, k)) : INFINITY;
+}
+
+// the sum of what the wavefronts have left in slots[kWaves], in every lane
+__device__ __forceinline__ int sum_of_waves(const int* slots) {
+  static_assert(kWaves == 16, "a row of lanes");
+  return static_cast<int>(row_sum(static_cast<uint32_t>(slots[threadIdx.x & (kWaves - 1)])));
+}
+
 // The remaining steps, exactly, on n undecided units in LDS beside the decided ones' bit sum `fixed`.
 // All threads; S is the same in all of them on entry and exit.  s_red: 2 kWaves ints.
 __device__ __forceinline__ void steps_on_list(const Problem& P, const float* list, int n, long long fixed,
@@ -362,10 +427,7 @@ __device__ __forceinline__ void steps_on_list(const Problem& P, const float* lis
     parity ^= 1;
     if (lane == 0) slots[wave] = s;
     __syncthreads();
-    int sum = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) sum += slots[w];
-    S.take(P.verdict(fixed + sum), lam);
+    S.take(P.verdict(fixed + __builtin_amdgcn_readfirstlane(sum_of_waves(slots))), lam);
   }
 }
 // the same by one wavefront that holds up to 64 PER units in registers
@@ -412,6 +474,58 @@ __device__ __forceinline__ void steps_on_few(const Problem& P, int n, long long 
   }
 }
 
+// The same by the whole workgroup, three steps at a time: wavefront i of the first eight evaluates the multiplier at node i of the tree of
+// the next three steps' outcomes (steps_on_histogram has the numbering), then all of them walk down it.  One wavefront that took a
+// step at a time needs 1.1 to 1.4 us each.  (Four wavefronts and two steps, sixteen and four: within 1 % of it.  The many-workgroup form,
+// whose list is in memory and goes to one wavefront's registers without a barrier: 4 x 70K units 45.0 -> 46.0 us, 8 x 128K the same.)
+// All threads; S is the same in all of them on entry and exit.  s_red: 2 kWaves ints.
+constexpr int kNodes = 8;
+template <int PER>
+__device__ __forceinline__ void steps_in_tree(const Problem& P, const float* list, int n, long long fixed, const Hull& h, Search& S, int* s_red) {
+  const int lane = threadIdx.x & 63;
+  const int node = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int depth = 31 - __clz(max(1, node));
+  static_assert(kNodes <= kWaves, "a wavefront per node");
+  const bool works = node > 0 && node < kNodes;
+  float w[PER];
+  if (works) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) w[i] = i * 64 + lane < n ? list[i * 64 + lane] : 0.f;
+  }
+  int parity = 0;
+  while (!S.done && S.it < P.max_iters) {
+    int* slots = s_red + parity * kWaves;        // alternating, so that one barrier per round is enough
+    parity ^= 1;
+    if (works) {
+      double lo = S.lo, hi = S.hi;
+      for (int d = depth - 1; d >= 0; --d) {
+        const double mid = (lo + hi) * 0.5;
+        if ((node >> d) & 1) hi = mid; else lo = mid;
+      }
+      const double lam = (lo + hi) * 0.5;
+      int v = lam > h.hi ? 1 : 0;          // outside the hull (uniform)
+      if (lam >= h.lo && lam <= h.hi) {
+        float t[kThr];
+        thresholds(P, lam, t);
+        v = P.verdict(fixed + bits_above(P, w, t));
+      }
+      if (lane == 0) slots[node] = v;
+    }
+    __syncthreads();
+    for (int cur = 1; cur < kNodes && !S.done && S.it < P.max_iters;) {
+      const int verdict = slots[cur];
+      S.take(verdict, (S.lo + S.hi) * 0.5);
+      cur = 2 * cur + (verdict != 0);
+    }
+  }
+}
+__device__ __forceinline__ void steps_on_short_list(const Problem& P, const float* list, int n, long long fixed, const Hull& h, Search& S, int* s_red) {
+  if (n <= 64) steps_in_tree<1>(P, list, n, fixed, h, S, s_red);
+  else if (n <= 256) steps_in_tree<4>(P, list, n, fixed, h, S, s_red);
+  else if (n <= 512) steps_in_tree<8>(P, list, n, fixed, h, S, s_red);
+  else steps_in_tree<16>(P, list, n, fixed, h, S, s_red);
+}
+
 __device__ __forceinline__ void report(const AllocArgs& a, int item, bool searched, const Search& S) {
   if (a.lam_out) a.lam_out[item] = searched && S.have ? S.best : __longlong_as_double(0x7FF8000000000000ll);
   if (a.iters_out) a.iters_out[item] = searched ? S.it : 0;
@@ -453,15 +567,16 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 constexpr int kMostRadius = 7;
 __device__ __forceinline__ void pool_quotients(const AllocArgs& a, float (&s)[4]) {
   const float n = static_cast<float>(a.pool);
-  bool odd = false;
+  // (sums of weights: not negative, so that their patterns are ordered as they are; zeros and NaN are divided)
+  const uint32_t u[4] = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+  const uint32_t least = min(min(min(u[0], u[1]), u[2]), u[3]), most = max(max(max(u[0], u[1]), u[2]), u[3]);
   float q[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float q0 = s[e] * a.pool_inv;
     q[e] = __builtin_fmaf(__builtin_fmaf(-q0, n, s[e]), a.pool_inv, q0);
-    odd |= !(s[e] == 0.f || (s[e] > 1e-25f && s[e] < 1e30f));
   }
-  if (__builtin_expect(__any(odd), 0)) {
+  if (__builtin_expect(__any(least < __float_as_uint(1e-25f) || most > __float_as_uint(1e30f)), 0)) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) q[e] = s[e] / n;
   }
@@ -489,10 +604,13 @@ __device__ __forceinline__ void pool_any(const AllocArgs& a, const float* w, flo
 // one compute unit works on an item, through the latency of its loads and about fifteen barriers and then the number of
 // instructions per unit and pass (load, histogram, gather, write).  Measured against fp64 comparisons and one step at a time: 4K
 // units 31 -> 8.4 us, 32K units (94 us in five kernels) -> 24 us, both with the counting kernels (10 us) gone; with the pooling,
-// which had a launch of its own, 9.5 and 28.
+// which had a launch of its own, 9.5 and 28.  By time stamps, 8K units were 1.7 us of pooling, 3.9 of histogram and its steps, 7.6 of
+// the other steps and 1.5 of the map, 32K units 5.1, 7.2, 7.5 and 4.0: with a class of 8K units whose steps are all taken in
+// registers, population counts turned into carries, and one range check per four quotients, eight items of 8K units 20.7 -> 14.0 us,
+// of 4K 9.5 -> 8.9, of 16K 2.3 less, of 32K 1.5 less; 128 items of 20K 31.1 -> 28.7.
 constexpr int kItemListCap = 24576;        // units of open buckets in LDS (96 KB beside 34 KB of histogram)
 template <int REG>
-constexpr size_t kItemLds = Anchored::kWords * sizeof(int) + (REG == 4 ? kWaves * sizeof(int4) : kItemListCap * sizeof(float));
+constexpr size_t kItemLds = Anchored::kWords * sizeof(int) + (REG <= 8 ? REG / 4 * kWaves * 2 * sizeof(uint32_t) : kItemListCap * sizeof(float));
 
 template <int REG>
 __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
@@ -500,7 +618,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   int* s_hist = reinterpret_cast<int*>(smem);
   float* s_list = reinterpret_cast<float*>(s_hist + Anchored::kWords);      // [kItemListCap]
-  int4* s_cnt = reinterpret_cast<int4*>(s_list);                                // [kQ][kWaves], after the search
+  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_list);                        // [kQ][kWaves][2], after the search
   __shared__ int s_wave[kWaves], s_red[2 * kWaves], s_n;
   __shared__ float s_max[kWaves];
   __shared__ Search s_search;
@@ -511,6 +629,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* w = a.w + it.off;
   uint8_t* __restrict__ bits = a.bits + it.off;
+  const int used = 4 * ((U + 4 * kThreads - 1) / (4 * kThreads));     // of a thread's units
   float v[REG];                            // units past the end read as 0: never above a threshold
   if (a.raw) w = a.raw + it.off;
 #pragma unroll
@@ -549,8 +668,9 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
         } else {
           pool_any(a, s_raw + kPad + u0 - a.pool / 2, x);
         }
+        const bool inside = 4 * (j + 1) * kThreads <= U;      // (uniform)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[4 * j + e] = u0 + e < U ? x[e] : 0.f;
+        for (int e = 0; e < 4; ++e) v[4 * j + e] = inside || u0 + e < U ? x[e] : 0.f;
       }
     }
     __syncthreads();
@@ -593,33 +713,24 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
       S = s_search;
       if (S.done || S.it >= P.max_iters) break;
       // the histogram cannot decide the next step
-      // Up to 4K units the other steps are taken on all of them, 0.3 us each: finding the open buckets, the list and its few
-      // units' steps took 4.2 us (4K units without the pooling 11.8 -> 8.4 us in all, 64 units and 64 steps 16 -> 12).  With 32 units
-      // per thread a
-      // step costs 2 us: two such steps in front of the list 25 -> 36 us.
-      if constexpr (REG == 4) {
+      // Up to 8K units the other steps are taken on all of them, 1 us each; up to 16K the first a.direct of them, 1.4 us each (see
+      // launch_short_items).  An item has 0 to 5 of them left.  The open buckets, the list and its few units' steps take 6 to 7 us: 5000
+      // units 19.2 -> 13.4 us in all, 8K 21.6 -> 15.7 (of eight items; a launch of them takes 2 us, events around it 2 more).  With 32
+      // units per thread a step costs 2.2 us, and the slowest of 128 items takes five: 34.2 -> 35.5.
+      if constexpr (REG <= 16) {
         int parity = 0;
-        while (!S.done && S.it < P.max_iters) {
+        for (int taken = 0; (REG <= 8 || taken < a.direct) && !S.done && S.it < P.max_iters; ++taken) {
           const double lam = (S.lo + S.hi) * 0.5;
-          int c = 0;
-#pragma unroll
-          for (int k = 0; k < kThr; ++k) {
-            const float tk = P.thr(lam, k);
-            int ck = 0;
-#pragma unroll
-            for (int j = 0; j < REG; ++j) ck += __popcll(__ballot(v[j] > tk));
-            c += P.step_bits[k] * ck;
-          }
+          thresholds(P, lam, t);
+          const int c = bits_above(P, v, t, used);
           int* slots = s_red + parity * kWaves;        // alternating, so that one barrier per step is enough
           parity ^= 1;
           if (lane == 0) slots[wave] = c;
           __syncthreads();
-          long long s = P.base;
-#pragma unroll
-          for (int i = 0; i < kWaves; ++i) s += slots[i];
-          S.take(P.verdict(s), lam);
+          S.take(P.verdict(P.base + __builtin_amdgcn_readfirstlane(sum_of_waves(slots))), lam);
         }
-        break;
+        if (REG <= 8 || S.done || S.it >= P.max_iters) break;
+        __syncthreads();                   // s_red is not read any more
       }
       Hull hull = bracket_of(S);
       OpenBuckets open(P, map, hull);
@@ -648,29 +759,14 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
           if ((mine >> j) & 1) *dst++ = v[j];
         __syncthreads();
         const long long fixed = open.fixed(P, s_hist);
-        if (n <= kFewOpen) {
-          if (wave == 0) {
-            steps_on_few(P, n, fixed, hull, S, [&](int i) { return s_list[i]; });
-            if (lane == 0) s_search = S;
-          }
-          __syncthreads();
-          S = s_search;
-        } else {
-          steps_on_list(P, s_list, n, fixed, hull, S, s_red);
-        }
+        if (n <= kFewOpen) steps_on_short_list(P, s_list, n, fixed, hull, S, s_red);
+        else steps_on_list(P, s_list, n, fixed, hull, S, s_red);
         break;
       }
       // too many for LDS: this one step on all units, then the histogram again with half the bracket
       const double lam = (S.lo + S.hi) * 0.5;
-      int c = 0;
-#pragma unroll
-      for (int k = 0; k < kThr; ++k) {
-        const float tk = P.thr(lam, k);
-        int ck = 0;
-#pragma unroll
-        for (int j = 0; j < REG; ++j) ck += __popcll(__ballot(v[j] > tk));
-        c += P.step_bits[k] * ck;
-      }
+      thresholds(P, lam, t);
+      const int c = bits_above(P, v, t, used);
       if (lane == 0) s_red[wave] = c;
       __syncthreads();
       long long s = P.base;
@@ -695,39 +791,46 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
     return;
   }
   __syncthreads();                         // the list is not read any more
+  // (Tiers are one bit each: a byte per unit counts them, eight bits per tier up to 32 lanes.)
 #pragma unroll
   for (int j = 0; j < kQ; ++j) {
     const int u0 = 4 * (j * kThreads + tid);
     if (4 * j * kThreads < U) {            // (uniform)
       uint32_t packed = 0;
-      int c[kThr] = {0, 0, 0, 0};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        int above[kThr];
-        packed |= static_cast<uint32_t>(tier_of(P, v[4 * j + e], t, above)) << (8 * e);
+        uint32_t b = static_cast<uint32_t>(P.tiers[0]);
 #pragma unroll
-        for (int k = 0; k < kThr; ++k) c[k] += above[k];
+        for (int k = 0; k < kThr; ++k) b = v[4 * j + e] > t[k] ? static_cast<uint32_t>(P.tiers[k + 1]) : b;      // thresholds ascend
+        packed |= b << (8 * e);
       }
       if (u0 + 3 < U) {
         reinterpret_cast<Bytes4*>(bits + u0)->v = packed;
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+        for (int e = 0; e < 4; ++e) {
           if (u0 + e < U) bits[u0 + e] = static_cast<uint8_t>(packed >> (8 * e));
+          else packed &= ~(0xFFu << (8 * e));
+        }
       }
-      if (lane == 0) s_cnt[j * kWaves + wave] = make_int4(c[0], c[1], c[2], c[3]);
+      uint32_t n = 0;                      // in tiers 16, 8, 4, 2
+#pragma unroll
+      for (int k = 0; k < 4; ++k) n |= static_cast<uint32_t>(__popc(packed & (0x10101010u >> k))) << (8 * k);
+      n = row_pair_sum(n);
+      if ((lane & 31) == 31) s_cnt[(j * kWaves + wave) * 2 + (lane >> 5)] = n;
     }
   }
   if (a.blk_counts) {
     __syncthreads();
     if (tid < nblk) {                      // block tid: wavefronts 4 tid .. 4 tid + 3 of the rounds in one line
-      int4 c = s_cnt[4 * tid];
+      uint32_t even = 0, odd = 0;
 #pragma unroll
-      for (int i = 1; i < 4; ++i) {
-        const int4 x = s_cnt[4 * tid + i];
-        c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t x = s_cnt[8 * tid + i];
+        even += x & 0x00FF00FFu;
+        odd += (x >> 8) & 0x00FF00FFu;
       }
-      a.blk_counts[it.blk0 + tid] = tier_counts(P, min(kBlockUnits, U - tid * kBlockUnits), c);
+      a.blk_counts[it.blk0 + tid] = make_int4(even & 0xFFFF, odd & 0xFFFF, even >> 16, odd >> 16);
     }
   }
 }
@@ -1175,7 +1278,10 @@ size_t state_bytes(int n_items) { return (static_cast<size_t>(n_items) * sizeof(
 // Items that the many-workgroup form takes at once: 130 KB of scratch each, 67 MB in all.
 constexpr int kMostTogether = 512;
 
-hipError_t launch_short_items(const AllocArgs& a, int n_items, int max_U, hipStream_t st) {
+hipError_t launch_short_items(AllocArgs a, int n_items, int max_U, hipStream_t st) {
+  // The launch ends with its slowest item, and of many some have more steps left than the list is worth: 32 items of 12K units
+  // 23.9 -> 22.4 us with up to nine such steps, 64 of 11K 26.8 -> 22.5, 128 of 14K 27.4 -> 28.9.
+  a.direct = n_items <= 64 ? 9 : 0;
   const dim3 grid(n_items), block(kThreads);
 #define RDKV_ITEMS(REG_)                                                              \
   {                                                                                   \
@@ -1184,6 +1290,7 @@ hipError_t launch_short_items(const AllocArgs& a, int n_items, int max_U, hipStr
     hipLaunchKernelGGL(allocate_item_kernel<REG_>, grid, block, kItemLds<REG_>, st, a); \
   }
   if (max_U <= 4 * kThreads) RDKV_ITEMS(4)
+  else if (max_U <= 8 * kThreads) RDKV_ITEMS(8)
   else if (max_U <= 16 * kThreads) RDKV_ITEMS(16)
   else RDKV_ITEMS(32)
 #undef RDKV_ITEMS

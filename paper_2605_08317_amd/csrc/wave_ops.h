@@ -41,6 +41,12 @@ __device__ __forceinline__ float row_sum(float v) {
   v += dpp_f32<0x122>(v);
   return v + dpp_f32<0x121>(v);
 }
+__device__ __forceinline__ uint32_t row_sum(uint32_t v) {
+  v += dpp_u32<0x128>(v);
+  v += dpp_u32<0x124>(v);
+  v += dpp_u32<0x122>(v);
+  return v + dpp_u32<0x121>(v);
+}
 __device__ __forceinline__ float sum_xor16(float v) {
   float o = v;
   swap_rows(v, o);
@@ -98,6 +104,14 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
   v += lanes_below<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
   v += lanes_below<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
   return v;
+}
+// sums over the wavefront's halves, in lanes 31 and 63
+__device__ __forceinline__ uint32_t row_pair_sum(uint32_t v) {
+  v += lanes_below<0x111, 0xF>(v);
+  v += lanes_below<0x112, 0xF>(v);
+  v += lanes_below<0x114, 0xF>(v);
+  v += lanes_below<0x118, 0xF>(v);
+  return v + lanes_below<0x142, 0xA>(v);
 }
 // maximum of numbers >= 0 (NaN is ignored), in every lane
 __device__ __forceinline__ float wave_max(float v) {

@@ -54,6 +54,7 @@ struct AllocArgs {
   int32_t* iters_out;          // [items] or null: bisection steps taken
   int4* blk_counts;            // [blocks] out: units of the block in tiers 16, 8, 4, 2; or null
   int32_t direct;              // allocate_item_kernel: steps taken on all units before the open ones are listed
+  CountPost post;              // allocate_item_kernel, channel_allocate_kernel: where the host waits for the results, or nulls
   const int32_t* order;        // the items of this launch, or null: all of them as they stand
   Batch batch;
   __device__ __forceinline__ int item_of(int slot) const { return order ? __builtin_amdgcn_readfirstlane(order[slot]) : slot; }
@@ -612,6 +613,11 @@ constexpr int kItemListCap = 24576;        // units of open buckets in LDS (96 K
 template <int REG>
 constexpr size_t kItemLds = Anchored::kWords * sizeof(int) + (REG <= 8 ? REG / 4 * kWaves * 2 * sizeof(uint32_t) : kItemListCap * sizeof(float));
 
+// Result `i` of an item for the host, which watches the words (the lanes that have one come here).
+__device__ __forceinline__ void post_word(uint64_t* words, int64_t i, uint32_t tag, uint32_t value) {
+  __hip_atomic_store(words + i, (static_cast<uint64_t>(tag) << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 template <int REG>
 __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   constexpr int kQ = REG / 4;
@@ -788,6 +794,7 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
       a.blk_counts[it.blk0 + tid] =
           make_int4(fill == 16 ? n : 0, fill == 8 ? n : 0, fill == 4 ? n : 0, fill == 2 ? n : 0);
     }
+    if (a.post.counts && tid < 4) post_word(a.post.counts, 4 * static_cast<int64_t>(item) + tid, a.post.tag, fill == (16 >> tid) ? U : 0);
     return;
   }
   __syncthreads();                         // the list is not read any more
@@ -822,8 +829,10 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
   }
   if (a.blk_counts) {
     __syncthreads();
+    if (wave > 0) return;
+    static_assert(REG <= 32, "a lane per block, and counts of 16 bits");
+    uint32_t even = 0, odd = 0;            // tiers 16 and 4; 8 and 2
     if (tid < nblk) {                      // block tid: wavefronts 4 tid .. 4 tid + 3 of the rounds in one line
-      uint32_t even = 0, odd = 0;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const uint32_t x = s_cnt[8 * tid + i];
@@ -831,6 +840,12 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
         odd += (x >> 8) & 0x00FF00FFu;
       }
       a.blk_counts[it.blk0 + tid] = make_int4(even & 0xFFFF, odd & 0xFFFF, even >> 16, odd >> 16);
+    }
+    if (a.post.counts) {
+      even = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_scan(even)), 63));
+      odd = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_scan(odd)), 63));
+      const uint32_t pair = tid & 1 ? odd : even;
+      if (tid < 4) post_word(a.post.counts, 4 * static_cast<int64_t>(item) + tid, a.post.tag, tid & 2 ? pair >> 16 : pair & 0xFFFF);
     }
   }
 }
@@ -1251,10 +1266,23 @@ __global__ __launch_bounds__(64) void channel_allocate_kernel(ChannelArgs c) {
 #pragma unroll
     for (int k = 0; k < kThr; ++k) t[k] = S.have ? P.thr(S.best, k) : INFINITY;
   }
+  int tier[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     int above[kThr];
-    bits[64 * j + lane] = static_cast<uint8_t>(fill >= 0 ? fill : tier_of(P, v[j], t, above));
+    tier[j] = fill >= 0 ? fill : tier_of(P, v[j], t, above);
+    bits[64 * j + lane] = static_cast<uint8_t>(tier[j]);
+  }
+  if (a.post.channels) {                   // word 4 k + p: which of the channels 32 p .. 32 p + 31 have 16 >> k bits
+    uint32_t word = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint64_t mask = __ballot(tier[j] == 16 >> k);
+        if (lane >> 1 == 2 * k + j) word = static_cast<uint32_t>(lane & 1 ? mask >> 32 : mask);
+      }
+    if (lane < 16) post_word(a.post.channels, 16 * static_cast<int64_t>(item) + lane, a.post.tag, word);
   }
   if (lane == 0) report(a, item, fill < 0, S);
 }
@@ -1339,11 +1367,12 @@ size_t allocate_scratch_bytes(int n_items, int max_U) {
 
 // Token maps of all items.  d_order (where allocate_needs_order): the items, the n_long of more than allocate_short_units()
 // first, the others with up to max_short units.  blk_counts: what the packing stage needs, or null.
+// post: where the items' counts go for the host, which only the launch of whole items does (up to allocate_short_units units).
 // raw: the weights before the pooling (window pool > 1), which the search then does itself; w is memory for the pooled ones.
 hipError_t launch_allocate(const float* raw, int pool, float* w, const Batch& batch, int max_U, const int32_t* d_order, int n_long,
                            int max_short, int n_hull, const int* hull_tiers,
                            const double* hull_r, double need_frac, int max_iters, uint8_t* bits, double* lam_out,
-                           int32_t* iters_out, int32_t* blk_counts, void* scratch, hipStream_t st) {
+                           int32_t* iters_out, int32_t* blk_counts, const CountPost& post, void* scratch, hipStream_t st) {
   const int n_items = batch.n_seqs * batch.hkv;
   if (n_items == 0) return hipSuccess;
   if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
@@ -1354,7 +1383,10 @@ hipError_t launch_allocate(const float* raw, int pool, float* w, const Batch& ba
     a.pool = pool;
     a.pool_inv = 1.0f / static_cast<float>(pool);
   }
-  if (max_U <= kItemUnits) return launch_short_items(a, n_items, max_U, st);
+  if (max_U <= kItemUnits) {
+    if (a.blk_counts) a.post = post;
+    return launch_short_items(a, n_items, max_U, st);
+  }
   if (!scratch || (!d_order && n_items > kMostTogether)) return hipErrorInvalidValue;
   if (!d_order) return launch_items_together(a, n_items, max_U, scratch, st);
   for (int first = 0; first < n_long; first += kMostTogether) {
@@ -1370,13 +1402,14 @@ hipError_t launch_allocate(const float* raw, int pool, float* w, const Batch& ba
 hipError_t launch_allocate_channels(const float* w_ch, const Batch& batch, const int32_t* blk_counts, double rk, int n_hull,
                                     const int* hull_tiers,
                                     const double* hull_r, double need_frac, int max_iters, uint8_t* bits_ch,
-                                    double* lam_out, int32_t* iters_out, hipStream_t st) {
+                                    double* lam_out, int32_t* iters_out, const CountPost& post, hipStream_t st) {
   const int n_items = batch.n_seqs * batch.hkv;
   if (n_items == 0) return hipSuccess;
   if (n_hull < 1 || n_hull > kMaxHull) return hipErrorInvalidValue;
   ChannelArgs c;
   c.a = make_args(w_ch, batch, n_hull, hull_tiers, hull_r, need_frac, max_iters, bits_ch, lam_out, iters_out);
   c.blk_counts = reinterpret_cast<const int4*>(blk_counts); c.rk = rk;
+  c.a.post = post;
   hipLaunchKernelGGL(channel_allocate_kernel, dim3(n_items), dim3(64), 0, st, c);
   return hipGetLastError();
 }

@@ -209,6 +209,14 @@ hipError_t launch_copy(const CopyArgs& a, hipStream_t st);
 // The same for a stream under capture: segments out of host memory only, whose bytes the recorded launches carry themselves.
 hipError_t launch_copy_by_value(const CopyArgs& a, hipStream_t st);
 
+// What the search's kernels leave for the host in staging memory by themselves: words of (tag, value), and the host watches
+// each.  Null: nobody waits.
+struct CountPost {
+  uint64_t* counts;                    // [items][4]: units in tiers 16, 8, 4, 2
+  uint64_t* channels;                  // [items][4 tiers][4]: which of 32 channels each have the tier's width
+  uint32_t tag;
+};
+
 struct DenseArgs {
   const uint16_t* K;
   const uint16_t* V;

@@ -94,11 +94,11 @@ __device__ __forceinline__ int item_slots(const WeightArgs& a, int item, int* fi
 }
 
 // The log-sum-exp (log2 domain) of a row of an item of n <= MANY runs (p: the first one's), with the additions of
-// row_lse_kernel, whose sixteen threads have at most two runs each then.
-constexpr int kFewRuns = 32;
+// row_lse_kernel, whose sixteen threads have at most three runs each then.
+constexpr int kFewRuns = 34;
 template <int MANY>
 __device__ __forceinline__ float lse_of_few(const float2* p, int row_slots, int n) {
-  static_assert(MANY <= 32, "two runs a thread");
+  static_assert(MANY <= 48, "three runs a thread");
   float2 v[MANY];
 #pragma unroll
   for (int k = 0; k < MANY; ++k) v[k] = p[static_cast<int64_t>(min(k, n - 1)) * row_slots];     // (the last one repeated, without a branch)
@@ -109,9 +109,12 @@ __device__ __forceinline__ float lse_of_few(const float2* p, int row_slots, int 
   for (int k = 0; k < min(MANY, 16); ++k) {
     float own = v[k].x, sum = k < n ? v[k].y : 0.f;
     if (k + 16 < MANY) {
-      const float2 hi = v[(k + 16) % MANY];
+      const float2 hi = v[(k + 16) % MANY], top = v[(k + 32) % MANY];
+      const bool third = k + 32 < MANY && k + 32 < n;
       own = k + 16 < n ? fmaxf(own, hi.x) : own;
+      if (k + 32 < MANY) own = third ? fmaxf(own, top.x) : own;
       sum = sum * fast_exp2(v[k].x - own) + (k + 16 < n ? hi.y * fast_exp2(hi.x - own) : 0.f);
+      if (k + 32 < MANY) sum += third ? top.y * fast_exp2(top.x - own) : 0.f;
     }
     l += sum * fast_exp2(own - m);
   }
@@ -678,6 +681,13 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   a.R = a.g * cfg.s_obs; a.row_slots = row_slots_of(a.R); a.causal = cfg.causal ? 1 : 0;
   a.n_items = static_cast<int32_t>(n_items); a.n_tiles = static_cast<int32_t>(n_tiles);
   a.workgroups = workgroups_of(n_tiles, kPass1PerCu);
+  // Where every tile has a workgroup, half as many if that spares the launch of the log-sum-exp (below): compressing 8 x 3800 tokens
+  // 60.6 -> 56.9 us, 2 x 4K 55.9 -> 53.6.  (Three or four tiles a run: 2 x 7000 tokens 56.8 -> 59.5; 256 rows, whose sums every
+  // workgroup reads: 4 x 4000 tokens 54.4 -> 55.4.)  Also with channel weights, which have that launch anyway, so that the token weights
+  // are the same bits with and without (8 x 3800 tokens 75.7 -> 74.4 us, 2 x 4K 63.4 -> 64.3).
+  const int64_t most_tiles = (max_T + kKeyTile - 1) / kKeyTile;
+  if (a.R <= 128 && a.workgroups == n_tiles && most_tiles > kFewRuns && (most_tiles + 1) / 2 + 1 <= kFewRuns)
+    a.workgroups = static_cast<int>((n_tiles + 1) / 2);
   const int64_t slots = a.workgroups + n_items;
   a.row_part = scratch;
   a.lse = a.row_part + slots * a.row_slots * 2;
@@ -686,7 +696,7 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   // pass 2 against pass 2: 16 x 1K tokens 3.9 + 16.0 -> 16.0 us, 4 x 8K (17 runs) 4.2 + 20.1 -> 21.5, 128 items of 20K tokens
   // 5.4 + 185.6 -> 188.8.  Eight items have 65 runs each, and every workgroup would read them: 32K tokens 4.7 + 18.5 -> 22.7, 128K
   // tokens and 256 rows 5.3 + 78 -> 88.
-  const int64_t most_runs = static_cast<int64_t>((max_T + kKeyTile - 1) / kKeyTile) * a.workgroups / n_tiles + 2;
+  const int64_t most_runs = a.workgroups == n_tiles ? most_tiles : most_tiles * a.workgroups / n_tiles + 2;
   if (!w_ch && most_runs <= kFewRuns && n_tiles < (1 << 22)) a.lse = nullptr;
   a.ksq_part = w_ch ? a.w_raw + total_tokens : nullptr;
   if (a.R <= 64) launch_passes<1, 2>(a, w_ch, st);

@@ -281,7 +281,8 @@ rdkv_status rdkv_decode_attn_bf16_noalloc(const void* K, const void* V, const in
 /*
  * Measurement aid (benchmarks).  While enabled, the calls above bracket their
  * kernels with HIP events on the call's own stream: the decode launch of
- * rdkv_decode_attn (merge included), the split-K kernel of rdkv_decode_attn_bf16,
+ * rdkv_decode_attn (merge included), the split-K kernel of rdkv_decode_attn_bf16 (which
+ * merges, too, where an item has few partials),
  * every kernel of rdkv_weights, every kernel of rdkv_allocate, and the kernels of
  * rdkv_pack in two or three brackets (tier counts, where the allocation has not
  * counted, and position lists before the call's one wait; quantize and pack after it;

@@ -125,13 +125,16 @@ __device__ __forceinline__ void partial_stores_done() { asm volatile("s_waitcnt 
 // reduces its slots with running maxima, and the SG groups are combined through LDS.  Sixteen bytes of a partial and one
 // (maximum, sum) pair per load -- with one channel and all heads per thread (96 loads instead of 16 at g = 4) the merge of
 // 21 slots took 2.75 us of a 12.3 us launch.
-template <int NT, int G>
+// THROUGH: the output goes through to memory like the partials (rows that other XCDs have stored to in this launch)
+template <int NT, int G, int kBatch = 8, bool THROUGH = false>
 __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int slot0, int nslots, float* smem) {
   constexpr int kCols = G * kHeadDim / 4;
   constexpr int SG = NT / kCols;
   static_assert(SG >= 1, "a workgroup covers a slot's partial");
-  constexpr int kBatch = 8;
   const int tid = threadIdx.x;
+  const auto put = [](float* p, float v) __attribute__((always_inline)) {
+    if constexpr (THROUGH) store_agent(p, v); else *p = v;
+  };
   const int col = tid & (kCols - 1), sg = tid / kCols, hd = col >> 5;
   float* s_m = smem + 16;                   // [SG][G]
   float* s_l = s_m + SG * G;                // [SG][G]
@@ -174,7 +177,7 @@ __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int sl
   if constexpr (SG == 1) {
     float* o = ma.out + qh0 * kHeadDim + 4 * col;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = l_run > 0.f ? o_run[k] / l_run : 0.f;
+    for (int k = 0; k < 4; ++k) put(o + k, l_run > 0.f ? o_run[k] / l_run : 0.f);
     if ((col & 31) == 0 && ma.lse != nullptr)
       ma.lse[qh0 + hd] = l_run > 0.f ? (m_run + __log2f(l_run)) * 0.6931471805599453f : -INFINITY;
     return;
@@ -194,7 +197,7 @@ __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int sl
       l = __builtin_fmaf(s_l[k * G + h], f, l);
       t = __builtin_fmaf(s_red[k * G * kHeadDim + idx], f, t);
     }
-    ma.out[qh0 * kHeadDim + idx] = l > 0.f ? t / l : 0.f;
+    put(ma.out + qh0 * kHeadDim + idx, l > 0.f ? t / l : 0.f);
     if ((idx & 127) == 0 && ma.lse != nullptr)
       ma.lse[qh0 + h] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
   }

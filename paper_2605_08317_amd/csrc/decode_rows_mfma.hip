@@ -11,14 +11,69 @@ using namespace tile;
 constexpr int kRowsWaves = 4;
 constexpr int kRowsWG = kRowsWaves * 64;
 
+// The merge inside the launch.  The caller's workspace holds no counter that starts at zero, and nothing else outlives the call, so
+// chunks announce themselves by the launch's tag, in the item's own output rows, which hold whatever they held before (two words a
+// chunk, NaNs that neither a result nor an earlier launch leaves).  A chunk stores its partial, its tag once that has landed, and
+// looks at all of the item's tags once its own has: the chunk whose tag lands last finds all of them, or finds that another one
+// has, and has begun to write the rows.  Several may find all of them; they write the same bits.  Nothing waits for anybody, and the
+// merge leaves no tag behind (a replayed launch has the same one).
+// What bounds it is four round trips to memory: partial, tag, tags, partials; and with many partials one compute unit's reading of
+// them (dense_together in rdkv_api.hip has the line and what was measured on both sides of it).
+template <int HS>
+__device__ __forceinline__ void merge_tagged(const DenseArgs& a, int item, int slot0, int split, int n, int g, uint8_t* smem) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  uint32_t* tags = reinterpret_cast<uint32_t*>(a.out + static_cast<int64_t>(item) * g * kHeadDim);
+  merge::partial_stores_done();
+  __syncthreads();
+  if (n > 1) {
+    int* s_all = reinterpret_cast<int*>(smem);
+    if (tid < 64) {
+      if (lane < 2) __hip_atomic_store(tags + 2 * split + lane, a.tag[lane & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      merge::partial_stores_done();
+      bool there = true;
+      if (lane < n) {
+        const uint32_t t0 = __hip_atomic_load(tags + 2 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t t1 = __hip_atomic_load(tags + 2 * lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        there = t0 == a.tag[0] && t1 == a.tag[1];
+      }
+      const bool all = __all(there);
+      if (tid == 0) *s_all = all;
+    }
+    __syncthreads();
+    if (*s_all == 0) return;
+    __syncthreads();                    // the merge uses that memory
+  }
+  const MergeArgs ma{a.part_acc, a.part_ml, nullptr, a.out, a.lse, g, 0, 0};
+  float* s = reinterpret_cast<float*>(smem);
+  // (one round trip for all that dense_together lets come here)
+  if constexpr (HS == 2) {
+    if (n <= 8) merge::merge_item<kRowsWG, 8, 8, true>(ma, item, slot0, n, s);
+    else merge::merge_item<kRowsWG, 8, 16, true>(ma, item, slot0, n, s);
+  } else if (g == 4) {
+    if (n <= 16) merge::merge_item<kRowsWG, 4, 8, true>(ma, item, slot0, n, s);
+    else merge::merge_item<kRowsWG, 4, 16, true>(ma, item, slot0, n, s);
+  } else if (g == 2) {
+    merge::merge_item<kRowsWG, 2, 16, true>(ma, item, slot0, n, s);
+  } else {
+    merge::merge_item<kRowsWG, 1, 8, true>(ma, item, slot0, n, s);
+  }
+}
+
 template <int HS>
 __global__ __launch_bounds__(kRowsWG, 2) void decode_dense_mfma_kernel(DenseArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int split = blockIdx.x, head = blockIdx.y, sl = blockIdx.z;
   const int T = a.T[sl];
   const int row0 = split * a.chunk_rows;
-  if (row0 >= T) return;
   const int g = a.hq / a.hkv;
+  if (row0 >= T) {
+    if (split == 0 && a.tag[0] != 0) {  // no rows at all, and no merge launch
+      const int64_t qh0 = static_cast<int64_t>(a.seq_base + sl) * a.hq + head * g;
+      for (int i = threadIdx.x; i < g * kHeadDim; i += kRowsWG) a.out[qh0 * kHeadDim + i] = 0.f;
+      if (a.lse != nullptr && static_cast<int>(threadIdx.x) < g) a.lse[qh0 + threadIdx.x] = -INFINITY;
+    }
+    return;
+  }
   const int rows = min(a.chunk_rows, T - row0);
   const int64_t first = a.row_off[sl] + static_cast<int64_t>(head) * T + row0;
   const uint8_t* kd = reinterpret_cast<const uint8_t*>(a.K) + first * (kHeadDim * 2);
@@ -27,7 +82,9 @@ __global__ __launch_bounds__(kRowsWG, 2) void decode_dense_mfma_kernel(DenseArgs
   const uint16_t* q = a.q + (static_cast<int64_t>(seq) * a.hq + head * g) * kHeadDim;
   const int64_t slot = (static_cast<int64_t>(sl) * a.hkv + head) * a.max_splits + split;
   process_rows_mfma<HS, false, kRowsWaves>(kd, vd, rows, g, q, smem, a.part_acc + slot * g * kHeadDim, a.part_ml + slot * g * 2,
-                               nullptr, nullptr);
+                               nullptr, nullptr, a.tag[0] != 0);
+  if (a.tag[0] != 0)
+    merge_tagged<HS>(a, seq * a.hkv + head, static_cast<int>(slot) - split, split, (T + a.chunk_rows - 1) / a.chunk_rows, g, smem);
 }
 
 template <int HS>

@@ -1,6 +1,8 @@
 // Host side of librdkv: argument validation, planning (segment table, split
 // schedule) and kernel launches behind the C ABI of include/rdkv.h.
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -604,6 +606,36 @@ void dense_plan(const int32_t* seq_lens, int batch, int hkv, int g, int* chunk_r
   int64_t cr = round_up(std::max<int64_t>(256, (total + resident - 1) / resident), 64);
   *chunk_rows = static_cast<int>(cr);
   *max_splits = std::max(1, static_cast<int>((max_T + cr - 1) / cr));
+}
+
+// Whether the launch merges its own partials (merge_tagged) instead of a second launch with a workgroup per query head.  The second
+// launch takes the GPU 4.5 us and the host 3 (calls of less than 11.5 us are bound by the host with it, of 8.5 without).  One
+// workgroup per item that reads all of its partials takes 2.7 us and 0.04 to 0.1 more for each of them: a win up to 48 of them
+// (microseconds a call, two launches and one; chunks of an item x query heads per KV head):
+//   2 items of 2K rows, 8 x 4      11.7   8.5      8 items of 8K, 32 x 1      11.8  10.7      128 items of 2K to 4K, 5 x 4   48.2  47.4
+// and, over at most 16 MiB of rows, up to 64, at four heads 96:
+//   8 items of 4K, 16 x 4          12.2   8.6      2 items of 6K, 24 x 4      12.4  10.8
+// Beyond either, one compute unit's reading takes longer than the launch:
+//   8 items of 8K, 32 x 4          11.8  13.8      32 items of 4K to 8K, 16 x 4  23.0  23.4   8 items of 32K, 64 x 4         29.3  32.7
+// or does so where a graph replays the call and the host is out of it (2 items of 2K, 8 x 4: 8.9, 8.1; 2 of 6K, 24 x 4: 9.1, 9.2; 8 of
+// 4K, 16 x 8: 10.8, 11.3; 2 of 12K, 47 x 2: 9.3, 9.5).
+constexpr int kDenseTagged = 64;       // chunks of an item that have room for their tags in its output rows, a lane each
+static_assert(2 * kDenseTagged <= kHeadDim, "one query head's row");
+bool dense_together(const int32_t* seq_lens, int batch, int hkv, int g, int max_splits) {
+  const int partials = g * max_splits;
+  if (max_splits > kDenseTagged || partials > (g == 4 ? 96 : 64)) return false;
+  if (partials <= 48) return true;
+  int64_t rows = 0;
+  for (int s = 0; s < batch; ++s) rows += static_cast<int64_t>(seq_lens[s]) * hkv;
+  return rows * (4 * kHeadDim) <= (static_cast<int64_t>(16) << 20);
+}
+
+// A tag that no other launch of the process has (DenseArgs::tag): two NaN patterns with 40 bits of a number between them, odd, so
+// that they are no value of a bf16 number's bits either.
+void next_tag(uint32_t (&tag)[2]) {
+  static std::atomic<uint64_t> next{static_cast<uint64_t>(std::chrono::steady_clock::now().time_since_epoch().count()) * 0x9E3779B97F4A7C15ull};
+  const uint64_t id = next.fetch_add(1, std::memory_order_relaxed);
+  for (int i = 0; i < 2; ++i) tag[i] = 0xFFE00001u | (static_cast<uint32_t>(id >> (20 * i)) & 0xFFFFFu) << 1;
 }
 
 // What a cache owns on the device.  rdkv_pack takes one block for the arena and every table (one trip through the
@@ -2183,6 +2215,12 @@ rdkv_status rdkv_decode_attn_bf16(const void* K, const void* V, const int32_t* s
   int chunk_rows, max_splits;
   dense_plan(seq_lens, batch, hkv, hq / hkv, &chunk_rows, &max_splits);
   const int64_t slots = static_cast<int64_t>(std::min(batch, kDenseMaxSeqs)) * hkv * max_splits;
+  // (a query in the output's memory has to be read before that is written)
+  const uint8_t* const q0 = static_cast<const uint8_t*>(q);
+  const uint8_t* const o0 = reinterpret_cast<const uint8_t*>(out);
+  const size_t heads = static_cast<size_t>(batch) * hq * kHeadDim;
+  const bool apart = q0 + heads * sizeof(uint16_t) <= o0 || o0 + heads * sizeof(float) <= q0;
+  const bool together = apart && dense_together(seq_lens, batch, hkv, g, max_splits);
   int64_t row_off = 0;
   for (int s0 = 0; s0 < batch; s0 += kDenseMaxSeqs) {
     const int ns = std::min(kDenseMaxSeqs, batch - s0);
@@ -2195,6 +2233,8 @@ rdkv_status rdkv_decode_attn_bf16(const void* K, const void* V, const int32_t* s
     a.out = out;
     a.lse = lse;
     a.hq = hq; a.hkv = hkv; a.batch = batch; a.chunk_rows = chunk_rows; a.max_splits = max_splits; a.seq_base = s0;
+    a.tag[0] = a.tag[1] = 0;
+    if (together) next_tag(a.tag);
     for (int i = 0; i < ns; ++i) {
       a.T[i] = seq_lens[s0 + i];
       a.row_off[i] = row_off;
@@ -2205,7 +2245,7 @@ rdkv_status rdkv_decode_attn_bf16(const void* K, const void* V, const int32_t* s
       TimedScope ts(RDKV_TIME_DECODE_BF16, st);
       RDKV_HIP(launch_decode_dense_split(a, g, ns, st));
     }
-    RDKV_HIP(launch_decode_dense_merge(a, g, ns, st));
+    if (!together) RDKV_HIP(launch_decode_dense_merge(a, g, ns, st));
   }
   return RDKV_OK;
 }

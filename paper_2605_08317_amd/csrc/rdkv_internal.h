@@ -226,6 +226,7 @@ struct DenseArgs {
   float* out;
   float* lse;
   int32_t hq, hkv, batch, chunk_rows, max_splits, seq_base;
+  uint32_t tag[2];     // of this launch, which merges its own partials; or zeros: a merge launch follows
   int32_t T[kDenseMaxSeqs];
   int64_t row_off[kDenseMaxSeqs];           // first row of the sequence block in K / V
 };

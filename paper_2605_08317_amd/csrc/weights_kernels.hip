@@ -49,6 +49,8 @@ struct WeightArgs {
   int32_t hq, hkv, g, s_obs, R, row_slots, causal;   // row_slots: R in whole sweeps of row groups
   int32_t n_items, n_tiles;      // items, key tiles of all of them
   int32_t workgroups;            // pass 1
+  int32_t sum_workgroups;        // pass 2, of those that sum
+  float* w_ch;                   // [items][128]: where pass 2's other workgroups leave the channel weights, or null
   Batch batch;
 };
 
@@ -121,10 +123,48 @@ __device__ __forceinline__ float lse_of_few(const float2* p, int row_slots, int 
   return l > 0.f ? m + __log2f(l) : INFINITY;
 }
 
+// w_c = ||Q[:,c]|| ||K[:,c]|| / sqrt(d): finishes the K sums of squares and adds the probe's column norms; a workgroup has
+// kChannelPart channels of an item, 8 threads per channel share the runs and the window rows (fixed order of additions).
+// Part of row_lse_kernel's launch, or of pass 2's where it makes the log-sum-exp itself: all need what pass 1 leaves (as a launch of
+// its own 4 us of a pass over 8 x 50K keys).
+constexpr int kChannelPart = 32;
+__device__ __forceinline__ void channel_weights(const WeightArgs& a, float* __restrict__ w_ch, int item, int part) {
+  static_assert(8 * kChannelPart == 256, "the threads of the kernels");
+  __shared__ float s_k[8][kChannelPart], s_q[8][kChannelPart];
+  const int lc = threadIdx.x & (kChannelPart - 1), sub = threadIdx.x / kChannelPart;
+  const int c = part * kChannelPart + lc;
+  int slot0;
+  const int n = item_slots(a, item, &slot0);
+  const int64_t b0 = slot0;
+  float ksq = 0.f;
+#pragma unroll 8
+  for (int b = sub; b < n; b += 8) ksq += a.ksq_part[(b0 + b) * kHeadDim + c];
+  const int seq = item / a.hkv, head = item % a.hkv;
+  const uint16_t* Qg = a.Q + (static_cast<int64_t>(seq) * a.hq + head * a.g) * a.s_obs * kHeadDim;
+  float qsq = 0.f;
+#pragma unroll 8
+  for (int r = sub; r < a.R; r += 8) {
+    const float q = __uint_as_float(static_cast<uint32_t>(Qg[r * kHeadDim + c]) << 16);
+    qsq = __builtin_fmaf(q, q, qsq);
+  }
+  s_k[sub][lc] = ksq;
+  s_q[sub][lc] = qsq;
+  __syncthreads();
+  if (sub == 0) {
+    ksq = qsq = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      ksq += s_k[k][lc];
+      qsq += s_q[k][lc];
+    }
+    w_ch[static_cast<int64_t>(item) * kHeadDim + c] = sqrtf(qsq) * sqrtf(ksq) * 0.08838834764831845f;
+  }
+}
+
 // One workgroup = one run of key tiles against all window rows of their items.
 //   NRT  32-row tiles of window rows per wavefront: 2, or 1 when the item has at most 64 rows
 //   RGW  row groups (of 32 NRT rows) worked on at a time: 4, or 2 when the item has at most 128 rows
-//   KSQ  pass 1 also sums the squares of K per channel
+//   KSQ  pass 1 also sums the squares of K per channel; pass 2 has workgroups behind the others that finish the channel weights
 // A wavefront owns row group wave % RGW and, of the two 32-key steps of a tile, both (RGW = 4) or one; more than four
 // row groups take a second sweep over the run.
 // The LDS image of a key tile is row-major with the 16-byte pieces of key r at position piece ^ (r % 16), which spreads
@@ -152,7 +192,18 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&s_keys[0][0]));   // LDS byte address
   const int prow = tid >> 4, piece = (tid & 15) ^ (prow & 15);   // this thread's key rows prow + 16 k and piece of the key
 
-  const int run0 = first_tile(blockIdx.x, gridDim.x, a.n_tiles), run1 = first_tile(blockIdx.x + 1, gridDim.x, a.n_tiles);
+  constexpr bool kSquares = PASS == 1 && KSQ;
+  int workgroups = gridDim.x;
+  if constexpr (PASS == 2 && KSQ) {
+    workgroups = a.sum_workgroups;
+    if (static_cast<int>(blockIdx.x) >= workgroups) {
+      constexpr int kParts = kHeadDim / kChannelPart;
+      const int k = static_cast<int>(blockIdx.x) - workgroups;
+      channel_weights(a, a.w_ch, k / kParts, k % kParts);
+      return;
+    }
+  }
+  const int run0 = first_tile(blockIdx.x, workgroups, a.n_tiles), run1 = first_tile(blockIdx.x + 1, workgroups, a.n_tiles);
   int seq = 0;                             // the sequence of tile run0: the last one that starts at or before it
   for (int s0 = 0; s0 < a.batch.n_seqs && a.batch.n_seqs > 1; s0 += 64) {
     const int s = s0 + lane;
@@ -182,7 +233,7 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
   // leading tiles of 64 valid keys that every row may look at (keys up to T - s_obs)
   const int n_plain = max(0, min(key1, a.causal ? T - a.s_obs + 1 : T) - key0) / kKeyTile;
   float ksq[8];
-  if constexpr (KSQ) {
+  if constexpr (kSquares) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) ksq[j] = 0.f;
   }
@@ -212,7 +263,7 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
       fetch(t + kBuffers - 1, cur == 0 ? kBuffers - 1 : cur - 1);
       const uint8_t* buf = s_keys[cur];
       cur = cur + 1 == kBuffers ? 0 : cur + 1;
-      if constexpr (KSQ) {
+      if constexpr (kSquares) {
         if (squares && sweep == 0) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
@@ -507,7 +558,7 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
     __syncthreads();                      // before the next sweep's keys overwrite the buffers
   }
 
-  if constexpr (KSQ) {
+  if constexpr (kSquares) {
     // threads with the same piece of the key: prow differs; thread (prow, piece) holds channels 8 piece .. + 7
     float* s_k = reinterpret_cast<float*>(s_keys[0]);       // [16 prow][128]
 #pragma unroll
@@ -524,48 +575,11 @@ __global__ __launch_bounds__(256, PASS == 1 ? kPass1PerCu : kPass2PerCu) void we
   }   // items of the run
 }
 
-// w_c = ||Q[:,c]|| ||K[:,c]|| / sqrt(d): finishes the K sums of squares and adds the probe's column norms; a workgroup has
-// kChannelPart channels of an item, 8 threads per channel share the runs and the window rows (fixed order of additions).
-// Part of row_lse_kernel's launch: both need what pass 1 leaves (as a launch of its own 4 us of a pass over 8 x 50K keys).
-constexpr int kChannelPart = 32;
-__device__ __forceinline__ void channel_weights(const WeightArgs& a, float* __restrict__ w_ch, int part) {
-  static_assert(8 * kChannelPart == 256, "the threads of row_lse_kernel");
-  __shared__ float s_k[8][kChannelPart], s_q[8][kChannelPart];
-  const int item = blockIdx.y, lc = threadIdx.x & (kChannelPart - 1), sub = threadIdx.x / kChannelPart;
-  const int c = part * kChannelPart + lc;
-  int slot0;
-  const int n = item_slots(a, item, &slot0);
-  const int64_t b0 = slot0;
-  float ksq = 0.f;
-#pragma unroll 8
-  for (int b = sub; b < n; b += 8) ksq += a.ksq_part[(b0 + b) * kHeadDim + c];
-  const int seq = item / a.hkv, head = item % a.hkv;
-  const uint16_t* Qg = a.Q + (static_cast<int64_t>(seq) * a.hq + head * a.g) * a.s_obs * kHeadDim;
-  float qsq = 0.f;
-#pragma unroll 8
-  for (int r = sub; r < a.R; r += 8) {
-    const float q = __uint_as_float(static_cast<uint32_t>(Qg[r * kHeadDim + c]) << 16);
-    qsq = __builtin_fmaf(q, q, qsq);
-  }
-  s_k[sub][lc] = ksq;
-  s_q[sub][lc] = qsq;
-  __syncthreads();
-  if (sub == 0) {
-    ksq = qsq = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      ksq += s_k[k][lc];
-      qsq += s_q[k][lc];
-    }
-    w_ch[static_cast<int64_t>(item) * kHeadDim + c] = sqrtf(qsq) * sqrtf(ksq) * 0.08838834764831845f;
-  }
-}
-
 // log-sum-exp of every window row over the runs of its item (log2 domain): 16 rows per workgroup, 16 threads stride
 // over a row's runs; the workgroups behind them: the channel weights, where they are wanted
 __global__ __launch_bounds__(256) void row_lse_kernel(WeightArgs a, float* __restrict__ w_ch) {
   if (static_cast<int>(blockIdx.x) * 16 >= a.row_slots) {
-    channel_weights(a, w_ch, static_cast<int>(blockIdx.x) - a.row_slots / 16);
+    channel_weights(a, w_ch, blockIdx.y, static_cast<int>(blockIdx.x) - a.row_slots / 16);
     return;
   }
   __shared__ float s_m[16][17], s_l[16][17];
@@ -658,7 +672,9 @@ void launch_passes(const WeightArgs& a, float* w_ch, hipStream_t st) {
   if (w_ch) hipLaunchKernelGGL((weights_kernel<1, NRT, RGW, true>), dim3(a.workgroups), dim3(256), 0, st, a);
   else hipLaunchKernelGGL((weights_kernel<1, NRT, RGW, false>), dim3(a.workgroups), dim3(256), 0, st, a);
   if (a.lse) hipLaunchKernelGGL(row_lse_kernel, dim3(a.row_slots / 16 + (w_ch ? kHeadDim / kChannelPart : 0), a.n_items), dim3(256), 0, st, a, w_ch);
-  hipLaunchKernelGGL((weights_kernel<2, NRT, RGW, false>), dim3(workgroups_of(a.n_tiles, kPass2PerCu)), dim3(256), 0, st, a);
+  const dim3 sums(a.sum_workgroups), sums_and_channels(a.sum_workgroups + a.n_items * (kHeadDim / kChannelPart));
+  if (a.w_ch) hipLaunchKernelGGL((weights_kernel<2, NRT, RGW, true>), sums_and_channels, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((weights_kernel<2, NRT, RGW, false>), sums, dim3(256), 0, st, a);
 }
 
 }  // namespace
@@ -683,8 +699,7 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   a.workgroups = workgroups_of(n_tiles, kPass1PerCu);
   // Where every tile has a workgroup, half as many if that spares the launch of the log-sum-exp (below): compressing 8 x 3800 tokens
   // 60.6 -> 56.9 us, 2 x 4K 55.9 -> 53.6.  (Three or four tiles a run: 2 x 7000 tokens 56.8 -> 59.5; 256 rows, whose sums every
-  // workgroup reads: 4 x 4000 tokens 54.4 -> 55.4.)  Also with channel weights, which have that launch anyway, so that the token weights
-  // are the same bits with and without (8 x 3800 tokens 75.7 -> 74.4 us, 2 x 4K 63.4 -> 64.3).
+  // workgroup reads: 4 x 4000 tokens 54.4 -> 55.4.)
   const int64_t most_tiles = (max_T + kKeyTile - 1) / kKeyTile;
   if (a.R <= 128 && a.workgroups == n_tiles && most_tiles > kFewRuns && (most_tiles + 1) / 2 + 1 <= kFewRuns)
     a.workgroups = static_cast<int>((n_tiles + 1) / 2);
@@ -695,9 +710,12 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   // An item of few runs needs no launch of its own for the log-sum-exp: pass 2 makes it while its first keys arrive.  Launch +
   // pass 2 against pass 2: 16 x 1K tokens 3.9 + 16.0 -> 16.0 us, 4 x 8K (17 runs) 4.2 + 20.1 -> 21.5, 128 items of 20K tokens
   // 5.4 + 185.6 -> 188.8.  Eight items have 65 runs each, and every workgroup would read them: 32K tokens 4.7 + 18.5 -> 22.7, 128K
-  // tokens and 256 rows 5.3 + 78 -> 88.
+  // tokens and 256 rows 5.3 + 78 -> 88.  The channel weights go along with whichever launch makes it: with
+  // pass 2 passes over 5 x 1K tokens of 4 heads 126.7 -> 122.2 us, 11 x 0.8K of 8 128.5 -> 126.4, 5 x 8K of 4 111.2 -> 110.2.
   const int64_t most_runs = a.workgroups == n_tiles ? most_tiles : most_tiles * a.workgroups / n_tiles + 2;
-  if (!w_ch && most_runs <= kFewRuns && n_tiles < (1 << 22)) a.lse = nullptr;
+  if (most_runs <= kFewRuns && n_tiles < (1 << 22)) a.lse = nullptr;
+  a.sum_workgroups = workgroups_of(n_tiles, kPass2PerCu);
+  a.w_ch = a.lse ? nullptr : w_ch;
   a.ksq_part = w_ch ? a.w_raw + total_tokens : nullptr;
   if (a.R <= 64) launch_passes<1, 2>(a, w_ch, st);
   else if (a.R <= 128) launch_passes<2, 2>(a, w_ch, st);

@@ -1,6 +1,6 @@
 """Token weights of short items, whose key tiles have a workgroup each or one for two, on both sides of the lines: 34 and 35 tiles (a
 workgroup each and 34 runs; pairs), 66 and 67 (34 runs of pairs; a launch for the log-sum-exp), 512 and 513 tiles in all, items that
-start in the middle of a pair.  Against the oracle, and the same bits with channel weights, for which that launch always runs."""
+start in the middle of a pair.  Against the oracle, and the same bits with channel weights."""
 import numpy as np
 import pytest
 import torch

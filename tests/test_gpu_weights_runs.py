@@ -58,7 +58,7 @@ def test_weights_over_row_and_tile_edges(seq_lens, hq, hkv, s_obs, causal, spike
         np.testing.assert_allclose(w_ch[s * hkv:(s + 1) * hkv], O.channel_weights(Ks, _np(Q[s])), rtol=1e-5)
 
 
-# One launch fewer where no item has more than 30 runs (and the channel weights are not wanted): the same additions, so the same bits.
+# One launch fewer where items have few runs, with and without the channel weights: the same additions, so the same bits.
 @pytest.mark.parametrize("seq_lens,hq,hkv,s_obs", [
     ((1,), 2, 2, 1),
     ((1920, 33, 63, 64, 65, 1025), 2, 2, 32),    # 64 rows; 30 runs, 17

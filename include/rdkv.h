@@ -255,6 +255,8 @@ rdkv_status rdkv_decode_attn(const rdkv_cache* cache, const void* q, float* out,
  *   K, V          DEVICE bf16 ragged [hkv][T_s][d] blocks
  *   seq_lens      HOST [batch]
  *   workspace     DEVICE scratch of at least rdkv_decode_bf16_workspace_bytes()
+ * Until the call's last kernel has ended, out may hold anything (items of few partials keep marks of their progress in
+ * their rows).
  */
 size_t rdkv_decode_bf16_workspace_bytes(const int32_t* seq_lens, int32_t batch, int32_t hq,
                                         int32_t hkv, int32_t head_dim);

@@ -16,6 +16,7 @@
 #include <utility>
 
 #include "decode_merge.h"
+#include "dense_plan.h"
 #include "rdkv_internal.h"
 
 namespace rdkv {
@@ -2233,11 +2234,12 @@ rdkv_status rdkv_decode_attn_bf16(const void* K, const void* V, const int32_t* s
   int chunk_rows, max_splits;
   dense_plan(seq_lens, batch, hkv, hq / hkv, &chunk_rows, &max_splits);
   const int64_t slots = static_cast<int64_t>(std::min(batch, kDenseMaxSeqs)) * hkv * max_splits;
-  // (a query in the output's memory has to be read before that is written)
-  const uint8_t* const q0 = static_cast<const uint8_t*>(q);
-  const uint8_t* const o0 = reinterpret_cast<const uint8_t*>(out);
-  const size_t heads = static_cast<size_t>(batch) * hq * kHeadDim;
-  const bool apart = q0 + heads * sizeof(uint16_t) <= o0 || o0 + heads * sizeof(float) <= q0;
+  const size_t heads = static_cast<size_t>(batch) * hq;
+  size_t rows = 0;
+  for (int i = 0; i < batch; ++i) rows += static_cast<size_t>(seq_lens[i]) * hkv;
+  const size_t row = kHeadDim * sizeof(uint16_t);
+  const bool apart = dense_outputs_apart({K, rows * row}, {V, rows * row}, {q, heads * row}, {out, heads * kHeadDim * sizeof(float)},
+                                         {lse, lse ? heads * sizeof(float) : 0});
   const bool together = apart && dense_together(seq_lens, batch, hkv, g, max_splits);
   int64_t row_off = 0;
   for (int s0 = 0; s0 < batch; s0 += kDenseMaxSeqs) {

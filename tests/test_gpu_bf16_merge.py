@@ -72,3 +72,27 @@ def test_query_in_the_outputs_memory():
     inside = out.view(torch.bfloat16).reshape(-1)[-q.numel():].view(q.shape)
     inside.copy_(q)
     _check(b.rdkv_decode_attn_bf16(K, V, list(lens), hkv * g, hkv, inside, out=out), ref)
+
+
+# The outputs in an input's memory, with more workgroups than the chip holds: nothing is written there before all of it is read.
+@pytest.mark.parametrize("lens,hkv,g", [((3000,) * 16, 8, 4), ((0, 300, 700), 2, 4)])
+@pytest.mark.parametrize("what,where,end", [("lse", "q", False), ("lse", "q", True), ("lse", "K", False), ("lse", "V", True), ("out", "q", True),
+                                            ("out", "K", False), ("out", "V", True)])
+def test_outputs_in_an_inputs_memory(lens, hkv, g, what, where, end):
+    b = B()
+    print(f"[case] {what} in {where}, {len(lens)} sequences", flush=True)
+    K, V, q = _inputs(lens, hkv, g, 11)
+    ref = _exact(lens, hkv, g, K, V, q)
+    n = q.numel() if what == "out" else q.shape[0] * q.shape[1]
+    home = torch.zeros(max(4 * n, 2 * {"q": q, "K": K, "V": V}[where].numel()), device="cuda", dtype=torch.uint8)
+    put = home.view(torch.bfloat16)
+    args = {"q": q, "K": K, "V": V}
+    x = args[where]
+    inside = put[put.numel() - x.numel():] if end else put[:x.numel()]
+    inside.copy_(x.reshape(-1))
+    args[where] = inside.view(x.shape)
+    shared = home.view(torch.float32)
+    shared = shared[shared.numel() - n:] if end else shared[:n]
+    outs = {what: shared.view(q.shape if what == "out" else q.shape[:-1])}
+    got = b.rdkv_decode_attn_bf16(args["K"], args["V"], list(lens), hkv * g, hkv, args["q"], **outs)
+    _check(got, ref)

@@ -24,6 +24,7 @@
 
 #include "rdkv_internal.h"
 #include "wave_ops.h"
+#include "weights_plan.h"
 
 namespace rdkv {
 
@@ -97,7 +98,6 @@ __device__ __forceinline__ int item_slots(const WeightArgs& a, int item, int* fi
 
 // The log-sum-exp (log2 domain) of a row of an item of n <= MANY runs (p: the first one's), with the additions of
 // row_lse_kernel, whose sixteen threads have at most three runs each then.
-constexpr int kFewRuns = 34;
 template <int MANY>
 __device__ __forceinline__ float lse_of_few(const float2* p, int row_slots, int n) {
   static_assert(MANY <= 48, "three runs a thread");
@@ -661,9 +661,6 @@ __global__ __launch_bounds__(256) void pool_kernel(const float* __restrict__ w_r
     if (t0 + 256 * j + tid < T) out[t0 + 256 * j + tid] = s[j] / count;
 }
 
-// one round of workgroups (per_cu of them stay resident on a compute unit), at least one tile each
-int workgroups_of(int64_t n_tiles, int per_cu) { return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(n_tiles, 256 * per_cu))); }
-
 // R in whole sweeps of row groups
 int row_slots_of(int R) { return R <= 64 ? 64 : R <= 128 ? 128 : (R + 255) / 256 * 256; }
 
@@ -700,13 +697,8 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   a.hq = cfg.hq; a.hkv = cfg.hkv; a.g = cfg.hq / cfg.hkv; a.s_obs = cfg.s_obs;
   a.R = a.g * cfg.s_obs; a.row_slots = row_slots_of(a.R); a.causal = cfg.causal ? 1 : 0;
   a.n_items = static_cast<int32_t>(n_items); a.n_tiles = static_cast<int32_t>(n_tiles);
-  a.workgroups = workgroups_of(n_tiles, kPass1PerCu);
-  // Where every tile has a workgroup, half as many if that spares the launch of the log-sum-exp (below): compressing 8 x 3800 tokens
-  // 60.6 -> 56.9 us, 2 x 4K 55.9 -> 53.6.  (Three or four tiles a run: 2 x 7000 tokens 56.8 -> 59.5; 256 rows, whose sums every
-  // workgroup reads: 4 x 4000 tokens 54.4 -> 55.4.)
-  const int64_t most_tiles = (max_T + kKeyTile - 1) / kKeyTile;
-  if (a.R <= 128 && a.workgroups == n_tiles && most_tiles > kFewRuns && (most_tiles + 1) / 2 + 1 <= kFewRuns)
-    a.workgroups = static_cast<int>((n_tiles + 1) / 2);
+  const RunPlan runs = run_plan(n_tiles, (max_T + kKeyTile - 1) / kKeyTile, a.R, kPass1PerCu);
+  a.workgroups = runs.workgroups;
   const int64_t slots = a.workgroups + n_items;
   a.row_part = scratch;
   a.lse = a.row_part + slots * a.row_slots * 2;
@@ -716,8 +708,7 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   // 5.4 + 185.6 -> 188.8.  Eight items have 65 runs each, and every workgroup would read them: 32K tokens 4.7 + 18.5 -> 22.7, 128K
   // tokens and 256 rows 5.3 + 78 -> 88.  The channel weights go along with whichever launch makes it: with
   // pass 2 passes over 5 x 1K tokens of 4 heads 126.7 -> 122.2 us, 11 x 0.8K of 8 128.5 -> 126.4, 5 x 8K of 4 111.2 -> 110.2.
-  const int64_t most_runs = a.workgroups == n_tiles ? most_tiles : most_tiles * a.workgroups / n_tiles + 2;
-  if (most_runs <= kFewRuns && n_tiles < (1 << 22)) a.lse = nullptr;
+  if (runs.few) a.lse = nullptr;
   a.sum_workgroups = workgroups_of(n_tiles, kPass2PerCu);
   a.w_ch = a.lse ? nullptr : w_ch;
   a.ksq_part = w_ch ? a.w_raw + total_tokens : nullptr;

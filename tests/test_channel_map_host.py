@@ -1,5 +1,6 @@
 """The channel map as the host reads it, eight channels at a time: the words of a K row of random maps against the rule (every tier's
-channels in whole words, the row to an even number of them), and every value that is no bit-width, in every place."""
+channels in whole words, the row to an even number of them), and every value that is no bit-width, in every place (packing refuses
+a map by the same function)."""
 import ctypes
 
 import numpy as np
@@ -26,7 +27,11 @@ def test_row_words_of_random_maps(seed):
 
 def test_values_that_are_no_width():
     rng = np.random.default_rng(0)
-    for v in set(range(256)) - {0, 2, 4, 8, 16}:
-        bits = rng.choice(np.array([0, 2, 4, 8, 16], np.uint8), size=128)
-        bits[rng.integers(128)] = v
-        assert _words(bits) == -1
+    maps = [rng.choice(np.array([0, 2, 4, 8, 16], np.uint8), size=128), np.zeros(128, np.uint8), np.full(128, 16, np.uint8)]
+    for good in maps:
+        assert _words(good) > 0 or not good.any()
+        for v in set(range(256)) - {0, 2, 4, 8, 16}:
+            for c in range(128):
+                bits = good.copy()
+                bits[c] = v
+                assert _words(bits) == -1, (v, c)

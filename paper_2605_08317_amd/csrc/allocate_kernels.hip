@@ -39,7 +39,7 @@ constexpr int kThr = kMaxHull - 1;
 constexpr int kBlockUnits = kPartBlock;   // units per block of the per-block tier counts
 static_assert(kBlockUnits == kThreads, "a quarter of a round of allocate_item_kernel is one block");
 
-struct AllocArgs {
+struct SearchArgs {
   const float* w;
   const float* raw;            // the weights before the pooling, which the search's first launch then does; or null
   int32_t pool;                // keys of a pooling window (odd, at most 15)
@@ -53,12 +53,22 @@ struct AllocArgs {
   double* lam_out;             // [items] or null: the multiplier of the returned allocation (NaN: no search ran)
   int32_t* iters_out;          // [items] or null: bisection steps taken
   int4* blk_counts;            // [blocks] out: units of the block in tiers 16, 8, 4, 2; or null
+};
+struct WholeItemArgs : SearchArgs {
   int32_t direct;              // allocate_item_kernel: steps taken on all units before the open ones are listed
   CountPost post;              // allocate_item_kernel, channel_allocate_kernel: where the host waits for the results, or nulls
+};
+// A kernel begins by reading some of its arguments out of cold memory, a line at a time: those that only some kernels have stand among
+// the others for these alone.  (With them for all, eight items of 128K units in the many-workgroup form: slice_max_kernel 5.71 -> 5.86 us,
+// hist_kernel 6.51 -> 6.81, gather_kernel 16.2 -> 16.5, write_kernel 4.9 -> 5.1.  Behind the batch, eight items of 4K to 16K units 14.2 ->
+// 14.5, 16.4 -> 16.7, 22.9 -> 23.4.)
+template <class Args>
+struct Batched : Args {
   const int32_t* order;        // the items of this launch, or null: all of them as they stand
   Batch batch;
   __device__ __forceinline__ int item_of(int slot) const { return order ? __builtin_amdgcn_readfirstlane(order[slot]) : slot; }
 };
+using AllocArgs = Batched<WholeItemArgs>;
 
 // largest fp32 number not above t (t >= 0): for fp32 w, (double) w > t exactly when w > below(t)
 __device__ __forceinline__ float below(double t) {
@@ -82,7 +92,7 @@ struct Problem {
   double r[kThr];
   int nh, max_iters;
   long long base, B_int, need; // base: the bit sum with every unit in the lowest tier
-  __device__ __forceinline__ Problem(const AllocArgs& a, int U, double budget) {
+  __device__ __forceinline__ Problem(const SearchArgs& a, int U, double budget) {
     nh = a.n_hull;
     max_iters = a.max_iters;
 #pragma unroll
@@ -527,7 +537,7 @@ __device__ __forceinline__ void steps_on_short_list(const Problem& P, const floa
   else steps_in_tree<16>(P, list, n, fixed, h, S, s_red);
 }
 
-__device__ __forceinline__ void report(const AllocArgs& a, int item, bool searched, const Search& S) {
+__device__ __forceinline__ void report(const SearchArgs& a, int item, bool searched, const Search& S) {
   if (a.lam_out) a.lam_out[item] = searched && S.have ? S.best : __longlong_as_double(0x7FF8000000000000ll);
   if (a.iters_out) a.iters_out[item] = searched ? S.it : 0;
 }
@@ -566,7 +576,7 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 // rounded reciprocal and one exact remainder (Markstein, IBM J. Res. Dev. 34, 1990), by division where the remainder could
 // underflow or is none.
 constexpr int kMostRadius = 7;
-__device__ __forceinline__ void pool_quotients(const AllocArgs& a, float (&s)[4]) {
+__device__ __forceinline__ void pool_quotients(const SearchArgs& a, float (&s)[4]) {
   const float n = static_cast<float>(a.pool);
   // (sums of weights: not negative, so that their patterns are ordered as they are; zeros and NaN are divided)
   const uint32_t u[4] = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
@@ -585,13 +595,13 @@ __device__ __forceinline__ void pool_quotients(const AllocArgs& a, float (&s)[4]
   for (int e = 0; e < 4; ++e) s[e] = q[e];
 }
 // four units of a window of five from the eight weights under it
-__device__ __forceinline__ void pool_five(const AllocArgs& a, const float (&t)[8], float (&v)[4]) {
+__device__ __forceinline__ void pool_five(const SearchArgs& a, const float (&t)[8], float (&v)[4]) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = (((t[e] + t[e + 1]) + t[e + 2]) + t[e + 3]) + t[e + 4];
   pool_quotients(a, v);
 }
 // ... of any window, the first of which starts at w[0]
-__device__ __forceinline__ void pool_any(const AllocArgs& a, const float* w, float (&v)[4]) {
+__device__ __forceinline__ void pool_any(const SearchArgs& a, const float* w, float (&v)[4]) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     v[e] = 0.f;
@@ -892,7 +902,7 @@ struct SearchState {
   int32_t n_list, arrive, fill;             // fill: >= 0: the tier of every unit
 };
 struct MultiArgs {
-  AllocArgs a;
+  Batched<SearchArgs> a;
   // per item of the launch (grid row), not of the batch
   int32_t* hist;        // [rows][kBuckets], zero on entry
   SearchState* state;   // [rows], zero on entry
@@ -999,7 +1009,7 @@ __device__ __forceinline__ float largest_unit(const MultiArgs& m, int row) {    
 __global__ __launch_bounds__(kThreads) void hist_kernel(MultiArgs m) {
   extern __shared__ __align__(16) unsigned char smem[];
   int* s_hist = reinterpret_cast<int*>(smem);
-  const AllocArgs& a = m.a;
+  const Batched<SearchArgs>& a = m.a;
   const int row = blockIdx.y;
   const ItemOf it(a.batch, a.item_of(row));
   const int U = it.T;
@@ -1040,7 +1050,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
   __shared__ int s_wave[kWaves], s_n, s_base, s_above[kThr], s_flag, s_red[2 * kWaves];
   __shared__ Search s_search;
   __shared__ Hull s_hull;
-  const AllocArgs& a = m.a;
+  const Batched<SearchArgs>& a = m.a;
   const int row = blockIdx.y, item = a.item_of(row);
   const ItemOf it(a.batch, item);
   const int U = it.T;
@@ -1182,7 +1192,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(MultiArgs m) {
 // the bit map and the tier counts, one block of units per workgroup of 256
 __global__ __launch_bounds__(256) void write_kernel(MultiArgs m) {
   __shared__ int4 s_cnt[4];
-  const AllocArgs& a = m.a;
+  const Batched<SearchArgs>& a = m.a;
   const int row = blockIdx.y, item = a.item_of(row);
   const ItemOf it(a.batch, item);
   const int U = it.T;
@@ -1327,7 +1337,8 @@ hipError_t launch_short_items(AllocArgs a, int n_items, int max_U, hipStream_t s
 
 hipError_t launch_items_together(const AllocArgs& a, int n_items, int max_U, void* scratch, hipStream_t st) {
   MultiArgs m;
-  m.a = a;
+  static_cast<SearchArgs&>(m.a) = a;
+  m.a.order = a.order; m.a.batch = a.batch;
   uint8_t* p = static_cast<uint8_t*>(scratch);
   m.hist = reinterpret_cast<int32_t*>(p);
   m.state = reinterpret_cast<SearchState*>(p + hist_bytes(n_items));

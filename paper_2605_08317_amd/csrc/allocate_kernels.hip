@@ -578,16 +578,17 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 constexpr int kMostRadius = 7;
 __device__ __forceinline__ void pool_quotients(const SearchArgs& a, float (&s)[4]) {
   const float n = static_cast<float>(a.pool);
-  // (sums of weights: not negative, so that their patterns are ordered as they are; zeros and NaN are divided)
+  // (sums of weights: not negative, so that their patterns are ordered as they are; less one, a zero, which is its own
+  // quotient, comes to the other end: with 97 in 100 weights zero eight items of 32K units 18.8 -> 17.7 us)
   const uint32_t u[4] = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
-  const uint32_t least = min(min(min(u[0], u[1]), u[2]), u[3]), most = max(max(max(u[0], u[1]), u[2]), u[3]);
+  const uint32_t least = min(min(min(u[0] - 1u, u[1] - 1u), u[2] - 1u), u[3] - 1u), most = max(max(max(u[0], u[1]), u[2]), u[3]);
   float q[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float q0 = s[e] * a.pool_inv;
     q[e] = __builtin_fmaf(__builtin_fmaf(-q0, n, s[e]), a.pool_inv, q0);
   }
-  if (__builtin_expect(__any(least < __float_as_uint(1e-25f) || most > __float_as_uint(1e30f)), 0)) {
+  if (__builtin_expect(__any(least < __float_as_uint(1e-25f) - 1u || most > __float_as_uint(1e30f)), 0)) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) q[e] = s[e] / n;
   }

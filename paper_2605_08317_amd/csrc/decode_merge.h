@@ -132,9 +132,6 @@ __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int sl
   constexpr int SG = NT / kCols;
   static_assert(SG >= 1, "a workgroup covers a slot's partial");
   const int tid = threadIdx.x;
-  const auto put = [](float* p, float v) __attribute__((always_inline)) {
-    if constexpr (THROUGH) store_agent(p, v); else *p = v;
-  };
   const int col = tid & (kCols - 1), sg = tid / kCols, hd = col >> 5;
   float* s_m = smem + 16;                   // [SG][G]
   float* s_l = s_m + SG * G;                // [SG][G]
@@ -177,7 +174,10 @@ __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int sl
   if constexpr (SG == 1) {
     float* o = ma.out + qh0 * kHeadDim + 4 * col;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) put(o + k, l_run > 0.f ? o_run[k] / l_run : 0.f);
+    for (int k = 0; k < 4; ++k) {
+      const float v = l_run > 0.f ? o_run[k] / l_run : 0.f;
+      if constexpr (THROUGH) store_agent(o + k, v); else o[k] = v;
+    }
     if ((col & 31) == 0 && ma.lse != nullptr)
       ma.lse[qh0 + hd] = l_run > 0.f ? (m_run + __log2f(l_run)) * 0.6931471805599453f : -INFINITY;
     return;
@@ -197,7 +197,8 @@ __device__ __forceinline__ void merge_item(const MergeArgs& ma, int item, int sl
       l = __builtin_fmaf(s_l[k * G + h], f, l);
       t = __builtin_fmaf(s_red[k * G * kHeadDim + idx], f, t);
     }
-    put(ma.out + qh0 * kHeadDim + idx, l > 0.f ? t / l : 0.f);
+    const float v = l > 0.f ? t / l : 0.f;
+    if constexpr (THROUGH) store_agent(ma.out + qh0 * kHeadDim + idx, v); else ma.out[qh0 * kHeadDim + idx] = v;
     if ((idx & 127) == 0 && ma.lse != nullptr)
       ma.lse[qh0 + h] = l > 0.f ? (mm + __log2f(l)) * 0.6931471805599453f : -INFINITY;
   }

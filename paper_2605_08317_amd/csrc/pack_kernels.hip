@@ -66,11 +66,12 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
   }
 }
 
-// One launch between the bit map and the host's wait for its counts; nothing in it needs the host:
+// One launch between the bit map and the packing; nothing in it needs the host:
 //   - the ascending position lists of every tier, item by item in scratch: item's first token + kept tokens of the higher
 //     tiers + rank (one workgroup = one block of 1024 tokens, a thread = four consecutive ones; the ranks of all four tiers
 //     come from one prefix sum over 16-bit fields)
-//   - the counts' way to the host, and what else is copied or filled then (copy_part)
+//   - the counts' way to the host, who waits for them and so for this launch, unless the search has posted them (CountPost: compressing
+//     items of up to 32K tokens), and what else is copied or filled then (copy_part)
 //   - the arena's plan (plan_part), by one workgroup
 //   - channel-wise K: the row layout of every item (layout_part), by the item's first workgroup
 // What bounds it is latency: two round trips to memory and the launch (4.4 us for two items of 4K tokens, 11.6 for 128 of 20K).
@@ -1048,7 +1049,8 @@ hipError_t launch_tier_count(const uint8_t* bits, const Batch& batch, int32_t* b
   return hipGetLastError();
 }
 
-// The position lists, the plan and what `copy` holds (planned; at least the counts on their way to the host), in one launch.
+// The position lists, the plan and what `copy` holds (planned; the counts on their way to the host where nobody has posted them, fills,
+// or nothing), in one launch.
 hipError_t launch_tier_scatter(const uint8_t* bits, const Batch& batch, const int32_t* blk_counts, int32_t* tier_idx,
                                const PlanArgs& plan, int max_T, const CopyArgs& copy, hipStream_t st) {
   const int max_blk = (max_T + kPartBlock - 1) / kPartBlock, others = copy.first[copy.n] + 1;

@@ -1053,8 +1053,9 @@ rdkv_status pack_impl(const rdkv_config* cfg, const Items& it, const Tables& tb,
   std::vector<int32_t> k_bits(mixed ? n : 0), k_quantized(mixed ? n : 0);      // of an item's channels: bits, how many below 16
   if (n > 0) {
     // the one wait of the pass: the tier counts size the arena and the split schedule.  A kernel writes them into pinned
-    // memory and the host watches for them (a copy to host memory and a wait for the stream: 25 us more).  It is the launch
-    // that makes the position lists and the packing kernels' tables, which need nothing from here.
+    // memory and the host watches for them (a copy to host memory and a wait for the stream: 25 us more).  It is the search's own
+    // where that has posted them, and else the launch that makes the position lists and the packing kernels' tables, which need
+    // nothing from here.
     if (!counted) {
       TimedScope ts(RDKV_TIME_PACK, st);      // first half of the stage: the tier counts
       PACK_HIP(launch_tier_count(bits_tok, tb.batch, d_blk_counts, it.max_T, st));

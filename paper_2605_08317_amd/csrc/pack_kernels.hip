@@ -133,23 +133,29 @@ __device__ __forceinline__ void plan_part(const ScatterArgs& a) {
     uint32_t words = 0, steps = 0;         // channel-wise: 32-bit words of a K row, its quantized steps
     if (p.bits_ch) {
       // Channels of every tier, eight bits each (at most 128).  Widths are one bit each; of a map that holds others, which the host
-      // refuses, the sums mean nothing.  All loads before the first sum: one after the other, a word at a time, they made the
-      // launch 12.5 us for 88 items and 8.0 for 32; now 5.6, what it takes for four.
+      // refuses, the sums mean nothing.  Four pieces' loads before the first sum: one after the other, a word at a time, they made the
+      // launch 12.0 us for 88 items and 7.0 for 32; now 4.7 and 5.2, what it takes for a few.  (All eight pieces of a map, which one lane
+      // has where there are more than 128 items, took 163 registers, a wavefront per SIMD from every workgroup of the launch: 128
+      // token-wise items of 20K tokens 9.6 -> 12.5 us, eight of 128K 6.0 -> 7.4.)
       uint32_t ch = 0;
-      constexpr int kPieces = kHeadDim / 16;
-      Bytes16 v[kPieces];
+      constexpr int kPieces = kHeadDim / 16, kAtOnce = 4;
       const Bytes16* map = reinterpret_cast<const Bytes16*>(p.bits_ch + static_cast<int64_t>(in ? item : 0) * kHeadDim);
+#pragma unroll 1
+      for (int k0 = 0; k0 * lanes < kPieces; k0 += kAtOnce) {
+        Bytes16 v[kAtOnce];
 #pragma unroll
-      for (int k = 0; k < kPieces; ++k) {
-        v[k] = Bytes16{{0, 0, 0, 0}};
-        if (in && sub + k * lanes < kPieces) v[k] = map[sub + k * lanes];
+        for (int k = 0; k < kAtOnce; ++k) {
+          const int piece = sub + (k0 + k) * lanes;
+          v[k] = Bytes16{{0, 0, 0, 0}};
+          if (in && piece < kPieces) v[k] = map[piece];
+        }
+#pragma unroll
+        for (int k = 0; k < kAtOnce; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ch += static_cast<uint32_t>(__popc(v[k].v[e] & (0x10101010u >> t))) << (8 * t);
       }
-#pragma unroll
-      for (int k = 0; k < kPieces; ++k)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) ch += static_cast<uint32_t>(__popc(v[k].v[e] & (0x10101010u >> t))) << (8 * t);
       ch = group_sum(ch, lanes);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {

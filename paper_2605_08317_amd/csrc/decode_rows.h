@@ -60,12 +60,12 @@ __device__ __forceinline__ void pv_steps(const uint8_t* s_stage, int lane, const
 }
 
 // TIERED: the chunk's partial goes to the split workspace for the launch's merging workgroups (LOOK) or is announced
-// (store_partial); otherwise it is only stored, for a launch that follows or (through: to memory) merge_tagged.
-template <int HS, bool TIERED, int NWV, bool LOOK = false>
+// (store_partial); otherwise it is only stored, for a launch that follows or (THROUGH: to memory) merge_tagged.
+template <int HS, bool TIERED, int NWV, bool LOOK = false, bool THROUGH = false>
 __device__ __forceinline__ uint32_t process_rows_mfma(const uint8_t* __restrict__ kd, const uint8_t* __restrict__ vd,
                                                   int rows, int g, const uint16_t* __restrict__ q, uint8_t* smem,
                                                   float* __restrict__ part_acc, float* __restrict__ part_ml,
-                                                  const MergeArgs* ma, const ChunkOut* co, bool through = false) {
+                                                  const MergeArgs* ma, const ChunkOut* co) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blk = lane >> 2, j = lane & 3;
@@ -173,13 +173,15 @@ __device__ __forceinline__ uint32_t process_rows_mfma(const uint8_t* __restrict_
         v = __builtin_fmaf(s_acc[w * g * kHeadDim + idx], f, v);
         ll = __builtin_fmaf(s_ml[ml_at<HS>(w, head, 0) + 1], f, ll);
       }
-      const auto put = [&](float* p, float x) __attribute__((always_inline)) {
-        if (through) merge::store_agent(p, x); else *p = x;
-      };
-      put(part_acc + idx, v);
+      if constexpr (THROUGH) merge::store_agent(part_acc + idx, v); else part_acc[idx] = v;
       if ((idx & 127) == 0) {
-        put(part_ml + head * 2, mm);
-        put(part_ml + head * 2 + 1, ll);
+        if constexpr (THROUGH) {
+          merge::store_agent(part_ml + head * 2, mm);
+          merge::store_agent(part_ml + head * 2 + 1, ll);
+        } else {
+          part_ml[head * 2] = mm;
+          part_ml[head * 2 + 1] = ll;
+        }
       }
     }
   }

@@ -45,7 +45,9 @@ __device__ __forceinline__ void merge_tagged(const DenseArgs& a, int item, int s
   }
   const MergeArgs ma{a.part_acc, a.part_ml, nullptr, a.out, a.lse, g, 0, 0};
   float* s = reinterpret_cast<float*>(smem);
-  // (one round trip for all that dense_together lets come here)
+  // (one round trip for all that dense_together lets come here, and not many more loads than there are partials: with sixteen a thread
+  // for two heads of up to 32, the launch took from a graph what two do or 0.2 us more; 2 x 2K rows 8.53, 8.48 -> 7.85 us, 16 x 4K with
+  // 62 MB 17.2, 17.8 -> 16.75)
   if constexpr (HS == 2) {
     if (n <= 8) merge::merge_item<kRowsWG, 8, 8, true>(ma, item, slot0, n, s);
     else merge::merge_item<kRowsWG, 8, 16, true>(ma, item, slot0, n, s);
@@ -53,13 +55,16 @@ __device__ __forceinline__ void merge_tagged(const DenseArgs& a, int item, int s
     if (n <= 16) merge::merge_item<kRowsWG, 4, 8, true>(ma, item, slot0, n, s);
     else merge::merge_item<kRowsWG, 4, 16, true>(ma, item, slot0, n, s);
   } else if (g == 2) {
-    merge::merge_item<kRowsWG, 2, 16, true>(ma, item, slot0, n, s);
+    if (n <= 32) merge::merge_item<kRowsWG, 2, 8, true>(ma, item, slot0, n, s);
+    else merge::merge_item<kRowsWG, 2, 16, true>(ma, item, slot0, n, s);
   } else {
     merge::merge_item<kRowsWG, 1, 8, true>(ma, item, slot0, n, s);
   }
 }
 
-template <int HS>
+// TOGETHER: it merges its own partials (an instantiation of its own, so that the launch that leaves them to another is not slower for the
+// merge's code and registers: one sequence of 20K rows, four heads, 13.56 -> 14.04 us a call).
+template <int HS, bool TOGETHER>
 __global__ __launch_bounds__(kRowsWG, 2) void decode_dense_mfma_kernel(DenseArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int split = blockIdx.x, head = blockIdx.y, sl = blockIdx.z;
@@ -67,7 +72,7 @@ __global__ __launch_bounds__(kRowsWG, 2) void decode_dense_mfma_kernel(DenseArgs
   const int row0 = split * a.chunk_rows;
   const int g = a.hq / a.hkv;
   if (row0 >= T) {
-    if (split == 0 && a.tag[0] != 0) {  // no rows at all, and no merge launch
+    if (TOGETHER && split == 0) {       // no rows at all, and no merge launch
       const int64_t qh0 = static_cast<int64_t>(a.seq_base + sl) * a.hq + head * g;
       for (int i = threadIdx.x; i < g * kHeadDim; i += kRowsWG) a.out[qh0 * kHeadDim + i] = 0.f;
       if (a.lse != nullptr && static_cast<int>(threadIdx.x) < g) a.lse[qh0 + threadIdx.x] = -INFINITY;
@@ -81,9 +86,9 @@ __global__ __launch_bounds__(kRowsWG, 2) void decode_dense_mfma_kernel(DenseArgs
   const int seq = a.seq_base + sl;
   const uint16_t* q = a.q + (static_cast<int64_t>(seq) * a.hq + head * g) * kHeadDim;
   const int64_t slot = (static_cast<int64_t>(sl) * a.hkv + head) * a.max_splits + split;
-  process_rows_mfma<HS, false, kRowsWaves>(kd, vd, rows, g, q, smem, a.part_acc + slot * g * kHeadDim, a.part_ml + slot * g * 2,
-                               nullptr, nullptr, a.tag[0] != 0);
-  if (a.tag[0] != 0)
+  process_rows_mfma<HS, false, kRowsWaves, false, TOGETHER>(kd, vd, rows, g, q, smem, a.part_acc + slot * g * kHeadDim,
+                                                            a.part_ml + slot * g * 2, nullptr, nullptr);
+  if constexpr (TOGETHER)
     merge_tagged<HS>(a, seq * a.hkv + head, static_cast<int>(slot) - split, split, (T + a.chunk_rows - 1) / a.chunk_rows, g, smem);
 }
 
@@ -102,20 +107,18 @@ __global__ __launch_bounds__(kRowsWG, 2) void decode_tiered_mfma_kernel(const Ch
 
 }  // namespace
 
-hipError_t launch_decode_dense_split(const DenseArgs& a, int g, int n_seqs, hipStream_t st) {
-  dim3 grid(a.max_splits, a.hkv, n_seqs), block(kRowsWG);
-  if (g > 4) {
-    const size_t lds = rows_lds_bytes<2, kRowsWaves>();
-    hipError_t e = RDKV_ALLOW_LDS((decode_dense_mfma_kernel<2>), lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_dense_mfma_kernel<2>, grid, block, lds, st, a);
-  } else {
-    const size_t lds = rows_lds_bytes<1, kRowsWaves>();
-    hipError_t e = RDKV_ALLOW_LDS((decode_dense_mfma_kernel<1>), lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_dense_mfma_kernel<1>, grid, block, lds, st, a);
-  }
+template <int HS, bool TOGETHER>
+static hipError_t launch_dense(const DenseArgs& a, int n_seqs, hipStream_t st) {
+  const size_t lds = rows_lds_bytes<HS, kRowsWaves>();
+  const hipError_t e = RDKV_ALLOW_LDS((decode_dense_mfma_kernel<HS, TOGETHER>), lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((decode_dense_mfma_kernel<HS, TOGETHER>), dim3(a.max_splits, a.hkv, n_seqs), dim3(kRowsWG), lds, st, a);
   return hipGetLastError();
+}
+hipError_t launch_decode_dense_split(const DenseArgs& a, int g, int n_seqs, hipStream_t st) {
+  const bool together = a.tag[0] != 0;
+  if (g > 4) return together ? launch_dense<2, true>(a, n_seqs, st) : launch_dense<2, false>(a, n_seqs, st);
+  return together ? launch_dense<1, true>(a, n_seqs, st) : launch_dense<1, false>(a, n_seqs, st);
 }
 
 hipError_t launch_decode_tiered_split(const Chunk* chunks, int n_chunks, const uint8_t* arena, const uint16_t* q,

@@ -809,7 +809,8 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
     return;
   }
   __syncthreads();                         // the list is not read any more
-  // (Tiers are one bit each: a byte per unit counts them, eight bits per tier up to 32 lanes.)
+  // (Tiers are one bit each: a byte per unit counts them, eight bits per tier up to 32 lanes.  Only where somebody wants the counts: a
+  // search by itself, eight items of 4K units 9.65 -> 9.3 us, of 20K 20.1 -> 19.7, of 32K 21.8 -> 21.1.)
 #pragma unroll
   for (int j = 0; j < kQ; ++j) {
     const int u0 = 4 * (j * kThreads + tid);
@@ -831,11 +832,13 @@ __global__ __launch_bounds__(kThreads) void allocate_item_kernel(AllocArgs a) {
           else packed &= ~(0xFFu << (8 * e));
         }
       }
-      uint32_t n = 0;                      // in tiers 16, 8, 4, 2
+      if (a.blk_counts) {
+        uint32_t n = 0;                    // in tiers 16, 8, 4, 2
 #pragma unroll
-      for (int k = 0; k < 4; ++k) n |= static_cast<uint32_t>(__popc(packed & (0x10101010u >> k))) << (8 * k);
-      n = row_pair_sum(n);
-      if ((lane & 31) == 31) s_cnt[(j * kWaves + wave) * 2 + (lane >> 5)] = n;
+        for (int k = 0; k < 4; ++k) n |= static_cast<uint32_t>(__popc(packed & (0x10101010u >> k))) << (8 * k);
+        n = row_pair_sum(n);
+        if ((lane & 31) == 31) s_cnt[(j * kWaves + wave) * 2 + (lane >> 5)] = n;
+      }
     }
   }
   if (a.blk_counts) {

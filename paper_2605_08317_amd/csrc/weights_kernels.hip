@@ -708,7 +708,7 @@ hipError_t launch_weights(const rdkv_config& cfg, const Batch& batch, int64_t n_
   // 5.4 + 185.6 -> 188.8.  Eight items have 65 runs each, and every workgroup would read them: 32K tokens 4.7 + 18.5 -> 22.7, 128K
   // tokens and 256 rows 5.3 + 78 -> 88.  The channel weights go along with whichever launch makes it: with
   // pass 2 passes over 5 x 1K tokens of 4 heads 126.7 -> 122.2 us, 11 x 0.8K of 8 128.5 -> 126.4, 5 x 8K of 4 111.2 -> 110.2.
-  if (runs.few) a.lse = nullptr;
+  if (lse_in_second_pass(runs, n_items, a.R, w_ch != nullptr)) a.lse = nullptr;
   a.sum_workgroups = workgroups_of(n_tiles, kPass2PerCu);
   a.w_ch = a.lse ? nullptr : w_ch;
   a.ksq_part = w_ch ? a.w_raw + total_tokens : nullptr;

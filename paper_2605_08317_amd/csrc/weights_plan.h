@@ -33,4 +33,12 @@ inline RunPlan run_plan(int64_t n_tiles, int64_t most_tiles, int rows, int per_c
   return RunPlan{all, false};
 }
 
+// Whether the second pass makes the log-sum-exp.  With channel weights, which go along with whichever launch makes it, their
+// workgroups (four an item) have the second pass's LDS and registers, two to a compute unit, and come behind it: with up to 128 window
+// rows and many items they take longer than the launch (microseconds, launch and second pass: 256 x 200 tokens of 2 heads 50.0, 54.1;
+// 128 x 300 of 8 91.2, 95.3; 256 x 200 145.1, 152.5; but 64 x 300 60.8, 61.1, 32 x 300 43.3, 41.2, and with 256 rows 124.9, 118.8).
+inline bool lse_in_second_pass(const RunPlan& plan, int64_t n_items, int rows, bool channels) {
+  return plan.few && !(channels && rows <= 128 && n_items > 256);
+}
+
 }  // namespace rdkv

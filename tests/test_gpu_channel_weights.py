@@ -23,3 +23,21 @@ def test_channel_weights_of_few_runs_and_many(lens, hq, s_obs):
     w_ch = b.rdkv_weights(b.Config(lens, hq, hkv, s_obs=s_obs), K.cuda(), Q.cuda(), want_channel=True)[1].cpu().numpy().reshape(-1, d)
     for s, Ks in enumerate(_split(K, lens, hkv, d)):
         np.testing.assert_allclose(w_ch[s * hkv:(s + 1) * hkv], O.channel_weights(Ks, _np(Q[s])), rtol=1e-5)
+
+
+# Items of few runs whose channel weights the launch of the log-sum-exp makes all the same (more than 256 of up to 128 rows): 256 and 258
+# items, and the same token weights as without.
+@pytest.mark.parametrize("hq,s_obs", [(2, 32), (4, 64), (8, 33)])
+@pytest.mark.parametrize("seqs", [128, 129])
+def test_channel_weights_of_many_items(seqs, hq, s_obs):
+    hkv, d, lens = 2, 128, [64 + k % 3 for k in range(seqs)]
+    print(f"[case] {seqs} sequences hq {hq} s_obs {s_obs}", flush=True)
+    b, gen = B(), torch.Generator().manual_seed(seqs + hq)
+    K = torch.randn(sum(lens) * hkv * d, generator=gen).to(torch.bfloat16)
+    Q = torch.randn((seqs, hq, s_obs, d), generator=gen).to(torch.bfloat16)
+    cfg = b.Config(lens, hq, hkv, s_obs=s_obs, budget_bits=[2.0] * seqs)
+    w, w_ch = b.rdkv_weights(cfg, K.cuda(), Q.cuda(), want_channel=True)
+    assert torch.equal(w, b.rdkv_weights(cfg, K.cuda(), Q.cuda())[0])
+    w_ch = w_ch.cpu().numpy().reshape(-1, d)
+    for s, Ks in enumerate(_split(K, lens, hkv, d)):
+        np.testing.assert_allclose(w_ch[s * hkv:(s + 1) * hkv], O.channel_weights(Ks, _np(Q[s])), rtol=1e-5)

@@ -618,8 +618,8 @@ void dense_plan(const int32_t* seq_lens, int batch, int hkv, int g, int* chunk_r
 //   8 items of 4K, 16 x 4          12.2   8.6      2 items of 6K, 24 x 4      12.4  10.8
 // Beyond either, one compute unit's reading takes longer than the launch:
 //   8 items of 8K, 32 x 4          11.8  13.8      32 items of 4K to 8K, 16 x 4  23.0  23.4   8 items of 32K, 64 x 4         29.3  32.7
-// or does so where a graph replays the call and the host is out of it (2 items of 2K, 8 x 4: 8.9, 8.1; 2 of 6K, 24 x 4: 9.1, 9.2; 8 of
-// 4K, 16 x 8: 10.8, 11.3; 2 of 12K, 47 x 2: 9.3, 9.5).
+// or does so where a graph replays the call and the host is out of it (2 items of 2K, 8 x 4: 8.8, 8.2; 2 of 6K, 24 x 4: 9.2, 9.2; 8 of
+// 4K, 16 x 8: 10.6, 11.1; 2 of 12K, 47 x 2: 9.4, 9.5, 47 x 4: 9.8, 11.0).
 constexpr int kDenseTagged = 64;       // chunks of an item that have room for their tags in its output rows, a lane each
 static_assert(2 * kDenseTagged <= kHeadDim, "one query head's row");
 bool dense_together(const int32_t* seq_lens, int batch, int hkv, int g, int max_splits) {

@@ -35,10 +35,11 @@ inline RunPlan run_plan(int64_t n_tiles, int64_t most_tiles, int rows, int per_c
 
 // Whether the second pass makes the log-sum-exp.  With channel weights, which go along with whichever launch makes it, their
 // workgroups (four an item) have the second pass's LDS and registers, two to a compute unit, and come behind it: with up to 128 window
-// rows and many items they take longer than the launch (microseconds, launch and second pass: 256 x 200 tokens of 2 heads 50.0, 54.1;
-// 128 x 300 of 8 91.2, 95.3; 256 x 200 145.1, 152.5; but 64 x 300 60.8, 61.1, 32 x 300 43.3, 41.2, and with 256 rows 124.9, 118.8).
+// rows and many items they take longer than the launch (microseconds, launch and second pass; 128 rows: 128 x 300 tokens of 8 heads
+// 91.2, 95.3, 64 x 300 60.8, 61.1, 32 x 300 43.3, 41.2; 32 rows: 256 x 200 of 2 heads 50.0, 54.1, 64 x 500 of 4 30.9, 32.0, 128 x 300 of 2 40.2,
+// 41.0, 64 x 300 of 2 35.6, 34.5; 256 rows: 128 x 300 of 8 124.9, 118.8).
 inline bool lse_in_second_pass(const RunPlan& plan, int64_t n_items, int rows, bool channels) {
-  return plan.few && !(channels && rows <= 128 && n_items > 256);
+  return plan.few && !(channels && rows <= 128 && n_items > (rows <= 64 ? 128 : 256));
 }
 
 }  // namespace rdkv

@@ -25,10 +25,10 @@ def test_channel_weights_of_few_runs_and_many(lens, hq, s_obs):
         np.testing.assert_allclose(w_ch[s * hkv:(s + 1) * hkv], O.channel_weights(Ks, _np(Q[s])), rtol=1e-5)
 
 
-# Items of few runs whose channel weights the launch of the log-sum-exp makes all the same (more than 256 of up to 128 rows): 256 and 258
-# items, and the same token weights as without.
+# Items of few runs whose channel weights the launch of the log-sum-exp makes all the same (more than 128 of up to 64 rows, than 256 of up to
+# 128): 128, 130, 256 and 258 items, and the same token weights as without.
 @pytest.mark.parametrize("hq,s_obs", [(2, 32), (4, 64), (8, 33)])
-@pytest.mark.parametrize("seqs", [128, 129])
+@pytest.mark.parametrize("seqs", [64, 65, 128, 129])
 def test_channel_weights_of_many_items(seqs, hq, s_obs):
     hkv, d, lens = 2, 128, [64 + k % 3 for k in range(seqs)]
     print(f"[case] {seqs} sequences hq {hq} s_obs {s_obs}", flush=True)

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void tier_count_kernel(const uint8_t* __restri
 //     items of up to 32K tokens), and what else is copied or filled then (copy_part)
 //   - the arena's plan (plan_part), by one workgroup
 //   - channel-wise K: the row layout of every item (layout_part), by the item's first workgroup
-// What bounds it is latency: two round trips to memory and the launch (4.4 us for two items of 4K tokens, 11.6 for 128 of 20K).
+// What bounds it is latency: two round trips to memory and the launch (4.4 us for two items of 4K tokens, 9.3 for 128 of 20K).
 // With the counts copied by a launch in front of the wait, and the tables and then the lists in two launches behind it,
 // compressing two heads of 4K keys took 58.0 us, eight of 128K 242; now 53.2 and 234.
 struct ScatterArgs {
